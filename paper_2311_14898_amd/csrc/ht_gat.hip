@@ -83,19 +83,20 @@ __global__ void __launch_bounds__(256) k_gat_pq(const float* __restrict__ T, int
 //   1. per item: the scores x_e (kept in w[]), their maximum m_i and s_i = sum mult_e exp(x_e - m_i);
 //   2. per row cut into several items: m_v = max m_i, Z_v = sum s_i exp(m_i - m_v), in a fixed order;
 //   3. per item: w_e = mult_e exp(x_e - m_v) / Z_v.
-__global__ void __launch_bounds__(256) k_gat_scores(const int32_t* __restrict__ it_row, const int64_t* __restrict__ it_e0,
-                                                    const int32_t* __restrict__ it_len, const int32_t* __restrict__ it_part,
-                                                    int64_t n_items, const int32_t* __restrict__ col,
-                                                    const float* __restrict__ mult, const float* __restrict__ p_chunk,
-                                                    const float* __restrict__ q, float slope, float* __restrict__ w,
-                                                    float* __restrict__ m_chunk, float* __restrict__ zinv_chunk,
+// Rows are vertices; w holds the entries from ent0 on, part_* the partial results from part0 on.
+__global__ void __launch_bounds__(256) k_gat_scores(const WorkItem* __restrict__ items, int64_t n_items, int64_t ent0, int64_t part0,
+                                                    const int32_t* __restrict__ col, const float* __restrict__ mult,
+                                                    const float* __restrict__ p, const float* __restrict__ q, float slope,
+                                                    float* __restrict__ w, float* __restrict__ m_row, float* __restrict__ zinv,
                                                     float* __restrict__ part_m, float* __restrict__ part_s) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t t = (int64_t)blockIdx.x * 4 + wave;
   if (t >= n_items) return;
-  const int32_t r = it_row[t], len = it_len[t], part = it_part[t];
-  const int64_t e0 = it_e0[t];
-  const float pv = p_chunk[r];
+  const WorkItem it = items[t];
+  const int32_t r = it.row, len = it.len, part = it.part;
+  const int64_t e0 = it.e0;
+  w -= ent0;
+  const float pv = p[r];
   float m = -3.0e38f;
   for (int32_t k = lane; k < len; k += 64) {
     const float x = lrelu(pv + q[col[e0 + k]], slope);
@@ -108,24 +109,25 @@ __global__ void __launch_bounds__(256) k_gat_scores(const int32_t* __restrict__ 
   s = wave_sum(s);
   if (lane == 0) {
     if (part >= 0) {
-      part_m[part] = m;
-      part_s[part] = s;
+      part_m[part - part0] = m;
+      part_s[part - part0] = s;
     } else {
-      m_chunk[r] = m;
-      zinv_chunk[r] = s > 0.f ? 1.f / s : 0.f;
+      m_row[r] = m;
+      zinv[r] = s > 0.f ? 1.f / s : 0.f;
     }
   }
 }
 
-__global__ void __launch_bounds__(256) k_gat_rowstats(const int32_t* __restrict__ fx_row, const int32_t* __restrict__ fx_part0,
-                                                      const int32_t* __restrict__ fx_nseg, int64_t n_fix,
+__global__ void __launch_bounds__(256) k_gat_rowstats(const CutRow* __restrict__ cuts, int64_t n_cut, int64_t part0,
                                                       const float* __restrict__ part_m, const float* __restrict__ part_s,
-                                                      float* __restrict__ m_chunk, float* __restrict__ zinv_chunk) {
+                                                      float* __restrict__ m_row, float* __restrict__ zinv) {
   // a wave per cut row; lanes take the row's items 64 apart, lane sums are added in lane order
   const int lane = threadIdx.x & 63;
   const int64_t f = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (f >= n_fix) return;
-  const int32_t p0 = fx_part0[f], ns = fx_nseg[f];
+  if (f >= n_cut) return;
+  const CutRow cut = cuts[f];
+  const int64_t p0 = cut.part0 - part0;
+  const int32_t ns = cut.nseg;
   float m = -3.0e38f;
   for (int32_t k = lane; k < ns; k += 64) m = fmaxf(m, part_m[p0 + k]);
   m = wave_max(m);
@@ -133,25 +135,26 @@ __global__ void __launch_bounds__(256) k_gat_rowstats(const int32_t* __restrict_
   for (int32_t k = lane; k < ns; k += 64) s += part_s[p0 + k] * expf(part_m[p0 + k] - m);
   s = wave_sum(s);
   if (lane == 0) {
-    m_chunk[fx_row[f]] = m;
-    zinv_chunk[fx_row[f]] = s > 0.f ? 1.f / s : 0.f;
+    m_row[cut.row] = m;
+    zinv[cut.row] = s > 0.f ? 1.f / s : 0.f;
   }
 }
 
-// wf / r_chunk / part_r (backward pass only, nullable): wf_e = w_e f_e with f_e = LeakyReLU'(y_e), the
+// wf / r_row / part_r (backward pass only, nullable): wf_e = w_e f_e with f_e = LeakyReLU'(y_e), the
 // weights of the destination pass, and their sum per item (per row when the row is one item).
-__global__ void __launch_bounds__(256) k_gat_coefs(const int32_t* __restrict__ it_row, const int64_t* __restrict__ it_e0,
-                                                   const int32_t* __restrict__ it_len, const int32_t* __restrict__ it_part,
-                                                   int64_t n_items, const float* __restrict__ mult,
-                                                   const float* __restrict__ m_chunk, const float* __restrict__ zinv_chunk,
-                                                   float slope, float* __restrict__ w, float* __restrict__ wf,
-                                                   float* __restrict__ r_chunk, float* __restrict__ part_r) {
+__global__ void __launch_bounds__(256) k_gat_coefs(const WorkItem* __restrict__ items, int64_t n_items, int64_t ent0, int64_t part0,
+                                                   const float* __restrict__ mult, const float* __restrict__ m_row,
+                                                   const float* __restrict__ zinv_row, float slope, float* __restrict__ w,
+                                                   float* __restrict__ wf, float* __restrict__ r_row, float* __restrict__ part_r) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t t = (int64_t)blockIdx.x * 4 + wave;
   if (t >= n_items) return;
-  const int32_t r = it_row[t], len = it_len[t];
-  const int64_t e0 = it_e0[t];
-  const float m = m_chunk[r], zinv = zinv_chunk[r];
+  const WorkItem it = items[t];
+  const int32_t r = it.row, len = it.len;
+  const int64_t e0 = it.e0;
+  w -= ent0;
+  if (wf) wf -= ent0;
+  const float m = m_row[r], zinv = zinv_row[r];
   float rs = 0.f;
   for (int32_t k = lane; k < len; k += 64) {
     const float x = w[e0 + k];       // the score LeakyReLU(y_e): same sign as y_e
@@ -166,9 +169,8 @@ __global__ void __launch_bounds__(256) k_gat_coefs(const int32_t* __restrict__ i
   if (wf) {
     rs = wave_sum(rs);
     if (lane == 0) {
-      const int32_t part = it_part[t];
-      if (part >= 0) part_r[part] = rs;
-      else r_chunk[r] = rs;
+      if (it.part >= 0) part_r[it.part - part0] = rs;
+      else r_row[r] = rs;
     }
   }
 }
@@ -217,7 +219,7 @@ __global__ void __launch_bounds__(256) k_gat_dz(const float* __restrict__ dh, in
 
 struct GatPass {
   // items of the source pass (rows = local sources of the chunk)
-  const int32_t* it_row; const int64_t* it_e0; const int32_t* it_len; const int32_t* it_part; int64_t n_items;
+  const WorkItem* items; int64_t n_items; int64_t part0;
   const int32_t* idx;        // per entry: local destination = row of `mat` to read
   const float* mult;         // multiplicity per entry (nullable: 1)
   const float* mat;          // rows gathered per entry: dz of the chunk
@@ -239,17 +241,18 @@ struct GatPass {
 };
 
 // per-row sums of rows cut into several items: a wave per row adds the item sums (lanes 64 apart, then lane order)
-__global__ void __launch_bounds__(256) k_gat_fix_scalar(const int32_t* __restrict__ fx_row, const int32_t* __restrict__ fx_part0,
-                                                        const int32_t* __restrict__ fx_nseg, int64_t n_fix,
+__global__ void __launch_bounds__(256) k_gat_fix_scalar(const CutRow* __restrict__ cuts, int64_t n_cut, int64_t part0,
                                                         const float* __restrict__ spart, float* __restrict__ row_sum) {
   const int lane = threadIdx.x & 63;
   const int64_t f = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (f >= n_fix) return;
-  const int32_t p0 = fx_part0[f], ns = fx_nseg[f];
+  if (f >= n_cut) return;
+  const CutRow cut = cuts[f];
+  const int64_t p0 = cut.part0 - part0;
+  const int32_t ns = cut.nseg;
   float s = 0.f;
   for (int32_t k = lane; k < ns; k += 64) s += spart[p0 + k];
   s = wave_sum(s);
-  if (lane == 0) row_sum[fx_row[f]] = s;
+  if (lane == 0) row_sum[cut.row] = s;
 }
 
 // Source pass: for local source i (vertex u) over its entries (u -> v) of the chunk, w_e recomputed:
@@ -261,9 +264,10 @@ __global__ void __launch_bounds__(256) k_gat_src(GatPass a) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t t = (int64_t)blockIdx.x * 4 + wave;
   if (t >= a.n_items) return;
-  const int32_t r = a.it_row[t];
-  const int64_t e0 = a.it_e0[t];
-  const int32_t len = a.it_len[t], part = a.it_part[t];
+  const WorkItem it = a.items[t];
+  const int32_t r = it.row;
+  const int64_t e0 = it.e0;
+  const int32_t len = it.len, part = it.part;
   const int32_t u_id = a.own_idx[r];
   float4 acc[VPL], G[VPL];
 #pragma unroll
@@ -318,7 +322,7 @@ __global__ void __launch_bounds__(256) k_gat_src(GatPass a) {
     }
   }
   float s = 0.f;
-  float* row = part >= 0 ? a.partial + (int64_t)part * a.out_ld : a.out + (int64_t)a.out_idx[r] * a.out_ld;
+  float* row = part >= 0 ? a.partial + (part - a.part0) * a.out_ld : a.out + (int64_t)a.out_idx[r] * a.out_ld;
 #pragma unroll
   for (int j = 0; j < VPL; ++j) {
     const int c = (j * 64 + lane) * 4;
@@ -347,9 +351,10 @@ __global__ void __launch_bounds__(256) k_gat_src_g(GatPass a) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t t = (int64_t)blockIdx.x * 4 + wave;
   if (t >= a.n_items) return;
-  const int32_t r = a.it_row[t];
-  const int64_t e0 = a.it_e0[t];
-  const int32_t len = a.it_len[t], part = a.it_part[t];
+  const WorkItem it = a.items[t];
+  const int32_t r = it.row;
+  const int64_t e0 = it.e0;
+  const int32_t len = it.len, part = it.part;
   const int32_t u_id = a.own_idx[r];
   const int grp = lane / G_, c4 = (lane % G_) * 4;
   const bool has = c4 < a.d;
@@ -404,7 +409,7 @@ __global__ void __launch_bounds__(256) k_gat_src_g(GatPass a) {
     acc.w += __shfl_xor(acc.w, o, 64);
   }
   float s = 0.f;
-  float* row = part >= 0 ? a.partial + (int64_t)part * a.out_ld : a.out + (int64_t)a.out_idx[r] * a.out_ld;
+  float* row = part >= 0 ? a.partial + (part - a.part0) * a.out_ld : a.out + (int64_t)a.out_idx[r] * a.out_ld;
   if (has) {
     const float4 mine = ld4(a.own + (int64_t)u_id * a.own_ld + c4);
     s = fmaf(mine.x, G.x, fmaf(mine.y, G.y, fmaf(mine.z, G.z, mine.w * G.w)));
@@ -586,9 +591,11 @@ int prepare(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const ht_te
 
 int softmax_chunk(ht_ctx* ctx, const ht_graph* g, const ChunkMeta& c, const ht_gat_desc* desc, const GatWs& ws, ht_stats* st,
                   Timer* tm, bool backward) {
-  const int32_t* col = g->merged ? g->ucol.p + c.ue0 : g->col.p + c.e0;
-  const float* mult = g->merged ? g->umult.p + c.ue0 : nullptr;
-  const ItemSet& it = c.fwd;
+  const int32_t* col = g->merged ? g->ucol.p : g->col.p;
+  const float* mult = g->merged ? g->umult.p : nullptr;
+  const ItemRange& it = c.fwd;
+  const WorkItem* items = g->fwd_items.items.p + it.it0;
+  const CutRow* cuts = g->fwd_items.cuts.p + it.cut0;
   // rows without an in-edge (possible without self-loops) have no item: coefficient sums of 0
   HT_TRY(ht_fill_zero(ctx, ctx->stream, ws.zinv + c.dst0, (size_t)(c.dst1 - c.dst0) * 4));
   if (it.n_items == 0) return HT_OK;
@@ -599,16 +606,14 @@ int softmax_chunk(ht_ctx* ctx, const ht_graph* g, const ChunkMeta& c, const ht_g
   if (backward) HT_TRY(ht_fill_zero(ctx, ctx->stream, ws.r + c.dst0, (size_t)(c.dst1 - c.dst0) * 4));
   const unsigned nb = (unsigned)((it.n_items + 3) / 4);
   tm->begin(&st->t_gat_softmax_ms);
-  k_gat_scores<<<nb, 256, 0, ctx->stream>>>(it.row, it.e0, it.len, it.part, it.n_items, col, mult, ws.p + c.dst0, ws.q,
-                                            desc->slope, ws.w, ws.m + c.dst0, ws.zinv + c.dst0, part, part_s);
-  if (it.n_fix > 0)
-    k_gat_rowstats<<<(unsigned)((it.n_fix + 3) / 4), 256, 0, ctx->stream>>>(it.fx_row, it.fx_part0, it.fx_nseg, it.n_fix,
-                                                                               part, part_s, ws.m + c.dst0, ws.zinv + c.dst0);
-  k_gat_coefs<<<nb, 256, 0, ctx->stream>>>(it.row, it.e0, it.len, it.part, it.n_items, mult, ws.m + c.dst0, ws.zinv + c.dst0,
-                                           desc->slope, ws.w, backward ? ws.wf : nullptr, ws.r + c.dst0, part_r);
-  if (backward && it.n_fix > 0)
-    k_gat_fix_scalar<<<(unsigned)((it.n_fix + 3) / 4), 256, 0, ctx->stream>>>(it.fx_row, it.fx_part0, it.fx_nseg, it.n_fix, part_r,
-                                                                             ws.r + c.dst0);
+  k_gat_scores<<<nb, 256, 0, ctx->stream>>>(items, it.n_items, c.ue0, it.part0, col, mult, ws.p, ws.q, desc->slope, ws.w, ws.m,
+                                            ws.zinv, part, part_s);
+  if (it.n_cut > 0)
+    k_gat_rowstats<<<(unsigned)((it.n_cut + 3) / 4), 256, 0, ctx->stream>>>(cuts, it.n_cut, it.part0, part, part_s, ws.m, ws.zinv);
+  k_gat_coefs<<<nb, 256, 0, ctx->stream>>>(items, it.n_items, c.ue0, it.part0, mult, ws.m, ws.zinv, desc->slope, ws.w,
+                                           backward ? ws.wf : nullptr, ws.r, part_r);
+  if (backward && it.n_cut > 0)
+    k_gat_fix_scalar<<<(unsigned)((it.n_cut + 3) / 4), 256, 0, ctx->stream>>>(cuts, it.n_cut, it.part0, part_r, ws.r);
   tm->end();
   HT_LAUNCH_CHECK(ctx);
   return HT_OK;
@@ -653,11 +658,12 @@ int gat_fwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
     float* partial = nullptr;
     if (c.fwd.n_part > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)g->max_fpart * H_out->ld * 4, (void**)&partial));
     SpmmArgs a{};
-    a.it_row = c.fwd.row; a.it_e0 = c.fwd.e0; a.it_len = c.fwd.len; a.it_part = c.fwd.part; a.n_items = c.fwd.n_items;
-    a.fx_row = c.fwd.fx_row; a.fx_part0 = c.fwd.fx_part0; a.fx_nseg = c.fwd.fx_nseg; a.n_fix = c.fwd.n_fix;
+    a.items = g->fwd_items.items.p + c.fwd.it0; a.n_items = c.fwd.n_items;
+    a.cuts = g->fwd_items.cuts.p + c.fwd.cut0; a.n_fix = c.fwd.n_cut;
+    a.part0 = c.fwd.part0; a.row0 = c.dst0;
     a.n_edges = g->merged ? c.nu : c.nnz;
-    a.idx = g->merged ? g->ucol.p + c.ue0 : g->col.p + c.e0;
-    a.w_edge = ws.w;
+    a.idx = g->merged ? g->ucol.p : g->col.p;
+    a.w_edge = ws.w; a.w0 = c.ue0;
     a.src = ws.T; a.src_ld = ws.ld_t; a.d = desc->d_out;
     a.out = out_host ? obuf[b] : H_out->ptr + c.dst0 * H_out->ld; a.out_ld = H_out->ld;
     a.accumulate = 0;
@@ -761,11 +767,12 @@ int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
       float* fpart = nullptr;
       if (c.fwd.n_part > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)g->max_fpart * ws.ld_t * 4, (void**)&fpart));
       SpmmArgs q{};
-      q.it_row = c.fwd.row; q.it_e0 = c.fwd.e0; q.it_len = c.fwd.len; q.it_part = c.fwd.part; q.n_items = c.fwd.n_items;
-      q.fx_row = c.fwd.fx_row; q.fx_part0 = c.fwd.fx_part0; q.fx_nseg = c.fwd.fx_nseg; q.n_fix = c.fwd.n_fix;
+      q.items = g->fwd_items.items.p + c.fwd.it0; q.n_items = c.fwd.n_items;
+      q.cuts = g->fwd_items.cuts.p + c.fwd.cut0; q.n_fix = c.fwd.n_cut;
+      q.part0 = c.fwd.part0; q.row0 = c.dst0;
       q.n_edges = g->merged ? c.nu : c.nnz;
-      q.idx = g->merged ? g->ucol.p + c.ue0 : g->col.p + c.e0;
-      q.w_edge = ws.wf;
+      q.idx = g->merged ? g->ucol.p : g->col.p;
+      q.w_edge = ws.wf; q.w0 = c.ue0;
       q.src = ws.T; q.src_ld = ws.ld_t; q.d = d;
       q.out = Q; q.out_ld = ws.ld_t;
       q.accumulate = 0;
@@ -779,20 +786,20 @@ int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
     // source pass
     float* partial = nullptr;
     if (c.bwd.n_part > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)g->max_bpart * ld_dt * 4, (void**)&partial));
-    a.it_row = c.bwd.row; a.it_e0 = c.bwd.e0; a.it_len = c.bwd.len; a.it_part = c.bwd.part; a.n_items = c.bwd.n_items;
-    a.idx = g->merged ? g->usdst.p + c.ue0 : g->sdst.p + c.e0;
-    a.mult = g->merged ? g->umult_bwd.p + c.ue0 : nullptr;
+    a.items = g->bwd_items.items.p + c.bwd.it0; a.n_items = c.bwd.n_items; a.part0 = c.bwd.part0;
+    a.idx = g->merged ? g->usdst.p : g->sdst.p;
+    a.mult = g->merged ? g->umult_bwd.p : nullptr;
     a.mat = dz; a.mat_ld = ws.ld_t;
-    a.own = ws.T; a.own_ld = ws.ld_t; a.own_idx = g->nbr.p + c.nbr_off;
-    a.out = dT; a.out_ld = ld_dt; a.out_idx = g->nbr.p + c.nbr_off;
+    a.own = ws.T; a.own_ld = ws.ld_t; a.own_idx = g->nbr.p;
+    a.out = dT; a.out_ld = ld_dt; a.out_idx = g->nbr.p;
     a.partial = partial; a.sc_col = sc_col;
     tm->begin(&local->t_gat_src_ms);
     if (a.n_items > 0) HT_TRY(launch_src(ctx, a, nvec));
-    if (c.bwd.n_fix > 0) {
+    if (c.bwd.n_cut > 0) {
       SpmmArgs f{};
-      f.fx_row = c.bwd.fx_row; f.fx_part0 = c.bwd.fx_part0; f.fx_nseg = c.bwd.fx_nseg; f.n_fix = c.bwd.n_fix;
+      f.cuts = g->bwd_items.cuts.p + c.bwd.cut0; f.n_fix = c.bwd.n_cut; f.part0 = c.bwd.part0;
       f.d = sc_col + 4;
-      f.out = dT; f.out_ld = ld_dt; f.out_idx = g->nbr.p + c.nbr_off;
+      f.out = dT; f.out_ld = ld_dt; f.out_idx = g->nbr.p;
       f.accumulate = 1;
       f.partial = partial;
       HT_TRY(ht_spmm_fix_launch(ctx, st, f));

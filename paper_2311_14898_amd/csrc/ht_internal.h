@@ -187,35 +187,41 @@ int ht_radix_sort_u64(ht_ctx* ctx, uint64_t* keys, uint64_t* tmp, int64_t n, int
 // Bitmap helpers: words are uint64, bit b of word w is element 64*w + b.
 // pref[w] = number of set bits before word w; pref[nw] = total.
 int ht_bitmap_prefix(ht_ctx* ctx, const uint64_t* bm, int64_t nw, int32_t* cnt_tmp, int64_t* pref);
-// Writes the indices of set bits, ascending, to out (size pref[nw]).
-int ht_bitmap_expand(ht_ctx* ctx, const uint64_t* bm, int64_t nw, const int64_t* pref, int32_t* out);
 
 // ---- graph -------------------------------------------------------------------------------
-// Work items of one aggregation direction of one chunk: a row with at most
-// HT_SEG edges is one item; a longer row is cut into items of HT_SEG edges whose
-// partial sums are added in item order by a second kernel.
-struct ItemSet {
-  DevArr<char> blob;          // one allocation behind the arrays below
-  int32_t* row = nullptr;     // [n_items] row of the item (local to the chunk)
-  int64_t* e0 = nullptr;      // [n_items] first edge, relative to the chunk's first edge
-  int32_t* len = nullptr;     // [n_items] edges in the item (<= HT_SEG)
-  int32_t* part = nullptr;    // [n_items] -1: the row's only item; else index of its partial sum
-  int32_t* fx_row = nullptr;  // [n_fix] rows with several items
-  int32_t* fx_part0 = nullptr;
-  int32_t* fx_nseg = nullptr;
-  int64_t n_items = 0, n_part = 0, n_fix = 0;
+// Work items of one aggregation direction: a row with at most HT_SEG entries is one item; a longer row is cut into items
+// of HT_SEG entries whose partial sums are added in item order by a second kernel.  Rows are destinations (forward) or
+// positions of the N arena (backward); rows, entries and partial sums are numbered over the whole graph, and a chunk's
+// items are a contiguous range of the list, so a launch can take one chunk or all of them.
+struct __attribute__((aligned(16))) WorkItem {
+  int32_t row;
+  uint32_t e0;     // first entry (stored edges, or distinct pairs when duplicates are merged)
+  int32_t len;     // entries (<= HT_SEG)
+  int32_t part;    // -1: the row's only item; else index of its partial sum
+};
+struct __attribute__((aligned(16))) CutRow {   // a row with several items
+  int32_t row, part0, nseg, pad;
+};
+struct GraphItems {
+  DevArr<WorkItem> items;
+  DevArr<CutRow> cuts;
+  int64_t n_items = 0, n_part = 0, n_cut = 0;
+};
+struct ItemRange {             // a chunk's share
+  int64_t it0 = 0, n_items = 0, part0 = 0, n_part = 0, cut0 = 0, n_cut = 0;
 };
 
 struct ChunkMeta {
+  int32_t id = 0;              // position in vertex order
   int64_t dst0 = 0, dst1 = 0;  // destination range
   int64_t e0 = 0, nnz = 0;     // edge range in the global CSC arrays
   int64_t ue0 = 0, nu = 0;     // range of distinct (destination, source) pairs in the merged arrays (= e0, nnz when not merged)
   int64_t nsrc = 0;            // |N_j|
-  int64_t nbr_off = 0;         // offset of N_j in the nbr / slot arenas
-  int64_t sptr_off = 0;        // offset of sptr_j in the sptr arena (nbr_off + j)
+  int64_t nbr_off = 0;         // offset of N_j in the nbr / slot arenas (chunks in vertex order)
+  int64_t sptr_off = 0;        // offset of sptr_j in the sptr arena (nbr_off + id)
   int64_t n_reuse = 0, n_load = 0, n_leave = 0;
   int64_t reuse_off = 0, load_off = 0, leave_off = 0;
-  ItemSet fwd, bwd;            // rows = destinations / rows = local sources
+  ItemRange fwd, bwd;
 };
 
 struct ht_graph {
@@ -257,8 +263,8 @@ struct ht_graph {
   DevArr<int32_t> usdst;       // [n_unique] local destination of each distinct pair, by-source order
   DevArr<float> uw_bwd;        // [n_unique] multiplicity * s[destination]
   DevArr<float> umult_bwd;     // [n_unique] multiplicity, by-source order
-  DevBlock blk_pairs, blk_chunks;   // the allocations behind the distinct-pair arrays and the per-chunk arenas
-  DevArr<char> items_mem;           // the allocation behind the chunks' work-item lists
+  GraphItems fwd_items, bwd_items;
+  DevBlock blk_csc, blk_pairs, blk_chunks;   // the allocations behind the CSC, the distinct-pair arrays, and the per-chunk arenas with the work items
   int64_t v_ori = 0, v_ru = 0, v_load = 0;  // v_load: rows actually loaded per pass with this buffer
   int64_t max_nsrc = 0, max_ndst = 0, max_nnz = 0, max_fpart = 0, max_bpart = 0;
   int64_t cache_rows = 0;
@@ -273,27 +279,25 @@ struct ht_graph {
 // owns an item; sums are taken in edge order, partial sums in item order.
 struct SpmmArgs {
   // items
-  const int32_t* it_row;
-  const int64_t* it_e0;
-  const int32_t* it_len;
-  const int32_t* it_part;
+  const WorkItem* items;
   int64_t n_items;
-  int64_t n_edges;        // edges covered by the items (for launch heuristics)
-  const int32_t* fx_row;
-  const int32_t* fx_part0;
-  const int32_t* fx_nseg;
+  int64_t n_edges;        // entries covered by the items (for launch heuristics)
+  const CutRow* cuts;
   int64_t n_fix;
+  int64_t part0 = 0;      // number of the first partial sum (row 0 of `partial`)
+  int64_t row0 = 0;       // row that is row 0 of `out` (when out_idx is null)
   // edges
-  const int32_t* idx;     // per edge: row of `src` to read (chunk-relative pointer)
+  const int32_t* idx;     // per entry: row of `src` to read
   const float* ew;        // per-edge weight table indexed by idx (nullable: weight 1)
-  const float* w_edge = nullptr;  // per-edge weights in edge order (takes precedence over ew)
+  const float* w_edge = nullptr;  // per-entry weights in entry order, the first one for entry w0 (takes precedence over ew)
+  int64_t w0 = 0;
   const float* src;       // source matrix
   int64_t src_ld;
   int32_t d;              // valid columns
   // output
   float* out;             // output matrix
   int64_t out_ld;
-  const int32_t* out_idx; // row r -> output row (nullable: r); bit 31 set => overwrite even when accumulating
+  const int32_t* out_idx; // row r -> output row (nullable: r - row0); bit 31 set => overwrite even when accumulating
   const float* post;      // per-row factor
   const int32_t* post_idx;// row r -> index into post (nullable: r)
   int32_t accumulate;     // 1: out += value
@@ -306,7 +310,7 @@ struct SpmmArgs {
   double* t_fix = nullptr;
 };
 int ht_spmm_launch(ht_ctx* ctx, hipStream_t st, const SpmmArgs& a);
-// Only the second kernel: rows fx_row[] = their partial rows added in item order (d, out*, partial, fx_* are read).
+// Only the second kernel: the cut rows = their partial rows added in item order (d, out*, partial, cuts, part0 are read).
 int ht_spmm_fix_launch(ht_ctx* ctx, hipStream_t st, const SpmmArgs& a);
 
 // Row gather / scatter (ht_spmm.hip)

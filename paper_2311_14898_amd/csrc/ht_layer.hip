@@ -183,6 +183,25 @@ int gather_chunk(Run& R, int j, const ht_tensor* H_in, const float* Hin, int d, 
   return HT_OK;
 }
 
+// Items and entries of chunk c for an aggregation: forward (rows = destinations, entries name sources by global id or by
+// buffer position) or backward (rows = positions of N_j, entries name the chunk's destination rows).
+void agg_args(const ht_graph* g, const ChunkMeta& c, bool fwd, bool buffer, SpmmArgs* a) {
+  const GraphItems& gi = fwd ? g->fwd_items : g->bwd_items;
+  const ItemRange& r = fwd ? c.fwd : c.bwd;
+  a->items = gi.items.p + r.it0; a->n_items = r.n_items;
+  a->cuts = gi.cuts.p + r.cut0; a->n_fix = r.n_cut;
+  a->part0 = r.part0;
+  a->row0 = fwd ? c.dst0 : c.nbr_off;
+  a->n_edges = g->merged ? c.nu : c.nnz;
+  if (g->merged) {
+    a->idx = !fwd ? g->usdst.p : buffer ? g->ucol_slot.p : g->ucol.p;
+    a->w_edge = !fwd ? g->uw_bwd.p : buffer ? g->umult.p : g->uw_fwd.p;
+  } else {
+    a->idx = !fwd ? g->sdst.p : buffer ? g->col_slot.p : g->col.p;
+    a->ew = !fwd ? g->s.p + c.dst0 : buffer ? nullptr : g->s.p;
+  }
+}
+
 // Aggregate of chunk j into out rows [0, ndst) (pitch out_ld) on the compute
 // stream.  src/src_ld: H_in read in place, or the neighbour buffer (rows already
 // scaled by s_u, indexed by buffer position).
@@ -194,22 +213,12 @@ int spmm_chunk(Run& R, int j, bool buffer, const float* src, int64_t src_ld, int
   float* partial = nullptr;
   if (c.fwd.n_part > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)g->max_fpart * out_ld * 4, (void**)&partial));
   SpmmArgs a{};
-  a.it_row = c.fwd.row; a.it_e0 = c.fwd.e0; a.it_len = c.fwd.len; a.it_part = c.fwd.part; a.n_items = c.fwd.n_items;
-  a.n_edges = c.nnz;
-  a.fx_row = c.fwd.fx_row; a.fx_part0 = c.fwd.fx_part0; a.fx_nseg = c.fwd.fx_nseg; a.n_fix = c.fwd.n_fix;
-  if (g->merged) {
-    a.idx = (buffer ? g->ucol_slot.p : g->ucol.p) + c.ue0;
-    a.w_edge = (buffer ? g->umult.p : g->uw_fwd.p) + c.ue0;
-    a.n_edges = c.nu;
-  } else {
-    a.idx = (buffer ? g->col_slot.p : g->col.p) + c.e0;
-    a.ew = buffer ? nullptr : g->s.p;
-  }
+  agg_args(g, c, true, buffer, &a);
   a.src = src;
   a.src_ld = src_ld;
   a.d = d;
   a.out = out; a.out_ld = out_ld; a.out_idx = nullptr;
-  a.post = g->s.p + c.dst0; a.post_idx = nullptr;
+  a.post = g->s.p; a.post_idx = nullptr;
   a.accumulate = 0;
   a.partial = partial;
   a.max_slabs = ctx->slabs_fwd;
@@ -824,25 +833,15 @@ int layer_bwd_impl(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, con
         const int64_t out_ld = gbuffer ? ld_i : dH_in->ld;
         if (cj.bwd.n_part > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)g->max_bpart * out_ld * 4, (void**)&partial));
         SpmmArgs a{};
-        a.it_row = cj.bwd.row; a.it_e0 = cj.bwd.e0; a.it_len = cj.bwd.len; a.it_part = cj.bwd.part; a.n_items = cj.bwd.n_items;
-        a.n_edges = cj.nnz;
-        a.fx_row = cj.bwd.fx_row; a.fx_part0 = cj.bwd.fx_part0; a.fx_nseg = cj.bwd.fx_nseg; a.n_fix = cj.bwd.n_fix;
-        if (g->merged) {
-          a.idx = g->usdst.p + cj.ue0;
-          a.w_edge = g->uw_bwd.p + cj.ue0;
-          a.n_edges = cj.nu;
-        } else {
-          a.idx = g->sdst.p + cj.e0;
-          a.ew = g->s.p + cj.dst0;
-        }
+        agg_args(g, cj, false, false, &a);
         a.src = da_chunk + (cj.dst0 - c.dst0) * ld_i;      // the chunk's rows inside the group's grad a
         a.src_ld = ld_i;
         a.d = di;
         a.out = gbuffer ? gbuf : dH_in->ptr;
         a.out_ld = out_ld;
-        a.out_idx = gbuffer ? g->gslot.p + cj.nbr_off : g->nbr.p + cj.nbr_off;
+        a.out_idx = gbuffer ? g->gslot.p : g->nbr.p;
         a.post = g->s.p;
-        a.post_idx = g->nbr.p + cj.nbr_off;
+        a.post_idx = g->nbr.p;
         a.accumulate = 1;
         a.partial = partial;
         a.max_slabs = ctx->slabs_bwd;
@@ -884,23 +883,6 @@ int need_hbm(ht_ctx* ctx, const ht_tensor* t, const char* name) {
   return HT_OK;
 }
 
-// Aggregation arguments of chunk j at width d: forward (rows = destinations, reading rows of
-// `src` by global id) or backward (rows = sources N_j, reading the chunk's destination rows).
-void agg_args_direct(const ht_graph* g, const ChunkMeta& c, bool fwd, SpmmArgs* a) {
-  const ItemSet& it = fwd ? c.fwd : c.bwd;
-  a->it_row = it.row; a->it_e0 = it.e0; a->it_len = it.len; a->it_part = it.part; a->n_items = it.n_items;
-  a->fx_row = it.fx_row; a->fx_part0 = it.fx_part0; a->fx_nseg = it.fx_nseg; a->n_fix = it.n_fix;
-  a->n_edges = c.nnz;
-  if (g->merged) {
-    a->idx = (fwd ? g->ucol.p : g->usdst.p) + c.ue0;
-    a->w_edge = (fwd ? g->uw_fwd.p : g->uw_bwd.p) + c.ue0;
-    a->n_edges = c.nu;
-  } else {
-    a->idx = fwd ? g->col.p + c.e0 : g->sdst.p + c.e0;
-    a->ew = fwd ? g->s.p : g->s.p + c.dst0;
-  }
-}
-
 int layer_fwd_update_first(Run& R, const ht_layer_desc* desc, const ht_tensor* H_in, const float* W, ht_tensor* H_out) {
   ht_ctx* ctx = R.ctx;
   const ht_graph* g = R.g;
@@ -931,10 +913,10 @@ int layer_fwd_update_first(Run& R, const ht_layer_desc* desc, const ht_tensor* H
     float* partial = nullptr;
     if (c.fwd.n_part > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)g->max_fpart * H_out->ld * 4, (void**)&partial));
     SpmmArgs a{};
-    agg_args_direct(g, c, true, &a);
+    agg_args(g, c, true, false, &a);
     a.src = T; a.src_ld = ld_t; a.d = dn;
     a.out = H_out->ptr + c.dst0 * H_out->ld; a.out_ld = H_out->ld; a.out_idx = nullptr;
-    a.post = g->s.p + c.dst0; a.post_idx = nullptr;
+    a.post = g->s.p; a.post_idx = nullptr;
     a.accumulate = 0;
     a.relu = desc->act == HT_ACT_RELU;
     a.partial = partial;
@@ -994,11 +976,11 @@ int layer_bwd_update_first(Run& R, const ht_layer_desc* desc, const ht_tensor* H
     float* partial = nullptr;
     if (c.bwd.n_part > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)g->max_bpart * ld_t * 4, (void**)&partial));
     SpmmArgs a{};
-    agg_args_direct(g, c, false, &a);
+    agg_args(g, c, false, false, &a);
     a.src = dz_rows; a.src_ld = dz_ld; a.d = dn;
     a.out = dT; a.out_ld = ld_t;
-    a.out_idx = g->nbr.p + c.nbr_off;
-    a.post = g->s.p; a.post_idx = g->nbr.p + c.nbr_off;
+    a.out_idx = g->nbr.p;
+    a.post = g->s.p; a.post_idx = g->nbr.p;
     a.accumulate = 1;
     a.partial = partial;
     a.max_slabs = ctx->slabs_bwd;

@@ -7,6 +7,15 @@
 // (N_j ^ N_{j-1} reused, N_j \ N_{j-1} loaded), Sec. 5.3 (V_ori, V_+ru),
 // Sec. 6 (same buffer position for duplicated vertices of adjacent chunks;
 // loaded rows take freed positions; topology rewritten to buffer positions).
+//
+// Every step runs over all chunks in one launch: the chunks' arrays lie behind
+// each other in vertex order, so an edge, a word of a neighbour bitmap or a
+// local source finds its chunk by a search in the n + 1 offsets (once per block,
+// then forward).  Only the buffer positions are made chunk by chunk, because
+// the positions a chunk's loads take are those the chunks before it left free.
+// With one set of launches per chunk a 10,000-vertex graph of 4 chunks took 380
+// launches and 2.2 ms with a first layer, now 0.85 ms; a graph of 2.45 M vertices,
+// 62 M edges and 16 chunks 1,606 launches and 27.1 ms, now 16.2 ms (MI355X).
 #include <algorithm>
 #include <atomic>
 #include <cstdlib>
@@ -16,18 +25,52 @@
 namespace {
 
 constexpr int TB = 256;
+constexpr int ETILE = 2048;      // entries of a sorted list one block handles
+constexpr int RTILE = 1024;      // rows one block cuts into work items
 inline unsigned nblk(int64_t n, int tb = TB) { return (unsigned)((n + tb - 1) / tb); }
 
-__global__ void k_check_ids(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, int64_t E, int64_t V,
-                            int32_t* __restrict__ flag) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= E) return;
-  int32_t u = src[i], v = dst[i];
-  if (u < 0 || v < 0 || u >= V || v >= V) *flag = 1;
+// ---- block-level helpers
+
+// last k in [0, n) with off[k] <= x (off ascending, off[0] <= x): the range that x lies in, empty ranges skipped
+__device__ __forceinline__ int find_range(const int64_t* __restrict__ off, int n, int64_t x) {
+  int lo = 0, hi = n;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (off[mid] <= x) lo = mid; else hi = mid;
+  }
+  return lo;
 }
 
+__device__ __forceinline__ uint64_t lanes_below(int lane) { return lane == 0 ? 0ull : (~0ull >> (64 - lane)); }
+
+// Exclusive sum over the 256 threads of a block, *total = sum of all.
+__device__ __forceinline__ uint64_t block_excl(uint64_t x, uint64_t* total) {
+  __shared__ uint64_t part[TB / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint64_t inc = x;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint64_t y = __shfl_up(inc, o, 64);
+    if (lane >= o) inc += y;
+  }
+  __syncthreads();   // a previous use of part
+  if (lane == 63) part[wave] = inc;
+  __syncthreads();
+  uint64_t before = 0, tot = 0;
+#pragma unroll
+  for (int w = 0; w < TB / 64; ++w) {
+    if (w < wave) before += part[w];
+    tot += part[w];
+  }
+  *total = tot;
+  return before + inc - x;
+}
+
+// ---- edges -> CSC
+
+// key = (destination << bitsV) | source; an id outside [0, V) raises the flag and becomes 0, so that nothing later leaves its array
 __global__ void k_pack_keys(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, int64_t E, int64_t V,
-                            int bitsV, int self_loops, uint64_t* __restrict__ keys) {
+                            int bitsV, int self_loops, uint64_t* __restrict__ keys, int64_t* __restrict__ flag) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t n = E + (self_loops ? V : 0);
   if (i >= n) return;
@@ -35,27 +78,101 @@ __global__ void k_pack_keys(const int32_t* __restrict__ src, const int32_t* __re
   if (i < E) {
     u = (uint64_t)(uint32_t)src[i];
     v = (uint64_t)(uint32_t)dst[i];
+    if (u >= (uint64_t)V || v >= (uint64_t)V) {
+      *flag = 1;
+      u = v = 0;
+    }
   } else {
     u = v = (uint64_t)(i - E);
   }
   keys[i] = (v << bitsV) | u;
 }
 
-__global__ void k_low_bits(const uint64_t* __restrict__ keys, int64_t n, uint64_t mask, int32_t* __restrict__ out) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = (int32_t)(keys[i] & mask);
+// From the sorted keys: sources, row offsets, and the number of distinct keys of each tile.
+__global__ void __launch_bounds__(TB) k_csc(const uint64_t* __restrict__ keys, int64_t n, int bitsV, int64_t V,
+                                            int32_t* __restrict__ col, int64_t* __restrict__ indptr,
+                                            int32_t* __restrict__ ucount) {
+  const uint64_t mask = ((uint64_t)1 << bitsV) - 1;
+  uint32_t uniq = 0;
+#pragma unroll
+  for (int r = 0; r < ETILE / TB; ++r) {
+    const int64_t i = (int64_t)blockIdx.x * ETILE + r * TB + threadIdx.x;
+    if (i >= n) break;
+    const uint64_t k = keys[i];
+    const uint64_t kp = i > 0 ? keys[i - 1] : ~k;
+    col[i] = (int32_t)(k & mask);
+    uniq += k != kp;
+    const int64_t row = (int64_t)(k >> bitsV), rp = i > 0 ? (int64_t)(kp >> bitsV) : -1;
+    for (int64_t q = rp + 1; q <= row; ++q) indptr[q] = i;
+    if (i == n - 1)
+      for (int64_t q = row + 1; q <= V; ++q) indptr[q] = n;
+  }
+  uint64_t tot;
+  block_excl(uniq, &tot);
+  if (threadIdx.x == 0) ucount[blockIdx.x] = (int32_t)tot;
 }
 
-// keys sorted by row = key >> shift; ptr[q] = first index whose row >= q, ptr[nrows] = n.
-__global__ void k_boundaries(const uint64_t* __restrict__ keys, int64_t n, int shift, int64_t nrows,
-                             int64_t* __restrict__ ptr) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int64_t r = (int64_t)(keys[i] >> shift);
-  const int64_t rp = i > 0 ? (int64_t)(keys[i - 1] >> shift) : -1;
-  for (int64_t q = rp + 1; q <= r; ++q) ptr[q] = i;
-  if (i == n - 1)
-    for (int64_t q = r + 1; q <= nrows; ++q) ptr[q] = n;
+// Positions of the first entry of every run of equal keys: upos[rank] = i, upos[nU] = n.  A wave takes 512
+// consecutive entries, so ranks follow the order of the list.  base[t] = runs before tile t.
+struct RunRanks {
+  uint64_t m[ETILE / TB];
+  int64_t off;     // rank of the wave's first run
+  int64_t first;   // the wave's first entry
+  __device__ __forceinline__ void find(const uint64_t* __restrict__ keys, int64_t n, const int64_t* __restrict__ base) {
+    __shared__ int32_t wtot[TB / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    first = (int64_t)blockIdx.x * ETILE + wave * (ETILE / 4);
+    int32_t tot = 0;
+#pragma unroll
+    for (int r = 0; r < ETILE / TB; ++r) {
+      const int64_t i = first + r * 64 + lane;
+      const bool start = i < n && (i == 0 || keys[i] != keys[i - 1]);
+      m[r] = __ballot(start);
+      tot += __popcll(m[r]);
+    }
+    if (lane == 0) wtot[wave] = tot;
+    __syncthreads();
+    off = base[blockIdx.x];
+    for (int w = 0; w < wave; ++w) off += wtot[w];
+  }
+};
+
+__global__ void __launch_bounds__(TB) k_runs_fwd(const uint64_t* __restrict__ keys, int64_t n, int bitsV, int64_t V,
+                                                 const int64_t* __restrict__ base, int64_t nU, uint32_t* __restrict__ upos,
+                                                 int64_t* __restrict__ uindptr) {
+  RunRanks R;
+  R.find(keys, n, base);
+  const int lane = threadIdx.x & 63;
+  const uint64_t lt = lanes_below(lane);
+#pragma unroll
+  for (int r = 0; r < ETILE / TB; ++r) {
+    const int64_t i = R.first + r * 64 + lane;
+    if (i < n) {
+      const int64_t rank = R.off + __popcll(R.m[r] & lt);
+      const int64_t row = (int64_t)(keys[i] >> bitsV), rp = i > 0 ? (int64_t)(keys[i - 1] >> bitsV) : -1;
+      if ((R.m[r] >> lane) & 1) upos[rank] = (uint32_t)i;
+      for (int64_t q = rp + 1; q <= row; ++q) uindptr[q] = rank;
+      if (i == n - 1) {
+        for (int64_t q = row + 1; q <= V; ++q) uindptr[q] = nU;
+        upos[nU] = (uint32_t)n;
+      }
+    }
+    R.off += __popcll(R.m[r]);
+  }
+}
+
+// distinct pairs in CSC order: source, weight multiplicity * s[source] (rows read in place), multiplicity (rows pre-scaled in the buffer)
+__global__ void k_merge_fwd(const uint32_t* __restrict__ upos, int64_t nU, const int32_t* __restrict__ col,
+                            const float* __restrict__ s, int32_t* __restrict__ ucol, float* __restrict__ uw,
+                            float* __restrict__ umult) {
+  int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (u >= nU) return;
+  const uint32_t e = upos[u];
+  const float m = (float)(upos[u + 1] - e);
+  const int32_t c = col[e];
+  ucol[u] = c;
+  uw[u] = m * s[c];
+  umult[u] = m;
 }
 
 __global__ void k_norm(const int64_t* __restrict__ indptr, int64_t V, float* __restrict__ s) {
@@ -65,41 +182,77 @@ __global__ void k_norm(const int64_t* __restrict__ indptr, int64_t V, float* __r
   s[v] = D > 0 ? (float)(1.0 / sqrt((double)D)) : 0.f;
 }
 
-// b[j] = min{ v in [0, V] : indptr[v] >= target[j] }
-__global__ void k_bounds(const int64_t* __restrict__ indptr, int64_t V, const int64_t* __restrict__ target, int n,
-                         int64_t* __restrict__ b) {
-  int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  const int64_t t = target[j];
-  int64_t lo = 0, hi = V;  // indptr[V] >= t always
-  while (lo < hi) {
-    int64_t mid = (lo + hi) >> 1;
-    if (indptr[mid] >= t) hi = mid; else lo = mid + 1;
+// Chunk boundaries b[0..n] and their edge offsets.  Edges: b[j] = min{ v in [0, V] : indptr[v] >= ceil(j Ep / n) };
+// vertices: b[j] = floor(j V / n).  (j Ep < 2^31 2^32)
+__global__ void k_bounds(const int64_t* __restrict__ indptr, int64_t V, int64_t Ep, int32_t n, int mode, int64_t* __restrict__ b,
+                         int64_t* __restrict__ eoff) {
+  int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (j > n) return;
+  int64_t v;
+  if (j == 0) v = 0;
+  else if (j == n) v = V;
+  else if (mode == HT_BALANCE_VERTICES) v = (int64_t)((uint64_t)j * (uint64_t)V / (uint64_t)n);
+  else {
+    const int64_t t = (int64_t)(((uint64_t)j * (uint64_t)Ep + (uint64_t)n - 1) / (uint64_t)n);
+    int64_t lo = 0, hi = V;   // indptr[V] >= t always
+    while (lo < hi) {
+      const int64_t mid = (lo + hi) >> 1;
+      if (indptr[mid] >= t) hi = mid; else lo = mid + 1;
+    }
+    v = lo;
   }
-  b[j] = lo;
+  b[j] = v;
+  eoff[j] = indptr[v];
 }
 
-// The set of sources of a chunk, N_j, as a bitmap.  Marking bits directly needs an atomic OR per entry, and the
+// out[i] = a[at[i]] for a handful of positions
+__global__ void k_gather_i64(const int64_t* __restrict__ a, const int64_t* __restrict__ at, int64_t n, int64_t* __restrict__ out) {
+  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) out[i] = a[at[i]];
+}
+// out[i] = a[i * stride]
+__global__ void k_gather_stride(const int64_t* __restrict__ a, int64_t stride, int64_t n, int64_t* __restrict__ out) {
+  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) out[i] = a[i * stride];
+}
+
+// ---- neighbour bitmaps: row k holds N_k, bit u of it is in word u / 64; rows are padded to whole tiles of 256 words
+
+// The set of sources of a chunk, N_k, as a bitmap.  Marking bits directly needs an atomic OR per entry, and the
 // XCDs' L2s only agree on a word through device-scope accesses, which travel to the memory side: with a plain
 // test first, then a device-scope test, then the atomic, a 14 M-entry chunk took 258 us (346 without the plain
 // test) and a 9.8 M-entry chunk of a 23 M-vertex graph 467 us.  So entries mark a byte per vertex with plain
 // stores instead (every writer stores the same 1, the caches merge bytes on write-back, nothing has to be
 // coherent before the kernel ends), and a second kernel packs 64 bytes into a word and clears them for the next
-// chunk.  A repeated source follows its first copy (sources ascend inside a destination) and is skipped; a byte
+// chunks.  A repeated source follows its first copy (sources ascend inside a destination) and is skipped; a byte
 // seen set (a cached view can only lag behind) is not stored again.
-__global__ void k_mark_bytes(const int32_t* __restrict__ col, int64_t nnz, uint8_t* seen) {
-  int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= nnz) return;
-  const uint32_t u = (uint32_t)col[t];
-  if (t > 0 && (uint32_t)col[t - 1] == u) return;
-  if (!seen[u]) seen[u] = 1;
+// Entries [e0, e0 + cnt) of chunks k0, k0 + 1, ...: row k - k0 of `seen`.
+__global__ void __launch_bounds__(TB) k_mark_bytes(const int32_t* __restrict__ col, int64_t e0, int64_t cnt,
+                                                   const int64_t* __restrict__ eoff, int n, int k0, uint8_t* seen,
+                                                   int64_t row_bytes) {
+  int k = find_range(eoff, n, e0 + (int64_t)blockIdx.x * ETILE);
+  int64_t end = eoff[k + 1], beg = eoff[k];
+#pragma unroll
+  for (int r = 0; r < ETILE / TB; ++r) {
+    const int64_t t = (int64_t)blockIdx.x * ETILE + r * TB + threadIdx.x;
+    if (t >= cnt) break;
+    const int64_t e = e0 + t;
+    while (e >= end) {
+      ++k;
+      beg = end;
+      end = eoff[k + 1];
+    }
+    const uint32_t u = (uint32_t)col[e];
+    if (e > beg && (uint32_t)col[e - 1] == u) continue;
+    uint8_t* p = seen + (int64_t)(k - k0) * row_bytes + u;
+    if (!*p) *p = 1;
+  }
 }
-// bm[w] = bit b set iff seen[64 w + b]; the bytes (0 or 1 each) are cleared.  Eight bytes become eight bits by
-// one multiplication: byte k sits at bit 8k and the factor's term 2^(56 - 7k) moves it to bit 56 + k; no two
-// (byte, term) pairs meet in one bit, so nothing carries.
-__global__ void k_pack_seen(uint8_t* seen, uint64_t* __restrict__ bm, int64_t nw) {
-  int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (w >= nw) return;
+// bm[w] = bit b set iff seen[64 w + b]; the bytes (0 or 1 each) are cleared, a tile's set bits are counted.  Eight bytes
+// become eight bits by one multiplication: byte k sits at bit 8k and the factor's term 2^(56 - 7k) moves it to bit
+// 56 + k; no two (byte, term) pairs meet in one bit, so nothing carries.  A block per tile of 256 words.
+__global__ void __launch_bounds__(TB) k_pack_seen(uint8_t* seen, uint64_t* __restrict__ bm, int32_t* __restrict__ tile_cnt) {
+  const int64_t w = (int64_t)blockIdx.x * TB + threadIdx.x;
   ulonglong2* p = reinterpret_cast<ulonglong2*>(seen + w * 64);
   uint64_t bits = 0;
 #pragma unroll
@@ -110,36 +263,122 @@ __global__ void k_pack_seen(uint8_t* seen, uint64_t* __restrict__ bm, int64_t nw
     if (v.x | v.y) p[q] = make_ulonglong2(0ull, 0ull);
   }
   bm[w] = bits;
+  uint64_t tot;
+  block_excl((uint64_t)__popcll(bits), &tot);
+  if (threadIdx.x == 0) tile_cnt[blockIdx.x] = (int32_t)tot;
 }
 
-// bm = the distinct values of col[0..nnz) as a bitmap of nw words; seen: nw * 64 zero bytes, zero again afterwards
-int mark_sources(ht_ctx* ctx, hipStream_t st, const int32_t* col, int64_t nnz, uint8_t* seen, int64_t nw, uint64_t* bm) {
-  if (nnz > 0) {
-    k_mark_bytes<<<nblk(nnz), TB, 0, st>>>(col, nnz, seen);
+constexpr int64_t SEEN_BYTES = (int64_t)256 << 20;   // byte maps of as many chunks at once as stay in the last-level cache
+
+// words of a row of the chunks' bitmaps
+inline int64_t bm_words(int64_t V) { return ceil_div64(ceil_div64(V, 64), TB) * TB; }
+// chunks marked at once
+inline int64_t mark_group(int64_t nwp, int32_t n) { return std::max<int64_t>(1, std::min<int64_t>(n, SEEN_BYTES / (nwp * 64))); }
+
+// The neighbour bitmaps of all n chunks (chunk k: entries eoff[k] .. eoff[k + 1] of col) and the set bits of each of
+// their tiles; seen: mark_group() rows of nwp * 64 zero bytes.
+int mark_chunks(ht_ctx* ctx, hipStream_t st, const int32_t* col, const int64_t* h_eoff, const int64_t* d_eoff, int32_t n,
+                int64_t nwp, uint8_t* seen, uint64_t* bm, int32_t* tile_cnt) {
+  const int64_t grp = mark_group(nwp, n), tiles = nwp / TB;
+  for (int64_t k0 = 0; k0 < n; k0 += grp) {
+    const int64_t k1 = std::min<int64_t>(n, k0 + grp), cnt = h_eoff[k1] - h_eoff[k0];
+    if (cnt > 0) {
+      k_mark_bytes<<<nblk(cnt, ETILE), TB, 0, st>>>(col, h_eoff[k0], cnt, d_eoff, n, (int)k0, seen, nwp * 64);
+      HT_LAUNCH_CHECK(ctx);
+    }
+    k_pack_seen<<<(unsigned)((k1 - k0) * tiles), TB, 0, st>>>(seen, bm + k0 * nwp, tile_cnt + k0 * tiles);
     HT_LAUNCH_CHECK(ctx);
   }
-  k_pack_seen<<<nblk(nw), TB, 0, st>>>(seen, bm, nw);   // writes every word of bm
-  HT_LAUNCH_CHECK(ctx);
   return HT_OK;
+}
+
+// base[t] = set bits before tile t: every word's prefix and the list of set bits (vertex ids, rows behind each other)
+__global__ void __launch_bounds__(TB) k_expand_rows(const uint64_t* __restrict__ bm, int64_t nwp, const int64_t* __restrict__ base,
+                                                    uint32_t* __restrict__ wpref, int32_t* __restrict__ out) {
+  const int64_t w = (int64_t)blockIdx.x * TB + threadIdx.x;
+  uint64_t bits = bm[w], tot;
+  int64_t p = base[blockIdx.x] + (int64_t)block_excl((uint64_t)__popcll(bits), &tot);
+  if (wpref) wpref[w] = (uint32_t)p;
+  const int32_t u0 = (int32_t)((w % nwp) * 64);
+  while (bits) {
+    out[p++] = u0 + __ffsll((unsigned long long)bits) - 1;
+    bits &= bits - 1;
+  }
+}
+
+// ---- reuse / load / leave lists
+
+// What chunk position j reuses, loads and releases, as words: adjacent reuse (Sec. 5.1) compares the chunk's bitmap with
+// those of its neighbours in the schedule; a schedule-aware buffer brings the rows that are resident before chunk j
+// (pbm row j, released rows taken out) and the rows that leave after it (ebm row j + 1).
+struct ListRows {
+  const uint64_t* bm;      // neighbour bitmaps, row = chunk id
+  const int32_t* order;    // schedule position -> chunk id
+  const uint64_t* pbm;     // nullable: adjacent reuse
+  const uint64_t* ebm;
+  int64_t nwp;
+  int32_t n;
+  __device__ __forceinline__ void words(int j, int64_t w, uint64_t* reuse, uint64_t* load, uint64_t* leave) const {
+    const uint64_t cur = bm[(int64_t)order[j] * nwp + w];
+    uint64_t prev, out;
+    if (pbm) {
+      prev = pbm[(int64_t)j * nwp + w];
+      out = ebm[(int64_t)(j + 1) * nwp + w];
+    } else {
+      prev = j > 0 ? bm[(int64_t)order[j - 1] * nwp + w] : 0ull;
+      out = j + 1 < n ? (cur & ~bm[(int64_t)order[j + 1] * nwp + w]) : cur;
+    }
+    *reuse = cur & prev;
+    *load = cur & ~prev;
+    *leave = out;
+  }
+};
+
+// cnt[0 / 1 / 2][j, tile]: members of a tile of the reuse / load / leave words of position j
+__global__ void __launch_bounds__(TB) k_list_counts(ListRows R, int64_t tiles, int32_t* __restrict__ cnt) {
+  const int64_t j = blockIdx.x / tiles, t = blockIdx.x % tiles;
+  uint64_t a, b, c, tot;
+  R.words((int)j, t * TB + threadIdx.x, &a, &b, &c);
+  // three counts of at most 2^14 each travel in one sum
+  block_excl((uint64_t)__popcll(a) | ((uint64_t)__popcll(b) << 20) | ((uint64_t)__popcll(c) << 40), &tot);
+  if (threadIdx.x < 3) cnt[(int64_t)threadIdx.x * R.n * tiles + blockIdx.x] = (int32_t)((tot >> (20 * threadIdx.x)) & 0xFFFFF);
+}
+
+__device__ __forceinline__ void put_bits(uint64_t bits, int32_t u0, int32_t* __restrict__ out) {
+  while (bits) {
+    *out++ = u0 + __ffsll((unsigned long long)bits) - 1;
+    bits &= bits - 1;
+  }
+}
+
+// the three lists, positions behind each other; base: exclusive prefix over cnt
+__global__ void __launch_bounds__(TB) k_list_expand(ListRows R, int64_t tiles, const int64_t* __restrict__ base,
+                                                    int32_t* __restrict__ reuse, int32_t* __restrict__ load,
+                                                    int32_t* __restrict__ leave) {
+  const int64_t j = blockIdx.x / tiles, t = blockIdx.x % tiles, nt = (int64_t)R.n * tiles;
+  uint64_t a, b, c, tot;
+  R.words((int)j, t * TB + threadIdx.x, &a, &b, &c);
+  const uint64_t off = block_excl((uint64_t)__popcll(a) | ((uint64_t)__popcll(b) << 20) | ((uint64_t)__popcll(c) << 40), &tot);
+  const int32_t u0 = (int32_t)((t * TB + threadIdx.x) * 64);
+  put_bits(a, u0, reuse + base[blockIdx.x] + (int64_t)(off & 0xFFFFF));
+  put_bits(b, u0, load + (base[nt + blockIdx.x] - base[nt]) + (int64_t)((off >> 20) & 0xFFFFF));
+  put_bits(c, u0, leave + (base[2 * nt + blockIdx.x] - base[2 * nt]) + (int64_t)((off >> 40) & 0xFFFFF));
 }
 
 // Sum of up to three per-thread counts over the grid into totals[0..2]: waves by shuffles, the block's four waves
 // through LDS, one atomic add per block and total (with one add per wave the adds of a 23 M-bit bitmap, all to the
 // same three words, took 180 us).  Launch with a bounded grid; the callers stride.
-__device__ __forceinline__ void block_add3(unsigned long long a, unsigned long long b, unsigned long long c,
-                                           unsigned long long* __restrict__ totals, int ntot) {
-  __shared__ unsigned long long part[4][3];
+__device__ __forceinline__ void block_add2(unsigned long long a, unsigned long long b, unsigned long long* __restrict__ totals, int ntot) {
+  __shared__ unsigned long long part[4][2];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     a += __shfl_down(a, o, 64);
     b += __shfl_down(b, o, 64);
-    c += __shfl_down(c, o, 64);
   }
   const int wave = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) {
     part[wave][0] = a;
     part[wave][1] = b;
-    part[wave][2] = c;
   }
   __syncthreads();
   if ((int)threadIdx.x < ntot) {
@@ -151,21 +390,11 @@ __device__ __forceinline__ void block_add3(unsigned long long a, unsigned long l
 constexpr int POPC_GRID = 256;
 inline unsigned popc_grid(int64_t nw) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(nblk(nw), POPC_GRID)); }
 
-// totals[0] += popc(cur), totals[1] += popc(cur & prev), totals[2] += popc(cur & res)
-__global__ void __launch_bounds__(256) k_popc3(const uint64_t* __restrict__ cur, const uint64_t* __restrict__ prev,
-                                               const uint64_t* __restrict__ res, int64_t nw,
-                                               unsigned long long* __restrict__ totals) {
-  unsigned long long a = 0, b = 0, c = 0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nw; i += (int64_t)gridDim.x * blockDim.x) {
-    const uint64_t w = cur[i];
-    a += __popcll(w);
-    b += __popcll(w & prev[i]);
-    c += __popcll(w & res[i]);
-  }
-  block_add3(a, b, c, totals, 3);
-}
-
 // ---- row-buffer schedule with a known future (release for room, farthest next use first)
+__global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
+  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) p[i] = v;
+}
 // nxt[i] = position of the next chunk after j that needs N_j[i] (n: none); chunks are visited last to first
 __global__ void k_next_use(const int32_t* __restrict__ nbr, int64_t n, int32_t* __restrict__ last, int32_t j,
                            int32_t* __restrict__ nxt) {
@@ -188,7 +417,18 @@ __global__ void __launch_bounds__(256) k_popc_union(const uint64_t* __restrict__
     a += __popcll(R[i] | cur[i]);
     b += __popcll(R[i] & cur[i]);
   }
-  block_add3(a, b, 0, totals, 2);
+  block_add2(a, b, totals, 2);
+}
+// totals[0] += members of the union of the n rows
+__global__ void __launch_bounds__(256) k_popc_all(const uint64_t* __restrict__ bm, int64_t nwp, int32_t n,
+                                                  unsigned long long* __restrict__ totals) {
+  unsigned long long a = 0;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nwp; i += (int64_t)gridDim.x * blockDim.x) {
+    uint64_t w = 0;
+    for (int32_t k = 0; k < n; ++k) w |= bm[(int64_t)k * nwp + i];
+    a += __popcll(w);
+  }
+  block_add2(a, 0, totals, 1);
 }
 // hist[nu[u]] += 1 for every u in the candidate set (integer counts: order does not matter).
 // nbins <= HIST_LDS_BINS: counted per block in LDS first, so the few global bins see one add per block.
@@ -279,216 +519,291 @@ __global__ void k_bm_or(uint64_t* __restrict__ acc, const uint64_t* __restrict__
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < nw) acc[i] |= x[i];
 }
-
-// op 0: a & b   1: a & ~b
-__global__ void k_bm_op(const uint64_t* __restrict__ a, const uint64_t* __restrict__ b, int64_t nw, int op,
-                        uint64_t* __restrict__ out) {
+// out = a & ~b (out may be a)
+__global__ void k_bm_minus(const uint64_t* a, const uint64_t* __restrict__ b, int64_t nw, uint64_t* out) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nw) out[i] = op == 0 ? (a[i] & b[i]) : (a[i] & ~b[i]);
+  if (i < nw) out[i] = a[i] & ~b[i];
 }
 
-// a &= ~b
-__global__ void k_bm_clear(uint64_t* __restrict__ a, const uint64_t* __restrict__ b, int64_t nw) {
+// ---- buffer positions (Sec. 6), chunk by chunk
+
+// every position free: ones, the last word cut to C bits
+__global__ void k_free_init(uint64_t* __restrict__ bm, int64_t nwC, int64_t C) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nw) a[i] &= ~b[i];
+  if (i < nwC) bm[i] = (i == nwC - 1 && (C & 63)) ? (~0ull >> (64 - (C & 63))) : ~0ull;
 }
-
-// rank of each edge's source among the set bits = its position in N_j
-__global__ void k_remap(const int32_t* __restrict__ col, int64_t nnz, const uint64_t* __restrict__ bm,
-                        const int64_t* __restrict__ pref, int32_t* __restrict__ col_local) {
-  int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= nnz) return;
-  const uint32_t u = (uint32_t)col[t];
-  const uint64_t w = bm[u >> 6];
-  const uint64_t below = (u & 63) ? (w & (~0ull >> (64 - (u & 63)))) : 0ull;
-  col_local[t] = (int32_t)(pref[u >> 6] + __popcll(below));
+__global__ void __launch_bounds__(TB) k_free_count(const uint64_t* __restrict__ bm, int64_t nwC, int32_t* __restrict__ tile_cnt) {
+  const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
+  uint64_t tot;
+  block_excl(i < nwC ? (uint64_t)__popcll(bm[i]) : 0ull, &tot);
+  if (threadIdx.x == 0) tile_cnt[blockIdx.x] = (int32_t)tot;
 }
-
-// key = (local source << 32) | local destination, one thread per edge
-__global__ void k_set_i64(int64_t* p, int64_t v) { *p = v; }
-
-// a[at[i]] and b[at[i]] (b may be null) for a handful of positions
-__global__ void k_gather_offsets(const int64_t* __restrict__ a, const int64_t* __restrict__ b, const int64_t* __restrict__ at,
-                                 int64_t n, int64_t* __restrict__ out_a, int64_t* __restrict__ out_b) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  out_a[i] = a[at[i]];
-  out_b[i] = b ? b[at[i]] : 0;
-}
-
-__global__ void k_csr_keys(const int64_t* __restrict__ indptr, int64_t dst0, int64_t dst1, int64_t e0, int64_t nnz,
-                           const int32_t* __restrict__ col_local, uint64_t* __restrict__ keys) {
-  int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= nnz) return;
-  const int64_t e = e0 + t;
-  int64_t lo = dst0, hi = dst1;  // find the last v with indptr[v] <= e
-  while (hi - lo > 1) {
-    int64_t mid = (lo + hi) >> 1;
-    if (indptr[mid] <= e) lo = mid; else hi = mid;
+// The loaded rows take the lowest free positions: free position number r goes to load[r].  A block hands out one tile of
+// 256 words; the free positions before it are the sum over the tiles before (tile_cnt), or over the words before when
+// there are few.  in -> out: blocks must not see each other's positions taken.
+__global__ void __launch_bounds__(TB) k_assign(const uint64_t* __restrict__ in, uint64_t* __restrict__ out, int64_t nwC,
+                                               const int32_t* __restrict__ tile_cnt, const int32_t* __restrict__ load,
+                                               int64_t n_load, int32_t* __restrict__ vslot, int32_t* __restrict__ load_slot) {
+  const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
+  uint64_t before = 0, tot;
+  if (tile_cnt)
+    for (int64_t t = threadIdx.x; t < (int64_t)blockIdx.x; t += TB) before += (uint64_t)tile_cnt[t];
+  else
+    for (int64_t t = threadIdx.x; t < (int64_t)blockIdx.x * TB; t += TB) before += (uint64_t)__popcll(in[t]);
+  block_excl(before, &before);
+  uint64_t w = i < nwC ? in[i] : 0ull;
+  int64_t r = (int64_t)(before + block_excl((uint64_t)__popcll(w), &tot));
+  if (i >= nwC) return;
+  while (w && r < n_load) {
+    const int b = __ffsll((unsigned long long)w) - 1;
+    const int32_t sl = (int32_t)(i * 64 + b);
+    vslot[load[r]] = sl;
+    load_slot[r] = sl;
+    w &= w - 1;
+    ++r;
   }
-  keys[t] = ((uint64_t)(uint32_t)col_local[t] << 32) | (uint64_t)(uint32_t)(lo - dst0);
+  out[i] = w;
 }
-
-// leave list of the previous chunk: remember the position, free it
-__global__ void k_evict(const int32_t* __restrict__ leave, int64_t n, int32_t* __restrict__ vslot,
-                        uint32_t* freebm32, int32_t* __restrict__ leave_slot) {
-  int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n) return;
-  const int32_t u = leave[k];
-  const int32_t sl = vslot[u];
-  leave_slot[k] = sl;
-  vslot[u] = -1;
+// Positions of the members of N_j (with bit 31 where a member was not resident before), and of the rows that leave after
+// chunk j, which become free.
+__global__ void k_lookup_evict(const int32_t* __restrict__ nbr, int64_t nsrc, const int32_t* __restrict__ vslot,
+                               const uint64_t* __restrict__ prev_bm, int32_t* __restrict__ slot, int32_t* __restrict__ gslot,
+                               const int32_t* __restrict__ leave, int64_t n_leave, uint32_t* freebm32,
+                               int32_t* __restrict__ leave_slot) {
+  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < nsrc) {
+    const uint32_t u = (uint32_t)nbr[i];
+    const int32_t sl = vslot[u];
+    slot[i] = sl;
+    const bool was = prev_bm && ((prev_bm[u >> 6] >> (u & 63)) & 1ull);
+    gslot[i] = was ? sl : (int32_t)((uint32_t)sl | 0x80000000u);
+    return;
+  }
+  i -= nsrc;
+  if (i >= n_leave) return;
+  const int32_t sl = vslot[leave[i]];
+  leave_slot[i] = sl;
   atomicOr(&freebm32[(uint32_t)sl >> 5], 1u << (sl & 31));
 }
 
-__global__ void k_assign(const int32_t* __restrict__ load, int64_t n, const int32_t* __restrict__ freelist,
-                         int32_t* __restrict__ vslot, uint32_t* freebm32, int32_t* __restrict__ load_slot) {
-  int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n) return;
-  const int32_t sl = freelist[k];
-  vslot[load[k]] = sl;
-  load_slot[k] = sl;
-  atomicAnd(&freebm32[(uint32_t)sl >> 5], ~(1u << (sl & 31)));
-}
+// ---- topology in local indices
 
-__global__ void k_lookup_slots(const int32_t* __restrict__ nbr, int64_t n, const int32_t* __restrict__ vslot,
-                               const uint64_t* __restrict__ prev_bm, int32_t* __restrict__ slot,
-                               int32_t* __restrict__ gslot) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const uint32_t u = (uint32_t)nbr[i];
-  const int32_t sl = vslot[u];
-  slot[i] = sl;
-  const bool was = (prev_bm[u >> 6] >> (u & 63)) & 1ull;
-  gslot[i] = was ? sl : (int32_t)((uint32_t)sl | 0x80000000u);
-}
-
-__global__ void k_map_i32(const int32_t* __restrict__ idx, int64_t n, const int32_t* __restrict__ table,
-                          int32_t* __restrict__ out) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = table[idx[i]];
-}
-
-__global__ void k_items_count(const int64_t* __restrict__ ptr, int64_t nrows, int HT_SEG, int32_t* __restrict__ nseg,
-                              int32_t* __restrict__ npart, int32_t* __restrict__ isfix) {
-  int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= nrows) return;
-  const int64_t len = ptr[r + 1] - ptr[r];
-  const int32_t k = len <= HT_SEG ? 1 : (int32_t)((len + HT_SEG - 1) / HT_SEG);
-  nseg[r] = k;
-  npart[r] = k > 1 ? k : 0;
-  isfix[r] = k > 1 ? 1 : 0;
-}
-
-__global__ void k_items_fill(const int64_t* __restrict__ ptr, int64_t ptr0, int64_t nrows, int HT_SEG,
-                             const int64_t* __restrict__ it_base, const int64_t* __restrict__ part_base,
-                             const int64_t* __restrict__ fix_base, int32_t* __restrict__ it_row,
-                             int64_t* __restrict__ it_e0, int32_t* __restrict__ it_len, int32_t* __restrict__ it_part,
-                             int32_t* __restrict__ fx_row, int32_t* __restrict__ fx_part0,
-                             int32_t* __restrict__ fx_nseg) {
-  int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= nrows) return;
-  const int64_t b = ptr[r] - ptr0, len = ptr[r + 1] - ptr[r];
-  const int64_t t0 = it_base[r];
-  const int32_t k = (int32_t)(it_base[r + 1] - t0);
-  const int64_t p0 = part_base[r];
-  for (int32_t q = 0; q < k; ++q) {
-    it_row[t0 + q] = (int32_t)r;
-    it_e0[t0 + q] = b + (int64_t)q * HT_SEG;
-    const int64_t rem = len - (int64_t)q * HT_SEG;
-    it_len[t0 + q] = (int32_t)(rem < HT_SEG ? rem : HT_SEG);
-    it_part[t0 + q] = k > 1 ? (int32_t)(p0 + q) : -1;
-  }
-  if (k > 1) {
-    const int64_t f = fix_base[r];
-    fx_row[f] = (int32_t)r;
-    fx_part0[f] = (int32_t)p0;
-    fx_nseg[f] = k;
+// For every edge in CSC order: the position of its source in N_k, its buffer position, and the sort key
+// (position of (k, source) in the N arena, local destination) of the by-source grouping.
+__global__ void __launch_bounds__(TB) k_remap(const uint64_t* __restrict__ csc_keys, int64_t n_edges, int bitsV,
+                                              const int64_t* __restrict__ eoff, const int64_t* __restrict__ bounds,
+                                              const int64_t* __restrict__ noff, int n, const uint64_t* __restrict__ bm,
+                                              int64_t nwp, const uint32_t* __restrict__ wpref, const int32_t* __restrict__ slot,
+                                              int32_t* __restrict__ col_local, int32_t* __restrict__ col_slot,
+                                              uint64_t* __restrict__ keys) {
+  int k = find_range(eoff, n, (int64_t)blockIdx.x * ETILE);
+  int64_t end = eoff[k + 1];
+  const uint64_t mask = ((uint64_t)1 << bitsV) - 1;
+#pragma unroll
+  for (int r = 0; r < ETILE / TB; ++r) {
+    const int64_t e = (int64_t)blockIdx.x * ETILE + r * TB + threadIdx.x;
+    if (e >= n_edges) break;
+    while (e >= end) end = eoff[++k + 1];
+    const uint64_t key = csc_keys[e];
+    const uint32_t u = (uint32_t)(key & mask);
+    const int64_t w = (int64_t)k * nwp + (u >> 6);
+    const uint64_t below = (u & 63) ? (bm[w] & (~0ull >> (64 - (u & 63)))) : 0ull;
+    const uint32_t p = wpref[w] + (uint32_t)__popcll(below);
+    col_local[e] = (int32_t)((int64_t)p - noff[k]);
+    col_slot[e] = slot[p];
+    keys[e] = ((uint64_t)p << 32) | (uint64_t)((int64_t)(key >> bitsV) - bounds[k]);
   }
 }
 
-// ---- merging of duplicate edges (a multigraph's repeated (u -> v) entries are adjacent in both
-// sorted orders): one entry per distinct pair with weight multiplicity * s.
-__global__ void k_dup_flags_u32(const int32_t* __restrict__ col, int64_t n, int32_t* __restrict__ flag) {
-  int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < n) flag[e] = (e == 0 || col[e] != col[e - 1]) ? 1 : 0;
+// From the keys sorted by arena position: local destinations, offsets of every local source inside its chunk
+// (chunk k's nsrc + 1 offsets start at arena position + k), distinct keys per tile (nullable).
+__global__ void __launch_bounds__(TB) k_by_source(const uint64_t* __restrict__ keys, int64_t n_edges,
+                                                  const int64_t* __restrict__ eoff, int n, int32_t* __restrict__ sdst,
+                                                  int64_t* __restrict__ sptr, int32_t* __restrict__ ucount) {
+  int k = find_range(eoff, n, (int64_t)blockIdx.x * ETILE);
+  int64_t end = eoff[k + 1], beg = eoff[k];
+  uint32_t uniq = 0;
+#pragma unroll
+  for (int r = 0; r < ETILE / TB; ++r) {
+    const int64_t i = (int64_t)blockIdx.x * ETILE + r * TB + threadIdx.x;
+    if (i >= n_edges) break;
+    while (i >= end) {
+      ++k;
+      beg = end;
+      end = eoff[k + 1];
+    }
+    const uint64_t key = keys[i], kp = i > 0 ? keys[i - 1] : ~key;
+    sdst[i] = (int32_t)(key & 0xFFFFFFFFull);
+    if ((key >> 32) != (kp >> 32)) sptr[(int64_t)(key >> 32) + k] = i - beg;
+    uniq += key != kp;
+  }
+  if (!ucount) return;
+  uint64_t tot;
+  block_excl(uniq, &tot);
+  if (threadIdx.x == 0) ucount[blockIdx.x] = (int32_t)tot;
 }
-__global__ void k_row_start_flags(const int64_t* __restrict__ indptr, int64_t V, int64_t n, int32_t* __restrict__ flag) {
-  int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v < V && indptr[v] < n) flag[indptr[v]] = 1;
+// the closing offset of every chunk: its number of entries
+__global__ void k_sptr_ends(const int64_t* __restrict__ noff, const int64_t* __restrict__ eoff, int n, int64_t* __restrict__ sptr) {
+  int k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k < n) sptr[noff[k + 1] + k] = eoff[k + 1] - eoff[k];
 }
-__global__ void k_dup_flags_u64(const uint64_t* __restrict__ keys, int64_t n, int32_t* __restrict__ flag) {
-  int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < n) flag[e] = (e == 0 || keys[e] != keys[e - 1]) ? 1 : 0;
+// the same for the distinct (source, destination) pairs
+__global__ void __launch_bounds__(TB) k_runs_bwd(const uint64_t* __restrict__ keys, int64_t n_edges,
+                                                 const int64_t* __restrict__ base, int64_t nU, const int64_t* __restrict__ eoff,
+                                                 const int64_t* __restrict__ ueoff, int n, uint32_t* __restrict__ upos,
+                                                 int64_t* __restrict__ usptr) {
+  RunRanks R;
+  R.find(keys, n_edges, base);
+  const int lane = threadIdx.x & 63;
+  const uint64_t lt = lanes_below(lane);
+  int k = find_range(eoff, n, (int64_t)blockIdx.x * ETILE);
+  int64_t end = eoff[k + 1];
+#pragma unroll
+  for (int r = 0; r < ETILE / TB; ++r) {
+    const int64_t i = R.first + r * 64 + lane;
+    if (i < n_edges) {
+      while (i >= end) end = eoff[++k + 1];
+      const int64_t rank = R.off + __popcll(R.m[r] & lt);
+      if ((R.m[r] >> lane) & 1) {
+        upos[rank] = (uint32_t)i;
+        if (i == 0 || (keys[i] >> 32) != (keys[i - 1] >> 32)) usptr[(int64_t)(keys[i] >> 32) + k] = rank - ueoff[k];
+      }
+      if (i == n_edges - 1) upos[nU] = (uint32_t)n_edges;
+    }
+    R.off += __popcll(R.m[r]);
+  }
 }
-// upos[u] = position of the u-th flagged entry; upos[nU] = n is written by the host
-__global__ void k_flag_positions(const int32_t* __restrict__ flag, const int64_t* __restrict__ rank, int64_t n,
-                                 int64_t* __restrict__ upos) {
-  int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < n && flag[e]) upos[rank[e]] = e;
+// by-source distinct pairs: local destination, weight multiplicity * s[destination], multiplicity
+__global__ void __launch_bounds__(TB) k_merge_bwd(const uint32_t* __restrict__ upos, int64_t nU, const uint64_t* __restrict__ keys,
+                                                  const int64_t* __restrict__ ueoff, const int64_t* __restrict__ bounds, int n,
+                                                  const float* __restrict__ s, int32_t* __restrict__ usdst,
+                                                  float* __restrict__ uw, float* __restrict__ umult) {
+  int k = find_range(ueoff, n, (int64_t)blockIdx.x * ETILE);
+  int64_t end = ueoff[k + 1];
+#pragma unroll
+  for (int r = 0; r < ETILE / TB; ++r) {
+    const int64_t u = (int64_t)blockIdx.x * ETILE + r * TB + threadIdx.x;
+    if (u >= nU) break;
+    while (u >= end) end = ueoff[++k + 1];
+    const uint32_t t = upos[u];
+    const float m = (float)(upos[u + 1] - t);
+    const int32_t d = (int32_t)(keys[t] & 0xFFFFFFFFull);
+    usdst[u] = d;
+    uw[u] = m * s[bounds[k] + d];
+    umult[u] = m;
+  }
 }
-// forward: ucol, weights mult*s[src] (rows read in place) and mult (rows pre-scaled in the buffer)
-__global__ void k_merge_fwd(const int64_t* __restrict__ upos, int64_t nU, const int32_t* __restrict__ col,
-                            const float* __restrict__ s, int32_t* __restrict__ ucol, float* __restrict__ uw,
-                            float* __restrict__ umult) {
-  int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (u >= nU) return;
-  const int64_t e = upos[u];
-  const float m = (float)(upos[u + 1] - e);
-  const int32_t c = col[e];
-  ucol[u] = c;
-  uw[u] = m * s[c];
-  umult[u] = m;
-}
-__global__ void k_uindptr(const int64_t* __restrict__ indptr, const int64_t* __restrict__ rank, int64_t V, int64_t n,
-                          int64_t nU, int64_t* __restrict__ uindptr) {
-  int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v > V) return;
-  const int64_t e = indptr[v];
-  uindptr[v] = e < n ? rank[e] : nU;
-}
-__global__ void k_gather_i32_at(const int64_t* __restrict__ pos, int64_t pos_off, int64_t n, const int32_t* __restrict__ table,
-                                int32_t* __restrict__ out) {
+__global__ void k_gather_i32(const int32_t* __restrict__ table, const uint32_t* __restrict__ at, int64_t n, int32_t* __restrict__ out) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = table[pos[i] - pos_off];
-}
-// backward: per distinct (local source, local destination): usdst, weight mult*s[dst], compacted keys
-__global__ void k_merge_bwd(const int64_t* __restrict__ upos, int64_t nU, const uint64_t* __restrict__ keys,
-                            const float* __restrict__ s_chunk, int32_t* __restrict__ usdst, float* __restrict__ uw,
-                            float* __restrict__ umult, uint64_t* __restrict__ ukeys) {
-  int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (u >= nU) return;
-  const int64_t t = upos[u];
-  const float m = (float)(upos[u + 1] - t);
-  const uint64_t k = keys[t];
-  const int32_t d = (int32_t)(k & 0xFFFFFFFFull);
-  usdst[u] = d;
-  uw[u] = m * s_chunk[d];
-  umult[u] = m;
-  ukeys[u] = k;
+  if (i < n) out[i] = table[at[i]];
 }
 
-// Dispatch order of work items: by the first row they read (edges of a row are
-// sorted by that index), so items in flight together read neighbouring rows.
-__global__ void k_item_keys(const int64_t* __restrict__ it_e0, const int32_t* __restrict__ it_len, int64_t n,
-                            const int32_t* __restrict__ idx, uint64_t* __restrict__ keys) {
-  int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n) return;
-  const uint32_t first = it_len[t] > 0 ? (uint32_t)idx[it_e0[t]] : 0u;
-  keys[t] = ((uint64_t)first << 32) | (uint64_t)(uint32_t)t;
+// ---- work items
+
+// The rows of one direction: destinations (entries ptr[r] .. ptr[r + 1]), or positions of the N arena, whose offsets are
+// relative to their chunk (chunk k's entries start at eoff[k], its offsets at arena position + k).
+struct RowSet {
+  const int64_t* ptr;
+  const int64_t* first;    // [n + 1] first row of every chunk
+  const int64_t* eoff;     // nullptr: destinations
+  int n;
+  __device__ __forceinline__ void get(int64_t r, int k, int64_t* e0, int64_t* len) const {
+    const int64_t* p = ptr + r + (eoff ? k : 0);
+    *e0 = p[0] + (eoff ? eoff[k] : 0);
+    *len = p[1] - p[0];
+  }
+};
+
+// items, items of cut rows, cut rows of every tile of RTILE rows
+__global__ void __launch_bounds__(TB) k_items_count(RowSet R, int64_t nrows, int seg, int64_t tiles, int32_t* __restrict__ cnt) {
+  int k = find_range(R.first, R.n, (int64_t)blockIdx.x * RTILE);
+  int64_t end = R.first[k + 1];
+  uint64_t items = 0, parts = 0, cuts = 0;
+#pragma unroll
+  for (int q = 0; q < RTILE / TB; ++q) {
+    const int64_t r = (int64_t)blockIdx.x * RTILE + q * TB + threadIdx.x;
+    if (r >= nrows) break;
+    while (r >= end) end = R.first[++k + 1];
+    int64_t e0, len;
+    R.get(r, k, &e0, &len);
+    const uint64_t m = len <= seg ? 1 : (uint64_t)((len + seg - 1) / seg);
+    items += m;
+    parts += m > 1 ? m : 0;
+    cuts += m > 1;
+  }
+  uint64_t t1, t2;
+  block_excl(items | (cuts << 40), &t1);
+  block_excl(parts, &t2);
+  if (threadIdx.x == 0) {
+    cnt[blockIdx.x] = (int32_t)(t1 & 0xFFFFFFFFFFull);
+    cnt[tiles + blockIdx.x] = (int32_t)t2;
+    cnt[2 * tiles + blockIdx.x] = (int32_t)(t1 >> 40);
+  }
 }
 
-__global__ void k_item_permute(const uint64_t* __restrict__ keys, int64_t n, const int32_t* __restrict__ row,
-                               const int64_t* __restrict__ e0, const int32_t* __restrict__ len,
-                               const int32_t* __restrict__ part, int32_t* __restrict__ row_o,
-                               int64_t* __restrict__ e0_o, int32_t* __restrict__ len_o, int32_t* __restrict__ part_o) {
+// The items in row order, their dispatch keys, the cut rows, and where every chunk's share starts (starts[0 / 1 / 2][k]).
+// Dispatch order: chunk by chunk, inside a chunk by the first row an item reads (entries of a row are sorted by that
+// index), so items in flight together read neighbouring rows.  fbits: bits of the key left for that row; a wider index
+// is rounded down (the order is about locality only).
+__global__ void __launch_bounds__(TB) k_items_fill(RowSet R, int64_t nrows, int seg, int64_t tiles, const int64_t* __restrict__ base,
+                                                   const int32_t* __restrict__ idx, int fbits, int fshift,
+                                                   WorkItem* __restrict__ item, uint64_t* __restrict__ keys,
+                                                   CutRow* __restrict__ cut, int64_t* __restrict__ starts) {
+  int k = find_range(R.first, R.n, (int64_t)blockIdx.x * RTILE);
+  int64_t end = R.first[k + 1];
+  const int n1 = R.n + 1;
+  int64_t at_i = base[blockIdx.x], at_p = base[tiles + blockIdx.x] - base[tiles], at_c = base[2 * tiles + blockIdx.x] - base[2 * tiles];
+  for (int q = 0; q < RTILE / TB; ++q) {
+    const int64_t r = (int64_t)blockIdx.x * RTILE + q * TB + threadIdx.x;
+    int64_t e0 = 0, len = 0;
+    uint64_t m = 0;
+    if (r < nrows) {
+      while (r >= end) end = R.first[++k + 1];
+      R.get(r, k, &e0, &len);
+      m = len <= seg ? 1 : (uint64_t)((len + seg - 1) / seg);
+    }
+    const bool is_cut = m > 1;
+    uint64_t t1, t2;
+    const uint64_t x = block_excl(m | ((uint64_t)is_cut << 40), &t1);
+    const uint64_t y = block_excl(is_cut ? m : 0, &t2);
+    const int64_t i0 = at_i + (int64_t)(x & 0xFFFFFFFFFFull), p0 = at_p + (int64_t)y, c0 = at_c + (int64_t)(x >> 40);
+    if (r < nrows) {
+      for (int kk = k; kk >= 0 && R.first[kk] == r; --kk) {   // chunks that start at this row (empty ones before it too)
+        starts[kk] = i0;
+        starts[n1 + kk] = p0;
+        starts[2 * n1 + kk] = c0;
+      }
+      for (int64_t j = 0; j < (int64_t)m; ++j) {
+        const int64_t b = e0 + j * seg, rem = len - j * seg;
+        WorkItem w;
+        w.row = (int32_t)r;
+        w.e0 = (uint32_t)b;
+        w.len = (int32_t)(rem < seg ? rem : seg);
+        w.part = is_cut ? (int32_t)(p0 + j) : -1;
+        item[i0 + j] = w;
+        if (keys) {
+          const uint32_t f = w.len > 0 ? (uint32_t)idx[b] >> fshift : 0u;
+          keys[i0 + j] = ((((uint64_t)k << fbits) | f) << 32) | (uint64_t)(uint32_t)(i0 + j);
+        }
+      }
+      if (is_cut) {
+        CutRow c;
+        c.row = (int32_t)r;
+        c.part0 = (int32_t)p0;
+        c.nseg = (int32_t)m;
+        c.pad = 0;
+        cut[c0] = c;
+      }
+    }
+    at_i += (int64_t)(t1 & 0xFFFFFFFFFFull);
+    at_p += (int64_t)t2;
+    at_c += (int64_t)(t1 >> 40);
+  }
+}
+
+__global__ void k_items_permute(const uint64_t* __restrict__ keys, int64_t n, const WorkItem* __restrict__ in, WorkItem* __restrict__ out) {
   int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n) return;
-  const uint32_t from = (uint32_t)(keys[t] & 0xFFFFFFFFull);
-  row_o[t] = row[from];
-  e0_o[t] = e0[from];
-  len_o[t] = len[from];
-  part_o[t] = part[from];
+  if (t < n) out[t] = in[(uint32_t)(keys[t] & 0xFFFFFFFFull)];
 }
 
 int bits_for(int64_t n) {  // bits needed for values 0..n-1 (at least 1)
@@ -497,101 +812,24 @@ int bits_for(int64_t n) {  // bits needed for values 0..n-1 (at least 1)
   return b;
 }
 
-struct ItemTmp {
-  DevBlock blk;
-  DevArr<int32_t> nseg, npart, isfix;
-  DevArr<int64_t> it_base, part_base, fix_base;
-  DevArr<char> stage;   // items in row order, before they are permuted into dispatch order
-  int64_t* totals = nullptr;   // pinned host memory for the three counts of a build_items call (set by the caller)
-  // the graph's block for all work-item lists (set by the caller): a list takes the next bytes of it, or an
-  // allocation of its own when the block is full
-  char* arena = nullptr;
-  size_t arena_cap = 0, arena_off = 0;
-  int alloc(ht_ctx* ctx, int64_t maxrows) {
-    for (int k = 0; k < 3; ++k) blk.add<int32_t>(maxrows);
-    for (int k = 0; k < 3; ++k) blk.add<int64_t>(maxrows + 1);
-    HT_TRY(blk.alloc(ctx));
-    blk.take(nseg, maxrows);
-    blk.take(npart, maxrows);
-    blk.take(isfix, maxrows);
-    blk.take(it_base, maxrows + 1);
-    blk.take(part_base, maxrows + 1);
-    blk.take(fix_base, maxrows + 1);
-    return HT_OK;
-  }
+// One direction's work items for all chunks.  made / keysA / keysB: room for every item; starts: 3 (n + 1) words on the device.
+struct ItemBuild {
+  RowSet rows;
+  int64_t nrows = 0, tiles = 0, bound = 0;
+  int seg = 0;
+  int32_t* cnt = nullptr;
+  int64_t *base = nullptr, *starts = nullptr;
 };
 
-// ptr: device offsets of nrows+1 entries; ptr0: value to subtract so item edges are chunk-relative.
-// idx: the chunk's per-edge row index array (what the aggregation reads), idx_range: its value range.
-// keysA/keysB: scratch of at least n_items entries each.
-int build_items(ht_ctx* ctx, ItemTmp& t, const int64_t* ptr, int64_t ptr0, int64_t nrows, const int32_t* idx,
-                int64_t idx_range, uint64_t* keysA, uint64_t* keysB, bool order, int seg, ItemSet* out) {
-  out->n_items = out->n_part = out->n_fix = 0;
-  if (nrows == 0) return HT_OK;
-  hipStream_t st = ctx->stream;
-  k_items_count<<<nblk(nrows), TB, 0, st>>>(ptr, nrows, seg, t.nseg.p, t.npart.p, t.isfix.p);
+// Items a list of `rows` rows with `entries` entries can make: ceil(len / seg) per row, at least one.
+inline int64_t item_bound(int64_t rows, int64_t entries, int seg) { return rows + entries / seg + 1; }
+inline int64_t cut_bound(int64_t entries, int seg) { return entries / seg + 1; }
+
+int count_items(ht_ctx* ctx, ItemBuild& b) {
+  if (b.nrows == 0) return HT_OK;
+  k_items_count<<<(unsigned)b.tiles, TB, 0, ctx->stream>>>(b.rows, b.nrows, b.seg, b.tiles, b.cnt);
   HT_LAUNCH_CHECK(ctx);
-  HT_TRY(ht_scan_i32(ctx, t.nseg.p, t.it_base.p, nrows, true));
-  HT_TRY(ht_scan_i32(ctx, t.npart.p, t.part_base.p, nrows, true));
-  HT_TRY(ht_scan_i32(ctx, t.isfix.p, t.fix_base.p, nrows, true));
-  int64_t* tot = t.totals;   // pinned: the three copies are queued without a stall each
-  HT_HIP(ctx, hipMemcpyAsync(&tot[0], t.it_base.p + nrows, 8, hipMemcpyDeviceToHost, st));
-  HT_HIP(ctx, hipMemcpyAsync(&tot[1], t.part_base.p + nrows, 8, hipMemcpyDeviceToHost, st));
-  HT_HIP(ctx, hipMemcpyAsync(&tot[2], t.fix_base.p + nrows, 8, hipMemcpyDeviceToHost, st));
-  HT_HIP(ctx, hipStreamSynchronize(st));
-  out->n_items = tot[0];
-  out->n_part = tot[1];
-  out->n_fix = tot[2];
-  // one allocation: e0 (8 B) first, then the 4-byte arrays
-  const size_t ni = (size_t)tot[0], nf = (size_t)tot[2];
-  const size_t bytes = ni * 8 + ni * 4 * 3 + nf * 4 * 3;
-  if (t.arena && t.arena_off + DevBlock::pad(bytes) <= t.arena_cap) {
-    out->blob.release();
-    out->blob.ctx = ctx;
-    out->blob.owned = false;
-    out->blob.p = t.arena + t.arena_off;
-    out->blob.n = bytes;
-    t.arena_off += DevBlock::pad(bytes);
-  } else {
-    HT_TRY(out->blob.alloc(ctx, bytes));
-  }
-  struct Lay { int64_t* e0; int32_t *row, *len, *part, *fx_row, *fx_part0, *fx_nseg; };
-  auto carve = [&](char* p) {
-    Lay l;
-    l.e0 = (int64_t*)p; p += ni * 8;
-    l.row = (int32_t*)p; p += ni * 4;
-    l.len = (int32_t*)p; p += ni * 4;
-    l.part = (int32_t*)p; p += ni * 4;
-    l.fx_row = (int32_t*)p; p += nf * 4;
-    l.fx_part0 = (int32_t*)p; p += nf * 4;
-    l.fx_nseg = (int32_t*)p;
-    return l;
-  };
-  const Lay fin = carve(out->blob.p);
-  out->e0 = fin.e0; out->row = fin.row; out->len = fin.len; out->part = fin.part;
-  out->fx_row = fin.fx_row; out->fx_part0 = fin.fx_part0; out->fx_nseg = fin.fx_nseg;
-  const bool sorted_items = order && ni > 1;
-  // Items are made in row order; when they are to be dispatched in the order of the first row they read, they
-  // are made in a staging block that outlives the chunk (no allocation per chunk) and permuted into place.
-  Lay made = fin;
-  if (sorted_items) {
-    if (t.stage.n < bytes) HT_TRY(t.stage.alloc(ctx, bytes + bytes / 4));
-    made = carve(t.stage.p);
-    made.fx_row = fin.fx_row; made.fx_part0 = fin.fx_part0; made.fx_nseg = fin.fx_nseg;   // cut-row lists keep row order
-  }
-  k_items_fill<<<nblk(nrows), TB, 0, st>>>(ptr, ptr0, nrows, seg, t.it_base.p, t.part_base.p, t.fix_base.p, made.row,
-                                          made.e0, made.len, made.part, made.fx_row, made.fx_part0, made.fx_nseg);
-  HT_LAUNCH_CHECK(ctx);
-  if (sorted_items) {
-    k_item_keys<<<nblk((int64_t)ni), TB, 0, st>>>(made.e0, made.len, (int64_t)ni, idx, keysA);
-    HT_LAUNCH_CHECK(ctx);
-    uint64_t* sorted = nullptr;
-    HT_TRY(ht_radix_sort_u64(ctx, keysA, keysB, (int64_t)ni, 32, 32 + bits_for(idx_range), &sorted));
-    k_item_permute<<<nblk((int64_t)ni), TB, 0, st>>>(sorted, (int64_t)ni, made.row, made.e0, made.len, made.part, fin.row,
-                                                    fin.e0, fin.len, fin.part);
-    HT_LAUNCH_CHECK(ctx);
-  }
-  return HT_OK;
+  return ht_scan_i32(ctx, b.cnt, b.base, 3 * b.tiles, true);
 }
 
 int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, const int32_t* dst_in, int32_t n,
@@ -601,7 +839,7 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
   const int mode = opts ? opts->balance_mode : HT_BALANCE_EDGES;
   const int ptr_loc = opts ? opts->ptr_loc : HT_PTR_DEVICE;
   const int64_t Ep = E + (self_loops ? V : 0);
-  // the per-edge kernels take one thread per stored edge, and a launch holds fewer than 2^32 threads
+  // the per-edge kernels take one thread per stored edge, and a launch holds fewer than 2^32 threads; entry positions are 32-bit
   if (Ep >= ((int64_t)1 << 32) - 4096)
     return ht_set_err(ctx, HT_EINVAL, "ht_partition: %lld stored edges; fewer than 2^32 are supported", (long long)Ep);
   g->ctx = ctx;
@@ -609,14 +847,24 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
   g->Ep = Ep;
   g->n = n;
   g->add_self_loops = self_loops;
-  // pinned host memory for the small counts read back from the device: 8 words for the work-item counts,
-  // then three lists of n + 1 boundary values
-  int64_t* hpin = nullptr;
+  const size_t n1 = (size_t)n + 1;
+  const int bitsV = bits_for(V);
+  const int64_t nwp = bm_words(V), T = nwp / TB;   // words and tiles of a bitmap row
+  const int64_t etiles = ceil_div64(std::max<int64_t>(Ep, 1), ETILE);
+  int seg_fwd = HT_SEG, seg_bwd = HT_SEG / 2;   // measured best at cfg2; the variables are for experiments
+  if (const char* v = getenv("HT_SEG_FWD")) seg_fwd = std::max(64, atoi(v));
+  if (const char* v = getenv("HT_SEG_BWD")) seg_bwd = std::max(64, atoi(v));
+  const char* ord_env = getenv("HT_ITEM_ORDER");
+  const bool order_items = !(ord_env && atoi(ord_env) == 0);
+
+  // pinned host memory for what is read back (a flag and a few counts, then lists of n + 1 offsets) and for the chunk order
+  int64_t* hp = nullptr;
   {
-    void* hp = nullptr;
-    HT_TRY(ht_host_scratch(ctx, HT_HS_READBACK, (size_t)(8 + 3 * ((size_t)n + 1)) * 8, &hp));
-    hpin = (int64_t*)hp;
+    void* p = nullptr;
+    HT_TRY(ht_host_scratch(ctx, HT_HS_READBACK, (8 + 9 * n1) * 8, &p));
+    hp = (int64_t*)p;
   }
+  int64_t* hl = hp + 8;
 
   // ---- edge list on the device
   DevArr<int32_t> src_copy, dst_copy;
@@ -630,181 +878,140 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
     src = src_copy.p;
     dst = dst_copy.p;
   }
-  if (E > 0) {
-    DevArr<int32_t> flag;
-    HT_TRY(flag.alloc(ctx, 1));
-    HT_HIP(ctx, hipMemsetAsync(flag.p, 0, 4, st));
-    k_check_ids<<<nblk(E), TB, 0, st>>>(src, dst, E, V, flag.p);
-    HT_LAUNCH_CHECK(ctx);
-    int32_t bad = 0;
-    HT_HIP(ctx, hipMemcpyAsync(&bad, flag.p, 4, hipMemcpyDeviceToHost, st));
-    HT_HIP(ctx, hipStreamSynchronize(st));
-    if (bad) return ht_set_err(ctx, HT_EINVAL, "ht_partition: a vertex id is outside [0, V)");
-  }
 
-  // ---- CSC by (destination, source)
-  const int bitsV = bits_for(V);
-  DevArr<uint64_t> keysA, keysB;
-  const size_t nkeys = (size_t)std::max<int64_t>(std::max(Ep, V), 1) + 64;  // also holds one key per work item
-  HT_TRY(keysA.alloc(ctx, nkeys));
-  HT_TRY(keysB.alloc(ctx, nkeys));
-  HT_TRY(g->indptr.alloc(ctx, (size_t)V + 1));
-  HT_TRY(g->col.alloc(ctx, (size_t)(Ep > 0 ? Ep : 1)));
-  HT_TRY(g->s.alloc(ctx, (size_t)V));
-  HT_HIP(ctx, hipMemsetAsync(g->indptr.p, 0, (V + 1) * 8, st));
-  if (Ep > 0) {
-    k_pack_keys<<<nblk(Ep), TB, 0, st>>>(src, dst, E, V, bitsV, self_loops, keysA.p);
-    HT_LAUNCH_CHECK(ctx);
-    uint64_t* sorted = nullptr;
-    HT_TRY(ht_radix_sort_u64(ctx, keysA.p, keysB.p, Ep, 0, 2 * bitsV, &sorted));
-    k_low_bits<<<nblk(Ep), TB, 0, st>>>(sorted, Ep, ((uint64_t)1 << bitsV) - 1, g->col.p);
-    HT_LAUNCH_CHECK(ctx);
-    k_boundaries<<<nblk(Ep), TB, 0, st>>>(sorted, Ep, bitsV, V, g->indptr.p);
-    HT_LAUNCH_CHECK(ctx);
+  // ---- temporaries of the whole call, one allocation
+  const int64_t grp = mark_group(nwp, n);
+  const size_t nkeys = (size_t)std::max<int64_t>(std::max(Ep, item_bound(V, Ep, std::min(seg_fwd, seg_bwd))), 1) + 64;
+  DevBlock tmp;
+  DevArr<uint64_t> keysA, keysB, allbm;
+  DevArr<int32_t> ucount, tile_cnt, list_cnt, d_order;
+  DevArr<int64_t> ubase, tbase, lbase, lists;   // lists: see L_* below
+  DevArr<uint8_t> seen;
+  DevArr<uint32_t> wpref;
+  enum { L_FLAG, L_BOUNDS, L_EOFF, L_UEOFF, L_NOFF, L_REUSE, L_LOAD, L_LEAVE, L_COUNT };
+  tmp.add<uint64_t>(nkeys);
+  tmp.add<uint64_t>(nkeys);
+  tmp.add<uint64_t>((size_t)n * nwp);
+  tmp.add<int32_t>((size_t)etiles);
+  tmp.add<int32_t>((size_t)n * T);
+  tmp.add<int32_t>((size_t)3 * n * T);
+  tmp.add<int32_t>((size_t)n);
+  tmp.add<int64_t>((size_t)etiles + 1);
+  tmp.add<int64_t>((size_t)n * T + 1);
+  tmp.add<int64_t>((size_t)3 * n * T + 1);
+  tmp.add<int64_t>(n1 * L_COUNT);
+  tmp.add<uint8_t>((size_t)grp * nwp * 64);
+  tmp.add<uint32_t>((size_t)n * nwp);
+  HT_TRY(tmp.alloc(ctx));
+  tmp.take(keysA, nkeys);
+  tmp.take(keysB, nkeys);
+  tmp.take(allbm, (size_t)n * nwp);
+  tmp.take(ucount, (size_t)etiles);
+  tmp.take(tile_cnt, (size_t)n * T);
+  tmp.take(list_cnt, (size_t)3 * n * T);
+  tmp.take(d_order, (size_t)n);
+  tmp.take(ubase, (size_t)etiles + 1);
+  tmp.take(tbase, (size_t)n * T + 1);
+  tmp.take(lbase, (size_t)3 * n * T + 1);
+  tmp.take(lists, n1 * L_COUNT);
+  tmp.take(seen, (size_t)grp * nwp * 64);
+  tmp.take(wpref, (size_t)n * nwp);
+  auto list = [&](int which) { return lists.p + (size_t)which * n1; };
+  HT_TRY(ht_fill_zero(ctx, st, list(L_FLAG), 8));
+  HT_TRY(ht_fill_zero(ctx, st, seen.p, seen.bytes()));
+
+  // ---- CSC by (destination, source), chunk boundaries
+  {
+    DevBlock& b = g->blk_csc;
+    b.add<int64_t>((size_t)V + 1);
+    b.add<int32_t>((size_t)std::max<int64_t>(Ep, 1));
+    b.add<float>((size_t)V);
+    HT_TRY(b.alloc(ctx));
+    b.take(g->indptr, (size_t)V + 1);
+    b.take(g->col, (size_t)std::max<int64_t>(Ep, 1));
+    b.take(g->s, (size_t)V);
   }
+  uint64_t* csc = keysA.p;
+  if (Ep > 0) {
+    k_pack_keys<<<nblk(Ep), TB, 0, st>>>(src, dst, E, V, bitsV, self_loops, keysA.p, list(L_FLAG));
+    HT_LAUNCH_CHECK(ctx);
+    HT_TRY(ht_radix_sort_u64(ctx, keysA.p, keysB.p, Ep, 0, 2 * bitsV, &csc));
+    k_csc<<<(unsigned)etiles, TB, 0, st>>>(csc, Ep, bitsV, V, g->col.p, g->indptr.p, ucount.p);
+    HT_LAUNCH_CHECK(ctx);
+    HT_TRY(ht_scan_i32(ctx, ucount.p, ubase.p, etiles, true));
+  } else {
+    HT_TRY(ht_fill_zero(ctx, st, g->indptr.p, (size_t)(V + 1) * 8));
+    HT_TRY(ht_fill_zero(ctx, st, ubase.p, (size_t)(etiles + 1) * 8));
+  }
+  uint64_t* other = csc == keysA.p ? keysB.p : keysA.p;
   k_norm<<<nblk(V), TB, 0, st>>>(g->indptr.p, V, g->s.p);
   HT_LAUNCH_CHECK(ctx);
+  k_bounds<<<nblk(n + 1), TB, 0, st>>>(g->indptr.p, V, Ep, n, mode, list(L_BOUNDS), list(L_EOFF));
+  HT_LAUNCH_CHECK(ctx);
+  HT_HIP(ctx, hipMemcpyAsync(&hp[0], list(L_FLAG), 8, hipMemcpyDeviceToHost, st));
+  HT_HIP(ctx, hipMemcpyAsync(&hp[1], ubase.p + etiles, 8, hipMemcpyDeviceToHost, st));
+  HT_HIP(ctx, hipMemcpyAsync(hl, list(L_BOUNDS), 2 * n1 * 8, hipMemcpyDeviceToHost, st));
+  HT_HIP(ctx, hipStreamSynchronize(st));
+  if (hp[0]) return ht_set_err(ctx, HT_EINVAL, "ht_partition: a vertex id is outside [0, V)");
   src_copy.release();
   dst_copy.release();
+  g->bounds.assign(hl, hl + n1);
+  const std::vector<int64_t> eoff(hl + n1, hl + 2 * n1);
+  const int64_t nU = hp[1];
 
-  // ---- duplicate edges: count the distinct (destination, source) pairs; merge when it pays
+  // ---- duplicate edges: one entry per distinct (destination, source) pair when that pays.  Merged arrays cost 16 B per
+  // distinct pair: worth it from about 5 % duplicates.
   const char* mg_env = getenv("HT_MERGE_DUPS");
-  const bool merge_allowed = !(mg_env && atoi(mg_env) == 0);
-  // flags and their ranks live in the two key buffers, which are idle between the sort above and the per-chunk
-  // sorts below (releasing 12 bytes per edge of separate arrays took 49 ms on a 1.3 G-edge graph)
-  struct { int32_t* p; } dflag{(int32_t*)keysA.p};
-  struct { int64_t* p; } drank{(int64_t*)keysB.p};
-  DevArr<int64_t> upos;
-  int64_t nU = Ep;
-  g->merged = false;
-  if (merge_allowed && Ep > 0) {
-    k_dup_flags_u32<<<nblk(Ep), TB, 0, st>>>(g->col.p, Ep, dflag.p);
+  DevArr<uint32_t> upos;
+  g->merged = !(mg_env && atoi(mg_env) == 0) && Ep > 0 && (double)nU <= 0.95 * (double)Ep;
+  if (g->merged) {
+    g->n_unique = nU;
+    HT_TRY(upos.alloc(ctx, (size_t)nU + 1));
+    DevBlock& b = g->blk_pairs;
+    b.add<int64_t>((size_t)V + 1);
+    for (int k = 0; k < 7; ++k) b.add<int32_t>((size_t)nU);
+    HT_TRY(b.alloc(ctx));
+    b.take(g->uindptr, (size_t)V + 1);
+    b.take(g->ucol, (size_t)nU);
+    b.take(g->ucol_slot, (size_t)nU);
+    b.take(g->uw_fwd, (size_t)nU);
+    b.take(g->umult, (size_t)nU);
+    b.take(g->usdst, (size_t)nU);
+    b.take(g->uw_bwd, (size_t)nU);
+    b.take(g->umult_bwd, (size_t)nU);
+    k_runs_fwd<<<(unsigned)etiles, TB, 0, st>>>(csc, Ep, bitsV, V, ubase.p, nU, upos.p, g->uindptr.p);
     HT_LAUNCH_CHECK(ctx);
-    k_row_start_flags<<<nblk(V), TB, 0, st>>>(g->indptr.p, V, Ep, dflag.p);
+    k_merge_fwd<<<nblk(nU), TB, 0, st>>>(upos.p, nU, g->col.p, g->s.p, g->ucol.p, g->uw_fwd.p, g->umult.p);
     HT_LAUNCH_CHECK(ctx);
-    HT_TRY(ht_scan_i32(ctx, dflag.p, drank.p, Ep, true));
-    HT_HIP(ctx, hipMemcpyAsync(&nU, drank.p + Ep, 8, hipMemcpyDeviceToHost, st));
-    HT_HIP(ctx, hipStreamSynchronize(st));
-    // merged arrays cost 16 B per distinct pair: worth it from about 5 % duplicates
-    if ((double)nU <= 0.95 * (double)Ep) {
-      g->merged = true;
-      g->n_unique = nU;
-      HT_TRY(upos.alloc(ctx, (size_t)nU + 1));
-      {
-        DevBlock& b = g->blk_pairs;
-        b.add<int64_t>((size_t)V + 1);
-        for (int k = 0; k < 7; ++k) b.add<int32_t>((size_t)nU);
-        HT_TRY(b.alloc(ctx));
-        b.take(g->uindptr, (size_t)V + 1);
-        b.take(g->ucol, (size_t)nU);
-        b.take(g->ucol_slot, (size_t)nU);
-        b.take(g->uw_fwd, (size_t)nU);
-        b.take(g->umult, (size_t)nU);
-        b.take(g->usdst, (size_t)nU);
-        b.take(g->uw_bwd, (size_t)nU);
-        b.take(g->umult_bwd, (size_t)nU);
-      }
-      k_flag_positions<<<nblk(Ep), TB, 0, st>>>(dflag.p, drank.p, Ep, upos.p);
-      HT_LAUNCH_CHECK(ctx);
-      k_set_i64<<<1, 1, 0, st>>>(upos.p + nU, Ep);
-      HT_LAUNCH_CHECK(ctx);
-      k_merge_fwd<<<nblk(nU), TB, 0, st>>>(upos.p, nU, g->col.p, g->s.p, g->ucol.p, g->uw_fwd.p, g->umult.p);
-      HT_LAUNCH_CHECK(ctx);
-      k_uindptr<<<nblk(V + 1), TB, 0, st>>>(g->indptr.p, drank.p, V, Ep, nU, g->uindptr.p);
-      HT_LAUNCH_CHECK(ctx);
-      HT_HIP(ctx, hipStreamSynchronize(st));
-    }
+    k_gather_i64<<<nblk((int64_t)n1), TB, 0, st>>>(g->uindptr.p, list(L_BOUNDS), (int64_t)n1, list(L_UEOFF));
+    HT_LAUNCH_CHECK(ctx);
   }
 
-  // ---- chunk boundaries
-  g->bounds.assign(n + 1, 0);
-  g->bounds[n] = V;
-  if (mode == HT_BALANCE_VERTICES) {
-    for (int j = 1; j < n; ++j) g->bounds[j] = (int64_t)(((__int128)j * V) / n);
-  } else if (n > 1) {
-    std::vector<int64_t> target(n - 1);
-    for (int j = 1; j < n; ++j) target[j - 1] = (int64_t)((((__int128)j * Ep) + n - 1) / n);
-    DevArr<int64_t> dt, db;
-    HT_TRY(dt.alloc(ctx, n - 1));
-    HT_TRY(db.alloc(ctx, n - 1));
-    HT_HIP(ctx, hipMemcpyAsync(dt.p, target.data(), (n - 1) * 8, hipMemcpyHostToDevice, st));
-    k_bounds<<<nblk(n - 1), TB, 0, st>>>(g->indptr.p, V, dt.p, n - 1, db.p);
-    HT_LAUNCH_CHECK(ctx);
-    HT_HIP(ctx, hipMemcpyAsync(&g->bounds[1], db.p, (n - 1) * 8, hipMemcpyDeviceToHost, st));
-    HT_HIP(ctx, hipStreamSynchronize(st));
-  }
-  // edge offsets of the chunk boundaries, in both edge spaces: one gather, one copy back
-  std::vector<int64_t> eoff(n + 1), ueoff(n + 1, 0);
-  {
-    const size_t nb1 = (size_t)n + 1;
-    DevArr<int64_t> dq;
-    HT_TRY(dq.alloc(ctx, 3 * nb1));
-    int64_t* hb = hpin + 8;
-    std::copy(g->bounds.begin(), g->bounds.end(), hb);
-    HT_HIP(ctx, hipMemcpyAsync(dq.p, hb, nb1 * 8, hipMemcpyHostToDevice, st));
-    k_gather_offsets<<<nblk((int64_t)nb1), TB, 0, st>>>(g->indptr.p, g->merged ? g->uindptr.p : nullptr, dq.p, (int64_t)nb1,
-                                                       dq.p + nb1, dq.p + 2 * nb1);
-    HT_LAUNCH_CHECK(ctx);
-    HT_HIP(ctx, hipMemcpyAsync(hb + nb1, dq.p + nb1, 2 * nb1 * 8, hipMemcpyDeviceToHost, st));
-    HT_HIP(ctx, hipStreamSynchronize(st));
-    std::copy(hb + nb1, hb + 2 * nb1, eoff.begin());
-    if (g->merged) std::copy(hb + 2 * nb1, hb + 3 * nb1, ueoff.begin());
-  }
-  g->chunks.clear();
-  g->chunks.resize(n);
-  for (int j = 0; j < n; ++j) {
-    ChunkMeta& c = g->chunks[j];
-    c.dst0 = g->bounds[j];
-    c.dst1 = g->bounds[j + 1];
-    c.e0 = eoff[j];
-    c.nnz = eoff[j + 1] - eoff[j];
-    c.ue0 = g->merged ? ueoff[j] : c.e0;
-    c.nu = g->merged ? ueoff[j + 1] - ueoff[j] : c.nnz;
-    g->max_ndst = std::max(g->max_ndst, c.dst1 - c.dst0);
-    g->max_nnz = std::max(g->max_nnz, c.nnz);
-  }
+  // ---- neighbour sets of all chunks as bitmaps (bit u of row k: u is in N_k; k = chunk id in vertex order)
+  HT_TRY(mark_chunks(ctx, st, g->col.p, eoff.data(), list(L_EOFF), n, nwp, seen.p, allbm.p, tile_cnt.p));
+  HT_TRY(ht_scan_i32(ctx, tile_cnt.p, tbase.p, (int64_t)n * T, true));
+  k_gather_stride<<<nblk((int64_t)n1), TB, 0, st>>>(tbase.p, T, (int64_t)n1, list(L_NOFF));
+  HT_LAUNCH_CHECK(ctx);
 
   // a buffer with room for every distinct source is the schedule-aware buffer at that size
   const bool keep_all = opts && opts->cache_rows == -1;
   const bool far_first = (opts && opts->cache_policy == HT_CACHE_FARTHEST) || keep_all;
-  const int64_t nw = ceil_div64(V, 64);
 
   // ---- chunk reorganisation (Alg. 4, phase 2; one GPU, so a batch is one chunk): the first chunk
   // stays first, then the unplaced chunk whose neighbour set overlaps most with the chunk placed last
-  // comes next (ties: smallest id).  All n neighbour bitmaps are kept for the n-1 greedy steps.
+  // comes next (ties: smallest id).
   g->order.resize(n);
   for (int j = 0; j < n; ++j) g->order[j] = j;
-  // The chunks' neighbour bitmaps (bit u of row j: u is in N_j) are needed by the reorganisation, the counting
-  // pass, the buffer simulation and the list pass.  When all n of them fit a modest share of the free memory
-  // they are marked once and kept, row = original chunk id; otherwise each use marks its own again.
-  DevArr<uint8_t> seen;   // one byte per vertex, zero between two uses
-  HT_TRY(seen.alloc(ctx, (size_t)nw * 64));
-  HT_HIP(ctx, hipMemsetAsync(seen.p, 0, (size_t)nw * 64, st));
-  auto mark_chunk = [&](const ChunkMeta& c, uint64_t* bm) -> int {
-    return mark_sources(ctx, st, g->col.p + c.e0, c.nnz, seen.p, nw, bm);
-  };
-  DevArr<uint64_t> allbm;
-  {
-    const size_t need = (size_t)n * (size_t)nw * 8;
-    size_t free_b = 0, total_b = 0;
-    HT_HIP(ctx, hipMemGetInfo(&free_b, &total_b));
-    const bool want_reorder = opts && opts->reorder_chunks && n > 2;
-    if (want_reorder || (need <= ((size_t)2 << 30) && need <= free_b / 16)) {
-      HT_TRY(allbm.alloc(ctx, (size_t)n * nw));
-      for (int j = 0; j < n; ++j) HT_TRY(mark_chunk(g->chunks[j], allbm.p + (size_t)j * nw));
-    }
-  }
   if (opts && opts->reorder_chunks && n > 2) {
-    uint64_t* bms = allbm.p;
     DevArr<unsigned long long> ov;
     HT_TRY(ov.alloc(ctx, n));
     std::vector<unsigned long long> hov(n);
     std::vector<char> placed(n, 0);
     placed[0] = 1;
-    const unsigned gx = (unsigned)std::min<int64_t>(ceil_div64(nw, TB), 64);
+    const unsigned gx = (unsigned)std::min<int64_t>(T, 64);
     for (int j = 1; j < n; ++j) {
-      HT_HIP(ctx, hipMemsetAsync(ov.p, 0, (size_t)n * 8, st));
-      k_overlap<<<dim3(gx, n), TB, 0, st>>>(bms, nw, bms + (size_t)g->order[j - 1] * nw, ov.p);
+      HT_TRY(ht_fill_zero(ctx, st, ov.p, (size_t)n * 8));
+      k_overlap<<<dim3(gx, n), TB, 0, st>>>(allbm.p, nwp, allbm.p + (size_t)g->order[j - 1] * nwp, ov.p);
       HT_LAUNCH_CHECK(ctx);
       HT_HIP(ctx, hipMemcpyAsync(hov.data(), ov.p, (size_t)n * 8, hipMemcpyDeviceToHost, st));
       HT_HIP(ctx, hipStreamSynchronize(st));
@@ -814,61 +1021,66 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
       g->order[j] = best;
       placed[best] = 1;
     }
-    std::vector<ChunkMeta> sorted_chunks(n);
-    for (int j = 0; j < n; ++j) sorted_chunks[j] = std::move(g->chunks[g->order[j]]);
-    g->chunks = std::move(sorted_chunks);
   }
-  // bitmap of the chunk at schedule position j: the kept one, or marked afresh into `scratch`
-  auto chunk_bm = [&](int j, uint64_t* scratch, uint64_t** out) -> int {
-    if (allbm.p) {
-      *out = allbm.p + (size_t)g->order[j] * nw;
-      return HT_OK;
+  std::copy(g->order.begin(), g->order.end(), (int32_t*)(hl + 8 * n1));
+  HT_HIP(ctx, hipMemcpyAsync(d_order.p, hl + 8 * n1, (size_t)n * 4, hipMemcpyHostToDevice, st));
+
+  // ---- reuse / load / leave lists: counted here for the adjacent rule; the schedule-aware buffer is simulated first
+  ListRows rows{allbm.p, d_order.p, nullptr, nullptr, nwp, n};
+  auto count_lists = [&]() -> int {
+    k_list_counts<<<(unsigned)(n * T), TB, 0, st>>>(rows, T, list_cnt.p);
+    HT_LAUNCH_CHECK(ctx);
+    HT_TRY(ht_scan_i32(ctx, list_cnt.p, lbase.p, (int64_t)3 * n * T, true));
+    for (int w = 0; w < 3; ++w) {
+      k_gather_stride<<<nblk((int64_t)n1), TB, 0, st>>>(lbase.p + (int64_t)w * n * T, T, (int64_t)n1, list(L_REUSE + w));
+      HT_LAUNCH_CHECK(ctx);
     }
-    HT_TRY(mark_chunk(g->chunks[j], scratch));
-    *out = scratch;
     return HT_OK;
   };
-
-  // ---- pass 1: |N_j|, |N_j ^ N_{j-1}| and |N_j ^ (N_0 u ... u N_{j-1})| for every chunk, in schedule order
-  DevBlock tmp1;
-  DevArr<uint64_t> bmA, bmB, bmT, bmR;
-  DevArr<unsigned long long> totals;
-  for (int k = 0; k < 4; ++k) tmp1.add<uint64_t>(nw);
-  tmp1.add<unsigned long long>((size_t)3 * n);
-  HT_TRY(tmp1.alloc(ctx));
-  tmp1.take(bmA, nw);
-  tmp1.take(bmB, nw);
-  tmp1.take(bmT, nw);
-  tmp1.take(bmR, nw);
-  tmp1.take(totals, (size_t)3 * n);
-  HT_HIP(ctx, hipMemsetAsync(totals.p, 0, (size_t)3 * n * 8, st));
-  uint64_t* cur = nullptr;
-  uint64_t* prev = bmB.p;   // the previous chunk's set (none before the first chunk)
-  HT_HIP(ctx, hipMemsetAsync(prev, 0, nw * 8, st));
-  HT_HIP(ctx, hipMemsetAsync(bmR.p, 0, nw * 8, st));
-  for (int j = 0; j < n; ++j) {
-    HT_TRY(chunk_bm(j, (j & 1) ? bmB.p : bmA.p, &cur));
-    k_popc3<<<popc_grid(nw), TB, 0, st>>>(cur, prev, bmR.p, nw, totals.p + 3 * j);
+  DevArr<unsigned long long> distinct;
+  if (far_first) {
+    HT_TRY(distinct.alloc(ctx, 1));
+    HT_TRY(ht_fill_zero(ctx, st, distinct.p, 8));
+    k_popc_all<<<popc_grid(nwp), TB, 0, st>>>(allbm.p, nwp, n, distinct.p);
     HT_LAUNCH_CHECK(ctx);
-    k_bm_or<<<nblk(nw), TB, 0, st>>>(bmR.p, cur, nw);
-    HT_LAUNCH_CHECK(ctx);
-    prev = cur;
+    HT_HIP(ctx, hipMemcpyAsync(&hp[2], distinct.p, 8, hipMemcpyDeviceToHost, st));
   }
-  std::vector<unsigned long long> htot(3 * n);
-  HT_HIP(ctx, hipMemcpyAsync(htot.data(), totals.p, (size_t)3 * n * 8, hipMemcpyDeviceToHost, st));
+  // (the adjacent rule's loads are also V_+ru, which every schedule reports)
+  HT_TRY(count_lists());
+  HT_HIP(ctx, hipMemcpyAsync(hl, list(L_UEOFF), (size_t)(L_COUNT - L_UEOFF) * n1 * 8, hipMemcpyDeviceToHost, st));
   HT_HIP(ctx, hipStreamSynchronize(st));
-  g->v_ori = g->v_ru = g->v_load = 0;
+  const std::vector<int64_t> ueoff(hl, hl + n1), noff(hl + n1, hl + 2 * n1);
+  std::vector<int64_t> offs[3];   // starts of every schedule position's reuse / load / leave list
+  auto take_offsets = [&](const int64_t* h) {
+    for (int w = 0; w < 3; ++w) {
+      offs[w].assign(h + (size_t)w * n1, h + (size_t)(w + 1) * n1);
+      const int64_t b0 = offs[w][0];
+      for (int64_t& x : offs[w]) x -= b0;
+    }
+  };
+  take_offsets(hl + (size_t)(L_REUSE - L_UEOFF) * n1);
+  g->v_ori = noff[n];
+  g->v_ru = offs[1][n];
+  g->chunks.clear();
+  g->chunks.resize(n);
   for (int j = 0; j < n; ++j) {
     ChunkMeta& c = g->chunks[j];
-    c.nsrc = (int64_t)htot[3 * j];
-    c.nbr_off = g->v_ori;
-    c.sptr_off = g->v_ori + j;
-    g->v_ori += c.nsrc;
-    g->v_ru += c.nsrc - (int64_t)htot[3 * j + 1];   // adjacent-chunk reuse only, as in Sec. 5.3
+    const int k = g->order[j];
+    c.id = k;
+    c.dst0 = g->bounds[k];
+    c.dst1 = g->bounds[k + 1];
+    c.e0 = eoff[k];
+    c.nnz = eoff[k + 1] - eoff[k];
+    c.ue0 = g->merged ? ueoff[k] : c.e0;
+    c.nu = g->merged ? ueoff[k + 1] - ueoff[k] : c.nnz;
+    c.nbr_off = noff[k];
+    c.nsrc = noff[k + 1] - noff[k];
+    c.sptr_off = noff[k] + k;
+    g->max_ndst = std::max(g->max_ndst, c.dst1 - c.dst0);
+    g->max_nnz = std::max(g->max_nnz, c.nnz);
     g->max_nsrc = std::max(g->max_nsrc, c.nsrc);
   }
-  int64_t n_distinct = 0;      // |N_0 u ... u N_{n-1}|
-  for (int j = 0; j < n; ++j) n_distinct += g->chunks[j].nsrc - (int64_t)htot[3 * j + 2];
+  const int64_t n_distinct = far_first ? hp[2] : 0;   // |N_0 u ... u N_{n-1}|
   int64_t C = opts ? opts->cache_rows : 0;
   if (keep_all) C = n_distinct;
   if (C <= 0) C = g->max_nsrc;
@@ -877,74 +1089,65 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
                       (long long)g->max_nsrc);
   const size_t vo = (size_t)std::max<int64_t>(g->v_ori, 1);
   HT_TRY(g->nbr.alloc(ctx, vo));
+  k_expand_rows<<<(unsigned)(n * T), TB, 0, st>>>(allbm.p, nwp, tbase.p, wpref.p, g->nbr.p);
+  HT_LAUNCH_CHECK(ctx);
 
-  // ---- schedule of the buffer.  Adjacent reuse follows from the counts above; the schedule-aware
-  // buffer (a row leaves after its last use, or for room with the farthest next use first) is
-  // simulated chunk by chunk on bitmaps: the rows released before chunk j (= leaving after chunk
-  // j-1) are kept as one bitmap per chunk for pass 2.
-  std::vector<int64_t> n_reuse(n), n_leave(n, 0);
-  DevArr<uint64_t> Ebm;      // [n x nw], row j: rows released before chunk j
-  if (!far_first) {
-    for (int j = 0; j < n; ++j) n_reuse[j] = (int64_t)htot[3 * j + 1];
-  } else {
-    DevArr<int32_t> nxt, last, nu;
+  // ---- schedule of a buffer that knows the future: a row leaves after its last use, or for room with the farthest next
+  // use first.  Simulated chunk by chunk on bitmaps; kept for the lists: the rows resident before every chunk (Pbm), the
+  // rows released before it (Ebm row j; row n: what is still resident at the end).
+  DevArr<uint64_t> Pbm, Ebm;
+  if (far_first) {
+    DevBlock fb;
+    DevArr<int32_t> nxt, last, nu, cnt1;
     DevArr<unsigned int> hist;
-    DevArr<unsigned long long> tot2, dead_cnt;
-    DevArr<int32_t> cnt1;
+    DevArr<unsigned long long> tot2;
     DevArr<int64_t> pref1;
-    DevArr<uint64_t> eqbm;
-    HT_TRY(nxt.alloc(ctx, vo));
-    HT_TRY(last.alloc(ctx, (size_t)V));
-    HT_TRY(nu.alloc(ctx, (size_t)V));
-    HT_TRY(hist.alloc(ctx, (size_t)n + 1));
-    HT_TRY(tot2.alloc(ctx, 2));
-    HT_TRY(dead_cnt.alloc(ctx, (size_t)n));
-    HT_HIP(ctx, hipMemsetAsync(dead_cnt.p, 0, (size_t)n * 8, st));
-    HT_TRY(cnt1.alloc(ctx, nw));
-    HT_TRY(pref1.alloc(ctx, nw + 1));
-    HT_TRY(eqbm.alloc(ctx, nw));
-    HT_TRY(Ebm.alloc(ctx, (size_t)n * nw));
-    HT_HIP(ctx, hipMemsetAsync(Ebm.p, 0, (size_t)n * nw * 8, st));
-    {
-      std::vector<int32_t> init((size_t)V, n);
-      HT_HIP(ctx, hipMemcpyAsync(last.p, init.data(), (size_t)V * 4, hipMemcpyHostToDevice, st));
-      HT_HIP(ctx, hipMemcpyAsync(nu.p, init.data(), (size_t)V * 4, hipMemcpyHostToDevice, st));
-      HT_HIP(ctx, hipStreamSynchronize(st));
-    }
-    // N_j lists and next uses, last chunk first
-    uint64_t* bmj = nullptr;   // N_j as a bitmap
+    DevArr<uint64_t> eqbm, bmT, bmR;
+    fb.add<int32_t>(vo); fb.add<int32_t>((size_t)V); fb.add<int32_t>((size_t)V); fb.add<int32_t>((size_t)nwp);
+    fb.add<unsigned int>(n1); fb.add<unsigned long long>((size_t)n + 2); fb.add<int64_t>((size_t)nwp + 1);
+    for (int k = 0; k < 3; ++k) fb.add<uint64_t>((size_t)nwp);
+    HT_TRY(fb.alloc(ctx));
+    fb.take(nxt, vo); fb.take(last, (size_t)V); fb.take(nu, (size_t)V); fb.take(cnt1, (size_t)nwp);
+    fb.take(hist, n1); fb.take(tot2, (size_t)n + 2); fb.take(pref1, (size_t)nwp + 1);
+    fb.take(eqbm, (size_t)nwp); fb.take(bmT, (size_t)nwp); fb.take(bmR, (size_t)nwp);
+    unsigned long long* dead_cnt = tot2.p + 2;
+    HT_TRY(Pbm.alloc(ctx, (size_t)n * nwp));
+    HT_TRY(Ebm.alloc(ctx, n1 * (size_t)nwp));
+    HT_TRY(ht_fill_zero(ctx, st, dead_cnt, (size_t)n * 8));
+    HT_TRY(ht_fill_zero(ctx, st, Ebm.p, Ebm.bytes()));
+    HT_TRY(ht_fill_zero(ctx, st, bmR.p, bmR.bytes()));
+    k_fill_i32<<<nblk(V), TB, 0, st>>>(last.p, V, n);
+    HT_LAUNCH_CHECK(ctx);
+    k_fill_i32<<<nblk(V), TB, 0, st>>>(nu.p, V, n);
+    HT_LAUNCH_CHECK(ctx);
+    // next uses, last chunk first
     for (int j = n - 1; j >= 0; --j) {
       const ChunkMeta& c = g->chunks[j];
-      HT_TRY(chunk_bm(j, bmA.p, &bmj));
-      HT_TRY(ht_bitmap_prefix(ctx, bmj, nw, cnt1.p, pref1.p));
-      HT_TRY(ht_bitmap_expand(ctx, bmj, nw, pref1.p, g->nbr.p + c.nbr_off));
       if (c.nsrc > 0) {
         k_next_use<<<nblk(c.nsrc), TB, 0, st>>>(g->nbr.p + c.nbr_off, c.nsrc, last.p, j, nxt.p + c.nbr_off);
         HT_LAUNCH_CHECK(ctx);
       }
     }
     // forward simulation: bmR = resident rows
-    HT_HIP(ctx, hipMemsetAsync(bmR.p, 0, nw * 8, st));
-    std::vector<unsigned int> hh((size_t)n + 1);
+    std::vector<unsigned int> hh(n1);
     for (int j = 0; j < n; ++j) {
       const ChunkMeta& c = g->chunks[j];
-      HT_TRY(chunk_bm(j, bmA.p, &bmj));
-      HT_HIP(ctx, hipMemsetAsync(tot2.p, 0, 16, st));
-      k_popc_union<<<popc_grid(nw), TB, 0, st>>>(bmR.p, bmj, nw, tot2.p);
+      const uint64_t* bmj = allbm.p + (size_t)c.id * nwp;   // N_j
+      HT_TRY(ht_fill_zero(ctx, st, tot2.p, 16));
+      k_popc_union<<<popc_grid(nwp), TB, 0, st>>>(bmR.p, bmj, nwp, tot2.p);
       HT_LAUNCH_CHECK(ctx);
       unsigned long long t2[2];
       HT_HIP(ctx, hipMemcpyAsync(t2, tot2.p, 16, hipMemcpyDeviceToHost, st));
       HT_HIP(ctx, hipStreamSynchronize(st));
-      n_reuse[j] = (int64_t)t2[1];
       const int64_t over = (int64_t)t2[0] - C;
       if (over > 0) {
-        uint64_t* E = Ebm.p + (size_t)j * nw;
-        k_bm_op<<<nblk(nw), TB, 0, st>>>(bmR.p, bmj, nw, 1, bmT.p);   // candidates: resident, not needed now
+        uint64_t* Ej = Ebm.p + (size_t)j * nwp;
+        k_bm_minus<<<nblk(nwp), TB, 0, st>>>(bmR.p, bmj, nwp, bmT.p);   // candidates: resident, not needed now
         HT_LAUNCH_CHECK(ctx);
-        HT_HIP(ctx, hipMemsetAsync(hist.p, 0, ((size_t)n + 1) * 4, st));
-        k_hist_nu<<<(unsigned)std::min<int64_t>(nblk(nw), 2048), TB, 0, st>>>(bmT.p, nw, nu.p, n + 1, hist.p);
+        HT_TRY(ht_fill_zero(ctx, st, hist.p, n1 * 4));
+        k_hist_nu<<<(unsigned)std::min<int64_t>(nblk(nwp), 2048), TB, 0, st>>>(bmT.p, nwp, nu.p, n + 1, hist.p);
         HT_LAUNCH_CHECK(ctx);
-        HT_HIP(ctx, hipMemcpyAsync(hh.data(), hist.p, ((size_t)n + 1) * 4, hipMemcpyDeviceToHost, st));
+        HT_HIP(ctx, hipMemcpyAsync(hh.data(), hist.p, n1 * 4, hipMemcpyDeviceToHost, st));
         HT_HIP(ctx, hipStreamSynchronize(st));
         int32_t t = n;
         int64_t cum = 0, m = 0;
@@ -956,63 +1159,47 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
           cum += hh[t];
         }
         if (t < 0) return ht_set_err(ctx, HT_ESTATE, "ht_partition: buffer schedule ran out of rows to release");
-        k_select_nu<<<nblk(nw), TB, 0, st>>>(bmT.p, nw, nu.p, t, E, eqbm.p);
+        k_select_nu<<<nblk(nwp), TB, 0, st>>>(bmT.p, nwp, nu.p, t, Ej, eqbm.p);
         HT_LAUNCH_CHECK(ctx);
-        HT_TRY(ht_bitmap_prefix(ctx, eqbm.p, nw, cnt1.p, pref1.p));
-        k_take_first<<<nblk(nw), TB, 0, st>>>(eqbm.p, pref1.p, nw, m, E);
+        HT_TRY(ht_bitmap_prefix(ctx, eqbm.p, nwp, cnt1.p, pref1.p));
+        k_take_first<<<nblk(nwp), TB, 0, st>>>(eqbm.p, pref1.p, nwp, m, Ej);
         HT_LAUNCH_CHECK(ctx);
-        k_bm_clear<<<nblk(nw), TB, 0, st>>>(bmR.p, E, nw);
+        k_bm_minus<<<nblk(nwp), TB, 0, st>>>(bmR.p, Ej, nwp, bmR.p);
         HT_LAUNCH_CHECK(ctx);
-        n_leave[j - 1] = over;     // j > 0 here: nothing is resident before the first chunk
       }
-      k_bm_or<<<nblk(nw), TB, 0, st>>>(bmR.p, bmj, nw);
+      HT_HIP(ctx, hipMemcpyAsync(Pbm.p + (size_t)j * nwp, bmR.p, (size_t)nwp * 8, hipMemcpyDeviceToDevice, st));
+      k_bm_or<<<nblk(nwp), TB, 0, st>>>(bmR.p, bmj, nwp);
       HT_LAUNCH_CHECK(ctx);
       if (c.nsrc > 0) {
         k_set_nu<<<nblk(c.nsrc), TB, 0, st>>>(g->nbr.p + c.nbr_off, c.nsrc, nxt.p + c.nbr_off, nu.p);
         HT_LAUNCH_CHECK(ctx);
         if (j + 1 < n) {   // rows that no later chunk needs leave now (after the last chunk everything does)
-          uint64_t* E1 = Ebm.p + (size_t)(j + 1) * nw;
+          uint64_t* E1 = Ebm.p + (size_t)(j + 1) * nwp;
           k_mark_dead<<<nblk(c.nsrc), TB, 0, st>>>(g->nbr.p + c.nbr_off, c.nsrc, nxt.p + c.nbr_off, n, (uint32_t*)E1,
-                                                   dead_cnt.p + j);
+                                                   dead_cnt + j);
           HT_LAUNCH_CHECK(ctx);
-          k_bm_clear<<<nblk(nw), TB, 0, st>>>(bmR.p, E1, nw);
+          k_bm_minus<<<nblk(nwp), TB, 0, st>>>(bmR.p, E1, nwp, bmR.p);
           HT_LAUNCH_CHECK(ctx);
         }
       }
     }
-    if (n > 1) {
-      std::vector<unsigned long long> hd((size_t)n);
-      HT_HIP(ctx, hipMemcpyAsync(hd.data(), dead_cnt.p, (size_t)n * 8, hipMemcpyDeviceToHost, st));
-      HT_HIP(ctx, hipStreamSynchronize(st));
-      for (int j = 0; j + 1 < n; ++j) n_leave[j] += (int64_t)hd[j];
-    }
-    if (n > 0) {
-      HT_HIP(ctx, hipMemsetAsync(tot2.p, 0, 16, st));
-      k_popc_union<<<popc_grid(nw), TB, 0, st>>>(bmR.p, bmR.p, nw, tot2.p);
-      HT_LAUNCH_CHECK(ctx);
-      unsigned long long t2[2];
-      HT_HIP(ctx, hipMemcpyAsync(t2, tot2.p, 16, hipMemcpyDeviceToHost, st));
-      HT_HIP(ctx, hipStreamSynchronize(st));
-      n_leave[n - 1] = (int64_t)t2[0];   // what is still resident leaves at the end of a pass
-    }
+    HT_HIP(ctx, hipMemcpyAsync(Ebm.p + (size_t)n * nwp, bmR.p, (size_t)nwp * 8, hipMemcpyDeviceToDevice, st));
+    rows.pbm = Pbm.p;
+    rows.ebm = Ebm.p;
+    HT_TRY(count_lists());
+    HT_HIP(ctx, hipMemcpyAsync(hl, list(L_REUSE), 3 * n1 * 8, hipMemcpyDeviceToHost, st));
+    HT_HIP(ctx, hipStreamSynchronize(st));
+    take_offsets(hl);
   }
+  g->v_load = offs[1][n];
   for (int j = 0; j < n; ++j) {
     ChunkMeta& c = g->chunks[j];
-    c.n_reuse = n_reuse[j];
-    c.n_load = c.nsrc - c.n_reuse;
-    c.reuse_off = c.nbr_off - g->v_load;
-    c.load_off = g->v_load;
-    g->v_load += c.n_load;
-  }
-  {
-    int64_t off = 0;
-    for (int j = 0; j < n; ++j) {
-      ChunkMeta& c = g->chunks[j];
-      if (far_first) c.n_leave = n_leave[j];
-      else c.n_leave = (j + 1 < n) ? c.nsrc - g->chunks[j + 1].n_reuse : c.nsrc;
-      c.leave_off = off;
-      off += c.n_leave;
-    }
+    c.reuse_off = offs[0][j];
+    c.load_off = offs[1][j];
+    c.leave_off = offs[2][j];
+    c.n_reuse = offs[0][j + 1] - c.reuse_off;
+    c.n_load = offs[1][j + 1] - c.load_off;
+    c.n_leave = offs[2][j + 1] - c.leave_off;
   }
   if (C < 1) C = 1;
   g->cache_rows = C;
@@ -1023,12 +1210,16 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
   const size_t vr = (size_t)std::max<int64_t>(g->v_load, 1);
   const size_t ep = (size_t)std::max<int64_t>(Ep, 1);
   const size_t n_reused = (size_t)std::max<int64_t>(g->v_ori - g->v_load, 1);
+  const int64_t n_ent = g->merged ? nU : Ep;
+  const int64_t fb_items = item_bound(V, n_ent, seg_fwd), bb_items = item_bound(g->v_ori, n_ent, seg_bwd);
   {
     DevBlock& b = g->blk_chunks;
     b.add<int32_t>(vo); b.add<int32_t>(vo); b.add<int64_t>(vo + n); b.add<int32_t>(n_reused);
     for (int k = 0; k < 4; ++k) b.add<int32_t>(vr);
     for (int k = 0; k < 3; ++k) b.add<int32_t>(ep);
     if (g->merged) b.add<int64_t>(vo + n);
+    b.add<WorkItem>((size_t)fb_items); b.add<CutRow>((size_t)cut_bound(n_ent, seg_fwd));
+    b.add<WorkItem>((size_t)bb_items); b.add<CutRow>((size_t)cut_bound(n_ent, seg_bwd));
     HT_TRY(b.alloc(ctx));
     b.take(g->slot, vo);
     b.take(g->gslot, vo);
@@ -1042,198 +1233,162 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
     b.take(g->col_slot, ep);
     b.take(g->sdst, ep);
     if (g->merged) b.take(g->usptr, vo + n);
+    b.take(g->fwd_items.items, (size_t)fb_items);
+    b.take(g->fwd_items.cuts, (size_t)cut_bound(n_ent, seg_fwd));
+    b.take(g->bwd_items.items, (size_t)bb_items);
+    b.take(g->bwd_items.cuts, (size_t)cut_bound(n_ent, seg_bwd));
+  }
+  const int64_t nwC = ceil_div64(C, 64), tC = ceil_div64(nwC, TB);
+  ItemBuild ib[2];
+  ib[0].nrows = V;
+  ib[0].seg = seg_fwd;
+  ib[0].bound = fb_items;
+  ib[0].rows = RowSet{g->merged ? g->uindptr.p : g->indptr.p, list(L_BOUNDS), nullptr, n};
+  ib[1].nrows = g->v_ori;
+  ib[1].seg = seg_bwd;
+  ib[1].bound = bb_items;
+  ib[1].rows = RowSet{g->merged ? g->usptr.p : g->sptr.p, list(L_NOFF), list(g->merged ? L_UEOFF : L_EOFF), n};
+  DevBlock tmp2;
+  DevArr<int32_t> vslot, free_cnt, icnt[2];
+  DevArr<uint64_t> freebm;
+  DevArr<int64_t> ibase[2], istarts;
+  DevArr<WorkItem> made;
+  for (ItemBuild& b : ib) b.tiles = ceil_div64(b.nrows, RTILE);
+  tmp2.add<int32_t>((size_t)V);
+  tmp2.add<int32_t>((size_t)tC);
+  tmp2.add<uint64_t>((size_t)2 * nwC);
+  for (const ItemBuild& b : ib) { tmp2.add<int32_t>((size_t)3 * b.tiles); tmp2.add<int64_t>((size_t)3 * b.tiles + 1); }
+  tmp2.add<int64_t>(6 * n1);
+  tmp2.add<WorkItem>((size_t)std::max(fb_items, bb_items));
+  HT_TRY(tmp2.alloc(ctx));
+  tmp2.take(vslot, (size_t)V);
+  tmp2.take(free_cnt, (size_t)tC);
+  tmp2.take(freebm, (size_t)2 * nwC);
+  for (int d = 0; d < 2; ++d) {
+    tmp2.take(icnt[d], (size_t)3 * ib[d].tiles);
+    tmp2.take(ibase[d], (size_t)3 * ib[d].tiles + 1);
+    ib[d].cnt = icnt[d].p;
+    ib[d].base = ibase[d].p;
+  }
+  tmp2.take(istarts, 6 * n1);
+  tmp2.take(made, (size_t)std::max(fb_items, bb_items));
+  ib[0].starts = istarts.p;
+  ib[1].starts = istarts.p + 3 * n1;
+
+  // ---- the lists, then the buffer positions, chunk by chunk
+  k_list_expand<<<(unsigned)(n * T), TB, 0, st>>>(rows, T, lbase.p, g->reuse.p, g->load.p, g->leave.p);
+  HT_LAUNCH_CHECK(ctx);
+  uint64_t* free_now = freebm.p;
+  uint64_t* free_next = freebm.p + nwC;
+  k_free_init<<<nblk(nwC), TB, 0, st>>>(free_now, nwC, C);
+  HT_LAUNCH_CHECK(ctx);
+  for (int j = 0; j < n; ++j) {
+    const ChunkMeta& c = g->chunks[j];
+    if (c.n_load > 0) {
+      const bool counted = nwC > 16 * TB;   // few words: every block adds up those before it by itself
+      if (counted) {
+        k_free_count<<<(unsigned)tC, TB, 0, st>>>(free_now, nwC, free_cnt.p);
+        HT_LAUNCH_CHECK(ctx);
+      }
+      k_assign<<<(unsigned)tC, TB, 0, st>>>(free_now, free_next, nwC, counted ? free_cnt.p : nullptr, g->load.p + c.load_off,
+                                            c.n_load, vslot.p, g->load_slot.p + c.load_off);
+      HT_LAUNCH_CHECK(ctx);
+      std::swap(free_now, free_next);
+    }
+    if (c.nsrc + c.n_leave > 0) {
+      const uint64_t* prev = far_first ? Pbm.p + (size_t)j * nwp
+                             : j > 0   ? allbm.p + (size_t)g->order[j - 1] * nwp
+                                       : nullptr;
+      k_lookup_evict<<<nblk(c.nsrc + c.n_leave), TB, 0, st>>>(g->nbr.p + c.nbr_off, c.nsrc, vslot.p, prev, g->slot.p + c.nbr_off,
+                                                             g->gslot.p + c.nbr_off, g->leave.p + c.leave_off, c.n_leave,
+                                                             (uint32_t*)free_now, g->leave_slot.p + c.leave_off);
+      HT_LAUNCH_CHECK(ctx);
+    }
   }
 
-  // ---- pass 2 temporaries
-  const int64_t nwC = ceil_div64(C, 64);
-  const int64_t nwmax = std::max(nw, nwC);
-  DevBlock tmp2;
-  DevArr<int32_t> cnt_tmp, vslot, freelist, mflag;
-  DevArr<int64_t> pref, mrank, mpos;
-  DevArr<uint64_t> freebm;
-  const size_t mnnz = (size_t)std::max<int64_t>(g->max_nnz, 1);
-  tmp2.add<int32_t>(nwmax); tmp2.add<int64_t>(nwmax + 1); tmp2.add<int32_t>((size_t)V); tmp2.add<int32_t>((size_t)C);
-  tmp2.add<uint64_t>(nwC);
-  if (g->merged) { tmp2.add<int32_t>(mnnz); tmp2.add<int64_t>(mnnz + 1); tmp2.add<int64_t>(mnnz + 1); }
-  HT_TRY(tmp2.alloc(ctx));
-  tmp2.take(cnt_tmp, nwmax);
-  tmp2.take(pref, nwmax + 1);
-  tmp2.take(vslot, (size_t)V);
-  tmp2.take(freelist, (size_t)C);
-  tmp2.take(freebm, nwC);
+  // ---- topology in local indices, the edges grouped by source
+  k_sptr_ends<<<nblk(n), TB, 0, st>>>(list(L_NOFF), list(L_EOFF), n, g->sptr.p);
+  HT_LAUNCH_CHECK(ctx);
   if (g->merged) {
-    tmp2.take(mflag, mnnz);
-    tmp2.take(mrank, mnnz + 1);
-    tmp2.take(mpos, mnnz + 1);
-  }
-  HT_HIP(ctx, hipMemsetAsync(vslot.p, 0xFF, (size_t)V * 4, st));
-  // every position free: all ones, the last word cut to C bits (its value travels from pinned memory)
-  HT_HIP(ctx, hipMemsetAsync(freebm.p, 0xFF, nwC * 8, st));
-  if (C % 64) {
-    hpin[4] = (int64_t)((~0ull) >> (64 - (C % 64)));
-    HT_HIP(ctx, hipMemcpyAsync(freebm.p + (nwC - 1), &hpin[4], 8, hipMemcpyHostToDevice, st));
-  }
-  ItemTmp itmp;
-  HT_TRY(itmp.alloc(ctx, std::max<int64_t>(std::max(g->max_ndst, g->max_nsrc), 1)));
-  itmp.totals = hpin;
-  const char* ord_env = getenv("HT_ITEM_ORDER");
-  const bool order_items = !(ord_env && atoi(ord_env) == 0);
-  int seg_fwd = HT_SEG, seg_bwd = HT_SEG / 2;   // measured best at cfg2; the variables are for experiments
-  if (const char* v = getenv("HT_SEG_FWD")) seg_fwd = std::max(64, atoi(v));
-  if (const char* v = getenv("HT_SEG_BWD")) seg_bwd = std::max(64, atoi(v));
-  // One block for the work-item lists of all chunks and both directions.  A row of len entries makes
-  // ceil(len / seg) items and is a cut row when that is more than one, so rows + entries / seg bounds the items
-  // and entries / seg the cut rows; the lists take 20 bytes per item and 12 per cut row.
-  {
-    size_t cap = 0;
-    for (int j = 0; j < n; ++j) {
-      const ChunkMeta& c = g->chunks[j];
-      const size_t ent = (size_t)(g->merged ? c.nu : c.nnz);
-      const size_t rows[2] = {(size_t)(c.dst1 - c.dst0), (size_t)c.nsrc};
-      const size_t seg[2] = {(size_t)seg_fwd, (size_t)seg_bwd};
-      for (int d = 0; d < 2; ++d) cap += DevBlock::pad(20 * (rows[d] + ent / seg[d] + 1) + 12 * (ent / seg[d] + 1));
-    }
-    HT_TRY(g->items_mem.alloc(ctx, cap));
-    itmp.arena = g->items_mem.p;
-    itmp.arena_cap = cap;
-  }
-  // prev: the previous chunk's set (adjacent reuse), or the resident rows, kept up to date in bmB (schedule-aware)
-  prev = bmB.p;
-  HT_HIP(ctx, hipMemsetAsync(prev, 0, nw * 8, st));
-  for (int j = 0; j < n; ++j) {
-    ChunkMeta& c = g->chunks[j];
-    int32_t* nbr_j = g->nbr.p + c.nbr_off;
-    int32_t* slot_j = g->slot.p + c.nbr_off;
-    int32_t* gslot_j = g->gslot.p + c.nbr_off;
-    int64_t* sptr_j = g->sptr.p + c.sptr_off;
-    // unique sorted sources and local indices
-    HT_TRY(chunk_bm(j, (far_first || !(j & 1)) ? bmA.p : bmB.p, &cur));
-    HT_TRY(ht_bitmap_prefix(ctx, cur, nw, cnt_tmp.p, pref.p));
-    HT_TRY(ht_bitmap_expand(ctx, cur, nw, pref.p, nbr_j));
-    if (c.nnz > 0) {
-      k_remap<<<nblk(c.nnz), TB, 0, st>>>(g->col.p + c.e0, c.nnz, cur, pref.p, g->col_local.p + c.e0);
-      HT_LAUNCH_CHECK(ctx);
-    }
-    // reuse / load / leave(previous chunk)
-    k_bm_op<<<nblk(nw), TB, 0, st>>>(cur, prev, nw, 0, bmT.p);
+    k_sptr_ends<<<nblk(n), TB, 0, st>>>(list(L_NOFF), list(L_UEOFF), n, g->usptr.p);
     HT_LAUNCH_CHECK(ctx);
-    HT_TRY(ht_bitmap_prefix(ctx, bmT.p, nw, cnt_tmp.p, pref.p));
-    HT_TRY(ht_bitmap_expand(ctx, bmT.p, nw, pref.p, g->reuse.p + c.reuse_off));
-    k_bm_op<<<nblk(nw), TB, 0, st>>>(cur, prev, nw, 1, bmT.p);
+  }
+  if (Ep > 0) {
+    k_remap<<<(unsigned)etiles, TB, 0, st>>>(csc, Ep, bitsV, list(L_EOFF), list(L_BOUNDS), list(L_NOFF), n, allbm.p, nwp, wpref.p,
+                                             g->slot.p, g->col_local.p, g->col_slot.p, other);
     HT_LAUNCH_CHECK(ctx);
-    HT_TRY(ht_bitmap_prefix(ctx, bmT.p, nw, cnt_tmp.p, pref.p));
-    HT_TRY(ht_bitmap_expand(ctx, bmT.p, nw, pref.p, g->load.p + c.load_off));
-    if (j > 0) {
-      ChunkMeta& pc = g->chunks[j - 1];
-      if (far_first) {
-        HT_HIP(ctx, hipMemcpyAsync(bmT.p, Ebm.p + (size_t)j * nw, nw * 8, hipMemcpyDeviceToDevice, st));
-      } else {
-        k_bm_op<<<nblk(nw), TB, 0, st>>>(prev, cur, nw, 1, bmT.p);
-        HT_LAUNCH_CHECK(ctx);
-      }
-      HT_TRY(ht_bitmap_prefix(ctx, bmT.p, nw, cnt_tmp.p, pref.p));
-      HT_TRY(ht_bitmap_expand(ctx, bmT.p, nw, pref.p, g->leave.p + pc.leave_off));
-      if (pc.n_leave > 0) {
-        k_evict<<<nblk(pc.n_leave), TB, 0, st>>>(g->leave.p + pc.leave_off, pc.n_leave, vslot.p,
-                                                 (uint32_t*)freebm.p, g->leave_slot.p + pc.leave_off);
-        HT_LAUNCH_CHECK(ctx);
-      }
-    }
-    // positions: loaded rows take the lowest free positions
-    if (c.n_load > 0) {
-      HT_TRY(ht_bitmap_prefix(ctx, freebm.p, nwC, cnt_tmp.p, pref.p));
-      HT_TRY(ht_bitmap_expand(ctx, freebm.p, nwC, pref.p, freelist.p));
-      k_assign<<<nblk(c.n_load), TB, 0, st>>>(g->load.p + c.load_off, c.n_load, freelist.p, vslot.p,
-                                              (uint32_t*)freebm.p, g->load_slot.p + c.load_off);
+    if (g->merged) {   // buffer positions of the distinct forward pairs
+      k_gather_i32<<<nblk(nU), TB, 0, st>>>(g->col_slot.p, upos.p, nU, g->ucol_slot.p);
       HT_LAUNCH_CHECK(ctx);
     }
-    if (c.nsrc > 0) {
-      k_lookup_slots<<<nblk(c.nsrc), TB, 0, st>>>(nbr_j, c.nsrc, vslot.p, prev, slot_j, gslot_j);
+    uint64_t* by_src = nullptr;
+    HT_TRY(ht_radix_sort_u64(ctx, other, csc, Ep, 32, 32 + bits_for(g->v_ori), &by_src));
+    k_by_source<<<(unsigned)etiles, TB, 0, st>>>(by_src, Ep, list(L_EOFF), n, g->sdst.p, g->sptr.p, g->merged ? ucount.p : nullptr);
+    HT_LAUNCH_CHECK(ctx);
+    if (g->merged) {
+      HT_TRY(ht_scan_i32(ctx, ucount.p, ubase.p, etiles, true));
+      k_runs_bwd<<<(unsigned)etiles, TB, 0, st>>>(by_src, Ep, ubase.p, nU, list(L_EOFF), list(L_UEOFF), n, upos.p, g->usptr.p);
       HT_LAUNCH_CHECK(ctx);
-    }
-    if (c.nnz > 0) {
-      k_map_i32<<<nblk(c.nnz), TB, 0, st>>>(g->col_local.p + c.e0, c.nnz, slot_j, g->col_slot.p + c.e0);
+      k_merge_bwd<<<nblk(nU, ETILE), TB, 0, st>>>(upos.p, nU, by_src, list(L_UEOFF), list(L_BOUNDS), n, g->s.p, g->usdst.p,
+                                                  g->uw_bwd.p, g->umult_bwd.p);
       HT_LAUNCH_CHECK(ctx);
-    }
-    // the same edges grouped by local source, destinations ascending inside a source
-    uint64_t* csr_sorted = nullptr;
-    HT_HIP(ctx, hipMemsetAsync(sptr_j, 0, (c.nsrc + 1) * 8, st));
-    if (c.nnz > 0) {
-      k_csr_keys<<<nblk(c.nnz), TB, 0, st>>>(g->indptr.p, c.dst0, c.dst1, c.e0, c.nnz, g->col_local.p + c.e0,
-                                             keysA.p);
-      HT_LAUNCH_CHECK(ctx);
-      uint64_t* sorted = nullptr;
-      HT_TRY(ht_radix_sort_u64(ctx, keysA.p, keysB.p, c.nnz, 32, 32 + bits_for(c.nsrc), &sorted));
-      k_low_bits<<<nblk(c.nnz), TB, 0, st>>>(sorted, c.nnz, 0xFFFFFFFFull, g->sdst.p + c.e0);
-      HT_LAUNCH_CHECK(ctx);
-      k_boundaries<<<nblk(c.nnz), TB, 0, st>>>(sorted, c.nnz, 32, c.nsrc, sptr_j);
-      HT_LAUNCH_CHECK(ctx);
-      csr_sorted = sorted;
-    }
-    // work items of both directions
-    // forward items are ordered by buffer-independent source id; backward ones by local destination
-    if (!g->merged) {
-      HT_TRY(build_items(ctx, itmp, g->indptr.p + c.dst0, c.e0, c.dst1 - c.dst0, g->col.p + c.e0, V, keysA.p, keysB.p,
-                         order_items, seg_fwd, &c.fwd));
-      HT_TRY(build_items(ctx, itmp, sptr_j, 0, c.nsrc, g->sdst.p + c.e0, c.dst1 - c.dst0, keysA.p, keysB.p, order_items,
-                         seg_bwd, &c.bwd));
-    } else {
-      int64_t* usptr_j = g->usptr.p + c.sptr_off;
-      HT_HIP(ctx, hipMemsetAsync(usptr_j, 0, (c.nsrc + 1) * 8, st));
-      if (c.nu > 0) {
-        // buffer positions of the distinct forward pairs
-        k_gather_i32_at<<<nblk(c.nu), TB, 0, st>>>(upos.p + c.ue0, c.e0, c.nu, g->col_slot.p + c.e0, g->ucol_slot.p + c.ue0);
-        HT_LAUNCH_CHECK(ctx);
-        // distinct (source, destination) pairs of the by-source order; csr_sorted holds the sorted keys
-        uint64_t* other = csr_sorted == keysA.p ? keysB.p : keysA.p;
-        k_dup_flags_u64<<<nblk(c.nnz), TB, 0, st>>>(csr_sorted, c.nnz, mflag.p);
-        HT_LAUNCH_CHECK(ctx);
-        HT_TRY(ht_scan_i32(ctx, mflag.p, mrank.p, c.nnz, false));
-        k_flag_positions<<<nblk(c.nnz), TB, 0, st>>>(mflag.p, mrank.p, c.nnz, mpos.p);
-        HT_LAUNCH_CHECK(ctx);
-        k_set_i64<<<1, 1, 0, st>>>(mpos.p + c.nu, c.nnz);
-        HT_LAUNCH_CHECK(ctx);
-        k_merge_bwd<<<nblk(c.nu), TB, 0, st>>>(mpos.p, c.nu, csr_sorted, g->s.p + c.dst0, g->usdst.p + c.ue0,
-                                               g->uw_bwd.p + c.ue0, g->umult_bwd.p + c.ue0, other);
-        HT_LAUNCH_CHECK(ctx);
-        k_boundaries<<<nblk(c.nu), TB, 0, st>>>(other, c.nu, 32, c.nsrc, usptr_j);
-        HT_LAUNCH_CHECK(ctx);
-      }
-      HT_TRY(build_items(ctx, itmp, g->uindptr.p + c.dst0, c.ue0, c.dst1 - c.dst0, g->ucol.p + c.ue0, V, keysA.p, keysB.p,
-                         order_items, seg_fwd, &c.fwd));
-      HT_TRY(build_items(ctx, itmp, usptr_j, 0, c.nsrc, g->usdst.p + c.ue0, c.dst1 - c.dst0, keysA.p, keysB.p,
-                         order_items, seg_bwd, &c.bwd));
-    }
-    g->max_fpart = std::max(g->max_fpart, c.fwd.n_part);
-    g->max_bpart = std::max(g->max_bpart, c.bwd.n_part);
-    if (far_first) {   // prev = resident rows: minus what was released before this chunk, plus this chunk's
-      k_bm_clear<<<nblk(nw), TB, 0, st>>>(prev, Ebm.p + (size_t)j * nw, nw);
-      HT_LAUNCH_CHECK(ctx);
-      k_bm_or<<<nblk(nw), TB, 0, st>>>(prev, cur, nw);
-      HT_LAUNCH_CHECK(ctx);
-    } else {
-      prev = cur;
     }
   }
-  // what is still buffered leaves at the end of a pass
-  if (n > 0) {
-    ChunkMeta& lc = g->chunks[n - 1];
-    if (far_first) {
-      if (lc.n_leave > 0) {
-        HT_TRY(ht_bitmap_prefix(ctx, prev, nw, cnt_tmp.p, pref.p));
-        HT_TRY(ht_bitmap_expand(ctx, prev, nw, pref.p, g->leave.p + lc.leave_off));
-        k_map_i32<<<nblk(lc.n_leave), TB, 0, st>>>(g->leave.p + lc.leave_off, lc.n_leave, vslot.p,
-                                                   g->leave_slot.p + lc.leave_off);
-        HT_LAUNCH_CHECK(ctx);
-      }
-    } else if (lc.nsrc > 0) {
-      HT_HIP(ctx, hipMemcpyAsync(g->leave.p + lc.leave_off, g->nbr.p + lc.nbr_off, lc.nsrc * 4,
-                                 hipMemcpyDeviceToDevice, st));
-      HT_HIP(ctx, hipMemcpyAsync(g->leave_slot.p + lc.leave_off, g->slot.p + lc.nbr_off, lc.nsrc * 4,
-                                 hipMemcpyDeviceToDevice, st));
-    }
+
+  // ---- work items of both directions: forward items are ordered by buffer-independent source id, backward ones by local destination
+  GraphItems* gi[2] = {&g->fwd_items, &g->bwd_items};
+  const int32_t* idx[2] = {g->merged ? g->ucol.p : g->col.p, g->merged ? g->usdst.p : g->sdst.p};
+  const int64_t range[2] = {V, g->max_ndst};
+  int64_t* htot = hp;   // three totals per direction
+  for (int d = 0; d < 2; ++d) {
+    HT_TRY(count_items(ctx, ib[d]));
+    if (ib[d].nrows > 0)
+      for (int w = 0; w < 3; ++w)
+        HT_HIP(ctx, hipMemcpyAsync(&htot[3 * d + w], ib[d].base + (w + 1) * ib[d].tiles, 8, hipMemcpyDeviceToHost, st));
   }
   HT_HIP(ctx, hipStreamSynchronize(st));
+  for (int d = 0; d < 2; ++d) {
+    ItemBuild& b = ib[d];
+    if (b.nrows == 0) continue;
+    const int64_t ni = htot[3 * d], np = htot[3 * d + 1] - htot[3 * d], nc = htot[3 * d + 2] - htot[3 * d + 1];
+    if (ni > b.bound || ni > (int64_t)nkeys) return ht_set_err(ctx, HT_ESTATE, "ht_partition: %lld work items, %lld expected at most", (long long)ni, (long long)b.bound);
+    gi[d]->n_items = ni;
+    gi[d]->n_part = np;
+    gi[d]->n_cut = nc;
+    const bool sorted_items = order_items && ni > 1;
+    const int kbits = n > 1 ? bits_for(n) : 0, vbits = bits_for(range[d]);
+    const int fbits = std::min(vbits, 32 - kbits), fshift = vbits - fbits;
+    WorkItem* into = sorted_items ? made.p : gi[d]->items.p;
+    k_items_fill<<<(unsigned)b.tiles, TB, 0, st>>>(b.rows, b.nrows, b.seg, b.tiles, b.base, idx[d], fbits, fshift, into,
+                                                   sorted_items ? keysA.p : nullptr, gi[d]->cuts.p, b.starts);
+    HT_LAUNCH_CHECK(ctx);
+    if (sorted_items) {
+      uint64_t* sorted = nullptr;
+      HT_TRY(ht_radix_sort_u64(ctx, keysA.p, keysB.p, ni, 32, 32 + kbits + fbits, &sorted));
+      k_items_permute<<<nblk(ni), TB, 0, st>>>(sorted, ni, made.p, gi[d]->items.p);
+      HT_LAUNCH_CHECK(ctx);
+    }
+  }
+  HT_HIP(ctx, hipMemcpyAsync(hl, istarts.p, 6 * n1 * 8, hipMemcpyDeviceToHost, st));
+  HT_HIP(ctx, hipStreamSynchronize(st));
+  for (int d = 0; d < 2; ++d) {
+    const int64_t tot[3] = {gi[d]->n_items, gi[d]->n_part, gi[d]->n_cut};
+    const std::vector<int64_t>& first = d == 0 ? g->bounds : noff;
+    // start of chunk k's share (chunks that start behind the last row have none)
+    auto at = [&](int w, int k) { return k < n && first[k] < ib[d].nrows ? hl[(size_t)(3 * d + w) * n1 + k] : tot[w]; };
+    for (int j = 0; j < n; ++j) {
+      ChunkMeta& c = g->chunks[j];
+      ItemRange& r = d == 0 ? c.fwd : c.bwd;
+      r.it0 = at(0, c.id);
+      r.n_items = at(0, c.id + 1) - r.it0;
+      r.part0 = at(1, c.id);
+      r.n_part = at(1, c.id + 1) - r.part0;
+      r.cut0 = at(2, c.id);
+      r.n_cut = at(2, c.id + 1) - r.cut0;
+      int64_t& mx = d == 0 ? g->max_fpart : g->max_bpart;
+      mx = std::max(mx, r.n_part);
+    }
+  }
   return HT_OK;
 }
 
@@ -1251,7 +1406,7 @@ int64_t ht_graph::hbm_bytes() const {
               sptr.bytes() + sdst.bytes() + slot.bytes() + gslot.bytes() + reuse.bytes() + load.bytes() +
               load_slot.bytes() + leave.bytes() + leave_slot.bytes() + uindptr.bytes() + ucol.bytes() +
               ucol_slot.bytes() + uw_fwd.bytes() + umult.bytes() + usdst.bytes() + uw_bwd.bytes() + umult_bwd.bytes() + usptr.bytes();
-  for (const ChunkMeta& c : chunks) b += c.fwd.blob.bytes() + c.bwd.blob.bytes();
+  for (const GraphItems* i : {&fwd_items, &bwd_items}) b += i->n_items * (int64_t)sizeof(WorkItem) + i->n_cut * (int64_t)sizeof(CutRow);
   return b;
 }
 
@@ -1376,17 +1531,25 @@ int ht_graph_reorganize(ht_ctx* ctx, const ht_graph* g, int32_t m, int32_t* layo
     if (g->order[j] != j)
       return ht_set_err(ctx, HT_ESTATE, "ht_graph_reorganize: the graph's chunks must be in vertex-id order (reorder_chunks = 0)");
   const int n = g->n / m, mn = g->n;
-  const int64_t nw = ceil_div64(g->V, 64);
+  const int64_t nw = bm_words(g->V);
   hipStream_t st = ctx->stream;
   DevArr<uint64_t> bms, U;
   HT_TRY(bms.alloc(ctx, (size_t)mn * nw));
   HT_TRY(U.alloc(ctx, (size_t)n * nw));
-  DevArr<uint8_t> seen;
-  HT_TRY(seen.alloc(ctx, (size_t)nw * 64));
-  HT_HIP(ctx, hipMemsetAsync(seen.p, 0, (size_t)nw * 64, st));
-  for (int c = 0; c < mn; ++c) {
-    const ChunkMeta& ch = g->chunks[c];
-    HT_TRY(mark_sources(ctx, st, g->col.p + ch.e0, ch.nnz, seen.p, nw, bms.p + (size_t)c * nw));
+  {
+    DevArr<uint8_t> seen;
+    DevArr<int32_t> tile_cnt;
+    DevArr<int64_t> d_eoff;
+    std::vector<int64_t> eoff;
+    for (const ChunkMeta& ch : g->chunks) eoff.push_back(ch.e0);
+    eoff.push_back(g->Ep);
+    HT_TRY(seen.alloc(ctx, (size_t)mark_group(nw, mn) * nw * 64));
+    HT_TRY(tile_cnt.alloc(ctx, (size_t)mn * (nw / TB)));
+    HT_TRY(d_eoff.alloc(ctx, eoff.size()));
+    HT_HIP(ctx, hipMemcpyAsync(d_eoff.p, eoff.data(), eoff.size() * 8, hipMemcpyHostToDevice, st));
+    HT_TRY(ht_fill_zero(ctx, st, seen.p, seen.bytes()));
+    HT_TRY(mark_chunks(ctx, st, g->col.p, eoff.data(), d_eoff.p, mn, nw, seen.p, bms.p, tile_cnt.p));
+    HT_HIP(ctx, hipStreamSynchronize(st));
   }
   DevArr<unsigned long long> cnt;
   HT_TRY(cnt.alloc(ctx, (size_t)2 * n));

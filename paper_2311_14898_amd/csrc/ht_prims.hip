@@ -1,5 +1,5 @@
 // Device-wide primitives for the integer (preprocessing) part: exclusive scan,
-// stable LSD radix sort of 64-bit keys, bitmap rank / expand.  Wave64 ballot,
+// stable LSD radix sort of 64-bit keys, bitmap rank.  Wave64 ballot,
 // popcount and shuffle scans do the in-wave work.
 #include "ht_internal.h"
 
@@ -277,20 +277,6 @@ __global__ void k_popc(const uint64_t* __restrict__ bm, int64_t nw, int32_t* __r
   if (i < nw) cnt[i] = __popcll(bm[i]);
 }
 
-__global__ void k_bm_expand(const uint64_t* __restrict__ bm, int64_t nw, const int64_t* __restrict__ pref,
-                            int32_t* __restrict__ out) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nw) return;
-  uint64_t w = bm[i];
-  int64_t p = pref[i];
-  const int32_t base = (int32_t)(i * 64);
-  while (w) {
-    int b = __ffsll((unsigned long long)w) - 1;
-    out[p++] = base + b;
-    w &= w - 1;
-  }
-}
-
 }  // namespace
 
 int ht_scan_i32(ht_ctx* ctx, const int32_t* in, int64_t* out, int64_t n, bool want_total) {
@@ -335,11 +321,4 @@ int ht_bitmap_prefix(ht_ctx* ctx, const uint64_t* bm, int64_t nw, int32_t* cnt_t
     HT_LAUNCH_CHECK(ctx);
   }
   return ht_scan_i32(ctx, cnt_tmp, pref, nw, true);
-}
-
-int ht_bitmap_expand(ht_ctx* ctx, const uint64_t* bm, int64_t nw, const int64_t* pref, int32_t* out) {
-  if (nw <= 0) return HT_OK;
-  k_bm_expand<<<(unsigned)ceil_div64(nw, 256), 256, 0, ctx->stream>>>(bm, nw, pref, out);
-  HT_LAUNCH_CHECK(ctx);
-  return HT_OK;
 }

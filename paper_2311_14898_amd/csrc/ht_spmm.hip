@@ -29,7 +29,7 @@ __device__ __forceinline__ float4 shfl_xor4(float4 v, int o) {
 // Final write of one output row's float4 column `c4` (in floats).
 __device__ __forceinline__ void write_out(const SpmmArgs& a, int32_t r, int c4, float4 v) {
   const float post = a.post ? a.post[a.post_idx ? a.post_idx[r] : r] : 1.f;
-  uint32_t orow = a.out_idx ? (uint32_t)a.out_idx[r] : (uint32_t)r;
+  uint32_t orow = a.out_idx ? (uint32_t)a.out_idx[r] : (uint32_t)(r - a.row0);
   const bool fresh = (orow & 0x80000000u) != 0u;
   orow &= 0x7FFFFFFFu;
   float* p = a.out + (int64_t)orow * a.out_ld + c4;
@@ -45,10 +45,11 @@ __global__ void __launch_bounds__(256) k_spmm_items(SpmmArgs a) {
   const int lane = threadIdx.x & 63;
   const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= a.n_items) return;
-  const int32_t r = a.it_row[t];
-  const int64_t e0 = a.it_e0[t];
-  const int32_t len = a.it_len[t];
-  const int32_t part = a.it_part[t];
+  const WorkItem it = a.items[t];
+  const int32_t r = it.row;
+  const int64_t e0 = it.e0;
+  const int32_t len = it.len;
+  const int32_t part = it.part;
   const int sub = lane / LPR, ll = lane % LPR;
   const int d4 = (a.d + 3) & ~3;
 
@@ -65,7 +66,7 @@ __global__ void __launch_bounds__(256) k_spmm_items(SpmmArgs a) {
     float my_w = 0.f;
     if (lane < n_here) {
       my_idx = a.idx[e0 + base + lane];
-      my_w = a.w_edge ? a.w_edge[e0 + base + lane] : (a.ew ? a.ew[my_idx] : 1.f);
+      my_w = a.w_edge ? a.w_edge[e0 - a.w0 + base + lane] : (a.ew ? a.ew[my_idx] : 1.f);
     }
     for (int32_t k = 0; k < n_here; k += G) {
       int32_t c;
@@ -97,7 +98,7 @@ __global__ void __launch_bounds__(256) k_spmm_items(SpmmArgs a) {
     if (!colok[j]) continue;
     const int c4 = (j * LPR + ll) * 4;
     if (part >= 0)
-      st4(a.partial + (int64_t)part * a.out_ld + c4, acc[j]);
+      st4(a.partial + (part - a.part0) * a.out_ld + c4, acc[j]);
     else
       write_out(a, r, c4, acc[j]);
   }
@@ -110,9 +111,10 @@ __global__ void __launch_bounds__(256) k_spmm_fix(SpmmArgs a) {
   __shared__ float4 sh[4][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t f = blockIdx.x;
-  const int32_t r = a.fx_row[f];
-  const int32_t p0 = a.fx_part0[f];
-  const int32_t ns = a.fx_nseg[f];
+  const CutRow cut = a.cuts[f];
+  const int32_t r = cut.row;
+  const int64_t p0 = cut.part0 - a.part0;
+  const int32_t ns = cut.nseg;
   const int d4 = (a.d + 3) & ~3;
   const int32_t per = (ns + 3) >> 2;
   const int32_t k0 = wave * per, k1 = (k0 + per) < ns ? (k0 + per) : ns;
@@ -120,7 +122,7 @@ __global__ void __launch_bounds__(256) k_spmm_fix(SpmmArgs a) {
     const int c4 = cb + lane * 4;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     if (c4 < d4) {
-      const float* p = a.partial + (int64_t)p0 * a.out_ld + c4;
+      const float* p = a.partial + p0 * a.out_ld + c4;
       int32_t k = k0;
       for (; k + 4 <= k1; k += 4) {
         const float4 v0 = ld4(p + (int64_t)(k + 0) * a.out_ld);
@@ -163,10 +165,11 @@ __global__ void __launch_bounds__(256) k_spmm_slab(SpmmArgs a, int S, int nvs, i
   const int v0 = slab * nvs;
   const int nv_here = (nvec - v0) < nvs ? (nvec - v0) : nvs;
   if (nv_here <= 0) return;
-  const int32_t r = a.it_row[t];
-  const int64_t e0 = a.it_e0[t];
-  const int32_t len = a.it_len[t];
-  const int32_t part = a.it_part[t];
+  const WorkItem it = a.items[t];
+  const int32_t r = it.row;
+  const int64_t e0 = it.e0;
+  const int32_t len = it.len;
+  const int32_t part = it.part;
   const int es = lane / nvs, vec = lane - es * nvs;
   const bool active = es < eps && vec < nv_here;
   const int coff = (v0 + vec) * 4;
@@ -179,7 +182,7 @@ __global__ void __launch_bounds__(256) k_spmm_slab(SpmmArgs a, int S, int nvs, i
     float my_w = 0.f;
     if (lane < n_here) {
       my_idx = a.idx[e0 + base + lane];
-      my_w = a.w_edge ? a.w_edge[e0 + base + lane] : (a.ew ? a.ew[my_idx] : 1.f);
+      my_w = a.w_edge ? a.w_edge[e0 - a.w0 + base + lane] : (a.ew ? a.ew[my_idx] : 1.f);
     }
     if (UNI) {
       // one edge per step for the whole wave: the index and weight are wave-uniform
@@ -233,7 +236,7 @@ __global__ void __launch_bounds__(256) k_spmm_slab(SpmmArgs a, int S, int nvs, i
   }
   if (es != 0 || vec >= nv_here) return;
   if (part >= 0)
-    st4(a.partial + (int64_t)part * a.out_ld + coff, tot);
+    st4(a.partial + (part - a.part0) * a.out_ld + coff, tot);
   else
     write_out(a, r, coff, tot);
 }
