@@ -256,7 +256,7 @@ typedef struct {
   double t_copy_ms;       /* contiguous H2D / D2H copies of chunk rows       */
   double t_cpu_accum_ms;  /* host-side gradient accumulation                 */
   double t_update_ms;
-  int64_t n_spmm_fwd, n_spmm_bwd, n_gemm; /* kernel launches behind the times */
+  int64_t n_spmm_fwd, n_spmm_bwd, n_gemm; /* aggregations (one per chunk; a launch may serve several chunks), GEMMs */
   int64_t edges;             /* stored edges aggregated (forward + backward)     */
   int64_t rows_loaded;       /* neighbour rows fetched into the buffer           */
   int64_t rows_reused;       /* neighbour rows reused in place                   */

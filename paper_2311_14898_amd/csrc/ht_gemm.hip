@@ -6,6 +6,8 @@
 //   TN: C[K x N] = A[M x K]^T B[M x N] reduction over the tall M, cut into
 //       slices whose partial tiles are added in slice order (no atomics).
 // The small operand W is first packed into a zero-padded tile-aligned copy.
+#include <algorithm>
+
 #include "ht_internal.h"
 
 namespace {
@@ -158,12 +160,13 @@ __global__ void __launch_bounds__(256) k_gemm_nn(const float* __restrict__ A, in
     }
 }
 
-// Partial tile of C[K x N] = A[M x K]^T B[M x N] over the M-slice blockIdx.z.
+// Partial tile of C[K x N] = A[M x K]^T B[M x N] over the M-slice blockIdx.z (rows tab[2z] .. tab[2z + 1], or slice_rows each).
 // P[slice][K x N] dense.  Block tile: BM output rows (k) x BN output columns.
 template <int BN, int WM, int WN, int TI, int TJ>
 __global__ void __launch_bounds__(256) k_gemm_tn(const float* __restrict__ A, int64_t lda,
                                                  const float* __restrict__ B, int64_t ldb, float* __restrict__ P,
-                                                 int64_t M, int K, int N, int64_t slice_rows) {
+                                                 int64_t M, int K, int N, int64_t slice_rows,
+                                                 const int64_t* __restrict__ tab) {
   static_assert(WM * WN == 4 && WM * TI * 32 == BM && WN * TJ * 32 == BN, "tile shape");
   __shared__ float As[BK * (BM + 4)];
   __shared__ float Bs[BK * (BN + 4)];
@@ -172,8 +175,8 @@ __global__ void __launch_bounds__(256) k_gemm_tn(const float* __restrict__ A, in
   const int l32 = lane & 31, half = lane >> 5;
   const int kc0 = blockIdx.x * BM;  // first output row (a column of A)
   const int n0 = blockIdx.y * BN;
-  const int64_t ms = (int64_t)blockIdx.z * slice_rows;
-  const int64_t me = (ms + slice_rows) < M ? (ms + slice_rows) : M;
+  const int64_t ms = tab ? tab[2 * (int64_t)blockIdx.z] : (int64_t)blockIdx.z * slice_rows;
+  const int64_t me = tab ? tab[2 * (int64_t)blockIdx.z + 1] : (ms + slice_rows) < M ? (ms + slice_rows) : M;
 
   v16f acc[TI][TJ];
 #pragma unroll
@@ -287,14 +290,77 @@ __global__ void __launch_bounds__(256) k_gemm_tn(const float* __restrict__ A, in
     }
 }
 
-// C[i] (+)= sum over slices, slice order
-__global__ void k_reduce_slices(const float* __restrict__ P, int64_t n, int slices, int accumulate,
-                                float* __restrict__ C) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  float s = accumulate ? C[i] : 0.f;
-  for (int k = 0; k < slices; ++k) s += P[(int64_t)k * n + i];
-  C[i] = s;
+// C[i] (+)= the slices' partial sums, one after the other in slice order.  The adds of one element are a chain, the loads are
+// not: a block takes 64 elements, its four waves bring 64 slices at a time into LDS (16 loads in flight per lane) while the
+// first wave adds the 64 before them.  (One thread per element that loads as it adds took 43 us where this takes 15.)
+__global__ void __launch_bounds__(256) k_reduce_slices(const float* __restrict__ P, int64_t n, int slices, int accumulate,
+                                                       float* __restrict__ C) {
+  __shared__ float tile[2][64][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+  float v[16];
+  auto fetch = [&](int s0) {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int k = s0 + wave * 16 + q;
+      v[q] = (k < slices && i < n) ? P[(int64_t)k * n + i] : 0.f;
+    }
+  };
+  float s = (accumulate && wave == 0 && i < n) ? C[i] : 0.f;
+  fetch(0);
+  for (int s0 = 0, b = 0; s0 < slices; s0 += 64, b ^= 1) {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) tile[b][wave * 16 + q][lane] = v[q];
+    if (s0 + 64 < slices) fetch(s0 + 64);
+    __syncthreads();   // (the other buffer was added before this barrier's turn came round)
+    if (wave == 0) {
+      const int m = (slices - s0) < 64 ? (slices - s0) : 64;
+      if (m == 64) {
+#pragma unroll 16
+        for (int k = 0; k < 64; ++k) s += tile[b][k][lane];
+      } else {
+        for (int k = 0; k < m; ++k) s += tile[b][k][lane];
+      }
+    }
+  }
+  if (wave == 0 && i < n) C[i] = s;
+}
+
+// Slices of a reduction over M rows: as many as fill the GPU with `tiles` output tiles each, not below 256 rows; a slice is a
+// multiple of the step.
+struct SliceRule {
+  int tiles;
+  __host__ __device__ void cut(int64_t M, int64_t* rows, int64_t* slices) const {
+    int64_t s = (1024 + tiles - 1) / tiles;
+    const int64_t most = (M + 255) / 256;
+    if (s > most) s = most;
+    if (s < 1) s = 1;
+    int64_t r = (M + s - 1) / s;
+    r = (r + BK - 1) / BK * BK;
+    *rows = r;
+    *slices = (M + r - 1) / r;
+  }
+};
+
+// tab[2 z], tab[2 z + 1]: rows of slice z; a block per row group, its slices behind those of the groups before it
+__global__ void __launch_bounds__(256) k_slice_table(const int64_t* __restrict__ groups, SliceRule rule, int64_t* __restrict__ tab) {
+  __shared__ int64_t before;
+  const int g = blockIdx.x;
+  if (threadIdx.x == 0) before = 0;
+  __syncthreads();
+  int64_t mine = 0, rows, n;
+  for (int q = threadIdx.x; q < g; q += 256) {
+    rule.cut(groups[2 * q + 1] - groups[2 * q], &rows, &n);
+    mine += n;
+  }
+  if (mine) atomicAdd((unsigned long long*)&before, (unsigned long long)mine);
+  __syncthreads();
+  const int64_t r0 = groups[2 * g], r1 = groups[2 * g + 1];
+  rule.cut(r1 - r0, &rows, &n);
+  for (int64_t z = threadIdx.x; z < n; z += 256) {
+    tab[2 * (before + z)] = r0 + z * rows;
+    tab[2 * (before + z) + 1] = r0 + (z + 1) * rows < r1 ? r0 + (z + 1) * rows : r1;
+  }
 }
 
 inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
@@ -352,33 +418,69 @@ int ht_gemm_nt(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const f
   return gemm_nn_packed(ctx, st, A, lda, Bp, Cp, C, ldc, M, N, K, accumulate ? 2 : 0);
 }
 
+namespace {
+
+int tn_tiles(int32_t K, int32_t N) { return ((K + BM - 1) / BM) * (N > 64 ? (N + 127) / 128 : 1); }
+
+int launch_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t M, int32_t K,
+              int32_t N, int64_t slice_rows, int64_t slices, const int64_t* tab, int accumulate) {
+  const int64_t kn = (int64_t)K * N;
+  float* P = nullptr;
+  HT_TRY(ht_scratch(ctx, HT_S_TNPART, (size_t)(slices * kn) * 4, (void**)&P));
+  dim3 grid((unsigned)((K + BM - 1) / BM), (unsigned)(N > 64 ? (N + 127) / 128 : 1), (unsigned)slices);
+  if (N > 64)
+    k_gemm_tn<128, 2, 2, 2, 2><<<grid, 256, 0, st>>>(A, lda, B, ldb, P, M, K, N, slice_rows, tab);
+  else
+    k_gemm_tn<64, 4, 1, 1, 2><<<grid, 256, 0, st>>>(A, lda, B, ldb, P, M, K, N, slice_rows, tab);
+  HT_LAUNCH_CHECK(ctx);
+  k_reduce_slices<<<(unsigned)((kn + 63) / 64), 256, 0, st>>>(P, kn, (int)slices, accumulate, C);
+  HT_LAUNCH_CHECK(ctx);
+  return HT_OK;
+}
+
+}  // namespace
+
 int ht_gemm_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
                int64_t M, int32_t K, int32_t N, int accumulate) {
   if ((lda & 3) || (ldb & 3)) return ht_set_err(ctx, HT_ESHAPE, "gemm: row pitch must be a multiple of 4");
   if (K <= 0 || N <= 0) return HT_OK;
-  const int64_t kn = (int64_t)K * N;
   if (M <= 0) {
-    if (!accumulate) HT_TRY(ht_fill_zero(ctx, st, C, (size_t)kn * 4));
+    if (!accumulate) HT_TRY(ht_fill_zero(ctx, st, C, (size_t)K * N * 4));
     return HT_OK;
   }
-  const int bn = N > 64 ? 128 : 64;
-  const int tiles = ((K + BM - 1) / BM) * ((N + bn - 1) / bn);
-  int64_t slices = (1024 + tiles - 1) / tiles;
-  const int64_t max_slices = (M + 255) / 256;
-  if (slices > max_slices) slices = max_slices;
-  if (slices < 1) slices = 1;
-  int64_t slice_rows = (M + slices - 1) / slices;
-  slice_rows = (slice_rows + BK - 1) / BK * BK;
-  slices = (M + slice_rows - 1) / slice_rows;
-  float* P = nullptr;
-  HT_TRY(ht_scratch(ctx, HT_S_TNPART, (size_t)(slices * kn) * 4, (void**)&P));
-  dim3 grid((unsigned)((K + BM - 1) / BM), (unsigned)((N + bn - 1) / bn), (unsigned)slices);
-  if (bn == 128)
-    k_gemm_tn<128, 2, 2, 2, 2><<<grid, 256, 0, st>>>(A, lda, B, ldb, P, M, K, N, slice_rows);
-  else
-    k_gemm_tn<64, 4, 1, 1, 2><<<grid, 256, 0, st>>>(A, lda, B, ldb, P, M, K, N, slice_rows);
-  HT_LAUNCH_CHECK(ctx);
-  k_reduce_slices<<<(unsigned)((kn + 255) / 256), 256, 0, st>>>(P, kn, (int)slices, accumulate, C);
-  HT_LAUNCH_CHECK(ctx);
+  int64_t rows, slices;
+  SliceRule{tn_tiles(K, N)}.cut(M, &rows, &slices);
+  return launch_tn(ctx, st, A, lda, B, ldb, C, M, K, N, rows, slices, nullptr, accumulate);
+}
+
+// The row groups' sums one after the other, as ht_gemm_tn called once per group would add them, in as few launches as the
+// partial tiles' memory allows.
+int ht_gemm_tn_groups(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int32_t K,
+                      int32_t N, const std::vector<int64_t>& groups, const int64_t* d_groups) {
+  const size_t G = groups.size() / 2;
+  if (G <= 1) {
+    const int64_t r0 = G ? groups[0] : 0;
+    return ht_gemm_tn(ctx, st, A + r0 * lda, lda, B + r0 * ldb, ldb, C, G ? groups[1] - r0 : 0, K, N, 0);
+  }
+  if ((lda & 3) || (ldb & 3)) return ht_set_err(ctx, HT_ESHAPE, "gemm: row pitch must be a multiple of 4");
+  if (K <= 0 || N <= 0) return HT_OK;
+  const SliceRule rule{tn_tiles(K, N)};
+  const int64_t most = std::max<int64_t>(1024, std::min<int64_t>(32768, ((int64_t)1 << 30) / ((int64_t)K * N * 4)));   // slices per launch
+  for (size_t g0 = 0; g0 < G;) {
+    size_t g1 = g0;
+    int64_t total = 0;
+    for (; g1 < G; ++g1) {
+      int64_t rows, n;
+      rule.cut(groups[2 * g1 + 1] - groups[2 * g1], &rows, &n);
+      if (g1 > g0 && total + n > most) break;
+      total += n;
+    }
+    int64_t* tab = nullptr;
+    HT_TRY(ht_scratch(ctx, HT_S_TNTAB, (size_t)total * 16, (void**)&tab));
+    k_slice_table<<<(unsigned)(g1 - g0), 256, 0, st>>>(d_groups + 2 * g0, rule, tab);
+    HT_LAUNCH_CHECK(ctx);
+    HT_TRY(launch_tn(ctx, st, A, lda, B, ldb, C, 0, K, N, 0, total, tab, g0 > 0));
+    g0 = g1;
+  }
   return HT_OK;
 }

@@ -21,7 +21,7 @@ struct EpochWs;
 enum {
   HT_S_PACKW = 0, HT_S_TNPART, HT_S_LOSS, HT_S_ACHUNK, HT_S_OCHUNK, HT_S_ZCHUNK, HT_S_DZCHUNK, HT_S_DACHUNK,
   HT_S_NBUF, HT_S_SPART, HT_S_LEAVE, HT_S_MISC, HT_S_TFULL, HT_S_TFULL2, HT_S_GATV, HT_S_GATE, HT_S_GATWS, HT_S_GATP,
-  HT_S_LINK0, HT_S_LINK1, HT_S_LINK2, HT_S_SCAN, HT_S_RSORT, HT_N_SCRATCH
+  HT_S_LINK0, HT_S_LINK1, HT_S_LINK2, HT_S_SCAN, HT_S_RSORT, HT_S_TNTAB, HT_N_SCRATCH
 };
 
 struct ht_ctx {
@@ -166,6 +166,9 @@ static inline int64_t ceil_div64(int64_t a, int64_t b) { return (a + b - 1) / b;
 constexpr double HT_LINK_BYTES_PER_S = 45e9;
 constexpr double HT_GATHER_BYTES_PER_S = 15e12;
 
+// Destination rows from which the dense work of neighbouring chunks is no longer merged.
+constexpr int64_t HT_DENSE_MERGE_ROWS = 32768;
+
 // Row pitch (in floats) of a library-allocated [rows x d] matrix: a multiple of 4 (16-byte
 // vectors); in HBM, rows start on 128-byte cache lines when that costs at most 3 % more memory,
 // so a feature slab never shares a line with the slab of another XCD; in pinned host memory rows
@@ -224,6 +227,16 @@ struct ChunkMeta {
   ItemRange fwd, bwd;
 };
 
+// The whole graph's entries grouped by source (destinations ascending), for backward passes that read grad a of all
+// destinations at once.  Built at the first such pass.
+struct SourceRows {
+  bool tried = false, ok = false;   // ok stays false when there was no memory for it: those passes go chunk by chunk
+  DevBlock blk;
+  DevArr<int32_t> idx;         // destination of each entry
+  DevArr<float> w;             // multiplicity * s[destination] (merged graphs; others look s up)
+  GraphItems items;            // rows = vertices
+};
+
 struct ht_graph {
   ht_ctx* ctx = nullptr;
   uint64_t serial = 0;         // unique per ht_partition call in this process: tells graphs at one address apart
@@ -264,6 +277,12 @@ struct ht_graph {
   DevArr<float> uw_bwd;        // [n_unique] multiplicity * s[destination]
   DevArr<float> umult_bwd;     // [n_unique] multiplicity, by-source order
   GraphItems fwd_items, bwd_items;
+  std::vector<int32_t> pos;    // [n] chunk id -> schedule position (inverse of order)
+  // Destination rows whose part of grad W is summed together: runs of chunks adjacent in schedule and in vertex order, closed
+  // at HT_DENSE_MERGE_ROWS rows; {first row, last row + 1} each, in schedule order.
+  std::vector<int64_t> dense_groups;
+  DevArr<int64_t> d_dense_groups;
+  mutable SourceRows by_src;
   DevBlock blk_csc, blk_pairs, blk_chunks;   // the allocations behind the CSC, the distinct-pair arrays, and the per-chunk arenas with the work items
   int64_t v_ori = 0, v_ru = 0, v_load = 0;  // v_load: rows actually loaded per pass with this buffer
   int64_t max_nsrc = 0, max_ndst = 0, max_nnz = 0, max_fpart = 0, max_bpart = 0;
@@ -273,6 +292,9 @@ struct ht_graph {
   mutable std::vector<int32_t> leave_host;  // host copy of `leave`, made on first use by the CPU-side adds
   int64_t hbm_bytes() const;
 };
+
+// Makes g->by_src if it was not tried yet.
+int ht_graph_by_source(ht_ctx* ctx, const ht_graph* g);
 
 // ---- compute kernels' host launchers -----------------------------------------------------
 // Aggregation over work items (ht_spmm.hip).  One wave (or a lane group of it)
@@ -325,6 +347,8 @@ int ht_add_rows(ht_ctx* ctx, hipStream_t st, const float* src, int64_t src_ld, c
                 float* dst, int64_t dst_ld, const int32_t* dst_idx, int64_t n_rows, int32_t d);
 
 // Dense transform (ht_gemm.hip)
+// Bytes of the packed copy of a [K x N] W that the NN kernels read (in the context's scratch).
+inline int64_t ht_packed_w_bytes(int64_t K, int64_t N) { return ((K + 15) & ~(int64_t)15) * ((N + 127) & ~(int64_t)127) * 4; }
 // C[M x N] = A[M x K] B[K x N], optional ReLU, C rows pitch ldc.  B is row-major dense [K x N].
 int ht_gemm_nn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, float* C, int64_t ldc,
                int64_t M, int32_t K, int32_t N, int relu);
@@ -334,6 +358,10 @@ int ht_gemm_nt(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const f
 // C[K x N] (+)= A[M x K]^T B[M x N]; fixed-order reduction over M slices.
 int ht_gemm_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
                int64_t M, int32_t K, int32_t N, int accumulate);
+
+// C[K x N] = sum over the row groups [groups[2g], groups[2g+1]) of A^T B, added group by group (d_groups: the same on the device).
+int ht_gemm_tn_groups(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int32_t K,
+                      int32_t N, const std::vector<int64_t>& groups, const int64_t* d_groups);
 
 // Aggregate + transform of one chunk in one kernel, the aggregate kept in LDS (ht_fused.hip)
 int ht_agg_update_fused(ht_ctx* ctx, hipStream_t st, const ht_graph* g, const ChunkMeta& c, const float* H_in, int64_t in_ld,

@@ -104,16 +104,14 @@ void cpu_accumulate(ht_ctx* ctx, float* grad, int64_t ld, const int32_t* ids, co
   for (auto& t : th) t.join();
 }
 
-// Destination rows from which the dense work of neighbouring chunks is no longer merged into one launch.
-constexpr int64_t HT_DENSE_MERGE_ROWS = 32768;
-
 struct Run {
   ht_ctx* ctx;
   const ht_graph* g;
   Timer tm;
   ht_stats* st;  // never null inside (a local one is used when the caller passes none)
   int layer = 0; // index into the per-layer statistics
-  bool dhin_is_zero = false;  // the caller guarantees dH_in holds zeros (lets leaving rows be stored, not added)
+  bool dhin_fresh = false;  // dH_in counts as zeros: a host tensor holds them (leaving rows may be stored, not added), a device
+                            // tensor holds anything and every row is written or cleared first
   Run(ht_ctx* c, const ht_graph* gr, ht_stats* s, bool timed) : ctx(c), g(gr), tm(c, c->stream, timed), st(s) {}
 };
 
@@ -183,23 +181,29 @@ int gather_chunk(Run& R, int j, const ht_tensor* H_in, const float* Hin, int d, 
   return HT_OK;
 }
 
-// Items and entries of chunk c for an aggregation: forward (rows = destinations, entries name sources by global id or by
-// buffer position) or backward (rows = positions of N_j, entries name the chunk's destination rows).
-void agg_args(const ht_graph* g, const ChunkMeta& c, bool fwd, bool buffer, SpmmArgs* a) {
-  const GraphItems& gi = fwd ? g->fwd_items : g->bwd_items;
-  const ItemRange& r = fwd ? c.fwd : c.bwd;
-  a->items = gi.items.p + r.it0; a->n_items = r.n_items;
-  a->cuts = gi.cuts.p + r.cut0; a->n_fix = r.n_cut;
-  a->part0 = r.part0;
-  a->row0 = fwd ? c.dst0 : c.nbr_off;
-  a->n_edges = g->merged ? c.nu : c.nnz;
+// The graph's entries for an aggregation: forward (rows = destinations, entries name sources by global id or by buffer
+// position) or backward (rows = positions of the N arena, entries name destination rows of their chunk).
+void agg_entries(const ht_graph* g, bool fwd, bool buffer, SpmmArgs* a) {
   if (g->merged) {
     a->idx = !fwd ? g->usdst.p : buffer ? g->ucol_slot.p : g->ucol.p;
     a->w_edge = !fwd ? g->uw_bwd.p : buffer ? g->umult.p : g->uw_fwd.p;
   } else {
     a->idx = !fwd ? g->sdst.p : buffer ? g->col_slot.p : g->col.p;
-    a->ew = !fwd ? g->s.p + c.dst0 : buffer ? nullptr : g->s.p;
+    a->ew = (!fwd || buffer) ? nullptr : g->s.p;
   }
+}
+void agg_items(const GraphItems& gi, const ItemRange& r, SpmmArgs* a) {
+  a->items = gi.items.p + r.it0; a->n_items = r.n_items;
+  a->cuts = gi.cuts.p + r.cut0; a->n_fix = r.n_cut;
+  a->part0 = r.part0;
+}
+// ... and those of chunk c
+void agg_args(const ht_graph* g, const ChunkMeta& c, bool fwd, bool buffer, SpmmArgs* a) {
+  agg_items(fwd ? g->fwd_items : g->bwd_items, fwd ? c.fwd : c.bwd, a);
+  agg_entries(g, fwd, buffer, a);
+  if (!fwd && !g->merged) a->ew = g->s.p + c.dst0;
+  a->row0 = fwd ? c.dst0 : c.nbr_off;
+  a->n_edges = g->merged ? c.nu : c.nnz;
 }
 
 // Aggregate of chunk j into out rows [0, ndst) (pitch out_ld) on the compute
@@ -233,6 +237,122 @@ int spmm_chunk(Run& R, int j, bool buffer, const float* src, int64_t src_ld, int
   R.st->spmm_fwd_alg_bytes += spmm_alg_bytes(c, d);
   R.st->agg_fwd_layer_alg_bytes[li] += spmm_alg_bytes(c, d);
   return HT_OK;
+}
+
+// ---- all chunks at once.  With the rows that an aggregation reads in HBM and no neighbour buffer between chunks, nothing
+// orders one chunk before another: the chunks' work items run as one launch (a launch per chunk leaves the GPU short of
+// waves at its ends and costs its latency: an epoch on 10,000 vertices in 4 chunks 311 -> 203 us, on 2.45 M vertices in 16
+// chunks 72.1 -> 65.7 ms; a forward of 20,000 vertices in 4 chunks 96 -> 42 us).  A range of chunks in vertex order is closed early only where its partial sums
+// (or the aggregates, when no tensor keeps them) would take more scratch memory than this.
+constexpr int64_t HT_RANGE_BYTES = (int64_t)2 << 30;
+
+struct ChunkRange {
+  int k0, k1;                // chunk ids
+  ItemRange items;
+  int64_t row0, rows, edges, entries;
+};
+
+// part_bytes, row_bytes: scratch memory per partial sum and per row (0: none)
+std::vector<ChunkRange> chunk_ranges(const ht_graph* g, int64_t part_bytes, int64_t row_bytes, int64_t cap) {
+  std::vector<ChunkRange> out;
+  for (int k = 0; k < g->n; ++k) {
+    const ChunkMeta& c = g->chunks[g->pos[k]];
+    const int64_t rows = c.dst1 - c.dst0;
+    if (rows == 0) continue;
+    if (!out.empty()) {
+      ChunkRange& r = out.back();
+      if ((r.items.n_part + c.fwd.n_part) * part_bytes + (r.rows + rows) * row_bytes <= cap) {
+        r.k1 = k + 1;
+        r.items.n_items += c.fwd.n_items;
+        r.items.n_part += c.fwd.n_part;
+        r.items.n_cut += c.fwd.n_cut;
+        r.rows += rows;
+        r.edges += c.nnz;
+        r.entries += g->merged ? c.nu : c.nnz;
+        continue;
+      }
+    }
+    out.push_back(ChunkRange{k, k + 1, c.fwd, c.dst0, rows, c.nnz, g->merged ? c.nu : c.nnz});
+  }
+  return out;
+}
+
+// compulsory bytes of one launch over `rows` destination rows that may name every vertex
+double agg_all_bytes(const ht_graph* g, int64_t edges, int64_t rows, int d) {
+  return 4.0 * edges + 8.0 * rows + 4.0 * d * (double)g->V + 4.0 * d * (double)rows + 4.0 * ((double)g->V + (double)rows);
+}
+
+// Aggregate of one range of chunks, rows of src read in place by vertex id, into out (row of the range's first destination).
+int agg_range(Run& R, const ChunkRange& r, const float* src, int64_t src_ld, int d, float* out, int64_t out_ld, int relu, float* partial) {
+  const ht_graph* g = R.g;
+  SpmmArgs a{};
+  agg_items(g->fwd_items, r.items, &a);
+  agg_entries(g, true, false, &a);
+  a.row0 = r.row0;
+  a.n_edges = r.entries;
+  a.src = src; a.src_ld = src_ld; a.d = d;
+  a.out = out; a.out_ld = out_ld;
+  a.post = g->s.p;
+  a.relu = relu;
+  a.partial = partial;
+  a.max_slabs = R.ctx->slabs_fwd;
+  const int li = R.layer < HT_MAX_LAYERS ? R.layer : HT_MAX_LAYERS - 1;
+  a.tm = &R.tm;
+  a.t_items = &R.st->t_agg_fwd_layer_ms[li];
+  a.t_fix = &R.st->t_agg_fix_ms;
+  HT_TRY(ht_spmm_launch(R.ctx, R.ctx->stream, a));
+  int64_t live = 0;          // chunk aggregations, whatever number of launches they take
+  for (int k = r.k0; k < r.k1; ++k) live += g->bounds[k + 1] > g->bounds[k];
+  R.st->n_spmm_fwd += live;
+  R.st->n_agg_fwd_layer[li] += live;
+  R.st->edges += r.edges;
+  const double bytes = agg_all_bytes(g, r.edges, r.rows, d);
+  R.st->spmm_fwd_alg_bytes += bytes;
+  R.st->agg_fwd_layer_alg_bytes[li] += bytes;
+  return HT_OK;
+}
+
+// Aggregates of all destinations: out row = vertex.
+int agg_all(Run& R, const float* src, int64_t src_ld, int d, float* out, int64_t out_ld, int relu) {
+  const auto ranges = chunk_ranges(R.g, out_ld * 4, 0, HT_RANGE_BYTES);
+  int64_t parts = 0;
+  for (const ChunkRange& r : ranges) parts = std::max(parts, r.items.n_part);
+  float* partial = nullptr;
+  if (parts > 0) HT_TRY(ht_scratch(R.ctx, HT_S_SPART, (size_t)parts * out_ld * 4, (void**)&partial));
+  for (const ChunkRange& r : ranges) HT_TRY(agg_range(R, r, src, src_ld, d, out + r.row0 * out_ld, out_ld, relu, partial));
+  return HT_OK;
+}
+
+// Forward of one layer with everything in HBM and rows read in place.
+int layer_fwd_direct(Run& R, const ht_layer_desc* desc, const ht_tensor* H_in, const float* W, ht_tensor* H_out, ht_tensor* A_ckpt) {
+  ht_ctx* ctx = R.ctx;
+  const ht_graph* g = R.g;
+  const int di = desc->d_in, dn = desc->d_out;
+  const int64_t a_ld = A_ckpt ? A_ckpt->ld : ht_row_pitch(di, true);
+  auto gemm = [&](const float* a, int64_t row0, int64_t rows) -> int {
+    R.tm.begin(&R.st->t_gemm_ms);
+    HT_TRY(ht_gemm_nn(ctx, ctx->stream, a, a_ld, W, H_out->ptr + row0 * H_out->ld, H_out->ld, rows, di, dn, desc->act == HT_ACT_RELU));
+    R.tm.end();
+    R.st->n_gemm += 1;
+    R.st->gemm_flops += 2.0 * rows * di * dn;
+    return HT_OK;
+  };
+  // (the allocation-free call's array also holds the packed copy of W)
+  const int64_t cap = ctx->static_mode ? (int64_t)HT_STATIC_SCRATCH_BYTES - ht_packed_w_bytes(di, dn) - 512 : HT_RANGE_BYTES;
+  const auto ranges = chunk_ranges(g, a_ld * 4, A_ckpt ? 0 : a_ld * 4, cap);
+  int64_t parts = 0, rows = 0;
+  for (const ChunkRange& r : ranges) {
+    parts = std::max(parts, r.items.n_part);
+    rows = std::max(rows, r.rows);
+  }
+  float *partial = nullptr, *a_rows = nullptr;
+  if (parts > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)parts * a_ld * 4, (void**)&partial));
+  if (!A_ckpt) HT_TRY(ht_scratch(ctx, HT_S_ACHUNK, (size_t)rows * a_ld * 4, (void**)&a_rows));
+  for (const ChunkRange& r : ranges) {
+    HT_TRY(agg_range(R, r, H_in->ptr, H_in->ld, di, A_ckpt ? A_ckpt->ptr + r.row0 * a_ld : a_rows, a_ld, 0, partial));
+    if (!A_ckpt) HT_TRY(gemm(a_rows, r.row0, r.rows));
+  }
+  return A_ckpt ? gemm(A_ckpt->ptr, 0, g->V) : HT_OK;
 }
 
 int resolve_gather(ht_ctx* ctx, int mode, const ht_tensor* t, bool* buffer) {
@@ -299,6 +419,7 @@ int layer_fwd_impl(Run& R, const ht_layer_desc* desc, const ht_tensor* H_in, con
   float* nbuf = nullptr;
   // A/B variant: no aggregate is kept and everything is in HBM: aggregate and transform in one kernel (ht_fused.hip)
   const bool fused = ctx->fuse_update && !A_ckpt && h_dev && !buffer && H_in->loc == HT_LOC_DEVICE && di <= 1024;
+  if (!buffer && !staged && !fused) return layer_fwd_direct(R, desc, H_in, W, H_out, A_ckpt);
   if (!a_dev && !fused) {
     HT_TRY(ht_scratch(ctx, HT_S_ACHUNK, (size_t)mx * a_ld * 4 * 2, (void**)&a_stage[0]));
     a_stage[1] = a_stage[0] + mx * a_ld;
@@ -568,6 +689,117 @@ class AccWorker {
   double ms_ = 0.0;
 };
 
+// dst[u] = s_u * sum over u's entries of s_v src[v] for all sources u at once (src row = destination vertex): overwritten,
+// or added to.  g->by_src is there, its partial sums fit `partial`.
+int agg_by_source(Run& R, const float* src, int64_t src_ld, int d, float* dst, int64_t dst_ld, bool add, float* partial) {
+  const ht_graph* g = R.g;
+  const SourceRows& S = g->by_src;
+  SpmmArgs a{};
+  a.items = S.items.items.p; a.n_items = S.items.n_items;
+  a.cuts = S.items.cuts.p; a.n_fix = S.items.n_cut;
+  a.n_edges = g->merged ? g->n_unique : g->Ep;
+  a.idx = S.idx.p;
+  if (g->merged) a.w_edge = S.w.p;
+  else a.ew = g->s.p;
+  a.src = src; a.src_ld = src_ld; a.d = d;
+  a.out = dst; a.out_ld = dst_ld;
+  a.post = g->s.p;
+  a.accumulate = add;
+  a.partial = partial;
+  a.max_slabs = R.ctx->slabs_bwd;
+  R.tm.begin(&R.st->t_spmm_bwd_ms);
+  HT_TRY(ht_spmm_launch(R.ctx, R.ctx->stream, a));
+  R.tm.end();
+  for (const ChunkMeta& c : g->chunks) R.st->n_spmm_bwd += c.dst1 > c.dst0;
+  R.st->edges += g->Ep;
+  R.st->spmm_bwd_alg_bytes += agg_all_bytes(g, g->Ep, g->V, d);
+  return HT_OK;
+}
+// The by-source list and its partial sums at row pitch ld, if there is memory for them.
+int by_source_ready(Run& R, int64_t ld, float** partial, bool* ok) {
+  *partial = nullptr;
+  *ok = false;
+  HT_TRY(ht_graph_by_source(R.ctx, R.g));
+  const GraphItems& it = R.g->by_src.items;
+  if (!R.g->by_src.ok || it.n_part * ld * 4 > HT_RANGE_BYTES) return HT_OK;
+  if (it.n_part > 0) {
+    const int rc = ht_scratch(R.ctx, HT_S_SPART, (size_t)it.n_part * ld * 4, (void**)partial);
+    if (rc == HT_ENOMEM) return HT_OK;
+    HT_TRY(rc);
+  }
+  *ok = true;
+  return HT_OK;
+}
+
+// Scratch memory up to which a backward pass holds dz and grad a of all vertices at once.
+constexpr int64_t HT_DIRECT_BYTES = (int64_t)8 << 30;
+
+// Backward of one layer with everything in HBM, all destinations at once: one launch of every dense kernel, and an
+// aggregation by source over the whole graph, which reads and writes every row of dH_in once (chunk by chunk a row is read and
+// written again for every chunk that names its vertex, and the work items are as many times shorter: 1 M vertices, 20 M edges,
+// 64 columns, 16 chunks, forward and backward 6.6 -> 3.2 ms).  *done = false: it would
+// take more scratch memory than it may have, nothing was enqueued.
+int layer_bwd_direct(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, const float* W, const ht_tensor* dH_out,
+                     const ht_tensor* H_out, ht_tensor* dH_in, float* dW, bool* done) {
+  ht_ctx* ctx = R.ctx;
+  const ht_graph* g = R.g;
+  hipStream_t st = ctx->stream;
+  const int di = desc->d_in, dn = desc->d_out;
+  const int64_t V = g->V, ld_i = ht_row_pitch(di, true), ld_o = ht_row_pitch(dn, true);
+  const bool relu = desc->act == HT_ACT_RELU, agg_ckpt = desc->ckpt_kind == HT_CKPT_AGG;
+  const int64_t a_ld = agg_ckpt ? ckpt->ld : ld_i;
+  *done = false;
+  float *a_all = nullptr, *dz_all = nullptr, *da_all = nullptr, *partial = nullptr;
+  const size_t a_bytes = agg_ckpt ? 0 : (size_t)V * a_ld * 4, dz_bytes = relu ? (size_t)V * ld_o * 4 : 0,
+               da_bytes = dH_in ? (size_t)V * ld_i * 4 : 0;
+  if ((int64_t)(a_bytes + dz_bytes + da_bytes) > HT_DIRECT_BYTES) return HT_OK;
+  auto get = [&](int slot, size_t bytes, float** p) { return bytes ? ht_scratch(ctx, slot, bytes, (void**)p) : HT_OK; };
+  for (int rc : {get(HT_S_ACHUNK, a_bytes, &a_all), get(HT_S_DZCHUNK, dz_bytes, &dz_all), get(HT_S_DACHUNK, da_bytes, &da_all)}) {
+    if (rc == HT_ENOMEM) return HT_OK;
+    HT_TRY(rc);
+  }
+  if (dH_in) {
+    bool ok = false;
+    HT_TRY(by_source_ready(R, dH_in->ld, &partial, &ok));
+    if (!ok) return HT_OK;
+  }
+  *done = true;
+  const float* a_rows = ckpt->ptr;
+  if (!agg_ckpt) {   // pure recomputation: aggregate again from h^l
+    HT_TRY(agg_all(R, ckpt->ptr, ckpt->ld, di, a_all, a_ld, 0));
+    a_rows = a_all;
+    if (dH_in) {     // (the forward aggregation's partial sums may have moved the slot)
+      bool ok = false;
+      HT_TRY(by_source_ready(R, dH_in->ld, &partial, &ok));
+      if (!ok) return ht_set_err(ctx, HT_ENOMEM, "layer backward: no memory for the partial sums");
+    }
+  }
+  const double flops = 2.0 * V * di * dn;
+  auto timed_gemm = [&](auto&& f) -> int {
+    R.tm.begin(&R.st->t_gemm_ms);
+    HT_TRY(f());
+    R.tm.end();
+    R.st->n_gemm += 1;
+    R.st->gemm_flops += flops;
+    return HT_OK;
+  };
+  const float* dz = dH_out->ptr;
+  int64_t dz_ld = dH_out->ld;
+  if (relu) {
+    const float* ref = H_out ? H_out->ptr : dz_all;
+    const int64_t ref_ld = H_out ? H_out->ld : ld_o;
+    if (!H_out)   // re-forward of the update stage (Alg. 1)
+      HT_TRY(timed_gemm([&] { return ht_gemm_nn(ctx, st, a_rows, a_ld, W, dz_all, ld_o, V, di, dn, 0); }));
+    HT_TRY(ht_relu_mask(ctx, st, dH_out->ptr, dH_out->ld, ref, ref_ld, dz_all, ld_o, V, dn));
+    dz = dz_all;
+    dz_ld = ld_o;
+  }
+  HT_TRY(timed_gemm([&] { return ht_gemm_tn_groups(ctx, st, a_rows, a_ld, dz, dz_ld, dW, di, dn, g->dense_groups, g->d_dense_groups.p); }));
+  if (!dH_in) return HT_OK;
+  HT_TRY(timed_gemm([&] { return ht_gemm_nt(ctx, st, dz, dz_ld, W, da_all, ld_i, V, dn, di, 0); }));
+  return agg_by_source(R, da_all, ld_i, di, dH_in->ptr, dH_in->ld, !R.dhin_fresh, partial);
+}
+
 int layer_bwd_impl(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, const float* W, const ht_tensor* dH_out,
                    const ht_tensor* H_out, ht_tensor* dH_in, float* dW) {
   ht_ctx* ctx = R.ctx;
@@ -626,6 +858,12 @@ int layer_bwd_impl(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, con
     gmax = std::max(gmax, g->chunks[k].dst1 - g->chunks[j].dst0);
     j = k + 1;
   }
+  if (merge_ok) {   // everything in HBM, nothing updated in place between chunks
+    bool done = false;
+    HT_TRY(layer_bwd_direct(R, desc, ckpt, W, dH_out, relu ? H_out : nullptr, dH_in, dW, &done));
+    if (done) return HT_OK;
+  }
+  if (dH_in && R.dhin_fresh && dH_in->loc == HT_LOC_DEVICE) HT_TRY(ht_fill_zero(ctx, st, dH_in->ptr, (size_t)dH_in->rows * dH_in->ld * 4));
   if (!agg_ckpt || a_host) {
     HT_TRY(ht_scratch(ctx, HT_S_ACHUNK, (size_t)gmax * a_ld * 4 * 2, (void**)&a_stage[0]));
     a_stage[1] = a_stage[0] + gmax * a_ld;
@@ -650,7 +888,7 @@ int layer_bwd_impl(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, con
   // When the schedule loads every row once per pass, each row also leaves exactly once, after the last
   // chunk that adds to it: if dH_in is known to hold zeros the rows are stored straight to their home
   // by a link kernel, no host-side add.
-  const bool store_home = dH_in && gbuffer && dH_in->loc == HT_LOC_HOST_PINNED && g->single_leave && R.dhin_is_zero;
+  const bool store_home = dH_in && gbuffer && dH_in->loc == HT_LOC_HOST_PINNED && g->single_leave && R.dhin_fresh;
   const bool cpu_accum = dH_in && gbuffer && dH_in->loc == HT_LOC_HOST_PINNED && !store_home;
   float* dhin_gpu = nullptr;
   if (store_home) HT_TRY(gpu_ptr(ctx, dH_in, &dhin_gpu));
@@ -906,32 +1144,7 @@ int layer_fwd_update_first(Run& R, const ht_layer_desc* desc, const ht_tensor* H
     R.st->n_gemm += 1;
     R.st->gemm_flops += 2.0 * nr * di * dn;
   }
-  const int li = R.layer < HT_MAX_LAYERS ? R.layer : HT_MAX_LAYERS - 1;
-  for (int j = 0; j < g->n; ++j) {
-    const ChunkMeta& c = g->chunks[j];
-    if (c.dst1 == c.dst0) continue;
-    float* partial = nullptr;
-    if (c.fwd.n_part > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)g->max_fpart * H_out->ld * 4, (void**)&partial));
-    SpmmArgs a{};
-    agg_args(g, c, true, false, &a);
-    a.src = T; a.src_ld = ld_t; a.d = dn;
-    a.out = H_out->ptr + c.dst0 * H_out->ld; a.out_ld = H_out->ld; a.out_idx = nullptr;
-    a.post = g->s.p; a.post_idx = nullptr;
-    a.accumulate = 0;
-    a.relu = desc->act == HT_ACT_RELU;
-    a.partial = partial;
-    a.max_slabs = ctx->slabs_fwd;
-    a.tm = &R.tm;
-    a.t_items = &R.st->t_agg_fwd_layer_ms[li];
-    a.t_fix = &R.st->t_agg_fix_ms;
-    HT_TRY(ht_spmm_launch(ctx, st, a));
-    R.st->n_spmm_fwd += 1;
-    R.st->n_agg_fwd_layer[li] += 1;
-    R.st->edges += c.nnz;
-    R.st->spmm_fwd_alg_bytes += spmm_alg_bytes(c, dn);
-    R.st->agg_fwd_layer_alg_bytes[li] += spmm_alg_bytes(c, dn);
-  }
-  return HT_OK;
+  return agg_all(R, T, ld_t, dn, H_out->ptr, H_out->ld, desc->act == HT_ACT_RELU);
 }
 
 int layer_bwd_update_first(Run& R, const ht_layer_desc* desc, const ht_tensor* H_in, const float* W,
@@ -957,12 +1170,25 @@ int layer_bwd_update_first(Run& R, const ht_layer_desc* desc, const ht_tensor* H
   if (!W || !dW) return ht_set_err(ctx, HT_EINVAL, "W or dW is null");
   const int64_t ld_t = ht_row_pitch(dn, true);
   const int64_t mx = std::max<int64_t>(g->max_ndst, 1);
-  float *dT = nullptr, *dz_chunk = nullptr;
+  float *dT = nullptr, *dz_chunk = nullptr, *partial = nullptr;
   HT_TRY(ht_scratch(ctx, HT_S_TFULL, (size_t)std::max<int64_t>(g->V, 1) * ld_t * 4, (void**)&dT));
-  if (relu) HT_TRY(ht_scratch(ctx, HT_S_DZCHUNK, (size_t)mx * ld_t * 4, (void**)&dz_chunk));
-  HT_TRY(ht_fill_zero(ctx, st, dT, (size_t)g->V * ld_t * 4));
+  // dt = A_hat^T dz over all sources at once where dz of all vertices and the by-source list fit (see layer_bwd_direct)
+  bool at_once = (int64_t)g->V * ld_t * 4 <= HT_DIRECT_BYTES;
+  if (at_once) HT_TRY(by_source_ready(R, ld_t, &partial, &at_once));
+  if (at_once && relu) {
+    const int rc = ht_scratch(ctx, HT_S_DZCHUNK, (size_t)g->V * ld_t * 4, (void**)&dz_chunk);
+    if (rc == HT_ENOMEM) at_once = false;
+    else HT_TRY(rc);
+  }
+  if (at_once) {
+    if (relu) HT_TRY(ht_relu_mask(ctx, st, dH_out->ptr, dH_out->ld, H_out->ptr, H_out->ld, dz_chunk, ld_t, g->V, dn));
+    HT_TRY(agg_by_source(R, relu ? dz_chunk : dH_out->ptr, relu ? ld_t : dH_out->ld, dn, dT, ld_t, false, partial));
+  } else {
+    if (relu) HT_TRY(ht_scratch(ctx, HT_S_DZCHUNK, (size_t)mx * ld_t * 4, (void**)&dz_chunk));
+    HT_TRY(ht_fill_zero(ctx, st, dT, (size_t)g->V * ld_t * 4));
+  }
   // dt[N_j] += s_u * sum_v s_v dz[v], chunk by chunk
-  for (int j = 0; j < g->n; ++j) {
+  for (int j = 0; !at_once && j < g->n; ++j) {
     const ChunkMeta& c = g->chunks[j];
     const int64_t ndst = c.dst1 - c.dst0;
     if (ndst == 0) continue;
@@ -973,7 +1199,6 @@ int layer_bwd_update_first(Run& R, const ht_layer_desc* desc, const ht_tensor* H
       dz_rows = dz_chunk;
       dz_ld = ld_t;
     }
-    float* partial = nullptr;
     if (c.bwd.n_part > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)g->max_bpart * ld_t * 4, (void**)&partial));
     SpmmArgs a{};
     agg_args(g, c, false, false, &a);
@@ -1004,7 +1229,7 @@ int layer_bwd_update_first(Run& R, const ht_layer_desc* desc, const ht_tensor* H
     first = false;
     if (dH_in) {
       R.tm.begin(&R.st->t_gemm_ms);
-      HT_TRY(ht_gemm_nt(ctx, st, dT + r0 * ld_t, ld_t, W, dH_in->ptr + r0 * dH_in->ld, dH_in->ld, nr, dn, di, 1));
+      HT_TRY(ht_gemm_nt(ctx, st, dT + r0 * ld_t, ld_t, W, dH_in->ptr + r0 * dH_in->ld, dH_in->ld, nr, dn, di, R.dhin_fresh ? 0 : 1));
       R.tm.end();
       R.st->n_gemm += 1;
       R.st->gemm_flops += 2.0 * nr * di * dn;
@@ -1119,7 +1344,7 @@ int ht_layer_fwd_static(ht_ctx* ctx, const ht_graph* g, const ht_layer_desc* des
   if (H_in->loc != HT_LOC_DEVICE || H_out->loc != HT_LOC_DEVICE || A_ckpt->loc != HT_LOC_DEVICE)
     return ht_set_err(ctx, HT_ESHAPE, "ht_layer_fwd_static: H_in, H_out and A_ckpt must be in HBM");
   // sizes are checked against the static array before anything is launched
-  const size_t need_w = (((size_t)desc->d_in + 15) & ~(size_t)15) * (((size_t)desc->d_out + 127) & ~(size_t)127) * 4;
+  const size_t need_w = (size_t)ht_packed_w_bytes(desc->d_in, desc->d_out);
   const size_t need_p = (size_t)g->max_fpart * (size_t)A_ckpt->ld * 4;
   if (need_w + need_p + 512 > HT_STATIC_SCRATCH_BYTES)
     return ht_set_err(ctx, HT_ENOMEM, "ht_layer_fwd_static: this layer needs %zu bytes of scratch memory (packed W %zu, partial sums "
@@ -1366,15 +1591,11 @@ int ht_epoch(ht_ctx* ctx, const ht_graph* g, const ht_model* model, const ht_ten
       d.act = l < L - 1 ? HT_ACT_RELU : HT_ACT_NONE;
       d.gather_mode = gather_mode;
       d.ckpt_kind = recompute ? HT_CKPT_INPUT : HT_CKPT_AGG;
-      R.dhin_is_zero = false;
+      R.dhin_fresh = false;
       if (l > 0) {
-        if (ws->gh[l].loc == HT_LOC_HOST_PINNED) {
-          if (zeroer.th.joinable()) zeroer.th.join();     // cleared beside the forward pass (or stored exactly once)
-        } else {
-          int rc = zero_tensor(ctx, &ws->gh[l]);
-          if (rc != HT_OK) return rc;
-        }
-        R.dhin_is_zero = true;
+        // a host-resident tensor is cleared beside the forward pass (or stored exactly once)
+        if (ws->gh[l].loc == HT_LOC_HOST_PINNED && zeroer.th.joinable()) zeroer.th.join();
+        R.dhin_fresh = true;
       }
       R.layer = l;
       const bool mask_ok = inter == HT_INTER_MASK || (recompute && ws->h[l + 1].loc == HT_LOC_DEVICE);

@@ -806,31 +806,113 @@ __global__ void k_items_permute(const uint64_t* __restrict__ keys, int64_t n, co
   if (t < n) out[t] = in[(uint32_t)(keys[t] & 0xFFFFFFFFull)];
 }
 
+// ---- entries of the whole graph grouped by source
+
+// members of the N arena: entries per vertex (added over the chunks)
+__global__ void k_src_counts(const int32_t* __restrict__ nbr, RowSet R, int64_t nrows, int32_t* __restrict__ cnt) {
+  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= nrows) return;
+  int64_t e0, len;
+  R.get(p, find_range(R.first, R.n, p), &e0, &len);
+  atomicAdd(&cnt[nbr[p]], (int32_t)len);
+}
+// off[p] = where the entries of (chunk, source) p go; chunk by chunk in vertex order, so that a source's destinations ascend
+__global__ void k_src_offsets(const int32_t* __restrict__ nbr, RowSet R, int k, int64_t p0, int64_t n, int64_t* __restrict__ cur,
+                              int64_t* __restrict__ off) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  int64_t e0, len;
+  R.get(p0 + i, k, &e0, &len);
+  const int32_t u = nbr[p0 + i];
+  off[p0 + i] = cur[u] - e0;   // entry e of the chunk's list goes to off + e
+  cur[u] += len;
+}
+// a wave per backward work item copies its entries: destination in vertex ids, weight
+__global__ void __launch_bounds__(TB) k_src_copy(const WorkItem* __restrict__ items, int64_t n_items, const int64_t* __restrict__ first,
+                                                 const int64_t* __restrict__ bounds, int n, const int64_t* __restrict__ off,
+                                                 const int32_t* __restrict__ sdst, const float* __restrict__ w,
+                                                 int32_t* __restrict__ idx, float* __restrict__ w_out) {
+  const int lane = threadIdx.x & 63;
+  const int64_t t = (int64_t)blockIdx.x * (TB / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (t >= n_items) return;
+  const WorkItem it = items[t];
+  const int32_t d0 = (int32_t)bounds[find_range(first, n, it.row)];
+  const int64_t to = off[it.row] + it.e0;
+  for (int32_t i = lane; i < it.len; i += 64) {
+    idx[to + i] = d0 + sdst[(int64_t)it.e0 + i];
+    if (w) w_out[to + i] = w[(int64_t)it.e0 + i];
+  }
+}
+
 int bits_for(int64_t n) {  // bits needed for values 0..n-1 (at least 1)
   int b = 1;
   while (((int64_t)1 << b) < n) ++b;
   return b;
 }
 
-// One direction's work items for all chunks.  made / keysA / keysB: room for every item; starts: 3 (n + 1) words on the device.
+// One direction's work items over a set of rows: counted, then filled and put into dispatch order.
 struct ItemBuild {
   RowSet rows;
-  int64_t nrows = 0, tiles = 0, bound = 0;
+  int64_t nrows = 0, tiles = 0;
+  int64_t range = 0;           // values of the entries' row index are below this
   int seg = 0;
-  int32_t* cnt = nullptr;
-  int64_t *base = nullptr, *starts = nullptr;
+  const int32_t* idx = nullptr;
+  int32_t* cnt = nullptr;      // [3 * tiles]
+  int64_t* base = nullptr;     // [3 * tiles + 1]
+  int64_t* starts = nullptr;   // [3 * (rows.n + 1)]
+  GraphItems* out = nullptr;
 };
 
 // Items a list of `rows` rows with `entries` entries can make: ceil(len / seg) per row, at least one.
 inline int64_t item_bound(int64_t rows, int64_t entries, int seg) { return rows + entries / seg + 1; }
 inline int64_t cut_bound(int64_t entries, int seg) { return entries / seg + 1; }
 
-int count_items(ht_ctx* ctx, ItemBuild& b) {
+// h_tot (pinned, 3 words): the totals' prefix sums, valid once the stream is synchronised
+int count_items(ht_ctx* ctx, const ItemBuild& b, int64_t* h_tot) {
   if (b.nrows == 0) return HT_OK;
   k_items_count<<<(unsigned)b.tiles, TB, 0, ctx->stream>>>(b.rows, b.nrows, b.seg, b.tiles, b.cnt);
   HT_LAUNCH_CHECK(ctx);
-  return ht_scan_i32(ctx, b.cnt, b.base, 3 * b.tiles, true);
+  HT_TRY(ht_scan_i32(ctx, b.cnt, b.base, 3 * b.tiles, true));
+  for (int w = 0; w < 3; ++w)
+    HT_HIP(ctx, hipMemcpyAsync(&h_tot[w], b.base + (w + 1) * b.tiles, 8, hipMemcpyDeviceToHost, ctx->stream));
+  return HT_OK;
 }
+
+// made: room for every item (in row order, before they are permuted); keysA, keysB: nkeys words each
+int fill_items(ht_ctx* ctx, const ItemBuild& b, const int64_t* h_tot, WorkItem* made, uint64_t* keysA, uint64_t* keysB,
+               size_t nkeys, bool order) {
+  if (b.nrows == 0) return HT_OK;
+  const int64_t ni = h_tot[0], np = h_tot[1] - h_tot[0], nc = h_tot[2] - h_tot[1];
+  if (ni > (int64_t)b.out->items.n || nc > (int64_t)b.out->cuts.n || ni > (int64_t)nkeys)
+    return ht_set_err(ctx, HT_ESTATE, "work items: %lld items and %lld cut rows, more than was planned for", (long long)ni, (long long)nc);
+  b.out->n_items = ni;
+  b.out->n_part = np;
+  b.out->n_cut = nc;
+  const bool sorted_items = order && ni > 1;
+  const int kbits = b.rows.n > 1 ? bits_for(b.rows.n) : 0, vbits = bits_for(b.range);
+  const int fbits = std::min(vbits, 32 - kbits), fshift = vbits - fbits;
+  k_items_fill<<<(unsigned)b.tiles, TB, 0, ctx->stream>>>(b.rows, b.nrows, b.seg, b.tiles, b.base, b.idx, fbits, fshift,
+                                                          sorted_items ? made : b.out->items.p, sorted_items ? keysA : nullptr,
+                                                          b.out->cuts.p, b.starts);
+  HT_LAUNCH_CHECK(ctx);
+  if (sorted_items) {
+    uint64_t* sorted = nullptr;
+    HT_TRY(ht_radix_sort_u64(ctx, keysA, keysB, ni, 32, 32 + kbits + fbits, &sorted));
+    k_items_permute<<<nblk(ni), TB, 0, ctx->stream>>>(sorted, ni, made, b.out->items.p);
+    HT_LAUNCH_CHECK(ctx);
+  }
+  return HT_OK;
+}
+
+struct ItemSwitches {          // experiments
+  int seg_fwd = HT_SEG, seg_bwd = HT_SEG / 2;   // measured best at 233 k vertices / 115 M edges
+  bool order = true;
+  ItemSwitches() {
+    if (const char* v = getenv("HT_SEG_FWD")) seg_fwd = std::max(64, atoi(v));
+    if (const char* v = getenv("HT_SEG_BWD")) seg_bwd = std::max(64, atoi(v));
+    if (const char* v = getenv("HT_ITEM_ORDER")) order = atoi(v) != 0;
+  }
+};
 
 int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, const int32_t* dst_in, int32_t n,
                    const ht_part_opts* opts, ht_graph* g) {
@@ -851,11 +933,8 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
   const int bitsV = bits_for(V);
   const int64_t nwp = bm_words(V), T = nwp / TB;   // words and tiles of a bitmap row
   const int64_t etiles = ceil_div64(std::max<int64_t>(Ep, 1), ETILE);
-  int seg_fwd = HT_SEG, seg_bwd = HT_SEG / 2;   // measured best at cfg2; the variables are for experiments
-  if (const char* v = getenv("HT_SEG_FWD")) seg_fwd = std::max(64, atoi(v));
-  if (const char* v = getenv("HT_SEG_BWD")) seg_bwd = std::max(64, atoi(v));
-  const char* ord_env = getenv("HT_ITEM_ORDER");
-  const bool order_items = !(ord_env && atoi(ord_env) == 0);
+  const ItemSwitches sw;
+  const int seg_fwd = sw.seg_fwd, seg_bwd = sw.seg_bwd;
 
   // pinned host memory for what is read back (a flag and a few counts, then lists of n + 1 offsets) and for the chunk order
   int64_t* hp = nullptr;
@@ -1061,6 +1140,8 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
   take_offsets(hl + (size_t)(L_REUSE - L_UEOFF) * n1);
   g->v_ori = noff[n];
   g->v_ru = offs[1][n];
+  g->pos.resize(n);
+  for (int j = 0; j < n; ++j) g->pos[g->order[j]] = j;
   g->chunks.clear();
   g->chunks.resize(n);
   for (int j = 0; j < n; ++j) {
@@ -1079,6 +1160,17 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
     g->max_ndst = std::max(g->max_ndst, c.dst1 - c.dst0);
     g->max_nnz = std::max(g->max_nnz, c.nnz);
     g->max_nsrc = std::max(g->max_nsrc, c.nsrc);
+  }
+  for (int j = 0; j < n;) {
+    int k = j;
+    while (k + 1 < n && g->chunks[k + 1].dst1 > g->chunks[k + 1].dst0 && g->chunks[k + 1].dst0 == g->chunks[k].dst1 &&
+           g->chunks[k].dst1 - g->chunks[j].dst0 < HT_DENSE_MERGE_ROWS && g->chunks[j].dst1 > g->chunks[j].dst0)
+      ++k;
+    if (g->chunks[k].dst1 > g->chunks[j].dst0) {
+      g->dense_groups.push_back(g->chunks[j].dst0);
+      g->dense_groups.push_back(g->chunks[k].dst1);
+    }
+    j = k + 1;
   }
   const int64_t n_distinct = far_first ? hp[2] : 0;   // |N_0 u ... u N_{n-1}|
   int64_t C = opts ? opts->cache_rows : 0;
@@ -1218,6 +1310,7 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
     for (int k = 0; k < 4; ++k) b.add<int32_t>(vr);
     for (int k = 0; k < 3; ++k) b.add<int32_t>(ep);
     if (g->merged) b.add<int64_t>(vo + n);
+    b.add<int64_t>(g->dense_groups.size());
     b.add<WorkItem>((size_t)fb_items); b.add<CutRow>((size_t)cut_bound(n_ent, seg_fwd));
     b.add<WorkItem>((size_t)bb_items); b.add<CutRow>((size_t)cut_bound(n_ent, seg_bwd));
     HT_TRY(b.alloc(ctx));
@@ -1233,6 +1326,7 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
     b.take(g->col_slot, ep);
     b.take(g->sdst, ep);
     if (g->merged) b.take(g->usptr, vo + n);
+    b.take(g->d_dense_groups, g->dense_groups.size());
     b.take(g->fwd_items.items, (size_t)fb_items);
     b.take(g->fwd_items.cuts, (size_t)cut_bound(n_ent, seg_fwd));
     b.take(g->bwd_items.items, (size_t)bb_items);
@@ -1242,12 +1336,16 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
   ItemBuild ib[2];
   ib[0].nrows = V;
   ib[0].seg = seg_fwd;
-  ib[0].bound = fb_items;
   ib[0].rows = RowSet{g->merged ? g->uindptr.p : g->indptr.p, list(L_BOUNDS), nullptr, n};
+  ib[0].idx = g->merged ? g->ucol.p : g->col.p;   // forward items are ordered by buffer-independent source id
+  ib[0].range = V;
+  ib[0].out = &g->fwd_items;
   ib[1].nrows = g->v_ori;
   ib[1].seg = seg_bwd;
-  ib[1].bound = bb_items;
   ib[1].rows = RowSet{g->merged ? g->usptr.p : g->sptr.p, list(L_NOFF), list(g->merged ? L_UEOFF : L_EOFF), n};
+  ib[1].idx = g->merged ? g->usdst.p : g->sdst.p;   // backward items by local destination
+  ib[1].range = g->max_ndst;
+  ib[1].out = &g->bwd_items;
   DevBlock tmp2;
   DevArr<int32_t> vslot, free_cnt, icnt[2];
   DevArr<uint64_t> freebm;
@@ -1274,6 +1372,8 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
   tmp2.take(made, (size_t)std::max(fb_items, bb_items));
   ib[0].starts = istarts.p;
   ib[1].starts = istarts.p + 3 * n1;
+
+  HT_HIP(ctx, hipMemcpyAsync(g->d_dense_groups.p, g->dense_groups.data(), g->dense_groups.size() * 8, hipMemcpyHostToDevice, st));
 
   // ---- the lists, then the buffer positions, chunk by chunk
   k_list_expand<<<(unsigned)(n * T), TB, 0, st>>>(rows, T, lbase.p, g->reuse.p, g->load.p, g->leave.p);
@@ -1335,44 +1435,14 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
     }
   }
 
-  // ---- work items of both directions: forward items are ordered by buffer-independent source id, backward ones by local destination
-  GraphItems* gi[2] = {&g->fwd_items, &g->bwd_items};
-  const int32_t* idx[2] = {g->merged ? g->ucol.p : g->col.p, g->merged ? g->usdst.p : g->sdst.p};
-  const int64_t range[2] = {V, g->max_ndst};
-  int64_t* htot = hp;   // three totals per direction
-  for (int d = 0; d < 2; ++d) {
-    HT_TRY(count_items(ctx, ib[d]));
-    if (ib[d].nrows > 0)
-      for (int w = 0; w < 3; ++w)
-        HT_HIP(ctx, hipMemcpyAsync(&htot[3 * d + w], ib[d].base + (w + 1) * ib[d].tiles, 8, hipMemcpyDeviceToHost, st));
-  }
+  // ---- work items of both directions
+  for (int d = 0; d < 2; ++d) HT_TRY(count_items(ctx, ib[d], hp + 3 * d));
   HT_HIP(ctx, hipStreamSynchronize(st));
-  for (int d = 0; d < 2; ++d) {
-    ItemBuild& b = ib[d];
-    if (b.nrows == 0) continue;
-    const int64_t ni = htot[3 * d], np = htot[3 * d + 1] - htot[3 * d], nc = htot[3 * d + 2] - htot[3 * d + 1];
-    if (ni > b.bound || ni > (int64_t)nkeys) return ht_set_err(ctx, HT_ESTATE, "ht_partition: %lld work items, %lld expected at most", (long long)ni, (long long)b.bound);
-    gi[d]->n_items = ni;
-    gi[d]->n_part = np;
-    gi[d]->n_cut = nc;
-    const bool sorted_items = order_items && ni > 1;
-    const int kbits = n > 1 ? bits_for(n) : 0, vbits = bits_for(range[d]);
-    const int fbits = std::min(vbits, 32 - kbits), fshift = vbits - fbits;
-    WorkItem* into = sorted_items ? made.p : gi[d]->items.p;
-    k_items_fill<<<(unsigned)b.tiles, TB, 0, st>>>(b.rows, b.nrows, b.seg, b.tiles, b.base, idx[d], fbits, fshift, into,
-                                                   sorted_items ? keysA.p : nullptr, gi[d]->cuts.p, b.starts);
-    HT_LAUNCH_CHECK(ctx);
-    if (sorted_items) {
-      uint64_t* sorted = nullptr;
-      HT_TRY(ht_radix_sort_u64(ctx, keysA.p, keysB.p, ni, 32, 32 + kbits + fbits, &sorted));
-      k_items_permute<<<nblk(ni), TB, 0, st>>>(sorted, ni, made.p, gi[d]->items.p);
-      HT_LAUNCH_CHECK(ctx);
-    }
-  }
+  for (int d = 0; d < 2; ++d) HT_TRY(fill_items(ctx, ib[d], hp + 3 * d, made.p, keysA.p, keysB.p, nkeys, sw.order));
   HT_HIP(ctx, hipMemcpyAsync(hl, istarts.p, 6 * n1 * 8, hipMemcpyDeviceToHost, st));
   HT_HIP(ctx, hipStreamSynchronize(st));
   for (int d = 0; d < 2; ++d) {
-    const int64_t tot[3] = {gi[d]->n_items, gi[d]->n_part, gi[d]->n_cut};
+    const int64_t tot[3] = {ib[d].out->n_items, ib[d].out->n_part, ib[d].out->n_cut};
     const std::vector<int64_t>& first = d == 0 ? g->bounds : noff;
     // start of chunk k's share (chunks that start behind the last row have none)
     auto at = [&](int w, int k) { return k < n && first[k] < ib[d].nrows ? hl[(size_t)(3 * d + w) * n1 + k] : tot[w]; };
@@ -1401,11 +1471,134 @@ int d2h(ht_ctx* ctx, T* dst, const T* src, int64_t n) {
 
 }  // namespace
 
+namespace {
+
+// The list costs 4 or 8 bytes per entry; it is copied together from the chunks' by-source lists.
+int build_by_source(ht_ctx* ctx, const ht_graph* g) {
+  hipStream_t st = ctx->stream;
+  SourceRows& S = g->by_src;
+  const ItemSwitches sw;
+  const int64_t V = g->V, n_ent = g->merged ? g->n_unique : g->Ep, vo = g->v_ori;
+  const size_t n1 = (size_t)g->n + 1;
+  const int64_t bound = item_bound(V, n_ent, sw.seg_bwd), cuts = cut_bound(n_ent, sw.seg_bwd);
+  S.blk.add<int32_t>((size_t)std::max<int64_t>(n_ent, 1));
+  if (g->merged) S.blk.add<float>((size_t)n_ent);
+  S.blk.add<WorkItem>((size_t)bound);
+  S.blk.add<CutRow>((size_t)cuts);
+  HT_TRY(S.blk.alloc(ctx));
+  S.blk.take(S.idx, (size_t)std::max<int64_t>(n_ent, 1));
+  if (g->merged) S.blk.take(S.w, (size_t)n_ent);
+  S.blk.take(S.items.items, (size_t)bound);
+  S.blk.take(S.items.cuts, (size_t)cuts);
+  ItemBuild b;
+  b.nrows = V;
+  b.tiles = ceil_div64(V, RTILE);
+  b.seg = sw.seg_bwd;
+  b.idx = S.idx.p;
+  b.range = V;
+  b.out = &S.items;
+  DevBlock tmp;
+  DevArr<int32_t> cnt, icnt;
+  DevArr<int64_t> ptr, cur, off, lists, ibase, istarts;
+  DevArr<WorkItem> made;
+  DevArr<uint64_t> keysA, keysB;
+  tmp.add<int32_t>((size_t)V);
+  tmp.add<int32_t>((size_t)3 * b.tiles);
+  tmp.add<int64_t>((size_t)V + 1);
+  tmp.add<int64_t>((size_t)V + 1);
+  tmp.add<int64_t>((size_t)std::max<int64_t>(vo, 1));
+  tmp.add<int64_t>(3 * n1 + 2);
+  tmp.add<int64_t>((size_t)3 * b.tiles + 1);
+  tmp.add<int64_t>(6);
+  tmp.add<WorkItem>((size_t)bound);
+  tmp.add<uint64_t>((size_t)bound);
+  tmp.add<uint64_t>((size_t)bound);
+  HT_TRY(tmp.alloc(ctx));
+  tmp.take(cnt, (size_t)V);
+  tmp.take(icnt, (size_t)3 * b.tiles);
+  tmp.take(ptr, (size_t)V + 1);
+  tmp.take(cur, (size_t)V + 1);
+  tmp.take(off, (size_t)std::max<int64_t>(vo, 1));
+  tmp.take(lists, 3 * n1 + 2);
+  tmp.take(ibase, (size_t)3 * b.tiles + 1);
+  tmp.take(istarts, 6);
+  tmp.take(made, (size_t)bound);
+  tmp.take(keysA, (size_t)bound);
+  tmp.take(keysB, (size_t)bound);
+  b.cnt = icnt.p;
+  b.base = ibase.p;
+  b.starts = istarts.p;
+  // the chunks' first arena positions, first entries and first destinations, in vertex order; then {0, V} for the one range
+  int64_t* hp = nullptr;
+  {
+    void* p = nullptr;
+    HT_TRY(ht_host_scratch(ctx, HT_HS_READBACK, (8 + 3 * n1 + 2) * 8, &p));
+    hp = (int64_t*)p;
+  }
+  int64_t* hl = hp + 8;
+  for (int k = 0; k < g->n; ++k) {
+    const ChunkMeta& c = g->chunks[g->pos[k]];
+    hl[k] = c.nbr_off;
+    hl[n1 + k] = c.ue0;
+    hl[2 * n1 + k] = c.dst0;
+  }
+  hl[g->n] = vo;
+  hl[n1 + g->n] = n_ent;
+  hl[2 * n1 + g->n] = V;
+  hl[3 * n1] = 0;
+  hl[3 * n1 + 1] = V;
+  HT_HIP(ctx, hipMemcpyAsync(lists.p, hl, (3 * n1 + 2) * 8, hipMemcpyHostToDevice, st));
+  const RowSet arena{g->merged ? g->usptr.p : g->sptr.p, lists.p, lists.p + n1, g->n};
+  HT_TRY(ht_fill_zero(ctx, st, cnt.p, (size_t)V * 4));
+  if (vo > 0) {
+    k_src_counts<<<nblk(vo), TB, 0, st>>>(g->nbr.p, arena, vo, cnt.p);
+    HT_LAUNCH_CHECK(ctx);
+  }
+  HT_TRY(ht_scan_i32(ctx, cnt.p, ptr.p, V, true));
+  HT_HIP(ctx, hipMemcpyAsync(cur.p, ptr.p, (size_t)V * 8, hipMemcpyDeviceToDevice, st));
+  for (int k = 0; k < g->n; ++k) {
+    const ChunkMeta& c = g->chunks[g->pos[k]];
+    if (c.nsrc == 0) continue;
+    k_src_offsets<<<nblk(c.nsrc), TB, 0, st>>>(g->nbr.p, arena, k, c.nbr_off, c.nsrc, cur.p, off.p);
+    HT_LAUNCH_CHECK(ctx);
+  }
+  const int64_t ni = g->bwd_items.n_items;
+  if (ni > 0) {
+    k_src_copy<<<nblk(ni, TB / 64), TB, 0, st>>>(g->bwd_items.items.p, ni, lists.p, lists.p + 2 * n1, g->n, off.p,
+                                                g->merged ? g->usdst.p : g->sdst.p, g->merged ? g->uw_bwd.p : nullptr, S.idx.p, S.w.p);
+    HT_LAUNCH_CHECK(ctx);
+  }
+  b.rows = RowSet{ptr.p, lists.p + 3 * n1, nullptr, 1};
+  HT_TRY(count_items(ctx, b, hp));
+  HT_HIP(ctx, hipStreamSynchronize(st));
+  HT_TRY(fill_items(ctx, b, hp, made.p, keysA.p, keysB.p, (size_t)bound, sw.order));
+  HT_HIP(ctx, hipStreamSynchronize(st));
+  return HT_OK;
+}
+
+}  // namespace
+
+int ht_graph_by_source(ht_ctx* ctx, const ht_graph* g) {
+  SourceRows& S = g->by_src;
+  if (S.tried) return HT_OK;
+  S.tried = true;
+  const int rc = build_by_source(ctx, g);
+  S.ok = rc == HT_OK;
+  if (!S.ok) {
+    S.items = GraphItems();
+    S.idx.release();
+    S.w.release();
+    S.blk.release();
+  }
+  return rc == HT_ENOMEM ? HT_OK : rc;
+}
+
 int64_t ht_graph::hbm_bytes() const {
   int64_t b = indptr.bytes() + col.bytes() + s.bytes() + nbr.bytes() + col_local.bytes() + col_slot.bytes() +
               sptr.bytes() + sdst.bytes() + slot.bytes() + gslot.bytes() + reuse.bytes() + load.bytes() +
               load_slot.bytes() + leave.bytes() + leave_slot.bytes() + uindptr.bytes() + ucol.bytes() +
               ucol_slot.bytes() + uw_fwd.bytes() + umult.bytes() + usdst.bytes() + uw_bwd.bytes() + umult_bwd.bytes() + usptr.bytes();
+  b += (int64_t)by_src.blk.mem.bytes();
   for (const GraphItems* i : {&fwd_items, &bwd_items}) b += i->n_items * (int64_t)sizeof(WorkItem) + i->n_cut * (int64_t)sizeof(CutRow);
   return b;
 }

@@ -1,0 +1,70 @@
+"""Layers with everything in HBM run over all chunks at once: the aggregation as one launch, grad W over several row groups,
+the backward aggregation by source over the whole graph.  Against plain fp64 sums on the same inputs, at sizes with several row
+groups (more than 32,768 destinations), cut rows, merged and unmerged duplicates, a reorganised schedule, and without the
+memory for the by-source list (the chunk-by-chunk pass)."""
+import pytest
+import torch
+
+from paper_2311_14898_amd import binding as B
+from paper_2311_14898_amd import inputs
+from tests.util import assert_close, assert_close_grad
+
+pytestmark = pytest.mark.gpu
+
+
+def _ref(V, src, dst, X, W, dz):
+    loop = torch.arange(V)
+    u, v = torch.cat([src.long(), loop]), torch.cat([dst.long(), loop])
+    s = torch.bincount(v, minlength=V).double().rsqrt()
+    w = s[u] * s[v]
+    A = torch.zeros(V, X.shape[1], dtype=torch.float64).index_add_(0, v, w[:, None] * X.double()[u])
+    da = dz.double() @ W.double().t()
+    dX = torch.zeros(V, X.shape[1], dtype=torch.float64).index_add_(0, u, w[:, None] * da[v])
+    return A, A @ W.double(), A.t() @ dz.double(), dX
+
+
+@pytest.mark.parametrize("V,E,d_in,d_out,n,reorder,lean", [
+    (120_003, 700_001, 21, 13, 9, False, False),      # several row groups, few duplicates
+    (120_003, 700_001, 21, 13, 9, True, False),       # ... in another schedule
+    (40_001, 4_000_000, 130, 70, 3, False, False),    # merged duplicates, cut rows, two groups
+    (40_001, 4_000_000, 130, 70, 3, False, True),     # the same without memory for the by-source list
+    (3, 4, 5, 3, 2, False, False),
+])
+def test_layer_all_chunks_at_once(V, E, d_in, d_out, n, reorder, lean):
+    src, dst = inputs.rmat_edges(V, E, 7) if V > 3 else (torch.tensor([0, 1, 2, 2], dtype=torch.int32), torch.tensor([1, 2, 0, 1], dtype=torch.int32))
+    g0 = torch.Generator().manual_seed(5)
+    X, W = torch.randn(V, d_in, generator=g0), torch.randn(d_in, d_out, generator=g0) / 4
+    dz, keep = torch.randn(V, d_out, generator=g0), torch.randn(V, d_out, generator=g0)
+    A, H, dW, dX = _ref(V, src, dst, X, W, dz * (keep > 0))
+    ctx = B.ht_ctx_create(0)
+    g = B.ht_partition(ctx, V, src.cuda(), dst.cuda(), n, reorder_chunks=reorder)
+    try:
+        Xd, Wd, dzd, kd = B.to_matrix(X), W.cuda(), B.to_matrix(dz), B.to_matrix(keep)
+        Hd, Ad, dXd, dWd = B.alloc_matrix(V, d_out), B.alloc_matrix(V, d_in), B.alloc_matrix(V, d_in), torch.empty(d_in, d_out, device="cuda")
+        if lean:   # the smallest budget that a backward pass gets through with: it cannot hold 8 bytes per distinct pair as well
+            base = B.ht_graph_info_get(g).hbm_bytes
+            for mb in range(0, 400, 4):
+                B.ht_ctx_set_hbm_budget(ctx, base + (mb << 20))
+                try:
+                    B.ht_layer_bwd(ctx, g, d_in, d_out, B.HT_ACT_RELU, Xd, Wd, dzd, dWd, dH_in=dXd, H_out=kd, ckpt_kind=B.HT_CKPT_INPUT)
+                    break
+                except B.HongtuError as e:
+                    assert e.code == B.HT_ENOMEM
+            B.ht_sync(ctx)
+            assert B.ht_graph_info_get(g).hbm_bytes == base, "the budget was meant to leave no room"
+            B.ht_ctx_set_hbm_budget(ctx, 0)      # (the list is not tried again)
+            dXd.zero_()
+        for kind in (B.HT_CKPT_AGG, B.HT_CKPT_INPUT):
+            B.ht_layer_fwd(ctx, g, d_in, d_out, B.HT_ACT_NONE, Xd, Wd, Hd, Ad if kind == B.HT_CKPT_AGG else None)
+            for again in range(2):   # dH_in is added to
+                B.ht_layer_bwd(ctx, g, d_in, d_out, B.HT_ACT_RELU, Ad if kind == B.HT_CKPT_AGG else Xd, Wd, dzd, dWd, dH_in=dXd, H_out=kd, ckpt_kind=kind)
+            B.ht_sync(ctx)
+            assert_close(Hd[:, :d_out].cpu().numpy(), H.numpy(), "H")
+            if kind == B.HT_CKPT_AGG:
+                assert_close(Ad[:, :d_in].cpu().numpy(), A.numpy(), "A")
+            assert_close_grad(dWd.cpu().numpy(), dW.numpy(), "dW")
+            assert_close_grad(dXd[:, :d_in].cpu().numpy(), 2 * dX.numpy(), "dX")
+            dXd.zero_()
+    finally:
+        B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)
