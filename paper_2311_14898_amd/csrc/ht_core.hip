@@ -115,6 +115,16 @@ int ht_scratch(ht_ctx* ctx, int slot, size_t bytes, void** out) {
   return HT_OK;
 }
 
+int ht_scratch_release(ht_ctx* ctx, int slot) {
+  if (ctx->static_mode || !ctx->scratch[slot]) return HT_OK;
+  HT_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  ht_dev_free(ctx, ctx->scratch[slot], ctx->scratch_bytes[slot]);
+  ctx->scratch[slot] = nullptr;
+  ctx->scratch_bytes[slot] = 0;
+  ++ctx->scratch_gen;
+  return HT_OK;
+}
+
 int ht_host_scratch(ht_ctx* ctx, int slot, size_t bytes, void** out) {
   if (ctx->hscratch_bytes[slot] < bytes) {
     if (ctx->hscratch[slot]) {
@@ -255,6 +265,7 @@ int64_t ht_ctx_graph_launches(const ht_ctx* ctx) { return ctx ? ctx->graph_launc
 int ht_ctx_set_hbm_budget(ht_ctx* ctx, int64_t bytes) {
   if (!ctx || bytes < 0) return HT_EINVAL;
   ctx->hbm_budget = bytes;
+  ctx->gat_keep_limit = 0;
   return HT_OK;
 }
 

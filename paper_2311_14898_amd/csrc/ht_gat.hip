@@ -11,10 +11,12 @@
 //   z_v = sum alpha_e t_u ;  h'_v = act(z_v)
 //
 // A chunk holds every in-edge of its destinations (Sec. 4.1), so the neighbour
-// softmax is complete inside a chunk.  Nothing of size O(E) survives a call: the
-// backward pass recomputes t, p, q and the coefficients (Sec. 4.2: for models
-// with edge computation recomputation is cheaper than caching O(|E|) data).
-// Per chunk, edge coefficients live in a scratch array of the chunk's size.
+// softmax is complete inside a chunk.  With everything in HBM the chunks run
+// together, as many as the scratch memory of their scores allows.  Nothing of size
+// O(E) survives a call: the backward pass of a layer call recomputes t, p, q and the
+// scores (Sec. 4.2: for models with edge computation recomputation is cheaper than
+// caching O(|E|) data); an epoch with room for it keeps rows of size O(V) from each
+// layer's forward pass (GatKeep), which spare its backward pass the recomputation.
 //
 // Backward.  With dz = dh' * act'(z) and S_v = dz_v . z_v  (= sum_e alpha_e dalpha_e):
 //   dalpha_e = dz_v . t_u ;  dy_e = alpha_e (dalpha_e - S_v) f_e ,  f_e = LeakyReLU'(y_e)
@@ -39,6 +41,9 @@ namespace {
 
 __device__ __forceinline__ float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }
 __device__ __forceinline__ void st4(float* p, float4 v) { *reinterpret_cast<float4*>(p) = v; }
+__device__ __forceinline__ float4 fma4(float w, float4 v, float4 a) {
+  return make_float4(fmaf(w, v.x, a.x), fmaf(w, v.y, a.y), fmaf(w, v.z, a.z), fmaf(w, v.w, a.w));
+}
 __device__ __forceinline__ float wave_sum(float x) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
@@ -78,11 +83,11 @@ __global__ void __launch_bounds__(256) k_gat_pq(const float* __restrict__ T, int
   }
 }
 
-// Neighbour softmax of the rows of one chunk in three steps over the work items (a wave per
+// Neighbour softmax of a range of rows in three steps over the work items (a wave per
 // item, so a hub row is shared by many waves):
 //   1. per item: the scores x_e (kept in w[]), their maximum m_i and s_i = sum mult_e exp(x_e - m_i);
 //   2. per row cut into several items: m_v = max m_i, Z_v = sum s_i exp(m_i - m_v), in a fixed order;
-//   3. per item: w_e = mult_e exp(x_e - m_v) / Z_v.
+//   3. where they are used: w_e = mult_e exp(x_e - m_v) / Z_v.
 // Rows are vertices; w holds the entries from ent0 on, part_* the partial results from part0 on.
 __global__ void __launch_bounds__(256) k_gat_scores(const WorkItem* __restrict__ items, int64_t n_items, int64_t ent0, int64_t part0,
                                                     const int32_t* __restrict__ col, const float* __restrict__ mult,
@@ -140,38 +145,129 @@ __global__ void __launch_bounds__(256) k_gat_rowstats(const CutRow* __restrict__
   }
 }
 
-// wf / r_row / part_r (backward pass only, nullable): wf_e = w_e f_e with f_e = LeakyReLU'(y_e), the
-// weights of the destination pass, and their sum per item (per row when the row is one item).
-__global__ void __launch_bounds__(256) k_gat_coefs(const WorkItem* __restrict__ items, int64_t n_items, int64_t ent0, int64_t part0,
-                                                   const float* __restrict__ mult, const float* __restrict__ m_row,
-                                                   const float* __restrict__ zinv_row, float slope, float* __restrict__ w,
-                                                   float* __restrict__ wf, float* __restrict__ r_row, float* __restrict__ part_r) {
+// The weighted sums over the in-edges of a row, the coefficients made on the way from the scores x_e that k_gat_scores left:
+//   AGG_Z: z_v = sum w_e t_u;   AGG_ZQ: also Q_v = sum w_e f_e t_u and r_v = sum w_e f_e (f_e = LeakyReLU'(y_e));   AGG_Q: Q, r
+// What bounds it is the gather of the rows of t (the slab split is that of the GCN aggregation, for its reasons); the second sum
+// of the same rows costs four fused multiply-adds per loaded float4, where a pass of its own costs the gather again, and the
+// exponential of an entry costs less than the kernel that wrote the coefficients and the read of them did (233 k vertices, 115 M
+// edges, widths 256 and 41: forward, coefficients and destination pass 14.1 ms per epoch as passes of their own, 6.0 ms here).
+struct GatAgg {
+  const WorkItem* items; int64_t n_items; int64_t ent0, part0, row0;
+  const int32_t* col; const float* mult;      // per entry of the graph
+  const float* x;                             // scores, the first one for entry ent0
+  const float* m; const float* zinv;          // per vertex
+  float slope;
+  const float* T; int64_t ld; int d;
+  float* z; int64_t z_ld; float* z_part; int relu;    // row r - row0
+  float* Q; int64_t q_ld; float* q_part;
+  float* r; float* r_part;                    // per vertex; per partial sum
+};
+enum { AGG_Z = 0, AGG_ZQ = 1, AGG_Q = 2 };
+
+template <bool UNI, int MODE>
+__global__ void __launch_bounds__(256) k_gat_agg(GatAgg a, int S, int nvs, int eps, int64_t grp_per_part, int slab0) {
+  constexpr int U = 4;
+  constexpr bool Z = MODE != AGG_Q, Q = MODE != AGG_Z;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t t = (int64_t)blockIdx.x * 4 + wave;
-  if (t >= n_items) return;
-  const WorkItem it = items[t];
-  const int32_t r = it.row, len = it.len;
+  const int xcd = blockIdx.x & 7;
+  const int slab = slab0 + xcd % S;
+  const int64_t i = blockIdx.x >> 3;
+  if (grp_per_part > 0 && i >= grp_per_part) return;
+  const int64_t grp = grp_per_part > 0 ? (int64_t)(xcd / S) * grp_per_part + i : i * (8 / S) + xcd / S;
+  const int64_t t = grp * 4 + wave;
+  if (t >= a.n_items) return;
+  const int nvec = (a.d + 3) >> 2;
+  const int v0 = slab * nvs;
+  const int nv_here = (nvec - v0) < nvs ? (nvec - v0) : nvs;
+  if (nv_here <= 0) return;
+  const WorkItem it = a.items[t];
+  const int32_t row = it.row, len = it.len;
   const int64_t e0 = it.e0;
-  w -= ent0;
-  if (wf) wf -= ent0;
-  const float m = m_row[r], zinv = zinv_row[r];
+  const int es = lane / nvs, vec = lane - es * nvs;
+  const bool active = es < eps && vec < nv_here;
+  const int coff = (v0 + vec) * 4;
+  const float* srcc = a.T + coff;
+  const float m = a.m[row], zinv = a.zinv[row];
+  const float* xs = a.x - a.ent0;
+  const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+  float4 acc = zero, G = zero;
   float rs = 0.f;
-  for (int32_t k = lane; k < len; k += 64) {
-    const float x = w[e0 + k];       // the score LeakyReLU(y_e): same sign as y_e
-    const float c = (mult ? mult[e0 + k] : 1.f) * expf(x - m) * zinv;
-    w[e0 + k] = c;
-    if (wf) {
-      const float cf = c * (x > 0.f ? 1.f : slope);
-      wf[e0 + k] = cf;
-      rs += cf;
+  for (int32_t base = 0; base < len; base += 64) {
+    const int32_t nh = (len - base) < 64 ? (len - base) : 64;
+    int32_t my_u = 0;
+    float my_c = 0.f, my_cf = 0.f;
+    if (lane < nh) {
+      const int64_t e = e0 + base + lane;
+      my_u = a.col[e];
+      const float x = xs[e];           // the score LeakyReLU(y_e): same sign as y_e
+      my_c = (a.mult ? a.mult[e] : 1.f) * expf(x - m) * zinv;
+      my_cf = my_c * (x > 0.f ? 1.f : a.slope);
+      if (Q) rs += my_cf;
+    }
+    const int step = UNI ? U : U * eps;
+    for (int32_t k = 0; k < nh; k += step) {
+      int32_t c[U];
+      float w[U], wf[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int kk = UNI ? k + u : k + u * eps + es;
+        const int kc = kk < nh ? kk : (nh - 1);     // past the end: the last entry again with weight 0
+        if (UNI) {
+          c[u] = __builtin_amdgcn_readlane(my_u, kc);
+          if (Z) w[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_c), kc));
+          if (Q) wf[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_cf), kc));
+        } else {
+          c[u] = __shfl(my_u, kc, 64);
+          if (Z) w[u] = __shfl(my_c, kc, 64);
+          if (Q) wf[u] = __shfl(my_cf, kc, 64);
+        }
+        if (kk >= nh) w[u] = wf[u] = 0.f;
+      }
+      if (active) {
+        float4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = ld4(srcc + (int64_t)c[u] * a.ld);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (Z) acc = fma4(w[u], v[u], acc);
+          if (Q) G = fma4(wf[u], v[u], G);
+        }
+      }
     }
   }
-  if (wf) {
-    rs = wave_sum(rs);
-    if (lane == 0) {
-      if (it.part >= 0) part_r[it.part - part0] = rs;
-      else r_row[r] = rs;
+  // the sum of a row's edge slots in slot order; slot 0 holds the result
+  auto slots = [&](float4 own) {
+    float4 tot = own;
+    for (int q = 1; q < eps; ++q) {
+      const int from = (lane + q * nvs) & 63;
+      tot.x += __shfl(own.x, from, 64);
+      tot.y += __shfl(own.y, from, 64);
+      tot.z += __shfl(own.z, from, 64);
+      tot.w += __shfl(own.w, from, 64);
     }
+    return tot;
+  };
+  if (Z) acc = slots(acc);
+  if (Q) {
+    G = slots(G);
+    if (slab == 0) {
+      rs = wave_sum(rs);
+      if (lane == 0) {
+        if (it.part >= 0) a.r_part[it.part - a.part0] = rs;
+        else a.r[row] = rs;
+      }
+    }
+  }
+  if (es != 0 || vec >= nv_here) return;
+  if (it.part >= 0) {
+    if (Z) st4(a.z_part + (it.part - a.part0) * a.z_ld + coff, acc);
+    if (Q) st4(a.q_part + (it.part - a.part0) * a.q_ld + coff, G);
+  } else {
+    if (Z) {
+      if (a.relu) acc = make_float4(acc.x > 0.f ? acc.x : 0.f, acc.y > 0.f ? acc.y : 0.f, acc.z > 0.f ? acc.z : 0.f, acc.w > 0.f ? acc.w : 0.f);
+      st4(a.z + (row - a.row0) * a.z_ld + coff, acc);
+    }
+    if (Q) st4(a.Q + (row - a.row0) * a.q_ld + coff, G);
   }
 }
 
@@ -218,24 +314,22 @@ __global__ void __launch_bounds__(256) k_gat_dz(const float* __restrict__ dh, in
 }
 
 struct GatPass {
-  // items of the source pass (rows = local sources of the chunk)
+  // items of the source pass (rows = local sources of a chunk, or vertices)
   const WorkItem* items; int64_t n_items; int64_t part0;
-  const int32_t* idx;        // per entry: local destination = row of `mat` to read
+  const int32_t* idx;        // per entry: row of `mat` to read (destination of the chunk, or vertex)
   const float* mult;         // multiplicity per entry (nullable: 1)
-  const float* mat;          // rows gathered per entry: dz of the chunk
+  const float* mat;          // rows gathered per entry: dz
   int64_t mat_ld;
   const float* own;          // the item's own row: t
   int64_t own_ld;
-  const int32_t* own_idx;    // row r -> row of `own`
+  const int32_t* own_idx;    // row r -> row of `own` and of `out` (nullable: r)
   int d;
-  const float* p; const float* q;        // per vertex
-  const float* m; const float* zinv;     // per vertex: the coefficients are recomputed from them
-  const float* S;            // per row of the chunk
-  const float* d4;           // per row of the chunk: (p_v, m_v, 1/Z_v, S_v)
-  int64_t dst0;              // first destination of the chunk
+  const float* q;            // per vertex
+  const float* d4;           // per row of `mat`: (p_v, m_v, 1/Z_v, S_v), from which the coefficients are recomputed
   float slope;
   // outputs
-  float* out; int64_t out_ld; const int32_t* out_idx;   // dt rows (accumulated), scalar in column sc_col
+  float* out; int64_t out_ld;  // dt rows, scalar in column sc_col
+  bool add;                    // out is added to
   float* partial;            // [n_part x out_ld] partial rows of cut items
   int sc_col;
 };
@@ -268,7 +362,7 @@ __global__ void __launch_bounds__(256) k_gat_src(GatPass a) {
   const int32_t r = it.row;
   const int64_t e0 = it.e0;
   const int32_t len = it.len, part = it.part;
-  const int32_t u_id = a.own_idx[r];
+  const int32_t u_id = a.own_idx ? a.own_idx[r] : r;
   float4 acc[VPL], G[VPL];
 #pragma unroll
   for (int j = 0; j < VPL; ++j) acc[j] = G[j] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -322,7 +416,7 @@ __global__ void __launch_bounds__(256) k_gat_src(GatPass a) {
     }
   }
   float s = 0.f;
-  float* row = part >= 0 ? a.partial + (part - a.part0) * a.out_ld : a.out + (int64_t)a.out_idx[r] * a.out_ld;
+  float* row = part >= 0 ? a.partial + (part - a.part0) * a.out_ld : a.out + (int64_t)u_id * a.out_ld;
 #pragma unroll
   for (int j = 0; j < VPL; ++j) {
     const int c = (j * 64 + lane) * 4;
@@ -330,7 +424,7 @@ __global__ void __launch_bounds__(256) k_gat_src(GatPass a) {
     const float4 mine = ld4(a.own + (int64_t)u_id * a.own_ld + c);   // pads of t are zero
     s = fmaf(mine.x, G[j].x, fmaf(mine.y, G[j].y, fmaf(mine.z, G[j].z, fmaf(mine.w, G[j].w, s))));
     float4 v = acc[j];
-    if (part < 0) {
+    if (part < 0 && a.add) {
       const float4 o = ld4(row + c);
       v = make_float4(o.x + v.x, o.y + v.y, o.z + v.z, o.w + v.w);
     }
@@ -340,7 +434,7 @@ __global__ void __launch_bounds__(256) k_gat_src(GatPass a) {
   if (lane == 0) {
     // the scalar travels in its own float4 column block behind the data columns
     float4 sc = make_float4(s - csum, 0.f, 0.f, 0.f);
-    if (part < 0) sc.x += row[a.sc_col];
+    if (part < 0 && a.add) sc.x += row[a.sc_col];
     st4(row + a.sc_col, sc);
   }
 }
@@ -355,7 +449,7 @@ __global__ void __launch_bounds__(256) k_gat_src_g(GatPass a) {
   const int32_t r = it.row;
   const int64_t e0 = it.e0;
   const int32_t len = it.len, part = it.part;
-  const int32_t u_id = a.own_idx[r];
+  const int32_t u_id = a.own_idx ? a.own_idx[r] : r;
   const int grp = lane / G_, c4 = (lane % G_) * 4;
   const bool has = c4 < a.d;
   const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -409,13 +503,13 @@ __global__ void __launch_bounds__(256) k_gat_src_g(GatPass a) {
     acc.w += __shfl_xor(acc.w, o, 64);
   }
   float s = 0.f;
-  float* row = part >= 0 ? a.partial + (part - a.part0) * a.out_ld : a.out + (int64_t)a.out_idx[r] * a.out_ld;
+  float* row = part >= 0 ? a.partial + (part - a.part0) * a.out_ld : a.out + (int64_t)u_id * a.out_ld;
   if (has) {
     const float4 mine = ld4(a.own + (int64_t)u_id * a.own_ld + c4);
     s = fmaf(mine.x, G.x, fmaf(mine.y, G.y, fmaf(mine.z, G.z, mine.w * G.w)));
     if (grp == 0) {
       float4 v = acc;
-      if (part < 0) {
+      if (part < 0 && a.add) {
         const float4 o = ld4(row + c4);
         v = make_float4(o.x + v.x, o.y + v.y, o.z + v.z, o.w + v.w);
       }
@@ -425,7 +519,7 @@ __global__ void __launch_bounds__(256) k_gat_src_g(GatPass a) {
   s = wave_sum(s);
   if (lane == 0) {
     float4 sc = make_float4(s - csum, 0.f, 0.f, 0.f);
-    if (part < 0) sc.x += row[a.sc_col];
+    if (part < 0 && a.add) sc.x += row[a.sc_col];
     st4(row + a.sc_col, sc);
   }
 }
@@ -450,10 +544,71 @@ __global__ void k_gat_split(const float* __restrict__ da4, int d, float* __restr
   }
 }
 
+// What a layer's forward pass leaves for its backward pass inside one epoch: t, the scores' halves, the softmax's row values, and
+// the sums that dp needs (Q, r).  Without it the backward pass makes all of this again.
+struct GatKeep {
+  float *T = nullptr, *Q = nullptr, *p = nullptr, *q = nullptr, *m = nullptr, *zinv = nullptr, *r = nullptr;
+};
+
 struct GatWs {
-  float *T, *p, *q, *m, *zinv, *S, *dp, *r, *pq4, *d4, *w, *wf;
+  float *T, *p, *q, *m, *zinv, *S, *dp, *r, *pq4, *d4;
   int64_t ld_t;
 };
+
+// A contiguous range of chunks in vertex order that runs as one set of launches.
+struct GatRange {
+  ItemRange it;
+  int64_t ent0, n_ent, row0, rows;
+};
+GatRange range_of(const ht_graph* g, const ChunkMeta& c) {
+  return GatRange{c.fwd, c.ue0, g->merged ? c.nu : c.nnz, c.dst0, c.dst1 - c.dst0};
+}
+// Scratch memory of one range (scores, partial sums), and of a backward pass that holds dz and Q of all vertices; what an epoch
+// keeps between its passes.  Beyond these the passes go chunk by chunk, and the backward pass recomputes.
+constexpr int64_t GAT_RANGE_BYTES = (int64_t)4 << 30, GAT_DIRECT_BYTES = (int64_t)8 << 30, GAT_KEEP_BYTES = (int64_t)16 << 30;
+// Chunks that follow each other in vertex order share a range while its scores (4 bytes per entry) and partial sums
+// (part_bytes each) stay below the cap: what a launch per chunk costs is in the launches and in the last waves of each
+// (20,011 vertices in 3 chunks: 861 -> 458 us per epoch; 233 k vertices, 115 M edges in 8: 26.0 -> 16.2 ms, the sums kept for
+// the backward pass included).
+std::vector<GatRange> ranges_of(const ht_graph* g, int64_t part_bytes, bool merge) {
+  std::vector<GatRange> out;
+  for (int k = 0; k < g->n; ++k) {
+    const GatRange c = range_of(g, g->chunks[g->pos[k]]);
+    if (c.rows == 0) continue;
+    if (merge && !out.empty()) {
+      GatRange& r = out.back();
+      if ((r.n_ent + c.n_ent) * 4 + (r.it.n_part + c.it.n_part) * part_bytes <= GAT_RANGE_BYTES) {
+        r.it.n_items += c.it.n_items;
+        r.it.n_part += c.it.n_part;
+        r.it.n_cut += c.it.n_cut;
+        r.n_ent += c.n_ent;
+        r.rows += c.rows;
+        continue;
+      }
+    }
+    out.push_back(c);
+  }
+  return out;
+}
+// Scratch memory for any of these ranges: scores, partial sums of the softmax and of z and Q (pitches z_ld, q_ld; 0: no such sum).
+struct RangeWs {
+  float *x = nullptr, *part = nullptr, *z_part = nullptr, *q_part = nullptr;
+  int64_t n_part = 0;
+};
+int range_ws(ht_ctx* ctx, const std::vector<GatRange>& ranges, int64_t z_ld, int64_t q_ld, RangeWs* ws) {
+  int64_t ent = 1;
+  ws->n_part = 0;
+  for (const GatRange& r : ranges) {
+    ent = std::max(ent, r.n_ent);
+    ws->n_part = std::max(ws->n_part, r.it.n_part);
+  }
+  HT_TRY(ht_scratch(ctx, HT_S_GATE, (size_t)ent * 4, (void**)&ws->x));
+  if (ws->n_part == 0) return HT_OK;
+  HT_TRY(ht_scratch(ctx, HT_S_GATP, (size_t)ws->n_part * 3 * 4, (void**)&ws->part));
+  HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)(ws->n_part * (z_ld + q_ld)) * 4, (void**)&ws->z_part));
+  ws->q_part = ws->z_part + ws->n_part * z_ld;
+  return HT_OK;
+}
 
 // Contiguous row ranges between pinned host memory and staging pairs in HBM: copies run on the
 // side streams, the compute stream waits for the block it needs and frees the block it has read.
@@ -534,25 +689,30 @@ int check_desc(ht_ctx* ctx, const ht_gat_desc* d) {
   return HT_OK;
 }
 
-// t = H W (pad columns zero), p, q
-constexpr int64_t BLOCK_HBM = (int64_t)1 << 22;    // rows per GEMM call
-
-int prepare(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const ht_tensor* H, const float* W, const float* a_dst,
-            const float* a_src, bool backward, GatWs* ws, ht_stats* st, Timer* tm, Link* lk) {
-  hipStream_t s = ctx->stream;
+int bind_ws(ht_ctx* ctx, const ht_graph* g, int d_out, const GatKeep* keep, GatWs* ws) {
   const int64_t V = std::max<int64_t>(g->V, 1);
-  ws->ld_t = ht_row_pitch(desc->d_out, true);
-  HT_TRY(ht_scratch(ctx, HT_S_TFULL, (size_t)V * ws->ld_t * 4, (void**)&ws->T));
+  ws->ld_t = ht_row_pitch(d_out, true);
+  if (keep) ws->T = keep->T;
+  else HT_TRY(ht_scratch(ctx, HT_S_TFULL, (size_t)V * ws->ld_t * 4, (void**)&ws->T));
   float* vec = nullptr;
   HT_TRY(ht_scratch(ctx, HT_S_GATV, (size_t)V * 16 * 4, (void**)&vec));
   ws->p = vec; ws->q = vec + V; ws->m = vec + 2 * V; ws->zinv = vec + 3 * V; ws->S = vec + 4 * V; ws->dp = vec + 5 * V;
   ws->r = vec + 6 * V;
   ws->pq4 = vec + 8 * V;      // 16-byte aligned whatever V is
-  ws->d4 = vec + 12 * V;      // per chunk, rows of the chunk
-  const size_t ne = (size_t)std::max<int64_t>(g->max_nnz, 1);
-  HT_TRY(ht_scratch(ctx, HT_S_GATE, ne * 4 * (backward ? 2 : 1), (void**)&ws->w));
-  ws->wf = backward ? ws->w + ne : nullptr;
-  if (ws->ld_t != desc->d_out) HT_TRY(ht_fill_zero(ctx, s, ws->T, (size_t)g->V * ws->ld_t * 4));
+  ws->d4 = vec + 12 * V;
+  if (keep) { ws->p = keep->p; ws->q = keep->q; ws->m = keep->m; ws->zinv = keep->zinv; ws->r = keep->r; }
+  return HT_OK;
+}
+
+// t = H W (pad columns that are read zero), p, q
+constexpr int64_t BLOCK_HBM = (int64_t)1 << 22;    // rows per GEMM call
+
+int prepare(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const ht_tensor* H, const float* W, const float* a_dst,
+            const float* a_src, const GatWs* ws, ht_stats* st, Timer* tm, Link* lk) {
+  hipStream_t s = ctx->stream;
+  const int64_t V = std::max<int64_t>(g->V, 1);
+  // (a row's float4 reads end at the next multiple of 4 columns: those pads are read, and 0 times a pad must be 0)
+  if (desc->d_out & 3) HT_TRY(ht_fill_zero(ctx, s, ws->T, (size_t)g->V * ws->ld_t * 4));
   const bool host = on_host(H);
   const int64_t step = host ? ctx->link_block_rows : BLOCK_HBM;   // rows per staged block / per GEMM call
   float* stage[2] = {nullptr, nullptr};
@@ -589,33 +749,73 @@ int prepare(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const ht_te
   return HT_OK;
 }
 
-int softmax_chunk(ht_ctx* ctx, const ht_graph* g, const ChunkMeta& c, const ht_gat_desc* desc, const GatWs& ws, ht_stats* st,
-                  Timer* tm, bool backward) {
-  const int32_t* col = g->merged ? g->ucol.p : g->col.p;
-  const float* mult = g->merged ? g->umult.p : nullptr;
-  const ItemRange& it = c.fwd;
-  const WorkItem* items = g->fwd_items.items.p + it.it0;
-  const CutRow* cuts = g->fwd_items.cuts.p + it.cut0;
-  // rows without an in-edge (possible without self-loops) have no item: coefficient sums of 0
-  HT_TRY(ht_fill_zero(ctx, ctx->stream, ws.zinv + c.dst0, (size_t)(c.dst1 - c.dst0) * 4));
+// Scores, row maxima and 1 / Z of a range (a row without an in-edge has an item of no entries: 1 / Z = 0).
+int softmax_range(ht_ctx* ctx, const ht_graph* g, const GatRange& r, const ht_gat_desc* desc, const GatWs& ws, const RangeWs& rw,
+                  ht_stats* st, Timer* tm) {
+  const ItemRange& it = r.it;
   if (it.n_items == 0) return HT_OK;
-  float* part = nullptr;
-  HT_TRY(ht_scratch(ctx, HT_S_GATP, (size_t)std::max<int64_t>(g->max_fpart, 1) * 3 * 4, (void**)&part));
-  float* part_s = part + std::max<int64_t>(g->max_fpart, 1);
-  float* part_r = part_s + std::max<int64_t>(g->max_fpart, 1);
-  if (backward) HT_TRY(ht_fill_zero(ctx, ctx->stream, ws.r + c.dst0, (size_t)(c.dst1 - c.dst0) * 4));
-  const unsigned nb = (unsigned)((it.n_items + 3) / 4);
+  float* part_s = rw.part ? rw.part + rw.n_part : nullptr;
   tm->begin(&st->t_gat_softmax_ms);
-  k_gat_scores<<<nb, 256, 0, ctx->stream>>>(items, it.n_items, c.ue0, it.part0, col, mult, ws.p, ws.q, desc->slope, ws.w, ws.m,
-                                            ws.zinv, part, part_s);
-  if (it.n_cut > 0)
-    k_gat_rowstats<<<(unsigned)((it.n_cut + 3) / 4), 256, 0, ctx->stream>>>(cuts, it.n_cut, it.part0, part, part_s, ws.m, ws.zinv);
-  k_gat_coefs<<<nb, 256, 0, ctx->stream>>>(items, it.n_items, c.ue0, it.part0, mult, ws.m, ws.zinv, desc->slope, ws.w,
-                                           backward ? ws.wf : nullptr, ws.r, part_r);
-  if (backward && it.n_cut > 0)
-    k_gat_fix_scalar<<<(unsigned)((it.n_cut + 3) / 4), 256, 0, ctx->stream>>>(cuts, it.n_cut, it.part0, part_r, ws.r);
-  tm->end();
+  k_gat_scores<<<(unsigned)((it.n_items + 3) / 4), 256, 0, ctx->stream>>>(
+      g->fwd_items.items.p + it.it0, it.n_items, r.ent0, it.part0, g->merged ? g->ucol.p : g->col.p, g->merged ? g->umult.p : nullptr,
+      ws.p, ws.q, desc->slope, rw.x, ws.m, ws.zinv, rw.part, part_s);
   HT_LAUNCH_CHECK(ctx);
+  if (it.n_cut > 0) {
+    k_gat_rowstats<<<(unsigned)((it.n_cut + 3) / 4), 256, 0, ctx->stream>>>(g->fwd_items.cuts.p + it.cut0, it.n_cut, it.part0, rw.part,
+                                                                            part_s, ws.m, ws.zinv);
+    HT_LAUNCH_CHECK(ctx);
+  }
+  tm->end();
+  return HT_OK;
+}
+
+template <bool UNI>
+void launch_agg(unsigned blocks, hipStream_t st, int mode, const GatAgg& a, const SlabShape& sh, int slab0) {
+  if (mode == AGG_Z) k_gat_agg<UNI, AGG_Z><<<blocks, 256, 0, st>>>(a, sh.S, sh.nvs, sh.eps, sh.grp_per_part, slab0);
+  else if (mode == AGG_ZQ) k_gat_agg<UNI, AGG_ZQ><<<blocks, 256, 0, st>>>(a, sh.S, sh.nvs, sh.eps, sh.grp_per_part, slab0);
+  else k_gat_agg<UNI, AGG_Q><<<blocks, 256, 0, st>>>(a, sh.S, sh.nvs, sh.eps, sh.grp_per_part, slab0);
+}
+
+// The sums of a range out of its scores: z (row 0 = the range's first row; relu) and / or Q (row 0 likewise) and r.
+int agg_range(ht_ctx* ctx, const ht_graph* g, const GatRange& rg, const ht_gat_desc* desc, const GatWs& ws, const RangeWs& rw, int mode,
+              float* z, int64_t z_ld, float* Q, double* t_items, double* t_fix, Timer* tm) {
+  const ItemRange& it = rg.it;
+  if (it.n_items == 0) return HT_OK;
+  hipStream_t st = ctx->stream;
+  SpmmArgs s{};
+  s.n_items = it.n_items; s.n_edges = rg.n_ent; s.src = ws.T; s.src_ld = ws.ld_t; s.d = desc->d_out;
+  SlabShape sh;
+  HT_TRY(ht_slab_shape(ctx, s, &sh));
+  GatAgg a{};
+  a.items = g->fwd_items.items.p + it.it0; a.n_items = it.n_items; a.ent0 = rg.ent0; a.part0 = it.part0; a.row0 = rg.row0;
+  a.col = g->merged ? g->ucol.p : g->col.p; a.mult = g->merged ? g->umult.p : nullptr;
+  a.x = rw.x; a.m = ws.m; a.zinv = ws.zinv; a.slope = desc->slope;
+  a.T = ws.T; a.ld = ws.ld_t; a.d = desc->d_out;
+  a.z = z; a.z_ld = z_ld; a.z_part = rw.z_part; a.relu = desc->act == HT_ACT_RELU;
+  a.Q = Q; a.q_ld = ws.ld_t; a.q_part = rw.q_part;
+  a.r = ws.r; a.r_part = rw.part ? rw.part + 2 * rw.n_part : nullptr;
+  if (t_items) tm->begin(t_items);
+  for (int p = 0; p < sh.P; ++p) {
+    if (sh.eps == 1) launch_agg<true>(sh.blocks, st, mode, a, sh, p * sh.S);
+    else launch_agg<false>(sh.blocks, st, mode, a, sh, p * sh.S);
+    HT_LAUNCH_CHECK(ctx);
+  }
+  if (t_items) tm->end();
+  if (it.n_cut == 0) return HT_OK;
+  if (t_fix) tm->begin(t_fix);
+  SpmmArgs f{};
+  f.cuts = g->fwd_items.cuts.p + it.cut0; f.n_fix = it.n_cut; f.part0 = it.part0; f.row0 = rg.row0; f.d = desc->d_out;
+  if (mode != AGG_Q) {
+    f.out = z; f.out_ld = z_ld; f.partial = rw.z_part; f.relu = a.relu;
+    HT_TRY(ht_spmm_fix_launch(ctx, st, f));
+  }
+  if (mode != AGG_Z) {
+    f.out = Q; f.out_ld = ws.ld_t; f.partial = rw.q_part; f.relu = 0;
+    HT_TRY(ht_spmm_fix_launch(ctx, st, f));
+    k_gat_fix_scalar<<<(unsigned)((it.n_cut + 3) / 4), 256, 0, st>>>(f.cuts, it.n_cut, it.part0, a.r_part, ws.r);
+    HT_LAUNCH_CHECK(ctx);
+  }
+  if (t_fix) tm->end();
   return HT_OK;
 }
 
@@ -631,8 +831,13 @@ int launch_src(ht_ctx* ctx, const GatPass& a, int nvec) {
   return HT_OK;
 }
 
+void release_range_ws(ht_ctx* ctx) {
+  for (int slot : {HT_S_GATE, HT_S_GATP, HT_S_SPART}) (void)ht_scratch_release(ctx, slot);
+}
+
+// keep (nullable, everything in HBM): where t, the row values, Q and r go for this epoch's backward pass
 int gat_fwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const ht_tensor* H_in, const float* W,
-                 const float* a_dst, const float* a_src, ht_tensor* H_out, ht_stats* local, Timer* tm, int layer) {
+                 const float* a_dst, const float* a_src, ht_tensor* H_out, const GatKeep* keep, ht_stats* local, Timer* tm, int layer) {
   HT_TRY(check_desc(ctx, desc));
   HT_TRY(check(ctx, g, desc, H_in, desc->d_in, "H_in"));
   HT_TRY(check(ctx, g, desc, H_out, desc->d_out, "H_out"));
@@ -641,7 +846,18 @@ int gat_fwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
   Link lk(ctx, local, tm);
   const bool out_host = on_host(H_out);
   if (on_host(H_in) || out_host) HT_TRY(lk.fork());
-  HT_TRY(prepare(ctx, g, desc, H_in, W, a_dst, a_src, false, &ws, local, tm, &lk));
+  HT_TRY(bind_ws(ctx, g, desc->d_out, keep, &ws));
+  const int64_t q_ld = keep ? ws.ld_t : 0;
+  auto ranges = ranges_of(g, (H_out->ld + q_ld + 3) * 4, !out_host);
+  RangeWs rw;
+  int rc = range_ws(ctx, ranges, H_out->ld, q_ld, &rw);
+  if (rc == HT_ENOMEM) {   // less memory at a time: chunk by chunk
+    release_range_ws(ctx);
+    ranges = ranges_of(g, 0, false);
+    rc = range_ws(ctx, ranges, H_out->ld, q_ld, &rw);
+  }
+  HT_TRY(rc);
+  HT_TRY(prepare(ctx, g, desc, H_in, W, a_dst, a_src, &ws, local, tm, &lk));
   float* obuf[2] = {nullptr, nullptr};
   hipEvent_t ev_ofree[2] = {nullptr, nullptr};
   if (out_host) {
@@ -649,54 +865,119 @@ int gat_fwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
     HT_TRY(ht_scratch(ctx, HT_S_LINK1, (size_t)rows * H_out->ld * 4 * 2, (void**)&obuf[0]));
     obuf[1] = obuf[0] + rows * H_out->ld;
   }
+  const int li = layer < HT_MAX_LAYERS ? layer : HT_MAX_LAYERS - 1;
   int q = 0;
-  for (int j = 0; j < g->n; ++j) {
-    const ChunkMeta& c = g->chunks[j];
-    if (c.dst1 == c.dst0) continue;
+  for (const GatRange& r : ranges) {
     const int b = q++ & 1;
-    HT_TRY(softmax_chunk(ctx, g, c, desc, ws, local, tm, false));
-    float* partial = nullptr;
-    if (c.fwd.n_part > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)g->max_fpart * H_out->ld * 4, (void**)&partial));
-    SpmmArgs a{};
-    a.items = g->fwd_items.items.p + c.fwd.it0; a.n_items = c.fwd.n_items;
-    a.cuts = g->fwd_items.cuts.p + c.fwd.cut0; a.n_fix = c.fwd.n_cut;
-    a.part0 = c.fwd.part0; a.row0 = c.dst0;
-    a.n_edges = g->merged ? c.nu : c.nnz;
-    a.idx = g->merged ? g->ucol.p : g->col.p;
-    a.w_edge = ws.w; a.w0 = c.ue0;
-    a.src = ws.T; a.src_ld = ws.ld_t; a.d = desc->d_out;
-    a.out = out_host ? obuf[b] : H_out->ptr + c.dst0 * H_out->ld; a.out_ld = H_out->ld;
-    a.accumulate = 0;
-    a.relu = desc->act == HT_ACT_RELU;
-    a.partial = partial;
-    a.tm = tm;
-    a.t_items = &local->t_agg_fwd_layer_ms[layer < HT_MAX_LAYERS ? layer : HT_MAX_LAYERS - 1];
-    a.t_fix = &local->t_agg_fix_ms;
+    HT_TRY(softmax_range(ctx, g, r, desc, ws, rw, local, tm));
     if (out_host) {
       HT_TRY(lk.wait(st, ev_ofree[b]));
-      // rows without an in-edge have no work item: their output is zero
-      HT_TRY(ht_fill_zero(ctx, st, obuf[b], (size_t)(c.dst1 - c.dst0) * H_out->ld * 4));
+      HT_TRY(ht_fill_zero(ctx, st, obuf[b], (size_t)r.rows * H_out->ld * 4));     // (pads reach the host)
     }
-    HT_TRY(ht_spmm_launch(ctx, st, a));
+    HT_TRY(agg_range(ctx, g, r, desc, ws, rw, keep ? AGG_ZQ : AGG_Z, out_host ? obuf[b] : H_out->ptr + r.row0 * H_out->ld, H_out->ld,
+                     keep ? keep->Q + r.row0 * ws.ld_t : nullptr, &local->t_agg_fwd_layer_ms[li], &local->t_agg_fix_ms, tm));
     if (out_host) {
       hipEvent_t ev_done = nullptr;
       HT_TRY(lk.rec(st, &ev_done));
       HT_TRY(lk.wait(lk.s_out, ev_done));
-      HT_TRY(lk.copy(lk.s_out, H_out->ptr + c.dst0 * H_out->ld, obuf[b], (size_t)(c.dst1 - c.dst0) * H_out->ld * 4, true));
+      HT_TRY(lk.copy(lk.s_out, H_out->ptr + r.row0 * H_out->ld, obuf[b], (size_t)r.rows * H_out->ld * 4, true));
       HT_TRY(lk.rec(lk.s_out, &ev_ofree[b]));
       lk.last_out = ev_ofree[b];
     }
+  }
+  for (const ChunkMeta& c : g->chunks) {   // chunk aggregations, whatever number of launches they take
+    if (c.dst1 == c.dst0) continue;
     local->n_spmm_fwd += 1;
-    local->n_agg_fwd_layer[layer < HT_MAX_LAYERS ? layer : HT_MAX_LAYERS - 1] += 1;
+    local->n_agg_fwd_layer[li] += 1;
     local->edges += c.nnz;
   }
   if (lk.used) HT_TRY(lk.join());
   return HT_OK;
 }
 
+// The source pass of a layer of width d can take all vertices at once (the list by source was tried).
+bool src_fits(const ht_graph* g, int d, bool kept) {
+  const int64_t ld = ht_row_pitch(d, true);
+  return g->by_src.ok && g->V * ld * 4 * (kept ? 1 : 2) <= GAT_DIRECT_BYTES && g->by_src.items.n_part * (ld + 4) * 4 <= GAT_RANGE_BYTES;
+}
+
+// Backward over the rows with everything in HBM, all vertices at once: dz of all rows, the destination pass over ranges of chunks
+// (or what the forward pass kept), and the source pass over the whole graph's entries by source, which writes every row of dt
+// once; chunk by chunk a row is read and written again for every chunk that names its vertex.  *done = false: it would take more
+// memory than it may have, nothing was enqueued.
+int gat_bwd_rows_direct(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const GatWs& ws, const GatKeep* keep,
+                        const ht_tensor* H_in, const float* W, const float* a_dst, const float* a_src, const ht_tensor* H_out,
+                        const ht_tensor* dH_out, float* dT, int64_t ld_dt, ht_stats* local, Timer* tm, Link* lk, bool* done) {
+  *done = false;
+  hipStream_t st = ctx->stream;
+  const int64_t V = g->V;
+  const int d = desc->d_out, nvec = (d + 3) / 4, sc_col = (int)ws.ld_t;
+  const size_t mat = (size_t)V * ws.ld_t * 4;
+  if (V <= 0) return HT_OK;
+  HT_TRY(ht_graph_by_source(ctx, g));
+  if (!src_fits(g, d, keep != nullptr)) return HT_OK;
+  const SourceRows& S = g->by_src;
+  float *dz = nullptr, *Q = keep ? keep->Q : nullptr;
+  float* s_part = nullptr;
+  std::vector<GatRange> ranges;
+  RangeWs rw;
+  auto take = [&]() -> int {
+    HT_TRY(ht_graph_by_source_mult(ctx, g));
+    HT_TRY(ht_scratch(ctx, HT_S_DZCHUNK, mat, (void**)&dz));
+    // the partial sums of both passes share a slot, one after the other
+    if (S.items.n_part > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)(S.items.n_part * ld_dt) * 4, (void**)&s_part));
+    if (!keep) {
+      HT_TRY(ht_scratch(ctx, HT_S_ACHUNK, mat, (void**)&Q));
+      ranges = ranges_of(g, (ws.ld_t + 3) * 4, true);
+      HT_TRY(range_ws(ctx, ranges, 0, ws.ld_t, &rw));
+      if (S.items.n_part > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)(S.items.n_part * ld_dt) * 4, (void**)&s_part));
+    }
+    // the dense steps behind this pass add to the caller's tensors: nothing may fail there for want of memory that is held here
+    HT_TRY(ht_gemm_reserve(ctx, V, d, 4));
+    return ht_gemm_reserve(ctx, V, desc->d_in, d);
+  };
+  const int rc = take();
+  if (rc == HT_ENOMEM) {
+    release_range_ws(ctx);
+    for (int slot : {HT_S_DZCHUNK, HT_S_ACHUNK}) (void)ht_scratch_release(ctx, slot);
+    return HT_OK;
+  }
+  HT_TRY(rc);
+  *done = true;
+  if (!keep) HT_TRY(prepare(ctx, g, desc, H_in, W, a_dst, a_src, &ws, local, tm, lk));
+  for (const GatRange& r : ranges) {
+    HT_TRY(softmax_range(ctx, g, r, desc, ws, rw, local, tm));
+    HT_TRY(agg_range(ctx, g, r, desc, ws, rw, AGG_Q, nullptr, 0, Q + r.row0 * ws.ld_t, &local->t_gat_dst_ms, &local->t_gat_dst_ms, tm));
+  }
+  tm->begin(&local->t_gat_dst_ms);
+  const unsigned nb = (unsigned)((V + 3) / 4);
+  k_gat_dz<<<nb, 256, 0, st>>>(dH_out->ptr, dH_out->ld, H_out->ptr, H_out->ld, desc->act == HT_ACT_RELU, V, d, dz, ws.ld_t, ws.S, ws.p,
+                               ws.m, ws.zinv, ws.d4);
+  HT_LAUNCH_CHECK(ctx);
+  k_gat_dp<<<nb, 256, 0, st>>>(dz, Q, ws.ld_t, d, ws.S, ws.r, V, ws.dp);
+  HT_LAUNCH_CHECK(ctx);
+  tm->end();
+  GatPass a{};
+  a.items = S.items.items.p; a.n_items = S.items.n_items;
+  a.idx = S.idx.p; a.mult = g->merged ? S.mult.p : nullptr;
+  a.mat = dz; a.mat_ld = ws.ld_t; a.own = ws.T; a.own_ld = ws.ld_t; a.d = d;
+  a.q = ws.q; a.d4 = ws.d4; a.slope = desc->slope;
+  a.out = dT; a.out_ld = ld_dt; a.partial = s_part; a.sc_col = sc_col;
+  tm->begin(&local->t_gat_src_ms);
+  HT_TRY(launch_src(ctx, a, nvec));
+  if (S.items.n_cut > 0) {
+    SpmmArgs f{};
+    f.cuts = S.items.cuts.p; f.n_fix = S.items.n_cut;
+    f.d = sc_col + 4; f.out = dT; f.out_ld = ld_dt; f.partial = s_part;
+    HT_TRY(ht_spmm_fix_launch(ctx, st, f));
+  }
+  tm->end();
+  return HT_OK;
+}
+
 int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const ht_tensor* H_in, const float* W,
                  const float* a_dst, const float* a_src, const ht_tensor* H_out, const ht_tensor* dH_out,
-                 ht_tensor* dH_in, float* dW, float* da_dst, float* da_src, ht_stats* local, Timer* tm,
+                 ht_tensor* dH_in, float* dW, float* da_dst, float* da_src, const GatKeep* keep, ht_stats* local, Timer* tm,
                  bool dhin_is_zero) {
   HT_TRY(check_desc(ctx, desc));
   HT_TRY(check(ctx, g, desc, H_in, desc->d_in, "H_in"));
@@ -707,8 +988,9 @@ int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
   GatWs ws{};
   Link lk(ctx, local, tm);
   const bool hin_host = on_host(H_in), hout_host = on_host(H_out), dho_host = on_host(dH_out), dhi_host = on_host(dH_in);
-  if (hin_host || hout_host || dho_host || dhi_host) HT_TRY(lk.fork());
-  HT_TRY(prepare(ctx, g, desc, H_in, W, a_dst, a_src, true, &ws, local, tm, &lk));
+  const bool on_link = hin_host || hout_host || dho_host || dhi_host;
+  if (on_link) HT_TRY(lk.fork());
+  HT_TRY(bind_ws(ctx, g, desc->d_out, keep, &ws));
   const int d = desc->d_out;
   const int nvec = (d + 3) / 4;
   const int sc_col = (int)ws.ld_t;              // the scalar column block sits behind the padded data columns
@@ -716,10 +998,19 @@ int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
   const int64_t mx = std::max<int64_t>(g->max_ndst, 1);
   float *dT = nullptr, *dz = nullptr, *Q = nullptr, *da4 = nullptr;
   HT_TRY(ht_scratch(ctx, HT_S_TFULL2, (size_t)std::max<int64_t>(g->V, 1) * ld_dt * 4, (void**)&dT));
-  HT_TRY(ht_scratch(ctx, HT_S_DZCHUNK, (size_t)mx * ws.ld_t * 4, (void**)&dz));
-  HT_TRY(ht_scratch(ctx, HT_S_ACHUNK, (size_t)mx * ws.ld_t * 4, (void**)&Q));
   HT_TRY(ht_scratch(ctx, HT_S_MISC, (size_t)d * 16, (void**)&da4));
-  HT_TRY(ht_fill_zero(ctx, st, dT, (size_t)g->V * ld_dt * 4));
+  bool at_once = false;
+  if (!on_link)
+    HT_TRY(gat_bwd_rows_direct(ctx, g, desc, ws, keep, H_in, W, a_dst, a_src, H_out, dH_out, dT, ld_dt, local, tm, &lk, &at_once));
+  if (!at_once && keep) return ht_set_err(ctx, HT_ENOMEM, "GAT backward: no memory for all vertices at once beside what the forward pass kept");
+  RangeWs rw;
+  if (!at_once) {
+    HT_TRY(range_ws(ctx, ranges_of(g, 0, false), 0, ws.ld_t, &rw));
+    HT_TRY(prepare(ctx, g, desc, H_in, W, a_dst, a_src, &ws, local, tm, &lk));
+    HT_TRY(ht_scratch(ctx, HT_S_DZCHUNK, (size_t)mx * ws.ld_t * 4, (void**)&dz));
+    HT_TRY(ht_scratch(ctx, HT_S_ACHUNK, (size_t)mx * ws.ld_t * 4, (void**)&Q));
+    HT_TRY(ht_fill_zero(ctx, st, dT, (size_t)g->V * ld_dt * 4));
+  }
   // host-resident H_out / dH_out: the rows of the next chunk are staged while this one computes
   float* hbuf[2] = {nullptr, nullptr};
   float* gbuf[2] = {nullptr, nullptr};
@@ -734,7 +1025,12 @@ int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
   }
   std::vector<int> live;
   for (int j = 0; j < g->n; ++j)
-    if (g->chunks[j].dst1 > g->chunks[j].dst0) live.push_back(j);
+    if (g->chunks[j].dst1 > g->chunks[j].dst0) {
+      live.push_back(j);
+      local->n_spmm_bwd += 2;
+      local->edges += 2 * g->chunks[j].nnz;
+    }
+  if (at_once) live.clear();
   auto stage_chunk = [&](size_t i) -> int {
     if (!(hout_host || dho_host) || i >= live.size()) return HT_OK;
     const ChunkMeta& c = g->chunks[live[i]];
@@ -751,7 +1047,8 @@ int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
     const int64_t ndst = c.dst1 - c.dst0;
     const int b = (int)(i & 1);
     HT_TRY(stage_chunk(i + 1));
-    HT_TRY(softmax_chunk(ctx, g, c, desc, ws, local, tm, true));
+    const GatRange range = range_of(g, c);
+    HT_TRY(softmax_range(ctx, g, range, desc, ws, rw, local, tm));
     if (hout_host || dho_host) HT_TRY(lk.wait(st, ev_in[b]));
     k_gat_dz<<<(unsigned)((ndst + 3) / 4), 256, 0, st>>>(dho_host ? gbuf[b] : dH_out->ptr + c.dst0 * dH_out->ld, dH_out->ld,
                                                           hout_host ? hbuf[b] : H_out->ptr + c.dst0 * H_out->ld, H_out->ld,
@@ -760,28 +1057,12 @@ int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
     HT_LAUNCH_CHECK(ctx);
     if (hout_host || dho_host) HT_TRY(lk.rec(st, &ev_free[b]));   // the staged rows have been consumed
     GatPass a{};
-    a.d = d; a.p = ws.p; a.q = ws.q; a.m = ws.m; a.zinv = ws.zinv; a.S = ws.S; a.d4 = ws.d4; a.dst0 = c.dst0; a.slope = desc->slope;
-    // destination pass: Q_v = sum_e w_e f_e t_u through the aggregation kernel, then dp_v = dz_v . Q_v - S_v r_v
+    a.d = d; a.q = ws.q; a.d4 = ws.d4; a.slope = desc->slope;
+    // destination pass: Q_v = sum_e w_e f_e t_u, then dp_v = dz_v . Q_v - S_v r_v
     tm->begin(&local->t_gat_dst_ms);
-    {
-      float* fpart = nullptr;
-      if (c.fwd.n_part > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)g->max_fpart * ws.ld_t * 4, (void**)&fpart));
-      SpmmArgs q{};
-      q.items = g->fwd_items.items.p + c.fwd.it0; q.n_items = c.fwd.n_items;
-      q.cuts = g->fwd_items.cuts.p + c.fwd.cut0; q.n_fix = c.fwd.n_cut;
-      q.part0 = c.fwd.part0; q.row0 = c.dst0;
-      q.n_edges = g->merged ? c.nu : c.nnz;
-      q.idx = g->merged ? g->ucol.p : g->col.p;
-      q.w_edge = ws.wf; q.w0 = c.ue0;
-      q.src = ws.T; q.src_ld = ws.ld_t; q.d = d;
-      q.out = Q; q.out_ld = ws.ld_t;
-      q.accumulate = 0;
-      q.partial = fpart;
-      HT_TRY(ht_fill_zero(ctx, st, Q, (size_t)ndst * ws.ld_t * 4));     // rows without an in-edge have no item
-      HT_TRY(ht_spmm_launch(ctx, st, q));
-      k_gat_dp<<<(unsigned)((ndst + 3) / 4), 256, 0, st>>>(dz, Q, ws.ld_t, d, ws.S, ws.r + c.dst0, ndst, ws.dp + c.dst0);
-      HT_LAUNCH_CHECK(ctx);
-    }
+    HT_TRY(agg_range(ctx, g, range, desc, ws, rw, AGG_Q, nullptr, 0, Q, nullptr, nullptr, tm));
+    k_gat_dp<<<(unsigned)((ndst + 3) / 4), 256, 0, st>>>(dz, Q, ws.ld_t, d, ws.S, ws.r + c.dst0, ndst, ws.dp + c.dst0);
+    HT_LAUNCH_CHECK(ctx);
     tm->end();
     // source pass
     float* partial = nullptr;
@@ -791,7 +1072,7 @@ int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
     a.mult = g->merged ? g->umult_bwd.p : nullptr;
     a.mat = dz; a.mat_ld = ws.ld_t;
     a.own = ws.T; a.own_ld = ws.ld_t; a.own_idx = g->nbr.p;
-    a.out = dT; a.out_ld = ld_dt; a.out_idx = g->nbr.p;
+    a.out = dT; a.out_ld = ld_dt; a.add = true;
     a.partial = partial; a.sc_col = sc_col;
     tm->begin(&local->t_gat_src_ms);
     if (a.n_items > 0) HT_TRY(launch_src(ctx, a, nvec));
@@ -805,8 +1086,6 @@ int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
       HT_TRY(ht_spmm_fix_launch(ctx, st, f));
     }
     tm->end();
-    local->n_spmm_bwd += 2;
-    local->edges += 2 * c.nnz;
   }
   if (g->V > 0) {
     k_gat_finish<<<(unsigned)std::min<int64_t>((g->V + 3) / 4, 1 << 22), 256, 0, st>>>(dT, ld_dt, d, sc_col, ws.dp, a_dst, a_src, g->V, ws.pq4);
@@ -837,7 +1116,7 @@ int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
     const int b = k & 1;
     const float* h_rows = H_in->ptr + r0 * H_in->ld;
     float* dh_rows = dH_in ? dH_in->ptr + r0 * dH_in->ld : nullptr;
-    const bool dh_add = !(dhi_host && dhin_is_zero);
+    const bool dh_add = !dhin_is_zero;
     if (hin_host || dhi_host) {
       hipEvent_t ev_bin = nullptr;
       HT_TRY(lk.wait(lk.s_in, ev_bfree[b]));
@@ -894,7 +1173,7 @@ int ht_gat_layer_fwd(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, co
   auto t0 = std::chrono::steady_clock::now();
   ht_stats local{};
   Timer tm(ctx, ctx->stream, stats != nullptr);
-  int rc = gat_fwd_impl(ctx, g, desc, H_in, W, a_dst, a_src, H_out, &local, &tm, 0);
+  int rc = gat_fwd_impl(ctx, g, desc, H_in, W, a_dst, a_src, H_out, nullptr, &local, &tm, 0);
   hipError_t e = hipStreamSynchronize(ctx->stream);
   if (rc == HT_OK && e == hipSuccess) rc = tm.resolve();
   ctx->ev_next = 0;
@@ -918,7 +1197,7 @@ int ht_gat_layer_bwd(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, co
   auto t0 = std::chrono::steady_clock::now();
   ht_stats local{};
   Timer tm(ctx, ctx->stream, stats != nullptr);
-  int rc = gat_bwd_impl(ctx, g, desc, H_in, W, a_dst, a_src, H_out, dH_out, dH_in, dW, da_dst, da_src, &local, &tm, false);
+  int rc = gat_bwd_impl(ctx, g, desc, H_in, W, a_dst, a_src, H_out, dH_out, dH_in, dW, da_dst, da_src, nullptr, &local, &tm, false);
   hipError_t e = hipStreamSynchronize(ctx->stream);
   if (rc == HT_OK && e == hipSuccess) rc = tm.resolve();
   ctx->ev_next = 0;
@@ -994,27 +1273,56 @@ int ht_gat_epoch(ht_ctx* ctx, const ht_graph* g, const ht_gat_model* model, cons
     ctx->ev_next = 0;
     return rc;
   };
-  for (int l = 0; l < L; ++l) {
-    ht_gat_desc d{model->dims[l], model->dims[l + 1], l < L - 1 ? HT_ACT_RELU : HT_ACT_NONE, model->slope};
-    int rc = gat_fwd_impl(ctx, g, &d, l == 0 ? X : &h[l], model->W[l], model->a_dst[l], model->a_src[l], &h[l + 1], &local, &tm, l);
-    if (rc != HT_OK) return fail(rc);
-  }
-  {
-    tm.begin(&local.t_loss_ms);
-    int rc = ht_softmax_ce(ctx, st, h[L].ptr, h[L].ld, labels, V, model->dims[L], gh[L].ptr, gh[L].ld, loss_dev);
-    tm.end();
-    if (rc != HT_OK) return fail(rc);
-  }
-  for (int l = L - 1; l >= 0; --l) {
-    ht_gat_desc d{model->dims[l], model->dims[l + 1], l < L - 1 ? HT_ACT_RELU : HT_ACT_NONE, model->slope};
-    if (l > 0 && gh[l].loc == HT_LOC_DEVICE) {   // (a host-resident gradient is written, not added to)
-      int rc = ht_fill_zero(ctx, st, gh[l].ptr, (size_t)V * gh[l].ld * 4);
-      if (rc != HT_OK) return fail(rc);
+  // What the layers' forward passes leave for their backward passes, with everything in HBM and room for it: the backward pass
+  // then neither transforms, scores nor gathers over the destinations again (each layer's second gather of t rides on the first).
+  std::vector<GatKeep> keep;
+  if (!h_host && X->loc == HT_LOC_DEVICE && V > 0) {
+    size_t kf = 0;
+    HT_TRY(ht_graph_by_source(ctx, g));
+    for (int l = 1; l <= L; ++l) kf += (size_t)V * (2 * ht_row_pitch(model->dims[l], true) + 5) + 7 * 32;
+    float* kp = nullptr;
+    bool room = kf * 4 <= (size_t)GAT_KEEP_BYTES && (ctx->gat_keep_limit == 0 || kf * 4 < ctx->gat_keep_limit);
+    for (int l = 1; l <= L; ++l) room = room && src_fits(g, model->dims[l], true);
+    if (room) {
+      const int rc = ht_scratch(ctx, HT_S_GATKEEP, kf * 4, (void**)&kp);
+      if (rc != HT_OK && rc != HT_ENOMEM) return rc;
     }
-    int rc = gat_bwd_impl(ctx, g, &d, l == 0 ? X : &h[l], model->W[l], model->a_dst[l], model->a_src[l], &h[l + 1], &gh[l + 1],
-                          l > 0 ? &gh[l] : nullptr, dW[l], dad[l], das[l], &local, &tm, true);
-    if (rc != HT_OK) return fail(rc);
+    auto cut = [&](size_t n) { float* p = kp; kp += (n + 31) & ~(size_t)31; return p; };
+    for (int l = 1; l <= L && kp; ++l) {
+      const size_t n = (size_t)V * ht_row_pitch(model->dims[l], true);
+      GatKeep k;
+      k.T = cut(n); k.Q = cut(n);
+      k.p = cut(V); k.q = cut(V); k.m = cut(V); k.zinv = cut(V); k.r = cut(V);
+      keep.push_back(k);
+    }
   }
+  auto passes = [&]() -> int {
+    for (int l = 0; l < L; ++l) {
+      ht_gat_desc d{model->dims[l], model->dims[l + 1], l < L - 1 ? HT_ACT_RELU : HT_ACT_NONE, model->slope};
+      HT_TRY(gat_fwd_impl(ctx, g, &d, l == 0 ? X : &h[l], model->W[l], model->a_dst[l], model->a_src[l], &h[l + 1],
+                          keep.empty() ? nullptr : &keep[l], &local, &tm, l));
+    }
+    tm.begin(&local.t_loss_ms);
+    HT_TRY(ht_softmax_ce(ctx, st, h[L].ptr, h[L].ld, labels, V, model->dims[L], gh[L].ptr, gh[L].ld, loss_dev));
+    tm.end();
+    for (int l = L - 1; l >= 0; --l) {
+      ht_gat_desc d{model->dims[l], model->dims[l + 1], l < L - 1 ? HT_ACT_RELU : HT_ACT_NONE, model->slope};
+      HT_TRY(gat_bwd_impl(ctx, g, &d, l == 0 ? X : &h[l], model->W[l], model->a_dst[l], model->a_src[l], &h[l + 1], &gh[l + 1],
+                          l > 0 ? &gh[l] : nullptr, dW[l], dad[l], das[l], keep.empty() ? nullptr : &keep[l], &local, &tm, true));
+    }
+    return HT_OK;
+  };
+  int rc = passes();
+  if (rc == HT_ENOMEM && !keep.empty()) {   // again without keeping anything (nothing of the caller's was changed yet)
+    (void)fail(rc);
+    ctx->gat_keep_limit = ctx->scratch_bytes[HT_S_GATKEEP] * 8 / 9;      // (a slot is an eighth larger than asked for)
+    (void)ht_scratch_release(ctx, HT_S_GATKEEP);
+    keep.clear();
+    local = ht_stats{};
+    tm.ev.clear();
+    rc = passes();
+  }
+  if (rc != HT_OK) return fail(rc);
   for (int l = 0; l < L; ++l) {
     int rc = ht_sgd(ctx, st, model->W[l], dW[l], (int64_t)model->dims[l] * model->dims[l + 1], model->lr);
     if (rc == HT_OK) rc = ht_sgd(ctx, st, model->a_dst[l], dad[l], model->dims[l + 1], model->lr);

@@ -453,6 +453,14 @@ int ht_gemm_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const f
   return launch_tn(ctx, st, A, lda, B, ldb, C, M, K, N, rows, slices, nullptr, accumulate);
 }
 
+int ht_gemm_reserve(ht_ctx* ctx, int64_t M, int32_t K, int32_t N) {
+  int64_t rows, slices;
+  SliceRule{tn_tiles(K, N)}.cut(std::max<int64_t>(M, 1), &rows, &slices);
+  void* p = nullptr;
+  HT_TRY(ht_scratch(ctx, HT_S_TNPART, (size_t)(slices * K * N) * 4, &p));
+  return ht_scratch(ctx, HT_S_PACKW, (size_t)std::max(ht_packed_w_bytes(K, N), ht_packed_w_bytes(N, K)), &p);
+}
+
 // The row groups' sums one after the other, as ht_gemm_tn called once per group would add them, in as few launches as the
 // partial tiles' memory allows.
 int ht_gemm_tn_groups(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int32_t K,

@@ -20,7 +20,7 @@ struct EpochWs;
 
 enum {
   HT_S_PACKW = 0, HT_S_TNPART, HT_S_LOSS, HT_S_ACHUNK, HT_S_OCHUNK, HT_S_ZCHUNK, HT_S_DZCHUNK, HT_S_DACHUNK,
-  HT_S_NBUF, HT_S_SPART, HT_S_LEAVE, HT_S_MISC, HT_S_TFULL, HT_S_TFULL2, HT_S_GATV, HT_S_GATE, HT_S_GATWS, HT_S_GATP,
+  HT_S_NBUF, HT_S_SPART, HT_S_LEAVE, HT_S_MISC, HT_S_TFULL, HT_S_TFULL2, HT_S_GATV, HT_S_GATE, HT_S_GATWS, HT_S_GATP, HT_S_GATKEEP,
   HT_S_LINK0, HT_S_LINK1, HT_S_LINK2, HT_S_SCAN, HT_S_RSORT, HT_S_TNTAB, HT_N_SCRATCH
 };
 
@@ -64,6 +64,7 @@ struct ht_ctx {
   int agg_phases = 1;     // HT_AGG_PHASES: slabs are spread over this many consecutive launches
   int64_t link_block_rows = (int64_t)1 << 20;   // HT_LINK_BLOCK_ROWS: rows per staged block of a host-resident tensor (GAT path)
   int agg_variant = 0;  // 0: feature slabs per XCD; 1: full-width rows per wave (HT_AGG_VARIANT, for A/B runs)
+  size_t gat_keep_limit = 0;   // a GAT epoch that kept this many bytes between its passes ran out of memory (0: none did)
   int fuse_update = 0;  // HT_FUSE_UPDATE=1: layers that keep no aggregate run aggregate + transform as one kernel (A/B)
   int n_threads = 0;  // host threads for CPU-side accumulation (0 = chosen on first use)
 };
@@ -96,6 +97,8 @@ int ht_dev_alloc(ht_ctx* ctx, void** out, size_t bytes);
 void ht_dev_free(ht_ctx* ctx, void* p, size_t bytes);
 // Grow-only scratch slot (kept on the context).
 int ht_scratch(ht_ctx* ctx, int slot, size_t bytes, void** out);
+// Gives a slot's memory back (after the work in flight).
+int ht_scratch_release(ht_ctx* ctx, int slot);
 // Grow-only pinned host scratch.
 constexpr int HT_HS_READBACK = 3;
 int ht_host_scratch(ht_ctx* ctx, int slot, size_t bytes, void** out);
@@ -234,6 +237,7 @@ struct SourceRows {
   DevBlock blk;
   DevArr<int32_t> idx;         // destination of each entry
   DevArr<float> w;             // multiplicity * s[destination] (merged graphs; others look s up)
+  DevArr<float> mult;          // multiplicity (merged graphs, made for the first GAT backward pass)
   GraphItems items;            // rows = vertices
 };
 
@@ -295,6 +299,8 @@ struct ht_graph {
 
 // Makes g->by_src if it was not tried yet.
 int ht_graph_by_source(ht_ctx* ctx, const ht_graph* g);
+// Makes g->by_src.mult of a merged graph whose by_src is there (HT_ENOMEM: no memory for it).
+int ht_graph_by_source_mult(ht_ctx* ctx, const ht_graph* g);
 
 // ---- compute kernels' host launchers -----------------------------------------------------
 // Aggregation over work items (ht_spmm.hip).  One wave (or a lane group of it)
@@ -332,6 +338,14 @@ struct SpmmArgs {
   double* t_fix = nullptr;
 };
 int ht_spmm_launch(ht_ctx* ctx, hipStream_t st, const SpmmArgs& a);
+// How an aggregation is spread over the XCDs (d, n_items, n_edges, src, src_ld and max_slabs of `a` are read): P launches of
+// S slabs of nvs float4 columns, eps entries per step of a wave.
+struct SlabShape {
+  int S, P, nvs, eps;
+  unsigned blocks;
+  int64_t grp_per_part;      // 0: items interleaved over the XCDs of a slab
+};
+int ht_slab_shape(ht_ctx* ctx, const SpmmArgs& a, SlabShape* out);
 // Only the second kernel: the cut rows = their partial rows added in item order (d, out*, partial, cuts, part0 are read).
 int ht_spmm_fix_launch(ht_ctx* ctx, hipStream_t st, const SpmmArgs& a);
 
@@ -359,6 +373,8 @@ int ht_gemm_nt(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const f
 int ht_gemm_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
                int64_t M, int32_t K, int32_t N, int accumulate);
 
+// Takes the scratch memory of ht_gemm_tn and ht_gemm_nt calls of up to M rows: no later call of these fails for want of it.
+int ht_gemm_reserve(ht_ctx* ctx, int64_t M, int32_t K, int32_t N);
 // C[K x N] = sum over the row groups [groups[2g], groups[2g+1]) of A^T B, added group by group (d_groups: the same on the device).
 int ht_gemm_tn_groups(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int32_t K,
                       int32_t N, const std::vector<int64_t>& groups, const int64_t* d_groups);

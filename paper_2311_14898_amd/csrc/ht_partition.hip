@@ -844,6 +844,13 @@ __global__ void __launch_bounds__(TB) k_src_copy(const WorkItem* __restrict__ it
   }
 }
 
+// The multiplicity out of w = multiplicity * s[destination]: both roundings together are off by less than 2^-23 of it, so
+// rounding to a whole number gives it back exactly below 2^22 (and its fp32 neighbour above).
+__global__ void __launch_bounds__(TB) k_src_mult(const float* __restrict__ w, const int32_t* __restrict__ idx, const float* __restrict__ s,
+                                                 int64_t n, float* __restrict__ mult) {
+  for (int64_t e = (int64_t)blockIdx.x * TB + threadIdx.x; e < n; e += (int64_t)gridDim.x * TB) mult[e] = rintf(w[e] / s[idx[e]]);
+}
+
 int bits_for(int64_t n) {  // bits needed for values 0..n-1 (at least 1)
   int b = 1;
   while (((int64_t)1 << b) < n) ++b;
@@ -1593,12 +1600,23 @@ int ht_graph_by_source(ht_ctx* ctx, const ht_graph* g) {
   return rc == HT_ENOMEM ? HT_OK : rc;
 }
 
+int ht_graph_by_source_mult(ht_ctx* ctx, const ht_graph* g) {
+  SourceRows& S = g->by_src;
+  if (!g->merged || S.mult.p) return HT_OK;
+  HT_TRY(S.mult.alloc(ctx, (size_t)g->n_unique));
+  if (g->n_unique > 0) {
+    k_src_mult<<<(unsigned)std::min<int64_t>((g->n_unique + TB - 1) / TB, 1 << 16), TB, 0, ctx->stream>>>(S.w.p, S.idx.p, g->s.p, g->n_unique, S.mult.p);
+    HT_LAUNCH_CHECK(ctx);
+  }
+  return HT_OK;
+}
+
 int64_t ht_graph::hbm_bytes() const {
   int64_t b = indptr.bytes() + col.bytes() + s.bytes() + nbr.bytes() + col_local.bytes() + col_slot.bytes() +
               sptr.bytes() + sdst.bytes() + slot.bytes() + gslot.bytes() + reuse.bytes() + load.bytes() +
               load_slot.bytes() + leave.bytes() + leave_slot.bytes() + uindptr.bytes() + ucol.bytes() +
               ucol_slot.bytes() + uw_fwd.bytes() + umult.bytes() + usdst.bytes() + uw_bwd.bytes() + umult_bwd.bytes() + usptr.bytes();
-  b += (int64_t)by_src.blk.mem.bytes();
+  b += (int64_t)(by_src.blk.mem.bytes() + by_src.mult.bytes());
   for (const GraphItems* i : {&fwd_items, &bwd_items}) b += i->n_items * (int64_t)sizeof(WorkItem) + i->n_cut * (int64_t)sizeof(CutRow);
   return b;
 }

@@ -308,6 +308,32 @@ static_assert(row_blocks(1000, 4, 64) == 64 && row_blocks(100, 4, 64) == 25 && r
 
 }  // namespace
 
+int ht_slab_shape(ht_ctx* ctx, const SpmmArgs& a, SlabShape* out) {
+  const int nvec = (a.d + 3) / 4;
+  // Slabs cost one pass over the item's indices each, so short rows get fewer:
+  // measured best on 256-wide rows is 4 slabs for ~500-edge items and 1 for ~80-edge items.
+  int S = nvec >= 32 ? 4 : nvec >= 16 ? 2 : 1;
+  const int64_t avg_len = a.n_edges / (a.n_items > 0 ? a.n_items : 1);
+  if (avg_len < 96) S = 1;
+  else if (avg_len < 192 && S > 2) S = 2;
+  if (a.max_slabs > 0) S = a.max_slabs;                // experiments: force a slab count
+  while (S > 1 && nvec / S < 1) S /= 2;
+  int P = ctx->agg_phases;
+  while (P > 1 && nvec / (S * P) < 1) P /= 2;
+  while (S < 8 && (nvec + S * P - 1) / (S * P) > 64) S *= 2;   // a slab must fit the 64 lanes of a wave
+  int nvs = (nvec + S * P - 1) / (S * P);
+  // rows that start on 128-byte lines: slabs in whole lines, so no line is fetched by two XCDs
+  if (ctx->slab_align && (a.src_ld & 31) == 0 && ((uintptr_t)a.src & 127) == 0 && nvs > 8 && ((nvs + 7) & ~7) <= 64) nvs = (nvs + 7) & ~7;
+  const int eps = 64 / nvs;
+  if (S < 1 || (S & (S - 1)) || S > 8 || nvs < 1 || nvs > 64 || eps < 1)
+    return ht_set_err(ctx, HT_ESHAPE, "aggregation: bad slab shape S=%d nvs=%d", S, nvs);
+  const int64_t groups = (a.n_items + 3) / 4;
+  const int parts = 8 / S;
+  const int64_t gpp = (groups + parts - 1) / parts;   // item groups per XCD of a slab
+  *out = SlabShape{S, P, nvs, eps, (unsigned)(gpp * 8), ctx->xcd_contig ? gpp : 0};
+  return HT_OK;
+}
+
 int ht_spmm_launch(ht_ctx* ctx, hipStream_t st, const SpmmArgs& a0) {
   if (a0.n_items <= 0) return HT_OK;
   if ((a0.src_ld & 3) || (a0.out_ld & 3)) return ht_set_err(ctx, HT_ESHAPE, "aggregation: row pitch must be a multiple of 4");
@@ -322,30 +348,12 @@ int ht_spmm_launch(ht_ctx* ctx, hipStream_t st, const SpmmArgs& a0) {
     int rc = HT_OK;
     if (a.tm && a.t_items) a.tm->begin(a.t_items);
     if (ctx->agg_variant == 0) {
-      // Slabs cost one pass over the item's indices each, so short rows get fewer:
-      // measured best on 256-wide rows is 4 slabs for ~500-edge items and 1 for ~80-edge items.
-      int S = nvec >= 32 ? 4 : nvec >= 16 ? 2 : 1;
-      const int64_t avg_len = a.n_edges / (a.n_items > 0 ? a.n_items : 1);
-      if (avg_len < 96) S = 1;
-      else if (avg_len < 192 && S > 2) S = 2;
-      if (a.max_slabs > 0) S = a.max_slabs;                // experiments: force a slab count
-      while (S > 1 && nvec / S < 1) S /= 2;
-      int P = ctx->agg_phases;
-      while (P > 1 && nvec / (S * P) < 1) P /= 2;
-      while (S < 8 && (nvec + S * P - 1) / (S * P) > 64) S *= 2;   // a slab must fit the 64 lanes of a wave
-      int nvs = (nvec + S * P - 1) / (S * P);
-      // rows that start on 128-byte lines: slabs in whole lines, so no line is fetched by two XCDs
-      if (ctx->slab_align && (a.src_ld & 31) == 0 && ((uintptr_t)a.src & 127) == 0 && nvs > 8 && ((nvs + 7) & ~7) <= 64) nvs = (nvs + 7) & ~7;
-      const int eps = 64 / nvs;
-      if (S < 1 || (S & (S - 1)) || S > 8 || nvs < 1 || nvs > 64 || eps < 1)
-        return ht_set_err(ctx, HT_ESHAPE, "aggregation: bad slab shape S=%d nvs=%d", S, nvs);
-      const int64_t groups = (a.n_items + 3) / 4;
-      const int parts = 8 / S;
-      const int64_t gpp = (groups + parts - 1) / parts;   // item groups per XCD of a slab
-      const int64_t rows8 = ctx->xcd_contig ? gpp : (groups + parts - 1) / parts;
-      for (int p = 0; p < P; ++p) {
-        const unsigned nb = (unsigned)(rows8 * 8);
-        const int64_t gp = ctx->xcd_contig ? gpp : 0;
+      SlabShape sh;
+      HT_TRY(ht_slab_shape(ctx, a, &sh));
+      const int S = sh.S, nvs = sh.nvs, eps = sh.eps;
+      for (int p = 0; p < sh.P; ++p) {
+        const unsigned nb = sh.blocks;
+        const int64_t gp = sh.grp_per_part;
         const bool uni = eps == 1 && ctx->agg_uniform;
         if (ctx->agg_unroll == 8) {
           if (uni) k_spmm_slab<8, true><<<nb, 256, 0, st>>>(a, S, nvs, eps, gp, p * S);
