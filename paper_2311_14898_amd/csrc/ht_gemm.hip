@@ -327,12 +327,20 @@ __global__ void __launch_bounds__(256) k_reduce_slices(const float* __restrict__
 }
 
 // Slices of a reduction over M rows: as many as fill the GPU with `tiles` output tiles each, not below 256 rows; a slice is a
-// multiple of the step.
+// multiple of the step.  `alone` (one row group, nothing beside it): down to 64 rows until there is a block per CU.  A slice is
+// a chain of loads, about 1.7 us per step of 16 rows, and slices add partial tiles to write and read: 10,000 rows, 64 x 32:
+// 28 -> 10 us; beyond a block per CU the chain is hidden by other blocks and only the partial tiles would grow.
 struct SliceRule {
   int tiles;
+  bool alone = false;
   __host__ __device__ void cut(int64_t M, int64_t* rows, int64_t* slices) const {
     int64_t s = (1024 + tiles - 1) / tiles;
-    const int64_t most = (M + 255) / 256;
+    int64_t most = (M + 255) / 256;
+    if (alone) {
+      const int64_t per_cu = (256 + tiles - 1) / tiles, finest = (M + 63) / 64;
+      const int64_t fine = finest < per_cu ? finest : per_cu;
+      if (fine > most) most = fine;
+    }
     if (s > most) s = most;
     if (s < 1) s = 1;
     int64_t r = (M + s - 1) / s;
@@ -449,13 +457,13 @@ int ht_gemm_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const f
     return HT_OK;
   }
   int64_t rows, slices;
-  SliceRule{tn_tiles(K, N)}.cut(M, &rows, &slices);
+  SliceRule{tn_tiles(K, N), true}.cut(M, &rows, &slices);
   return launch_tn(ctx, st, A, lda, B, ldb, C, M, K, N, rows, slices, nullptr, accumulate);
 }
 
 int ht_gemm_reserve(ht_ctx* ctx, int64_t M, int32_t K, int32_t N) {
   int64_t rows, slices;
-  SliceRule{tn_tiles(K, N)}.cut(std::max<int64_t>(M, 1), &rows, &slices);
+  SliceRule{tn_tiles(K, N), true}.cut(std::max<int64_t>(M, 1), &rows, &slices);
   void* p = nullptr;
   HT_TRY(ht_scratch(ctx, HT_S_TNPART, (size_t)(slices * K * N) * 4, &p));
   return ht_scratch(ctx, HT_S_PACKW, (size_t)std::max(ht_packed_w_bytes(K, N), ht_packed_w_bytes(N, K)), &p);
