@@ -150,7 +150,7 @@ __global__ void __launch_bounds__(256) k_gat_rowstats(const CutRow* __restrict__
 // What bounds it is the gather of the rows of t (the slab split is that of the GCN aggregation, for its reasons); the second sum
 // of the same rows costs four fused multiply-adds per loaded float4, where a pass of its own costs the gather again, and the
 // exponential of an entry costs less than the kernel that wrote the coefficients and the read of them did (233 k vertices, 115 M
-// edges, widths 256 and 41: forward, coefficients and destination pass 14.1 ms per epoch as passes of their own, 6.0 ms here).
+// edges, widths 256 and 41: forward, coefficients and destination pass 12.3 ms per epoch as passes of their own, 6.0 ms here).
 struct GatAgg {
   const WorkItem* items; int64_t n_items; int64_t ent0, part0, row0;
   const int32_t* col; const float* mult;      // per entry of the graph
@@ -235,15 +235,14 @@ __global__ void __launch_bounds__(256) k_gat_agg(GatAgg a, int S, int nvs, int e
       }
     }
   }
-  // the sum of a row's edge slots in slot order; slot 0 holds the result
-  auto slots = [&](float4 own) {
-    float4 tot = own;
-    for (int q = 1; q < eps; ++q) {
-      const int from = (lane + q * nvs) & 63;
-      tot.x += __shfl(own.x, from, 64);
-      tot.y += __shfl(own.y, from, 64);
-      tot.z += __shfl(own.z, from, 64);
-      tot.w += __shfl(own.w, from, 64);
+  // the sum of a row's edge slots, the upper half added to the lower one until slot 0 holds the result (one after the other, 31
+  // additions at 7 columns: 20 k vertices, 300 k edges, 33 and 7 columns, 43 -> 20 us per launch)
+  auto slots = [&](float4 tot) {
+    for (int n = eps; n > 1;) {
+      const int h = (n + 1) >> 1, from = (lane + h * nvs) & 63;
+      const float4 o = make_float4(__shfl(tot.x, from, 64), __shfl(tot.y, from, 64), __shfl(tot.z, from, 64), __shfl(tot.w, from, 64));
+      if (es + h < n) tot = make_float4(tot.x + o.x, tot.y + o.y, tot.z + o.z, tot.w + o.w);
+      n = h;
     }
     return tot;
   };

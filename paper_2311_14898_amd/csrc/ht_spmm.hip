@@ -227,12 +227,14 @@ __global__ void __launch_bounds__(256) k_spmm_slab(SpmmArgs a, int S, int nvs, i
       }
     }
   }
-  // add the edge slots in slot order; slot 0 holds the result
+  // add the edge slots, the upper half to the lower one until slot 0 holds the result (narrow rows have up to 64 slots: one after
+  // the other they took longer than a short row's loads)
   float4 tot = acc;
-  for (int q = 1; q < eps; ++q) {
-    const int from = (lane + q * nvs) & 63;
-    float4 o = make_float4(__shfl(acc.x, from, 64), __shfl(acc.y, from, 64), __shfl(acc.z, from, 64), __shfl(acc.w, from, 64));
-    tot = add4(tot, o);
+  for (int n = eps; n > 1;) {
+    const int h = (n + 1) >> 1, from = (lane + h * nvs) & 63;
+    const float4 o = make_float4(__shfl(tot.x, from, 64), __shfl(tot.y, from, 64), __shfl(tot.z, from, 64), __shfl(tot.w, from, 64));
+    if (es + h < n) tot = add4(tot, o);
+    n = h;
   }
   if (es != 0 || vec >= nv_here) return;
   if (part >= 0)
