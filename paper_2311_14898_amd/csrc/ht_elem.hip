@@ -99,9 +99,18 @@ __global__ void k_finish_loss(const double* __restrict__ sum, const unsigned lon
   *loss = T > 0 ? (float)(*sum / (double)T) : 0.f;
 }
 
-__global__ void k_sgd(float* __restrict__ W, const float* __restrict__ dW, int64_t n, float lr) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) W[i] = W[i] - lr * dW[i];
+// One launch for all parameters of a model (a launch each costs its 4 us whatever the size): tensor t has the blocks from
+// first[t] on.
+struct SgdBatch {
+  int n;
+  unsigned first[HT_SGD_MAX + 1];
+  ht_sgd_item t[HT_SGD_MAX];
+};
+__global__ void k_sgd(SgdBatch b, float lr) {
+  int k = 0;
+  while (k + 1 < b.n && blockIdx.x >= b.first[k + 1]) ++k;
+  const int64_t i = (int64_t)(blockIdx.x - b.first[k]) * blockDim.x + threadIdx.x;
+  if (i < b.t[k].n) b.t[k].W[i] = b.t[k].W[i] - lr * b.t[k].dW[i];
 }
 
 // n16 16-byte words from p16 (16-byte aligned), then the words of the ragged ends; a bounded grid
@@ -167,10 +176,23 @@ int ht_softmax_ce(ht_ctx* ctx, hipStream_t st, const float* logits, int64_t ld, 
   return HT_OK;
 }
 
-int ht_sgd(ht_ctx* ctx, hipStream_t st, float* W, const float* dW, int64_t n, float lr) {
-  if (n <= 0) return HT_OK;
-  k_sgd<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(W, dW, n, lr);
-  HT_LAUNCH_CHECK(ctx);
+int ht_sgd(ht_ctx* ctx, hipStream_t st, const std::vector<ht_sgd_item>& items, float lr) {
+  for (size_t i = 0; i < items.size();) {
+    SgdBatch b{};
+    for (; i < items.size() && b.n < HT_SGD_MAX; ++i) {
+      const ht_sgd_item& it = items[i];
+      if (it.n <= 0) continue;
+      bool shared = false;      // (parameters that share memory are updated one after the other)
+      for (int k = 0; k < b.n; ++k) shared = shared || (it.W < b.t[k].W + b.t[k].n && b.t[k].W < it.W + it.n);
+      if (shared) break;
+      b.t[b.n] = it;
+      b.first[b.n + 1] = b.first[b.n] + (unsigned)((it.n + 255) / 256);
+      ++b.n;
+    }
+    if (b.n == 0) continue;
+    k_sgd<<<b.first[b.n], 256, 0, st>>>(b, lr);
+    HT_LAUNCH_CHECK(ctx);
+  }
   return HT_OK;
 }
 

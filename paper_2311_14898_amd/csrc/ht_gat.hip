@@ -62,21 +62,45 @@ __device__ __forceinline__ float coef(float y, float slope, float m, float zinv,
   return mult * expf(x - m) * zinv;
 }
 
-// p[v] = a_dst . T[v], q[v] = a_src . T[v]; a wave per vertex
+// sum over a group of `lpr` lanes (a power of two)
+__device__ __forceinline__ float group_sum(float x, int lpr) {
+  for (int o = lpr >> 1; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+  return x;
+}
+// the attention vectors (at most 1024 long) in LDS, zero behind their end
+struct AttVec {
+  float4 dst[256], src[256];
+};
+__device__ __forceinline__ void load_att(AttVec& s, const float* a_dst, const float* a_src, int d) {
+  for (int c = threadIdx.x; c < ((d + 3) & ~3); c += 256) {
+    reinterpret_cast<float*>(s.dst)[c] = c < d ? a_dst[c] : 0.f;
+    reinterpret_cast<float*>(s.src)[c] = c < d ? a_src[c] : 0.f;
+  }
+  __syncthreads();
+}
+__device__ __forceinline__ float dot4(float4 a, float4 b, float s) { return fmaf(a.x, b.x, fmaf(a.y, b.y, fmaf(a.z, b.z, fmaf(a.w, b.w, s)))); }
+// Lanes per row of the kernels below, which go over the rows of a matrix once: a float4 each, 8 to 64 (a wave per row left most
+// lanes of narrow rows idle: 20 k rows of 33 and 7 columns, 6.7 + 5.4 us for dz and dp, 5.0 us for both now).
+unsigned row_grid(int64_t rows, int lpr) { return (unsigned)std::min<int64_t>((rows * lpr + 255) / 256, 8192); }
+int row_lanes(int64_t ld) { return ld <= 32 ? 8 : ld <= 64 ? 16 : ld <= 128 ? 32 : 64; }
+
+// p[v] = a_dst . T[v], q[v] = a_src . T[v]; lpr lanes per vertex
 __global__ void __launch_bounds__(256) k_gat_pq(const float* __restrict__ T, int64_t ld, int d, const float* __restrict__ a_dst,
                                                 const float* __restrict__ a_src, int64_t V, float* __restrict__ p,
-                                                float* __restrict__ q) {
-  const int lane = threadIdx.x & 63;
-  for (int64_t v = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); v < V; v += (int64_t)gridDim.x * 4) {
+                                                float* __restrict__ q, int lpr) {
+  __shared__ AttVec sa;
+  load_att(sa, a_dst, a_src, d);
+  const int rpb = 256 / lpr, ll = threadIdx.x % lpr;
+  for (int64_t v = (int64_t)blockIdx.x * rpb + threadIdx.x / lpr; v < V; v += (int64_t)gridDim.x * rpb) {
     float sp = 0.f, sq = 0.f;
-    for (int c = lane; c < d; c += 64) {
-      const float t = T[v * ld + c];
-      sp = fmaf(a_dst[c], t, sp);
-      sq = fmaf(a_src[c], t, sq);
+    for (int c = ll * 4; c < d; c += lpr * 4) {   // (the pads of t up to the next multiple of 4 are zero)
+      const float4 t = ld4(T + v * ld + c);
+      sp = dot4(sa.dst[c >> 2], t, sp);
+      sq = dot4(sa.src[c >> 2], t, sq);
     }
-    sp = wave_sum(sp);
-    sq = wave_sum(sq);
-    if (lane == 0) {
+    sp = group_sum(sp, lpr);
+    sq = group_sum(sq, lpr);
+    if (ll == 0) {
       p[v] = sp;
       q[v] = sq;
     }
@@ -270,45 +294,42 @@ __global__ void __launch_bounds__(256) k_gat_agg(GatAgg a, int S, int nvs, int e
   }
 }
 
-// dp_v = dz_v . Q_v - S_v r_v; a wave per row of the chunk
-__global__ void __launch_bounds__(256) k_gat_dp(const float* __restrict__ dz, const float* __restrict__ Q, int64_t ld, int d,
-                                                const float* __restrict__ S, const float* __restrict__ r_chunk, int64_t rows,
-                                                float* __restrict__ dp_chunk) {
-  const int lane = threadIdx.x & 63;
-  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (r >= rows) return;
-  float s = 0.f;
-  for (int c = lane; c < d; c += 64) s = fmaf(dz[r * ld + c], Q[r * ld + c], s);
-  s = wave_sum(s);
-  if (lane == 0) dp_chunk[r] = s - S[r] * r_chunk[r];
-}
-
-// dz = dh * [h > 0] (or dh), pad columns zero, S_v = dz_v . h_v, and d4[row] = (p_v, m_v, 1/Z_v, S_v) (p, m, zinv
-// point at the chunk's first destination); a wave per row of the chunk
+// Over the rows of a range, lpr lanes per row: dz = dh * [h > 0] (or dh), pad columns zero; S_v = dz_v . h_v;
+// dp_v = dz_v . Q_v - S_v r_v; d4[row] = (p_v, m_v, 1/Z_v, S_v).  (p, m, zinv, r, dp point at the range's first row.)
 __global__ void __launch_bounds__(256) k_gat_dz(const float* __restrict__ dh, int64_t ld_dh, const float* __restrict__ h,
                                                 int64_t ld_h, int relu, int64_t rows, int d, float* __restrict__ dz,
-                                                int64_t ld_dz, float* __restrict__ S, const float* __restrict__ p,
+                                                const float* __restrict__ Q, int64_t ld, const float* __restrict__ p,
                                                 const float* __restrict__ m, const float* __restrict__ zinv,
-                                                float* __restrict__ d4) {
-  const int lane = threadIdx.x & 63;
-  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (r >= rows) return;
-  float s = 0.f;
-  for (int c = lane; c < (int)ld_dz; c += 64) {
-    float g = 0.f;
-    if (c < d) {
-      const float hv = h[r * ld_h + c];
-      g = dh[r * ld_dh + c];
-      if (relu && !(hv > 0.f)) g = 0.f;
-      s = fmaf(g, hv, s);
+                                                const float* __restrict__ r, float* __restrict__ dp, float* __restrict__ d4, int lpr) {
+  const int rpb = 256 / lpr, ll = threadIdx.x % lpr;
+  for (int64_t v = (int64_t)blockIdx.x * rpb + threadIdx.x / lpr; v < rows; v += (int64_t)gridDim.x * rpb) {
+    float S = 0.f, dq = 0.f;
+    for (int c = ll * 4; c < (int)ld; c += lpr * 4) {
+      float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (c < d) {   // (rows are pitched to a multiple of 4: pads are read and dropped)
+        float4 hv = ld4(h + v * ld_h + c), qv = ld4(Q + v * ld + c);
+        g = ld4(dh + v * ld_dh + c);
+        if (c + 1 >= d) hv.y = qv.y = g.y = 0.f;
+        if (c + 2 >= d) hv.z = qv.z = g.z = 0.f;
+        if (c + 3 >= d) hv.w = qv.w = g.w = 0.f;
+        if (relu) {
+          if (!(hv.x > 0.f)) g.x = 0.f;
+          if (!(hv.y > 0.f)) g.y = 0.f;
+          if (!(hv.z > 0.f)) g.z = 0.f;
+          if (!(hv.w > 0.f)) g.w = 0.f;
+        }
+        S = dot4(g, hv, S);
+        dq = dot4(g, qv, dq);
+      }
+      st4(dz + v * ld + c, g);
     }
-    dz[r * ld_dz + c] = g;
-  }
-  s = wave_sum(s);
-  if (lane == 0) {
-    S[r] = s;
-    // what the source pass needs of a destination, in one 16-byte read per entry instead of four 4-byte ones
-    st4(d4 + r * 4, make_float4(p[r], m[r], zinv[r], s));
+    S = group_sum(S, lpr);
+    dq = group_sum(dq, lpr);
+    if (ll == 0) {
+      dp[v] = dq - S * r[v];
+      // what the source pass needs of a destination, in one 16-byte read per entry instead of four 4-byte ones
+      st4(d4 + v * 4, make_float4(p[v], m[v], zinv[v], S));
+    }
   }
 }
 
@@ -333,19 +354,49 @@ struct GatPass {
   int sc_col;
 };
 
-// per-row sums of rows cut into several items: a wave per row adds the item sums (lanes 64 apart, then lane order)
-__global__ void __launch_bounds__(256) k_gat_fix_scalar(const CutRow* __restrict__ cuts, int64_t n_cut, int64_t part0,
-                                                        const float* __restrict__ spart, float* __restrict__ row_sum) {
-  const int lane = threadIdx.x & 63;
-  const int64_t f = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (f >= n_cut) return;
-  const CutRow cut = cuts[f];
-  const int64_t p0 = cut.part0 - part0;
-  const int32_t ns = cut.nseg;
-  float s = 0.f;
-  for (int32_t k = lane; k < ns; k += 64) s += spart[p0 + k];
-  s = wave_sum(s);
-  if (lane == 0) row_sum[cut.row] = s;
+// Cut rows of k_gat_agg: the partial sums of z, Q and r added in item order, a block per row (each wave a contiguous quarter)
+__global__ void __launch_bounds__(256) k_gat_fix(GatAgg a, const CutRow* __restrict__ cuts, int mode) {
+  __shared__ float4 sh[4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const CutRow cut = cuts[blockIdx.x];
+  const int64_t p0 = cut.part0 - a.part0;
+  const int32_t ns = cut.nseg, per = (ns + 3) >> 2;
+  const int32_t k0 = wave * per, k1 = (k0 + per) < ns ? (k0 + per) : ns;
+  const int d4 = (a.d + 3) & ~3;
+  auto rows = [&](const float* part, int64_t ld, float* out, bool relu) {
+    for (int cb = 0; cb < d4; cb += 256) {
+      const int c4 = cb + lane * 4;
+      float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (c4 < d4) {
+        const float* p = part + p0 * ld + c4;
+#pragma unroll 4
+        for (int32_t k = k0; k < k1; ++k) {
+          const float4 v = ld4(p + (int64_t)k * ld);
+          s = make_float4(s.x + v.x, s.y + v.y, s.z + v.z, s.w + v.w);
+        }
+      }
+      sh[wave][lane] = s;
+      __syncthreads();
+      if (wave == 0 && c4 < d4) {
+        for (int q = 1; q < 4; ++q) {
+          const float4 v = sh[q][lane];
+          s = make_float4(s.x + v.x, s.y + v.y, s.z + v.z, s.w + v.w);
+        }
+        if (relu) s = make_float4(s.x > 0.f ? s.x : 0.f, s.y > 0.f ? s.y : 0.f, s.z > 0.f ? s.z : 0.f, s.w > 0.f ? s.w : 0.f);
+        st4(out + (cut.row - a.row0) * ld + c4, s);
+      }
+      __syncthreads();
+    }
+  };
+  if (mode != AGG_Q) rows(a.z_part, a.z_ld, a.z, a.relu != 0);
+  if (mode == AGG_Z) return;
+  rows(a.q_part, a.q_ld, a.Q, false);
+  if (wave == 0) {
+    float s = 0.f;
+    for (int32_t k = lane; k < ns; k += 64) s += a.r_part[p0 + k];
+    s = wave_sum(s);
+    if (lane == 0) a.r[cut.row] = s;
+  }
 }
 
 // Source pass: for local source i (vertex u) over its entries (u -> v) of the chunk, w_e recomputed:
@@ -526,12 +577,22 @@ __global__ void __launch_bounds__(256) k_gat_src_g(GatPass a) {
 // dt_v += dp_v a_dst + dq_v a_src; the pair (dp_v, dq_v) also goes to a [V x 4] matrix for da = T^T [dp dq]
 __global__ void __launch_bounds__(256) k_gat_finish(float* __restrict__ dT, int64_t ld, int d, int sc_col,
                                                     const float* __restrict__ dp, const float* __restrict__ a_dst,
-                                                    const float* __restrict__ a_src, int64_t V, float* __restrict__ pq4) {
-  const int lane = threadIdx.x & 63;
-  for (int64_t v = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); v < V; v += (int64_t)gridDim.x * 4) {
+                                                    const float* __restrict__ a_src, int64_t V, float* __restrict__ pq4, int lpr) {
+  __shared__ AttVec sa;
+  load_att(sa, a_dst, a_src, d);
+  const int rpb = 256 / lpr, ll = threadIdx.x % lpr;
+  for (int64_t v = (int64_t)blockIdx.x * rpb + threadIdx.x / lpr; v < V; v += (int64_t)gridDim.x * rpb) {
     const float dpv = dp[v], dqv = dT[v * ld + sc_col];
-    for (int c = lane; c < d; c += 64) dT[v * ld + c] += dpv * a_dst[c] + dqv * a_src[c];
-    if (lane == 0) st4(pq4 + v * 4, make_float4(dpv, dqv, 0.f, 0.f));
+    for (int c = ll * 4; c < d; c += lpr * 4) {
+      float4 t = ld4(dT + v * ld + c);
+      const float4 ad = sa.dst[c >> 2], as = sa.src[c >> 2];
+      t.x += dpv * ad.x + dqv * as.x;
+      t.y += dpv * ad.y + dqv * as.y;
+      t.z += dpv * ad.z + dqv * as.z;
+      t.w += dpv * ad.w + dqv * as.w;
+      st4(dT + v * ld + c, t);
+    }
+    if (ll == 0) st4(pq4 + v * 4, make_float4(dpv, dqv, 0.f, 0.f));
   }
 }
 
@@ -550,7 +611,7 @@ struct GatKeep {
 };
 
 struct GatWs {
-  float *T, *p, *q, *m, *zinv, *S, *dp, *r, *pq4, *d4;
+  float *T, *p, *q, *m, *zinv, *dp, *r, *pq4, *d4;
   int64_t ld_t;
 };
 
@@ -695,8 +756,8 @@ int bind_ws(ht_ctx* ctx, const ht_graph* g, int d_out, const GatKeep* keep, GatW
   else HT_TRY(ht_scratch(ctx, HT_S_TFULL, (size_t)V * ws->ld_t * 4, (void**)&ws->T));
   float* vec = nullptr;
   HT_TRY(ht_scratch(ctx, HT_S_GATV, (size_t)V * 16 * 4, (void**)&vec));
-  ws->p = vec; ws->q = vec + V; ws->m = vec + 2 * V; ws->zinv = vec + 3 * V; ws->S = vec + 4 * V; ws->dp = vec + 5 * V;
-  ws->r = vec + 6 * V;
+  ws->p = vec; ws->q = vec + V; ws->m = vec + 2 * V; ws->zinv = vec + 3 * V; ws->dp = vec + 4 * V;
+  ws->r = vec + 5 * V;
   ws->pq4 = vec + 8 * V;      // 16-byte aligned whatever V is
   ws->d4 = vec + 12 * V;
   if (keep) { ws->p = keep->p; ws->q = keep->q; ws->m = keep->m; ws->zinv = keep->zinv; ws->r = keep->r; }
@@ -742,7 +803,8 @@ int prepare(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const ht_te
     st->gemm_flops += 2.0 * nr * desc->d_in * desc->d_out;
   }
   if (g->V > 0) {
-    k_gat_pq<<<(unsigned)std::min<int64_t>((g->V + 3) / 4, 1 << 22), 256, 0, s>>>(ws->T, ws->ld_t, desc->d_out, a_dst, a_src, g->V, ws->p, ws->q);
+    const int lpr = row_lanes(ws->ld_t);
+    k_gat_pq<<<row_grid(g->V, lpr), 256, 0, s>>>(ws->T, ws->ld_t, desc->d_out, a_dst, a_src, g->V, ws->p, ws->q, lpr);
     HT_LAUNCH_CHECK(ctx);
   }
   return HT_OK;
@@ -802,18 +864,8 @@ int agg_range(ht_ctx* ctx, const ht_graph* g, const GatRange& rg, const ht_gat_d
   if (t_items) tm->end();
   if (it.n_cut == 0) return HT_OK;
   if (t_fix) tm->begin(t_fix);
-  SpmmArgs f{};
-  f.cuts = g->fwd_items.cuts.p + it.cut0; f.n_fix = it.n_cut; f.part0 = it.part0; f.row0 = rg.row0; f.d = desc->d_out;
-  if (mode != AGG_Q) {
-    f.out = z; f.out_ld = z_ld; f.partial = rw.z_part; f.relu = a.relu;
-    HT_TRY(ht_spmm_fix_launch(ctx, st, f));
-  }
-  if (mode != AGG_Z) {
-    f.out = Q; f.out_ld = ws.ld_t; f.partial = rw.q_part; f.relu = 0;
-    HT_TRY(ht_spmm_fix_launch(ctx, st, f));
-    k_gat_fix_scalar<<<(unsigned)((it.n_cut + 3) / 4), 256, 0, st>>>(f.cuts, it.n_cut, it.part0, a.r_part, ws.r);
-    HT_LAUNCH_CHECK(ctx);
-  }
+  k_gat_fix<<<(unsigned)it.n_cut, 256, 0, st>>>(a, g->fwd_items.cuts.p + it.cut0, mode);
+  HT_LAUNCH_CHECK(ctx);
   if (t_fix) tm->end();
   return HT_OK;
 }
@@ -949,11 +1001,9 @@ int gat_bwd_rows_direct(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc,
     HT_TRY(agg_range(ctx, g, r, desc, ws, rw, AGG_Q, nullptr, 0, Q + r.row0 * ws.ld_t, &local->t_gat_dst_ms, &local->t_gat_dst_ms, tm));
   }
   tm->begin(&local->t_gat_dst_ms);
-  const unsigned nb = (unsigned)((V + 3) / 4);
-  k_gat_dz<<<nb, 256, 0, st>>>(dH_out->ptr, dH_out->ld, H_out->ptr, H_out->ld, desc->act == HT_ACT_RELU, V, d, dz, ws.ld_t, ws.S, ws.p,
-                               ws.m, ws.zinv, ws.d4);
-  HT_LAUNCH_CHECK(ctx);
-  k_gat_dp<<<nb, 256, 0, st>>>(dz, Q, ws.ld_t, d, ws.S, ws.r, V, ws.dp);
+  const int lpr = row_lanes(ws.ld_t);
+  k_gat_dz<<<row_grid(V, lpr), 256, 0, st>>>(dH_out->ptr, dH_out->ld, H_out->ptr, H_out->ld, desc->act == HT_ACT_RELU, V, d, dz, Q, ws.ld_t,
+                                             ws.p, ws.m, ws.zinv, ws.r, ws.dp, ws.d4, lpr);
   HT_LAUNCH_CHECK(ctx);
   tm->end();
   GatPass a{};
@@ -992,6 +1042,7 @@ int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
   HT_TRY(bind_ws(ctx, g, desc->d_out, keep, &ws));
   const int d = desc->d_out;
   const int nvec = (d + 3) / 4;
+  const int lpr = row_lanes(ws.ld_t);
   const int sc_col = (int)ws.ld_t;              // the scalar column block sits behind the padded data columns
   const int64_t ld_dt = ws.ld_t + 4;
   const int64_t mx = std::max<int64_t>(g->max_ndst, 1);
@@ -1048,21 +1099,19 @@ int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
     HT_TRY(stage_chunk(i + 1));
     const GatRange range = range_of(g, c);
     HT_TRY(softmax_range(ctx, g, range, desc, ws, rw, local, tm));
-    if (hout_host || dho_host) HT_TRY(lk.wait(st, ev_in[b]));
-    k_gat_dz<<<(unsigned)((ndst + 3) / 4), 256, 0, st>>>(dho_host ? gbuf[b] : dH_out->ptr + c.dst0 * dH_out->ld, dH_out->ld,
-                                                          hout_host ? hbuf[b] : H_out->ptr + c.dst0 * H_out->ld, H_out->ld,
-                                                          desc->act == HT_ACT_RELU, ndst, d, dz, ws.ld_t, ws.S, ws.p + c.dst0,
-                                                          ws.m + c.dst0, ws.zinv + c.dst0, ws.d4);
-    HT_LAUNCH_CHECK(ctx);
-    if (hout_host || dho_host) HT_TRY(lk.rec(st, &ev_free[b]));   // the staged rows have been consumed
-    GatPass a{};
-    a.d = d; a.q = ws.q; a.d4 = ws.d4; a.slope = desc->slope;
-    // destination pass: Q_v = sum_e w_e f_e t_u, then dp_v = dz_v . Q_v - S_v r_v
+    // destination pass: Q_v = sum_e w_e f_e t_u, then dz, S and dp
     tm->begin(&local->t_gat_dst_ms);
     HT_TRY(agg_range(ctx, g, range, desc, ws, rw, AGG_Q, nullptr, 0, Q, nullptr, nullptr, tm));
-    k_gat_dp<<<(unsigned)((ndst + 3) / 4), 256, 0, st>>>(dz, Q, ws.ld_t, d, ws.S, ws.r + c.dst0, ndst, ws.dp + c.dst0);
+    if (hout_host || dho_host) HT_TRY(lk.wait(st, ev_in[b]));
+    k_gat_dz<<<row_grid(ndst, lpr), 256, 0, st>>>(dho_host ? gbuf[b] : dH_out->ptr + c.dst0 * dH_out->ld, dH_out->ld,
+                                                  hout_host ? hbuf[b] : H_out->ptr + c.dst0 * H_out->ld, H_out->ld,
+                                                  desc->act == HT_ACT_RELU, ndst, d, dz, Q, ws.ld_t, ws.p + c.dst0, ws.m + c.dst0,
+                                                  ws.zinv + c.dst0, ws.r + c.dst0, ws.dp + c.dst0, ws.d4, lpr);
     HT_LAUNCH_CHECK(ctx);
+    if (hout_host || dho_host) HT_TRY(lk.rec(st, &ev_free[b]));   // the staged rows have been consumed
     tm->end();
+    GatPass a{};
+    a.d = d; a.q = ws.q; a.d4 = ws.d4; a.slope = desc->slope;
     // source pass
     float* partial = nullptr;
     if (c.bwd.n_part > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)g->max_bpart * ld_dt * 4, (void**)&partial));
@@ -1087,7 +1136,7 @@ int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
     tm->end();
   }
   if (g->V > 0) {
-    k_gat_finish<<<(unsigned)std::min<int64_t>((g->V + 3) / 4, 1 << 22), 256, 0, st>>>(dT, ld_dt, d, sc_col, ws.dp, a_dst, a_src, g->V, ws.pq4);
+    k_gat_finish<<<row_grid(g->V, lpr), 256, 0, st>>>(dT, ld_dt, d, sc_col, ws.dp, a_dst, a_src, g->V, ws.pq4, lpr);
     HT_LAUNCH_CHECK(ctx);
   }
   // da = T^T [dp dq 0 0]; dW = H^T dt; dH += dt W^T, in row blocks; host-resident H_in / dH_in blocks go
@@ -1322,12 +1371,14 @@ int ht_gat_epoch(ht_ctx* ctx, const ht_graph* g, const ht_gat_model* model, cons
     rc = passes();
   }
   if (rc != HT_OK) return fail(rc);
+  std::vector<ht_sgd_item> params;
   for (int l = 0; l < L; ++l) {
-    int rc = ht_sgd(ctx, st, model->W[l], dW[l], (int64_t)model->dims[l] * model->dims[l + 1], model->lr);
-    if (rc == HT_OK) rc = ht_sgd(ctx, st, model->a_dst[l], dad[l], model->dims[l + 1], model->lr);
-    if (rc == HT_OK) rc = ht_sgd(ctx, st, model->a_src[l], das[l], model->dims[l + 1], model->lr);
-    if (rc != HT_OK) return fail(rc);
+    params.push_back({model->W[l], dW[l], (int64_t)model->dims[l] * model->dims[l + 1]});
+    params.push_back({model->a_dst[l], dad[l], model->dims[l + 1]});
+    params.push_back({model->a_src[l], das[l], model->dims[l + 1]});
   }
+  rc = ht_sgd(ctx, st, params, model->lr);
+  if (rc != HT_OK) return fail(rc);
   {
     hipError_t e = hipMemcpyAsync(loss_out, loss_dev, 4, hipMemcpyDeviceToHost, st);
     if (e != hipSuccess) return fail(ht_set_err(ctx, HT_EHIP, "loss copy: %s", hipGetErrorString(e)));

@@ -389,7 +389,14 @@ int ht_relu_mask(ht_ctx* ctx, hipStream_t st, const float* dh, int64_t ld_dh, co
                  float* dz, int64_t ld_dz, int64_t rows, int32_t cols);
 int ht_softmax_ce(ht_ctx* ctx, hipStream_t st, const float* logits, int64_t ld, const int32_t* labels, int64_t V,
                   int32_t C, float* grad, int64_t ld_g, float* loss_dev /*1 float*/);
-int ht_sgd(ht_ctx* ctx, hipStream_t st, float* W, const float* dW, int64_t n, float lr);
+// W -= lr dW for every item
+struct ht_sgd_item {
+  float* W;
+  const float* dW;
+  int64_t n;
+};
+constexpr int HT_SGD_MAX = 3 * HT_MAX_LAYERS;   // items per launch
+int ht_sgd(ht_ctx* ctx, hipStream_t st, const std::vector<ht_sgd_item>& items, float lr);
 int ht_fill_zero(ht_ctx* ctx, hipStream_t st, void* p, size_t bytes);
 
 // stats helpers: HIP-event pairs around phases, each on the stream that runs the phase

@@ -1611,10 +1611,9 @@ int ht_epoch(ht_ctx* ctx, const ht_graph* g, const ht_model* model, const ht_ten
     }
     // ---- parameter update (Alg. 1)
     R.tm.begin(&R.st->t_update_ms);
-    for (int l = 0; l < L; ++l) {
-      int rc = ht_sgd(ctx, ctx->stream, model->W[l], ws->dW[l], (int64_t)model->dims[l] * model->dims[l + 1], model->lr);
-      if (rc != HT_OK) return rc;
-    }
+    std::vector<ht_sgd_item> params;
+    for (int l = 0; l < L; ++l) params.push_back({model->W[l], ws->dW[l], (int64_t)model->dims[l] * model->dims[l + 1]});
+    HT_TRY(ht_sgd(ctx, ctx->stream, params, model->lr));
     R.tm.end();
     return HT_OK;
   };
