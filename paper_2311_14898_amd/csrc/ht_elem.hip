@@ -25,78 +25,95 @@ __global__ void k_relu_mask(const float* __restrict__ dh, int64_t ld_dh, const f
   *reinterpret_cast<float4*>(dz + r * ld_dz + c) = o;
 }
 
-__global__ void k_count_labelled(const int32_t* __restrict__ labels, int64_t V, unsigned long long* __restrict__ T) {
-  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  unsigned long long c = (v < V && labels[v] >= 0) ? 1ull : 0ull;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) c += __shfl_down(c, o, 64);
-  if ((threadIdx.x & 63) == 0 && c) atomicAdd(T, c);
-}
+// The loss in three launches whatever V is: labelled vertices per block; gradient rows and per-block loss sums; their total.
+// (With an atomic per wave for the count, a wave per vertex and the vertices' losses through memory it was six, 1.5 ms at 2.45 M
+// vertices and 47 classes, where the rows' bytes take 0.2; now 0.4 ms.)
+constexpr int COUNT_BLOCKS = 256;
+constexpr int64_t LOSS_BLOCKS = 4096;
 
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o, 64));
-  return x;
-}
-__device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  return x;
-}
-
-// One wave per vertex, classes across lanes.  loss_v[v] = lse - x[y] (0 if unlabelled).
-__global__ void __launch_bounds__(256) k_softmax_ce(const float* __restrict__ logits, int64_t ld,
-                                                    const int32_t* __restrict__ labels, int64_t V, int C,
-                                                    const unsigned long long* __restrict__ Tp,
-                                                    float* __restrict__ grad, int64_t ld_g,
-                                                    float* __restrict__ loss_v) {
-  const int lane = threadIdx.x & 63;
-  // (a bounded grid that strides: a launch holds fewer than 2^32 threads, 64 V can be more)
-  for (int64_t v = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); v < V; v += (int64_t)gridDim.x * 4) {
-    const int32_t y = labels[v];
-    const float* x = logits + v * ld;
-    float* g = grad + v * ld_g;
-    if (y < 0) {
-      for (int c = lane; c < C; c += 64) g[c] = 0.f;
-      if (lane == 0) loss_v[v] = 0.f;
-      continue;
-    }
-    const float invT = 1.f / (float)(*Tp);
-    float m = -INFINITY;
-    for (int c = lane; c < C; c += 64) m = fmaxf(m, x[c]);
-    m = wave_max(m);
-    float z = 0.f;
-    for (int c = lane; c < C; c += 64) z += expf(x[c] - m);
-    z = wave_sum(z);
-    const float lse = m + logf(z);
-    for (int c = lane; c < C; c += 64) g[c] = (expf(x[c] - lse) - (c == y ? 1.f : 0.f)) * invT;
-    if (lane == 0) loss_v[v] = lse - x[y];
-  }
-}
-
-// Fixed-order sum of n floats in fp64: 256-thread blocks of 4096 elements, then one block.
-__global__ void __launch_bounds__(256) k_sum_stage(const float* __restrict__ in_f, const double* __restrict__ in_d,
-                                                   int64_t n, double* __restrict__ out) {
-  __shared__ double sh[256];
-  const int64_t base = (int64_t)blockIdx.x * 4096;
-  double s = 0.0;
-  for (int i = 0; i < 16; ++i) {
-    const int64_t idx = base + (int64_t)i * 256 + threadIdx.x;
-    if (idx < n) s += in_f ? (double)in_f[idx] : in_d[idx];
-  }
-  sh[threadIdx.x] = s;
+template <typename T>
+__device__ __forceinline__ T block_sum(T x, T* sh) {   // 256 threads, in a fixed order; all get the result
+  sh[threadIdx.x] = x;
   __syncthreads();
   for (int o = 128; o > 0; o >>= 1) {
     if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[blockIdx.x] = sh[0];
+  return sh[0];
 }
 
-__global__ void k_finish_loss(const double* __restrict__ sum, const unsigned long long* __restrict__ Tp,
-                              float* __restrict__ loss) {
-  const unsigned long long T = *Tp;
-  *loss = T > 0 ? (float)(*sum / (double)T) : 0.f;
+__global__ void __launch_bounds__(256) k_count_labelled(const int32_t* __restrict__ labels, int64_t V, unsigned long long* __restrict__ cnt) {
+  __shared__ unsigned long long sh[256];
+  unsigned long long c = 0;
+  for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < V; v += (int64_t)gridDim.x * 256) c += labels[v] >= 0;
+  c = block_sum(c, sh);
+  if (threadIdx.x == 0) cnt[blockIdx.x] = c;
+}
+
+__device__ __forceinline__ float4 logits4(const float* x, int c, int C) {   // columns past the end (pads) count as -inf
+  float4 v = *reinterpret_cast<const float4*>(x + c);
+  if (c + 1 >= C) v.y = -INFINITY;
+  if (c + 2 >= C) v.z = -INFINITY;
+  if (c + 3 >= C) v.w = -INFINITY;
+  return v;
+}
+
+// lpr lanes per vertex, four classes per lane and step.  loss[block] = sum of lse - x[y] over the block's labelled vertices.
+__global__ void __launch_bounds__(256) k_softmax_ce(const float* __restrict__ logits, int64_t ld,
+                                                    const int32_t* __restrict__ labels, int64_t V, int C,
+                                                    const unsigned long long* __restrict__ cnt, int n_cnt,
+                                                    float* __restrict__ grad, int64_t ld_g, double* __restrict__ loss, int lpr) {
+  __shared__ double sh[256];
+  __shared__ unsigned long long shc[256];
+  const unsigned long long T = block_sum((int)threadIdx.x < n_cnt ? cnt[threadIdx.x] : 0ull, shc);
+  const float invT = 1.f / (float)T;
+  const int rpb = 256 / lpr, ll = threadIdx.x % lpr;
+  double mine = 0.0;
+  for (int64_t v = (int64_t)blockIdx.x * rpb + threadIdx.x / lpr; v < V; v += (int64_t)gridDim.x * rpb) {
+    const int32_t y = labels[v];
+    const float* x = logits + v * ld;
+    float* g = grad + v * ld_g;
+    if (y < 0) {
+      for (int c = ll * 4; c < C; c += lpr * 4) *reinterpret_cast<float4*>(g + c) = make_float4(0.f, 0.f, 0.f, 0.f);
+      continue;
+    }
+    float m = -INFINITY;
+    for (int c = ll * 4; c < C; c += lpr * 4) {
+      const float4 t = logits4(x, c, C);
+      m = fmaxf(m, fmaxf(fmaxf(t.x, t.y), fmaxf(t.z, t.w)));
+    }
+    for (int o = lpr >> 1; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    float z = 0.f;
+    for (int c = ll * 4; c < C; c += lpr * 4) {
+      const float4 t = logits4(x, c, C);
+      z += (expf(t.x - m) + expf(t.y - m)) + (expf(t.z - m) + expf(t.w - m));
+    }
+    for (int o = lpr >> 1; o > 0; o >>= 1) z += __shfl_xor(z, o, 64);
+    const float lse = m + logf(z);
+    for (int c = ll * 4; c < C; c += lpr * 4) {
+      const float4 t = logits4(x, c, C);
+      float4 o;
+      o.x = (expf(t.x - lse) - (c == y ? 1.f : 0.f)) * invT;
+      o.y = (expf(t.y - lse) - (c + 1 == y ? 1.f : 0.f)) * invT;
+      o.z = (expf(t.z - lse) - (c + 2 == y ? 1.f : 0.f)) * invT;
+      o.w = (expf(t.w - lse) - (c + 3 == y ? 1.f : 0.f)) * invT;
+      *reinterpret_cast<float4*>(g + c) = o;
+    }
+    if (ll == 0) mine += (double)(lse - x[y]);
+  }
+  const double s = block_sum(mine, sh);
+  if (threadIdx.x == 0) loss[blockIdx.x] = s;
+}
+
+__global__ void __launch_bounds__(256) k_finish_loss(const double* __restrict__ part, int n, const unsigned long long* __restrict__ cnt,
+                                                     int n_cnt, float* __restrict__ loss) {
+  __shared__ double sh[256];
+  __shared__ unsigned long long shc[256];
+  double s = 0.0;
+  for (int i = threadIdx.x; i < n; i += 256) s += part[i];
+  s = block_sum(s, sh);
+  const unsigned long long T = block_sum((int)threadIdx.x < n_cnt ? cnt[threadIdx.x] : 0ull, shc);
+  if (threadIdx.x == 0) *loss = T > 0 ? (float)(s / (double)T) : 0.f;
 }
 
 // One launch for all parameters of a model (a launch each costs its 4 us whatever the size): tensor t has the blocks from
@@ -138,40 +155,23 @@ int ht_relu_mask(ht_ctx* ctx, hipStream_t st, const float* dh, int64_t ld_dh, co
   return HT_OK;
 }
 
-// scratch slot 2: per-vertex losses, stage sums, labelled count
 int ht_softmax_ce(ht_ctx* ctx, hipStream_t st, const float* logits, int64_t ld, const int32_t* labels, int64_t V,
                   int32_t C, float* grad, int64_t ld_g, float* loss_dev) {
   if (V <= 0 || C <= 0) return ht_set_err(ctx, HT_EINVAL, "loss: empty input");
-  const int64_t nb1 = (V + 4095) / 4096;
-  const int64_t nb2 = (nb1 + 4095) / 4096;
-  const size_t bytes = 16 + (size_t)V * 4 + 16 + (size_t)(nb1 + nb2 + 2) * 8;
+  if ((ld & 3) || (ld_g & 3)) return ht_set_err(ctx, HT_ESHAPE, "loss: row pitch must be a multiple of 4");
+  int lpr = 4;
+  while (lpr < 64 && lpr * 4 < C) lpr *= 2;
+  const unsigned nc = (unsigned)std::min<int64_t>((V + 255) / 256, COUNT_BLOCKS);
+  const unsigned nb = (unsigned)std::min<int64_t>((V * lpr + 255) / 256, LOSS_BLOCKS);
   char* p = nullptr;
-  HT_TRY(ht_scratch(ctx, HT_S_LOSS, bytes, (void**)&p));
-  unsigned long long* T = (unsigned long long*)p;
-  double* st1 = (double*)(p + 16);
-  double* st2 = st1 + nb1;
-  double* st3 = st2 + nb2;
-  float* loss_v = (float*)(st3 + 2);
-  HT_TRY(ht_fill_zero(ctx, st, T, 16));
-  k_count_labelled<<<(unsigned)((V + 255) / 256), 256, 0, st>>>(labels, V, T);
+  HT_TRY(ht_scratch(ctx, HT_S_LOSS, (size_t)(COUNT_BLOCKS + LOSS_BLOCKS) * 8, (void**)&p));
+  unsigned long long* cnt = (unsigned long long*)p;
+  double* part = (double*)p + COUNT_BLOCKS;
+  k_count_labelled<<<nc, 256, 0, st>>>(labels, V, cnt);
   HT_LAUNCH_CHECK(ctx);
-  k_softmax_ce<<<(unsigned)std::min<int64_t>((V + 3) / 4, 1 << 22), 256, 0, st>>>(logits, ld, labels, V, C, T, grad, ld_g, loss_v);
+  k_softmax_ce<<<nb, 256, 0, st>>>(logits, ld, labels, V, C, cnt, (int)nc, grad, ld_g, part, lpr);
   HT_LAUNCH_CHECK(ctx);
-  k_sum_stage<<<(unsigned)nb1, 256, 0, st>>>(loss_v, nullptr, V, st1);
-  HT_LAUNCH_CHECK(ctx);
-  const double* fin = st1;
-  if (nb1 > 1) {
-    k_sum_stage<<<(unsigned)nb2, 256, 0, st>>>(nullptr, st1, nb1, st2);
-    HT_LAUNCH_CHECK(ctx);
-    fin = st2;
-    if (nb2 > 1) {
-      if (nb2 > 4096) return ht_set_err(ctx, HT_ESHAPE, "loss: too many vertices for the 3-stage sum");
-      k_sum_stage<<<1, 256, 0, st>>>(nullptr, st2, nb2, st3);
-      HT_LAUNCH_CHECK(ctx);
-      fin = st3;
-    }
-  }
-  k_finish_loss<<<1, 1, 0, st>>>(fin, T, loss_dev);
+  k_finish_loss<<<1, 256, 0, st>>>(part, (int)nb, cnt, (int)nc, loss_dev);
   HT_LAUNCH_CHECK(ctx);
   return HT_OK;
 }
