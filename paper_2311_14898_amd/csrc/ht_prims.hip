@@ -161,13 +161,21 @@ int scan_impl(ht_ctx* ctx, const Tin* in, int64_t* out, int64_t n, bool want_tot
 // ------------------------------------------------------------------ radix sort
 constexpr int RS_THREADS = 256;
 constexpr int RS_WAVES = RS_THREADS / 64;
-constexpr int RS_ROUNDS = 16;
-constexpr int RS_TILE = RS_THREADS * RS_ROUNDS;  // keys per block
 constexpr int RS_BINS = 256;
+constexpr int rs_tile(int rounds) { return RS_THREADS * rounds; }   // keys per block
+// A pass counts digits per block, turns the counts into places, and scatters.  Long inputs take 16 keys per thread and a scan
+// launch between the two kernels.  Short ones (up to RS_SHORT_BLOCKS blocks) take 8 keys per thread, for more blocks with shorter
+// chains, and every block of the scatter adds up the counts by itself, a digit per thread: that is at most 128 rows of 1 KB out
+// of the L2, where the scan is a launch of one block (110,000 keys: 23 -> 12 us per pass).
+constexpr int RS_LONG = 16, RS_SHORT = 8;
+constexpr int64_t RS_SHORT_BLOCKS = 128;
 
+// table: [digit][block] for the scan, [block][digit] for short inputs
+template <int ROUNDS>
 __global__ void __launch_bounds__(RS_THREADS) k_rs_hist(const uint64_t* __restrict__ keys, int64_t n, int shift,
                                                        uint32_t mask, int32_t* __restrict__ table,
                                                        int64_t nblocks) {
+  constexpr int RS_TILE = rs_tile(ROUNDS);
   __shared__ uint32_t h[RS_BINS];
   h[threadIdx.x] = 0;
   __syncthreads();
@@ -178,7 +186,8 @@ __global__ void __launch_bounds__(RS_THREADS) k_rs_hist(const uint64_t* __restri
     if (idx < n) atomicAdd(&h[(uint32_t)(keys[idx] >> shift) & mask], 1u);
   }
   __syncthreads();
-  table[(int64_t)threadIdx.x * nblocks + blockIdx.x] = (int32_t)h[threadIdx.x];
+  if (ROUNDS == RS_SHORT) table[(int64_t)blockIdx.x * RS_BINS + threadIdx.x] = (int32_t)h[threadIdx.x];
+  else table[(int64_t)threadIdx.x * nblocks + blockIdx.x] = (int32_t)h[threadIdx.x];
 }
 
 // Stable scatter.  Key order inside a block is (wave, round, lane) = index
@@ -187,10 +196,12 @@ __global__ void __launch_bounds__(RS_THREADS) k_rs_hist(const uint64_t* __restri
 // The block first puts its keys into digit order in LDS and then writes them out in that order, so that
 // consecutive lanes store consecutive keys of one digit's run (a lane storing its own key straight to its
 // final place touches a 128-byte line of the output from up to 16 different store instructions).
+template <int RS_ROUNDS>
 __global__ void __launch_bounds__(RS_THREADS) k_rs_scatter(const uint64_t* __restrict__ in,
                                                           uint64_t* __restrict__ out, int64_t n, int shift,
                                                           uint32_t mask, const int64_t* __restrict__ offs,
-                                                          int64_t nblocks) {
+                                                          const int32_t* __restrict__ table, int64_t nblocks) {
+  constexpr int RS_TILE = rs_tile(RS_ROUNDS);
   __shared__ uint32_t cnt[RS_WAVES][RS_BINS];
   __shared__ int64_t goff[RS_BINS];     // where the block's run of a digit starts in the output, minus lstart
   __shared__ uint32_t lstart[RS_BINS];  // where it starts in the block's tile
@@ -249,7 +260,31 @@ __global__ void __launch_bounds__(RS_THREADS) k_rs_scatter(const uint64_t* __res
       if (w < wave) off += wtot[w];
     const uint32_t ls = off + inc - run;
     lstart[dgt] = ls;
-    goff[dgt] = offs[(int64_t)dgt * nblocks + blockIdx.x] - (int64_t)ls;
+    if (RS_ROUNDS != RS_SHORT) {
+      goff[dgt] = offs[(int64_t)dgt * nblocks + blockIdx.x] - (int64_t)ls;
+    } else {   // keys of smaller digits, and of this digit in the blocks before
+      uint32_t earlier = 0, total = 0;
+#pragma unroll 16
+      for (int b = 0; b < (int)nblocks; ++b) {
+        const uint32_t c = (uint32_t)table[b * RS_BINS + dgt];
+        total += c;
+        earlier += b < (int)blockIdx.x ? c : 0u;
+      }
+      uint32_t upto = total;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(upto, o, 64);
+        if (lane >= o) upto += y;
+      }
+      __syncthreads();   // (wtot is read above)
+      if (lane == 63) wtot[wave] = upto;
+      __syncthreads();
+      uint32_t lower = upto - total;
+#pragma unroll
+      for (int w = 0; w < RS_WAVES; ++w)
+        if (w < wave) lower += wtot[w];
+      goff[dgt] = (int64_t)(lower + earlier) - (int64_t)ls;
+    }
   }
   __syncthreads();
 #pragma unroll
@@ -290,7 +325,8 @@ int ht_radix_sort_u64(ht_ctx* ctx, uint64_t* keys, uint64_t* tmp, int64_t n, int
                       uint64_t** sorted) {
   *sorted = keys;
   if (n <= 1 || bit_hi <= bit_lo) return HT_OK;
-  const int64_t nblocks = ceil_div64(n, RS_TILE);
+  const bool brief = n <= RS_SHORT_BLOCKS * rs_tile(RS_SHORT);
+  const int64_t nblocks = ceil_div64(n, rs_tile(brief ? RS_SHORT : RS_LONG));
   // per-block digit counts and their offsets, in a scratch slot of the context (no allocation per call)
   const size_t cells = (size_t)(RS_BINS * nblocks);
   char* rs = nullptr;
@@ -302,10 +338,16 @@ int ht_radix_sort_u64(ht_ctx* ctx, uint64_t* keys, uint64_t* tmp, int64_t n, int
   for (int shift = bit_lo; shift < bit_hi; shift += 8) {
     const int bits = (bit_hi - shift) < 8 ? (bit_hi - shift) : 8;
     const uint32_t mask = (1u << bits) - 1u;
-    k_rs_hist<<<(unsigned)nblocks, RS_THREADS, 0, ctx->stream>>>(a, n, shift, mask, table.p, nblocks);
-    HT_LAUNCH_CHECK(ctx);
-    HT_TRY(ht_scan_i32(ctx, table.p, offs.p, RS_BINS * nblocks, false));
-    k_rs_scatter<<<(unsigned)nblocks, RS_THREADS, 0, ctx->stream>>>(a, b, n, shift, mask, offs.p, nblocks);
+    if (brief) {
+      k_rs_hist<RS_SHORT><<<(unsigned)nblocks, RS_THREADS, 0, ctx->stream>>>(a, n, shift, mask, table.p, nblocks);
+      HT_LAUNCH_CHECK(ctx);
+      k_rs_scatter<RS_SHORT><<<(unsigned)nblocks, RS_THREADS, 0, ctx->stream>>>(a, b, n, shift, mask, nullptr, table.p, nblocks);
+    } else {
+      k_rs_hist<RS_LONG><<<(unsigned)nblocks, RS_THREADS, 0, ctx->stream>>>(a, n, shift, mask, table.p, nblocks);
+      HT_LAUNCH_CHECK(ctx);
+      HT_TRY(ht_scan_i32(ctx, table.p, offs.p, RS_BINS * nblocks, false));
+      k_rs_scatter<RS_LONG><<<(unsigned)nblocks, RS_THREADS, 0, ctx->stream>>>(a, b, n, shift, mask, offs.p, nullptr, nblocks);
+    }
     HT_LAUNCH_CHECK(ctx);
     uint64_t* t = a;
     a = b;
