@@ -817,24 +817,30 @@ int softmax_range(ht_ctx* ctx, const ht_graph* g, const GatRange& r, const ht_ga
   if (it.n_items == 0) return HT_OK;
   float* part_s = rw.part ? rw.part + rw.n_part : nullptr;
   tm->begin(&st->t_gat_softmax_ms);
-  k_gat_scores<<<(unsigned)((it.n_items + 3) / 4), 256, 0, ctx->stream>>>(
-      g->fwd_items.items.p + it.it0, it.n_items, r.ent0, it.part0, g->merged ? g->ucol.p : g->col.p, g->merged ? g->umult.p : nullptr,
-      ws.p, ws.q, desc->slope, rw.x, ws.m, ws.zinv, rw.part, part_s);
-  HT_LAUNCH_CHECK(ctx);
-  if (it.n_cut > 0) {
-    k_gat_rowstats<<<(unsigned)((it.n_cut + 3) / 4), 256, 0, ctx->stream>>>(g->fwd_items.cuts.p + it.cut0, it.n_cut, it.part0, rw.part,
-                                                                            part_s, ws.m, ws.zinv);
+  HT_TRY(ht_in_launches(it.n_items, HT_LAUNCH_WAVES, [&](int64_t i, int64_t n) {
+    k_gat_scores<<<(unsigned)((n + 3) / 4), 256, 0, ctx->stream>>>(
+        g->fwd_items.items.p + it.it0 + i, n, r.ent0, it.part0, g->merged ? g->ucol.p : g->col.p, g->merged ? g->umult.p : nullptr,
+        ws.p, ws.q, desc->slope, rw.x, ws.m, ws.zinv, rw.part, part_s);
     HT_LAUNCH_CHECK(ctx);
-  }
+    return (int)HT_OK;
+  }));
+  HT_TRY(ht_in_launches(it.n_cut, HT_LAUNCH_WAVES, [&](int64_t i, int64_t n) {
+    k_gat_rowstats<<<(unsigned)((n + 3) / 4), 256, 0, ctx->stream>>>(g->fwd_items.cuts.p + it.cut0 + i, n, it.part0, rw.part, part_s,
+                                                                     ws.m, ws.zinv);
+    HT_LAUNCH_CHECK(ctx);
+    return (int)HT_OK;
+  }));
   tm->end();
   return HT_OK;
 }
 
 template <bool UNI>
-void launch_agg(unsigned blocks, hipStream_t st, int mode, const GatAgg& a, const SlabShape& sh, int slab0) {
-  if (mode == AGG_Z) k_gat_agg<UNI, AGG_Z><<<blocks, 256, 0, st>>>(a, sh.S, sh.nvs, sh.eps, sh.grp_per_part, slab0);
-  else if (mode == AGG_ZQ) k_gat_agg<UNI, AGG_ZQ><<<blocks, 256, 0, st>>>(a, sh.S, sh.nvs, sh.eps, sh.grp_per_part, slab0);
-  else k_gat_agg<UNI, AGG_Q><<<blocks, 256, 0, st>>>(a, sh.S, sh.nvs, sh.eps, sh.grp_per_part, slab0);
+void launch_agg(hipStream_t st, int mode, const GatAgg& a, const SlabShape& sh, int slab0) {
+  int64_t gpp;
+  const unsigned blocks = sh.grid(a.n_items, &gpp);
+  if (mode == AGG_Z) k_gat_agg<UNI, AGG_Z><<<blocks, 256, 0, st>>>(a, sh.S, sh.nvs, sh.eps, gpp, slab0);
+  else if (mode == AGG_ZQ) k_gat_agg<UNI, AGG_ZQ><<<blocks, 256, 0, st>>>(a, sh.S, sh.nvs, sh.eps, gpp, slab0);
+  else k_gat_agg<UNI, AGG_Q><<<blocks, 256, 0, st>>>(a, sh.S, sh.nvs, sh.eps, gpp, slab0);
 }
 
 // The sums of a range out of its scores: z (row 0 = the range's first row; relu) and / or Q (row 0 likewise) and r.
@@ -856,30 +862,43 @@ int agg_range(ht_ctx* ctx, const ht_graph* g, const GatRange& rg, const ht_gat_d
   a.Q = Q; a.q_ld = ws.ld_t; a.q_part = rw.q_part;
   a.r = ws.r; a.r_part = rw.part ? rw.part + 2 * rw.n_part : nullptr;
   if (t_items) tm->begin(t_items);
-  for (int p = 0; p < sh.P; ++p) {
-    if (sh.eps == 1) launch_agg<true>(sh.blocks, st, mode, a, sh, p * sh.S);
-    else launch_agg<false>(sh.blocks, st, mode, a, sh, p * sh.S);
-    HT_LAUNCH_CHECK(ctx);
-  }
+  for (int p = 0; p < sh.P; ++p)
+    HT_TRY(ht_in_launches(it.n_items, sh.launch_items(), [&](int64_t i, int64_t n) {
+      GatAgg b = a;
+      b.items += i;
+      b.n_items = n;
+      if (sh.eps == 1) launch_agg<true>(st, mode, b, sh, p * sh.S);
+      else launch_agg<false>(st, mode, b, sh, p * sh.S);
+      HT_LAUNCH_CHECK(ctx);
+      return (int)HT_OK;
+    }));
   if (t_items) tm->end();
   if (it.n_cut == 0) return HT_OK;
   if (t_fix) tm->begin(t_fix);
-  k_gat_fix<<<(unsigned)it.n_cut, 256, 0, st>>>(a, g->fwd_items.cuts.p + it.cut0, mode);
-  HT_LAUNCH_CHECK(ctx);
+  HT_TRY(ht_in_launches(it.n_cut, HT_LAUNCH_WAVES / 4, [&](int64_t i, int64_t n) {
+    k_gat_fix<<<(unsigned)n, 256, 0, st>>>(a, g->fwd_items.cuts.p + it.cut0 + i, mode);
+    HT_LAUNCH_CHECK(ctx);
+    return (int)HT_OK;
+  }));
   if (t_fix) tm->end();
   return HT_OK;
 }
 
-int launch_src(ht_ctx* ctx, const GatPass& a, int nvec) {
-  const unsigned nb = (unsigned)((a.n_items + 3) / 4);
-  if (nvec <= 8) k_gat_src_g<8><<<nb, 256, 0, ctx->stream>>>(a);
-  else if (nvec <= 16) k_gat_src_g<16><<<nb, 256, 0, ctx->stream>>>(a);
-  else if (nvec <= 32) k_gat_src_g<32><<<nb, 256, 0, ctx->stream>>>(a);
-  else if (nvec <= 64) k_gat_src<1><<<nb, 256, 0, ctx->stream>>>(a);
-  else if (nvec <= 128) k_gat_src<2><<<nb, 256, 0, ctx->stream>>>(a);
-  else k_gat_src<4><<<nb, 256, 0, ctx->stream>>>(a);
-  HT_LAUNCH_CHECK(ctx);
-  return HT_OK;
+int launch_src(ht_ctx* ctx, const GatPass& all, int nvec) {
+  return ht_in_launches(all.n_items, HT_LAUNCH_WAVES, [&](int64_t i, int64_t n) {
+    GatPass a = all;
+    a.items += i;
+    a.n_items = n;
+    const unsigned nb = (unsigned)((n + 3) / 4);
+    if (nvec <= 8) k_gat_src_g<8><<<nb, 256, 0, ctx->stream>>>(a);
+    else if (nvec <= 16) k_gat_src_g<16><<<nb, 256, 0, ctx->stream>>>(a);
+    else if (nvec <= 32) k_gat_src_g<32><<<nb, 256, 0, ctx->stream>>>(a);
+    else if (nvec <= 64) k_gat_src<1><<<nb, 256, 0, ctx->stream>>>(a);
+    else if (nvec <= 128) k_gat_src<2><<<nb, 256, 0, ctx->stream>>>(a);
+    else k_gat_src<4><<<nb, 256, 0, ctx->stream>>>(a);
+    HT_LAUNCH_CHECK(ctx);
+    return (int)HT_OK;
+  });
 }
 
 void release_range_ws(ht_ctx* ctx) {

@@ -338,12 +338,30 @@ struct SpmmArgs {
   double* t_fix = nullptr;
 };
 int ht_spmm_launch(ht_ctx* ctx, hipStream_t st, const SpmmArgs& a);
+// A launch of 2^32 threads or more is not rejected, its excess is silently dropped.  Kernels that take a wave per work item, or
+// a block of 4 waves per cut row, therefore go in launches of at most this many waves (2^31 threads; a graph of 70 M vertices
+// has more items than one launch can hold).
+constexpr int64_t HT_LAUNCH_WAVES = (int64_t)1 << 25;
+template <class F>
+int ht_in_launches(int64_t n, int64_t most, F&& launch) {   // launch(first, count)
+  for (int64_t i = 0; i < n; i += most) {
+    const int rc = launch(i, (n - i) < most ? (n - i) : most);
+    if (rc != HT_OK) return rc;
+  }
+  return HT_OK;
+}
 // How an aggregation is spread over the XCDs (d, n_items, n_edges, src, src_ld and max_slabs of `a` are read): P launches of
 // S slabs of nvs float4 columns, eps entries per step of a wave.
 struct SlabShape {
   int S, P, nvs, eps;
-  unsigned blocks;
-  int64_t grp_per_part;      // 0: items interleaved over the XCDs of a slab
+  bool contig;               // each XCD of a slab takes a contiguous part of the items (else they are interleaved)
+  int64_t launch_items() const { return HT_LAUNCH_WAVES / S; }
+  // blocks of 4 waves for one launch over n items; grp_per_part: groups of 4 items per part, 0 where they are interleaved
+  unsigned grid(int64_t n, int64_t* grp_per_part) const {
+    const int64_t parts = 8 / S, gpp = ((n + 3) / 4 + parts - 1) / parts;
+    *grp_per_part = contig ? gpp : 0;
+    return (unsigned)(gpp * 8);
+  }
 };
 int ht_slab_shape(ht_ctx* ctx, const SpmmArgs& a, SlabShape* out);
 // Only the second kernel: the cut rows = their partial rows added in item order (d, out*, partial, cuts, part0 are read).

@@ -1571,9 +1571,12 @@ int build_by_source(ht_ctx* ctx, const ht_graph* g) {
   }
   const int64_t ni = g->bwd_items.n_items;
   if (ni > 0) {
-    k_src_copy<<<nblk(ni, TB / 64), TB, 0, st>>>(g->bwd_items.items.p, ni, lists.p, lists.p + 2 * n1, g->n, off.p,
-                                                g->merged ? g->usdst.p : g->sdst.p, g->merged ? g->uw_bwd.p : nullptr, S.idx.p, S.w.p);
-    HT_LAUNCH_CHECK(ctx);
+    HT_TRY(ht_in_launches(ni, HT_LAUNCH_WAVES, [&](int64_t i, int64_t m) {
+      k_src_copy<<<nblk(m, TB / 64), TB, 0, st>>>(g->bwd_items.items.p + i, m, lists.p, lists.p + 2 * n1, g->n, off.p,
+                                                 g->merged ? g->usdst.p : g->sdst.p, g->merged ? g->uw_bwd.p : nullptr, S.idx.p, S.w.p);
+      HT_LAUNCH_CHECK(ctx);
+      return (int)HT_OK;
+    }));
   }
   b.rows = RowSet{ptr.p, lists.p + 3 * n1, nullptr, 1};
   HT_TRY(count_items(ctx, b, hp));

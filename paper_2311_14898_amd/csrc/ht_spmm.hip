@@ -245,10 +245,24 @@ __global__ void __launch_bounds__(256) k_spmm_slab(SpmmArgs a, int S, int nvs, i
 
 template <int LPR, int VPL>
 int launch_items(ht_ctx* ctx, hipStream_t st, const SpmmArgs& a) {
-  const unsigned blocks = (unsigned)((a.n_items + 3) / 4);
-  k_spmm_items<LPR, VPL><<<blocks, 256, 0, st>>>(a);
-  HT_LAUNCH_CHECK(ctx);
-  return HT_OK;
+  return ht_in_launches(a.n_items, HT_LAUNCH_WAVES, [&](int64_t i, int64_t n) {
+    SpmmArgs b = a;
+    b.items += i;
+    b.n_items = n;
+    k_spmm_items<LPR, VPL><<<(unsigned)((n + 3) / 4), 256, 0, st>>>(b);
+    HT_LAUNCH_CHECK(ctx);
+    return (int)HT_OK;
+  });
+}
+
+int launch_fix(ht_ctx* ctx, hipStream_t st, const SpmmArgs& a) {
+  return ht_in_launches(a.n_fix, HT_LAUNCH_WAVES / 4, [&](int64_t i, int64_t n) {
+    SpmmArgs b = a;
+    b.cuts += i;
+    k_spmm_fix<<<(unsigned)n, 256, 0, st>>>(b);
+    HT_LAUNCH_CHECK(ctx);
+    return (int)HT_OK;
+  });
 }
 
 // dst[dst_idx[k]] = scale[src_idx[k]] * src[src_idx[k]]; a lane group per row,
@@ -329,10 +343,7 @@ int ht_slab_shape(ht_ctx* ctx, const SpmmArgs& a, SlabShape* out) {
   const int eps = 64 / nvs;
   if (S < 1 || (S & (S - 1)) || S > 8 || nvs < 1 || nvs > 64 || eps < 1)
     return ht_set_err(ctx, HT_ESHAPE, "aggregation: bad slab shape S=%d nvs=%d", S, nvs);
-  const int64_t groups = (a.n_items + 3) / 4;
-  const int parts = 8 / S;
-  const int64_t gpp = (groups + parts - 1) / parts;   // item groups per XCD of a slab
-  *out = SlabShape{S, P, nvs, eps, (unsigned)(gpp * 8), ctx->xcd_contig ? gpp : 0};
+  *out = SlabShape{S, P, nvs, eps, ctx->xcd_contig != 0};
   return HT_OK;
 }
 
@@ -353,19 +364,23 @@ int ht_spmm_launch(ht_ctx* ctx, hipStream_t st, const SpmmArgs& a0) {
       SlabShape sh;
       HT_TRY(ht_slab_shape(ctx, a, &sh));
       const int S = sh.S, nvs = sh.nvs, eps = sh.eps;
-      for (int p = 0; p < sh.P; ++p) {
-        const unsigned nb = sh.blocks;
-        const int64_t gp = sh.grp_per_part;
+      for (int p = 0; p < sh.P; ++p) rc = rc != HT_OK ? rc : ht_in_launches(a.n_items, sh.launch_items(), [&](int64_t i, int64_t n) {
+        SpmmArgs b = a;
+        b.items += i;
+        b.n_items = n;
+        int64_t gp;
+        const unsigned nb = sh.grid(n, &gp);
         const bool uni = eps == 1 && ctx->agg_uniform;
         if (ctx->agg_unroll == 8) {
-          if (uni) k_spmm_slab<8, true><<<nb, 256, 0, st>>>(a, S, nvs, eps, gp, p * S);
-          else k_spmm_slab<8, false><<<nb, 256, 0, st>>>(a, S, nvs, eps, gp, p * S);
+          if (uni) k_spmm_slab<8, true><<<nb, 256, 0, st>>>(b, S, nvs, eps, gp, p * S);
+          else k_spmm_slab<8, false><<<nb, 256, 0, st>>>(b, S, nvs, eps, gp, p * S);
         } else {
-          if (uni) k_spmm_slab<4, true><<<nb, 256, 0, st>>>(a, S, nvs, eps, gp, p * S);
-          else k_spmm_slab<4, false><<<nb, 256, 0, st>>>(a, S, nvs, eps, gp, p * S);
+          if (uni) k_spmm_slab<4, true><<<nb, 256, 0, st>>>(b, S, nvs, eps, gp, p * S);
+          else k_spmm_slab<4, false><<<nb, 256, 0, st>>>(b, S, nvs, eps, gp, p * S);
         }
         HT_LAUNCH_CHECK(ctx);
-      }
+        return (int)HT_OK;
+      });
     } else if (nvec <= 8) rc = launch_items<8, 1>(ctx, st, a);
     else if (nvec <= 16) rc = launch_items<16, 1>(ctx, st, a);
     else if (nvec <= 32) rc = launch_items<32, 1>(ctx, st, a);
@@ -377,9 +392,8 @@ int ht_spmm_launch(ht_ctx* ctx, hipStream_t st, const SpmmArgs& a0) {
     if (rc != HT_OK) return rc;
     if (a.n_fix > 0) {
       if (a.tm && a.t_fix) a.tm->begin(a.t_fix);
-      k_spmm_fix<<<(unsigned)a.n_fix, 256, 0, st>>>(a);
+      HT_TRY(launch_fix(ctx, st, a));
       if (a.tm && a.t_fix) a.tm->end();
-      HT_LAUNCH_CHECK(ctx);
     }
   }
   return HT_OK;
@@ -388,9 +402,7 @@ int ht_spmm_launch(ht_ctx* ctx, hipStream_t st, const SpmmArgs& a0) {
 int ht_spmm_fix_launch(ht_ctx* ctx, hipStream_t st, const SpmmArgs& a) {
   if (a.n_fix <= 0) return HT_OK;
   if (a.out_ld & 3) return ht_set_err(ctx, HT_ESHAPE, "aggregation: row pitch must be a multiple of 4");
-  k_spmm_fix<<<(unsigned)a.n_fix, 256, 0, st>>>(a);
-  HT_LAUNCH_CHECK(ctx);
-  return HT_OK;
+  return launch_fix(ctx, st, a);
 }
 
 int ht_gather_rows(ht_ctx* ctx, hipStream_t st, const float* src, int64_t src_ld, const int32_t* src_idx, float* dst,

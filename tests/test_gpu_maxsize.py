@@ -282,3 +282,40 @@ def test_tensors_of_more_than_2_to_32_words():
             B.ht_graph_destroy(g)
     finally:
         B.ht_ctx_destroy(ctx)
+
+
+def test_layer_with_more_items_than_a_launch_holds():
+    """A GCN layer, forward and backward, on 70 M isolated vertices: a wave per work item would be 4.5 G threads, more than a
+    launch holds.  The aggregation over the self-loops alone is the identity: h' = relu(X W) and its gradients row by row."""
+    if torch.cuda.mem_get_info()[0] < 60e9:
+        pytest.skip("needs a GPU with 60 GB of free memory")
+    V, d = 70_000_000, 4
+    ctx = B.ht_ctx_create(0)
+    none = torch.empty(0, dtype=torch.int32, device="cuda")
+    g = B.ht_partition(ctx, V, none, none, 64)
+    try:
+        gen = torch.Generator("cuda").manual_seed(5)
+        X, dH = (torch.empty((V, d), device="cuda").uniform_(-1, 1, generator=gen) for _ in range(2))
+        W = inputs.glorot_weights([d, d])[0].cuda()
+        H, A = (torch.full((V, d), 7.0, device="cuda") for _ in range(2))
+        dX = torch.zeros((V, d), device="cuda")            # (gradients are added to it)
+        dW = torch.empty_like(W)
+        B.ht_layer_fwd(ctx, g, d, d, B.HT_ACT_RELU, X, W, H, A)
+        B.ht_layer_bwd(ctx, g, d, d, B.HT_ACT_RELU, A, W, dH, dW, H_out=H, dH_in=dX, ckpt_kind=B.HT_CKPT_AGG)
+        B.ht_sync(ctx)
+        want_dw = torch.zeros((d, d), dtype=torch.float64, device="cuda")
+        for r0 in range(0, V, 10_000_000):
+            x, h, dz = X[r0:r0 + 10_000_000].double(), H[r0:r0 + 10_000_000], dH[r0:r0 + 10_000_000].double()
+            want = torch.relu(x @ W.double())
+            # sums of 4 products of values below 1 and 0.87: fp32 rounds 8 times, each by at most 2^-24 of the largest sum, 3.5
+            assert float((h.double() - want).abs().max()) <= 8 * 2.0 ** -24 * 3.5, r0
+            dz = dz * (h > 0)
+            assert float((dX[r0:r0 + 10_000_000].double() - dz @ W.double().t()).abs().max()) <= 8 * 2.0 ** -24 * 3.5, r0
+            want_dw += x.t() @ dz
+        # 70 M products below 1: each fp32 partial sum is off by at most 2^-24 of a partial sum; far below 1e-4 of the largest entry
+        # plus what independent signs leave of the sum (sqrt(V / 18))
+        scale = float(want_dw.abs().max()) + (V / 18) ** 0.5
+        assert float((dW.double() - want_dw).abs().max()) <= 1e-4 * scale
+    finally:
+        B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)
