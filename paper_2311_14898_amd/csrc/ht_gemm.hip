@@ -299,7 +299,7 @@ __global__ void __launch_bounds__(256) k_gemm_tn(const float* __restrict__ A, in
 // 2.4e-7, 602 x 256 4.4e-7 | 3.7e-7; A^T B over 100,000 rows, 256 x 256 4.4e-7 | 3.5e-7, 233 k rows, 602 x 256 5.6e-7 | 3.4e-7 (with
 // the small products summed apart; in one sum with the large ones it was 8.3e-7: thousands of rows, rounded six times per step).
 // 2.45 M rows, 256 x 256: A W 3.08 -> 2.35 ms, A^T B 2.92 -> 2.51; 233 k rows, 602 x 256: 0.68 -> 0.44 and 0.70 -> 0.60 ms.
-// Values below about 2^-110 lose the low bits of their third part: an absolute error of 2^-134 of a product's other factor.
+// Values below about 2^-110 lose the low bits of their third part: an error of up to 2^-134 times the other factor.
 // Values that are not finite, or round to infinity as bf16, would leave NaN where an fp32 product has an infinity: a block whose
 // tile holds anything but finite numbers computes it again in fp32, element by element.
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
