@@ -1073,8 +1073,13 @@ int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
     HT_TRY(gat_bwd_rows_direct(ctx, g, desc, ws, keep, H_in, W, a_dst, a_src, H_out, dH_out, dT, ld_dt, local, tm, &lk, &at_once));
   if (!at_once && keep) return ht_set_err(ctx, HT_ENOMEM, "GAT backward: no memory for all vertices at once beside what the forward pass kept");
   RangeWs rw;
+  float* src_part = nullptr;
   if (!at_once) {
+    // Both passes of a chunk keep their partial sums in one slot, one after the other.  It is taken at the larger size before
+    // either pointer into it is kept: a slot that grew between two chunks would leave the first pass writing into freed memory.
+    if (g->max_bpart > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)g->max_bpart * ld_dt * 4, (void**)&src_part));
     HT_TRY(range_ws(ctx, ranges_of(g, 0, false), 0, ws.ld_t, &rw));
+    if (g->max_bpart > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)g->max_bpart * ld_dt * 4, (void**)&src_part));
     HT_TRY(prepare(ctx, g, desc, H_in, W, a_dst, a_src, &ws, local, tm, &lk));
     HT_TRY(ht_scratch(ctx, HT_S_DZCHUNK, (size_t)mx * ws.ld_t * 4, (void**)&dz));
     HT_TRY(ht_scratch(ctx, HT_S_ACHUNK, (size_t)mx * ws.ld_t * 4, (void**)&Q));
@@ -1132,15 +1137,13 @@ int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
     GatPass a{};
     a.d = d; a.q = ws.q; a.d4 = ws.d4; a.slope = desc->slope;
     // source pass
-    float* partial = nullptr;
-    if (c.bwd.n_part > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)g->max_bpart * ld_dt * 4, (void**)&partial));
     a.items = g->bwd_items.items.p + c.bwd.it0; a.n_items = c.bwd.n_items; a.part0 = c.bwd.part0;
     a.idx = g->merged ? g->usdst.p : g->sdst.p;
     a.mult = g->merged ? g->umult_bwd.p : nullptr;
     a.mat = dz; a.mat_ld = ws.ld_t;
     a.own = ws.T; a.own_ld = ws.ld_t; a.own_idx = g->nbr.p;
     a.out = dT; a.out_ld = ld_dt; a.add = true;
-    a.partial = partial; a.sc_col = sc_col;
+    a.partial = src_part; a.sc_col = sc_col;
     tm->begin(&local->t_gat_src_ms);
     if (a.n_items > 0) HT_TRY(launch_src(ctx, a, nvec));
     if (c.bwd.n_cut > 0) {
@@ -1149,7 +1152,7 @@ int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
       f.d = sc_col + 4;
       f.out = dT; f.out_ld = ld_dt; f.out_idx = g->nbr.p;
       f.accumulate = 1;
-      f.partial = partial;
+      f.partial = src_part;
       HT_TRY(ht_spmm_fix_launch(ctx, st, f));
     }
     tm->end();

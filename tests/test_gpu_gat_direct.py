@@ -77,3 +77,32 @@ def test_gat_epoch_all_chunks_at_once(graph, dims, n, loops, lean):
     finally:
         B.ht_graph_destroy(g)
         B.ht_ctx_destroy(ctx)
+
+
+def test_gat_backward_chunk_pass_partial_sums_of_both_directions():
+    """The chunk-by-chunk backward pass (host-resident input) keeps the partial sums of cut destinations and of cut sources in one
+    slot: here the sources need many times more of it, and destinations are cut in the first and in the last chunk."""
+    V, di, dn, n = 4_003, 12, 21, 4
+    gen = torch.Generator().manual_seed(8)
+    hubs = torch.arange(20).repeat_interleave(1500)                       # sources with about 1500 entries each
+    src = torch.cat([torch.randint(0, V, (4 * V,), generator=gen), hubs, torch.randint(0, V, (1600,), generator=gen)])
+    dst = torch.cat([torch.randint(0, V, (4 * V + hubs.numel(),), generator=gen), torch.tensor([3, V - 2]).repeat_interleave(800)])
+    src, dst = src.to(torch.int32), dst.to(torch.int32)
+    X, dH = torch.randn(V, di, generator=gen), torch.randn(V, dn, generator=gen)
+    W, a_dst, a_src = torch.randn(di, dn, generator=gen) / di ** 0.5, torch.randn(dn, generator=gen) / 4, torch.randn(dn, generator=gen) / 4
+    indptr, col = orc.csc_build(V, src.numpy(), dst.numpy(), True)
+    p = (W.numpy(), a_dst.numpy(), a_src.numpy())
+    fwd = orc.gat_layer_fwd(indptr, col, X.numpy(), *p, relu=False)
+    ref = orc.gat_layer_bwd(indptr, col, X.numpy(), *p, fwd, dH.numpy(), relu=False, want_dH=True)
+    ctx = B.ht_ctx_create(0)
+    g = B.ht_partition(ctx, V, src.cuda(), dst.cuda(), n)
+    try:
+        Xh, H, dHd, dX = B.to_matrix(X, B.HT_LOC_HOST_PINNED), B.to_matrix(torch.from_numpy(fwd["h"]).float()), B.to_matrix(dH), B.alloc_matrix(V, di)
+        dW, dad, das = torch.empty(di, dn, device="cuda"), torch.empty(dn, device="cuda"), torch.empty(dn, device="cuda")
+        B.ht_gat_layer_bwd(ctx, g, di, dn, B.HT_ACT_NONE, Xh, W.cuda(), a_dst.cuda(), a_src.cuda(), H, dHd, dW, dad, das, dH_in=dX)
+        B.ht_sync(ctx)
+        for got, name in ((dX[:, :di], "dH"), (dW, "dW"), (dad, "da_dst"), (das, "da_src")):
+            assert_close_grad(got.cpu().numpy(), ref[name], name)
+    finally:
+        B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)
