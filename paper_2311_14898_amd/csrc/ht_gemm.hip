@@ -1,7 +1,7 @@
 // Dense transform of the update stage (Eq. 2: linear + ReLU) and its gradient
 // GEMMs (Sec. 2.3: grad W = a^T (ReLU'(aW) * grad h'), grad a = grad z W^T) on
-// the fp32 matrix cores (v_mfma_f32_32x32x2_f32), LDS-tiled for 64-wide waves.  Large products
-// with wide outputs run on the bf16 matrix cores in fp32 precision (k_split_nn, k_split_tn).
+// the fp32 matrix cores (v_mfma_f32_32x32x2_f32), LDS-tiled for 64-wide waves.  grad W with
+// wide outputs runs on the bf16 matrix cores in fp32 precision (k_split_tn).
 //
 //   NN: C[M x N] = A[M x K] Bp        M = chunk rows (tall), K, N = layer widths
 //   TN: C[K x N] = A[M x K]^T B[M x N] reduction over the tall M, cut into
@@ -291,23 +291,20 @@ __global__ void __launch_bounds__(256) k_gemm_tn(const float* __restrict__ A, in
     }
 }
 
-// ---- the same products on the bf16 matrix cores, in fp32 precision.
+// ---- A^T B on the bf16 matrix cores, in fp32 precision.
 // Every fp32 value is split into three bf16 values whose sum it is to 24 bits (x = x0 + x1 + x2, each the rounding of what the ones
-// before leave), and six of the nine partial products are added in fp32, smallest first; the three left out are below 2^-26 of
-// the product.  Six 32x32x16 bf16 steps take 192 clocks where eight 32x32x2 fp32 steps take 512, and fewer fp32 sums
-// are rounded.  Relative errors against fp64 (2-norm; fp32 products | these): A W at 129 x 67 2.0e-7 | 1.7e-7, 256 x 256 2.9e-7 |
-// 2.4e-7, 602 x 256 4.4e-7 | 3.7e-7; A^T B over 100,000 rows, 256 x 256 4.4e-7 | 3.5e-7, 233 k rows, 602 x 256 5.6e-7 | 3.4e-7 (with
+// before leave), and six of the nine partial products are added in fp32, smallest first.  Six 32x32x16 bf16 steps take 192 clocks
+// where eight 32x32x2 fp32 steps take 512, and fewer fp32 sums are rounded.  Relative errors against fp64 (2-norm; fp32 products |
+// these): 100,000 rows, 256 x 256 4.4e-7 | 3.5e-7, 233 k rows, 602 x 256 5.6e-7 | 3.4e-7 (with
 // the small products summed apart; in one sum with the large ones it was 8.3e-7: thousands of rows, rounded six times per step).
-// 2.45 M rows, 256 x 256: A W 3.08 -> 2.35 ms, A^T B 2.92 -> 2.51; 233 k rows, 602 x 256: 0.68 -> 0.44 and 0.70 -> 0.60 ms.
-// Values below about 2^-110 lose the low bits of their third part: an error of up to 2^-134 times the other factor.
+// (A W and dZ W^T stay in fp32.  Split in the same way, with two sums, they are as exact, but take 2.72 ms instead of 2.88 and 2.97
+// instead of 2.87 at 2.45 M rows, 256 x 256; with one sum, 2.47 and 2.54 ms, the matrix cores' rounding of small addends is
+// felt: single products off by up to 2^-23, and sums over rows that a ReLU has masked 15 % further off than in fp32.)
 // Values that are not finite, or round to infinity as bf16, would leave NaN where an fp32 product has an infinity: a block whose
 // tile holds anything but finite numbers computes it again in fp32, element by element.
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
-typedef float v4f __attribute__((ext_vector_type(4)));
 constexpr int SK = 32;                       // reduction depth of one LDS stage: two steps of 16
 constexpr int SB = BM * 16;                  // bf16 per [128 rows][16] block of a stage [plane][step]
-constexpr int SA = SB + 64;                  // the same where two steps are written by one wave: 128 bytes apart, in other banks
 
 __device__ __forceinline__ void split3(float x, __bf16* p) {
   p[0] = (__bf16)x;
@@ -315,20 +312,16 @@ __device__ __forceinline__ void split3(float x, __bf16* p) {
   p[1] = (__bf16)r;
   p[2] = (__bf16)(r - (float)p[1]);
 }
-// a wave's 64 x 64 part of the block's 128 x 128; APART: the five small partial products have sums of their own
-template <bool APART>
+// a wave's 64 x 64 part of the block's 128 x 128; the five small partial products have sums of their own
 struct SplitTile {
-  v16f acc[2][2], low[APART ? 2 : 1][APART ? 2 : 1];
+  v16f acc[2][2], low[2][2];
   __device__ __forceinline__ void clear() {
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          acc[i][j][e] = 0.f;
-          if (APART) low[i][j][e] = 0.f;
-        }
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = low[i][j][e] = 0.f;
   }
   __device__ __forceinline__ void join() {
 #pragma unroll
@@ -338,8 +331,7 @@ struct SplitTile {
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[i][j][e] += low[i][j][e];
   }
-  // one LDS stage; As, Bs: [plane][step][row][16], PA_ and PB_ apart
-  template <int PA_, int PB_>
+  // one LDS stage; As, Bs: [plane][step][row][16]
   __device__ __forceinline__ void stage(const __bf16* As, const __bf16* Bs, int wm, int wn, int l32, int half) {
 #pragma unroll
     for (int st = 0; st < 2; ++st) {
@@ -348,8 +340,8 @@ struct SplitTile {
       for (int p = 0; p < 3; ++p)
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-          a[p][i] = *reinterpret_cast<const v8bf*>(As + (p * 2 + st) * PA_ + (wm * 64 + i * 32 + l32) * 16 + half * 8);
-          b[p][i] = *reinterpret_cast<const v8bf*>(Bs + (p * 2 + st) * PB_ + (wn * 64 + i * 32 + l32) * 16 + half * 8);
+          a[p][i] = *reinterpret_cast<const v8bf*>(As + (p * 2 + st) * SB + (wm * 64 + i * 32 + l32) * 16 + half * 8);
+          b[p][i] = *reinterpret_cast<const v8bf*>(Bs + (p * 2 + st) * SB + (wn * 64 + i * 32 + l32) * 16 + half * 8);
         }
       constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
 #pragma unroll
@@ -358,7 +350,7 @@ struct SplitTile {
         for (int i = 0; i < 2; ++i)
 #pragma unroll
           for (int j = 0; j < 2; ++j) {
-            v16f& s = APART && q < 5 ? low[APART ? i : 0][APART ? j : 0] : acc[i][j];
+            v16f& s = q < 5 ? low[i][j] : acc[i][j];
             s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[q]][i], b[PB[q]][j], s, 0, 0, 0);
           }
     }
@@ -374,129 +366,6 @@ struct SplitTile {
     return ok;
   }
 };
-
-// W (transpose = 1: W^T) split into the stages that k_split_nn copies: [column block][stage][plane][step][column][16]
-__global__ void k_pack_split(const float* __restrict__ W, int K, int N, int transpose, __bf16* __restrict__ out, int stages, int64_t total) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;   // (column, row) of the padded operand
-  if (i >= total) return;
-  const int kk = (int)(i % SK);
-  const int64_t t = i / SK;
-  const int c = (int)(t % BM), st = (int)(t / BM % stages), cb = (int)(t / BM / stages);
-  const int r = st * SK + kk, col = cb * BM + c;
-  float v = 0.f;
-  if (r < K && col < N) v = transpose ? W[(int64_t)col * K + r] : W[(int64_t)r * N + col];
-  __bf16 p[3];
-  split3(v, p);
-  __bf16* o = out + ((int64_t)cb * stages + st) * (6 * SB) + (kk >> 4) * SB + c * 16 + (kk & 15);
-  o[0] = p[0];
-  o[2 * SB] = p[1];
-  o[4 * SB] = p[2];
-}
-
-// Row and column block of a workgroup.  Workgroups go to the 8 XCDs round-robin: the column blocks of a row block run 8 workgroups
-// apart, on one XCD and close in time, so that the row block of A comes out of its L2 after the first (one after the other over
-// all row blocks, A was read from memory once per column block).
-__device__ __forceinline__ void tile_of_block(int64_t* mb, int* nb) {
-  *mb = blockIdx.x;
-  *nb = blockIdx.y;
-  if (gridDim.y > 1) {
-    const int64_t gx = gridDim.x, full = gx & ~(int64_t)7, ny = gridDim.y, L = (int64_t)blockIdx.y * gx + blockIdx.x;
-    if (L < full * ny) {
-      *mb = L / (8 * ny) * 8 + (L & 7);
-      *nb = (int)((L >> 3) % ny);
-    } else {
-      *mb = full + (L - full * ny) % (gx - full);
-      *nb = (int)((L - full * ny) / (gx - full));
-    }
-  }
-}
-
-// C = A W (+ReLU, or added to C); W is also given as it is, for blocks with values that are not finite
-__global__ void __launch_bounds__(256, 3) k_split_nn(const float* __restrict__ A, int64_t lda, const __bf16* __restrict__ Bp,
-                                                  const float* __restrict__ W, int transpose, float* __restrict__ C, int64_t ldc,
-                                                  int64_t M, int K, int N, int relu) {
-  __shared__ __attribute__((aligned(16))) __bf16 As[6 * SA];
-  __shared__ __attribute__((aligned(16))) __bf16 Bs[6 * SB];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, half = lane >> 5;
-  int64_t mb;
-  int nb;
-  tile_of_block(&mb, &nb);
-  const int64_t m0 = mb * BM;
-  const int n0 = nb * 128, stages = (K + SK - 1) / SK;
-  constexpr int NB = 6 * SB / 8, NBT = NB / 256;   // 16-byte words of B per stage
-  static_assert(NBT * 256 == NB, "");
-  const v4f* Bw = reinterpret_cast<const v4f*>(Bp + (int64_t)nb * stages * (6 * SB));
-  const bool interior = m0 + BM <= M;
-  const int kq = tid & 7;
-  float4 ra[4];
-  v4f rb[NBT];
-  auto fetch = [&](int s) {
-    const int gk = s * SK + kq * 4;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t gm = m0 + (tid >> 3) + u * 32;
-      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-      if ((interior || gm < M) && gk < K) {
-        v = ld4g(A + gm * lda + gk);
-        if (gk + 4 > K) {
-          if (gk + 1 >= K) v.y = 0.f;
-          if (gk + 2 >= K) v.z = 0.f;
-          v.w = 0.f;
-        }
-      }
-      ra[u] = v;
-    }
-#pragma unroll
-    for (int u = 0; u < NBT; ++u) rb[u] = Bw[(int64_t)s * NB + tid + u * 256];
-  };
-  auto stash = [&]() {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      __bf16 p[4][3];
-      split3(ra[u].x, p[0]);
-      split3(ra[u].y, p[1]);
-      split3(ra[u].z, p[2]);
-      split3(ra[u].w, p[3]);
-      __bf16* d = As + (kq >> 2) * SA + ((tid >> 3) + u * 32) * 16 + (kq & 3) * 4;
-#pragma unroll
-      for (int q = 0; q < 3; ++q) *reinterpret_cast<v4bf*>(d + q * 2 * SA) = v4bf{p[0][q], p[1][q], p[2][q], p[3][q]};
-    }
-#pragma unroll
-    for (int u = 0; u < NBT; ++u) reinterpret_cast<v4f*>(Bs)[tid + u * 256] = rb[u];
-  };
-  SplitTile<false> t;
-  t.clear();
-  fetch(0);
-  for (int s = 0; s < stages; ++s) {
-    stash();
-    __syncthreads();
-    if (s + 1 < stages) fetch(s + 1);
-    t.stage<SA, SB>(As, Bs, wm, wn, l32, half);
-    __syncthreads();
-  }
-  const bool again = __syncthreads_or(!t.all_finite());
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int gc = n0 + wn * 64 + j * 32 + l32;
-      if (gc >= N) continue;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int64_t gr = m0 + wm * 64 + i * 32 + (e >> 2) * 8 + half * 4 + (e & 3);
-        if (!interior && gr >= M) continue;
-        float v = t.acc[i][j][e];
-        if (again) {
-          v = 0.f;
-          for (int k = 0; k < K; ++k) v = fmaf(A[gr * lda + k], transpose ? W[(int64_t)gc * K + k] : W[(int64_t)k * N + gc], v);
-        }
-        if (relu & 1) v = v > 0.f ? v : 0.f;
-        if (relu & 2) v += C[gr * ldc + gc];
-        C[gr * ldc + gc] = v;
-      }
-    }
-}
 
 // Partial tile of C[K x N] = A^T B over a slice of rows, as k_gemm_tn
 __global__ void __launch_bounds__(256, 2) k_split_tn(const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
@@ -548,7 +417,7 @@ __global__ void __launch_bounds__(256, 2) k_split_tn(const float* __restrict__ A
       for (int q = 0; q < 3; ++q) *reinterpret_cast<v8bf*>(S + (q * 2 + st) * SB + c * 16 + h * 8) = o[q];
     }
   };
-  SplitTile<true> t;
+  SplitTile t;
   t.clear();
   if (ms < me) fetch(ms);
   for (int64_t mm = ms; mm < me; mm += SK) {
@@ -556,7 +425,7 @@ __global__ void __launch_bounds__(256, 2) k_split_tn(const float* __restrict__ A
     put(rb, has_b, Bs);
     __syncthreads();
     if (mm + SK < me) fetch(mm + SK);
-    t.stage<SB, SB>(As, Bs, wm, wn, l32, half);
+    t.stage(As, Bs, wm, wn, l32, half);
     __syncthreads();
   }
   t.join();
@@ -680,26 +549,6 @@ int gemm_nn_packed(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, con
   return HT_OK;
 }
 
-// Which products go through the split kernels: both output dimensions of the tile filled (N > 64; the narrow tiles are bound by
-// memory either way), a reduction of at least one stage, and enough row blocks that the packing of W and the deeper stage pay.
-// (The allocation-free call's static array is sized for the fp32 pack.)
-bool use_split(const ht_ctx* ctx, int64_t M, int K, int N) { return !ctx->static_mode && N > 64 && K >= SK && M >= 8192; }
-
-size_t split_pack_bytes(int K, int N) { return (size_t)((N + BM - 1) / BM) * ((K + SK - 1) / SK) * (6 * SB) * 2; }
-
-int split_nn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* W, int transpose, float* C, int64_t ldc, int64_t M,
-             int K, int N, int relu) {
-  __bf16* Bp = nullptr;
-  HT_TRY(ht_scratch(ctx, HT_S_PACKW, split_pack_bytes(K, N), (void**)&Bp));
-  const int stages = (K + SK - 1) / SK, nb = (N + BM - 1) / BM;
-  const int64_t total = (int64_t)nb * stages * BM * SK;
-  k_pack_split<<<(unsigned)((total + 255) / 256), 256, 0, st>>>(W, K, N, transpose, Bp, stages, total);
-  HT_LAUNCH_CHECK(ctx);
-  k_split_nn<<<dim3((unsigned)((M + BM - 1) / BM), (unsigned)nb), 256, 0, st>>>(A, lda, Bp, W, transpose, C, ldc, M, K, N, relu);
-  HT_LAUNCH_CHECK(ctx);
-  return HT_OK;
-}
-
 }  // namespace
 
 // scratch slots: 0 = packed W, 1 = TN partial tiles
@@ -717,7 +566,6 @@ int ht_pack_w(ht_ctx* ctx, hipStream_t st, const float* W, int32_t K, int32_t N,
 int ht_gemm_nn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, float* C, int64_t ldc,
                int64_t M, int32_t K, int32_t N, int relu) {
   if (lda & 3) return ht_set_err(ctx, HT_ESHAPE, "gemm: row pitch must be a multiple of 4");
-  if (use_split(ctx, M, K, N)) return split_nn(ctx, st, A, lda, B, 0, C, ldc, M, K, N, relu);
   const int Kp = round_up(K, BK), Np = round_up(N, 128);
   float* Bp = nullptr;
   HT_TRY(ht_scratch(ctx, HT_S_PACKW, (size_t)Kp * Np * 4, (void**)&Bp));
@@ -730,7 +578,6 @@ int ht_gemm_nt(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const f
                int64_t M, int32_t N, int32_t K, int accumulate) {
   // C[M x K] = A[M x N] (B[K x N])^T : reduction over N, output width K
   if (lda & 3) return ht_set_err(ctx, HT_ESHAPE, "gemm: row pitch must be a multiple of 4");
-  if (use_split(ctx, M, N, K)) return split_nn(ctx, st, A, lda, B, 1, C, ldc, M, N, K, accumulate ? 2 : 0);
   const int Rp = round_up(N, BK), Cp = round_up(K, 128);
   float* Bp = nullptr;
   HT_TRY(ht_scratch(ctx, HT_S_PACKW, (size_t)Rp * Cp * 4, (void**)&Bp));
@@ -782,7 +629,7 @@ int ht_gemm_reserve(ht_ctx* ctx, int64_t M, int32_t K, int32_t N) {
   SliceRule{tn_tiles(K, N), true}.cut(std::max<int64_t>(M, 1), &rows, &slices);
   void* p = nullptr;
   HT_TRY(ht_scratch(ctx, HT_S_TNPART, (size_t)(slices * K * N) * 4, &p));
-  return ht_scratch(ctx, HT_S_PACKW, std::max((size_t)std::max(ht_packed_w_bytes(K, N), ht_packed_w_bytes(N, K)), std::max(split_pack_bytes(K, N), split_pack_bytes(N, K))), &p);
+  return ht_scratch(ctx, HT_S_PACKW, (size_t)std::max(ht_packed_w_bytes(K, N), ht_packed_w_bytes(N, K)), &p);
 }
 
 // The row groups' sums one after the other, as ht_gemm_tn called once per group would add them, in as few launches as the

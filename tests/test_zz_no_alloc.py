@@ -48,6 +48,11 @@ def test_static_scratch_layer_forward_matches_the_allocating_entry_point():
         g2, H2, W2 = _case(ctx, 900, 5_000, 700, 40, 24, 3, seed=2)
         gs.append(g2)
         _both(ctx, g2, 900, 40, 24, H2, W2)
+        # thousands of rows and wide outputs: no kernel that only the allocating call would take (bits differ otherwise)
+        for V, E, d_in, d_out, n, seed in ((9_000, 60_000, 129, 96, 4, 3), (40_001, 200_000, 64, 200, 3, 4), (8_500, 30_000, 300, 129, 2, 5)):
+            g4, H4, W4 = _case(ctx, V, E, 1000, d_in, d_out, n, seed)
+            gs.append(g4)
+            _both(ctx, g4, V, d_in, d_out, H4, W4)
         # and the first again, after the smaller one
         _both(ctx, g1, 6000, 200, 96, H1, W1)
         # beyond the array: a 4096 x 2048 weight matrix packs to 32 MiB
