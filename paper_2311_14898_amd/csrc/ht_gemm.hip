@@ -292,27 +292,35 @@ __global__ void __launch_bounds__(256) k_gemm_tn(const float* __restrict__ A, in
 }
 
 // ---- A^T B on the bf16 matrix cores, in fp32 precision.
-// Every fp32 value is split into three bf16 values whose sum it is to 24 bits (x = x0 + x1 + x2, each the rounding of what the ones
-// before leave), and six of the nine partial products are added in fp32, smallest first.  Six 32x32x16 bf16 steps take 192 clocks
-// where eight 32x32x2 fp32 steps take 512, and fewer fp32 sums are rounded.  Relative errors against fp64 (2-norm; fp32 products |
-// these): 100,000 rows, 256 x 256 4.4e-7 | 3.5e-7, 233 k rows, 602 x 256 5.6e-7 | 3.4e-7 (with
-// the small products summed apart; in one sum with the large ones it was 8.3e-7: thousands of rows, rounded six times per step).
+// Every fp32 value is split into three bf16 values whose sum it is (x = x0 + x1 + x2, each the rounding of what the ones before
+// leave: |x1| <= 2^-8 |x|, |x2| <= 2^-17 |x|), and eight of the nine partial products are added in fp32, smallest first; x2 y2 is
+// below 2^-33 of the product.  (Without x1 y2 and x2 y1, up to 2^-24 of it together, single products were off by up to 1.75 x
+// 2^-24, now by 1.002 x; in fp32 by 1 x.)  The operands are scaled by 2^24 first and the sums by 2^-48 at the end, both exact: the
+// last part of every fp32 number, subnormal ones too, is then a normal bf16 (unscaled, factors below 2^-110 lost low bits).
+// Eight 32x32x16 bf16 steps take 256 clocks where eight 32x32x2 fp32 steps take 512, and fewer fp32 sums are rounded.  Relative
+// errors against fp64 (2-norm; fp32 products | these): 60,000 rows, 256 x 128 4.0e-7 | 2.9e-7, half of them masked 3.5e-7 | 2.9e-7,
+// 233 k rows, 602 x 256 8.7e-7 | 3.4e-7 (with the small products summed apart: thousands of rows, rounded eight times per step).
+// fp32 -> these: 2.45 M rows, 100 x 256 1.60 -> 1.28 ms, 256 x 256 2.84 -> 2.69; 1 M rows, 160 x 128 0.62 -> 0.53; 233 k rows,
+// 602 x 256 0.73 -> 0.67; 116 k rows, 301 x 129 238 -> 197 us; 60 k rows, 129 x 67 69 -> 50.
 // (A W and dZ W^T stay in fp32.  Split in the same way, with two sums, they are as exact, but take 2.72 ms instead of 2.88 and 2.97
 // instead of 2.87 at 2.45 M rows, 256 x 256; with one sum, 2.47 and 2.54 ms, the matrix cores' rounding of small addends is
 // felt: single products off by up to 2^-23, and sums over rows that a ReLU has masked 15 % further off than in fp32.)
-// Values that are not finite, or round to infinity as bf16, would leave NaN where an fp32 product has an infinity: a block whose
-// tile holds anything but finite numbers computes it again in fp32, element by element.
+// Values that are not finite, or whose scaled products are not (beyond about 2^80), would leave NaN where an fp32 product has an
+// infinity or a number: a block whose tile holds anything but finite numbers computes it again in fp32, element by element.
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 constexpr int SK = 32;                       // reduction depth of one LDS stage: two steps of 16
 constexpr int SB = BM * 16;                  // bf16 per [128 rows][16] block of a stage [plane][step]
 
+constexpr float SPLIT_SCALE = 0x1p24f, SPLIT_UNSCALE = 0x1p-48f;   // of each operand; of the sums
+
 __device__ __forceinline__ void split3(float x, __bf16* p) {
+  x *= SPLIT_SCALE;
   p[0] = (__bf16)x;
   const float r = x - (float)p[0];
   p[1] = (__bf16)r;
   p[2] = (__bf16)(r - (float)p[1]);
 }
-// a wave's 64 x 64 part of the block's 128 x 128; the five small partial products have sums of their own
+// a wave's 64 x 64 part of the block's 128 x 128; the seven small partial products have sums of their own
 struct SplitTile {
   v16f acc[2][2], low[2][2];
   __device__ __forceinline__ void clear() {
@@ -343,14 +351,14 @@ struct SplitTile {
           a[p][i] = *reinterpret_cast<const v8bf*>(As + (p * 2 + st) * SB + (wm * 64 + i * 32 + l32) * 16 + half * 8);
           b[p][i] = *reinterpret_cast<const v8bf*>(Bs + (p * 2 + st) * SB + (wn * 64 + i * 32 + l32) * 16 + half * 8);
         }
-      constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+      constexpr int PA[8] = {2, 1, 2, 0, 1, 1, 0, 0}, PB[8] = {1, 2, 0, 2, 1, 0, 1, 0};
 #pragma unroll
-      for (int q = 0; q < 6; ++q)
+      for (int q = 0; q < 8; ++q)
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
           for (int j = 0; j < 2; ++j) {
-            v16f& s = q < 5 ? low[i][j] : acc[i][j];
+            v16f& s = q < 7 ? low[i][j] : acc[i][j];
             s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[q]][i], b[PB[q]][j], s, 0, 0, 0);
           }
     }
@@ -441,7 +449,7 @@ __global__ void __launch_bounds__(256, 2) k_split_tn(const float* __restrict__ A
       for (int e = 0; e < 16; ++e) {
         const int gr = kc0 + wm * 64 + i * 32 + (e >> 2) * 8 + half * 4 + (e & 3);
         if (gr >= K) continue;
-        float v = t.acc[i][j][e];
+        float v = t.acc[i][j][e] * SPLIT_UNSCALE;
         if (again) {
           v = 0.f;
           for (int64_t m = ms; m < me; ++m) v = fmaf(A[m * lda + gr], B[m * ldb + gc], v);
