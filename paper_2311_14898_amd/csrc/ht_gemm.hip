@@ -599,13 +599,22 @@ namespace {
 
 int tn_tiles(int32_t K, int32_t N) { return ((K + BM - 1) / BM) * (N > 64 ? (N + 127) / 128 : 1); }
 
+// Which grad W goes through k_split_tn: both sides of the tile filled, and enough rows, or enough work in all, that its deeper stages
+// and longer prologue pay.  us in fp32 | split, at rows x K x N.  Beyond the line: 60 k x 129 x 67 69 | 50, 60 k x 256 x 128 57 | 56,
+// 20 k x 256 x 256 51 | 49, 9 k x 602 x 256 66 | 55.  Before it: 20 k x 256 x 128 29 | 31, 9 k x 256 x 256 27 | 31,
+// 4 k x 256 x 256 20 | 22, 1 k x 256 x 256 17 | 19.
+bool use_split_tn(int64_t rows, int32_t K, int32_t N) {
+  return K > 64 && N > 64 && (rows >= 32768 || (double)rows * K * N >= 1e9);
+}
+
+// rows: destination rows behind all slices
 int launch_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t M, int32_t K,
-              int32_t N, int64_t slice_rows, int64_t slices, const int64_t* tab, int accumulate) {
+              int32_t N, int64_t slice_rows, int64_t slices, const int64_t* tab, int64_t rows, int accumulate) {
   const int64_t kn = (int64_t)K * N;
   float* P = nullptr;
   HT_TRY(ht_scratch(ctx, HT_S_TNPART, (size_t)(slices * kn) * 4, (void**)&P));
   dim3 grid((unsigned)((K + BM - 1) / BM), (unsigned)(N > 64 ? (N + 127) / 128 : 1), (unsigned)slices);
-  if (N > 64 && K > 64)
+  if (use_split_tn(rows, K, N))
     k_split_tn<<<grid, 256, 0, st>>>(A, lda, B, ldb, P, M, K, N, slice_rows, tab);
   else if (N > 64)
     k_gemm_tn<128, 2, 2, 2, 2><<<grid, 256, 0, st>>>(A, lda, B, ldb, P, M, K, N, slice_rows, tab);
@@ -629,7 +638,7 @@ int ht_gemm_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const f
   }
   int64_t rows, slices;
   SliceRule{tn_tiles(K, N), true}.cut(M, &rows, &slices);
-  return launch_tn(ctx, st, A, lda, B, ldb, C, M, K, N, rows, slices, nullptr, accumulate);
+  return launch_tn(ctx, st, A, lda, B, ldb, C, M, K, N, rows, slices, nullptr, M, accumulate);
 }
 
 int ht_gemm_reserve(ht_ctx* ctx, int64_t M, int32_t K, int32_t N) {
@@ -653,6 +662,8 @@ int ht_gemm_tn_groups(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, 
   if (K <= 0 || N <= 0) return HT_OK;
   const SliceRule rule{tn_tiles(K, N)};
   const int64_t most = std::max<int64_t>(1024, std::min<int64_t>(32768, ((int64_t)1 << 30) / ((int64_t)K * N * 4)));   // slices per launch
+  int64_t all = 0;
+  for (size_t k = 0; k < G; ++k) all += groups[2 * k + 1] - groups[2 * k];
   for (size_t g0 = 0; g0 < G;) {
     size_t g1 = g0;
     int64_t total = 0;
@@ -666,7 +677,7 @@ int ht_gemm_tn_groups(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, 
     HT_TRY(ht_scratch(ctx, HT_S_TNTAB, (size_t)total * 16, (void**)&tab));
     k_slice_table<<<(unsigned)(g1 - g0), 256, 0, st>>>(d_groups + 2 * g0, rule, tab);
     HT_LAUNCH_CHECK(ctx);
-    HT_TRY(launch_tn(ctx, st, A, lda, B, ldb, C, 0, K, N, 0, total, tab, g0 > 0));
+    HT_TRY(launch_tn(ctx, st, A, lda, B, ldb, C, 0, K, N, 0, total, tab, all, g0 > 0));
     g0 = g1;
   }
   return HT_OK;

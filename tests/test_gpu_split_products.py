@@ -32,7 +32,9 @@ def _run(ctx, X, W, dH):
 
 
 @gpu
-@pytest.mark.parametrize("V,di,dn", [(8192, 32, 65), (8193, 33, 128), (9001, 129, 127), (8320, 256, 129), (8191, 96, 96), (12_345, 65, 66)])
+@pytest.mark.parametrize("V,di,dn", [(8192, 32, 65), (8193, 33, 128), (9001, 129, 127), (8320, 256, 129), (8191, 96, 96), (12_345, 65, 66),
+                                     (32_768, 65, 65), (32_769, 66, 128), (33_001, 129, 127), (32_767, 96, 96), (32_800, 64, 65),
+                                     (15_201, 256, 257), (1500, 1000, 700)])
 @pytest.mark.parametrize("lo,hi", [(-30, 30), (0, 0)])
 def test_split_products_match_fp64(ctx, V, di, dn, lo, hi):
     gen = torch.Generator().manual_seed(V)
