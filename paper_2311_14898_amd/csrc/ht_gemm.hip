@@ -306,7 +306,8 @@ __global__ void __launch_bounds__(256) k_gemm_tn(const float* __restrict__ A, in
 // instead of 2.87 at 2.45 M rows, 256 x 256; with one sum, 2.47 and 2.54 ms, the matrix cores' rounding of small addends is
 // felt: single products off by up to 2^-23, and sums over rows that a ReLU has masked 15 % further off than in fp32.)
 // Values that are not finite, or whose scaled products are not (beyond about 2^80), would leave NaN where an fp32 product has an
-// infinity or a number: a block whose tile holds anything but finite numbers computes it again in fp32, element by element.
+// infinity or a number: a block whose tile holds anything but finite numbers computes it again on the fp32 matrix cores.  (233 k rows, 602 x 256:
+// 0.8 ms; 1.4 with one NaN in A, 2.0 with whole columns of them: element by element they took 16 and 46.)
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 constexpr int SK = 32;                       // reduction depth of one LDS stage: two steps of 16
 constexpr int SB = BM * 16;                  // bf16 per [128 rows][16] block of a stage [plane][step]
@@ -373,7 +374,50 @@ struct SplitTile {
         for (int e = 0; e < 16; ++e) ok = ok && fabsf(acc[i][j][e]) < INFINITY;
     return ok;
   }
+  __device__ __forceinline__ void unscale() {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] *= SPLIT_UNSCALE;
+  }
+  // The tile again on the fp32 matrix cores: a(row, k) and b(column, k) for k in [k0, k1), 0 outside the operands.  As, Bs: [BK][BM + 4]
+  template <class FA, class FB>
+  __device__ __forceinline__ void in_fp32(float* As, float* Bs, int64_t k0, int64_t k1, int wm, int wn, int l32, int half, FA a, FB b) {
+    constexpr int P = BM + 4;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    const int c = threadIdx.x & (BM - 1), h = threadIdx.x >> 7;
+    for (int64_t k = k0; k < k1; k += BK) {
+#pragma unroll 1
+      for (int u = h; u < BK; u += 2) {
+        As[u * P + c] = k + u < k1 ? a(c, k + u) : 0.f;
+        Bs[u * P + c] = k + u < k1 ? b(c, k + u) : 0.f;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int kk = 0; kk < BK; kk += 2) {
+        float af[2], bf[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          af[i] = As[(kk + half) * P + wm * 64 + i * 32 + l32];
+          bf[i] = Bs[(kk + half) * P + wn * 64 + i * 32 + l32];
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i], bf[j], acc[i][j], 0, 0, 0);
+      }
+      __syncthreads();
+    }
+  }
 };
+static_assert(BK * (BM + 4) * sizeof(float) <= 6 * SB * sizeof(__bf16), "the fp32 stages fit where the split ones were");
 
 // Partial tile of C[K x N] = A^T B over a slice of rows, as k_gemm_tn
 __global__ void __launch_bounds__(256, 2) k_split_tn(const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
@@ -437,7 +481,12 @@ __global__ void __launch_bounds__(256, 2) k_split_tn(const float* __restrict__ A
     __syncthreads();
   }
   t.join();
-  const bool again = __syncthreads_or(!t.all_finite());
+  if (__syncthreads_or(!t.all_finite()))
+    t.in_fp32(reinterpret_cast<float*>(As), reinterpret_cast<float*>(Bs), ms, me, wm, wn, l32, half,
+              [&](int r, int64_t m) { return kc0 + r < K ? A[m * lda + kc0 + r] : 0.f; },
+              [&](int q, int64_t m) { return n0 + q < N ? B[m * ldb + n0 + q] : 0.f; });
+  else
+    t.unscale();
   float* Ps = P + (int64_t)blockIdx.z * K * N;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -448,13 +497,7 @@ __global__ void __launch_bounds__(256, 2) k_split_tn(const float* __restrict__ A
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int gr = kc0 + wm * 64 + i * 32 + (e >> 2) * 8 + half * 4 + (e & 3);
-        if (gr >= K) continue;
-        float v = t.acc[i][j][e] * SPLIT_UNSCALE;
-        if (again) {
-          v = 0.f;
-          for (int64_t m = ms; m < me; ++m) v = fmaf(A[m * lda + gr], B[m * ldb + gc], v);
-        }
-        Ps[(int64_t)gr * N + gc] = v;
+        if (gr < K) Ps[(int64_t)gr * N + gc] = t.acc[i][j][e];
       }
     }
 }

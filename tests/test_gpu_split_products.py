@@ -49,21 +49,26 @@ def test_split_products_match_fp64(ctx, V, di, dn, lo, hi):
 
 
 @gpu
-def test_split_products_not_finite(ctx):
-    V, di, dn = 8500, 70, 100
+@pytest.mark.parametrize("V", [8500, 33_000])
+def test_split_products_not_finite(ctx, V):
+    di, dn = 70, 100
     gen = torch.Generator().manual_seed(1)
     X, W, dH = torch.randn(V, di, generator=gen), torch.randn(di, dn, generator=gen), torch.randn(V, dn, generator=gen)
     X[200, 69], X[8499, 0], X[400, 7] = 3.4e38, float("nan"), -3.4e38       # (3.4e38 rounds to infinity as bf16)
+    X[300, 5], dH[300, 6] = 2.0 ** 60, 2.0 ** 30                            # (finite in fp32, not in the splits' scale)
     W[7], W[69] = W[7] * 1e-3, W[69] * 1e-3                                 # (and its products stay finite)
     dH[130, 99], dH[131, 98] = float("inf"), float("-inf")
     H, dW, dX = _run(ctx, X, W, dH)
     keep = torch.ones(V, dtype=torch.bool)
     keep[[130, 131]] = False                                                # (the aggregation behind dX turns infinities into NaN)
-    for got, want in ((H, X @ W), (dW, X.t() @ dH), (dX[keep], (dH @ W.t())[keep])):
+    for got, a, b in ((H, X, W), (dW, X.t(), dH), (dX[keep], dH[keep], W.t())):
+        exact, size = a.double() @ b.double(), a.double().abs() @ b.double().abs()
+        want = a @ b                                                        # (fp32: infinities and NaN where its partial sums leave the range)
         nan, ok = torch.isnan(want), torch.isfinite(want)
         assert torch.equal(torch.isnan(got), nan) and torch.equal(torch.isfinite(got), ok)
         assert torch.equal(got[~ok & ~nan], want[~ok & ~nan])
-        assert ((got[ok] - want[ok]).abs() <= 1e-4 * want[ok].abs() + 1e-3).float().mean() > 0.999
+        # the bound of the finite sums above, for every element
+        assert ((got.double() - exact).abs()[ok] <= (8 * a.shape[1] ** 0.5 * 2.0 ** -24 * size)[ok]).all()
 
 
 # One product per output element: an fp32 product is off by at most 2^-24 of it, and so is the split one up to what its smaller
