@@ -122,7 +122,8 @@ __global__ void __launch_bounds__(256) k_gat_scores(const WorkItem* __restrict__
   const int64_t t = (int64_t)blockIdx.x * 4 + wave;
   if (t >= n_items) return;
   const WorkItem it = items[t];
-  const int32_t r = it.row, len = it.len, part = it.part;
+  const uint32_t r = it.row;
+  const int32_t len = it.len, part = it.part;
   const int64_t e0 = it.e0;
   w -= ent0;
   const float pv = p[r];
@@ -205,7 +206,8 @@ __global__ void __launch_bounds__(256) k_gat_agg(GatAgg a, int S, int nvs, int e
   const int nv_here = (nvec - v0) < nvs ? (nvec - v0) : nvs;
   if (nv_here <= 0) return;
   const WorkItem it = a.items[t];
-  const int32_t row = it.row, len = it.len;
+  const uint32_t row = it.row;
+  const int32_t len = it.len;
   const int64_t e0 = it.e0;
   const int es = lane / nvs, vec = lane - es * nvs;
   const bool active = es < eps && vec < nv_here;
@@ -409,10 +411,10 @@ __global__ void __launch_bounds__(256) k_gat_src(GatPass a) {
   const int64_t t = (int64_t)blockIdx.x * 4 + wave;
   if (t >= a.n_items) return;
   const WorkItem it = a.items[t];
-  const int32_t r = it.row;
+  const uint32_t r = it.row;
   const int64_t e0 = it.e0;
   const int32_t len = it.len, part = it.part;
-  const int32_t u_id = a.own_idx ? a.own_idx[r] : r;
+  const int32_t u_id = a.own_idx ? a.own_idx[r] : (int32_t)r;
   float4 acc[VPL], G[VPL];
 #pragma unroll
   for (int j = 0; j < VPL; ++j) acc[j] = G[j] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -496,10 +498,10 @@ __global__ void __launch_bounds__(256) k_gat_src_g(GatPass a) {
   const int64_t t = (int64_t)blockIdx.x * 4 + wave;
   if (t >= a.n_items) return;
   const WorkItem it = a.items[t];
-  const int32_t r = it.row;
+  const uint32_t r = it.row;
   const int64_t e0 = it.e0;
   const int32_t len = it.len, part = it.part;
-  const int32_t u_id = a.own_idx ? a.own_idx[r] : r;
+  const int32_t u_id = a.own_idx ? a.own_idx[r] : (int32_t)r;
   const int grp = lane / G_, c4 = (lane % G_) * 4;
   const bool has = c4 < a.d;
   const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);

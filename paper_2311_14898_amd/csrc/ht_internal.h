@@ -200,13 +200,14 @@ int ht_bitmap_prefix(ht_ctx* ctx, const uint64_t* bm, int64_t nw, int32_t* cnt_t
 // positions of the N arena (backward); rows, entries and partial sums are numbered over the whole graph, and a chunk's
 // items are a contiguous range of the list, so a launch can take one chunk or all of them.
 struct __attribute__((aligned(16))) WorkItem {
-  int32_t row;
+  uint32_t row;    // (positions of the N arena: up to 2^32 of them)
   uint32_t e0;     // first entry (stored edges, or distinct pairs when duplicates are merged)
   int32_t len;     // entries (<= HT_SEG)
   int32_t part;    // -1: the row's only item; else index of its partial sum
 };
 struct __attribute__((aligned(16))) CutRow {   // a row with several items
-  int32_t row, part0, nseg, pad;
+  uint32_t row;
+  int32_t part0, nseg, pad;
 };
 struct GraphItems {
   DevArr<WorkItem> items;

@@ -776,7 +776,7 @@ __global__ void __launch_bounds__(TB) k_items_fill(RowSet R, int64_t nrows, int 
       for (int64_t j = 0; j < (int64_t)m; ++j) {
         const int64_t b = e0 + j * seg, rem = len - j * seg;
         WorkItem w;
-        w.row = (int32_t)r;
+        w.row = (uint32_t)r;
         w.e0 = (uint32_t)b;
         w.len = (int32_t)(rem < seg ? rem : seg);
         w.part = is_cut ? (int32_t)(p0 + j) : -1;
@@ -788,7 +788,7 @@ __global__ void __launch_bounds__(TB) k_items_fill(RowSet R, int64_t nrows, int 
       }
       if (is_cut) {
         CutRow c;
-        c.row = (int32_t)r;
+        c.row = (uint32_t)r;
         c.part0 = (int32_t)p0;
         c.nseg = (int32_t)m;
         c.pad = 0;

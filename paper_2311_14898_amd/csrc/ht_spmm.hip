@@ -27,7 +27,7 @@ __device__ __forceinline__ float4 shfl_xor4(float4 v, int o) {
 }
 
 // Final write of one output row's float4 column `c4` (in floats).
-__device__ __forceinline__ void write_out(const SpmmArgs& a, int32_t r, int c4, float4 v) {
+__device__ __forceinline__ void write_out(const SpmmArgs& a, uint32_t r, int c4, float4 v) {
   const float post = a.post ? a.post[a.post_idx ? a.post_idx[r] : r] : 1.f;
   uint32_t orow = a.out_idx ? (uint32_t)a.out_idx[r] : (uint32_t)(r - a.row0);
   const bool fresh = (orow & 0x80000000u) != 0u;
@@ -46,7 +46,7 @@ __global__ void __launch_bounds__(256) k_spmm_items(SpmmArgs a) {
   const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= a.n_items) return;
   const WorkItem it = a.items[t];
-  const int32_t r = it.row;
+  const uint32_t r = it.row;
   const int64_t e0 = it.e0;
   const int32_t len = it.len;
   const int32_t part = it.part;
@@ -112,7 +112,7 @@ __global__ void __launch_bounds__(256) k_spmm_fix(SpmmArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t f = blockIdx.x;
   const CutRow cut = a.cuts[f];
-  const int32_t r = cut.row;
+  const uint32_t r = cut.row;
   const int64_t p0 = cut.part0 - a.part0;
   const int32_t ns = cut.nseg;
   const int d4 = (a.d + 3) & ~3;
@@ -166,7 +166,7 @@ __global__ void __launch_bounds__(256) k_spmm_slab(SpmmArgs a, int S, int nvs, i
   const int nv_here = (nvec - v0) < nvs ? (nvec - v0) : nvs;
   if (nv_here <= 0) return;
   const WorkItem it = a.items[t];
-  const int32_t r = it.row;
+  const uint32_t r = it.row;
   const int64_t e0 = it.e0;
   const int32_t len = it.len;
   const int32_t part = it.part;

@@ -319,3 +319,37 @@ def test_layer_with_more_items_than_a_launch_holds():
     finally:
         B.ht_graph_destroy(g)
         B.ht_ctx_destroy(ctx)
+
+
+def test_chunk_pass_with_more_than_2_31_chunk_sources():
+    """129 chunks that all name each of 2^24 sources: 2^31 + 2^24 (chunk, source) pairs, so positions in the arena of neighbour
+    lists need 32 bits.  The backward pass through the gradient buffer finds every row's vertex and buffer position by them."""
+    if torch.cuda.mem_get_info()[0] < 240e9:
+        pytest.skip("needs a GPU with 240 GB of free memory")
+    V, k, d = 1 << 24, 129, 4
+    E = V * k
+    src, dst = torch.empty(E, dtype=torch.int32, device="cuda"), torch.empty(E, dtype=torch.int32, device="cuda")
+    for e0 in range(0, E, V):                          # edge e: e mod V -> e / k; a chunk holds V edges in a row, all sources once
+        e = torch.arange(e0, e0 + V, device="cuda")
+        src[e0:e0 + V], dst[e0:e0 + V] = e % V, torch.div(e, k, rounding_mode="floor")
+    ctx = B.ht_ctx_create(0)
+    g = B.ht_partition(ctx, V, src, dst, k, add_self_loops=False)
+    try:
+        del src, dst, e
+        assert B.ht_graph_info_get(g).v_ori >= 1 << 31
+        gen = torch.Generator("cuda").manual_seed(6)
+        A, dH = (torch.empty((V, d), device="cuda").uniform_(-1, 1, generator=gen) for _ in range(2))
+        W = inputs.glorot_weights([d, d])[0].cuda()
+        dX, dW = torch.zeros((V, d), device="cuda"), torch.empty_like(W)
+        B.ht_layer_bwd(ctx, g, d, d, B.HT_ACT_NONE, A, W, dH, dW, dH_in=dX, ckpt_kind=B.HT_CKPT_AGG, gather_mode=B.HT_GATHER_BUFFER)
+        B.ht_sync(ctx)
+        da = dH.double() @ W.double().t()
+        want = torch.zeros_like(da)
+        u = torch.arange(V, device="cuda")
+        for j in range(k):                             # every vertex has k in-edges: both factors of the normalisation are k^-1/2
+            want += da[torch.div(u + j * V, k, rounding_mode="floor")] / k
+        # k products of values below 2 / k, rounded twice each and once more per addition
+        assert float((dX.double() - want).abs().max()) <= (k + 4) * 2.0 ** -24 * 2
+    finally:
+        B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)
