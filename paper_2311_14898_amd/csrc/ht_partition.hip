@@ -28,6 +28,9 @@ constexpr int TB = 256;
 constexpr int ETILE = 2048;      // entries of a sorted list one block handles
 constexpr int RTILE = 1024;      // rows one block cuts into work items
 inline unsigned nblk(int64_t n, int tb = TB) { return (unsigned)((n + tb - 1) / tb); }
+// Blocks per launch of the kernels that take a block per tile of every chunk's bitmap: n V / 64 threads in all, and a launch of
+// 2^32 threads or more silently drops its excess (from n V = 2^38 on: 268 M vertices in 1,024 chunks).
+constexpr int64_t TILE_LAUNCH = HT_LAUNCH_WAVES * 64 / TB;
 
 // ---- block-level helpers
 
@@ -293,11 +296,12 @@ int mark_chunks(ht_ctx* ctx, hipStream_t st, const int32_t* col, const int64_t* 
 }
 
 // base[t] = set bits before tile t: every word's prefix and the list of set bits (vertex ids, rows behind each other)
+// (tile0: the launch's first tile)
 __global__ void __launch_bounds__(TB) k_expand_rows(const uint64_t* __restrict__ bm, int64_t nwp, const int64_t* __restrict__ base,
-                                                    uint32_t* __restrict__ wpref, int32_t* __restrict__ out) {
-  const int64_t w = (int64_t)blockIdx.x * TB + threadIdx.x;
+                                                    uint32_t* __restrict__ wpref, int32_t* __restrict__ out, int64_t tile0) {
+  const int64_t tile = tile0 + blockIdx.x, w = tile * TB + threadIdx.x;
   uint64_t bits = bm[w], tot;
-  int64_t p = base[blockIdx.x] + (int64_t)block_excl((uint64_t)__popcll(bits), &tot);
+  int64_t p = base[tile] + (int64_t)block_excl((uint64_t)__popcll(bits), &tot);
   if (wpref) wpref[w] = (uint32_t)p;
   const int32_t u0 = (int32_t)((w % nwp) * 64);
   while (bits) {
@@ -335,13 +339,13 @@ struct ListRows {
 };
 
 // cnt[0 / 1 / 2][j, tile]: members of a tile of the reuse / load / leave words of position j
-__global__ void __launch_bounds__(TB) k_list_counts(ListRows R, int64_t tiles, int32_t* __restrict__ cnt) {
-  const int64_t j = blockIdx.x / tiles, t = blockIdx.x % tiles;
+__global__ void __launch_bounds__(TB) k_list_counts(ListRows R, int64_t tiles, int32_t* __restrict__ cnt, int64_t tile0) {
+  const int64_t tile = tile0 + blockIdx.x, j = tile / tiles, t = tile % tiles;
   uint64_t a, b, c, tot;
   R.words((int)j, t * TB + threadIdx.x, &a, &b, &c);
   // three counts of at most 2^14 each travel in one sum
   block_excl((uint64_t)__popcll(a) | ((uint64_t)__popcll(b) << 20) | ((uint64_t)__popcll(c) << 40), &tot);
-  if (threadIdx.x < 3) cnt[(int64_t)threadIdx.x * R.n * tiles + blockIdx.x] = (int32_t)((tot >> (20 * threadIdx.x)) & 0xFFFFF);
+  if (threadIdx.x < 3) cnt[(int64_t)threadIdx.x * R.n * tiles + tile] = (int32_t)((tot >> (20 * threadIdx.x)) & 0xFFFFF);
 }
 
 __device__ __forceinline__ void put_bits(uint64_t bits, int32_t u0, int32_t* __restrict__ out) {
@@ -354,15 +358,15 @@ __device__ __forceinline__ void put_bits(uint64_t bits, int32_t u0, int32_t* __r
 // the three lists, positions behind each other; base: exclusive prefix over cnt
 __global__ void __launch_bounds__(TB) k_list_expand(ListRows R, int64_t tiles, const int64_t* __restrict__ base,
                                                     int32_t* __restrict__ reuse, int32_t* __restrict__ load,
-                                                    int32_t* __restrict__ leave) {
-  const int64_t j = blockIdx.x / tiles, t = blockIdx.x % tiles, nt = (int64_t)R.n * tiles;
+                                                    int32_t* __restrict__ leave, int64_t tile0) {
+  const int64_t tile = tile0 + blockIdx.x, j = tile / tiles, t = tile % tiles, nt = (int64_t)R.n * tiles;
   uint64_t a, b, c, tot;
   R.words((int)j, t * TB + threadIdx.x, &a, &b, &c);
   const uint64_t off = block_excl((uint64_t)__popcll(a) | ((uint64_t)__popcll(b) << 20) | ((uint64_t)__popcll(c) << 40), &tot);
   const int32_t u0 = (int32_t)((t * TB + threadIdx.x) * 64);
-  put_bits(a, u0, reuse + base[blockIdx.x] + (int64_t)(off & 0xFFFFF));
-  put_bits(b, u0, load + (base[nt + blockIdx.x] - base[nt]) + (int64_t)((off >> 20) & 0xFFFFF));
-  put_bits(c, u0, leave + (base[2 * nt + blockIdx.x] - base[2 * nt]) + (int64_t)((off >> 40) & 0xFFFFF));
+  put_bits(a, u0, reuse + base[tile] + (int64_t)(off & 0xFFFFF));
+  put_bits(b, u0, load + (base[nt + tile] - base[nt]) + (int64_t)((off >> 20) & 0xFFFFF));
+  put_bits(c, u0, leave + (base[2 * nt + tile] - base[2 * nt]) + (int64_t)((off >> 40) & 0xFFFFF));
 }
 
 // Sum of up to three per-thread counts over the grid into totals[0..2]: waves by shuffles, the block's four waves
@@ -1114,8 +1118,11 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
   // ---- reuse / load / leave lists: counted here for the adjacent rule; the schedule-aware buffer is simulated first
   ListRows rows{allbm.p, d_order.p, nullptr, nullptr, nwp, n};
   auto count_lists = [&]() -> int {
-    k_list_counts<<<(unsigned)(n * T), TB, 0, st>>>(rows, T, list_cnt.p);
-    HT_LAUNCH_CHECK(ctx);
+    HT_TRY(ht_in_launches((int64_t)n * T, TILE_LAUNCH, [&](int64_t t, int64_t m) {
+      k_list_counts<<<(unsigned)m, TB, 0, st>>>(rows, T, list_cnt.p, t);
+      HT_LAUNCH_CHECK(ctx);
+      return (int)HT_OK;
+    }));
     HT_TRY(ht_scan_i32(ctx, list_cnt.p, lbase.p, (int64_t)3 * n * T, true));
     for (int w = 0; w < 3; ++w) {
       k_gather_stride<<<nblk((int64_t)n1), TB, 0, st>>>(lbase.p + (int64_t)w * n * T, T, (int64_t)n1, list(L_REUSE + w));
@@ -1188,8 +1195,11 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
                       (long long)g->max_nsrc);
   const size_t vo = (size_t)std::max<int64_t>(g->v_ori, 1);
   HT_TRY(g->nbr.alloc(ctx, vo));
-  k_expand_rows<<<(unsigned)(n * T), TB, 0, st>>>(allbm.p, nwp, tbase.p, wpref.p, g->nbr.p);
-  HT_LAUNCH_CHECK(ctx);
+  HT_TRY(ht_in_launches((int64_t)n * T, TILE_LAUNCH, [&](int64_t t, int64_t m) {
+    k_expand_rows<<<(unsigned)m, TB, 0, st>>>(allbm.p, nwp, tbase.p, wpref.p, g->nbr.p, t);
+    HT_LAUNCH_CHECK(ctx);
+    return (int)HT_OK;
+  }));
 
   // ---- schedule of a buffer that knows the future: a row leaves after its last use, or for room with the farthest next
   // use first.  Simulated chunk by chunk on bitmaps; kept for the lists: the rows resident before every chunk (Pbm), the
@@ -1383,8 +1393,11 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
   HT_HIP(ctx, hipMemcpyAsync(g->d_dense_groups.p, g->dense_groups.data(), g->dense_groups.size() * 8, hipMemcpyHostToDevice, st));
 
   // ---- the lists, then the buffer positions, chunk by chunk
-  k_list_expand<<<(unsigned)(n * T), TB, 0, st>>>(rows, T, lbase.p, g->reuse.p, g->load.p, g->leave.p);
-  HT_LAUNCH_CHECK(ctx);
+  HT_TRY(ht_in_launches((int64_t)n * T, TILE_LAUNCH, [&](int64_t t, int64_t m) {
+    k_list_expand<<<(unsigned)m, TB, 0, st>>>(rows, T, lbase.p, g->reuse.p, g->load.p, g->leave.p, t);
+    HT_LAUNCH_CHECK(ctx);
+    return (int)HT_OK;
+  }));
   uint64_t* free_now = freebm.p;
   uint64_t* free_next = freebm.p + nwC;
   k_free_init<<<nblk(nwC), TB, 0, st>>>(free_now, nwC, C);

@@ -353,3 +353,31 @@ def test_chunk_pass_with_more_than_2_31_chunk_sources():
     finally:
         B.ht_graph_destroy(g)
         B.ht_ctx_destroy(ctx)
+
+
+def test_partition_with_more_bitmap_words_than_a_launch_holds():
+    """2^30 vertices in 257 chunks: a thread per word of every chunk's neighbour bitmap would be more than a launch holds.  Edges
+    v -> v + 1 alone, so that every list is known: chunk j's sources are its destinations and the one before, which the chunk
+    before it also reads."""
+    if torch.cuda.mem_get_info()[0] < 200e9:
+        pytest.skip("needs a GPU with 200 GB of free memory")
+    V, n = 1 << 30, 257
+    src = torch.arange(V - 1, dtype=torch.int32, device="cuda")
+    ctx = B.ht_ctx_create(0)
+    g = B.ht_partition(ctx, V, src, src + 1, n, balance_mode=B.HT_BALANCE_VERTICES, reorder_chunks=True)
+    try:
+        del src
+        info = B.ht_graph_info_get(g)
+        assert info.v_ori == V + n - 1 and info.v_ru == info.v_load == V
+        assert np.array_equal(B.ht_graph_chunk_order(g), np.arange(n))
+        for j in (0, 1, 128, n - 1):                      # (the last chunk's words lie beyond 2^32 threads)
+            ch = B.ht_graph_export_chunk(g, j)
+            b0, b1 = j * V // n, (j + 1) * V // n
+            first = max(b0 - 1, 0)
+            assert np.array_equal(ch["nbr"], np.arange(first, b1)), j
+            assert np.array_equal(ch["reuse"], np.arange(first, b0)) and np.array_equal(ch["load"], np.arange(b0, b1)), j
+            assert np.array_equal(ch["leave"], np.arange(first, b1 - 1 if j < n - 1 else b1)), j
+            assert np.array_equal(ch["nbr"][ch["col_local"]], ch["col"]), j
+    finally:
+        B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)
