@@ -279,10 +279,10 @@ inline int64_t bm_words(int64_t V) { return ceil_div64(ceil_div64(V, 64), TB) * 
 inline int64_t mark_group(int64_t nwp, int32_t n) { return std::max<int64_t>(1, std::min<int64_t>(n, SEEN_BYTES / (nwp * 64))); }
 
 // The neighbour bitmaps of all n chunks (chunk k: entries eoff[k] .. eoff[k + 1] of col) and the set bits of each of
-// their tiles; seen: mark_group() rows of nwp * 64 zero bytes.
+// their tiles; seen: grp rows of nwp * 64 zero bytes.
 int mark_chunks(ht_ctx* ctx, hipStream_t st, const int32_t* col, const int64_t* h_eoff, const int64_t* d_eoff, int32_t n,
-                int64_t nwp, uint8_t* seen, uint64_t* bm, int32_t* tile_cnt) {
-  const int64_t grp = mark_group(nwp, n), tiles = nwp / TB;
+                int64_t nwp, int64_t grp, uint8_t* seen, uint64_t* bm, int32_t* tile_cnt) {
+  const int64_t tiles = nwp / TB;
   for (int64_t k0 = 0; k0 < n; k0 += grp) {
     const int64_t k1 = std::min<int64_t>(n, k0 + grp), cnt = h_eoff[k1] - h_eoff[k0];
     if (cnt > 0) {
@@ -295,13 +295,26 @@ int mark_chunks(ht_ctx* ctx, hipStream_t st, const int32_t* col, const int64_t* 
   return HT_OK;
 }
 
-// base[t] = set bits before tile t: every word's prefix and the list of set bits (vertex ids, rows behind each other)
+// ... and of chunk k alone
+int mark_chunk(ht_ctx* ctx, hipStream_t st, const int32_t* col, const int64_t* h_eoff, const int64_t* d_eoff, int32_t n, int k,
+               int64_t nwp, uint8_t* seen, uint64_t* bm, int32_t* tile_cnt) {
+  const int64_t cnt = h_eoff[k + 1] - h_eoff[k];
+  if (cnt > 0) {
+    k_mark_bytes<<<nblk(cnt, ETILE), TB, 0, st>>>(col, h_eoff[k], cnt, d_eoff, n, k, seen, nwp * 64);
+    HT_LAUNCH_CHECK(ctx);
+  }
+  k_pack_seen<<<(unsigned)(nwp / TB), TB, 0, st>>>(seen, bm, tile_cnt);
+  HT_LAUNCH_CHECK(ctx);
+  return HT_OK;
+}
+
+// p0 + base[t] = set bits before tile t: every word's prefix and the list of set bits (vertex ids, rows behind each other)
 // (tile0: the launch's first tile)
 __global__ void __launch_bounds__(TB) k_expand_rows(const uint64_t* __restrict__ bm, int64_t nwp, const int64_t* __restrict__ base,
-                                                    uint32_t* __restrict__ wpref, int32_t* __restrict__ out, int64_t tile0) {
+                                                    uint32_t* __restrict__ wpref, int32_t* __restrict__ out, int64_t tile0, int64_t p0) {
   const int64_t tile = tile0 + blockIdx.x, w = tile * TB + threadIdx.x;
   uint64_t bits = bm[w], tot;
-  int64_t p = base[tile] + (int64_t)block_excl((uint64_t)__popcll(bits), &tot);
+  int64_t p = p0 + base[tile] + (int64_t)block_excl((uint64_t)__popcll(bits), &tot);
   if (wpref) wpref[w] = (uint32_t)p;
   const int32_t u0 = (int32_t)((w % nwp) * 64);
   while (bits) {
@@ -316,21 +329,23 @@ __global__ void __launch_bounds__(TB) k_expand_rows(const uint64_t* __restrict__
 // those of its neighbours in the schedule; a schedule-aware buffer brings the rows that are resident before chunk j
 // (pbm row j, released rows taken out) and the rows that leave after it (ebm row j + 1).
 struct ListRows {
-  const uint64_t* bm;      // neighbour bitmaps, row = chunk id
-  const int32_t* order;    // schedule position -> chunk id
-  const uint64_t* pbm;     // nullable: adjacent reuse
+  const uint64_t* bm;      // neighbour bitmaps, row = chunk id (or position mod 3)
+  const int32_t* order;    // schedule position -> chunk id; nullable: bm holds the rows of positions j0 - 1, j0 and j0 + 1 alone
+  const uint64_t* pbm;     // row = position from j0 on; nullable: adjacent reuse
   const uint64_t* ebm;
   int64_t nwp;
   int32_t n;
+  int32_t j0, nj;          // the launch's positions
+  __device__ __forceinline__ uint64_t word(int j, int64_t w) const { return bm[(int64_t)(order ? order[j] : j % 3) * nwp + w]; }
   __device__ __forceinline__ void words(int j, int64_t w, uint64_t* reuse, uint64_t* load, uint64_t* leave) const {
-    const uint64_t cur = bm[(int64_t)order[j] * nwp + w];
+    const uint64_t cur = word(j, w);
     uint64_t prev, out;
     if (pbm) {
-      prev = pbm[(int64_t)j * nwp + w];
+      prev = pbm[(int64_t)(j - j0) * nwp + w];
       out = ebm[(int64_t)(j + 1) * nwp + w];
     } else {
-      prev = j > 0 ? bm[(int64_t)order[j - 1] * nwp + w] : 0ull;
-      out = j + 1 < n ? (cur & ~bm[(int64_t)order[j + 1] * nwp + w]) : cur;
+      prev = j > 0 ? word(j - 1, w) : 0ull;
+      out = j + 1 < n ? (cur & ~word(j + 1, w)) : cur;
     }
     *reuse = cur & prev;
     *load = cur & ~prev;
@@ -338,14 +353,14 @@ struct ListRows {
   }
 };
 
-// cnt[0 / 1 / 2][j, tile]: members of a tile of the reuse / load / leave words of position j
+// cnt[0 / 1 / 2][j, tile]: members of a tile of the reuse / load / leave words of position j0 + j
 __global__ void __launch_bounds__(TB) k_list_counts(ListRows R, int64_t tiles, int32_t* __restrict__ cnt, int64_t tile0) {
   const int64_t tile = tile0 + blockIdx.x, j = tile / tiles, t = tile % tiles;
   uint64_t a, b, c, tot;
-  R.words((int)j, t * TB + threadIdx.x, &a, &b, &c);
+  R.words(R.j0 + (int)j, t * TB + threadIdx.x, &a, &b, &c);
   // three counts of at most 2^14 each travel in one sum
   block_excl((uint64_t)__popcll(a) | ((uint64_t)__popcll(b) << 20) | ((uint64_t)__popcll(c) << 40), &tot);
-  if (threadIdx.x < 3) cnt[(int64_t)threadIdx.x * R.n * tiles + tile] = (int32_t)((tot >> (20 * threadIdx.x)) & 0xFFFFF);
+  if (threadIdx.x < 3) cnt[(int64_t)threadIdx.x * R.nj * tiles + tile] = (int32_t)((tot >> (20 * threadIdx.x)) & 0xFFFFF);
 }
 
 __device__ __forceinline__ void put_bits(uint64_t bits, int32_t u0, int32_t* __restrict__ out) {
@@ -359,14 +374,20 @@ __device__ __forceinline__ void put_bits(uint64_t bits, int32_t u0, int32_t* __r
 __global__ void __launch_bounds__(TB) k_list_expand(ListRows R, int64_t tiles, const int64_t* __restrict__ base,
                                                     int32_t* __restrict__ reuse, int32_t* __restrict__ load,
                                                     int32_t* __restrict__ leave, int64_t tile0) {
-  const int64_t tile = tile0 + blockIdx.x, j = tile / tiles, t = tile % tiles, nt = (int64_t)R.n * tiles;
+  const int64_t tile = tile0 + blockIdx.x, j = tile / tiles, t = tile % tiles, nt = (int64_t)R.nj * tiles;
   uint64_t a, b, c, tot;
-  R.words((int)j, t * TB + threadIdx.x, &a, &b, &c);
+  R.words(R.j0 + (int)j, t * TB + threadIdx.x, &a, &b, &c);
   const uint64_t off = block_excl((uint64_t)__popcll(a) | ((uint64_t)__popcll(b) << 20) | ((uint64_t)__popcll(c) << 40), &tot);
   const int32_t u0 = (int32_t)((t * TB + threadIdx.x) * 64);
   put_bits(a, u0, reuse + base[tile] + (int64_t)(off & 0xFFFFF));
   put_bits(b, u0, load + (base[nt + tile] - base[nt]) + (int64_t)((off >> 20) & 0xFFFFF));
   put_bits(c, u0, leave + (base[2 * nt + tile] - base[2 * nt]) + (int64_t)((off >> 40) & 0xFFFFF));
+}
+
+// out[0 .. 3]: members of one chunk's N, reuse, load and leave lists, from the prefix sums over their tiles
+__global__ void k_put_counts(const int64_t* __restrict__ tbase, const int64_t* __restrict__ lbase, int64_t tiles, int64_t* __restrict__ out) {
+  const int w = threadIdx.x;
+  if (w < 4) out[w] = w == 0 ? tbase[tiles] : lbase[w * tiles] - lbase[(w - 1) * tiles];
 }
 
 // Sum of up to three per-thread counts over the grid into totals[0..2]: waves by shuffles, the block's four waves
@@ -592,25 +613,25 @@ __global__ void k_lookup_evict(const int32_t* __restrict__ nbr, int64_t nsrc, co
 
 // ---- topology in local indices
 
-// For every edge in CSC order: the position of its source in N_k, its buffer position, and the sort key
+// For the edges [e0, e1) in CSC order (bm, wpref: from chunk k0's row on): the position of its source in N_k, its buffer position, and the sort key
 // (position of (k, source) in the N arena, local destination) of the by-source grouping.
-__global__ void __launch_bounds__(TB) k_remap(const uint64_t* __restrict__ csc_keys, int64_t n_edges, int bitsV,
+__global__ void __launch_bounds__(TB) k_remap(const uint64_t* __restrict__ csc_keys, int64_t e0, int64_t e1, int k0, int bitsV,
                                               const int64_t* __restrict__ eoff, const int64_t* __restrict__ bounds,
                                               const int64_t* __restrict__ noff, int n, const uint64_t* __restrict__ bm,
                                               int64_t nwp, const uint32_t* __restrict__ wpref, const int32_t* __restrict__ slot,
                                               int32_t* __restrict__ col_local, int32_t* __restrict__ col_slot,
                                               uint64_t* __restrict__ keys) {
-  int k = find_range(eoff, n, (int64_t)blockIdx.x * ETILE);
+  int k = find_range(eoff, n, e0 + (int64_t)blockIdx.x * ETILE);
   int64_t end = eoff[k + 1];
   const uint64_t mask = ((uint64_t)1 << bitsV) - 1;
 #pragma unroll
   for (int r = 0; r < ETILE / TB; ++r) {
-    const int64_t e = (int64_t)blockIdx.x * ETILE + r * TB + threadIdx.x;
-    if (e >= n_edges) break;
+    const int64_t e = e0 + (int64_t)blockIdx.x * ETILE + r * TB + threadIdx.x;
+    if (e >= e1) break;
     while (e >= end) end = eoff[++k + 1];
     const uint64_t key = csc_keys[e];
     const uint32_t u = (uint32_t)(key & mask);
-    const int64_t w = (int64_t)k * nwp + (u >> 6);
+    const int64_t w = (int64_t)(k - k0) * nwp + (u >> 6);
     const uint64_t below = (u & 63) ? (bm[w] & (~0ull >> (64 - (u & 63)))) : 0ull;
     const uint32_t p = wpref[w] + (uint32_t)__popcll(below);
     col_local[e] = (int32_t)((int64_t)p - noff[k]);
@@ -805,9 +826,10 @@ __global__ void __launch_bounds__(TB) k_items_fill(RowSet R, int64_t nrows, int 
   }
 }
 
-__global__ void k_items_permute(const uint64_t* __restrict__ keys, int64_t n, const WorkItem* __restrict__ in, WorkItem* __restrict__ out) {
+// (in: from item i0 on)
+__global__ void k_items_permute(const uint64_t* __restrict__ keys, int64_t n, const WorkItem* __restrict__ in, uint32_t i0, WorkItem* __restrict__ out) {
   int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < n) out[t] = in[(uint32_t)(keys[t] & 0xFFFFFFFFull)];
+  if (t < n) out[t] = in[(uint32_t)(keys[t] & 0xFFFFFFFFull) - i0];
 }
 
 // ---- entries of the whole graph grouped by source
@@ -867,6 +889,7 @@ struct ItemBuild {
   int64_t nrows = 0, tiles = 0;
   int64_t range = 0;           // values of the entries' row index are below this
   int seg = 0;
+  const int64_t* h_first = nullptr;   // host copy of rows.first
   const int32_t* idx = nullptr;
   int32_t* cnt = nullptr;      // [3 * tiles]
   int64_t* base = nullptr;     // [3 * tiles + 1]
@@ -889,9 +912,10 @@ int count_items(ht_ctx* ctx, const ItemBuild& b, int64_t* h_tot) {
   return HT_OK;
 }
 
-// made: room for every item (in row order, before they are permuted); keysA, keysB: nkeys words each
-int fill_items(ht_ctx* ctx, const ItemBuild& b, const int64_t* h_tot, WorkItem* made, uint64_t* keysA, uint64_t* keysB,
-               size_t nkeys, bool order) {
+// made: room for n_made items in row order, before they are permuted; keysA, keysB: nkeys words each.  Where made does not hold all
+// items, they are put in order range by range (the order is by range first in any case; h_starts: pinned, rows.n + 1 words).
+int fill_items(ht_ctx* ctx, const ItemBuild& b, const int64_t* h_tot, WorkItem* made, size_t n_made, uint64_t* keysA, uint64_t* keysB,
+               size_t nkeys, bool order, int64_t* h_starts = nullptr) {
   if (b.nrows == 0) return HT_OK;
   const int64_t ni = h_tot[0], np = h_tot[1] - h_tot[0], nc = h_tot[2] - h_tot[1];
   if (ni > (int64_t)b.out->items.n || nc > (int64_t)b.out->cuts.n || ni > (int64_t)nkeys)
@@ -899,18 +923,35 @@ int fill_items(ht_ctx* ctx, const ItemBuild& b, const int64_t* h_tot, WorkItem* 
   b.out->n_items = ni;
   b.out->n_part = np;
   b.out->n_cut = nc;
-  const bool sorted_items = order && ni > 1;
+  const bool sorted_items = order && ni > 1, at_once = ni <= (int64_t)n_made;
   const int kbits = b.rows.n > 1 ? bits_for(b.rows.n) : 0, vbits = bits_for(b.range);
   const int fbits = std::min(vbits, 32 - kbits), fshift = vbits - fbits;
   k_items_fill<<<(unsigned)b.tiles, TB, 0, ctx->stream>>>(b.rows, b.nrows, b.seg, b.tiles, b.base, b.idx, fbits, fshift,
-                                                          sorted_items ? made : b.out->items.p, sorted_items ? keysA : nullptr,
+                                                          sorted_items && at_once ? made : b.out->items.p, sorted_items ? keysA : nullptr,
                                                           b.out->cuts.p, b.starts);
   HT_LAUNCH_CHECK(ctx);
-  if (sorted_items) {
+  if (!sorted_items) return HT_OK;
+  auto sort_range = [&](int64_t i0, int64_t n, const WorkItem* from, int bits) -> int {
     uint64_t* sorted = nullptr;
-    HT_TRY(ht_radix_sort_u64(ctx, keysA, keysB, ni, 32, 32 + kbits + fbits, &sorted));
-    k_items_permute<<<nblk(ni), TB, 0, ctx->stream>>>(sorted, ni, made, b.out->items.p);
+    HT_TRY(ht_radix_sort_u64(ctx, keysA + i0, keysB + i0, n, 32, 32 + bits, &sorted));
+    k_items_permute<<<nblk(n), TB, 0, ctx->stream>>>(sorted, n, from, (uint32_t)i0, b.out->items.p + i0);
     HT_LAUNCH_CHECK(ctx);
+    return HT_OK;
+  };
+  if (at_once) return sort_range(0, ni, made, kbits + fbits);
+  HT_HIP(ctx, hipMemcpyAsync(h_starts, b.starts, ((size_t)b.rows.n + 1) * 8, hipMemcpyDeviceToHost, ctx->stream));
+  HT_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  // (a range behind the last row has no start of its own)
+  const std::vector<int64_t> starts(h_starts, h_starts + b.rows.n);
+  int64_t end = ni;
+  for (int k = b.rows.n - 1; k >= 0; --k) {
+    if (b.h_first[k] >= b.nrows) continue;
+    const int64_t i0 = starts[k], n = end - i0;
+    end = i0;
+    if (n <= 1) continue;
+    if (n > (int64_t)n_made) return ht_set_err(ctx, HT_ESTATE, "work items: a chunk has %lld, more than was planned for", (long long)n);
+    HT_HIP(ctx, hipMemcpyAsync(made, b.out->items.p + i0, (size_t)n * sizeof(WorkItem), hipMemcpyDeviceToDevice, ctx->stream));
+    HT_TRY(sort_range(i0, n, made, fbits));
   }
   return HT_OK;
 }
@@ -925,8 +966,14 @@ struct ItemSwitches {          // experiments
   }
 };
 
+// Bytes of bitmaps and word prefixes up to which all chunks' rows are held at once.  Beyond (n V / 8 bytes of bitmaps alone: many
+// chunks of many vertices), and where all rows do not fit a sixteenth of the free memory, a few rows are marked at a time.
+constexpr int64_t ROWS_BYTES = (int64_t)3 << 30, ROWS_SMALL = (int64_t)256 << 20;
+
+// lean: as little temporary memory as the steps can do with (three bitmap rows, one byte map, work items ordered chunk by chunk),
+// where the memory for all chunks at once was refused; the graph is the same.
 int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, const int32_t* dst_in, int32_t n,
-                   const ht_part_opts* opts, ht_graph* g) {
+                   const ht_part_opts* opts, bool lean, ht_graph* g) {
   hipStream_t st = ctx->stream;
   const int self_loops = opts ? (opts->add_self_loops != 0) : 1;
   const int mode = opts ? opts->balance_mode : HT_BALANCE_EDGES;
@@ -970,7 +1017,19 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
   }
 
   // ---- temporaries of the whole call, one allocation
-  const int64_t grp = mark_group(nwp, n);
+  bool by_chunk = lean;
+  {
+    const int64_t need = (int64_t)n * nwp * 12;
+    if (need > ROWS_BYTES) by_chunk = true;
+    else if (need > ROWS_SMALL) {
+      size_t free_b = 0, total_b = 0;
+      HT_HIP(ctx, hipMemGetInfo(&free_b, &total_b));
+      if (need > (int64_t)(free_b / 16)) by_chunk = true;
+    }
+    if (const char* v = getenv("HT_PART_BY_CHUNK")) by_chunk = by_chunk || atoi(v) != 0;   // for tests
+  }
+  const int64_t grp = by_chunk ? 1 : mark_group(nwp, n);
+  const int64_t nrow = by_chunk ? 3 : n, nlist = by_chunk ? 1 : n;   // bitmap rows held; positions listed at once
   const size_t nkeys = (size_t)std::max<int64_t>(std::max(Ep, item_bound(V, Ep, std::min(seg_fwd, seg_bwd))), 1) + 64;
   DevBlock tmp;
   DevArr<uint64_t> keysA, keysB, allbm;
@@ -981,31 +1040,31 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
   enum { L_FLAG, L_BOUNDS, L_EOFF, L_UEOFF, L_NOFF, L_REUSE, L_LOAD, L_LEAVE, L_COUNT };
   tmp.add<uint64_t>(nkeys);
   tmp.add<uint64_t>(nkeys);
-  tmp.add<uint64_t>((size_t)n * nwp);
+  tmp.add<uint64_t>((size_t)nrow * nwp);
   tmp.add<int32_t>((size_t)etiles);
-  tmp.add<int32_t>((size_t)n * T);
-  tmp.add<int32_t>((size_t)3 * n * T);
+  tmp.add<int32_t>((size_t)nlist * T);
+  tmp.add<int32_t>((size_t)3 * nlist * T);
   tmp.add<int32_t>((size_t)n);
   tmp.add<int64_t>((size_t)etiles + 1);
-  tmp.add<int64_t>((size_t)n * T + 1);
-  tmp.add<int64_t>((size_t)3 * n * T + 1);
+  tmp.add<int64_t>((size_t)nlist * T + 1);
+  tmp.add<int64_t>((size_t)3 * nlist * T + 1);
   tmp.add<int64_t>(n1 * L_COUNT);
   tmp.add<uint8_t>((size_t)grp * nwp * 64);
-  tmp.add<uint32_t>((size_t)n * nwp);
+  tmp.add<uint32_t>((size_t)nlist * nwp);
   HT_TRY(tmp.alloc(ctx));
   tmp.take(keysA, nkeys);
   tmp.take(keysB, nkeys);
-  tmp.take(allbm, (size_t)n * nwp);
+  tmp.take(allbm, (size_t)nrow * nwp);
   tmp.take(ucount, (size_t)etiles);
-  tmp.take(tile_cnt, (size_t)n * T);
-  tmp.take(list_cnt, (size_t)3 * n * T);
+  tmp.take(tile_cnt, (size_t)nlist * T);
+  tmp.take(list_cnt, (size_t)3 * nlist * T);
   tmp.take(d_order, (size_t)n);
   tmp.take(ubase, (size_t)etiles + 1);
-  tmp.take(tbase, (size_t)n * T + 1);
-  tmp.take(lbase, (size_t)3 * n * T + 1);
+  tmp.take(tbase, (size_t)nlist * T + 1);
+  tmp.take(lbase, (size_t)3 * nlist * T + 1);
   tmp.take(lists, n1 * L_COUNT);
   tmp.take(seen, (size_t)grp * nwp * 64);
-  tmp.take(wpref, (size_t)n * nwp);
+  tmp.take(wpref, (size_t)nlist * nwp);
   auto list = [&](int which) { return lists.p + (size_t)which * n1; };
   HT_TRY(ht_fill_zero(ctx, st, list(L_FLAG), 8));
   HT_TRY(ht_fill_zero(ctx, st, seen.p, seen.bytes()));
@@ -1077,11 +1136,18 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
     HT_LAUNCH_CHECK(ctx);
   }
 
-  // ---- neighbour sets of all chunks as bitmaps (bit u of row k: u is in N_k; k = chunk id in vertex order)
-  HT_TRY(mark_chunks(ctx, st, g->col.p, eoff.data(), list(L_EOFF), n, nwp, seen.p, allbm.p, tile_cnt.p));
-  HT_TRY(ht_scan_i32(ctx, tile_cnt.p, tbase.p, (int64_t)n * T, true));
-  k_gather_stride<<<nblk((int64_t)n1), TB, 0, st>>>(tbase.p, T, (int64_t)n1, list(L_NOFF));
-  HT_LAUNCH_CHECK(ctx);
+  // ---- neighbour sets of the chunks as bitmaps (bit u of row k: u is in N_k; k = chunk id in vertex order)
+  if (!by_chunk) {
+    HT_TRY(mark_chunks(ctx, st, g->col.p, eoff.data(), list(L_EOFF), n, nwp, grp, seen.p, allbm.p, tile_cnt.p));
+    HT_TRY(ht_scan_i32(ctx, tile_cnt.p, tbase.p, (int64_t)n * T, true));
+    k_gather_stride<<<nblk((int64_t)n1), TB, 0, st>>>(tbase.p, T, (int64_t)n1, list(L_NOFF));
+    HT_LAUNCH_CHECK(ctx);
+  }
+  // chunk by chunk: the row of schedule position j, marked into one of three
+  auto mark_row = [&](int j, int32_t* cnt) -> int {
+    return mark_chunk(ctx, st, g->col.p, eoff.data(), list(L_EOFF), n, g->order[j], nwp, seen.p, allbm.p + (j % 3) * nwp, cnt);
+  };
+  auto row_of = [&](int j) { return allbm.p + (size_t)(by_chunk ? j % 3 : g->order[j]) * nwp; };
 
   // a buffer with room for every distinct source is the schedule-aware buffer at that size
   const bool keep_all = opts && opts->cache_rows == -1;
@@ -1095,13 +1161,23 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
   if (opts && opts->reorder_chunks && n > 2) {
     DevArr<unsigned long long> ov;
     HT_TRY(ov.alloc(ctx, n));
+    DevArr<uint64_t> rows_tmp;      // (the greedy steps compare every chunk with every other)
+    const uint64_t* bms = allbm.p;
+    if (by_chunk) {
+      DevArr<int32_t> cnt_tmp;
+      HT_TRY(rows_tmp.alloc(ctx, (size_t)n * nwp));
+      HT_TRY(cnt_tmp.alloc(ctx, (size_t)n * T));
+      HT_TRY(mark_chunks(ctx, st, g->col.p, eoff.data(), list(L_EOFF), n, nwp, grp, seen.p, rows_tmp.p, cnt_tmp.p));
+      HT_HIP(ctx, hipStreamSynchronize(st));
+      bms = rows_tmp.p;
+    }
     std::vector<unsigned long long> hov(n);
     std::vector<char> placed(n, 0);
     placed[0] = 1;
     const unsigned gx = (unsigned)std::min<int64_t>(T, 64);
     for (int j = 1; j < n; ++j) {
       HT_TRY(ht_fill_zero(ctx, st, ov.p, (size_t)n * 8));
-      k_overlap<<<dim3(gx, n), TB, 0, st>>>(allbm.p, nwp, allbm.p + (size_t)g->order[j - 1] * nwp, ov.p);
+      k_overlap<<<dim3(gx, n), TB, 0, st>>>(bms, nwp, bms + (size_t)g->order[j - 1] * nwp, ov.p);
       HT_LAUNCH_CHECK(ctx);
       HT_HIP(ctx, hipMemcpyAsync(hov.data(), ov.p, (size_t)n * 8, hipMemcpyDeviceToHost, st));
       HT_HIP(ctx, hipStreamSynchronize(st));
@@ -1116,34 +1192,95 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
   HT_HIP(ctx, hipMemcpyAsync(d_order.p, hl + 8 * n1, (size_t)n * 4, hipMemcpyHostToDevice, st));
 
   // ---- reuse / load / leave lists: counted here for the adjacent rule; the schedule-aware buffer is simulated first
-  ListRows rows{allbm.p, d_order.p, nullptr, nullptr, nwp, n};
+  ListRows rows{allbm.p, by_chunk ? nullptr : d_order.p, nullptr, nullptr, nwp, n, 0, (int32_t)nlist};
   auto count_lists = [&]() -> int {
-    HT_TRY(ht_in_launches((int64_t)n * T, TILE_LAUNCH, [&](int64_t t, int64_t m) {
+    HT_TRY(ht_in_launches((int64_t)rows.nj * T, TILE_LAUNCH, [&](int64_t t, int64_t m) {
       k_list_counts<<<(unsigned)m, TB, 0, st>>>(rows, T, list_cnt.p, t);
       HT_LAUNCH_CHECK(ctx);
       return (int)HT_OK;
     }));
-    HT_TRY(ht_scan_i32(ctx, list_cnt.p, lbase.p, (int64_t)3 * n * T, true));
+    return ht_scan_i32(ctx, list_cnt.p, lbase.p, (int64_t)3 * rows.nj * T, true);
+  };
+  auto list_starts = [&]() -> int {
     for (int w = 0; w < 3; ++w) {
       k_gather_stride<<<nblk((int64_t)n1), TB, 0, st>>>(lbase.p + (int64_t)w * n * T, T, (int64_t)n1, list(L_REUSE + w));
       HT_LAUNCH_CHECK(ctx);
     }
     return HT_OK;
   };
-  DevArr<unsigned long long> distinct;
-  if (far_first) {
-    HT_TRY(distinct.alloc(ctx, 1));
-    HT_TRY(ht_fill_zero(ctx, st, distinct.p, 8));
-    k_popc_all<<<popc_grid(nwp), TB, 0, st>>>(allbm.p, nwp, n, distinct.p);
-    HT_LAUNCH_CHECK(ctx);
-    HT_HIP(ctx, hipMemcpyAsync(&hp[2], distinct.p, 8, hipMemcpyDeviceToHost, st));
-  }
-  // (the adjacent rule's loads are also V_+ru, which every schedule reports)
-  HT_TRY(count_lists());
-  HT_HIP(ctx, hipMemcpyAsync(hl, list(L_UEOFF), (size_t)(L_COUNT - L_UEOFF) * n1 * 8, hipMemcpyDeviceToHost, st));
-  HT_HIP(ctx, hipStreamSynchronize(st));
-  const std::vector<int64_t> ueoff(hl, hl + n1), noff(hl + n1, hl + 2 * n1);
+  auto expand_lists = [&](int32_t* reuse, int32_t* load, int32_t* leave) -> int {
+    return ht_in_launches((int64_t)rows.nj * T, TILE_LAUNCH, [&](int64_t t, int64_t m) {
+      k_list_expand<<<(unsigned)m, TB, 0, st>>>(rows, T, lbase.p, reuse, load, leave, t);
+      HT_LAUNCH_CHECK(ctx);
+      return (int)HT_OK;
+    });
+  };
+  std::vector<int64_t> ueoff, noff;
   std::vector<int64_t> offs[3];   // starts of every schedule position's reuse / load / leave list
+  int64_t n_distinct = 0;         // |N_0 u ... u N_{n-1}| (schedule-aware buffer)
+  if (!by_chunk) {
+    DevArr<unsigned long long> distinct;
+    if (far_first) {
+      HT_TRY(distinct.alloc(ctx, 1));
+      HT_TRY(ht_fill_zero(ctx, st, distinct.p, 8));
+      k_popc_all<<<popc_grid(nwp), TB, 0, st>>>(allbm.p, nwp, n, distinct.p);
+      HT_LAUNCH_CHECK(ctx);
+      HT_HIP(ctx, hipMemcpyAsync(&hp[2], distinct.p, 8, hipMemcpyDeviceToHost, st));
+    }
+    // (the adjacent rule's loads are also V_+ru, which every schedule reports)
+    HT_TRY(count_lists());
+    HT_TRY(list_starts());
+    HT_HIP(ctx, hipMemcpyAsync(hl, list(L_UEOFF), (size_t)(L_COUNT - L_UEOFF) * n1 * 8, hipMemcpyDeviceToHost, st));
+    HT_HIP(ctx, hipStreamSynchronize(st));
+    ueoff.assign(hl, hl + n1);
+    noff.assign(hl + n1, hl + 2 * n1);
+    if (far_first) n_distinct = hp[2];
+  } else {
+    DevArr<int64_t> counts;   // |N|, reuse, load, leave of every position
+    DevArr<uint64_t> all;     // N_0 u N_1 u ...
+    DevArr<unsigned long long> distinct;
+    HT_TRY(counts.alloc(ctx, (size_t)4 * n));
+    if (far_first) {
+      HT_TRY(all.alloc(ctx, (size_t)nwp));
+      HT_TRY(distinct.alloc(ctx, 1));
+      HT_TRY(ht_fill_zero(ctx, st, all.p, all.bytes()));
+      HT_TRY(ht_fill_zero(ctx, st, distinct.p, 8));
+    }
+    for (int j = 0; j < n; ++j) {
+      if (j == 0) HT_TRY(mark_row(0, tile_cnt.p));
+      HT_TRY(ht_scan_i32(ctx, tile_cnt.p, tbase.p, T, true));       // (tile_cnt: row j's)
+      if (j + 1 < n) HT_TRY(mark_row(j + 1, tile_cnt.p));
+      rows.j0 = j;
+      HT_TRY(count_lists());
+      k_put_counts<<<1, 64, 0, st>>>(tbase.p, lbase.p, T, counts.p + 4 * j);
+      HT_LAUNCH_CHECK(ctx);
+      if (far_first) {
+        k_bm_or<<<nblk(nwp), TB, 0, st>>>(all.p, row_of(j), nwp);
+        HT_LAUNCH_CHECK(ctx);
+      }
+    }
+    if (far_first) {
+      k_popc_all<<<popc_grid(nwp), TB, 0, st>>>(all.p, nwp, 1, distinct.p);
+      HT_LAUNCH_CHECK(ctx);
+      HT_HIP(ctx, hipMemcpyAsync(&hp[2], distinct.p, 8, hipMemcpyDeviceToHost, st));
+    }
+    std::vector<int64_t> h4((size_t)4 * n);
+    HT_HIP(ctx, hipMemcpyAsync(h4.data(), counts.p, (size_t)4 * n * 8, hipMemcpyDeviceToHost, st));
+    HT_HIP(ctx, hipMemcpyAsync(hl, list(L_UEOFF), n1 * 8, hipMemcpyDeviceToHost, st));
+    HT_HIP(ctx, hipStreamSynchronize(st));
+    ueoff.assign(hl, hl + n1);
+    noff.assign(n1, 0);
+    for (int j = 0; j < n; ++j) noff[g->order[j] + 1] = h4[(size_t)4 * j];
+    for (int k = 0; k < n; ++k) noff[k + 1] += noff[k];
+    for (int w = 0; w < 3; ++w) {
+      offs[w].assign(n1, 0);
+      for (int j = 0; j < n; ++j) offs[w][j + 1] = offs[w][j] + h4[(size_t)4 * j + 1 + w];
+    }
+    std::copy(noff.begin(), noff.end(), hl);
+    HT_HIP(ctx, hipMemcpyAsync(list(L_NOFF), hl, n1 * 8, hipMemcpyHostToDevice, st));
+    HT_HIP(ctx, hipStreamSynchronize(st));
+    if (far_first) n_distinct = hp[2];
+  }
   auto take_offsets = [&](const int64_t* h) {
     for (int w = 0; w < 3; ++w) {
       offs[w].assign(h + (size_t)w * n1, h + (size_t)(w + 1) * n1);
@@ -1151,7 +1288,7 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
       for (int64_t& x : offs[w]) x -= b0;
     }
   };
-  take_offsets(hl + (size_t)(L_REUSE - L_UEOFF) * n1);
+  if (!by_chunk) take_offsets(hl + (size_t)(L_REUSE - L_UEOFF) * n1);
   g->v_ori = noff[n];
   g->v_ru = offs[1][n];
   g->pos.resize(n);
@@ -1186,7 +1323,6 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
     }
     j = k + 1;
   }
-  const int64_t n_distinct = far_first ? hp[2] : 0;   // |N_0 u ... u N_{n-1}|
   int64_t C = opts ? opts->cache_rows : 0;
   if (keep_all) C = n_distinct;
   if (C <= 0) C = g->max_nsrc;
@@ -1195,11 +1331,19 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
                       (long long)g->max_nsrc);
   const size_t vo = (size_t)std::max<int64_t>(g->v_ori, 1);
   HT_TRY(g->nbr.alloc(ctx, vo));
-  HT_TRY(ht_in_launches((int64_t)n * T, TILE_LAUNCH, [&](int64_t t, int64_t m) {
-    k_expand_rows<<<(unsigned)m, TB, 0, st>>>(allbm.p, nwp, tbase.p, wpref.p, g->nbr.p, t);
+  if (!by_chunk)
+    HT_TRY(ht_in_launches((int64_t)n * T, TILE_LAUNCH, [&](int64_t t, int64_t m) {
+      k_expand_rows<<<(unsigned)m, TB, 0, st>>>(allbm.p, nwp, tbase.p, wpref.p, g->nbr.p, t, 0);
+      HT_LAUNCH_CHECK(ctx);
+      return (int)HT_OK;
+    }));
+  // chunk by chunk: row j's word prefixes and its list, from its tile counts
+  auto expand_row = [&](int j) -> int {
+    HT_TRY(ht_scan_i32(ctx, tile_cnt.p, tbase.p, T, true));
+    k_expand_rows<<<(unsigned)T, TB, 0, st>>>(row_of(j), nwp, tbase.p, wpref.p, g->nbr.p, 0, noff[g->order[j]]);
     HT_LAUNCH_CHECK(ctx);
-    return (int)HT_OK;
-  }));
+    return HT_OK;
+  };
 
   // ---- schedule of a buffer that knows the future: a row leaves after its last use, or for room with the farthest next
   // use first.  Simulated chunk by chunk on bitmaps; kept for the lists: the rows resident before every chunk (Pbm), the
@@ -1220,7 +1364,7 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
     fb.take(hist, n1); fb.take(tot2, (size_t)n + 2); fb.take(pref1, (size_t)nwp + 1);
     fb.take(eqbm, (size_t)nwp); fb.take(bmT, (size_t)nwp); fb.take(bmR, (size_t)nwp);
     unsigned long long* dead_cnt = tot2.p + 2;
-    HT_TRY(Pbm.alloc(ctx, (size_t)n * nwp));
+    HT_TRY(Pbm.alloc(ctx, (size_t)nlist * nwp));
     HT_TRY(Ebm.alloc(ctx, n1 * (size_t)nwp));
     HT_TRY(ht_fill_zero(ctx, st, dead_cnt, (size_t)n * 8));
     HT_TRY(ht_fill_zero(ctx, st, Ebm.p, Ebm.bytes()));
@@ -1232,6 +1376,10 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
     // next uses, last chunk first
     for (int j = n - 1; j >= 0; --j) {
       const ChunkMeta& c = g->chunks[j];
+      if (by_chunk) {
+        HT_TRY(mark_row(j, tile_cnt.p));
+        HT_TRY(expand_row(j));
+      }
       if (c.nsrc > 0) {
         k_next_use<<<nblk(c.nsrc), TB, 0, st>>>(g->nbr.p + c.nbr_off, c.nsrc, last.p, j, nxt.p + c.nbr_off);
         HT_LAUNCH_CHECK(ctx);
@@ -1239,9 +1387,11 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
     }
     // forward simulation: bmR = resident rows
     std::vector<unsigned int> hh(n1);
+    std::vector<int64_t> n_reuse((size_t)n), n_leave((size_t)n, 0);
     for (int j = 0; j < n; ++j) {
       const ChunkMeta& c = g->chunks[j];
-      const uint64_t* bmj = allbm.p + (size_t)c.id * nwp;   // N_j
+      const uint64_t* bmj = row_of(j);   // N_j
+      if (by_chunk) HT_TRY(mark_row(j, tile_cnt.p));
       HT_TRY(ht_fill_zero(ctx, st, tot2.p, 16));
       k_popc_union<<<popc_grid(nwp), TB, 0, st>>>(bmR.p, bmj, nwp, tot2.p);
       HT_LAUNCH_CHECK(ctx);
@@ -1249,7 +1399,9 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
       HT_HIP(ctx, hipMemcpyAsync(t2, tot2.p, 16, hipMemcpyDeviceToHost, st));
       HT_HIP(ctx, hipStreamSynchronize(st));
       const int64_t over = (int64_t)t2[0] - C;
+      n_reuse[j] = (int64_t)t2[1];
       if (over > 0) {
+        n_leave[j - 1] += over;     // j > 0 here: nothing is resident before the first chunk
         uint64_t* Ej = Ebm.p + (size_t)j * nwp;
         k_bm_minus<<<nblk(nwp), TB, 0, st>>>(bmR.p, bmj, nwp, bmT.p);   // candidates: resident, not needed now
         HT_LAUNCH_CHECK(ctx);
@@ -1276,7 +1428,7 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
         k_bm_minus<<<nblk(nwp), TB, 0, st>>>(bmR.p, Ej, nwp, bmR.p);
         HT_LAUNCH_CHECK(ctx);
       }
-      HT_HIP(ctx, hipMemcpyAsync(Pbm.p + (size_t)j * nwp, bmR.p, (size_t)nwp * 8, hipMemcpyDeviceToDevice, st));
+      if (!by_chunk) HT_HIP(ctx, hipMemcpyAsync(Pbm.p + (size_t)j * nwp, bmR.p, (size_t)nwp * 8, hipMemcpyDeviceToDevice, st));
       k_bm_or<<<nblk(nwp), TB, 0, st>>>(bmR.p, bmj, nwp);
       HT_LAUNCH_CHECK(ctx);
       if (c.nsrc > 0) {
@@ -1295,10 +1447,27 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
     HT_HIP(ctx, hipMemcpyAsync(Ebm.p + (size_t)n * nwp, bmR.p, (size_t)nwp * 8, hipMemcpyDeviceToDevice, st));
     rows.pbm = Pbm.p;
     rows.ebm = Ebm.p;
-    HT_TRY(count_lists());
-    HT_HIP(ctx, hipMemcpyAsync(hl, list(L_REUSE), 3 * n1 * 8, hipMemcpyDeviceToHost, st));
-    HT_HIP(ctx, hipStreamSynchronize(st));
-    take_offsets(hl);
+    if (!by_chunk) {
+      HT_TRY(count_lists());
+      HT_TRY(list_starts());
+      HT_HIP(ctx, hipMemcpyAsync(hl, list(L_REUSE), 3 * n1 * 8, hipMemcpyDeviceToHost, st));
+      HT_HIP(ctx, hipStreamSynchronize(st));
+      take_offsets(hl);
+    } else {   // counted on the way
+      HT_TRY(ht_fill_zero(ctx, st, tot2.p, 16));
+      k_popc_union<<<popc_grid(nwp), TB, 0, st>>>(bmR.p, bmR.p, nwp, tot2.p);
+      HT_LAUNCH_CHECK(ctx);
+      std::vector<unsigned long long> dead((size_t)n + 2);
+      HT_HIP(ctx, hipMemcpyAsync(dead.data(), tot2.p, dead.size() * 8, hipMemcpyDeviceToHost, st));
+      HT_HIP(ctx, hipStreamSynchronize(st));
+      for (int j = 0; j + 1 < n; ++j) n_leave[j] += (int64_t)dead[j + 2];
+      n_leave[n - 1] = (int64_t)dead[0];      // what is still resident leaves at the end of a pass
+      for (int j = 0; j < n; ++j) {
+        offs[0][j + 1] = offs[0][j] + n_reuse[j];
+        offs[1][j + 1] = offs[1][j] + g->chunks[j].nsrc - n_reuse[j];
+        offs[2][j + 1] = offs[2][j] + n_leave[j];
+      }
+    }
   }
   g->v_load = offs[1][n];
   for (int j = 0; j < n; ++j) {
@@ -1363,6 +1532,14 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
   ib[1].idx = g->merged ? g->usdst.p : g->sdst.p;   // backward items by local destination
   ib[1].range = g->max_ndst;
   ib[1].out = &g->bwd_items;
+  ib[0].h_first = g->bounds.data();
+  ib[1].h_first = noff.data();
+  int64_t n_made = std::max(fb_items, bb_items);     // items put in order at once
+  if (lean) {
+    n_made = 1;
+    for (const ChunkMeta& c : g->chunks)
+      n_made = std::max(n_made, std::max(item_bound(c.dst1 - c.dst0, c.nu, seg_fwd), item_bound(c.nsrc, c.nu, seg_bwd)));
+  }
   DevBlock tmp2;
   DevArr<int32_t> vslot, free_cnt, icnt[2];
   DevArr<uint64_t> freebm;
@@ -1374,7 +1551,7 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
   tmp2.add<uint64_t>((size_t)2 * nwC);
   for (const ItemBuild& b : ib) { tmp2.add<int32_t>((size_t)3 * b.tiles); tmp2.add<int64_t>((size_t)3 * b.tiles + 1); }
   tmp2.add<int64_t>(6 * n1);
-  tmp2.add<WorkItem>((size_t)std::max(fb_items, bb_items));
+  tmp2.add<WorkItem>((size_t)n_made);
   HT_TRY(tmp2.alloc(ctx));
   tmp2.take(vslot, (size_t)V);
   tmp2.take(free_cnt, (size_t)tC);
@@ -1386,23 +1563,18 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
     ib[d].base = ibase[d].p;
   }
   tmp2.take(istarts, 6 * n1);
-  tmp2.take(made, (size_t)std::max(fb_items, bb_items));
+  tmp2.take(made, (size_t)n_made);
   ib[0].starts = istarts.p;
   ib[1].starts = istarts.p + 3 * n1;
 
   HT_HIP(ctx, hipMemcpyAsync(g->d_dense_groups.p, g->dense_groups.data(), g->dense_groups.size() * 8, hipMemcpyHostToDevice, st));
 
   // ---- the lists, then the buffer positions, chunk by chunk
-  HT_TRY(ht_in_launches((int64_t)n * T, TILE_LAUNCH, [&](int64_t t, int64_t m) {
-    k_list_expand<<<(unsigned)m, TB, 0, st>>>(rows, T, lbase.p, g->reuse.p, g->load.p, g->leave.p, t);
-    HT_LAUNCH_CHECK(ctx);
-    return (int)HT_OK;
-  }));
   uint64_t* free_now = freebm.p;
   uint64_t* free_next = freebm.p + nwC;
   k_free_init<<<nblk(nwC), TB, 0, st>>>(free_now, nwC, C);
   HT_LAUNCH_CHECK(ctx);
-  for (int j = 0; j < n; ++j) {
+  auto positions = [&](int j) -> int {
     const ChunkMeta& c = g->chunks[j];
     if (c.n_load > 0) {
       const bool counted = nwC > 16 * TB;   // few words: every block adds up those before it by itself
@@ -1416,13 +1588,45 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
       std::swap(free_now, free_next);
     }
     if (c.nsrc + c.n_leave > 0) {
-      const uint64_t* prev = far_first ? Pbm.p + (size_t)j * nwp
-                             : j > 0   ? allbm.p + (size_t)g->order[j - 1] * nwp
-                                       : nullptr;
+      const uint64_t* prev = far_first ? Pbm.p + (size_t)(by_chunk ? 0 : j) * nwp : j > 0 ? row_of(j - 1) : nullptr;
       k_lookup_evict<<<nblk(c.nsrc + c.n_leave), TB, 0, st>>>(g->nbr.p + c.nbr_off, c.nsrc, vslot.p, prev, g->slot.p + c.nbr_off,
                                                              g->gslot.p + c.nbr_off, g->leave.p + c.leave_off, c.n_leave,
                                                              (uint32_t*)free_now, g->leave_slot.p + c.leave_off);
       HT_LAUNCH_CHECK(ctx);
+    }
+    return HT_OK;
+  };
+  // edges [e0, e1), the first of them of chunk k0, whose bitmap row is bm
+  auto remap = [&](int64_t e0, int64_t e1, int k0, const uint64_t* bm) -> int {
+    if (e1 <= e0) return HT_OK;
+    k_remap<<<nblk(e1 - e0, ETILE), TB, 0, st>>>(csc, e0, e1, k0, bitsV, list(L_EOFF), list(L_BOUNDS), list(L_NOFF), n, bm, nwp, wpref.p,
+                                                 g->slot.p, g->col_local.p, g->col_slot.p, other);
+    HT_LAUNCH_CHECK(ctx);
+    return HT_OK;
+  };
+  if (!by_chunk) {
+    HT_TRY(expand_lists(g->reuse.p, g->load.p, g->leave.p));
+    for (int j = 0; j < n; ++j) HT_TRY(positions(j));
+    HT_TRY(remap(0, Ep, 0, allbm.p));
+  } else {
+    if (far_first) HT_TRY(ht_fill_zero(ctx, st, Pbm.p, Pbm.bytes()));
+    for (int j = 0; j < n; ++j) {
+      const ChunkMeta& c = g->chunks[j];
+      if (j == 0 || far_first) HT_TRY(mark_row(j, tile_cnt.p));
+      HT_TRY(expand_row(j));                                        // (tile_cnt: row j's)
+      if (far_first) {   // Pbm: the rows resident before chunk j
+        k_bm_minus<<<nblk(nwp), TB, 0, st>>>(Pbm.p, Ebm.p + (size_t)j * nwp, nwp, Pbm.p);
+        HT_LAUNCH_CHECK(ctx);
+      } else if (j + 1 < n) HT_TRY(mark_row(j + 1, tile_cnt.p));
+      rows.j0 = j;
+      HT_TRY(count_lists());
+      HT_TRY(expand_lists(g->reuse.p + c.reuse_off, g->load.p + c.load_off, g->leave.p + c.leave_off));
+      HT_TRY(positions(j));
+      HT_TRY(remap(c.e0, c.e0 + c.nnz, c.id, row_of(j)));
+      if (far_first) {
+        k_bm_or<<<nblk(nwp), TB, 0, st>>>(Pbm.p, row_of(j), nwp);
+        HT_LAUNCH_CHECK(ctx);
+      }
     }
   }
 
@@ -1434,9 +1638,6 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
     HT_LAUNCH_CHECK(ctx);
   }
   if (Ep > 0) {
-    k_remap<<<(unsigned)etiles, TB, 0, st>>>(csc, Ep, bitsV, list(L_EOFF), list(L_BOUNDS), list(L_NOFF), n, allbm.p, nwp, wpref.p,
-                                             g->slot.p, g->col_local.p, g->col_slot.p, other);
-    HT_LAUNCH_CHECK(ctx);
     if (g->merged) {   // buffer positions of the distinct forward pairs
       k_gather_i32<<<nblk(nU), TB, 0, st>>>(g->col_slot.p, upos.p, nU, g->ucol_slot.p);
       HT_LAUNCH_CHECK(ctx);
@@ -1458,7 +1659,7 @@ int partition_impl(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src_in, con
   // ---- work items of both directions
   for (int d = 0; d < 2; ++d) HT_TRY(count_items(ctx, ib[d], hp + 3 * d));
   HT_HIP(ctx, hipStreamSynchronize(st));
-  for (int d = 0; d < 2; ++d) HT_TRY(fill_items(ctx, ib[d], hp + 3 * d, made.p, keysA.p, keysB.p, nkeys, sw.order));
+  for (int d = 0; d < 2; ++d) HT_TRY(fill_items(ctx, ib[d], hp + 3 * d, made.p, (size_t)n_made, keysA.p, keysB.p, nkeys, sw.order, hl));
   HT_HIP(ctx, hipMemcpyAsync(hl, istarts.p, 6 * n1 * 8, hipMemcpyDeviceToHost, st));
   HT_HIP(ctx, hipStreamSynchronize(st));
   for (int d = 0; d < 2; ++d) {
@@ -1594,7 +1795,7 @@ int build_by_source(ht_ctx* ctx, const ht_graph* g) {
   b.rows = RowSet{ptr.p, lists.p + 3 * n1, nullptr, 1};
   HT_TRY(count_items(ctx, b, hp));
   HT_HIP(ctx, hipStreamSynchronize(st));
-  HT_TRY(fill_items(ctx, b, hp, made.p, keysA.p, keysB.p, (size_t)bound, sw.order));
+  HT_TRY(fill_items(ctx, b, hp, made.p, (size_t)bound, keysA.p, keysB.p, (size_t)bound, sw.order));
   HT_HIP(ctx, hipStreamSynchronize(st));
   return HT_OK;
 }
@@ -1656,7 +1857,16 @@ int ht_partition(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src, const in
   ht_graph* g = new (std::nothrow) ht_graph();
   if (g) g->serial = next_serial.fetch_add(1);
   if (!g) return ht_set_err(ctx, HT_ENOMEM, "ht_partition: host allocation failed");
-  int rc = partition_impl(ctx, V, E, src, dst, n_chunks, opts, g);
+  int rc = partition_impl(ctx, V, E, src, dst, n_chunks, opts, false, g);
+  if (rc == HT_ENOMEM) {
+    (void)hipStreamSynchronize(ctx->stream);
+    const uint64_t serial = g->serial;
+    delete g;
+    g = new (std::nothrow) ht_graph();
+    if (!g) return ht_set_err(ctx, HT_ENOMEM, "ht_partition: host allocation failed");
+    g->serial = serial;
+    rc = partition_impl(ctx, V, E, src, dst, n_chunks, opts, true, g);
+  }
   if (rc != HT_OK) {
     (void)hipStreamSynchronize(ctx->stream);
     delete g;
@@ -1770,12 +1980,18 @@ int ht_graph_reorganize(ht_ctx* ctx, const ht_graph* g, int32_t m, int32_t* layo
     std::vector<int64_t> eoff;
     for (const ChunkMeta& ch : g->chunks) eoff.push_back(ch.e0);
     eoff.push_back(g->Ep);
-    HT_TRY(seen.alloc(ctx, (size_t)mark_group(nw, mn) * nw * 64));
+    int64_t grp = mark_group(nw, mn);
+    int rc = seen.alloc(ctx, (size_t)grp * nw * 64);
+    if (rc == HT_ENOMEM && grp > 1) {
+      grp = 1;
+      rc = seen.alloc(ctx, (size_t)nw * 64);
+    }
+    HT_TRY(rc);
     HT_TRY(tile_cnt.alloc(ctx, (size_t)mn * (nw / TB)));
     HT_TRY(d_eoff.alloc(ctx, eoff.size()));
     HT_HIP(ctx, hipMemcpyAsync(d_eoff.p, eoff.data(), eoff.size() * 8, hipMemcpyHostToDevice, st));
     HT_TRY(ht_fill_zero(ctx, st, seen.p, seen.bytes()));
-    HT_TRY(mark_chunks(ctx, st, g->col.p, eoff.data(), d_eoff.p, mn, nw, seen.p, bms.p, tile_cnt.p));
+    HT_TRY(mark_chunks(ctx, st, g->col.p, eoff.data(), d_eoff.p, mn, nw, grp, seen.p, bms.p, tile_cnt.p));
     HT_HIP(ctx, hipStreamSynchronize(st));
   }
   DevArr<unsigned long long> cnt;

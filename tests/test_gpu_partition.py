@@ -323,3 +323,85 @@ def test_reorganize_finds_planted_locality(ctx):
     for i in range(m):
         assert [int(perms[i][layout[i * n + j]]) for j in range(n)] == [int(perms[0][layout[j]]) for j in range(n)]
     assert before[0] == after[0] and after[1] <= n * blk and before[1] > 2 * after[1]
+
+
+def _arrays(g):
+    out = [x for x in B.ht_graph_export_csc(g)] + [B.ht_graph_chunk_order(g)]
+    info = B.ht_graph_info_get(g)
+    for j in range(info.n_chunks):
+        ch = B.ht_graph_export_chunk(g, j)
+        ci = ch.pop("info")
+        out += [ch[k] for k in sorted(ch)] + [np.array([ci.dst_begin, ci.dst_end, ci.nnz, ci.n_src, ci.n_reuse, ci.n_load, ci.n_leave])]
+    return out + [np.array([info.v_ori, info.v_ru, info.v_load, info.cache_rows, info.max_nsrc])]
+
+
+@pytest.mark.parametrize("opts", [dict(), dict(reorder_chunks=True), dict(cache_policy=B.HT_CACHE_FARTHEST),
+                                  dict(cache_rows=-1, reorder_chunks=True), dict(cache_policy=B.HT_CACHE_FARTHEST, rows=1.2)])
+@pytest.mark.parametrize("V,E,n", [(20_011, 300_007, 9), (700, 9_000, 40), (64, 3, 70), (9_001, 900_000, 4)])
+@pytest.mark.parametrize("how", ["by chunk", "lean"])
+def test_chunk_by_chunk_lists_are_those_of_all_chunks_at_once(opts, V, E, n, how, monkeypatch):
+    """The route with a few bitmap rows at a time (many chunks of many vertices, or no memory for all) builds the same graph; so
+    does the one that also orders its work items chunk by chunk: the gradients of a layer keep their bits."""
+    src, dst = inputs.rmat_edges(V, E, seed=V) if E > 3 else (torch.tensor([0, 1, 2], dtype=torch.int32), torch.tensor([5, 5, 9], dtype=torch.int32))
+    src, dst, opts = src.cuda(), dst.cuda(), dict(opts)
+    share = opts.pop("rows", None)
+    made = []
+
+    def build(**kw):
+        made.append([B.ht_ctx_create(0), None])
+        made[-1][1] = B.ht_partition(made[-1][0], V, src, dst, n, **kw)
+        return made[-1]
+    try:
+        if share:
+            opts["cache_rows"] = min(V, int(B.ht_graph_info_get(build()[1]).max_nsrc * share))
+        first = build(**opts)
+        if how == "by chunk":
+            monkeypatch.setenv("HT_PART_BY_CHUNK", "1")
+            second = build(**opts)
+        else:                                # the smallest budget, found in steps, is met by the lean route alone
+            made.append([B.ht_ctx_create(0), None])
+            second, lo, hi = made[-1], 0, 256 << 20
+            while hi - lo > 16384 or second[1] is None:
+                mid = (lo + hi) // 2 if hi - lo > 16384 else hi
+                B.ht_ctx_set_hbm_budget(second[0], mid)
+                try:
+                    if second[1] is not None:
+                        B.ht_graph_destroy(second[1])
+                        second[1] = None
+                    second[1] = B.ht_partition(second[0], V, src, dst, n, **opts)
+                    hi = mid
+                except B.HongtuError as e:
+                    assert e.code == B.HT_ENOMEM
+                    lo = mid
+            B.ht_ctx_set_hbm_budget(second[0], 0)
+        for a, b in zip(*(_arrays(g) for _, g in (first, second))):
+            assert np.array_equal(a, b)
+        X = B.to_matrix(torch.randn(V, 8, generator=torch.Generator().manual_seed(1)))
+        W, outs = torch.eye(8, device="cuda"), []
+        for ctx, g in (first, second):
+            dX, dW, H = B.alloc_matrix(V, 8), torch.empty(8, 8, device="cuda"), B.alloc_matrix(V, 8)
+            B.ht_layer_fwd(ctx, g, 8, 8, B.HT_ACT_NONE, X, W, H, gather_mode=B.HT_GATHER_BUFFER)
+            B.ht_layer_bwd(ctx, g, 8, 8, B.HT_ACT_NONE, X, W, X, dW, dH_in=dX, ckpt_kind=B.HT_CKPT_AGG, gather_mode=B.HT_GATHER_BUFFER)
+            B.ht_sync(ctx)
+            outs.append((H, dX, dW))
+        assert all(torch.equal(a, b) for a, b in zip(*outs))
+    finally:
+        for ctx, g in made:
+            if g is not None:
+                B.ht_graph_destroy(g)
+            B.ht_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("V,E,n,mib,opts", [(500, 3_000, 100, 0.47, dict()), (200_003, 1_000_000, 2000, 153.4, dict()),
+                                            (200_003, 1_000_000, 400, 113.7, dict(cache_policy=B.HT_CACHE_FARTHEST)),
+                                            (200_003, 1_000_000, 400, 107.5, dict(reorder_chunks=True))])
+def test_many_chunks_fit_a_byte_budget(V, E, n, mib, opts):
+    """The budgets are what these calls need when every step goes chunk by chunk and holds no more than four bitmap rows (the
+    graph arrays, two key buffers of 8 bytes per edge, item lists); the bitmaps of all chunks would take up to 600 MiB."""
+    src, dst = inputs.rmat_edges(V, E, 6)
+    ctx = B.ht_ctx_create(0)
+    try:
+        B.ht_ctx_set_hbm_budget(ctx, int(mib * 2 ** 20))
+        B.ht_graph_destroy(B.ht_partition(ctx, V, src.cuda(), dst.cuda(), n, **opts))
+    finally:
+        B.ht_ctx_destroy(ctx)
