@@ -83,7 +83,16 @@ int ht_ctx_destroy(ht_ctx *ctx);
 /* Block until all work enqueued through ctx has finished. */
 int ht_sync(ht_ctx *ctx);
 /* Cap on bytes the library may allocate in HBM through this context
- * (0 = no cap).  Exceeding it makes the allocating call return HT_ENOMEM. */
+ * (0 = no cap).  Exceeding it makes the allocating call return HT_ENOMEM.
+ *
+ * Scratch memory: calls keep the device memory they work in for later calls,
+ * until ht_ctx_destroy.  Where there is room they take more of it than they
+ * need, to run all chunks at once: up to 8 GiB of rows and 4 GiB of partial
+ * sums, and on a graph from its first backward pass on its entries grouped by
+ * source (4 or 8 bytes each); ht_gat_epoch up to 16 GiB more for rows kept
+ * between its passes.  A call that is refused memory, by the cap or by the
+ * device, gives all of that back and is made again chunk by chunk, so no call
+ * fails for memory that an earlier one or a faster pass holds. */
 int ht_ctx_set_hbm_budget(ht_ctx *ctx, int64_t bytes);
 /* Number of ht_epoch calls on this context that ran as one HIP graph launch
  * (ht_plan_opts.use_graph); -1 for a null context. */
@@ -382,8 +391,11 @@ typedef struct {
 
 /* Alg. 1 with GAT layers: forward (ReLU between layers, none after the
  * last), softmax cross-entropy over labelled vertices (labels[v] >= 0, device
- * int32 [V]), backward with each layer's intermediates recomputed from its
- * input, W -= lr dW and a -= lr da.  X [V x dims[0]]: HBM or pinned host.
+ * int32 [V]), backward, W -= lr dW and a -= lr da.  With everything in HBM each
+ * layer's forward pass keeps rows of size O(V) for its backward pass, in up to
+ * 16 GiB of scratch memory (2 x d_out + 5 floats per vertex and layer); beyond
+ * that, and with host-resident tensors, the backward pass recomputes a layer's
+ * intermediates from its input.  X [V x dims[0]]: HBM or pinned host.
  * loss_out: host float, valid on return (the call synchronises). */
 int ht_gat_epoch(ht_ctx *ctx, const ht_graph *g, const ht_gat_model *model, const ht_tensor *X,
                  const int32_t *labels, float *loss_out, ht_stats *stats);

@@ -1,4 +1,5 @@
 // Context, error reporting, allocation accounting, event timers.
+#include <algorithm>
 #include <cstdarg>
 #include <cstdlib>
 
@@ -77,6 +78,8 @@ void ht_dev_free(ht_ctx* ctx, void* p, size_t bytes) {
   if (ctx) ctx->hbm_used -= (int64_t)bytes;
 }
 
+static size_t ht_scratch_size(size_t bytes) { return bytes + bytes / 8 + 256; }   // of a slot that is asked for so many
+
 int ht_scratch(ht_ctx* ctx, int slot, size_t bytes, void** out) {
   if (ctx->static_mode) {
     // a piece of the static array per slot: cut at the slot's first request of this call, kept for its later ones
@@ -105,7 +108,7 @@ int ht_scratch(ht_ctx* ctx, int slot, size_t bytes, void** out) {
       ctx->scratch[slot] = nullptr;
       ctx->scratch_bytes[slot] = 0;
     }
-    size_t want = bytes + bytes / 8 + 256;
+    const size_t want = ht_scratch_size(bytes);
     int rc = ht_dev_alloc(ctx, &ctx->scratch[slot], want);
     if (rc != HT_OK) return rc;
     ctx->scratch_bytes[slot] = want;
@@ -123,6 +126,77 @@ int ht_scratch_release(ht_ctx* ctx, int slot) {
   ctx->scratch_bytes[slot] = 0;
   ++ctx->scratch_gen;
   return HT_OK;
+}
+
+int64_t ht_room(ht_ctx* ctx) {
+  int64_t room = INT64_MAX;
+  size_t free_b = 0, total_b = 0;
+  if (hipMemGetInfo(&free_b, &total_b) == hipSuccess) room = (int64_t)free_b;
+  else (void)hipGetLastError();
+  if (ctx->hbm_budget > 0) room = std::min(room, std::max<int64_t>(0, ctx->hbm_budget - ctx->hbm_used));
+  return room;
+}
+
+ScratchMark::ScratchMark(ht_ctx* c) : ctx(c) { std::copy(c->scratch_bytes, c->scratch_bytes + HT_N_SCRATCH, was); }
+void ScratchMark::undo() {
+  for (int k = 0; k < HT_N_SCRATCH; ++k)
+    if (ctx->scratch_bytes[k] > was[k]) (void)ht_scratch_release(ctx, k);
+}
+
+int ht_scratch_all(ht_ctx* ctx, const std::vector<ScratchWant>& want, int64_t beside) {
+  size_t need[HT_N_SCRATCH] = {};
+  for (const ScratchWant& w : want) need[w.slot] = std::max(need[w.slot], w.bytes);
+  int64_t grow = beside, freed = 0;
+  for (int k = 0; k < HT_N_SCRATCH; ++k)
+    if (need[k] > ctx->scratch_bytes[k]) {
+      grow += (int64_t)ht_scratch_size(need[k]);
+      freed += (int64_t)ctx->scratch_bytes[k];
+    }
+  if (grow == 0) return HT_OK;
+  if (ctx->no_grow || grow - freed > ht_room(ctx)) return HT_ENOMEM;
+  ScratchMark mark(ctx);
+  for (int k = 0; k < HT_N_SCRATCH; ++k) {
+    void* p = nullptr;
+    const int rc = need[k] > 0 ? ht_scratch(ctx, k, need[k], &p) : HT_OK;
+    if (rc == HT_OK) continue;
+    mark.undo();
+    if (rc == HT_ENOMEM) ctx->tight_room = ht_room(ctx);   // (there was room by the figures, and yet none)
+    return rc;
+  }
+  return HT_OK;
+}
+
+int ht_scratch_each(ht_ctx* ctx, const std::vector<ScratchWant>& want) {
+  for (const ScratchWant& w : want) {
+    void* p = nullptr;
+    HT_TRY(ht_scratch(ctx, w.slot, w.bytes, &p));
+  }
+  return HT_OK;
+}
+
+bool ht_may_spend(ht_ctx* ctx) {
+  if (ctx->lean) return false;
+  if (ctx->tight_room < 0) return true;
+  if (ctx->no_grow || ht_room(ctx) <= ctx->tight_room) return false;
+  ctx->tight_room = -1;
+  return true;
+}
+
+int64_t ht_held(const ht_ctx* ctx) {
+  int64_t held = 0;
+  for (size_t b : ctx->scratch_bytes) held += (int64_t)b;
+  for (const ht_graph* g : ctx->graphs) held += (int64_t)(g->by_src.blk.mem.bytes() + g->by_src.mult.bytes());
+  return held;
+}
+
+bool ht_give_back(ht_ctx* ctx) {
+  if (ctx->static_mode || ctx->no_grow || ctx->lean || ht_held(ctx) == 0) return false;
+  (void)hipStreamSynchronize(ctx->stream);
+  for (hipStream_t s : ctx->side) (void)hipStreamSynchronize(s);
+  for (int k = 0; k < HT_N_SCRATCH; ++k) (void)ht_scratch_release(ctx, k);
+  for (const ht_graph* g : ctx->graphs) g->by_src = SourceRows();
+  ++ctx->scratch_gen;      // (captured epochs hold pointers into the lists as well)
+  return true;
 }
 
 int ht_host_scratch(ht_ctx* ctx, int slot, size_t bytes, void** out) {
@@ -243,6 +317,7 @@ int ht_ctx_destroy(ht_ctx* ctx) {
       (void)hipStreamDestroy(ctx->side[i]);
     }
   ht_epoch_ws_free(ctx);
+  for (ht_graph* g : ctx->graphs) g->ctx = nullptr;
   for (int i = 0; i < HT_N_SCRATCH; ++i)
     if (ctx->scratch[i]) ht_dev_free(ctx, ctx->scratch[i], ctx->scratch_bytes[i]);
   for (int i = 0; i < 4; ++i)
@@ -265,6 +340,7 @@ int64_t ht_ctx_graph_launches(const ht_ctx* ctx) { return ctx ? ctx->graph_launc
 int ht_ctx_set_hbm_budget(ht_ctx* ctx, int64_t bytes) {
   if (!ctx || bytes < 0) return HT_EINVAL;
   ctx->hbm_budget = bytes;
+  ctx->tight_room = -1;
   ctx->gat_keep_limit = 0;
   return HT_OK;
 }

@@ -657,6 +657,17 @@ struct RangeWs {
   float *x = nullptr, *part = nullptr, *z_part = nullptr, *q_part = nullptr;
   int64_t n_part = 0;
 };
+// what range_ws will ask for
+void range_wants(const std::vector<GatRange>& ranges, int64_t ld, std::vector<ScratchWant>* want) {
+  int64_t ent = 1, parts = 0;
+  for (const GatRange& r : ranges) {
+    ent = std::max(ent, r.n_ent);
+    parts = std::max(parts, r.it.n_part);
+  }
+  want->push_back({HT_S_GATE, (size_t)ent * 4});
+  want->push_back({HT_S_GATP, (size_t)parts * 3 * 4});
+  want->push_back({HT_S_SPART, (size_t)(parts * ld) * 4});
+}
 int range_ws(ht_ctx* ctx, const std::vector<GatRange>& ranges, int64_t z_ld, int64_t q_ld, RangeWs* ws) {
   int64_t ent = 1;
   ws->n_part = 0;
@@ -903,8 +914,13 @@ int launch_src(ht_ctx* ctx, const GatPass& all, int nvec) {
   });
 }
 
-void release_range_ws(ht_ctx* ctx) {
-  for (int slot : {HT_S_GATE, HT_S_GATP, HT_S_SPART}) (void)ht_scratch_release(ctx, slot);
+// The scratch memory of the dense steps of a backward pass, over V rows in blocks of `step`.
+void dense_wants(int64_t V, int64_t step, int d_in, int d, std::vector<ScratchWant>* want) {
+  for (int64_t rows : {std::min(step, V), V % step}) {
+    want->push_back({HT_S_TNPART, ht_gemm_tn_bytes(rows, d, 4)});
+    want->push_back({HT_S_TNPART, ht_gemm_tn_bytes(rows, d_in, d)});
+  }
+  want->push_back({HT_S_PACKW, (size_t)ht_packed_w_bytes(d, d_in)});
 }
 
 // keep (nullable, everything in HBM): where t, the row values, Q and r go for this epoch's backward pass
@@ -920,15 +936,14 @@ int gat_fwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
   if (on_host(H_in) || out_host) HT_TRY(lk.fork());
   HT_TRY(bind_ws(ctx, g, desc->d_out, keep, &ws));
   const int64_t q_ld = keep ? ws.ld_t : 0;
-  auto ranges = ranges_of(g, (H_out->ld + q_ld + 3) * 4, !out_host);
+  auto ranges = ranges_of(g, (H_out->ld + q_ld + 3) * 4, !out_host && ht_may_spend(ctx));
+  std::vector<ScratchWant> want = {{HT_S_PACKW, (size_t)ht_packed_w_bytes(desc->d_in, desc->d_out)}};
+  range_wants(ranges, H_out->ld + q_ld, &want);
+  const int rc = ht_scratch_all(ctx, want);
+  if (rc == HT_ENOMEM) ranges = ranges_of(g, 0, false);   // less memory at a time: chunk by chunk
+  else HT_TRY(rc);
   RangeWs rw;
-  int rc = range_ws(ctx, ranges, H_out->ld, q_ld, &rw);
-  if (rc == HT_ENOMEM) {   // less memory at a time: chunk by chunk
-    release_range_ws(ctx);
-    ranges = ranges_of(g, 0, false);
-    rc = range_ws(ctx, ranges, H_out->ld, q_ld, &rw);
-  }
-  HT_TRY(rc);
+  HT_TRY(range_ws(ctx, ranges, H_out->ld, q_ld, &rw));
   HT_TRY(prepare(ctx, g, desc, H_in, W, a_dst, a_src, &ws, local, tm, &lk));
   float* obuf[2] = {nullptr, nullptr};
   hipEvent_t ev_ofree[2] = {nullptr, nullptr};
@@ -967,10 +982,10 @@ int gat_fwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
   return HT_OK;
 }
 
-// The source pass of a layer of width d can take all vertices at once (the list by source was tried).
+// The source pass of a layer of width d can take all vertices at once (with the list by source, once that is there).
 bool src_fits(const ht_graph* g, int d, bool kept) {
   const int64_t ld = ht_row_pitch(d, true);
-  return g->by_src.ok && g->V * ld * 4 * (kept ? 1 : 2) <= GAT_DIRECT_BYTES && g->by_src.items.n_part * (ld + 4) * 4 <= GAT_RANGE_BYTES;
+  return g->V * ld * 4 * (kept ? 1 : 2) <= GAT_DIRECT_BYTES && g->by_src.items.n_part * (ld + 4) * 4 <= GAT_RANGE_BYTES;
 }
 
 // Backward over the rows with everything in HBM, all vertices at once: dz of all rows, the destination pass over ranges of chunks
@@ -986,35 +1001,43 @@ int gat_bwd_rows_direct(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc,
   const int d = desc->d_out, nvec = (d + 3) / 4, sc_col = (int)ws.ld_t;
   const size_t mat = (size_t)V * ws.ld_t * 4;
   if (V <= 0) return HT_OK;
-  HT_TRY(ht_graph_by_source(ctx, g));
-  if (!src_fits(g, d, keep != nullptr)) return HT_OK;
+  if (!ht_may_spend(ctx) || !src_fits(g, d, keep != nullptr)) return HT_OK;
   const SourceRows& S = g->by_src;
   float *dz = nullptr, *Q = keep ? keep->Q : nullptr;
   float* s_part = nullptr;
   std::vector<GatRange> ranges;
   RangeWs rw;
+  ScratchMark mark(ctx);
   auto take = [&]() -> int {
-    HT_TRY(ht_graph_by_source_mult(ctx, g));
-    HT_TRY(ht_scratch(ctx, HT_S_DZCHUNK, mat, (void**)&dz));
-    // the partial sums of both passes share a slot, one after the other
-    if (S.items.n_part > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)(S.items.n_part * ld_dt) * 4, (void**)&s_part));
+    std::vector<ScratchWant> want = {{HT_S_DZCHUNK, mat}};
     if (!keep) {
-      HT_TRY(ht_scratch(ctx, HT_S_ACHUNK, mat, (void**)&Q));
       ranges = ranges_of(g, (ws.ld_t + 3) * 4, true);
-      HT_TRY(range_ws(ctx, ranges, 0, ws.ld_t, &rw));
-      if (S.items.n_part > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)(S.items.n_part * ld_dt) * 4, (void**)&s_part));
+      want.push_back({HT_S_ACHUNK, mat});
+      want.push_back({HT_S_PACKW, (size_t)ht_packed_w_bytes(desc->d_in, d)});
+      range_wants(ranges, ws.ld_t, &want);
     }
     // the dense steps behind this pass add to the caller's tensors: nothing may fail there for want of memory that is held here
-    HT_TRY(ht_gemm_reserve(ctx, V, d, 4));
-    return ht_gemm_reserve(ctx, V, desc->d_in, d);
+    dense_wants(V, BLOCK_HBM, desc->d_in, d, &want);
+    HT_TRY(ht_scratch_all(ctx, want, ht_graph_by_source_bytes(g) + (g->merged && !S.mult.p ? g->n_unique * 4 : 0)));
+    HT_TRY(ht_graph_by_source(ctx, g));
+    if (!src_fits(g, d, keep != nullptr)) return HT_ENOMEM;
+    HT_TRY(ht_graph_by_source_mult(ctx, g));
+    // (the partial sums of both passes share a slot, one after the other)
+    want.push_back({HT_S_SPART, (size_t)(S.items.n_part * ld_dt) * 4});
+    return ht_scratch_all(ctx, want);
   };
   const int rc = take();
   if (rc == HT_ENOMEM) {
-    release_range_ws(ctx);
-    for (int slot : {HT_S_DZCHUNK, HT_S_ACHUNK}) (void)ht_scratch_release(ctx, slot);
+    mark.undo();
     return HT_OK;
   }
   HT_TRY(rc);
+  HT_TRY(ht_scratch(ctx, HT_S_DZCHUNK, mat, (void**)&dz));
+  if (!keep) {
+    HT_TRY(ht_scratch(ctx, HT_S_ACHUNK, mat, (void**)&Q));
+    HT_TRY(range_ws(ctx, ranges, 0, ws.ld_t, &rw));
+  }
+  HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)(S.items.n_part * ld_dt) * 4, (void**)&s_part));
   *done = true;
   if (!keep) HT_TRY(prepare(ctx, g, desc, H_in, W, a_dst, a_src, &ws, local, tm, lk));
   for (const GatRange& r : ranges) {
@@ -1048,7 +1071,7 @@ int gat_bwd_rows_direct(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc,
 int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const ht_tensor* H_in, const float* W,
                  const float* a_dst, const float* a_src, const ht_tensor* H_out, const ht_tensor* dH_out,
                  ht_tensor* dH_in, float* dW, float* da_dst, float* da_src, const GatKeep* keep, ht_stats* local, Timer* tm,
-                 bool dhin_is_zero) {
+                 bool dhin_is_zero, bool* changed) {
   HT_TRY(check_desc(ctx, desc));
   HT_TRY(check(ctx, g, desc, H_in, desc->d_in, "H_in"));
   HT_TRY(check(ctx, g, desc, H_out, desc->d_out, "H_out"));
@@ -1179,6 +1202,12 @@ int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
     HT_TRY(ht_scratch(ctx, HT_S_LINK1, (size_t)brows * dH_in->ld * 4 * 2, (void**)&sD[0]));
     sD[1] = sD[0] + brows * dH_in->ld;
   }
+  {
+    std::vector<ScratchWant> want;
+    dense_wants(g->V, step, desc->d_in, d, &want);
+    HT_TRY(ht_scratch_each(ctx, want));
+  }
+  *changed = true;    // dH_in is added to from here on
   // the staging memory was used by the earlier phases: copies into it start behind their last reader
   if (lk.used) HT_TRY(lk.fork());
   bool first = true;
@@ -1232,6 +1261,20 @@ int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
   return HT_OK;
 }
 
+// The end of a layer call.
+int gat_done(ht_ctx* ctx, int rc, ht_stats* local, Timer* tm, std::chrono::steady_clock::time_point t0, ht_stats* stats) {
+  hipError_t e = hipStreamSynchronize(ctx->stream);
+  if (rc == HT_OK && e == hipSuccess) rc = tm->resolve();
+  ctx->ev_next = 0;
+  if (rc != HT_OK) return rc;
+  HT_HIP(ctx, e);
+  if (stats) {
+    local->t_total_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
+    *stats = *local;
+  }
+  return HT_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1242,20 +1285,13 @@ int ht_gat_layer_fwd(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, co
   if (!g || !desc || !H_in || !H_out || !W || !a_dst || !a_src) return ht_set_err(ctx, HT_EINVAL, "ht_gat_layer_fwd: null argument");
   if (g->ctx != ctx) return ht_set_err(ctx, HT_ESTATE, "graph belongs to another context");
   HT_HIP(ctx, hipSetDevice(ctx->device));
-  auto t0 = std::chrono::steady_clock::now();
-  ht_stats local{};
-  Timer tm(ctx, ctx->stream, stats != nullptr);
-  int rc = gat_fwd_impl(ctx, g, desc, H_in, W, a_dst, a_src, H_out, nullptr, &local, &tm, 0);
-  hipError_t e = hipStreamSynchronize(ctx->stream);
-  if (rc == HT_OK && e == hipSuccess) rc = tm.resolve();
-  ctx->ev_next = 0;
-  if (rc != HT_OK) return rc;
-  HT_HIP(ctx, e);
-  if (stats) {
-    local.t_total_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
-    *stats = local;
-  }
-  return HT_OK;
+  return ht_with_room(ctx, [&]() -> int {
+    auto t0 = std::chrono::steady_clock::now();
+    ht_stats local{};
+    Timer tm(ctx, ctx->stream, stats != nullptr);
+    int rc = gat_fwd_impl(ctx, g, desc, H_in, W, a_dst, a_src, H_out, nullptr, &local, &tm, 0);
+    return gat_done(ctx, rc, &local, &tm, t0, stats);
+  });
 }
 
 int ht_gat_layer_bwd(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const ht_tensor* H_in, const float* W,
@@ -1266,30 +1302,24 @@ int ht_gat_layer_bwd(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, co
     return ht_set_err(ctx, HT_EINVAL, "ht_gat_layer_bwd: null argument");
   if (g->ctx != ctx) return ht_set_err(ctx, HT_ESTATE, "graph belongs to another context");
   HT_HIP(ctx, hipSetDevice(ctx->device));
-  auto t0 = std::chrono::steady_clock::now();
-  ht_stats local{};
-  Timer tm(ctx, ctx->stream, stats != nullptr);
-  int rc = gat_bwd_impl(ctx, g, desc, H_in, W, a_dst, a_src, H_out, dH_out, dH_in, dW, da_dst, da_src, nullptr, &local, &tm, false);
-  hipError_t e = hipStreamSynchronize(ctx->stream);
-  if (rc == HT_OK && e == hipSuccess) rc = tm.resolve();
-  ctx->ev_next = 0;
-  if (rc != HT_OK) return rc;
-  HT_HIP(ctx, e);
-  if (stats) {
-    local.t_total_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
-    *stats = local;
-  }
-  return HT_OK;
+  bool changed = false;
+  return ht_with_room(ctx, [&]() -> int {
+    auto t0 = std::chrono::steady_clock::now();
+    ht_stats local{};
+    Timer tm(ctx, ctx->stream, stats != nullptr);
+    int rc = gat_bwd_impl(ctx, g, desc, H_in, W, a_dst, a_src, H_out, dH_out, dH_in, dW, da_dst, da_src, nullptr, &local, &tm, false, &changed);
+    return gat_done(ctx, rc, &local, &tm, t0, stats);
+  }, &changed);
 }
 
-// Alg. 1 with GAT layers: forward over the layers (only the layer outputs are kept), softmax
-// cross-entropy on the labelled vertices, backward layer by layer with every layer's
-// intermediates recomputed from its input, SGD step on W^l and a^l.  With res_h = HT_RES_HOST
+// Alg. 1 with GAT layers: forward over the layers, softmax cross-entropy on the labelled
+// vertices, backward layer by layer, SGD step on W^l and a^l.  Beside the layer outputs a
+// forward pass keeps rows of size O(V) for its backward pass where there is room for them
+// (GatKeep); elsewhere every layer's intermediates are recomputed from its input.  With res_h = HT_RES_HOST
 // the layer outputs h^1..h^{L-1} and their gradients live in pinned host memory (Alg. 1 keeps
 // h^l and grad h^l on the CPU); the logits h^L and their gradient stay in HBM for the loss.
-int ht_gat_epoch(ht_ctx* ctx, const ht_graph* g, const ht_gat_model* model, const ht_tensor* X, const int32_t* labels,
-                 float* loss_out, ht_stats* stats) {
-  if (!ctx) return HT_EINVAL;
+static int gat_epoch_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_model* model, const ht_tensor* X, const int32_t* labels,
+                          float* loss_out, ht_stats* stats) {
   if (!g || !model || !X || !labels || !loss_out) return ht_set_err(ctx, HT_EINVAL, "ht_gat_epoch: null argument");
   if (g->ctx != ctx) return ht_set_err(ctx, HT_ESTATE, "graph belongs to another context");
   const int L = model->n_layers;
@@ -1350,14 +1380,19 @@ int ht_gat_epoch(ht_ctx* ctx, const ht_graph* g, const ht_gat_model* model, cons
   std::vector<GatKeep> keep;
   if (!h_host && X->loc == HT_LOC_DEVICE && V > 0) {
     size_t kf = 0;
-    HT_TRY(ht_graph_by_source(ctx, g));
     for (int l = 1; l <= L; ++l) kf += (size_t)V * (2 * ht_row_pitch(model->dims[l], true) + 5) + 7 * 32;
     float* kp = nullptr;
-    bool room = kf * 4 <= (size_t)GAT_KEEP_BYTES && (ctx->gat_keep_limit == 0 || kf * 4 < ctx->gat_keep_limit);
-    for (int l = 1; l <= L; ++l) room = room && src_fits(g, model->dims[l], true);
+    bool room = kf * 4 <= (size_t)GAT_KEEP_BYTES && ht_may_spend(ctx) &&
+                (ctx->gat_keep_limit == 0 || kf * 4 < ctx->gat_keep_limit || ht_room(ctx) > ctx->gat_keep_room);
     if (room) {
-      const int rc = ht_scratch(ctx, HT_S_GATKEEP, kf * 4, (void**)&kp);
+      ScratchMark mark(ctx);
+      int rc = ht_scratch_all(ctx, {{HT_S_GATKEEP, kf * 4}}, ht_graph_by_source_bytes(g));
+      if (rc == HT_OK) rc = ht_graph_by_source(ctx, g);
       if (rc != HT_OK && rc != HT_ENOMEM) return rc;
+      room = rc == HT_OK;
+      for (int l = 1; l <= L; ++l) room = room && src_fits(g, model->dims[l], true);
+      if (room) HT_TRY(ht_scratch(ctx, HT_S_GATKEEP, kf * 4, (void**)&kp));
+      else mark.undo();
     }
     auto cut = [&](size_t n) { float* p = kp; kp += (n + 31) & ~(size_t)31; return p; };
     for (int l = 1; l <= L && kp; ++l) {
@@ -1368,6 +1403,7 @@ int ht_gat_epoch(ht_ctx* ctx, const ht_graph* g, const ht_gat_model* model, cons
       keep.push_back(k);
     }
   }
+  bool changed = false;   // (only this call's own buffers)
   auto passes = [&]() -> int {
     for (int l = 0; l < L; ++l) {
       ht_gat_desc d{model->dims[l], model->dims[l + 1], l < L - 1 ? HT_ACT_RELU : HT_ACT_NONE, model->slope};
@@ -1380,7 +1416,7 @@ int ht_gat_epoch(ht_ctx* ctx, const ht_graph* g, const ht_gat_model* model, cons
     for (int l = L - 1; l >= 0; --l) {
       ht_gat_desc d{model->dims[l], model->dims[l + 1], l < L - 1 ? HT_ACT_RELU : HT_ACT_NONE, model->slope};
       HT_TRY(gat_bwd_impl(ctx, g, &d, l == 0 ? X : &h[l], model->W[l], model->a_dst[l], model->a_src[l], &h[l + 1], &gh[l + 1],
-                          l > 0 ? &gh[l] : nullptr, dW[l], dad[l], das[l], keep.empty() ? nullptr : &keep[l], &local, &tm, true));
+                          l > 0 ? &gh[l] : nullptr, dW[l], dad[l], das[l], keep.empty() ? nullptr : &keep[l], &local, &tm, true, &changed));
     }
     return HT_OK;
   };
@@ -1389,6 +1425,7 @@ int ht_gat_epoch(ht_ctx* ctx, const ht_graph* g, const ht_gat_model* model, cons
     (void)fail(rc);
     ctx->gat_keep_limit = ctx->scratch_bytes[HT_S_GATKEEP] * 8 / 9;      // (a slot is an eighth larger than asked for)
     (void)ht_scratch_release(ctx, HT_S_GATKEEP);
+    ctx->gat_keep_room = ht_room(ctx);
     keep.clear();
     local = ht_stats{};
     tm.ev.clear();
@@ -1421,6 +1458,13 @@ int ht_gat_epoch(ht_ctx* ctx, const ht_graph* g, const ht_gat_model* model, cons
     *stats = local;
   }
   return HT_OK;
+}
+
+int ht_gat_epoch(ht_ctx* ctx, const ht_graph* g, const ht_gat_model* model, const ht_tensor* X, const int32_t* labels,
+                 float* loss_out, ht_stats* stats) {
+  if (!ctx) return HT_EINVAL;
+  // (the caller's parameters change in the last launch, behind everything that takes memory)
+  return ht_with_room(ctx, [&] { return gat_epoch_impl(ctx, g, model, X, labels, loss_out, stats); });
 }
 
 }  // extern "C"

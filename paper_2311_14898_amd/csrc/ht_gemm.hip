@@ -684,12 +684,43 @@ int ht_gemm_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const f
   return launch_tn(ctx, st, A, lda, B, ldb, C, M, K, N, rows, slices, nullptr, M, accumulate);
 }
 
-int ht_gemm_reserve(ht_ctx* ctx, int64_t M, int32_t K, int32_t N) {
+size_t ht_gemm_tn_bytes(int64_t M, int32_t K, int32_t N) {
   int64_t rows, slices;
   SliceRule{tn_tiles(K, N), true}.cut(std::max<int64_t>(M, 1), &rows, &slices);
-  void* p = nullptr;
-  HT_TRY(ht_scratch(ctx, HT_S_TNPART, (size_t)(slices * K * N) * 4, &p));
-  return ht_scratch(ctx, HT_S_PACKW, (size_t)std::max(ht_packed_w_bytes(K, N), ht_packed_w_bytes(N, K)), &p);
+  return (size_t)(slices * K * N) * 4;
+}
+
+namespace {
+
+// [g0, g1) and its slices: the row groups that one launch of ht_gemm_tn_groups takes
+size_t next_groups(const SliceRule& rule, int32_t K, int32_t N, const std::vector<int64_t>& groups, size_t g0, int64_t* slices) {
+  const int64_t most = std::max<int64_t>(1024, std::min<int64_t>(32768, ((int64_t)1 << 30) / ((int64_t)K * N * 4)));   // slices per launch
+  size_t g1 = g0;
+  *slices = 0;
+  for (; g1 < groups.size() / 2; ++g1) {
+    int64_t rows, n;
+    rule.cut(groups[2 * g1 + 1] - groups[2 * g1], &rows, &n);
+    if (g1 > g0 && *slices + n > most) break;
+    *slices += n;
+  }
+  return g1;
+}
+
+}  // namespace
+
+void ht_gemm_groups_wants(int32_t K, int32_t N, const std::vector<int64_t>& groups, std::vector<ScratchWant>* want) {
+  const size_t G = groups.size() / 2;
+  if (G <= 1) {
+    want->push_back({HT_S_TNPART, ht_gemm_tn_bytes(G ? groups[1] - groups[0] : 0, K, N)});
+    return;
+  }
+  const SliceRule rule{tn_tiles(K, N)};
+  for (size_t g0 = 0; g0 < G;) {
+    int64_t slices;
+    g0 = next_groups(rule, K, N, groups, g0, &slices);
+    want->push_back({HT_S_TNPART, (size_t)(slices * K * N) * 4});
+    want->push_back({HT_S_TNTAB, (size_t)slices * 16});
+  }
 }
 
 // The row groups' sums one after the other, as ht_gemm_tn called once per group would add them, in as few launches as the
@@ -704,18 +735,11 @@ int ht_gemm_tn_groups(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, 
   if ((lda & 3) || (ldb & 3)) return ht_set_err(ctx, HT_ESHAPE, "gemm: row pitch must be a multiple of 4");
   if (K <= 0 || N <= 0) return HT_OK;
   const SliceRule rule{tn_tiles(K, N)};
-  const int64_t most = std::max<int64_t>(1024, std::min<int64_t>(32768, ((int64_t)1 << 30) / ((int64_t)K * N * 4)));   // slices per launch
   int64_t all = 0;
   for (size_t k = 0; k < G; ++k) all += groups[2 * k + 1] - groups[2 * k];
   for (size_t g0 = 0; g0 < G;) {
-    size_t g1 = g0;
-    int64_t total = 0;
-    for (; g1 < G; ++g1) {
-      int64_t rows, n;
-      rule.cut(groups[2 * g1 + 1] - groups[2 * g1], &rows, &n);
-      if (g1 > g0 && total + n > most) break;
-      total += n;
-    }
+    int64_t total;
+    const size_t g1 = next_groups(rule, K, N, groups, g0, &total);
     int64_t* tab = nullptr;
     HT_TRY(ht_scratch(ctx, HT_S_TNTAB, (size_t)total * 16, (void**)&tab));
     k_slice_table<<<(unsigned)(g1 - g0), 256, 0, st>>>(d_groups + 2 * g0, rule, tab);

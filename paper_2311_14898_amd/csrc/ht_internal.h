@@ -17,6 +17,7 @@
 constexpr int HT_SEG = 256;
 
 struct EpochWs;
+struct ht_graph;
 
 enum {
   HT_S_PACKW = 0, HT_S_TNPART, HT_S_LOSS, HT_S_ACHUNK, HT_S_OCHUNK, HT_S_ZCHUNK, HT_S_DZCHUNK, HT_S_DACHUNK,
@@ -64,7 +65,12 @@ struct ht_ctx {
   int agg_phases = 1;     // HT_AGG_PHASES: slabs are spread over this many consecutive launches
   int64_t link_block_rows = (int64_t)1 << 20;   // HT_LINK_BLOCK_ROWS: rows per staged block of a host-resident tensor (GAT path)
   int agg_variant = 0;  // 0: feature slabs per XCD; 1: full-width rows per wave (HT_AGG_VARIANT, for A/B runs)
-  size_t gat_keep_limit = 0;   // a GAT epoch that kept this many bytes between its passes ran out of memory (0: none did)
+  std::vector<ht_graph*> graphs;   // the graphs of this context (each may hold a by-source list)
+  bool lean = false;           // the call is being made again with as little memory as it can do with (ht_with_room)
+  bool no_grow = false;        // inside a stream capture: nothing may be allocated
+  int64_t tight_room = -1;     // room that was left after the last such call (-1: none since memory was plentiful)
+  size_t gat_keep_limit = 0;   // a GAT epoch that kept this many bytes between its passes ran out of memory (0: none did) ...
+  int64_t gat_keep_room = 0;   // ... and had this much room without them
   int fuse_update = 0;  // HT_FUSE_UPDATE=1: layers that keep no aggregate run aggregate + transform as one kernel (A/B)
   int n_threads = 0;  // host threads for CPU-side accumulation (0 = chosen on first use)
 };
@@ -99,6 +105,42 @@ void ht_dev_free(ht_ctx* ctx, void* p, size_t bytes);
 int ht_scratch(ht_ctx* ctx, int slot, size_t bytes, void** out);
 // Gives a slot's memory back (after the work in flight).
 int ht_scratch_release(ht_ctx* ctx, int slot);
+// Bytes that can still be allocated: by the byte budget and by the device's free memory.
+int64_t ht_room(ht_ctx* ctx);
+
+// Several slots that a pass takes together.
+struct ScratchWant { int slot; size_t bytes; };
+// All of them at these sizes, or HT_ENOMEM and none of them larger than before.  What has to grow is looked up in ht_room first (with
+// `beside` further bytes that the caller is about to take), so that a pass that does not fit frees and allocates nothing, call after call.
+int ht_scratch_all(ht_ctx* ctx, const std::vector<ScratchWant>& want, int64_t beside = 0);
+// The slots one after the other, whatever it takes (HT_ENOMEM: some of them).
+int ht_scratch_each(ht_ctx* ctx, const std::vector<ScratchWant>& want);
+// Releases the slots that have grown since it was made.
+struct ScratchMark {
+  ht_ctx* ctx;
+  size_t was[HT_N_SCRATCH];
+  explicit ScratchMark(ht_ctx* c);
+  void undo();
+};
+
+// Memory that only makes calls faster (all chunks at once, by-source lists, rows kept between passes) must not be what a call is
+// refused for.  Passes that can do with less ask ht_may_spend first, and fall back when they are refused memory; a call that is refused
+// all the same is made again once everything the context can do without was given back (scratch slots, by-source lists), with `lean`
+// set.  From then on nothing is spent until there is more room than was left by that call.
+bool ht_may_spend(ht_ctx* ctx);
+bool ht_give_back(ht_ctx* ctx);   // false: there was nothing to give back
+int64_t ht_held(const ht_ctx* ctx);   // bytes that ht_give_back would free
+// `changed`: the call has begun to change what the caller handed in, and cannot be made again.
+template <class F>
+int ht_with_room(ht_ctx* ctx, F&& call, const bool* changed = nullptr) {
+  int rc = call();
+  if (rc != HT_ENOMEM || (changed && *changed) || !ht_give_back(ctx)) return rc;
+  ctx->lean = true;
+  rc = call();
+  ctx->lean = false;
+  if (rc == HT_OK) ctx->tight_room = ht_room(ctx);
+  return rc;
+}
 // Grow-only pinned host scratch.
 constexpr int HT_HS_READBACK = 3;
 int ht_host_scratch(ht_ctx* ctx, int slot, size_t bytes, void** out);
@@ -232,9 +274,9 @@ struct ChunkMeta {
 };
 
 // The whole graph's entries grouped by source (destinations ascending), for backward passes that read grad a of all
-// destinations at once.  Built at the first such pass.
+// destinations at once.  Built at the first such pass that has memory for it; the others go chunk by chunk.
 struct SourceRows {
-  bool tried = false, ok = false;   // ok stays false when there was no memory for it: those passes go chunk by chunk
+  bool ok = false;
   DevBlock blk;
   DevArr<int32_t> idx;         // destination of each entry
   DevArr<float> w;             // multiplicity * s[destination] (merged graphs; others look s up)
@@ -298,8 +340,10 @@ struct ht_graph {
   int64_t hbm_bytes() const;
 };
 
-// Makes g->by_src if it was not tried yet.
+// Makes g->by_src if it is not there (HT_ENOMEM: it may not have, or there is no memory for it).
 int ht_graph_by_source(ht_ctx* ctx, const ht_graph* g);
+// Bytes that making it takes (0: it is there).
+int64_t ht_graph_by_source_bytes(const ht_graph* g);
 // Makes g->by_src.mult of a merged graph whose by_src is there (HT_ENOMEM: no memory for it).
 int ht_graph_by_source_mult(ht_ctx* ctx, const ht_graph* g);
 
@@ -392,8 +436,10 @@ int ht_gemm_nt(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const f
 int ht_gemm_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
                int64_t M, int32_t K, int32_t N, int accumulate);
 
-// Takes the scratch memory of ht_gemm_tn and ht_gemm_nt calls of up to M rows: no later call of these fails for want of it.
-int ht_gemm_reserve(ht_ctx* ctx, int64_t M, int32_t K, int32_t N);
+// Bytes of the partial tiles (slot HT_S_TNPART) of an ht_gemm_tn call over M rows.
+size_t ht_gemm_tn_bytes(int64_t M, int32_t K, int32_t N);
+// The scratch memory of an ht_gemm_tn_groups call.
+void ht_gemm_groups_wants(int32_t K, int32_t N, const std::vector<int64_t>& groups, std::vector<ScratchWant>* want);
 // C[K x N] = sum over the row groups [groups[2g], groups[2g+1]) of A^T B, added group by group (d_groups: the same on the device).
 int ht_gemm_tn_groups(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int32_t K,
                       int32_t N, const std::vector<int64_t>& groups, const int64_t* d_groups);

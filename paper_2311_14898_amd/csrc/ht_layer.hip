@@ -112,6 +112,7 @@ struct Run {
   int layer = 0; // index into the per-layer statistics
   bool dhin_fresh = false;  // dH_in counts as zeros: a host tensor holds them (leaving rows may be stored, not added), a device
                             // tensor holds anything and every row is written or cleared first
+  bool changed = false;     // the caller's gradients may have been added to: the call cannot be made again
   Run(ht_ctx* c, const ht_graph* gr, ht_stats* s, bool timed) : ctx(c), g(gr), tm(c, c->stream, timed), st(s) {}
 };
 
@@ -312,11 +313,23 @@ int agg_range(Run& R, const ChunkRange& r, const float* src, int64_t src_ld, int
   return HT_OK;
 }
 
-// Aggregates of all destinations: out row = vertex.
-int agg_all(Run& R, const float* src, int64_t src_ld, int d, float* out, int64_t out_ld, int relu) {
-  const auto ranges = chunk_ranges(R.g, out_ld * 4, 0, HT_RANGE_BYTES);
+int64_t most_parts(const std::vector<ChunkRange>& ranges) {
   int64_t parts = 0;
   for (const ChunkRange& r : ranges) parts = std::max(parts, r.items.n_part);
+  return parts;
+}
+
+// Aggregates of all destinations: out row = vertex.
+int agg_all(Run& R, const float* src, int64_t src_ld, int d, float* out, int64_t out_ld, int relu) {
+  auto ranges = chunk_ranges(R.g, out_ld * 4, 0, ht_may_spend(R.ctx) ? HT_RANGE_BYTES : 0);
+  int64_t parts = most_parts(ranges);
+  const int rc = ht_scratch_all(R.ctx, {{HT_S_SPART, (size_t)(parts * out_ld) * 4}});
+  if (rc == HT_ENOMEM) {   // less memory at a time: chunk by chunk
+    ranges = chunk_ranges(R.g, out_ld * 4, 0, 0);
+    parts = most_parts(ranges);
+  } else {
+    HT_TRY(rc);
+  }
   float* partial = nullptr;
   if (parts > 0) HT_TRY(ht_scratch(R.ctx, HT_S_SPART, (size_t)parts * out_ld * 4, (void**)&partial));
   for (const ChunkRange& r : ranges) HT_TRY(agg_range(R, r, src, src_ld, d, out + r.row0 * out_ld, out_ld, relu, partial));
@@ -337,13 +350,22 @@ int layer_fwd_direct(Run& R, const ht_layer_desc* desc, const ht_tensor* H_in, c
     R.st->gemm_flops += 2.0 * rows * di * dn;
     return HT_OK;
   };
-  // (the allocation-free call's array also holds the packed copy of W)
-  const int64_t cap = ctx->static_mode ? (int64_t)HT_STATIC_SCRATCH_BYTES - ht_packed_w_bytes(di, dn) - 512 : HT_RANGE_BYTES;
-  const auto ranges = chunk_ranges(g, a_ld * 4, A_ckpt ? 0 : a_ld * 4, cap);
+  std::vector<ChunkRange> ranges;
   int64_t parts = 0, rows = 0;
-  for (const ChunkRange& r : ranges) {
-    parts = std::max(parts, r.items.n_part);
-    rows = std::max(rows, r.rows);
+  auto plan = [&](int64_t cap) {
+    ranges = chunk_ranges(g, a_ld * 4, A_ckpt ? 0 : a_ld * 4, cap);
+    parts = most_parts(ranges);
+    rows = 0;
+    for (const ChunkRange& r : ranges) rows = std::max(rows, r.rows);
+  };
+  // (the allocation-free call's array also holds the packed copy of W)
+  if (ctx->static_mode) plan((int64_t)HT_STATIC_SCRATCH_BYTES - ht_packed_w_bytes(di, dn) - 512);
+  else {
+    plan(ht_may_spend(ctx) ? HT_RANGE_BYTES : 0);
+    const int rc = ht_scratch_all(ctx, {{HT_S_SPART, (size_t)(parts * a_ld) * 4}, {HT_S_ACHUNK, A_ckpt ? 0 : (size_t)(rows * a_ld) * 4},
+                                        {HT_S_PACKW, (size_t)ht_packed_w_bytes(di, dn)}});
+    if (rc == HT_ENOMEM) plan(0);   // less memory at a time: chunk by chunk
+    else HT_TRY(rc);
   }
   float *partial = nullptr, *a_rows = nullptr;
   if (parts > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)parts * a_ld * 4, (void**)&partial));
@@ -715,20 +737,22 @@ int agg_by_source(Run& R, const float* src, int64_t src_ld, int d, float* dst, i
   R.st->spmm_bwd_alg_bytes += agg_all_bytes(g, g->Ep, g->V, d);
   return HT_OK;
 }
-// The by-source list and its partial sums at row pitch ld, if there is memory for them.
-int by_source_ready(Run& R, int64_t ld, float** partial, bool* ok) {
-  *partial = nullptr;
-  *ok = false;
-  HT_TRY(ht_graph_by_source(R.ctx, R.g));
-  const GraphItems& it = R.g->by_src.items;
-  if (!R.g->by_src.ok || it.n_part * ld * 4 > HT_RANGE_BYTES) return HT_OK;
-  if (it.n_part > 0) {
-    const int rc = ht_scratch(R.ctx, HT_S_SPART, (size_t)it.n_part * ld * 4, (void**)partial);
-    if (rc == HT_ENOMEM) return HT_OK;
-    HT_TRY(rc);
+// A by-source pass over rows of pitch ld keeps this many bytes of partial sums (of a list that is there).
+size_t by_source_parts(const ht_graph* g, int64_t ld) { return (size_t)(g->by_src.items.n_part * ld) * 4; }
+// Takes the slots and the by-source list, or HT_ENOMEM and nothing larger than before.  parts: bytes of other partial sums that share
+// their slot.
+int take_by_source(ht_ctx* ctx, const ht_graph* g, std::vector<ScratchWant> want, int64_t ld, size_t parts) {
+  if (!ht_may_spend(ctx) || by_source_parts(g, ld) > (size_t)HT_RANGE_BYTES) return HT_ENOMEM;
+  ScratchMark mark(ctx);
+  int rc = ht_scratch_all(ctx, want, ht_graph_by_source_bytes(g));
+  if (rc == HT_OK) rc = ht_graph_by_source(ctx, g);
+  if (rc == HT_OK) {
+    const size_t mine = by_source_parts(g, ld);
+    want.push_back({HT_S_SPART, std::max(mine, parts)});
+    rc = mine > (size_t)HT_RANGE_BYTES ? HT_ENOMEM : ht_scratch_all(ctx, want);
   }
-  *ok = true;
-  return HT_OK;
+  if (rc == HT_ENOMEM) mark.undo();
+  return rc;
 }
 
 // Scratch memory up to which a backward pass holds dz and grad a of all vertices at once.
@@ -752,28 +776,27 @@ int layer_bwd_direct(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, c
   float *a_all = nullptr, *dz_all = nullptr, *da_all = nullptr, *partial = nullptr;
   const size_t a_bytes = agg_ckpt ? 0 : (size_t)V * a_ld * 4, dz_bytes = relu ? (size_t)V * ld_o * 4 : 0,
                da_bytes = dH_in ? (size_t)V * ld_i * 4 : 0;
-  if ((int64_t)(a_bytes + dz_bytes + da_bytes) > HT_DIRECT_BYTES) return HT_OK;
-  auto get = [&](int slot, size_t bytes, float** p) { return bytes ? ht_scratch(ctx, slot, bytes, (void**)p) : HT_OK; };
-  for (int rc : {get(HT_S_ACHUNK, a_bytes, &a_all), get(HT_S_DZCHUNK, dz_bytes, &dz_all), get(HT_S_DACHUNK, da_bytes, &da_all)}) {
-    if (rc == HT_ENOMEM) return HT_OK;
-    HT_TRY(rc);
-  }
-  if (dH_in) {
-    bool ok = false;
-    HT_TRY(by_source_ready(R, dH_in->ld, &partial, &ok));
-    if (!ok) return HT_OK;
-  }
+  if (!ht_may_spend(ctx) || (int64_t)(a_bytes + dz_bytes + da_bytes) > HT_DIRECT_BYTES) return HT_OK;
+  // everything that this pass will ask for: nothing may fail once dH_in is being added to
+  const size_t fwd_parts = agg_ckpt ? 0 : (size_t)(most_parts(chunk_ranges(g, a_ld * 4, 0, HT_RANGE_BYTES)) * a_ld) * 4;
+  std::vector<ScratchWant> want = {{HT_S_ACHUNK, a_bytes}, {HT_S_DZCHUNK, dz_bytes}, {HT_S_DACHUNK, da_bytes}, {HT_S_SPART, fwd_parts},
+                                   {HT_S_PACKW, (size_t)std::max(ht_packed_w_bytes(di, dn), ht_packed_w_bytes(dn, di))}};
+  ht_gemm_groups_wants(di, dn, g->dense_groups, &want);
+  const int rc = dH_in ? take_by_source(ctx, g, want, dH_in->ld, fwd_parts) : ht_scratch_all(ctx, want);
+  if (rc == HT_ENOMEM) return HT_OK;
+  HT_TRY(rc);
+  auto get = [&](int slot, size_t bytes, float** p) { return bytes ? ht_scratch(ctx, slot, bytes, (void**)p) : (int)HT_OK; };
+  HT_TRY(get(HT_S_ACHUNK, a_bytes, &a_all));
+  HT_TRY(get(HT_S_DZCHUNK, dz_bytes, &dz_all));
+  HT_TRY(get(HT_S_DACHUNK, da_bytes, &da_all));
+  if (dH_in) HT_TRY(get(HT_S_SPART, by_source_parts(g, dH_in->ld), &partial));
   *done = true;
   const float* a_rows = ckpt->ptr;
   if (!agg_ckpt) {   // pure recomputation: aggregate again from h^l
     HT_TRY(agg_all(R, ckpt->ptr, ckpt->ld, di, a_all, a_ld, 0));
     a_rows = a_all;
-    if (dH_in) {     // (the forward aggregation's partial sums may have moved the slot)
-      bool ok = false;
-      HT_TRY(by_source_ready(R, dH_in->ld, &partial, &ok));
-      if (!ok) return ht_set_err(ctx, HT_ENOMEM, "layer backward: no memory for the partial sums");
-    }
   }
+  R.changed = true;
   const double flops = 2.0 * V * di * dn;
   auto timed_gemm = [&](auto&& f) -> int {
     R.tm.begin(&R.st->t_gemm_ms);
@@ -884,6 +907,16 @@ int layer_bwd_impl(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, con
     HT_TRY(ht_scratch(ctx, HT_S_DACHUNK, (size_t)gmax * ld_i * 4, (void**)&da_chunk));
     if (gbuffer) HT_TRY(ht_scratch(ctx, HT_S_MISC, (size_t)g->cache_rows * ld_i * 4, (void**)&gbuf));
   }
+  // what the chunks ask for on the way, each in turn: nothing may fail once dH_in is being added to
+  {
+    const int64_t out_ld = dH_in ? (gbuffer ? ld_i : dH_in->ld) : 0;
+    std::vector<ScratchWant> want = {{HT_S_SPART, (size_t)std::max(agg_ckpt ? 0 : g->max_fpart * a_ld, g->max_bpart * out_ld) * 4}};
+    if (relu && !H_out) want.push_back({HT_S_PACKW, (size_t)ht_packed_w_bytes(di, dn)});
+    if (dH_in) want.push_back({HT_S_PACKW, (size_t)ht_packed_w_bytes(dn, di)});
+    for (const auto& gr : groups)
+      want.push_back({HT_S_TNPART, ht_gemm_tn_bytes(g->chunks[gr.second].dst1 - g->chunks[gr.first].dst0, di, dn)});
+    HT_TRY(ht_scratch_each(ctx, want));
+  }
   // CPU-side accumulation (Alg. 3): host copy of the leave lists, device and pinned staging pairs
   // When the schedule loads every row once per pass, each row also leaves exactly once, after the last
   // chunk that adds to it: if dH_in is known to hold zeros the rows are stored straight to their home
@@ -916,6 +949,7 @@ int layer_bwd_impl(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, con
   Pipe P(ctx);
   AccWorker worker(ctx);   // declared after P: joined before P's destructor waits for the streams
   if (cpu_accum) worker.start();
+  R.changed = true;
   P.fence = (in_host || cpu_accum || store_home) && !ctx->no_link_fence;
   if (in_host) {
     hipEvent_t ev_start = nullptr;
@@ -1172,19 +1206,31 @@ int layer_bwd_update_first(Run& R, const ht_layer_desc* desc, const ht_tensor* H
   const int64_t mx = std::max<int64_t>(g->max_ndst, 1);
   float *dT = nullptr, *dz_chunk = nullptr, *partial = nullptr;
   HT_TRY(ht_scratch(ctx, HT_S_TFULL, (size_t)std::max<int64_t>(g->V, 1) * ld_t * 4, (void**)&dT));
+  const int64_t step = (int64_t)1 << 22;   // rows per dense launch
+  std::vector<ScratchWant> want = {{HT_S_TNPART, ht_gemm_tn_bytes(std::min(step, g->V), di, dn)},
+                                   {HT_S_TNPART, ht_gemm_tn_bytes(g->V % step, di, dn)}};
+  if (dH_in) want.push_back({HT_S_PACKW, (size_t)ht_packed_w_bytes(dn, di)});
   // dt = A_hat^T dz over all sources at once where dz of all vertices and the by-source list fit (see layer_bwd_direct)
   bool at_once = (int64_t)g->V * ld_t * 4 <= HT_DIRECT_BYTES;
-  if (at_once) HT_TRY(by_source_ready(R, ld_t, &partial, &at_once));
-  if (at_once && relu) {
-    const int rc = ht_scratch(ctx, HT_S_DZCHUNK, (size_t)g->V * ld_t * 4, (void**)&dz_chunk);
-    if (rc == HT_ENOMEM) at_once = false;
-    else HT_TRY(rc);
+  if (at_once) {
+    std::vector<ScratchWant> all = want;
+    if (relu) all.push_back({HT_S_DZCHUNK, (size_t)g->V * ld_t * 4});
+    const int rc = take_by_source(ctx, g, all, ld_t, 0);
+    at_once = rc == HT_OK;
+    if (rc != HT_ENOMEM) HT_TRY(rc);
   }
+  const size_t dz_bytes = relu ? (size_t)(at_once ? g->V : mx) * ld_t * 4 : 0,
+               part_bytes = at_once ? by_source_parts(g, ld_t) : (size_t)(g->max_bpart * ld_t) * 4;
+  want.push_back({HT_S_DZCHUNK, dz_bytes});
+  want.push_back({HT_S_SPART, part_bytes});
+  HT_TRY(ht_scratch_each(ctx, want));
+  dz_chunk = (float*)ctx->scratch[HT_S_DZCHUNK];
+  partial = (float*)ctx->scratch[HT_S_SPART];
+  R.changed = true;
   if (at_once) {
     if (relu) HT_TRY(ht_relu_mask(ctx, st, dH_out->ptr, dH_out->ld, H_out->ptr, H_out->ld, dz_chunk, ld_t, g->V, dn));
     HT_TRY(agg_by_source(R, relu ? dz_chunk : dH_out->ptr, relu ? ld_t : dH_out->ld, dn, dT, ld_t, false, partial));
   } else {
-    if (relu) HT_TRY(ht_scratch(ctx, HT_S_DZCHUNK, (size_t)mx * ld_t * 4, (void**)&dz_chunk));
     HT_TRY(ht_fill_zero(ctx, st, dT, (size_t)g->V * ld_t * 4));
   }
   // dt[N_j] += s_u * sum_v s_v dz[v], chunk by chunk
@@ -1199,7 +1245,6 @@ int layer_bwd_update_first(Run& R, const ht_layer_desc* desc, const ht_tensor* H
       dz_rows = dz_chunk;
       dz_ld = ld_t;
     }
-    if (c.bwd.n_part > 0) HT_TRY(ht_scratch(ctx, HT_S_SPART, (size_t)g->max_bpart * ld_t * 4, (void**)&partial));
     SpmmArgs a{};
     agg_args(g, c, false, false, &a);
     a.src = dz_rows; a.src_ld = dz_ld; a.d = dn;
@@ -1217,7 +1262,6 @@ int layer_bwd_update_first(Run& R, const ht_layer_desc* desc, const ht_tensor* H
     R.st->spmm_bwd_alg_bytes += spmm_alg_bytes(c, dn);
   }
   // dW = h^T dt, dH_in += dt W^T over row ranges
-  const int64_t step = (int64_t)1 << 22;
   bool first = true;
   for (int64_t r0 = 0; r0 < g->V; r0 += step) {
     const int64_t nr = std::min(step, g->V - r0);
@@ -1315,19 +1359,21 @@ int ht_layer_fwd(ht_ctx* ctx, const ht_graph* g, const ht_layer_desc* desc, cons
   if (g->ctx != ctx) return ht_set_err(ctx, HT_ESTATE, "graph belongs to another context");
   if (desc->d_in <= 0 || desc->d_out <= 0) return ht_set_err(ctx, HT_ESHAPE, "layer widths must be positive");
   HT_HIP(ctx, hipSetDevice(ctx->device));
-  auto t0 = std::chrono::steady_clock::now();
-  ht_stats local{};
-  Run R(ctx, g, &local, stats != nullptr);
   if (desc->order != HT_ORDER_AGG_FIRST && desc->order != HT_ORDER_UPDATE_FIRST)
     return ht_set_err(ctx, HT_EINVAL, "unknown stage order %d", desc->order);
-  int rc = desc->order == HT_ORDER_UPDATE_FIRST ? layer_fwd_update_first(R, desc, H_in, W, H_out)
-                                                : layer_fwd_impl(R, desc, H_in, W, H_out, A_ckpt);
-  if (rc != HT_OK) {
-    (void)hipStreamSynchronize(ctx->stream);
-    ctx->ev_next = 0;
-    return rc;
-  }
-  return finish(R, stats, t0, false);
+  return ht_with_room(ctx, [&]() -> int {
+    auto t0 = std::chrono::steady_clock::now();
+    ht_stats local{};
+    Run R(ctx, g, &local, stats != nullptr);
+    int rc = desc->order == HT_ORDER_UPDATE_FIRST ? layer_fwd_update_first(R, desc, H_in, W, H_out)
+                                                  : layer_fwd_impl(R, desc, H_in, W, H_out, A_ckpt);
+    if (rc != HT_OK) {
+      (void)hipStreamSynchronize(ctx->stream);
+      ctx->ev_next = 0;
+      return rc;
+    }
+    return finish(R, stats, t0, false);
+  });
 }
 
 // ht_layer_fwd for callers that cannot allocate: the same kernels in the same order, with the two scratch buffers of
@@ -1368,24 +1414,27 @@ int ht_layer_bwd(ht_ctx* ctx, const ht_graph* g, const ht_layer_desc* desc, cons
   if (g->ctx != ctx) return ht_set_err(ctx, HT_ESTATE, "graph belongs to another context");
   if (desc->d_in <= 0 || desc->d_out <= 0) return ht_set_err(ctx, HT_ESHAPE, "layer widths must be positive");
   HT_HIP(ctx, hipSetDevice(ctx->device));
-  auto t0 = std::chrono::steady_clock::now();
-  ht_stats local{};
-  Run R(ctx, g, &local, stats != nullptr);
   if (desc->order != HT_ORDER_AGG_FIRST && desc->order != HT_ORDER_UPDATE_FIRST)
     return ht_set_err(ctx, HT_EINVAL, "unknown stage order %d", desc->order);
-  int rc = desc->order == HT_ORDER_UPDATE_FIRST ? layer_bwd_update_first(R, desc, ckpt, W, dH_out, H_out, dH_in, dW)
-                                                : layer_bwd_impl(R, desc, ckpt, W, dH_out, H_out, dH_in, dW);
-  if (rc != HT_OK) {
-    (void)hipStreamSynchronize(ctx->stream);
-    ctx->ev_next = 0;
-    return rc;
-  }
-  return finish(R, stats, t0, false);
+  bool changed = false;
+  return ht_with_room(ctx, [&]() -> int {
+    auto t0 = std::chrono::steady_clock::now();
+    ht_stats local{};
+    Run R(ctx, g, &local, stats != nullptr);
+    int rc = desc->order == HT_ORDER_UPDATE_FIRST ? layer_bwd_update_first(R, desc, ckpt, W, dH_out, H_out, dH_in, dW)
+                                                  : layer_bwd_impl(R, desc, ckpt, W, dH_out, H_out, dH_in, dW);
+    changed = R.changed;
+    if (rc != HT_OK) {
+      (void)hipStreamSynchronize(ctx->stream);
+      ctx->ev_next = 0;
+      return rc;
+    }
+    return finish(R, stats, t0, false);
+  }, &changed);
 }
 
-int ht_epoch(ht_ctx* ctx, const ht_graph* g, const ht_model* model, const ht_tensor* X, const int32_t* labels,
-             const ht_plan_opts* plan, float* loss_out, ht_stats* stats) {
-  if (!ctx) return HT_EINVAL;
+static int epoch_impl(ht_ctx* ctx, const ht_graph* g, const ht_model* model, const ht_tensor* X, const int32_t* labels,
+                      const ht_plan_opts* plan, float* loss_out, ht_stats* stats) {
   if (!g || !model || !X || !labels || !loss_out) return ht_set_err(ctx, HT_EINVAL, "ht_epoch: null argument");
   if (g->ctx != ctx) return ht_set_err(ctx, HT_ESTATE, "graph belongs to another context");
   const int L = model->n_layers;
@@ -1642,9 +1691,9 @@ int ht_epoch(ht_ctx* ctx, const ht_graph* g, const ht_model* model, const ht_ten
     hipGraph_t graph = nullptr;
     hipError_t e = hipStreamBeginCapture(ctx->stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return fail(ht_set_err(ctx, HT_EHIP, "hipStreamBeginCapture: %s", hipGetErrorString(e)));
-    in_capture = true;
+    in_capture = ctx->no_grow = true;
     int rc = enqueue();
-    in_capture = false;
+    in_capture = ctx->no_grow = false;
     e = hipStreamEndCapture(ctx->stream, &graph);
     if (const char* dbg = getenv("HT_GRAPH_DEBUG"))
       if (atoi(dbg) == 2 && rc == HT_OK) rc = ht_set_err(ctx, HT_ESTATE, "capture discarded on request");   // exercises the fallback
@@ -1683,6 +1732,13 @@ int ht_epoch(ht_ctx* ctx, const ht_graph* g, const ht_model* model, const ht_ten
   local.plan_res_a = recompute ? 0 : res_a;
   local.plan_res_g = res_g;
   return finish(R, stats, t0, true);
+}
+
+int ht_epoch(ht_ctx* ctx, const ht_graph* g, const ht_model* model, const ht_tensor* X, const int32_t* labels,
+             const ht_plan_opts* plan, float* loss_out, ht_stats* stats) {
+  if (!ctx) return HT_EINVAL;
+  // (the caller's weights change in the last launch, behind everything that takes memory)
+  return ht_with_room(ctx, [&] { return epoch_impl(ctx, g, model, X, labels, plan, loss_out, stats); });
 }
 
 int ht_tensor_zero(ht_ctx* ctx, ht_tensor* t) {

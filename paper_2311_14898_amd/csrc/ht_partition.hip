@@ -1695,6 +1695,27 @@ int d2h(ht_ctx* ctx, T* dst, const T* src, int64_t n) {
 namespace {
 
 // The list costs 4 or 8 bytes per entry; it is copied together from the chunks' by-source lists.
+void plan_by_source(const ht_graph* g, DevBlock* kept, DevBlock* tmp) {
+  const ItemSwitches sw;
+  const int64_t V = g->V, n_ent = g->merged ? g->n_unique : g->Ep, bound = item_bound(V, n_ent, sw.seg_bwd);
+  const size_t n1 = (size_t)g->n + 1, tiles = (size_t)ceil_div64(V, RTILE);
+  kept->add<int32_t>((size_t)std::max<int64_t>(n_ent, 1));
+  if (g->merged) kept->add<float>((size_t)n_ent);
+  kept->add<WorkItem>((size_t)bound);
+  kept->add<CutRow>((size_t)cut_bound(n_ent, sw.seg_bwd));
+  tmp->add<int32_t>((size_t)V);
+  tmp->add<int32_t>(3 * tiles);
+  tmp->add<int64_t>((size_t)V + 1);
+  tmp->add<int64_t>((size_t)V + 1);
+  tmp->add<int64_t>((size_t)std::max<int64_t>(g->v_ori, 1));
+  tmp->add<int64_t>(3 * n1 + 2);
+  tmp->add<int64_t>(3 * tiles + 1);
+  tmp->add<int64_t>(6);
+  tmp->add<WorkItem>((size_t)bound);
+  tmp->add<uint64_t>((size_t)bound);
+  tmp->add<uint64_t>((size_t)bound);
+}
+
 int build_by_source(ht_ctx* ctx, const ht_graph* g) {
   hipStream_t st = ctx->stream;
   SourceRows& S = g->by_src;
@@ -1702,10 +1723,8 @@ int build_by_source(ht_ctx* ctx, const ht_graph* g) {
   const int64_t V = g->V, n_ent = g->merged ? g->n_unique : g->Ep, vo = g->v_ori;
   const size_t n1 = (size_t)g->n + 1;
   const int64_t bound = item_bound(V, n_ent, sw.seg_bwd), cuts = cut_bound(n_ent, sw.seg_bwd);
-  S.blk.add<int32_t>((size_t)std::max<int64_t>(n_ent, 1));
-  if (g->merged) S.blk.add<float>((size_t)n_ent);
-  S.blk.add<WorkItem>((size_t)bound);
-  S.blk.add<CutRow>((size_t)cuts);
+  DevBlock tmp;
+  plan_by_source(g, &S.blk, &tmp);
   HT_TRY(S.blk.alloc(ctx));
   S.blk.take(S.idx, (size_t)std::max<int64_t>(n_ent, 1));
   if (g->merged) S.blk.take(S.w, (size_t)n_ent);
@@ -1718,22 +1737,10 @@ int build_by_source(ht_ctx* ctx, const ht_graph* g) {
   b.idx = S.idx.p;
   b.range = V;
   b.out = &S.items;
-  DevBlock tmp;
   DevArr<int32_t> cnt, icnt;
   DevArr<int64_t> ptr, cur, off, lists, ibase, istarts;
   DevArr<WorkItem> made;
   DevArr<uint64_t> keysA, keysB;
-  tmp.add<int32_t>((size_t)V);
-  tmp.add<int32_t>((size_t)3 * b.tiles);
-  tmp.add<int64_t>((size_t)V + 1);
-  tmp.add<int64_t>((size_t)V + 1);
-  tmp.add<int64_t>((size_t)std::max<int64_t>(vo, 1));
-  tmp.add<int64_t>(3 * n1 + 2);
-  tmp.add<int64_t>((size_t)3 * b.tiles + 1);
-  tmp.add<int64_t>(6);
-  tmp.add<WorkItem>((size_t)bound);
-  tmp.add<uint64_t>((size_t)bound);
-  tmp.add<uint64_t>((size_t)bound);
   HT_TRY(tmp.alloc(ctx));
   tmp.take(cnt, (size_t)V);
   tmp.take(icnt, (size_t)3 * b.tiles);
@@ -1802,19 +1809,25 @@ int build_by_source(ht_ctx* ctx, const ht_graph* g) {
 
 }  // namespace
 
+int64_t ht_graph_by_source_bytes(const ht_graph* g) {
+  if (g->by_src.ok) return 0;
+  DevBlock kept, tmp;
+  plan_by_source(g, &kept, &tmp);
+  return (int64_t)(kept.planned + tmp.planned);
+}
+
 int ht_graph_by_source(ht_ctx* ctx, const ht_graph* g) {
   SourceRows& S = g->by_src;
-  if (S.tried) return HT_OK;
-  S.tried = true;
+  if (S.ok) return HT_OK;
+  if (ctx->no_grow || !ht_may_spend(ctx)) return HT_ENOMEM;
   const int rc = build_by_source(ctx, g);
   S.ok = rc == HT_OK;
   if (!S.ok) {
-    S.items = GraphItems();
-    S.idx.release();
-    S.w.release();
-    S.blk.release();
+    (void)hipStreamSynchronize(ctx->stream);
+    S = SourceRows();
+    if (rc == HT_ENOMEM) ctx->tight_room = ht_room(ctx);
   }
-  return rc == HT_ENOMEM ? HT_OK : rc;
+  return rc;
 }
 
 int ht_graph_by_source_mult(ht_ctx* ctx, const ht_graph* g) {
@@ -1860,6 +1873,7 @@ int ht_partition(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src, const in
   int rc = partition_impl(ctx, V, E, src, dst, n_chunks, opts, false, g);
   if (rc == HT_ENOMEM) {
     (void)hipStreamSynchronize(ctx->stream);
+    (void)ht_give_back(ctx);
     const uint64_t serial = g->serial;
     delete g;
     g = new (std::nothrow) ht_graph();
@@ -1872,6 +1886,7 @@ int ht_partition(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src, const in
     delete g;
     return rc;
   }
+  ctx->graphs.push_back(g);
   g->partition_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
   *out = g;
   return HT_OK;
@@ -1879,7 +1894,11 @@ int ht_partition(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src, const in
 
 int ht_graph_destroy(ht_graph* g) {
   if (!g) return HT_EINVAL;
-  if (g->ctx) (void)hipStreamSynchronize(g->ctx->stream);
+  if (g->ctx) {
+    (void)hipStreamSynchronize(g->ctx->stream);
+    std::vector<ht_graph*>& all = g->ctx->graphs;
+    all.erase(std::remove(all.begin(), all.end(), g), all.end());
+  }
   delete g;
   return HT_OK;
 }
