@@ -1461,6 +1461,9 @@ static int epoch_impl(ht_ctx* ctx, const ht_graph* g, const ht_model* model, con
     // buffers of a previous epoch with the same shape are reused, so count them as free
     if (ctx->ws)
       for (size_t b : ctx->ws->dev_bytes_of) budget += (int64_t)b;
+    // so is what calls before this one keep for later ones: it is given back where the tensors need it, and must not move them to the
+    // host in the second epoch
+    budget += ht_held(ctx);
   }
   auto bytes_of = [&](int l0, int l1) {
     int64_t b = 0;
