@@ -140,7 +140,7 @@ int64_t ht_room(ht_ctx* ctx) {
 ScratchMark::ScratchMark(ht_ctx* c) : ctx(c) { std::copy(c->scratch_bytes, c->scratch_bytes + HT_N_SCRATCH, was); }
 void ScratchMark::undo() {
   for (int k = 0; k < HT_N_SCRATCH; ++k)
-    if (ctx->scratch_bytes[k] > was[k]) (void)ht_scratch_release(ctx, k);
+    if (ctx->scratch_bytes[k] > was[k] && !(k == HT_S_LIST && ctx->list_owner)) (void)ht_scratch_release(ctx, k);
 }
 
 int ht_scratch_all(ht_ctx* ctx, const std::vector<ScratchWant>& want, int64_t beside) {
@@ -185,7 +185,7 @@ bool ht_may_spend(ht_ctx* ctx) {
 int64_t ht_held(const ht_ctx* ctx) {
   int64_t held = 0;
   for (size_t b : ctx->scratch_bytes) held += (int64_t)b;
-  for (const ht_graph* g : ctx->graphs) held += (int64_t)(g->by_src.blk.mem.bytes() + g->by_src.mult.bytes());
+  for (const ht_graph* g : ctx->graphs) held += (int64_t)((g == ctx->list_owner ? 0 : g->by_src.blk.mem.bytes()) + g->by_src.mult.bytes());
   return held;
 }
 
@@ -195,6 +195,7 @@ bool ht_give_back(ht_ctx* ctx) {
   for (hipStream_t s : ctx->side) (void)hipStreamSynchronize(s);
   for (int k = 0; k < HT_N_SCRATCH; ++k) (void)ht_scratch_release(ctx, k);
   for (const ht_graph* g : ctx->graphs) g->by_src = SourceRows();
+  ctx->list_owner = nullptr;
   ++ctx->scratch_gen;      // (captured epochs hold pointers into the lists as well)
   return true;
 }

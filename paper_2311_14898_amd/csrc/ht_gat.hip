@@ -1018,8 +1018,12 @@ int gat_bwd_rows_direct(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc,
     }
     // the dense steps behind this pass add to the caller's tensors: nothing may fail there for want of memory that is held here
     dense_wants(V, BLOCK_HBM, desc->d_in, d, &want);
-    HT_TRY(ht_scratch_all(ctx, want, ht_graph_by_source_bytes(g) + (g->merged && !S.mult.p ? g->n_unique * 4 : 0)));
-    HT_TRY(ht_graph_by_source(ctx, g));
+    int64_t list;
+    size_t making;
+    ht_graph_by_source_bytes(g, &list, &making);
+    want.push_back({HT_S_DZCHUNK, making});
+    HT_TRY(ht_scratch_all(ctx, want, list + (g->merged && !S.mult.p ? g->n_unique * 4 : 0)));
+    HT_TRY(ht_graph_by_source(ctx, g, HT_S_DZCHUNK));
     if (!src_fits(g, d, keep != nullptr)) return HT_ENOMEM;
     HT_TRY(ht_graph_by_source_mult(ctx, g));
     // (the partial sums of both passes share a slot, one after the other)
@@ -1386,8 +1390,11 @@ static int gat_epoch_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_model* mo
                 (ctx->gat_keep_limit == 0 || kf * 4 < ctx->gat_keep_limit || ht_room(ctx) > ctx->gat_keep_room);
     if (room) {
       ScratchMark mark(ctx);
-      int rc = ht_scratch_all(ctx, {{HT_S_GATKEEP, kf * 4}}, ht_graph_by_source_bytes(g));
-      if (rc == HT_OK) rc = ht_graph_by_source(ctx, g);
+      int64_t list;
+      size_t making;
+      ht_graph_by_source_bytes(g, &list, &making);
+      int rc = ht_scratch_all(ctx, {{HT_S_GATKEEP, kf * 4}, {HT_S_DZCHUNK, making}}, list);
+      if (rc == HT_OK) rc = ht_graph_by_source(ctx, g, HT_S_DZCHUNK);
       if (rc != HT_OK && rc != HT_ENOMEM) return rc;
       room = rc == HT_OK;
       for (int l = 1; l <= L; ++l) room = room && src_fits(g, model->dims[l], true);

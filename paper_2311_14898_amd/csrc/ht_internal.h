@@ -22,7 +22,7 @@ struct ht_graph;
 enum {
   HT_S_PACKW = 0, HT_S_TNPART, HT_S_LOSS, HT_S_ACHUNK, HT_S_OCHUNK, HT_S_ZCHUNK, HT_S_DZCHUNK, HT_S_DACHUNK,
   HT_S_NBUF, HT_S_SPART, HT_S_LEAVE, HT_S_MISC, HT_S_TFULL, HT_S_TFULL2, HT_S_GATV, HT_S_GATE, HT_S_GATWS, HT_S_GATP, HT_S_GATKEEP,
-  HT_S_LINK0, HT_S_LINK1, HT_S_LINK2, HT_S_SCAN, HT_S_RSORT, HT_S_TNTAB, HT_N_SCRATCH
+  HT_S_LINK0, HT_S_LINK1, HT_S_LINK2, HT_S_SCAN, HT_S_RSORT, HT_S_TNTAB, HT_S_LIST, HT_N_SCRATCH
 };
 
 struct ht_ctx {
@@ -65,6 +65,7 @@ struct ht_ctx {
   int agg_phases = 1;     // HT_AGG_PHASES: slabs are spread over this many consecutive launches
   int64_t link_block_rows = (int64_t)1 << 20;   // HT_LINK_BLOCK_ROWS: rows per staged block of a host-resident tensor (GAT path)
   int agg_variant = 0;  // 0: feature slabs per XCD; 1: full-width rows per wave (HT_AGG_VARIANT, for A/B runs)
+  const ht_graph* list_owner = nullptr;  // whose by-source list is in HT_S_LIST (null: nobody's)
   std::vector<ht_graph*> graphs;   // the graphs of this context (each may hold a by-source list)
   bool lean = false;           // the call is being made again with as little memory as it can do with (ht_with_room)
   bool no_grow = false;        // inside a stream capture: nothing may be allocated
@@ -115,7 +116,7 @@ struct ScratchWant { int slot; size_t bytes; };
 int ht_scratch_all(ht_ctx* ctx, const std::vector<ScratchWant>& want, int64_t beside = 0);
 // The slots one after the other, whatever it takes (HT_ENOMEM: some of them).
 int ht_scratch_each(ht_ctx* ctx, const std::vector<ScratchWant>& want);
-// Releases the slots that have grown since it was made.
+// Releases the slots that have grown since it was made (a by-source list that was made meanwhile stays).
 struct ScratchMark {
   ht_ctx* ctx;
   size_t was[HT_N_SCRATCH];
@@ -190,6 +191,19 @@ struct DevBlock {
   template <typename T>
   void add(size_t count) { planned += pad(count * sizeof(T)); }
   int alloc(ht_ctx* c) { taken = 0; return mem.alloc(c, planned > 0 ? planned : 1); }
+  // the same in a scratch slot of the context, which stays its owner
+  int alloc_in(ht_ctx* c, int slot) {
+    void* p = nullptr;
+    const int rc = ht_scratch(c, slot, planned > 0 ? planned : 1, &p);
+    if (rc != HT_OK) return rc;
+    mem.release();
+    mem.p = (char*)p;
+    mem.n = planned;
+    mem.ctx = c;
+    mem.owned = false;
+    taken = 0;
+    return HT_OK;
+  }
   template <typename T>
   void take(DevArr<T>& a, size_t count) {
     a.release();
@@ -249,7 +263,8 @@ struct __attribute__((aligned(16))) WorkItem {
 };
 struct __attribute__((aligned(16))) CutRow {   // a row with several items
   uint32_t row;
-  int32_t part0, nseg, pad;
+  int32_t part0, nseg;
+  uint32_t item0;              // its first item, in row order
 };
 struct GraphItems {
   DevArr<WorkItem> items;
@@ -340,10 +355,10 @@ struct ht_graph {
   int64_t hbm_bytes() const;
 };
 
-// Makes g->by_src if it is not there (HT_ENOMEM: it may not have, or there is no memory for it).
-int ht_graph_by_source(ht_ctx* ctx, const ht_graph* g);
-// Bytes that making it takes (0: it is there).
-int64_t ht_graph_by_source_bytes(const ht_graph* g);
+// Makes g->by_src if it is not there (HT_ENOMEM: it may not have, or there is no memory for it).  The slot is overwritten on the way.
+int ht_graph_by_source(ht_ctx* ctx, const ht_graph* g, int slot);
+// Bytes that it takes, and that making it takes of the slot (0: it is there).
+void ht_graph_by_source_bytes(const ht_graph* g, int64_t* list, size_t* slot);
 // Makes g->by_src.mult of a merged graph whose by_src is there (HT_ENOMEM: no memory for it).
 int ht_graph_by_source_mult(ht_ctx* ctx, const ht_graph* g);
 

@@ -740,12 +740,16 @@ int agg_by_source(Run& R, const float* src, int64_t src_ld, int d, float* dst, i
 // A by-source pass over rows of pitch ld keeps this many bytes of partial sums (of a list that is there).
 size_t by_source_parts(const ht_graph* g, int64_t ld) { return (size_t)(g->by_src.items.n_part * ld) * 4; }
 // Takes the slots and the by-source list, or HT_ENOMEM and nothing larger than before.  parts: bytes of other partial sums that share
-// their slot.
-int take_by_source(ht_ctx* ctx, const ht_graph* g, std::vector<ScratchWant> want, int64_t ld, size_t parts) {
+// their slot.  slot: one that is written after the list was made.
+int take_by_source(ht_ctx* ctx, const ht_graph* g, std::vector<ScratchWant> want, int64_t ld, size_t parts, int slot) {
   if (!ht_may_spend(ctx) || by_source_parts(g, ld) > (size_t)HT_RANGE_BYTES) return HT_ENOMEM;
   ScratchMark mark(ctx);
-  int rc = ht_scratch_all(ctx, want, ht_graph_by_source_bytes(g));
-  if (rc == HT_OK) rc = ht_graph_by_source(ctx, g);
+  int64_t list;
+  size_t making;
+  ht_graph_by_source_bytes(g, &list, &making);
+  want.push_back({slot, making});
+  int rc = ht_scratch_all(ctx, want, list);
+  if (rc == HT_OK) rc = ht_graph_by_source(ctx, g, slot);
   if (rc == HT_OK) {
     const size_t mine = by_source_parts(g, ld);
     want.push_back({HT_S_SPART, std::max(mine, parts)});
@@ -782,7 +786,7 @@ int layer_bwd_direct(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, c
   std::vector<ScratchWant> want = {{HT_S_ACHUNK, a_bytes}, {HT_S_DZCHUNK, dz_bytes}, {HT_S_DACHUNK, da_bytes}, {HT_S_SPART, fwd_parts},
                                    {HT_S_PACKW, (size_t)std::max(ht_packed_w_bytes(di, dn), ht_packed_w_bytes(dn, di))}};
   ht_gemm_groups_wants(di, dn, g->dense_groups, &want);
-  const int rc = dH_in ? take_by_source(ctx, g, want, dH_in->ld, fwd_parts) : ht_scratch_all(ctx, want);
+  const int rc = dH_in ? take_by_source(ctx, g, want, dH_in->ld, fwd_parts, HT_S_DACHUNK) : ht_scratch_all(ctx, want);
   if (rc == HT_ENOMEM) return HT_OK;
   HT_TRY(rc);
   auto get = [&](int slot, size_t bytes, float** p) { return bytes ? ht_scratch(ctx, slot, bytes, (void**)p) : (int)HT_OK; };
@@ -1215,7 +1219,7 @@ int layer_bwd_update_first(Run& R, const ht_layer_desc* desc, const ht_tensor* H
   if (at_once) {
     std::vector<ScratchWant> all = want;
     if (relu) all.push_back({HT_S_DZCHUNK, (size_t)g->V * ld_t * 4});
-    const int rc = take_by_source(ctx, g, all, ld_t, 0);
+    const int rc = take_by_source(ctx, g, all, ld_t, 0, HT_S_DZCHUNK);
     at_once = rc == HT_OK;
     if (rc != HT_ENOMEM) HT_TRY(rc);
   }

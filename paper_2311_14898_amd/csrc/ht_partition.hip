@@ -769,11 +769,32 @@ __global__ void __launch_bounds__(TB) k_items_count(RowSet R, int64_t nrows, int
 // The items in row order, their dispatch keys, the cut rows, and where every chunk's share starts (starts[0 / 1 / 2][k]).
 // Dispatch order: chunk by chunk, inside a chunk by the first row an item reads (entries of a row are sorted by that
 // index), so items in flight together read neighbouring rows.  fbits: bits of the key left for that row; a wider index
-// is rounded down (the order is about locality only).
-__global__ void __launch_bounds__(TB) k_items_fill(RowSet R, int64_t nrows, int seg, int64_t tiles, const int64_t* __restrict__ base,
-                                                   const int32_t* __restrict__ idx, int fbits, int fshift,
-                                                   WorkItem* __restrict__ item, uint64_t* __restrict__ keys,
+// is rounded down (the order is about locality only).  The items of rows cut into more than FILL_ALONE are left to k_items_fill_cut: a
+// thread that wrote a hub's thousands one after the other held up the whole launch (116 k vertices, 57 M edges by source: 491 us,
+// the two launches 33).
+constexpr int FILL_ALONE = 4;
+struct ItemOut {
+  int seg, fbits, fshift;
+  const int32_t* idx;
+  WorkItem* item;
+  uint64_t* keys;
+  __device__ __forceinline__ void put(uint32_t row, int k, int64_t e0, int64_t len, int64_t i0, int64_t p0, int64_t j) const {   // p0 < 0: not cut
+    const int64_t b = e0 + j * seg, rem = len - j * seg;
+    WorkItem w;
+    w.row = row;
+    w.e0 = (uint32_t)b;
+    w.len = (int32_t)(rem < seg ? rem : seg);
+    w.part = p0 >= 0 ? (int32_t)(p0 + j) : -1;
+    item[i0 + j] = w;
+    if (keys) {
+      const uint32_t f = w.len > 0 ? (uint32_t)idx[b] >> fshift : 0u;
+      keys[i0 + j] = ((((uint64_t)k << fbits) | f) << 32) | (uint64_t)(uint32_t)(i0 + j);
+    }
+  }
+};
+__global__ void __launch_bounds__(TB) k_items_fill(RowSet R, int64_t nrows, int64_t tiles, const int64_t* __restrict__ base, ItemOut out,
                                                    CutRow* __restrict__ cut, int64_t* __restrict__ starts) {
+  const int seg = out.seg;
   int k = find_range(R.first, R.n, (int64_t)blockIdx.x * RTILE);
   int64_t end = R.first[k + 1];
   const int n1 = R.n + 1;
@@ -798,25 +819,14 @@ __global__ void __launch_bounds__(TB) k_items_fill(RowSet R, int64_t nrows, int 
         starts[n1 + kk] = p0;
         starts[2 * n1 + kk] = c0;
       }
-      for (int64_t j = 0; j < (int64_t)m; ++j) {
-        const int64_t b = e0 + j * seg, rem = len - j * seg;
-        WorkItem w;
-        w.row = (uint32_t)r;
-        w.e0 = (uint32_t)b;
-        w.len = (int32_t)(rem < seg ? rem : seg);
-        w.part = is_cut ? (int32_t)(p0 + j) : -1;
-        item[i0 + j] = w;
-        if (keys) {
-          const uint32_t f = w.len > 0 ? (uint32_t)idx[b] >> fshift : 0u;
-          keys[i0 + j] = ((((uint64_t)k << fbits) | f) << 32) | (uint64_t)(uint32_t)(i0 + j);
-        }
-      }
+      if (m <= FILL_ALONE)
+        for (int64_t j = 0; j < (int64_t)m; ++j) out.put((uint32_t)r, k, e0, len, i0, is_cut ? p0 : -1, j);
       if (is_cut) {
         CutRow c;
         c.row = (uint32_t)r;
         c.part0 = (int32_t)p0;
         c.nseg = (int32_t)m;
-        c.pad = 0;
+        c.item0 = (uint32_t)i0;
         cut[c0] = c;
       }
     }
@@ -824,6 +834,18 @@ __global__ void __launch_bounds__(TB) k_items_fill(RowSet R, int64_t nrows, int 
     at_p += (int64_t)t2;
     at_c += (int64_t)(t1 >> 40);
   }
+}
+
+// the items of the rows that k_items_fill left out, a wave per cut row
+__global__ void __launch_bounds__(TB) k_items_fill_cut(RowSet R, const CutRow* __restrict__ cut, int64_t n_cut, ItemOut out) {
+  const int64_t f = (int64_t)blockIdx.x * (TB / 64) + (threadIdx.x >> 6);
+  if (f >= n_cut) return;
+  const CutRow c = cut[f];
+  if (c.nseg <= FILL_ALONE) return;
+  const int k = find_range(R.first, R.n, c.row);
+  int64_t e0, len;
+  R.get(c.row, k, &e0, &len);
+  for (int32_t j = threadIdx.x & 63; j < c.nseg; j += 64) out.put(c.row, k, e0, len, c.item0, c.part0, j);
 }
 
 // (in: from item i0 on)
@@ -853,20 +875,36 @@ __global__ void k_src_offsets(const int32_t* __restrict__ nbr, RowSet R, int k, 
   off[p0 + i] = cur[u] - e0;   // entry e of the chunk's list goes to off + e
   cur[u] += len;
 }
-// a wave per backward work item copies its entries: destination in vertex ids, weight
+// SRC_LANES lanes per backward work item copy its entries: destination in vertex ids, weight.  What bounds it is the chain of loads
+// before an item's first entry, so the more items in flight the better (most have a few dozen entries; 116 k vertices, 57 M edges in 7
+// chunks: 234 us, a wave per item 351).
+constexpr int SRC_LANES = 16;
 __global__ void __launch_bounds__(TB) k_src_copy(const WorkItem* __restrict__ items, int64_t n_items, const int64_t* __restrict__ first,
                                                  const int64_t* __restrict__ bounds, int n, const int64_t* __restrict__ off,
                                                  const int32_t* __restrict__ sdst, const float* __restrict__ w,
                                                  int32_t* __restrict__ idx, float* __restrict__ w_out) {
-  const int lane = threadIdx.x & 63;
-  const int64_t t = (int64_t)blockIdx.x * (TB / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t t = (int64_t)blockIdx.x * (TB / SRC_LANES) + threadIdx.x / SRC_LANES;
   if (t >= n_items) return;
   const WorkItem it = items[t];
-  const int32_t d0 = (int32_t)bounds[find_range(first, n, it.row)];
   const int64_t to = off[it.row] + it.e0;
-  for (int32_t i = lane; i < it.len; i += 64) {
-    idx[to + i] = d0 + sdst[(int64_t)it.e0 + i];
-    if (w) w_out[to + i] = w[(int64_t)it.e0 + i];
+  const int32_t d0 = (int32_t)bounds[find_range(first, n, it.row)];
+  for (int32_t i0 = threadIdx.x % SRC_LANES; i0 < it.len; i0 += 4 * SRC_LANES) {
+    int32_t d[4];
+    float v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int32_t i = i0 + q * SRC_LANES;
+      const int64_t e = (int64_t)it.e0 + (i < it.len ? i : i0);
+      d[q] = sdst[e];
+      if (w) v[q] = w[e];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int32_t i = i0 + q * SRC_LANES;
+      if (i >= it.len) break;
+      idx[to + i] = d0 + d[q];
+      if (w) w_out[to + i] = v[q];
+    }
   }
 }
 
@@ -907,8 +945,10 @@ int count_items(ht_ctx* ctx, const ItemBuild& b, int64_t* h_tot) {
   k_items_count<<<(unsigned)b.tiles, TB, 0, ctx->stream>>>(b.rows, b.nrows, b.seg, b.tiles, b.cnt);
   HT_LAUNCH_CHECK(ctx);
   HT_TRY(ht_scan_i32(ctx, b.cnt, b.base, 3 * b.tiles, true));
-  for (int w = 0; w < 3; ++w)
-    HT_HIP(ctx, hipMemcpyAsync(&h_tot[w], b.base + (w + 1) * b.tiles, 8, hipMemcpyDeviceToHost, ctx->stream));
+  void* d_tot = nullptr;     // (one launch that writes to the host: a copy each took longer)
+  HT_HIP(ctx, hipHostGetDevicePointer(&d_tot, h_tot, 0));
+  k_gather_stride<<<1, TB, 0, ctx->stream>>>(b.base + b.tiles, b.tiles, 3, (int64_t*)d_tot);
+  HT_LAUNCH_CHECK(ctx);
   return HT_OK;
 }
 
@@ -926,10 +966,15 @@ int fill_items(ht_ctx* ctx, const ItemBuild& b, const int64_t* h_tot, WorkItem* 
   const bool sorted_items = order && ni > 1, at_once = ni <= (int64_t)n_made;
   const int kbits = b.rows.n > 1 ? bits_for(b.rows.n) : 0, vbits = bits_for(b.range);
   const int fbits = std::min(vbits, 32 - kbits), fshift = vbits - fbits;
-  k_items_fill<<<(unsigned)b.tiles, TB, 0, ctx->stream>>>(b.rows, b.nrows, b.seg, b.tiles, b.base, b.idx, fbits, fshift,
-                                                          sorted_items && at_once ? made : b.out->items.p, sorted_items ? keysA : nullptr,
-                                                          b.out->cuts.p, b.starts);
+  const ItemOut to{b.seg, fbits, fshift, b.idx, sorted_items && at_once ? made : b.out->items.p, sorted_items ? keysA : nullptr};
+  k_items_fill<<<(unsigned)b.tiles, TB, 0, ctx->stream>>>(b.rows, b.nrows, b.tiles, b.base, to, b.out->cuts.p, b.starts);
   HT_LAUNCH_CHECK(ctx);
+  if (np > FILL_ALONE)
+    HT_TRY(ht_in_launches(nc, HT_LAUNCH_WAVES, [&](int64_t i, int64_t m) {
+      k_items_fill_cut<<<nblk(m, TB / 64), TB, 0, ctx->stream>>>(b.rows, b.out->cuts.p + i, m, to);
+      HT_LAUNCH_CHECK(ctx);
+      return (int)HT_OK;
+    }));
   if (!sorted_items) return HT_OK;
   auto sort_range = [&](int64_t i0, int64_t n, const WorkItem* from, int bits) -> int {
     uint64_t* sorted = nullptr;
@@ -1704,9 +1749,8 @@ void plan_by_source(const ht_graph* g, DevBlock* kept, DevBlock* tmp) {
   kept->add<WorkItem>((size_t)bound);
   kept->add<CutRow>((size_t)cut_bound(n_ent, sw.seg_bwd));
   tmp->add<int32_t>((size_t)V);
+  tmp->add<int64_t>((size_t)V + 1);
   tmp->add<int32_t>(3 * tiles);
-  tmp->add<int64_t>((size_t)V + 1);
-  tmp->add<int64_t>((size_t)V + 1);
   tmp->add<int64_t>((size_t)std::max<int64_t>(g->v_ori, 1));
   tmp->add<int64_t>(3 * n1 + 2);
   tmp->add<int64_t>(3 * tiles + 1);
@@ -1716,7 +1760,7 @@ void plan_by_source(const ht_graph* g, DevBlock* kept, DevBlock* tmp) {
   tmp->add<uint64_t>((size_t)bound);
 }
 
-int build_by_source(ht_ctx* ctx, const ht_graph* g) {
+int build_by_source(ht_ctx* ctx, const ht_graph* g, int slot) {
   hipStream_t st = ctx->stream;
   SourceRows& S = g->by_src;
   const ItemSwitches sw;
@@ -1725,7 +1769,14 @@ int build_by_source(ht_ctx* ctx, const ht_graph* g) {
   const int64_t bound = item_bound(V, n_ent, sw.seg_bwd), cuts = cut_bound(n_ent, sw.seg_bwd);
   DevBlock tmp;
   plan_by_source(g, &S.blk, &tmp);
-  HT_TRY(S.blk.alloc(ctx));
+  // The list of one graph at a time is kept in a slot of the context, where the next graph finds the memory after this one was
+  // destroyed (13 MiB from the device: 320 us, more than the rest of the list's making)
+  if (!ctx->list_owner) {
+    HT_TRY(S.blk.alloc_in(ctx, HT_S_LIST));
+    ctx->list_owner = g;
+  } else {
+    HT_TRY(S.blk.alloc(ctx));
+  }
   S.blk.take(S.idx, (size_t)std::max<int64_t>(n_ent, 1));
   if (g->merged) S.blk.take(S.w, (size_t)n_ent);
   S.blk.take(S.items.items, (size_t)bound);
@@ -1738,14 +1789,13 @@ int build_by_source(ht_ctx* ctx, const ht_graph* g) {
   b.range = V;
   b.out = &S.items;
   DevArr<int32_t> cnt, icnt;
-  DevArr<int64_t> ptr, cur, off, lists, ibase, istarts;
+  DevArr<int64_t> ptr, off, lists, ibase, istarts;
   DevArr<WorkItem> made;
   DevArr<uint64_t> keysA, keysB;
-  HT_TRY(tmp.alloc(ctx));
+  HT_TRY(tmp.alloc_in(ctx, slot));   // (an allocation of its own and its release took as long as the rest of this together)
   tmp.take(cnt, (size_t)V);
-  tmp.take(icnt, (size_t)3 * b.tiles);
   tmp.take(ptr, (size_t)V + 1);
-  tmp.take(cur, (size_t)V + 1);
+  tmp.take(icnt, (size_t)3 * b.tiles);
   tmp.take(off, (size_t)std::max<int64_t>(vo, 1));
   tmp.take(lists, 3 * n1 + 2);
   tmp.take(ibase, (size_t)3 * b.tiles + 1);
@@ -1777,23 +1827,23 @@ int build_by_source(ht_ctx* ctx, const ht_graph* g) {
   hl[3 * n1 + 1] = V;
   HT_HIP(ctx, hipMemcpyAsync(lists.p, hl, (3 * n1 + 2) * 8, hipMemcpyHostToDevice, st));
   const RowSet arena{g->merged ? g->usptr.p : g->sptr.p, lists.p, lists.p + n1, g->n};
-  HT_TRY(ht_fill_zero(ctx, st, cnt.p, (size_t)V * 4));
+  // ptr[u + 1] runs from where u's entries start to where they end while the chunks take their places, and is then the start of u + 1
+  HT_TRY(ht_fill_zero(ctx, st, cnt.p, (size_t)((char*)(ptr.p + 1) - (char*)cnt.p)));   // ... and ptr[0]
   if (vo > 0) {
     k_src_counts<<<nblk(vo), TB, 0, st>>>(g->nbr.p, arena, vo, cnt.p);
     HT_LAUNCH_CHECK(ctx);
   }
-  HT_TRY(ht_scan_i32(ctx, cnt.p, ptr.p, V, true));
-  HT_HIP(ctx, hipMemcpyAsync(cur.p, ptr.p, (size_t)V * 8, hipMemcpyDeviceToDevice, st));
+  HT_TRY(ht_scan_i32(ctx, cnt.p, ptr.p + 1, V, false));
   for (int k = 0; k < g->n; ++k) {
     const ChunkMeta& c = g->chunks[g->pos[k]];
     if (c.nsrc == 0) continue;
-    k_src_offsets<<<nblk(c.nsrc), TB, 0, st>>>(g->nbr.p, arena, k, c.nbr_off, c.nsrc, cur.p, off.p);
+    k_src_offsets<<<nblk(c.nsrc), TB, 0, st>>>(g->nbr.p, arena, k, c.nbr_off, c.nsrc, ptr.p + 1, off.p);
     HT_LAUNCH_CHECK(ctx);
   }
   const int64_t ni = g->bwd_items.n_items;
   if (ni > 0) {
-    HT_TRY(ht_in_launches(ni, HT_LAUNCH_WAVES, [&](int64_t i, int64_t m) {
-      k_src_copy<<<nblk(m, TB / 64), TB, 0, st>>>(g->bwd_items.items.p + i, m, lists.p, lists.p + 2 * n1, g->n, off.p,
+    HT_TRY(ht_in_launches(ni, HT_LAUNCH_WAVES * 64 / SRC_LANES, [&](int64_t i, int64_t m) {
+      k_src_copy<<<nblk(m, TB / SRC_LANES), TB, 0, st>>>(g->bwd_items.items.p + i, m, lists.p, lists.p + 2 * n1, g->n, off.p,
                                                  g->merged ? g->usdst.p : g->sdst.p, g->merged ? g->uw_bwd.p : nullptr, S.idx.p, S.w.p);
       HT_LAUNCH_CHECK(ctx);
       return (int)HT_OK;
@@ -1802,29 +1852,30 @@ int build_by_source(ht_ctx* ctx, const ht_graph* g) {
   b.rows = RowSet{ptr.p, lists.p + 3 * n1, nullptr, 1};
   HT_TRY(count_items(ctx, b, hp));
   HT_HIP(ctx, hipStreamSynchronize(st));
-  HT_TRY(fill_items(ctx, b, hp, made.p, (size_t)bound, keysA.p, keysB.p, (size_t)bound, sw.order));
-  HT_HIP(ctx, hipStreamSynchronize(st));
-  return HT_OK;
+  return fill_items(ctx, b, hp, made.p, (size_t)bound, keysA.p, keysB.p, (size_t)bound, sw.order);
 }
 
 }  // namespace
 
-int64_t ht_graph_by_source_bytes(const ht_graph* g) {
-  if (g->by_src.ok) return 0;
+void ht_graph_by_source_bytes(const ht_graph* g, int64_t* list, size_t* slot) {
   DevBlock kept, tmp;
-  plan_by_source(g, &kept, &tmp);
-  return (int64_t)(kept.planned + tmp.planned);
+  if (!g->by_src.ok) plan_by_source(g, &kept, &tmp);
+  // (in its slot, which may hold some of it)
+  *list = g->by_src.ok ? 0 : (int64_t)(kept.planned + kept.planned / 8);
+  if (!g->ctx->list_owner) *list = std::max<int64_t>(0, *list - (int64_t)g->ctx->scratch_bytes[HT_S_LIST]);
+  *slot = tmp.planned;
 }
 
-int ht_graph_by_source(ht_ctx* ctx, const ht_graph* g) {
+int ht_graph_by_source(ht_ctx* ctx, const ht_graph* g, int slot) {
   SourceRows& S = g->by_src;
   if (S.ok) return HT_OK;
   if (ctx->no_grow || !ht_may_spend(ctx)) return HT_ENOMEM;
-  const int rc = build_by_source(ctx, g);
+  const int rc = build_by_source(ctx, g, slot);
   S.ok = rc == HT_OK;
   if (!S.ok) {
     (void)hipStreamSynchronize(ctx->stream);
     S = SourceRows();
+    if (ctx->list_owner == g) ctx->list_owner = nullptr;
     if (rc == HT_ENOMEM) ctx->tight_room = ht_room(ctx);
   }
   return rc;
@@ -1898,6 +1949,7 @@ int ht_graph_destroy(ht_graph* g) {
     (void)hipStreamSynchronize(g->ctx->stream);
     std::vector<ht_graph*>& all = g->ctx->graphs;
     all.erase(std::remove(all.begin(), all.end(), g), all.end());
+    if (g->ctx->list_owner == g) g->ctx->list_owner = nullptr;
   }
   delete g;
   return HT_OK;

@@ -68,3 +68,66 @@ def test_layer_all_chunks_at_once(V, E, d_in, d_out, n, reorder, lean):
     finally:
         B.ht_graph_destroy(g)
         B.ht_ctx_destroy(ctx)
+
+
+def _bwd_check(ctx, g, V, src, dst, d_in, d_out, seed):
+    gen = torch.Generator().manual_seed(seed)
+    X, W, dz = torch.randn(V, d_in, generator=gen), torch.randn(d_in, d_out, generator=gen) / 4, torch.randn(V, d_out, generator=gen)
+    A, H, dW, dX = _ref(V, src, dst, X, W, dz)
+    Hd, Ad, dXd, dWd = B.alloc_matrix(V, d_out), B.alloc_matrix(V, d_in), B.alloc_matrix(V, d_in), torch.empty(d_in, d_out, device="cuda")
+    B.ht_layer_fwd(ctx, g, d_in, d_out, B.HT_ACT_NONE, B.to_matrix(X), W.cuda(), Hd, Ad)
+    B.ht_layer_bwd(ctx, g, d_in, d_out, B.HT_ACT_NONE, Ad, W.cuda(), B.to_matrix(dz), dWd, dH_in=dXd)
+    B.ht_sync(ctx)
+    assert_close(Hd[:, :d_out].cpu().numpy(), H.numpy(), "H")
+    assert_close_grad(dWd.cpu().numpy(), dW.numpy(), "dW")
+    assert_close_grad(dXd[:, :d_in].cpu().numpy(), dX.numpy(), "dX")
+
+
+@pytest.mark.parametrize("n", [1, 3])
+def test_rows_cut_into_few_and_many_items(n):
+    """Destinations and sources of 4, 5, 64, 65 and more items, just below and above each line (256 entries an item forward, 128
+    backward), some of them neighbours, in several tiles of rows and chunks."""
+    V, gen = 20_011, torch.Generator().manual_seed(1)
+    lens = [256 * k + e for k in (1, 4, 5, 64, 65) for e in (0, 1)] + [128 * k + e for k in (4, 5) for e in (0, 1)]
+    hubs = list(range(len(lens))) + [1023 + 7 * i for i in range(len(lens))] + [V - 1 - i for i in range(len(lens))]
+    src, dst = [torch.randint(0, V, (30_000,), generator=gen)], [torch.randint(0, V, (30_000,), generator=gen)]
+    for i, h in enumerate(hubs):
+        others = torch.randperm(V, generator=gen)[:lens[i % len(lens)]]
+        a, b = (src, dst) if i % 2 else (dst, src)      # by turns a hub of in- and of out-edges
+        a.append(torch.full_like(others, h))
+        b.append(others)
+    src, dst = torch.cat(src).to(torch.int32), torch.cat(dst).to(torch.int32)
+    ctx = B.ht_ctx_create(0)
+    g = B.ht_partition(ctx, V, src.cuda(), dst.cuda(), n)
+    try:
+        _bwd_check(ctx, g, V, src, dst, 24, 12, 2)
+    finally:
+        B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)
+
+
+def test_graphs_of_one_context_and_their_lists():
+    """The first graph's by-source list lies in the context and is taken over by a later graph once it is destroyed; a second live graph
+    has its own."""
+    ctx = B.ht_ctx_create(0)
+    graphs = {}
+    sizes = dict(a=(5_003, 60_000, 3), b=(9_001, 200_003, 4), c=(4_001, 30_001, 2), d=(15_013, 400_000, 5))
+    try:
+        def make(k):
+            V, E, n = sizes[k]
+            src, dst = inputs.rmat_edges(V, E, ord(k))
+            graphs[k] = (B.ht_partition(ctx, V, src.cuda(), dst.cuda(), n), V, src, dst)
+        def check(k):
+            g, V, src, dst = graphs[k]
+            _bwd_check(ctx, g, V, src, dst, 20, 9, ord(k))
+        for step in ("+a", "a", "+b", "b", "a", "-a", "b", "+c", "c", "b", "+d", "d", "c", "-c", "b", "d", "+a", "a", "d", "-b", "-d", "a"):
+            if step[0] == "+":
+                make(step[1])
+            elif step[0] == "-":
+                B.ht_graph_destroy(graphs.pop(step[1])[0])
+            else:
+                check(step)
+    finally:
+        for g, *_ in graphs.values():
+            B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)
