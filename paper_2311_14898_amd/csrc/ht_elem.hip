@@ -7,8 +7,9 @@
 
 namespace {
 
-__global__ void k_relu_mask(const float* __restrict__ dh, int64_t ld_dh, const float* __restrict__ ref,
-                            int64_t ld_ref, float* __restrict__ dz, int64_t ld_dz, int64_t rows, int cols4) {
+// (dz may be ref: a thread writes only where it alone has read)
+__global__ void k_relu_mask(const float* __restrict__ dh, int64_t ld_dh, const float* ref,
+                            int64_t ld_ref, float* dz, int64_t ld_dz, int64_t rows, int cols4) {
   // one thread per float4 of the padded row
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int vec_per_row = cols4 >> 2;
