@@ -183,13 +183,13 @@ def main_gat(args):
 
 
 def read_traffic(name):
-    """HBM bytes per launch of the dominant kernel, from the committed rocprofv3 counter summary."""
+    """HBM bytes per pass of the dominant kernel (all chunks), from the committed rocprofv3 counter summary."""
     path = os.path.join(ROOT, "profiles", name)
     if not os.path.exists(path):
         return None
     with open(path) as f:
         for line in f:
-            if line.startswith("traffic_bytes_per_launch:"):
+            if line.startswith("traffic_bytes_per_pass:"):
                 return float(line.split(":")[1])
     return None
 
@@ -531,18 +531,19 @@ def main():
     gteps = tot["edges"] / elapsed / 1e9      # stored edges aggregated per second (L forward + L-1 backward passes)
 
     # roofline of the dominant kernel: the layer-0 forward aggregation (widest rows, every chunk)
-    avg_ms = agg["t"] / max(agg["n"], 1)
-    bytes_per_launch = agg["bytes"] / max(agg["n"], 1)
-    achieved = bytes_per_launch / (avg_ms * 1e-3) / 1e9 if avg_ms > 0 else 0.0
+    # (agg["n"] counts chunk aggregations; with everything in HBM one launch serves all chunks of a pass)
+    pass_ms = agg["t"] / args.steps
+    bytes_per_pass = agg["bytes"] / args.steps
+    achieved = bytes_per_pass / (pass_ms * 1e-3) / 1e9 if pass_ms > 0 else 0.0
     traffic = read_traffic(f"agg_fwd_{args.workload}_traffic.txt") if args.scale == 1.0 else None
     roofline = {"bound": "hbm", "kernel": "forward aggregation, layer 0 (k_spmm_slab)", "achieved": achieved,
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                 "traffic_source": None if traffic is None else f"profiles/agg_fwd_{args.workload}_traffic.txt (two rocprofv3 --pmc runs of this "
                                   "command, committed; not measured in this run)",
-                "sustained_frac": None if traffic is None or avg_ms <= 0 else traffic / (avg_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                "sustained_note": "traffic / launch time / peak: the bytes that crossed the L2 boundary, re-reads included; frac "
+                "sustained_frac": None if traffic is None or pass_ms <= 0 else traffic / (pass_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
+                "sustained_note": "traffic / time of a pass / peak: the bytes that crossed the L2 boundary, re-reads included; frac "
                                   "counts only the algorithmic bytes",
-                "avg_launch_ms": avg_ms, "launches": agg["n"], "algorithmic_bytes_per_launch": bytes_per_launch,
+                "ms_per_pass": pass_ms, "passes": args.steps, "chunks_per_pass": agg["n"] / args.steps, "algorithmic_bytes_per_pass": bytes_per_pass,
                 "gathered_GBs_cacheless": 4.0 * w.dims[0] * Ep / max(agg["t"] / args.steps * 1e-3, 1e-12) / 1e9}
 
     out = {"metric": "GCN full-graph epoch time (s) + aggregation GTEPS + HBM GB/s, 1xMI355X",
@@ -564,6 +565,8 @@ def main():
            "agg_fwd_layer_ms_per_step": [x / args.steps for x in tot["t_agg_fwd_layer_ms"][:L]],
            "gemm_tflops": tot["gemm_flops"] / max(tot["t_gemm_ms"] * 1e-3, 1e-12) / 1e12,
            "gemm_frac_of_fp32_mfma_peak": tot["gemm_flops"] / max(tot["t_gemm_ms"] * 1e-3, 1e-12) / 1e12 / FP32_MFMA_PEAK_TFLOPS,
+           "gemm_note": "all products together; A W and dZ W^T run on the fp32 matrix cores, grad W of long wide layers on the bf16 ones in "
+                        "eight partial products (their ceiling is an eighth of the bf16 peak)",
            "partition_medges_per_s": Ep / max(info.partition_ms * 1e-3, 1e-12) / 1e6,
            "link": {"h2d_gbps_over_epoch": tot["bytes_h2d"] / elapsed / 1e9, "d2h_gbps_over_epoch": tot["bytes_d2h"] / elapsed / 1e9,
                     "measured_one_way_gbps": 57.0, "measured_two_way_gbps_each": 46.0,
