@@ -1921,8 +1921,9 @@ int ht_partition(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src, const in
   ht_graph* g = new (std::nothrow) ht_graph();
   if (g) g->serial = next_serial.fetch_add(1);
   if (!g) return ht_set_err(ctx, HT_ENOMEM, "ht_partition: host allocation failed");
+  const bool held = ht_held(ctx) > 0;
   int rc = partition_impl(ctx, V, E, src, dst, n_chunks, opts, false, g);
-  if (rc == HT_ENOMEM) {
+  for (int again = held ? 0 : 1; rc == HT_ENOMEM && again < 2; ++again) {   // with what earlier calls hold given back, then with less memory
     (void)hipStreamSynchronize(ctx->stream);
     (void)ht_give_back(ctx);
     const uint64_t serial = g->serial;
@@ -1930,7 +1931,7 @@ int ht_partition(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src, const in
     g = new (std::nothrow) ht_graph();
     if (!g) return ht_set_err(ctx, HT_ENOMEM, "ht_partition: host allocation failed");
     g->serial = serial;
-    rc = partition_impl(ctx, V, E, src, dst, n_chunks, opts, true, g);
+    rc = partition_impl(ctx, V, E, src, dst, n_chunks, opts, again > 0, g);
   }
   if (rc != HT_OK) {
     (void)hipStreamSynchronize(ctx->stream);
@@ -2029,7 +2030,7 @@ int ht_graph_chunk_order(const ht_graph* g, int32_t* order) {
 
 // Alg. 4 on neighbour bitmaps: one |V|-bit map per subgraph and one per batch union; every greedy
 // step is one launch that counts the common members of all candidates with the current union.
-int ht_graph_reorganize(ht_ctx* ctx, const ht_graph* g, int32_t m, int32_t* layout, int64_t* before, int64_t* after) {
+static int reorganize_impl(ht_ctx* ctx, const ht_graph* g, int32_t m, int32_t* layout, int64_t* before, int64_t* after) {
   if (!ctx) return HT_EINVAL;
   if (!g || !layout) return ht_set_err(ctx, HT_EINVAL, "ht_graph_reorganize: null argument");
   if (g->ctx != ctx) return ht_set_err(ctx, HT_ESTATE, "graph belongs to another context");
@@ -2144,6 +2145,11 @@ int ht_graph_reorganize(ht_ctx* ctx, const ht_graph* g, int32_t m, int32_t* layo
   for (int c = 0; c < mn; ++c) layout[c] = lay[c];
   HT_HIP(ctx, hipStreamSynchronize(st));
   return HT_OK;
+}
+
+int ht_graph_reorganize(ht_ctx* ctx, const ht_graph* g, int32_t m, int32_t* layout, int64_t* before, int64_t* after) {
+  if (!ctx) return HT_EINVAL;
+  return ht_with_room(ctx, [&] { return reorganize_impl(ctx, g, m, layout, before, after); });
 }
 
 }  // extern "C"

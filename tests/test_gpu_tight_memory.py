@@ -137,6 +137,33 @@ def test_smallest_budget(data, what, held):
         c.close()
 
 
+def test_partition_beside_a_filled_context(data):
+    """A second graph is partitioned in what two graphs alone need, whatever calls on the first one have left in the context."""
+    def second(c):
+        return B.ht_partition(c.ctx, data["V"], data["src"], data["dst"], data["n"])
+    lo, hi = data["smallest"], 1024.0
+    while hi - lo > 0.05:
+        mid, c = (lo + hi) / 2, Ctx(data)
+        c.budget(mid)
+        try:
+            B.ht_graph_destroy(second(c))
+            hi = mid
+        except B.HongtuError as e:
+            assert e.code == B.HT_ENOMEM
+            lo = mid
+        c.close()
+    c = Ctx(data)
+    try:
+        want = c.run("bwd_recompute")
+        c.budget(hi + SLACK)
+        g = second(c)
+        c.budget(0)
+        _close(c.run("bwd_recompute"), want, "the first graph afterwards")
+        B.ht_graph_destroy(g)
+    finally:
+        c.close()
+
+
 def test_graph_capture_under_a_tight_budget(data):
     """Epochs that go chunk by chunk for want of memory settle on their scratch memory, so that they can be captured and replayed."""
     c = Ctx(data)
