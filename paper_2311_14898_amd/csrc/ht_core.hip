@@ -128,11 +128,17 @@ int ht_scratch_release(ht_ctx* ctx, int slot) {
   return HT_OK;
 }
 
-int64_t ht_room(ht_ctx* ctx) {
+int64_t ht_device_free(ht_ctx* ctx) {
   int64_t room = INT64_MAX;
   size_t free_b = 0, total_b = 0;
   if (hipMemGetInfo(&free_b, &total_b) == hipSuccess) room = (int64_t)free_b;
   else (void)hipGetLastError();
+  if (ctx->device_bytes > 0) room = std::min(room, std::max<int64_t>(0, ctx->device_bytes - ctx->hbm_used));
+  return room;
+}
+
+int64_t ht_room(ht_ctx* ctx) {
+  int64_t room = ht_device_free(ctx);
   if (ctx->hbm_budget > 0) room = std::min(room, std::max<int64_t>(0, ctx->hbm_budget - ctx->hbm_used));
   return room;
 }
@@ -291,6 +297,7 @@ int ht_ctx_create(ht_ctx** out, int device, void* hip_stream) {
   if (const char* v = getenv("HT_SLAB_ALIGN")) c->slab_align = atoi(v);
   if (const char* v = getenv("HT_FUSE_UPDATE")) c->fuse_update = atoi(v);
   if (const char* v = getenv("HT_AGG_PHASES")) c->agg_phases = atoi(v) > 1 ? atoi(v) : 1;
+  if (const char* v = getenv("HT_DEVICE_BYTES")) c->device_bytes = atoll(v);
   if (const char* v = getenv("HT_LINK_BLOCK_ROWS")) c->link_block_rows = atoll(v) > 0 ? atoll(v) : c->link_block_rows;
   if (hip_stream) {
     c->stream = (hipStream_t)hip_stream;

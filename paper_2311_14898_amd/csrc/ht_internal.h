@@ -72,6 +72,7 @@ struct ht_ctx {
   int64_t tight_room = -1;     // room that was left after the last such call (-1: none since memory was plentiful)
   size_t gat_keep_limit = 0;   // a GAT epoch that kept this many bytes between its passes ran out of memory (0: none did) ...
   int64_t gat_keep_room = 0;   // ... and had this much room without them
+  int64_t device_bytes = 0;    // HT_DEVICE_BYTES: plan as if the device had no more memory than this for the context (0: as it reports)
   int fuse_update = 0;  // HT_FUSE_UPDATE=1: layers that keep no aggregate run aggregate + transform as one kernel (A/B)
   int n_threads = 0;  // host threads for CPU-side accumulation (0 = chosen on first use)
 };
@@ -106,6 +107,8 @@ void ht_dev_free(ht_ctx* ctx, void* p, size_t bytes);
 int ht_scratch(ht_ctx* ctx, int slot, size_t bytes, void** out);
 // Gives a slot's memory back (after the work in flight).
 int ht_scratch_release(ht_ctx* ctx, int slot);
+// What the device reports free.
+int64_t ht_device_free(ht_ctx* ctx);
 // Bytes that can still be allocated: by the byte budget and by the device's free memory.
 int64_t ht_room(ht_ctx* ctx);
 

@@ -1459,9 +1459,7 @@ static int epoch_impl(ht_ctx* ctx, const ht_graph* g, const ht_model* model, con
   const int gather_mode = plan ? plan->gather_mode : HT_GATHER_AUTO;
   int64_t budget = plan ? plan->hbm_budget_bytes : 0;
   if (budget == 0) {
-    size_t fr = 0, tot = 0;
-    HT_HIP(ctx, hipMemGetInfo(&fr, &tot));
-    budget = (int64_t)fr - ((int64_t)2 << 30);
+    budget = ht_device_free(ctx) - ((int64_t)2 << 30);
     // buffers of a previous epoch with the same shape are reused, so count them as free
     if (ctx->ws)
       for (size_t b : ctx->ws->dev_bytes_of) budget += (int64_t)b;
