@@ -89,10 +89,12 @@ int ht_sync(ht_ctx *ctx);
  * until ht_ctx_destroy.  Where there is room they take more of it than they
  * need, to run all chunks at once: up to 8 GiB of rows and 4 GiB of partial
  * sums, and on a graph from its first backward pass on its entries grouped by
- * source (4 or 8 bytes each); ht_gat_epoch up to 16 GiB more for rows kept
- * between its passes.  A call that is refused memory, by the cap or by the
- * device, gives all of that back and is made again chunk by chunk, so no call
- * fails for memory that an earlier one or a faster pass holds. */
+ * source (4 or 8 bytes each; up to 1 GiB of a destroyed graph's stay for the
+ * next one); ht_gat_epoch up to 16 GiB more for rows kept between its passes.
+ * A call that is refused memory, by the cap or by the device, gives all of
+ * that back and is made again chunk by chunk, so no call fails for memory that
+ * an earlier one or a faster pass holds.
+ */
 int ht_ctx_set_hbm_budget(ht_ctx *ctx, int64_t bytes);
 /* Number of ht_epoch calls on this context that ran as one HIP graph launch
  * (ht_plan_opts.use_graph); -1 for a null context. */

@@ -1760,6 +1760,9 @@ void plan_by_source(const ht_graph* g, DevBlock* kept, DevBlock* tmp) {
   tmp->add<uint64_t>((size_t)bound);
 }
 
+// A destroyed graph's list memory is kept for the next graph up to this size.
+constexpr size_t LIST_KEPT_BYTES = (size_t)1 << 30;
+
 int build_by_source(ht_ctx* ctx, const ht_graph* g, int slot) {
   hipStream_t st = ctx->stream;
   SourceRows& S = g->by_src;
@@ -1950,7 +1953,10 @@ int ht_graph_destroy(ht_graph* g) {
     (void)hipStreamSynchronize(g->ctx->stream);
     std::vector<ht_graph*>& all = g->ctx->graphs;
     all.erase(std::remove(all.begin(), all.end(), g), all.end());
-    if (g->ctx->list_owner == g) g->ctx->list_owner = nullptr;
+    if (g->ctx->list_owner == g) {
+      g->ctx->list_owner = nullptr;
+      if (g->ctx->scratch_bytes[HT_S_LIST] > LIST_KEPT_BYTES) (void)ht_scratch_release(g->ctx, HT_S_LIST);
+    }
   }
   delete g;
   return HT_OK;
