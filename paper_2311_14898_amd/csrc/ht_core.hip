@@ -191,7 +191,8 @@ bool ht_may_spend(ht_ctx* ctx) {
 int64_t ht_held(const ht_ctx* ctx) {
   int64_t held = 0;
   for (size_t b : ctx->scratch_bytes) held += (int64_t)b;
-  for (const ht_graph* g : ctx->graphs) held += (int64_t)((g == ctx->list_owner ? 0 : g->by_src.blk.mem.bytes()) + g->by_src.mult.bytes());
+  for (const ht_graph* g : ctx->graphs)
+    held += (int64_t)((g == ctx->list_owner ? 0 : g->by_src.blk.mem.bytes()) + g->by_src.mult.bytes()) + g->plan_fwd.bytes() + g->plan_bwd.bytes();
   return held;
 }
 
@@ -202,7 +203,11 @@ bool ht_give_back(ht_ctx* ctx) {
   (void)hipStreamSynchronize(ctx->stream);
   for (hipStream_t s : ctx->side) (void)hipStreamSynchronize(s);
   for (int k = 0; k < HT_N_SCRATCH; ++k) (void)ht_scratch_release(ctx, k);
-  for (const ht_graph* g : ctx->graphs) g->by_src = SourceRows();
+  for (const ht_graph* g : ctx->graphs) {
+    g->by_src = SourceRows();
+    g->plan_fwd.release();
+    g->plan_bwd.release();
+  }
   ctx->list_owner = nullptr;
   ++ctx->scratch_gen;      // (captured epochs hold pointers into the lists as well)
   return true;
@@ -295,6 +300,10 @@ int ht_ctx_create(ht_ctx** out, int device, void* hip_stream) {
   if (const char* v = getenv("HT_AGG_UNROLL")) c->agg_unroll = atoi(v) == 8 ? 8 : 4;
   if (const char* v = getenv("HT_AGG_UNIFORM")) c->agg_uniform = atoi(v);
   if (const char* v = getenv("HT_SLAB_ALIGN")) c->slab_align = atoi(v);
+  if (const char* v = getenv("HT_DENSE")) c->dense = atoi(v);
+  if (const char* v = getenv("HT_FINE")) c->fine = atoi(v);
+  if (const char* v = getenv("HT_DENSE_WORK")) c->dense_work = std::max<int64_t>(1, atoll(v));
+  if (const char* v = getenv("HT_FINE_WORK")) c->fine_work = std::max<int64_t>(1, atoll(v));
   if (const char* v = getenv("HT_FUSE_UPDATE")) c->fuse_update = atoi(v);
   if (const char* v = getenv("HT_AGG_PHASES")) c->agg_phases = atoi(v) > 1 ? atoi(v) : 1;
   if (const char* v = getenv("HT_DEVICE_BYTES")) c->device_bytes = atoll(v);

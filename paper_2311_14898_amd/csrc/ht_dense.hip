@@ -1,0 +1,744 @@
+// Aggregation over the dense core of a graph on the matrix cores (Eq. 2's AGGREGATE and its backward).
+//
+// On a power-law graph the rows with most entries and the columns named most often meet in blocks that are far from sparse (233 k vertices,
+// 78 M distinct pairs: two thirds of them lie in tiles of 256 rows x 64 columns that are at least 5 % full, once both sides are
+// sorted by degree).  A gather moves 4 d bytes per entry and is held up by the requests a CU can have in flight; a tile's product
+// costs the same whatever it holds, so above a few per cent of fill it is cheaper on the matrix cores.
+//
+// The entries in such tiles are multiplicities, small whole numbers that bf16 holds exactly (those above 255 stay with the gather).  The rows
+// they multiply, s_u h_u in fp32, are split into three bf16 values whose sum they are, so that every product is exact and what
+// is rounded is the fp32 sums alone, one rounding per 16 products where the gather rounds each.  The large and the two small parts have sums of their own
+// (one sum for all three would round the small ones away: see k_split_tn).
+//
+// What a tile does not hold, the work items of ht_spmm.hip do, over a list of the remaining entries; k_spmm_fix adds both in a
+// fixed order, so results are bit-reproducible.
+//
+// Measured, ms an epoch, all entries by 256-entry items | with this: 233 k vertices, 115 M edges, 602-256-41 20.8 | 13.0; 116 k, 57 M, 301-129-47
+// 4.18 | 2.86; 2.45 M, 62 M, 100-256-256-47 64.3 | 51.2 (there 14 % of the entries lie in tiles; the short items of the rest give as much).
+// Relative error against fp64 (2-norm), all by items | with this: 40 k vertices, 4 M edges, 602 columns 3.4e-8 | 3.0e-8; 20 k, 2 M, 41 columns
+// 3.2e-8 | 3.2e-8; 5 k, 0.4 M, 130 columns 4.3e-8 | 3.5e-8.
+#include <algorithm>
+#include <vector>
+
+#include "ht_internal.h"
+
+namespace {
+
+constexpr int TB = 256;
+constexpr int64_t PART_ENTRIES = 32768;         // entries that one block looks at
+constexpr int MAX_RB = 512, MAX_CG = 2048;      // row blocks and column groups looked at: the 131,072 rows and columns with most entries
+constexpr int ETILE = 2048;
+// Entries from which a tile is taken, 4 % of its cells.  A tile takes 28 ns of the card for 256 columns at 0.95 PFLOP/s; what its entries
+// would take in the gather is 0.05 ns each where rows come out of L2 and up to 0.17 where they do not.  Epochs with the line at 200, 300, 450, 650 entries:
+// 233 k vertices, 115 M edges 18.4, 18.2, 17.1, 17.1 ms, 2.45 M, 62 M 65.9, 65.6, 64.5, 65.8; 60 k, 3 M edges, layer at 450, 650, 1000, 2000 537, 513, 480,
+// 468 us (all with other kernels beside them).
+constexpr int32_t DENSE_LEAST = 650;
+constexpr int SEG_BLOCKS = 512;                 // segments that a graph's tiles are cut into at least
+// (smaller than that the rows stay in the L2s whatever the order: 100 k rows of 40 columns, 10 M entries 388 -> 409 us a layer with short
+// items; 60 k of 129, 3 M entries 441 -> 413, 300 k of 64, 6 M entries 643 -> 588, 1 M of 128, 30 M entries 4.4 -> 3.6 ms)
+constexpr int64_t FINE_ROWS = (int64_t)24 << 20;
+constexpr int REST_SEG = 48, FINE_SEG = 64;     // entries of a work item
+inline unsigned nblk(int64_t n, int tb = TB) { return (unsigned)((n + tb - 1) / tb); }
+
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+
+// ---- choosing the tiles
+
+// key = (most entries first, vertex)
+__global__ void k_rank_keys(const int64_t* __restrict__ ptr, const int32_t* __restrict__ cnt, int64_t V, uint64_t* __restrict__ keys) {
+  const int64_t v = (int64_t)blockIdx.x * TB + threadIdx.x;
+  if (v >= V) return;
+  const int64_t deg = ptr ? ptr[v + 1] - ptr[v] : (int64_t)cnt[v];
+  const uint64_t k = 0xFFFFFFu - (uint64_t)(deg < 0xFFFFFF ? deg : 0xFFFFFF);
+  keys[v] = (k << 32) | (uint64_t)v;
+}
+// order[i] = the i-th vertex (-1 behind the last), rank[v] = its place
+__global__ void k_rank(const uint64_t* __restrict__ keys, int64_t V, int64_t n_order, int32_t* __restrict__ order, int32_t* __restrict__ rank) {
+  const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
+  const int32_t v = i < V ? (int32_t)(keys[i] & 0xFFFFFFFFu) : -1;
+  if (v >= 0 && rank) rank[v] = (int32_t)i;
+  if (i < n_order) order[i] = v;
+}
+
+// The entries of row blocks, in parts of about PART_ENTRIES: part p of block b takes an equal share of them, counted through its rows one
+// after the other, so that neither a hub's row nor many short ones hold a part up.  Duplicates of an unmerged list come one after the other.
+struct RowEntries {
+  const int64_t* ptr;
+  const int32_t* idx;
+  const int32_t* order;    // rows by rank
+  const int32_t* crank;    // ranks of the columns
+  const int64_t* part0;    // [n_rb + 1] first part of each row block
+  int n_rb;
+};
+// parts of every row block
+__global__ void __launch_bounds__(TB) k_dense_parts(const int64_t* __restrict__ ptr, const int32_t* __restrict__ order, int32_t* __restrict__ parts) {
+  __shared__ unsigned long long sum;
+  if (threadIdx.x == 0) sum = 0;
+  __syncthreads();
+  const int32_t row = order[(int64_t)blockIdx.x * DENSE_ROWS + threadIdx.x];
+  if (row >= 0) atomicAdd(&sum, (unsigned long long)(ptr[row + 1] - ptr[row]));
+  __syncthreads();
+  if (threadIdx.x == 0) parts[blockIdx.x] = (int32_t)((sum + PART_ENTRIES - 1) / PART_ENTRIES);
+}
+// The block's part: its rows' first entries and where they lie in the count.
+struct Part {
+  int rb;
+  int64_t f0, f1;          // the share
+  const int64_t* at;       // [DENSE_ROWS + 1] entries before each row
+  const int64_t* first;    // [DENSE_ROWS] first entry of each row
+  __device__ __forceinline__ bool open(const RowEntries& R) {
+    __shared__ int64_t s_at[DENSE_ROWS + 1], s_first[DENSE_ROWS], s_wave[TB / 64];
+    if ((int64_t)blockIdx.x >= R.part0[R.n_rb]) return false;
+    int lo = 0, hi = R.n_rb;
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (R.part0[mid] <= (int64_t)blockIdx.x) lo = mid; else hi = mid;
+    }
+    rb = lo;
+    const int64_t p = blockIdx.x - R.part0[rb], P = R.part0[rb + 1] - R.part0[rb];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int32_t row = R.order[(int64_t)rb * DENSE_ROWS + tid];
+    const int64_t e0 = row >= 0 ? R.ptr[row] : 0, len = row >= 0 ? R.ptr[row + 1] - e0 : 0;
+    int64_t inc = len;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int64_t y = __shfl_up(inc, o, 64);
+      if (lane >= o) inc += y;
+    }
+    if (lane == 63) s_wave[tid >> 6] = inc;
+    __syncthreads();
+    int64_t before = 0, tot = 0;
+#pragma unroll
+    for (int w = 0; w < TB / 64; ++w) {
+      if (w < (tid >> 6)) before += s_wave[w];
+      tot += s_wave[w];
+    }
+    s_at[tid] = before + inc - len;
+    s_first[tid] = e0;
+    if (tid == 0) s_at[DENSE_ROWS] = tot;
+    at = s_at;
+    first = s_first;
+    f0 = tot * p / P;
+    f1 = tot * (p + 1) / P;
+    __syncthreads();
+    return true;
+  }
+  // row (in the block) of entry f of the count
+  __device__ __forceinline__ int row_of(int64_t f) const {
+    int lo = 0;
+#pragma unroll
+    for (int b = DENSE_ROWS / 2; b > 0; b >>= 1)
+      if (at[lo + b] <= f) lo += b;
+    return lo;
+  }
+};
+static_assert(DENSE_ROWS == TB, "a thread per row");
+
+// cnt[part][column group] = distinct entries
+__global__ void __launch_bounds__(TB) k_dense_count(RowEntries R, int n_cg, bool merged, int32_t* __restrict__ cnt) {
+  __shared__ int32_t hist[MAX_CG];
+  for (int c = threadIdx.x; c < n_cg; c += TB) hist[c] = 0;
+  Part P;
+  if (!P.open(R)) return;
+  const int32_t limit = n_cg * DENSE_COLS;
+  for (int64_t f = P.f0 + threadIdx.x; f < P.f1; f += 4 * TB) {
+    int32_t u[4];
+    bool ok[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t x = f + q * TB;
+      ok[q] = x < P.f1;
+      if (!ok[q]) continue;
+      const int r = P.row_of(x);
+      const int64_t e = P.first[r] + (x - P.at[r]);
+      u[q] = R.idx[e];
+      if (!merged && x > P.at[r] && R.idx[e - 1] == u[q]) ok[q] = false;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int32_t c = ok[q] ? R.crank[u[q]] : limit;
+      if (c < limit) atomicAdd(&hist[c / DENSE_COLS], 1);
+    }
+  }
+  __syncthreads();
+  int32_t* out = cnt + (int64_t)blockIdx.x * n_cg;
+  for (int c = threadIdx.x; c < n_cg; c += TB) out[c] = hist[c];
+}
+
+// flag[block][group] = 1 where the tile is full enough; entries: what those hold together, and the column groups up to the last of them
+__global__ void __launch_bounds__(TB) k_dense_select(const int32_t* __restrict__ cnt, const int64_t* __restrict__ part0, int n_cg, int64_t n, int32_t least, int32_t* __restrict__ flag,
+                                                     unsigned long long* __restrict__ entries) {
+  const int64_t t = (int64_t)blockIdx.x * TB + threadIdx.x;
+  __shared__ int32_t used;
+  if (threadIdx.x == 0) used = 0;
+  __syncthreads();
+  int32_t sum = 0;
+  if (t < n) {
+    const int64_t rb = t / n_cg, cg = t % n_cg, p1 = part0[rb + 1];
+    for (int64_t p = part0[rb]; p < p1; ++p) sum += cnt[p * n_cg + cg];
+    const bool take = sum >= least;
+    flag[t] = take;
+    if (!take) sum = 0;
+    if (take) atomicMax(&used, (int32_t)cg + 1);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  if ((threadIdx.x & 63) == 0 && sum > 0) atomicAdd(entries, (unsigned long long)sum);
+  __syncthreads();
+  if (threadIdx.x == 0 && used > 0) atomicMax(entries + 1, (unsigned long long)used);
+}
+
+// tile numbers in place of the flags (-1: not taken), the tiles' column groups, and to the host: first[block] = tiles before it, then the entries
+__global__ void __launch_bounds__(TB) k_dense_tiles(const int64_t* __restrict__ id, int n_cg, int64_t n, int64_t n_rb, int32_t* __restrict__ flag,
+                                                    int32_t* __restrict__ tile_cg, const unsigned long long* __restrict__ entries,
+                                                    int64_t* __restrict__ host) {
+  const int64_t t = (int64_t)blockIdx.x * TB + threadIdx.x;
+  if (t <= n_rb) host[t] = id[t * n_cg];
+  if (t == 0) {
+    host[n_rb + 1] = (int64_t)entries[0];
+    host[n_rb + 2] = (int64_t)entries[1];
+  }
+  if (t >= n) return;
+  const bool take = flag[t] != 0;
+  flag[t] = take ? (int32_t)id[t] : -1;
+  if (take) tile_cg[id[t]] = (int32_t)(t % n_cg);
+}
+
+// ---- filling them
+
+__global__ void k_row_lengths(const int64_t* __restrict__ ptr, int64_t V, int32_t* __restrict__ len) {
+  const int64_t v = (int64_t)blockIdx.x * TB + threadIdx.x;
+  if (v < V) len[v] = (int32_t)(ptr[v + 1] - ptr[v]);
+}
+
+// byte of (row, column) of a tile: 32-column stages, 32-row parts, and 16 bytes for each lane of the wave that multiplies them: its
+// eight columns of the first 16, then of the second
+__device__ __forceinline__ int64_t cell_at(int64_t tile, int row, int col) {
+  const int k = col & 31;
+  return tile * DENSE_ROWS * DENSE_COLS + (col >> 5) * (DENSE_ROWS * 32) + (row >> 5) * 1024 + ((k >> 3) & 1) * 512 + (row & 31) * 16 +
+         (k >> 4) * 8 + (k & 7);
+}
+
+// The entries of the taken tiles go into their cells; keep[e] = 0 for them, and rest[row] loses them.
+__global__ void __launch_bounds__(TB) k_dense_fill(RowEntries R, const float* __restrict__ w, const float* __restrict__ s, int n_cg,
+                                                   const int32_t* __restrict__ tile_of, uint8_t* __restrict__ cells, uint8_t* __restrict__ keep,
+                                                   int32_t* __restrict__ rest, int32_t* __restrict__ pos) {
+  __shared__ int32_t tab[MAX_CG], gone[DENSE_ROWS];
+  Part P;
+  if (!P.open(R)) return;
+  const int32_t* mine = tile_of + (int64_t)P.rb * n_cg;
+  int any = 0;
+  for (int c = threadIdx.x; c < n_cg; c += TB) {
+    tab[c] = mine[c];
+    any |= tab[c] >= 0;
+  }
+  gone[threadIdx.x] = 0;
+  if (!__syncthreads_or(any)) return;
+  const int32_t limit = n_cg * DENSE_COLS;
+  for (int64_t f = P.f0 + threadIdx.x; f < P.f1; f += TB) {
+    const int r = P.row_of(f);
+    const int64_t e0 = P.first[r], e = e0 + (f - P.at[r]), e1 = e0 + (P.at[r + 1] - P.at[r]);
+    const int32_t u = R.idx[e], c = R.crank[u];
+    const int32_t t = c < limit ? tab[c / DENSE_COLS] : -1;
+    if (t < 0) continue;
+    float m = 0.f;
+    bool first = true;
+    if (w) {
+      // (the multiplicity out of w = multiplicity * s: both roundings together are off by less than 2^-23 of it)
+      m = rintf(w[e] / s[u]);
+    } else {   // a run of equal entries; one of more than 255 stays as it is
+      int64_t a = e, z = e + 1;
+      while (a > e0 && e - a < 256 && R.idx[a - 1] == u) --a;
+      while (z < e1 && z - e < 256 && R.idx[z] == u) ++z;
+      m = (float)(z - a);
+      first = a == e;
+    }
+    if (!(m >= 1.f && m <= 255.f)) continue;
+    if (first) cells[cell_at(t, r, c % DENSE_COLS)] = (uint8_t)m;
+    keep[e] = 0;
+    atomicAdd(&gone[r], 1);
+  }
+  __syncthreads();
+  const int32_t row = R.order[(int64_t)P.rb * DENSE_ROWS + threadIdx.x];
+  if (row < 0) return;
+  if (gone[threadIdx.x] > 0) atomicSub(&rest[row], gone[threadIdx.x]);
+  pos[row] = (int32_t)(P.rb * DENSE_ROWS + threadIdx.x);
+}
+
+// entries kept of every ETILE of them
+__global__ void __launch_bounds__(TB) k_keep_count(const uint8_t* __restrict__ keep, int64_t n, int32_t* __restrict__ cnt) {
+  __shared__ int32_t part[TB / 64];
+  int32_t sum = 0;
+  const int64_t e = (int64_t)blockIdx.x * ETILE + threadIdx.x * 8;
+  if (e + 8 <= n) {
+    const uint64_t q = *reinterpret_cast<const uint64_t*>(keep + e);
+    sum = __popcll(q);
+  } else {
+    for (int j = 0; j < 8; ++j) sum += e + j < n ? keep[e + j] : 0;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
+  __syncthreads();
+  if (threadIdx.x == 0) cnt[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
+}
+__global__ void __launch_bounds__(TB) k_keep_copy(const uint8_t* __restrict__ keep, int64_t n, const int64_t* __restrict__ base,
+                                                  const int32_t* __restrict__ idx, const float* __restrict__ w, const float* __restrict__ s,
+                                                  int32_t* __restrict__ idx_out, float* __restrict__ w_out) {
+  __shared__ int32_t part[TB / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t first = (int64_t)blockIdx.x * ETILE + wave * (ETILE / 4);
+  uint64_t m[ETILE / TB];
+  int32_t tot = 0;
+#pragma unroll
+  for (int r = 0; r < ETILE / TB; ++r) {
+    const int64_t e = first + r * 64 + lane;
+    m[r] = __ballot(e < n && keep[e] != 0);
+    tot += __popcll(m[r]);
+  }
+  if (lane == 0) part[wave] = tot;
+  __syncthreads();
+  int64_t at = base[blockIdx.x];
+  for (int k = 0; k < wave; ++k) at += part[k];
+#pragma unroll
+  for (int r = 0; r < ETILE / TB; ++r) {
+    const int64_t e = first + r * 64 + lane;
+    if ((m[r] >> lane) & 1) {
+      const int64_t to = at + __popcll(m[r] & (lane == 0 ? 0ull : (~0ull >> (64 - lane))));
+      const int32_t u = idx[e];
+      idx_out[to] = u;
+      w_out[to] = w ? w[e] : s[u];
+    }
+    at += __popcll(m[r]);
+  }
+}
+
+// ---- the products
+
+constexpr float DSCALE = 0x1p24f, DUNSCALE = 0x1p-24f;
+// Rows with larger values (or any that are not finite) go entry by entry: 0 x inf would reach rows that do not name them, and scaled sums could
+// overflow.  Below it 2^20 products of 255 and the scale stay finite.
+constexpr float DLARGEST = 0x1p64f;
+
+// s_u h_u of 32 columns as three bf16 each, in the order in which k_dense reads them: [column block][part][16 columns][feature][16].
+// bad[group][feature / 64]: something in it is too large or not finite.  Grid: groups of 32 columns x 64 features.
+__global__ void __launch_bounds__(TB) k_dense_pack(const float* __restrict__ src, int64_t ld, const float* __restrict__ s, int d, int dp, int n128,
+                                                   const int32_t* __restrict__ cols, __bf16* __restrict__ planes, uint8_t* __restrict__ bad) {
+  const int f = blockIdx.y * 64 + (threadIdx.x & 63), oct = threadIdx.x >> 6;
+  const bool wide = f < n128 * 128;
+  const int f0 = wide ? f & ~127 : n128 * 128, bn = wide ? 128 : 64;
+  const int64_t g = blockIdx.x;
+  v8bf p[3];
+  int odd = 0;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int32_t u = cols[g * 32 + oct * 8 + j];
+    float x = 0.f;
+    if (u >= 0 && f < d) x = s[u] * src[(int64_t)u * ld + f];
+    odd |= !(fabsf(x) <= DLARGEST);
+    x *= DSCALE;
+    p[0][j] = (__bf16)x;
+    const float r = x - (float)p[0][j];
+    p[1][j] = (__bf16)r;
+    p[2][j] = (__bf16)(r - (float)p[1][j]);
+  }
+  __bf16* out = planes + g * dp * 96 + (int64_t)f0 * 96 + ((oct >> 1) * bn + (f - f0)) * 16 + (oct & 1) * 8;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) *reinterpret_cast<v8bf*>(out + q * 2 * bn * 16) = p[q];
+  odd = __syncthreads_or(odd);
+  if (threadIdx.x == 0) bad[g * (dp / 64) + blockIdx.y] = (uint8_t)(odd != 0);
+}
+
+struct DenseArgs {
+  const uint8_t* cells;
+  const int32_t* tile_cg;
+  const DenseSeg* segs;
+  const int32_t* cols;
+  const __bf16* planes;
+  const uint8_t* bad;
+  const float* src;
+  const float* s;
+  int64_t ld, out_ld;
+  int d, dp, f0;
+  float* partial;         // [segment][256] rows
+};
+
+// eight whole numbers below 256 as bf16
+__device__ __forceinline__ v8bf cells8(uint32_t lo, uint32_t hi) {
+  auto two = [](float a, float b) { return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u); };
+  v4u r;
+  r.x = two((float)(lo & 255u), (float)((lo >> 8) & 255u));
+  r.y = two((float)((lo >> 16) & 255u), (float)(lo >> 24));
+  r.z = two((float)(hi & 255u), (float)((hi >> 8) & 255u));
+  r.w = two((float)((hi >> 16) & 255u), (float)(hi >> 24));
+  return __builtin_bit_cast(v8bf, r);
+}
+
+// One segment (tiles of one row block) x BN features: 8 waves of 64 rows x BN / 2 features, one block per CU (128 accumulators a lane).
+// 256 rows, because every column's parts are read once per row block and 128 rows would ask L2 for 32 bytes a clock and CU, all
+// it gives; 32 columns a stage, in order of the lanes that multiply them, so that they go to LDS as they are.  22.6 k tiles
+// x 1,152 columns (602 + 256 + 256) 2.66 ms, 0.96 PFLOP/s of the three products; an 8192^3 bf16 product of the vendor's library runs at 1.23.  Loads one stage
+// ahead 3.2 ms; two and three ahead 3.0; the stage's column group out of LDS instead of memory (its load waited for all before it) 2.66.
+template <int BN>
+__global__ void __launch_bounds__(512) k_dense(DenseArgs a) {
+  constexpr int TJ = BN / 64, STAGE = 6 * BN * 16, CH = STAGE * 2 / 16, NB = (CH + 511) / 512;   // 16-byte pieces of a stage
+  __shared__ __attribute__((aligned(16))) __bf16 Bs[2][STAGE];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, half = lane >> 5;
+  const DenseSeg seg = a.segs[blockIdx.x];
+  const int f0 = a.f0 + (int)blockIdx.y * BN;
+  __shared__ int32_t cg[DENSE_SEG];   // (read from memory on the way, a stage's number would wait for every load before it)
+  if (tid < seg.n) cg[tid] = a.tile_cg[seg.tile0 + tid];
+  __syncthreads();
+  float* out = a.partial + (int64_t)blockIdx.x * DENSE_ROWS * a.out_ld;
+
+  int odd = 0;
+  for (int t = tid; t < seg.n * 2 * (BN / 64); t += 512) {
+    const int g = t / (BN / 64);
+    odd |= a.bad[((int64_t)cg[g >> 1] * 2 + (g & 1)) * (a.dp / 64) + f0 / 64 + t % (BN / 64)];
+  }
+  if (__syncthreads_or(odd)) {   // entry by entry: a feature per thread, four rows at a time
+    const int f = f0 + tid % BN;
+    if (f >= ((a.d + 3) & ~3)) return;
+    for (int r0 = tid / BN * 4; r0 < DENSE_ROWS; r0 += 512 / BN * 4) {
+      float acc[4] = {0.f, 0.f, 0.f, 0.f};
+      for (int t = 0; t < seg.n; ++t)
+        for (int q = 0; q < 4; ++q) {
+          const uint8_t* c = a.cells + cell_at(seg.tile0 + t, r0, (q >> 1) * 32 + (q & 1) * 8);
+          v4u m[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) m[i] = *reinterpret_cast<const v4u*>(c + i * 16);
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+              uint32_t bits = m[i][x];
+              while (bits) {
+                const int b = (__ffs(bits) - 1) >> 3;
+                const float mult = (float)((bits >> (b * 8)) & 255u);
+                bits &= ~(255u << (b * 8));
+                const int k = (q >> 1) * 32 + (x >> 1) * 16 + (q & 1) * 8 + (x & 1) * 4 + b;
+                const int32_t u = a.cols[(int64_t)cg[t] * DENSE_COLS + k];
+                if (f < a.d) acc[i] = fmaf(mult, a.s[u] * a.src[(int64_t)u * a.ld + f], acc[i]);
+              }
+            }
+        }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) out[(int64_t)(r0 + i) * a.out_ld + f] = acc[i];
+    }
+    return;
+  }
+
+  v16f hi[2][TJ], lo[2][TJ];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) hi[i][j][e] = lo[i][j][e] = 0.f;
+
+  const int S = seg.n * 2;
+  // Pieces of the columns' rows travel through registers into one of two LDS stages, three stages ahead of their use; the cells, two.
+  v4u rb[2][NB], ra[2][2];
+  auto fetch_b = [&](int st, v4u* r) {
+    if (st >= S) return;
+    const int group = __builtin_amdgcn_readfirstlane(cg[st >> 1]) * 2 + (st & 1);
+    const v4u* p = reinterpret_cast<const v4u*>(a.planes + (int64_t)group * a.dp * 96 + (int64_t)f0 * 96);
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+      if (CH % 512 == 0 || tid + q * 512 < CH) r[q] = p[tid + q * 512];
+  };
+  auto store_b = [&](int b, const v4u* r) {
+    v4u* p = reinterpret_cast<v4u*>(Bs[b]);
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+      if (CH % 512 == 0 || tid + q * 512 < CH) p[tid + q * 512] = r[q];
+  };
+  auto fetch_a = [&](int st, v4u* r) {
+    if (st >= S) return;
+    const v4u* p = reinterpret_cast<const v4u*>(a.cells + ((int64_t)seg.tile0 * 2 + st) * (DENSE_ROWS * 32) + wm * 2048);
+    r[0] = p[lane];
+    r[1] = p[lane + 64];
+  };
+  fetch_b(0, rb[0]);
+  fetch_a(0, ra[0]);
+  fetch_b(1, rb[1]);
+  fetch_a(1, ra[1]);
+  store_b(0, rb[0]);
+  fetch_b(2, rb[0]);
+  for (int st0 = 0; st0 < S; st0 += 2)   // (S is even)
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      const int st = st0 + x;
+      __syncthreads();
+      v8bf m[2][2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        m[0][i] = cells8(ra[x][i].x, ra[x][i].y);
+        m[1][i] = cells8(ra[x][i].z, ra[x][i].w);
+      }
+      if (st + 1 < S) store_b(x ^ 1, rb[x ^ 1]);
+      fetch_a(st + 2, ra[x]);
+      fetch_b(st + 3, rb[x ^ 1]);
+      const __bf16* B = Bs[x] + (wn * (BN / 2) + l32) * 16 + half * 8;
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+          v8bf b[TJ];
+#pragma unroll
+          for (int j = 0; j < TJ; ++j) b[j] = *reinterpret_cast<const v8bf*>(B + ((p * 2 + k) * BN + j * 32) * 16);
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) {
+              v16f& c = p == 0 ? hi[i][j] : lo[i][j];
+              c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(m[k][i], b[j], c, 0, 0, 0);
+            }
+        }
+    }
+#pragma unroll
+  for (int j = 0; j < TJ; ++j) {
+    const int f = f0 + wn * (BN / 2) + j * 32 + l32;
+    if (f >= ((a.d + 3) & ~3)) continue;   // (zeros up to whole float4)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int r = wm * 64 + i * 32 + (e >> 2) * 8 + half * 4 + (e & 3);
+        out[(int64_t)r * a.out_ld + f] = (hi[i][j][e] + lo[i][j][e]) * DUNSCALE;
+      }
+  }
+}
+
+int pad_features(int d, int* n128) {
+  *n128 = d / 128 + (d % 128 > 64);
+  return *n128 * 128 + (d > *n128 * 128 ? 64 : 0);
+}
+
+// Scratch memory of the making; it is the products' own slot, which is not in use yet.
+struct DenseTmp {
+  DevBlock blk;
+  DevArr<uint64_t> keysA, keysB;
+  DevArr<int32_t> cnt, crank, order_r, order_c, rparts, parts, flag, tile_cg, rest, kcnt;
+  DevArr<int64_t> part0, id, kbase, total;
+  DevArr<uint8_t> keep;
+  int64_t V, n_ent, n_rb, n_cg, n_parts;
+  template <class F>
+  void each(F&& f) {
+    const int64_t T = n_rb * n_cg, et = ceil_div64(n_ent, ETILE);
+    f(keysA, V);
+    f(keysB, V);
+    f(cnt, V);
+    f(crank, V);
+    f(order_r, n_rb * DENSE_ROWS);
+    f(order_c, n_cg * DENSE_COLS);
+    f(rparts, n_rb);
+    f(part0, n_rb + 1);
+    f(parts, n_parts * n_cg);
+    f(flag, T);
+    f(tile_cg, T);
+    f(rest, V);
+    f(kcnt, et);
+    f(id, T + 1);
+    f(kbase, et + 1);
+    f(total, 2);
+    f(keep, n_ent);
+  }
+  DenseTmp(int64_t v, int64_t e) : V(v), n_ent(e) {
+    n_rb = std::min<int64_t>(ceil_div64(v, DENSE_ROWS), MAX_RB);
+    n_cg = std::min<int64_t>(ceil_div64(v, DENSE_COLS), MAX_CG);
+    n_parts = e / PART_ENTRIES + n_rb;      // at most
+    each([&](auto& a, int64_t n) { blk.add<std::remove_reference_t<decltype(*a.p)>>((size_t)n); });
+  }
+  void take() {
+    each([&](auto& a, int64_t n) { blk.take(a, (size_t)n); });
+  }
+};
+
+// Counts the graph's dense tiles (D.taken), and makes the dense part where they hold enough for a pass over d columns.
+int build_dense(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, DenseSide& D) {
+  hipStream_t st = ctx->stream;
+  const int64_t V = g->V, n_ent = ht_entries(g);
+  const int64_t *dst_ptr = ht_row_ptr(g, true), *ptr = ht_row_ptr(g, fwd);
+  const int32_t* idx = fwd ? (g->merged ? g->ucol.p : g->col.p) : g->by_src.idx.p;
+  const float* w = !g->merged ? nullptr : fwd ? g->uw_fwd.p : g->by_src.w.p;
+  DenseTmp t(V, n_ent);
+  // (no more than a quarter of what is there: other passes want memory too)
+  const int64_t room = ht_room(ctx);
+  if ((int64_t)t.blk.planned > room / 4 && t.blk.planned > ctx->scratch_bytes[HT_S_DENSE]) return HT_ENOMEM;
+  HT_TRY(t.blk.alloc_in(ctx, HT_S_DENSE));
+  t.take();
+  const int64_t n_rb = t.n_rb, T = n_rb * t.n_cg;
+  const int n_cg = (int)t.n_cg;
+  // both sides by their number of entries
+  for (int side = 0; side < 2; ++side) {
+    const bool rows = side == 0, by_dst = rows == fwd;
+    if (!by_dst) HT_TRY(ht_graph_source_counts(ctx, g, t.cnt.p));
+    k_rank_keys<<<nblk(V), TB, 0, st>>>(by_dst ? dst_ptr : nullptr, t.cnt.p, V, t.keysA.p);
+    HT_LAUNCH_CHECK(ctx);
+    uint64_t* sorted = nullptr;
+    HT_TRY(ht_radix_sort_u64(ctx, t.keysA.p, t.keysB.p, V, 32, 56, &sorted));
+    const int64_t n_order = rows ? n_rb * DENSE_ROWS : t.n_cg * DENSE_COLS;
+    k_rank<<<nblk(std::max(V, n_order)), TB, 0, st>>>(sorted, V, n_order, rows ? t.order_r.p : t.order_c.p, rows ? nullptr : t.crank.p);
+    HT_LAUNCH_CHECK(ctx);
+  }
+  const RowEntries R{ptr, idx, t.order_r.p, t.crank.p, t.part0.p, (int)n_rb};
+  k_dense_parts<<<(unsigned)n_rb, TB, 0, st>>>(ptr, t.order_r.p, t.rparts.p);
+  HT_LAUNCH_CHECK(ctx);
+  HT_TRY(ht_scan_i32(ctx, t.rparts.p, t.part0.p, n_rb, true));
+  void *p = nullptr, *host_dev = nullptr;
+  HT_TRY(ht_host_scratch(ctx, HT_HS_READBACK, (size_t)(n_rb + 8) * 8, &p));
+  int64_t* host = (int64_t*)p;
+  HT_HIP(ctx, hipHostGetDevicePointer(&host_dev, host, 0));
+  k_dense_count<<<(unsigned)t.n_parts, TB, 0, st>>>(R, n_cg, g->merged, t.parts.p);
+  HT_LAUNCH_CHECK(ctx);
+  HT_TRY(ht_fill_zero(ctx, st, t.total.p, 16));
+  k_dense_select<<<nblk(T), TB, 0, st>>>(t.parts.p, t.part0.p, n_cg, T, DENSE_LEAST, t.flag.p, (unsigned long long*)t.total.p);
+  HT_LAUNCH_CHECK(ctx);
+  HT_TRY(ht_scan_i32(ctx, t.flag.p, t.id.p, T, true));
+  k_dense_tiles<<<nblk(std::max(T, n_rb + 1)), TB, 0, st>>>(t.id.p, n_cg, T, n_rb, t.flag.p, t.tile_cg.p, (const unsigned long long*)t.total.p,
+                                                          (int64_t*)host_dev);
+  HT_LAUNCH_CHECK(ctx);
+  HT_HIP(ctx, hipStreamSynchronize(st));
+  const std::vector<int64_t> first(host, host + n_rb + 1);
+  const int64_t n_tiles = first[n_rb], taken = host[n_rb + 1];
+  D.taken = taken;
+  if (taken * d < ctx->dense_work) return HT_OK;
+  // segments: the tiles of a row block, cut where there are more than a block should work through
+  const int64_t seg_tiles = std::min<int64_t>(DENSE_SEG, std::max<int64_t>(2, n_tiles / SEG_BLOCKS));
+  std::vector<DenseSeg> segs;
+  std::vector<int32_t> seg0(n_rb + 1);
+  for (int64_t b = 0; b < n_rb; ++b) {
+    seg0[b] = (int32_t)segs.size();
+    const int64_t n = first[b + 1] - first[b], k = ceil_div64(n, seg_tiles);
+    for (int64_t j = 0; j < k; ++j) {
+      const int64_t a = n * j / k, z = n * (j + 1) / k;
+      segs.push_back(DenseSeg{(int32_t)(first[b] + a), (int32_t)(z - a)});
+    }
+  }
+  seg0[n_rb] = (int32_t)segs.size();
+  D.n_tiles = n_tiles;
+  D.n_segs = (int64_t)segs.size();
+  D.n_cols = host[n_rb + 2] * DENSE_COLS;
+  const size_t cell_bytes = (size_t)n_tiles * DENSE_ROWS * DENSE_COLS;
+  if ((int64_t)cell_bytes + 8 * (n_ent - taken) > room / 4) return HT_ENOMEM;
+  D.tiles.add<uint8_t>(cell_bytes);
+  D.tiles.add<int32_t>((size_t)n_tiles);
+  D.tiles.add<DenseSeg>(segs.size());
+  D.tiles.add<int32_t>(seg0.size());
+  D.tiles.add<int32_t>((size_t)V);
+  D.tiles.add<int32_t>((size_t)D.n_cols);
+  HT_TRY(D.tiles.alloc(ctx));
+  D.tiles.take(D.cells, cell_bytes);
+  D.tiles.take(D.tile_cg, (size_t)n_tiles);
+  D.tiles.take(D.segs, segs.size());
+  D.tiles.take(D.seg0, seg0.size());
+  D.tiles.take(D.pos, (size_t)V);
+  D.tiles.take(D.cols, (size_t)D.n_cols);
+  HT_HIP(ctx, hipMemcpyAsync(D.segs.p, segs.data(), segs.size() * sizeof(DenseSeg), hipMemcpyHostToDevice, st));
+  HT_HIP(ctx, hipMemcpyAsync(D.seg0.p, seg0.data(), seg0.size() * 4, hipMemcpyHostToDevice, st));
+  HT_HIP(ctx, hipMemcpyAsync(D.cols.p, t.order_c.p, (size_t)D.n_cols * 4, hipMemcpyDeviceToDevice, st));
+  HT_HIP(ctx, hipMemcpyAsync(D.tile_cg.p, t.tile_cg.p, (size_t)n_tiles * 4, hipMemcpyDeviceToDevice, st));
+  HT_TRY(ht_fill_zero(ctx, st, D.cells.p, cell_bytes));
+  HT_TRY(ht_fill_words(ctx, st, D.pos.p, (size_t)V * 4, 0xFFFFFFFFu));
+  HT_TRY(ht_fill_words(ctx, st, t.keep.p, ((size_t)n_ent + 3) & ~(size_t)3, 0x01010101u));
+  k_row_lengths<<<nblk(V), TB, 0, st>>>(ptr, V, t.rest.p);
+  HT_LAUNCH_CHECK(ctx);
+  k_dense_fill<<<(unsigned)t.n_parts, TB, 0, st>>>(R, w, g->s.p, n_cg, t.flag.p, D.cells.p, t.keep.p, t.rest.p, D.pos.p);
+  HT_LAUNCH_CHECK(ctx);
+  // what is left, in the same order
+  const int64_t et = ceil_div64(n_ent, ETILE);
+  k_keep_count<<<(unsigned)et, TB, 0, st>>>(t.keep.p, n_ent, t.kcnt.p);
+  HT_LAUNCH_CHECK(ctx);
+  HT_TRY(ht_scan_i32(ctx, t.kcnt.p, t.kbase.p, et, true));
+  HT_HIP(ctx, hipMemcpyAsync(host, t.kbase.p + et, 8, hipMemcpyDeviceToHost, st));
+  HT_HIP(ctx, hipStreamSynchronize(st));
+  D.n_rest = host[0];
+  D.rest.add<int32_t>((size_t)std::max<int64_t>(D.n_rest, 1));
+  D.rest.add<float>((size_t)std::max<int64_t>(D.n_rest, 1));
+  D.rest.add<int64_t>((size_t)V + 1);
+  HT_TRY(D.rest.alloc(ctx));
+  D.rest.take(D.idx, (size_t)std::max<int64_t>(D.n_rest, 1));
+  D.rest.take(D.w, (size_t)std::max<int64_t>(D.n_rest, 1));
+  DevArr<int64_t> rptr;
+  D.rest.take(rptr, (size_t)V + 1);
+  k_keep_copy<<<(unsigned)et, TB, 0, st>>>(t.keep.p, n_ent, t.kbase.p, idx, w, g->s.p, D.idx.p, D.w.p);
+  HT_LAUNCH_CHECK(ctx);
+  HT_TRY(ht_scan_i32(ctx, t.rest.p, rptr.p, V, true));
+  HT_TRY(ht_graph_row_items(ctx, V, rptr.p, D.n_rest, D.idx.p, D.pos.p, REST_SEG, HT_S_DENSE, &D.items));
+  D.ok = true;
+  return HT_OK;
+}
+
+}  // namespace
+
+int ht_pass_plan(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, PassPlan* out) {
+  *out = PassPlan();
+  GraphPlan& P = fwd ? g->plan_fwd : g->plan_bwd;
+  const int64_t n_ent = ht_entries(g);
+  if (n_ent >= ((int64_t)1 << 31)) return HT_OK;
+  const bool may = !ctx->static_mode && !ctx->no_grow && ht_may_spend(ctx);
+  // makes `what` (its part of the plan) unless there was no memory for it with as much room as there is now
+  auto make = [&](auto& what, auto&& build) -> int {
+    if (!may || (what.refused >= 0 && ht_room(ctx) <= what.refused)) return HT_OK;
+    const int rc = build();
+    if (rc != HT_ENOMEM) return rc;
+    (void)hipStreamSynchronize(ctx->stream);
+    what = std::remove_reference_t<decltype(what)>();
+    (void)ht_scratch_release(ctx, HT_S_DENSE);
+    what.refused = ht_room(ctx);
+    return HT_OK;
+  };
+  if (ctx->dense && n_ent * d >= ctx->dense_work) {
+    DenseSide& D = P.dense;
+    if (!D.ok && (D.taken < 0 || D.taken * d >= ctx->dense_work)) HT_TRY(make(D, [&] { return build_dense(ctx, g, fwd, d, D); }));
+    if (D.ok && D.taken * d >= ctx->dense_work) {
+      out->items = &D.items;
+      out->dense = &D;
+      return HT_OK;
+    }
+  }
+  if (ctx->fine && n_ent * d >= ctx->fine_work && (ctx->fine_work < HT_FINE_WORK || g->V * d * 4 >= FINE_ROWS)) {
+    ShortItems& F = P.fine;
+    if (!F.ok)
+      HT_TRY(make(F, [&]() -> int {
+        const int32_t* idx = fwd ? (g->merged ? g->ucol.p : g->col.p) : g->by_src.idx.p;
+        HT_TRY(ht_graph_row_items(ctx, g->V, ht_row_ptr(g, fwd), n_ent, idx, nullptr, FINE_SEG, HT_S_DENSE, &F.items));
+        F.ok = true;
+        return HT_OK;
+      }));
+    if (F.ok) out->items = &F.items;
+  }
+  return HT_OK;
+}
+
+size_t ht_dense_bytes(const DenseSide& D, int d) {
+  int n128;
+  const size_t dp = (size_t)pad_features(d, &n128);
+  return (size_t)D.n_cols / 32 * (dp * 192 + dp / 64) + 256;
+}
+
+// The segments' sums into partial ([segment][256] rows of pitch out_ld).
+int ht_dense_launch(ht_ctx* ctx, hipStream_t st, const DenseSide& D, const float* src, int64_t ld, const float* s, int32_t d, float* partial,
+                    int64_t out_ld) {
+  int n128;
+  const int dp = pad_features(d, &n128);
+  void* mem = nullptr;
+  HT_TRY(ht_scratch(ctx, HT_S_DENSE, ht_dense_bytes(D, d), &mem));
+  __bf16* planes = (__bf16*)mem;
+  uint8_t* bad = (uint8_t*)mem + (size_t)D.n_cols / 32 * dp * 192;
+  k_dense_pack<<<dim3((unsigned)(D.n_cols / 32), dp / 64), TB, 0, st>>>(src, ld, s, d, dp, n128, D.cols.p, planes, bad);
+  HT_LAUNCH_CHECK(ctx);
+  DenseArgs a{D.cells.p, D.tile_cg.p, D.segs.p, D.cols.p, planes, bad, src, s, ld, out_ld, d, dp, 0, partial};
+  if (n128 > 0) k_dense<128><<<dim3((unsigned)D.n_segs, n128), 512, 0, st>>>(a);
+  HT_LAUNCH_CHECK(ctx);
+  if (dp > n128 * 128) {
+    a.f0 = n128 * 128;
+    k_dense<64><<<dim3((unsigned)D.n_segs, 1), 512, 0, st>>>(a);
+    HT_LAUNCH_CHECK(ctx);
+  }
+  return HT_OK;
+}

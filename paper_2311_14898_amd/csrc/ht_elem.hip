@@ -134,12 +134,12 @@ __global__ void k_sgd(SgdBatch b, float lr) {
 // n16 16-byte words from p16 (16-byte aligned), then the words of the ragged ends; a bounded grid
 // that strides, so the launch also fits a HIP graph node at any size
 __global__ void k_zero(uint4* __restrict__ p16, int64_t n16, uint32_t* __restrict__ head, int n_head,
-                       uint32_t* __restrict__ tail, int n_tail) {
+                       uint32_t* __restrict__ tail, int n_tail, uint32_t v) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  for (int64_t i = t; i < n16; i += stride) p16[i] = make_uint4(0u, 0u, 0u, 0u);
-  if (t < n_head) head[t] = 0u;
-  if (t < n_tail) tail[t] = 0u;
+  for (int64_t i = t; i < n16; i += stride) p16[i] = make_uint4(v, v, v, v);
+  if (t < n_head) head[t] = v;
+  if (t < n_tail) tail[t] = v;
 }
 
 }  // namespace
@@ -198,7 +198,7 @@ int ht_sgd(ht_ctx* ctx, hipStream_t st, const std::vector<ht_sgd_item>& items, f
   return HT_OK;
 }
 
-int ht_fill_zero(ht_ctx* ctx, hipStream_t st, void* p, size_t bytes) {
+int ht_fill_words(ht_ctx* ctx, hipStream_t st, void* p, size_t bytes, uint32_t value) {
   if (bytes == 0) return HT_OK;
   if (bytes & 3) return ht_set_err(ctx, HT_EINVAL, "fill: size must be a multiple of 4");
   if ((uintptr_t)p & 3) return ht_set_err(ctx, HT_EINVAL, "fill: pointer must be 4-byte aligned");
@@ -211,7 +211,7 @@ int ht_fill_zero(ht_ctx* ctx, hipStream_t st, void* p, size_t bytes) {
   int64_t blocks = (n16 + 255) / 256;
   if (blocks > 16384) blocks = 16384;
   if (blocks < 1) blocks = 1;
-  k_zero<<<(unsigned)blocks, 256, 0, st>>>((uint4*)(w + n_head), n16, w, n_head, w + n_head + 4 * n16, n_tail);
+  k_zero<<<(unsigned)blocks, 256, 0, st>>>((uint4*)(w + n_head), n16, w, n_head, w + n_head + 4 * n16, n_tail, value);
   HT_LAUNCH_CHECK(ctx);
   return HT_OK;
 }

@@ -16,13 +16,19 @@
 // Shorter items read a narrower range of source rows, which is what keeps them in L2.
 constexpr int HT_SEG = 256;
 
+// Entries times columns of one pass from which a graph's plan is made and used (ht_dense.hip): entries in dense tiles, all entries.  Layers
+// forward and backward, us without | with tiles at millions in them: 3e4 vertices, 3 M edges, 300 columns (360) 491 | 499, 1e4, 4 M, 128
+// (170) 195 | 195, 1e5, 10 M, 128 (510) 675 | 696; 3e4, 12 M, 300 (1,200) 1,096 | 824, 1e5, 40 M, 128 (2,200) 1,581 | 1,162.  A plan takes a
+// millisecond or two to make, so it is left where a pass would gain less than some 100 us; short items (0.2 ms) where it would gain less than 5.
+constexpr int64_t HT_DENSE_WORK = 1000000000, HT_FINE_WORK = 200000000;
+
 struct EpochWs;
 struct ht_graph;
 
 enum {
   HT_S_PACKW = 0, HT_S_TNPART, HT_S_LOSS, HT_S_ACHUNK, HT_S_OCHUNK, HT_S_ZCHUNK, HT_S_DZCHUNK, HT_S_DACHUNK,
   HT_S_NBUF, HT_S_SPART, HT_S_LEAVE, HT_S_MISC, HT_S_TFULL, HT_S_TFULL2, HT_S_GATV, HT_S_GATE, HT_S_GATWS, HT_S_GATP, HT_S_GATKEEP,
-  HT_S_LINK0, HT_S_LINK1, HT_S_LINK2, HT_S_SCAN, HT_S_RSORT, HT_S_TNTAB, HT_S_LIST, HT_N_SCRATCH
+  HT_S_LINK0, HT_S_LINK1, HT_S_LINK2, HT_S_SCAN, HT_S_RSORT, HT_S_TNTAB, HT_S_LIST, HT_S_DENSE, HT_N_SCRATCH
 };
 
 struct ht_ctx {
@@ -73,6 +79,9 @@ struct ht_ctx {
   size_t gat_keep_limit = 0;   // a GAT epoch that kept this many bytes between its passes ran out of memory (0: none did) ...
   int64_t gat_keep_room = 0;   // ... and had this much room without them
   int64_t device_bytes = 0;    // HT_DEVICE_BYTES: plan as if the device had no more memory than this for the context (0: as it reports)
+  int dense = 1;               // HT_DENSE=0: no products over a graph's dense tiles (ht_dense.hip)
+  int fine = 1;                // HT_FINE=0: no shorter work items for training passes
+  int64_t dense_work = HT_DENSE_WORK, fine_work = HT_FINE_WORK;   // HT_DENSE_WORK, HT_FINE_WORK
   int fuse_update = 0;  // HT_FUSE_UPDATE=1: layers that keep no aggregate run aggregate + transform as one kernel (A/B)
   int n_threads = 0;  // host threads for CPU-side accumulation (0 = chosen on first use)
 };
@@ -299,7 +308,60 @@ struct SourceRows {
   DevArr<int32_t> idx;         // destination of each entry
   DevArr<float> w;             // multiplicity * s[destination] (merged graphs; others look s up)
   DevArr<float> mult;          // multiplicity (merged graphs, made for the first GAT backward pass)
+  DevArr<int64_t> ptr;         // [V + 1] first entry of every source
   GraphItems items;            // rows = vertices
+};
+
+// How passes that are made over a graph again and again (training passes with everything in HBM) take one direction's entries: made at
+// the first such pass that has memory for it, kept with the graph, given back with the by-source list (ht_dense.hip).
+//
+// Shorter work items over the same entries: the items in flight at one time read a narrower range of rows, more of which L2 keeps.
+struct ShortItems {
+  bool ok = false;
+  int64_t refused = -1;          // there was no memory for it with this much room
+  GraphItems items;              // rows = destinations, or sources
+};
+// Tiles of DENSE_ROWS x DENSE_COLS multiplicities, rows and columns in order of their number of entries, and work items over the entries in
+// no tile.
+constexpr int DENSE_ROWS = 256, DENSE_COLS = 64;
+constexpr int DENSE_SEG = 64;    // tiles that one block multiplies at most
+struct DenseSeg {
+  int32_t tile0, n;              // consecutive tiles of one row block
+};
+struct DenseSide {
+  bool ok = false;
+  int64_t taken = -1;            // entries that the graph's dense tiles hold (-1: not counted yet)
+  int64_t refused = -1;
+  DevBlock tiles, rest;
+  DevArr<uint8_t> cells;         // the tiles' multiplicities
+  DevArr<int32_t> tile_cg;       // column group of each tile
+  DevArr<DenseSeg> segs;
+  DevArr<int32_t> seg0;          // first segment of each row block, then their number
+  DevArr<int32_t> pos;           // [V] row block * DENSE_ROWS + row in it (-1: the row is in none)
+  DevArr<int32_t> cols;          // [n_cols] vertex of each column (-1: none)
+  DevArr<int32_t> idx;           // entries in no tile ...
+  DevArr<float> w;               // ... and their weights
+  GraphItems items;              // rows in row blocks are all cut rows
+  int64_t n_tiles = 0, n_segs = 0, n_cols = 0, n_rest = 0;
+};
+struct GraphPlan {
+  ShortItems fine;
+  DenseSide dense;
+  int64_t bytes() const {
+    return (int64_t)(fine.items.items.bytes() + fine.items.cuts.bytes() + dense.tiles.mem.bytes() + dense.rest.mem.bytes() +
+                     dense.items.items.bytes() + dense.items.cuts.bytes());
+  }
+  void release() {               // what was counted stays known
+    const int64_t taken = dense.taken;
+    *this = GraphPlan();
+    dense.taken = taken;
+  }
+};
+// What a pass takes of it.
+struct PassPlan {
+  const GraphItems* items = nullptr;   // null: the graph's own items
+  const DenseSide* dense = nullptr;    // null: all entries by these items
+  int64_t parts() const { return items ? items->n_part + (dense ? dense->n_segs * DENSE_ROWS : 0) : 0; }   // of the items, then of the segments
 };
 
 struct ht_graph {
@@ -348,6 +410,7 @@ struct ht_graph {
   std::vector<int64_t> dense_groups;
   DevArr<int64_t> d_dense_groups;
   mutable SourceRows by_src;
+  mutable GraphPlan plan_fwd, plan_bwd;
   DevBlock blk_csc, blk_pairs, blk_chunks;   // the allocations behind the CSC, the distinct-pair arrays, and the per-chunk arenas with the work items
   int64_t v_ori = 0, v_ru = 0, v_load = 0;  // v_load: rows actually loaded per pass with this buffer
   int64_t max_nsrc = 0, max_ndst = 0, max_nnz = 0, max_fpart = 0, max_bpart = 0;
@@ -364,6 +427,23 @@ int ht_graph_by_source(ht_ctx* ctx, const ht_graph* g, int slot);
 void ht_graph_by_source_bytes(const ht_graph* g, int64_t* list, size_t* slot);
 // Makes g->by_src.mult of a merged graph whose by_src is there (HT_ENOMEM: no memory for it).
 int ht_graph_by_source_mult(ht_ctx* ctx, const ht_graph* g);
+
+// Distinct entries (entries, where duplicates are not merged) of every source, into cnt[V].
+int ht_graph_source_counts(ht_ctx* ctx, const ht_graph* g, int32_t* cnt);
+// Work items over rows 0 .. V - 1 with entries ptr[r] .. ptr[r + 1] of idx (values below V); rows with pos[r] >= 0 (pos may be null) become cut
+// rows whatever their length.  The slot is overwritten on the way.
+int ht_graph_row_items(ht_ctx* ctx, int64_t V, const int64_t* ptr, int64_t n_ent, const int32_t* idx, const int32_t* pos, int seg, int slot,
+                       GraphItems* out);
+// Rows of a direction's list: first entries of its rows.
+inline const int64_t* ht_row_ptr(const ht_graph* g, bool fwd) { return !fwd ? g->by_src.ptr.p : g->merged ? g->uindptr.p : g->indptr.p; }
+inline int64_t ht_entries(const ht_graph* g) { return g->merged ? g->n_unique : g->Ep; }
+// What a pass over rows of d columns should take, made if it is not there and may be.  (Backward: by_src is there.)
+int ht_pass_plan(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, PassPlan* out);
+// Scratch memory (slot HT_S_DENSE) of a pass over rows of d columns.
+size_t ht_dense_bytes(const DenseSide& D, int d);
+// The segments' sums of s_u src[u] into partial: DENSE_ROWS rows of pitch out_ld each.
+int ht_dense_launch(ht_ctx* ctx, hipStream_t st, const DenseSide& D, const float* src, int64_t ld, const float* s, int32_t d, float* partial,
+                    int64_t out_ld);
 
 // ---- compute kernels' host launchers -----------------------------------------------------
 // Aggregation over work items (ht_spmm.hip).  One wave (or a lane group of it)
@@ -395,6 +475,10 @@ struct SpmmArgs {
   float* partial;         // [n_part x out_ld] workspace
   int relu = 0;           // clamp the finished row at 0 (only without accumulate)
   int max_slabs = 0;      // cap on the number of feature slabs (0 = by width)
+  // the dense part's sums, from partial sum dense_part on (null: there is none)
+  const int32_t* dense_pos = nullptr;
+  const int32_t* dense_seg0 = nullptr;
+  int64_t dense_part = 0;
   // optional timing of the two kernels (null: not timed)
   struct Timer* tm = nullptr;
   double* t_items = nullptr;
@@ -480,7 +564,8 @@ struct ht_sgd_item {
 };
 constexpr int HT_SGD_MAX = 3 * HT_MAX_LAYERS;   // items per launch
 int ht_sgd(ht_ctx* ctx, hipStream_t st, const std::vector<ht_sgd_item>& items, float lr);
-int ht_fill_zero(ht_ctx* ctx, hipStream_t st, void* p, size_t bytes);
+int ht_fill_words(ht_ctx* ctx, hipStream_t st, void* p, size_t bytes, uint32_t value);
+inline int ht_fill_zero(ht_ctx* ctx, hipStream_t st, void* p, size_t bytes) { return ht_fill_words(ctx, st, p, bytes, 0u); }
 
 // stats helpers: HIP-event pairs around phases, each on the stream that runs the phase
 struct Timer {

@@ -112,6 +112,7 @@ struct Run {
   int layer = 0; // index into the per-layer statistics
   bool dhin_fresh = false;  // dH_in counts as zeros: a host tensor holds them (leaving rows may be stored, not added), a device
                             // tensor holds anything and every row is written or cleared first
+  bool planned = false;     // one of many passes over this graph: it may make and use the graph's plan (ht_dense.hip)
   bool changed = false;     // the caller's gradients may have been added to: the call cannot be made again
   Run(ht_ctx* c, const ht_graph* gr, ht_stats* s, bool timed) : ctx(c), g(gr), tm(c, c->stream, timed), st(s) {}
 };
@@ -278,13 +279,60 @@ std::vector<ChunkRange> chunk_ranges(const ht_graph* g, int64_t part_bytes, int6
   return out;
 }
 
+ChunkRange whole_graph(const ht_graph* g) {
+  ChunkRange r{0, g->n, ItemRange{}, 0, g->V, g->Ep, g->merged ? g->n_unique : g->Ep};
+  r.items.n_items = g->fwd_items.n_items;
+  r.items.n_part = g->fwd_items.n_part;
+  r.items.n_cut = g->fwd_items.n_cut;
+  return r;
+}
+
 // compulsory bytes of one launch over `rows` destination rows that may name every vertex
 double agg_all_bytes(const ht_graph* g, int64_t edges, int64_t rows, int d) {
   return 4.0 * edges + 8.0 * rows + 4.0 * d * (double)g->V + 4.0 * d * (double)rows + 4.0 * ((double)g->V + (double)rows);
 }
 
+// Scratch memory up to which a planned pass keeps partial sums.
+constexpr int64_t HT_PLAN_BYTES = (int64_t)8 << 30;
+
+// What a pass over rows of d columns, partial sums at pitch ld, takes of the graph's plan, and the scratch memory of that; nothing where
+// there is none or no memory for it.
+int take_plan(Run& R, bool fwd, int d, int64_t ld, PassPlan* out) {
+  ht_ctx* ctx = R.ctx;
+  *out = PassPlan();
+  if (!R.planned || ctx->agg_variant != 0) return HT_OK;
+  PassPlan p;
+  HT_TRY(ht_pass_plan(ctx, R.g, fwd, d, &p));
+  const int64_t part_bytes = p.parts() * ld * 4;
+  if (!p.items || part_bytes > HT_PLAN_BYTES) return HT_OK;
+  const int rc = ht_scratch_all(ctx, {{HT_S_SPART, (size_t)part_bytes}, {HT_S_DENSE, p.dense ? ht_dense_bytes(*p.dense, d) : 0}});
+  if (rc == HT_OK) *out = p;
+  return rc == HT_ENOMEM ? (int)HT_OK : rc;
+}
+// The pass's launches, `a` being those of the unplanned pass over the whole graph with the partial sums in place.
+int planned_launch(Run& R, const PassPlan& p, SpmmArgs a) {
+  const ht_graph* g = R.g;
+  a.items = p.items->items.p; a.n_items = p.items->n_items;
+  a.cuts = p.items->cuts.p; a.n_fix = p.items->n_cut;
+  a.part0 = 0;
+  a.row0 = 0;
+  if (p.dense) {
+    const DenseSide& D = *p.dense;
+    a.n_edges = D.n_rest;
+    a.idx = D.idx.p;
+    a.w_edge = D.w.p;
+    a.dense_pos = D.pos.p; a.dense_seg0 = D.seg0.p;
+    a.dense_part = p.items->n_part;
+    if (a.tm && a.t_items) a.tm->begin(a.t_items);
+    HT_TRY(ht_dense_launch(R.ctx, R.ctx->stream, D, a.src, a.src_ld, g->s.p, a.d, a.partial + p.items->n_part * a.out_ld, a.out_ld));
+    if (a.tm && a.t_items) a.tm->end();
+  }
+  return ht_spmm_launch(R.ctx, R.ctx->stream, a);
+}
+
 // Aggregate of one range of chunks, rows of src read in place by vertex id, into out (row of the range's first destination).
-int agg_range(Run& R, const ChunkRange& r, const float* src, int64_t src_ld, int d, float* out, int64_t out_ld, int relu, float* partial) {
+int agg_range(Run& R, const ChunkRange& r, const float* src, int64_t src_ld, int d, float* out, int64_t out_ld, int relu, float* partial,
+              const PassPlan& plan = PassPlan()) {   // (a plan's range is the whole graph)
   const ht_graph* g = R.g;
   SpmmArgs a{};
   agg_items(g->fwd_items, r.items, &a);
@@ -301,7 +349,7 @@ int agg_range(Run& R, const ChunkRange& r, const float* src, int64_t src_ld, int
   a.tm = &R.tm;
   a.t_items = &R.st->t_agg_fwd_layer_ms[li];
   a.t_fix = &R.st->t_agg_fix_ms;
-  HT_TRY(ht_spmm_launch(R.ctx, R.ctx->stream, a));
+  HT_TRY(plan.items ? planned_launch(R, plan, a) : ht_spmm_launch(R.ctx, R.ctx->stream, a));
   int64_t live = 0;          // chunk aggregations, whatever number of launches they take
   for (int k = r.k0; k < r.k1; ++k) live += g->bounds[k + 1] > g->bounds[k];
   R.st->n_spmm_fwd += live;
@@ -321,6 +369,9 @@ int64_t most_parts(const std::vector<ChunkRange>& ranges) {
 
 // Aggregates of all destinations: out row = vertex.
 int agg_all(Run& R, const float* src, int64_t src_ld, int d, float* out, int64_t out_ld, int relu) {
+  PassPlan plan;
+  HT_TRY(take_plan(R, true, d, out_ld, &plan));
+  if (plan.items) return agg_range(R, whole_graph(R.g), src, src_ld, d, out, out_ld, relu, (float*)R.ctx->scratch[HT_S_SPART], plan);
   auto ranges = chunk_ranges(R.g, out_ld * 4, 0, ht_may_spend(R.ctx) ? HT_RANGE_BYTES : 0);
   int64_t parts = most_parts(ranges);
   const int rc = ht_scratch_all(R.ctx, {{HT_S_SPART, (size_t)(parts * out_ld) * 4}});
@@ -358,6 +409,17 @@ int layer_fwd_direct(Run& R, const ht_layer_desc* desc, const ht_tensor* H_in, c
     rows = 0;
     for (const ChunkRange& r : ranges) rows = std::max(rows, r.rows);
   };
+  PassPlan again;
+  HT_TRY(take_plan(R, true, di, a_ld, &again));
+  if (again.items && (A_ckpt || g->V * a_ld * 4 <= HT_RANGE_BYTES)) {
+    const int rc = ht_scratch_all(ctx, {{HT_S_ACHUNK, A_ckpt ? 0 : (size_t)(g->V * a_ld) * 4}, {HT_S_PACKW, (size_t)ht_packed_w_bytes(di, dn)}});
+    if (rc == HT_OK) {
+      float* a = A_ckpt ? A_ckpt->ptr : (float*)ctx->scratch[HT_S_ACHUNK];
+      HT_TRY(agg_range(R, whole_graph(g), H_in->ptr, H_in->ld, di, a, a_ld, 0, (float*)ctx->scratch[HT_S_SPART], again));
+      return gemm(a, 0, g->V);
+    }
+    if (rc != HT_ENOMEM) HT_TRY(rc);
+  }
   // (the allocation-free call's array also holds the packed copy of W)
   if (ctx->static_mode) plan((int64_t)HT_STATIC_SCRATCH_BYTES - ht_packed_w_bytes(di, dn) - 512);
   else {
@@ -713,7 +775,7 @@ class AccWorker {
 
 // dst[u] = s_u * sum over u's entries of s_v src[v] for all sources u at once (src row = destination vertex): overwritten,
 // or added to.  g->by_src is there, its partial sums fit `partial`.
-int agg_by_source(Run& R, const float* src, int64_t src_ld, int d, float* dst, int64_t dst_ld, bool add, float* partial) {
+int agg_by_source(Run& R, const float* src, int64_t src_ld, int d, float* dst, int64_t dst_ld, bool add, float* partial, const PassPlan& plan) {
   const ht_graph* g = R.g;
   const SourceRows& S = g->by_src;
   SpmmArgs a{};
@@ -730,7 +792,7 @@ int agg_by_source(Run& R, const float* src, int64_t src_ld, int d, float* dst, i
   a.partial = partial;
   a.max_slabs = R.ctx->slabs_bwd;
   R.tm.begin(&R.st->t_spmm_bwd_ms);
-  HT_TRY(ht_spmm_launch(R.ctx, R.ctx->stream, a));
+  HT_TRY(plan.items ? planned_launch(R, plan, a) : ht_spmm_launch(R.ctx, R.ctx->stream, a));
   R.tm.end();
   for (const ChunkMeta& c : g->chunks) R.st->n_spmm_bwd += c.dst1 > c.dst0;
   R.st->edges += g->Ep;
@@ -793,7 +855,12 @@ int layer_bwd_direct(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, c
   HT_TRY(get(HT_S_ACHUNK, a_bytes, &a_all));
   HT_TRY(get(HT_S_DZCHUNK, dz_bytes, &dz_all));
   HT_TRY(get(HT_S_DACHUNK, da_bytes, &da_all));
-  if (dH_in) HT_TRY(get(HT_S_SPART, by_source_parts(g, dH_in->ld), &partial));
+  // (both passes' partial sums before a pointer to them is kept)
+  PassPlan plan, again;
+  if (!agg_ckpt) HT_TRY(take_plan(R, true, di, a_ld, &again));
+  if (dH_in) HT_TRY(take_plan(R, false, di, dH_in->ld, &plan));
+  if (plan.items) partial = (float*)ctx->scratch[HT_S_SPART];
+  else if (dH_in) HT_TRY(get(HT_S_SPART, by_source_parts(g, dH_in->ld), &partial));
   *done = true;
   const float* a_rows = ckpt->ptr;
   if (!agg_ckpt) {   // pure recomputation: aggregate again from h^l
@@ -824,7 +891,7 @@ int layer_bwd_direct(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, c
   HT_TRY(timed_gemm([&] { return ht_gemm_tn_groups(ctx, st, a_rows, a_ld, dz, dz_ld, dW, di, dn, g->dense_groups, g->d_dense_groups.p); }));
   if (!dH_in) return HT_OK;
   HT_TRY(timed_gemm([&] { return ht_gemm_nt(ctx, st, dz, dz_ld, W, da_all, ld_i, V, dn, di, 0); }));
-  return agg_by_source(R, da_all, ld_i, di, dH_in->ptr, dH_in->ld, !R.dhin_fresh, partial);
+  return agg_by_source(R, da_all, ld_i, di, dH_in->ptr, dH_in->ld, !R.dhin_fresh, partial, plan);
 }
 
 int layer_bwd_impl(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, const float* W, const ht_tensor* dH_out,
@@ -1228,12 +1295,14 @@ int layer_bwd_update_first(Run& R, const ht_layer_desc* desc, const ht_tensor* H
   want.push_back({HT_S_DZCHUNK, dz_bytes});
   want.push_back({HT_S_SPART, part_bytes});
   HT_TRY(ht_scratch_each(ctx, want));
+  PassPlan plan;
+  if (at_once) HT_TRY(take_plan(R, false, dn, ld_t, &plan));
   dz_chunk = (float*)ctx->scratch[HT_S_DZCHUNK];
   partial = (float*)ctx->scratch[HT_S_SPART];
   R.changed = true;
   if (at_once) {
     if (relu) HT_TRY(ht_relu_mask(ctx, st, dH_out->ptr, dH_out->ld, H_out->ptr, H_out->ld, dz_chunk, ld_t, g->V, dn));
-    HT_TRY(agg_by_source(R, relu ? dz_chunk : dH_out->ptr, relu ? ld_t : dH_out->ld, dn, dT, ld_t, false, partial));
+    HT_TRY(agg_by_source(R, relu ? dz_chunk : dH_out->ptr, relu ? ld_t : dH_out->ld, dn, dT, ld_t, false, partial, plan));
   } else {
     HT_TRY(ht_fill_zero(ctx, st, dT, (size_t)g->V * ld_t * 4));
   }
@@ -1369,6 +1438,7 @@ int ht_layer_fwd(ht_ctx* ctx, const ht_graph* g, const ht_layer_desc* desc, cons
     auto t0 = std::chrono::steady_clock::now();
     ht_stats local{};
     Run R(ctx, g, &local, stats != nullptr);
+    R.planned = A_ckpt != nullptr;
     int rc = desc->order == HT_ORDER_UPDATE_FIRST ? layer_fwd_update_first(R, desc, H_in, W, H_out)
                                                   : layer_fwd_impl(R, desc, H_in, W, H_out, A_ckpt);
     if (rc != HT_OK) {
@@ -1425,6 +1495,7 @@ int ht_layer_bwd(ht_ctx* ctx, const ht_graph* g, const ht_layer_desc* desc, cons
     auto t0 = std::chrono::steady_clock::now();
     ht_stats local{};
     Run R(ctx, g, &local, stats != nullptr);
+    R.planned = true;
     int rc = desc->order == HT_ORDER_UPDATE_FIRST ? layer_bwd_update_first(R, desc, ckpt, W, dH_out, H_out, dH_in, dW)
                                                   : layer_bwd_impl(R, desc, ckpt, W, dH_out, H_out, dH_in, dW);
     changed = R.changed;
@@ -1566,6 +1637,7 @@ static int epoch_impl(ht_ctx* ctx, const ht_graph* g, const ht_model* model, con
 
   ht_stats local{};
   Run R(ctx, g, &local, stats != nullptr);
+  R.planned = true;
   if (plan && plan->stats_detail == HT_STATS_AGG_FWD) {
     R.tm.only_lo = &local.t_agg_fwd_layer_ms[0];
     R.tm.only_hi = &local.t_agg_fwd_layer_ms[0] + HT_MAX_LAYERS;

@@ -732,10 +732,16 @@ struct RowSet {
   const int64_t* first;    // [n + 1] first row of every chunk
   const int64_t* eoff;     // nullptr: destinations
   int n;
+  const int32_t* pos = nullptr;   // rows with pos[r] >= 0 are cut rows however short they are (and without an item where they are empty)
   __device__ __forceinline__ void get(int64_t r, int k, int64_t* e0, int64_t* len) const {
     const int64_t* p = ptr + r + (eoff ? k : 0);
     *e0 = p[0] + (eoff ? eoff[k] : 0);
     *len = p[1] - p[0];
+  }
+  __device__ __forceinline__ bool forced(int64_t r) const { return pos && pos[r] >= 0; }
+  // items of row r
+  __device__ __forceinline__ uint64_t items(int64_t len, int seg, bool forced) const {
+    return len > seg ? (uint64_t)((len + seg - 1) / seg) : forced && len == 0 ? 0 : 1;
   }
 };
 
@@ -751,10 +757,11 @@ __global__ void __launch_bounds__(TB) k_items_count(RowSet R, int64_t nrows, int
     while (r >= end) end = R.first[++k + 1];
     int64_t e0, len;
     R.get(r, k, &e0, &len);
-    const uint64_t m = len <= seg ? 1 : (uint64_t)((len + seg - 1) / seg);
+    const bool forced = R.forced(r);
+    const uint64_t m = R.items(len, seg, forced);
     items += m;
-    parts += m > 1 ? m : 0;
-    cuts += m > 1;
+    parts += m > 1 || forced ? m : 0;
+    cuts += m > 1 || forced;
   }
   uint64_t t1, t2;
   block_excl(items | (cuts << 40), &t1);
@@ -774,7 +781,7 @@ __global__ void __launch_bounds__(TB) k_items_count(RowSet R, int64_t nrows, int
 // the two launches 33).
 constexpr int FILL_ALONE = 4;
 struct ItemOut {
-  int seg, fbits, fshift;
+  int seg, fbits, fshift, classes;   // classes: bits of the key in front of that row for the item's length, longest first
   const int32_t* idx;
   WorkItem* item;
   uint64_t* keys;
@@ -788,7 +795,8 @@ struct ItemOut {
     item[i0 + j] = w;
     if (keys) {
       const uint32_t f = w.len > 0 ? (uint32_t)idx[b] >> fshift : 0u;
-      keys[i0 + j] = ((((uint64_t)k << fbits) | f) << 32) | (uint64_t)(uint32_t)(i0 + j);
+      const uint32_t c = classes ? (uint32_t)(((int64_t)(seg - w.len) << classes) / (seg + 1)) : 0u;
+      keys[i0 + j] = ((((((uint64_t)k << classes) | c) << fbits) | f) << 32) | (uint64_t)(uint32_t)(i0 + j);
     }
   }
 };
@@ -803,12 +811,14 @@ __global__ void __launch_bounds__(TB) k_items_fill(RowSet R, int64_t nrows, int6
     const int64_t r = (int64_t)blockIdx.x * RTILE + q * TB + threadIdx.x;
     int64_t e0 = 0, len = 0;
     uint64_t m = 0;
+    bool is_cut = false;
     if (r < nrows) {
       while (r >= end) end = R.first[++k + 1];
       R.get(r, k, &e0, &len);
-      m = len <= seg ? 1 : (uint64_t)((len + seg - 1) / seg);
+      const bool forced = R.forced(r);
+      m = R.items(len, seg, forced);
+      is_cut = m > 1 || forced;
     }
-    const bool is_cut = m > 1;
     uint64_t t1, t2;
     const uint64_t x = block_excl(m | ((uint64_t)is_cut << 40), &t1);
     const uint64_t y = block_excl(is_cut ? m : 0, &t2);
@@ -926,7 +936,7 @@ struct ItemBuild {
   RowSet rows;
   int64_t nrows = 0, tiles = 0;
   int64_t range = 0;           // values of the entries' row index are below this
-  int seg = 0;
+  int seg = 0, classes = 0;
   const int64_t* h_first = nullptr;   // host copy of rows.first
   const int32_t* idx = nullptr;
   int32_t* cnt = nullptr;      // [3 * tiles]
@@ -965,8 +975,8 @@ int fill_items(ht_ctx* ctx, const ItemBuild& b, const int64_t* h_tot, WorkItem* 
   b.out->n_cut = nc;
   const bool sorted_items = order && ni > 1, at_once = ni <= (int64_t)n_made;
   const int kbits = b.rows.n > 1 ? bits_for(b.rows.n) : 0, vbits = bits_for(b.range);
-  const int fbits = std::min(vbits, 32 - kbits), fshift = vbits - fbits;
-  const ItemOut to{b.seg, fbits, fshift, b.idx, sorted_items && at_once ? made : b.out->items.p, sorted_items ? keysA : nullptr};
+  const int fbits = std::min(vbits, 32 - kbits - b.classes), fshift = vbits - fbits;
+  const ItemOut to{b.seg, fbits, fshift, b.classes, b.idx, sorted_items && at_once ? made : b.out->items.p, sorted_items ? keysA : nullptr};
   k_items_fill<<<(unsigned)b.tiles, TB, 0, ctx->stream>>>(b.rows, b.nrows, b.tiles, b.base, to, b.out->cuts.p, b.starts);
   HT_LAUNCH_CHECK(ctx);
   if (np > FILL_ALONE)
@@ -983,7 +993,7 @@ int fill_items(ht_ctx* ctx, const ItemBuild& b, const int64_t* h_tot, WorkItem* 
     HT_LAUNCH_CHECK(ctx);
     return HT_OK;
   };
-  if (at_once) return sort_range(0, ni, made, kbits + fbits);
+  if (at_once) return sort_range(0, ni, made, kbits + b.classes + fbits);
   HT_HIP(ctx, hipMemcpyAsync(h_starts, b.starts, ((size_t)b.rows.n + 1) * 8, hipMemcpyDeviceToHost, ctx->stream));
   HT_HIP(ctx, hipStreamSynchronize(ctx->stream));
   // (a range behind the last row has no start of its own)
@@ -996,7 +1006,7 @@ int fill_items(ht_ctx* ctx, const ItemBuild& b, const int64_t* h_tot, WorkItem* 
     if (n <= 1) continue;
     if (n > (int64_t)n_made) return ht_set_err(ctx, HT_ESTATE, "work items: a chunk has %lld, more than was planned for", (long long)n);
     HT_HIP(ctx, hipMemcpyAsync(made, b.out->items.p + i0, (size_t)n * sizeof(WorkItem), hipMemcpyDeviceToDevice, ctx->stream));
-    HT_TRY(sort_range(i0, n, made, fbits));
+    HT_TRY(sort_range(i0, n, made, b.classes + fbits));
   }
   return HT_OK;
 }
@@ -1748,8 +1758,8 @@ void plan_by_source(const ht_graph* g, DevBlock* kept, DevBlock* tmp) {
   if (g->merged) kept->add<float>((size_t)n_ent);
   kept->add<WorkItem>((size_t)bound);
   kept->add<CutRow>((size_t)cut_bound(n_ent, sw.seg_bwd));
+  kept->add<int64_t>((size_t)V + 1);
   tmp->add<int32_t>((size_t)V);
-  tmp->add<int64_t>((size_t)V + 1);
   tmp->add<int32_t>(3 * tiles);
   tmp->add<int64_t>((size_t)std::max<int64_t>(g->v_ori, 1));
   tmp->add<int64_t>(3 * n1 + 2);
@@ -1784,6 +1794,7 @@ int build_by_source(ht_ctx* ctx, const ht_graph* g, int slot) {
   if (g->merged) S.blk.take(S.w, (size_t)n_ent);
   S.blk.take(S.items.items, (size_t)bound);
   S.blk.take(S.items.cuts, (size_t)cuts);
+  S.blk.take(S.ptr, (size_t)V + 1);
   ItemBuild b;
   b.nrows = V;
   b.tiles = ceil_div64(V, RTILE);
@@ -1792,12 +1803,12 @@ int build_by_source(ht_ctx* ctx, const ht_graph* g, int slot) {
   b.range = V;
   b.out = &S.items;
   DevArr<int32_t> cnt, icnt;
-  DevArr<int64_t> ptr, off, lists, ibase, istarts;
+  DevArr<int64_t> off, lists, ibase, istarts;
+  DevArr<int64_t>& ptr = S.ptr;
   DevArr<WorkItem> made;
   DevArr<uint64_t> keysA, keysB;
   HT_TRY(tmp.alloc_in(ctx, slot));   // (an allocation of its own and its release took as long as the rest of this together)
   tmp.take(cnt, (size_t)V);
-  tmp.take(ptr, (size_t)V + 1);
   tmp.take(icnt, (size_t)3 * b.tiles);
   tmp.take(off, (size_t)std::max<int64_t>(vo, 1));
   tmp.take(lists, 3 * n1 + 2);
@@ -1831,7 +1842,8 @@ int build_by_source(ht_ctx* ctx, const ht_graph* g, int slot) {
   HT_HIP(ctx, hipMemcpyAsync(lists.p, hl, (3 * n1 + 2) * 8, hipMemcpyHostToDevice, st));
   const RowSet arena{g->merged ? g->usptr.p : g->sptr.p, lists.p, lists.p + n1, g->n};
   // ptr[u + 1] runs from where u's entries start to where they end while the chunks take their places, and is then the start of u + 1
-  HT_TRY(ht_fill_zero(ctx, st, cnt.p, (size_t)((char*)(ptr.p + 1) - (char*)cnt.p)));   // ... and ptr[0]
+  HT_TRY(ht_fill_zero(ctx, st, cnt.p, (size_t)V * 4));
+  HT_TRY(ht_fill_zero(ctx, st, ptr.p, 8));
   if (vo > 0) {
     k_src_counts<<<nblk(vo), TB, 0, st>>>(g->nbr.p, arena, vo, cnt.p);
     HT_LAUNCH_CHECK(ctx);
@@ -1895,12 +1907,85 @@ int ht_graph_by_source_mult(ht_ctx* ctx, const ht_graph* g) {
   return HT_OK;
 }
 
+int ht_graph_source_counts(ht_ctx* ctx, const ht_graph* g, int32_t* cnt) {
+  const size_t n1 = (size_t)g->n + 1;
+  DevArr<int64_t> lists;
+  HT_TRY(lists.alloc(ctx, 2 * n1));
+  void* p = nullptr;
+  HT_TRY(ht_host_scratch(ctx, HT_HS_READBACK, 2 * n1 * 8, &p));
+  int64_t* hl = (int64_t*)p;
+  for (int k = 0; k < g->n; ++k) {
+    const ChunkMeta& c = g->chunks[g->pos[k]];
+    hl[k] = c.nbr_off;
+    hl[n1 + k] = c.ue0;
+  }
+  hl[g->n] = g->v_ori;
+  hl[n1 + g->n] = g->merged ? g->n_unique : g->Ep;
+  HT_HIP(ctx, hipMemcpyAsync(lists.p, hl, 2 * n1 * 8, hipMemcpyHostToDevice, ctx->stream));
+  HT_TRY(ht_fill_zero(ctx, ctx->stream, cnt, (size_t)g->V * 4));
+  if (g->v_ori > 0) {
+    const RowSet arena{g->merged ? g->usptr.p : g->sptr.p, lists.p, lists.p + n1, g->n};
+    k_src_counts<<<nblk(g->v_ori), TB, 0, ctx->stream>>>(g->nbr.p, arena, g->v_ori, cnt);
+    HT_LAUNCH_CHECK(ctx);
+  }
+  HT_HIP(ctx, hipStreamSynchronize(ctx->stream));   // (the lists go with this call)
+  return HT_OK;
+}
+
+int ht_graph_row_items(ht_ctx* ctx, int64_t V, const int64_t* ptr, int64_t n_ent, const int32_t* idx, const int32_t* pos, int seg, int slot,
+                       GraphItems* out) {
+  const ItemSwitches sw;
+  ItemBuild b;
+  b.nrows = V;
+  b.tiles = ceil_div64(V, RTILE);
+  b.seg = seg;
+  b.idx = idx;
+  b.range = V;
+  b.out = out;
+  const int64_t bound = item_bound(V, n_ent, b.seg);
+  DevBlock tmp;
+  DevArr<int32_t> cnt;
+  DevArr<int64_t> base, starts, first;
+  DevArr<WorkItem> made;
+  DevArr<uint64_t> keysA, keysB;
+  tmp.add<int32_t>((size_t)(3 * b.tiles));
+  tmp.add<int64_t>((size_t)(3 * b.tiles + 1));
+  tmp.add<int64_t>(6);
+  tmp.add<int64_t>(2);
+  tmp.add<WorkItem>((size_t)bound);
+  tmp.add<uint64_t>((size_t)bound);
+  tmp.add<uint64_t>((size_t)bound);
+  HT_TRY(tmp.alloc_in(ctx, slot));
+  tmp.take(cnt, (size_t)(3 * b.tiles));
+  tmp.take(base, (size_t)(3 * b.tiles + 1));
+  tmp.take(starts, 6);
+  tmp.take(first, 2);
+  tmp.take(made, (size_t)bound);
+  tmp.take(keysA, (size_t)bound);
+  tmp.take(keysB, (size_t)bound);
+  b.cnt = cnt.p;
+  b.base = base.p;
+  b.starts = starts.p;
+  void* p = nullptr;
+  HT_TRY(ht_host_scratch(ctx, HT_HS_READBACK, 8 * 8, &p));
+  int64_t* h = (int64_t*)p;
+  h[4] = 0;
+  h[5] = V;
+  HT_HIP(ctx, hipMemcpyAsync(first.p, h + 4, 16, hipMemcpyHostToDevice, ctx->stream));
+  b.rows = RowSet{ptr, first.p, nullptr, 1, pos};
+  HT_TRY(count_items(ctx, b, h));
+  HT_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  HT_TRY(out->items.alloc(ctx, (size_t)std::max<int64_t>(h[0], 1)));
+  HT_TRY(out->cuts.alloc(ctx, (size_t)std::max<int64_t>(h[2] - h[1], 1)));
+  return fill_items(ctx, b, h, made.p, (size_t)bound, keysA.p, keysB.p, (size_t)bound, sw.order);
+}
+
 int64_t ht_graph::hbm_bytes() const {
   int64_t b = indptr.bytes() + col.bytes() + s.bytes() + nbr.bytes() + col_local.bytes() + col_slot.bytes() +
               sptr.bytes() + sdst.bytes() + slot.bytes() + gslot.bytes() + reuse.bytes() + load.bytes() +
               load_slot.bytes() + leave.bytes() + leave_slot.bytes() + uindptr.bytes() + ucol.bytes() +
               ucol_slot.bytes() + uw_fwd.bytes() + umult.bytes() + usdst.bytes() + uw_bwd.bytes() + umult_bwd.bytes() + usptr.bytes();
-  b += (int64_t)(by_src.blk.mem.bytes() + by_src.mult.bytes());
+  b += (int64_t)(by_src.blk.mem.bytes() + by_src.mult.bytes()) + plan_fwd.bytes() + plan_bwd.bytes();
   for (const GraphItems* i : {&fwd_items, &bwd_items}) b += i->n_items * (int64_t)sizeof(WorkItem) + i->n_cut * (int64_t)sizeof(CutRow);
   return b;
 }

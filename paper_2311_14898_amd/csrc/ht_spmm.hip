@@ -114,24 +114,36 @@ __global__ void __launch_bounds__(256) k_spmm_fix(SpmmArgs a) {
   const CutRow cut = a.cuts[f];
   const uint32_t r = cut.row;
   const int64_t p0 = cut.part0 - a.part0;
-  const int32_t ns = cut.nseg;
+  // the row's own partial sums, then those of the segments of its row block
+  int32_t ns = cut.nseg, n_own = ns;
+  const float* dense = nullptr;
+  if (a.dense_pos) {
+    const int32_t at = a.dense_pos[r];
+    if (at >= 0) {
+      const int32_t s0 = a.dense_seg0[at / DENSE_ROWS];
+      ns += a.dense_seg0[at / DENSE_ROWS + 1] - s0;
+      dense = a.partial + (a.dense_part + (int64_t)s0 * DENSE_ROWS + at % DENSE_ROWS) * a.out_ld;
+    }
+  }
   const int d4 = (a.d + 3) & ~3;
   const int32_t per = (ns + 3) >> 2;
-  const int32_t k0 = wave * per, k1 = (k0 + per) < ns ? (k0 + per) : ns;
+  const int32_t k0 = wave * per < ns ? wave * per : ns, k1 = (k0 + per) < ns ? (k0 + per) : ns;
   for (int cb = 0; cb < d4; cb += 256) {
     const int c4 = cb + lane * 4;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
     if (c4 < d4) {
-      const float* p = a.partial + p0 * a.out_ld + c4;
-      int32_t k = k0;
-      for (; k + 4 <= k1; k += 4) {
-        const float4 v0 = ld4(p + (int64_t)(k + 0) * a.out_ld);
-        const float4 v1 = ld4(p + (int64_t)(k + 1) * a.out_ld);
-        const float4 v2 = ld4(p + (int64_t)(k + 2) * a.out_ld);
-        const float4 v3 = ld4(p + (int64_t)(k + 3) * a.out_ld);
-        acc = add4(add4(add4(add4(acc, v0), v1), v2), v3);
-      }
-      for (; k < k1; ++k) acc = add4(acc, ld4(p + (int64_t)k * a.out_ld));
+      auto add = [&](const float* p, int64_t pitch, int32_t k, int32_t end) {
+        for (; k + 4 <= end; k += 4) {
+          const float4 v0 = ld4(p + (int64_t)(k + 0) * pitch);
+          const float4 v1 = ld4(p + (int64_t)(k + 1) * pitch);
+          const float4 v2 = ld4(p + (int64_t)(k + 2) * pitch);
+          const float4 v3 = ld4(p + (int64_t)(k + 3) * pitch);
+          acc = add4(add4(add4(add4(acc, v0), v1), v2), v3);
+        }
+        for (; k < end; ++k) acc = add4(acc, ld4(p + (int64_t)k * pitch));
+      };
+      add(a.partial + p0 * a.out_ld + c4, a.out_ld, k0, k1 < n_own ? k1 : n_own);
+      if (k1 > n_own) add(dense + c4, a.out_ld * DENSE_ROWS, (k0 > n_own ? k0 : n_own) - n_own, k1 - n_own);
     }
     sh[wave][lane] = acc;
     __syncthreads();
@@ -348,7 +360,7 @@ int ht_slab_shape(ht_ctx* ctx, const SpmmArgs& a, SlabShape* out) {
 }
 
 int ht_spmm_launch(ht_ctx* ctx, hipStream_t st, const SpmmArgs& a0) {
-  if (a0.n_items <= 0) return HT_OK;
+  if (a0.n_items <= 0 && a0.n_fix <= 0) return HT_OK;   // (no items, but cut rows: the dense part holds everything)
   if ((a0.src_ld & 3) || (a0.out_ld & 3)) return ht_set_err(ctx, HT_ESHAPE, "aggregation: row pitch must be a multiple of 4");
   // wide rows go in column blocks of 1024 floats
   for (int c0 = 0; c0 < a0.d; c0 += 1024) {
