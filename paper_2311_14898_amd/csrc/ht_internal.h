@@ -475,6 +475,8 @@ struct SpmmArgs {
   float* partial;         // [n_part x out_ld] workspace
   int relu = 0;           // clamp the finished row at 0 (only without accumulate)
   int max_slabs = 0;      // cap on the number of feature slabs (0 = by width)
+  bool units = false;     // items are short and in order of length: column units may be used
+  int64_t src_rows = 0;   // rows of src (for that choice)
   // the dense part's sums, from partial sum dense_part on (null: there is none)
   const int32_t* dense_pos = nullptr;
   const int32_t* dense_seg0 = nullptr;

@@ -316,6 +316,8 @@ int planned_launch(Run& R, const PassPlan& p, SpmmArgs a) {
   a.cuts = p.items->cuts.p; a.n_fix = p.items->n_cut;
   a.part0 = 0;
   a.row0 = 0;
+  a.units = true;
+  a.src_rows = g->V;
   if (p.dense) {
     const DenseSide& D = *p.dense;
     a.n_edges = D.n_rest;

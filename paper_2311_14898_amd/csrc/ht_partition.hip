@@ -1939,6 +1939,7 @@ int ht_graph_row_items(ht_ctx* ctx, int64_t V, const int64_t* ptr, int64_t n_ent
   b.nrows = V;
   b.tiles = ceil_div64(V, RTILE);
   b.seg = seg;
+  b.classes = 3;   // (items of like length in a wave: k_spmm_unit works on several; 2.45 M vertices, 62 M edges 52.0 -> 51.0 ms an epoch)
   b.idx = idx;
   b.range = V;
   b.out = out;

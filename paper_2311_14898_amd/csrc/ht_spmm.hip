@@ -7,6 +7,8 @@
 // lane groups that take interleaved edges and are summed in a fixed order.
 // No atomics: a row cut into several items is finished by a second kernel
 // that adds the partial sums in item order, so results are bit-reproducible.
+#include <type_traits>
+
 #include "ht_internal.h"
 
 namespace {
@@ -255,6 +257,89 @@ __global__ void __launch_bounds__(256) k_spmm_slab(SpmmArgs a, int S, int nvs, i
     write_out(a, r, coff, tot);
 }
 
+// Column units: LPR lanes own one item and one unit of LPR float4 columns (two cache lines, one for rows that have no more), a wave so many
+// items, and XCD x reads unit unit0 + x % S alone.  Where the rows do not fit the caches this is bound by what crosses the fabric
+// (5 to 7 TB/s), so what counts is what L2 keeps: its 4 MB hold 16 k rows' units instead of 4 k whole rows of 256 columns.  Measured on
+// lists of short items (the slab kernel | this): 233 k vertices, the 26 M entries outside dense tiles, 602 and 256 columns 14.75 | 13.64 ms an
+// epoch, L2 hits 28 -> 67 %; 2.45 M vertices, 62 M edges, 256 columns 57.6 | 51.9 ms, hits 24 -> 46 %.  One line a unit keeps more (56 %)
+// but reads every index twice as often: 57.4 ms; four row reads in flight a lane: 8 52.8, 16 60.4 where this takes 52.7.
+constexpr int UNIT_LANES = 16;
+template <int LPR, bool SMALL>
+__global__ void __launch_bounds__(256) k_spmm_unit(SpmmArgs a, int S, int unit0) {
+  constexpr int U = 4;
+  constexpr int G = 64 / LPR;
+  using Off = std::conditional_t<SMALL, uint32_t, uint64_t>;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int xcd = blockIdx.x & 7, unit = unit0 + xcd % S;
+  const int64_t grp = (int64_t)(blockIdx.x >> 3) * (8 / S) + xcd / S;
+  const int64_t t = (grp * 4 + wave) * G + lane / LPR;
+  const int ll = lane % LPR;
+  const int nvec = (a.d + 3) >> 2, vec = unit * LPR + ll;
+  const bool active = vec < nvec;
+  WorkItem it{0u, 0u, 0, -1};
+  if (t < a.n_items) it = a.items[t];
+  const int32_t len = it.len;
+  int32_t most = len, least = len;
+#pragma unroll
+  for (int o = LPR; o < 64; o <<= 1) {
+    const int32_t x = __shfl_xor(most, o, 64), y = __shfl_xor(least, o, 64);
+    most = x > most ? x : most;
+    least = y < least ? y : least;
+  }
+  most = __builtin_amdgcn_readfirstlane(most);
+  least = __builtin_amdgcn_readfirstlane(least);
+  const Off mine = (Off)((active ? vec : unit * LPR) * 16), pitch = (Off)a.src_ld * 4;
+  const int32_t* ip = a.idx + it.e0;
+  const float* wp = a.w_edge ? a.w_edge + ((int64_t)it.e0 - a.w0) : nullptr;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  auto fetch = [&](int32_t b, int32_t* c, float* w) {   // entry b + ll of the item
+    const int32_t k = b + ll;
+    *c = 0;
+    *w = 0.f;
+    if (k < len) {
+      *c = ip[k];
+      *w = wp ? wp[k] : (a.ew ? a.ew[*c] : 1.f);
+    }
+  };
+  int32_t c0;
+  float w0;
+  fetch(0, &c0, &w0);
+  for (int32_t b = 0; b < most; b += LPR) {
+    const Off o1 = (Off)(uint32_t)c0 * pitch;
+    const float w1 = w0;
+    if (b + LPR < most) fetch(b + LPR, &c0, &w0);
+#pragma unroll
+    for (int k0 = 0; k0 < LPR; k0 += U) {
+      if (b + k0 >= most) break;
+      float4 v[U];
+      float w[U];
+      if (b + k0 + U <= least) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const Off o = __shfl(o1, k0 + u, LPR);
+          w[u] = __shfl(w1, k0 + u, LPR);
+          v[u] = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(a.src) + (Off)(o + mine));
+        }
+      } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const Off o = __shfl(o1, k0 + u, LPR);
+          w[u] = __shfl(w1, k0 + u, LPR);
+          v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (b + k0 + u < len) v[u] = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(a.src) + (Off)(o + mine));
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) acc = fma4(w[u], v[u], acc);
+    }
+  }
+  if (!active || t >= a.n_items) return;
+  if (it.part >= 0)
+    st4(a.partial + (it.part - a.part0) * a.out_ld + vec * 4, acc);
+  else
+    write_out(a, it.row, vec * 4, acc);
+}
+
 template <int LPR, int VPL>
 int launch_items(ht_ctx* ctx, hipStream_t st, const SpmmArgs& a) {
   return ht_in_launches(a.n_items, HT_LAUNCH_WAVES, [&](int64_t i, int64_t n) {
@@ -334,6 +419,14 @@ static_assert(row_blocks(1ll << 26, 4, 0) * 256 < (1ll << 32), "a row launch mus
 static_assert(row_blocks(111'000'000ll, 4, 0) == HT_ROW_GRID_MAX && row_blocks(int64_t(1) << 40, 1, 0) == HT_ROW_GRID_MAX, "");
 static_assert(row_blocks(1000, 4, 64) == 64 && row_blocks(100, 4, 64) == 25 && row_blocks(5, 4, 0) == 2, "");
 
+// Rows go in column units where those are whole cache lines (a line that two units share is fetched twice: 2 M vertices, 30 M edges, 200
+// columns in rows of 800 bytes 13.5 -> 15.9 ms a layer) or there is one unit, and where the rows that are read are more than the caches
+// hold (116 k rows of 132: no difference; 60 k of 132: 86 us a pass, 70 expected of the slab kernel; 1 M of 64: 950 -> 870).
+bool unit_shape(const SpmmArgs& a, int nvec) {
+  const bool lines = (a.src_ld & 31) == 0 && ((uintptr_t)a.src & 127) == 0;
+  return (lines || nvec <= UNIT_LANES) && a.src_rows * a.src_ld * 4 >= ((int64_t)64 << 20);
+}
+
 }  // namespace
 
 int ht_slab_shape(ht_ctx* ctx, const SpmmArgs& a, SlabShape* out) {
@@ -372,7 +465,26 @@ int ht_spmm_launch(ht_ctx* ctx, hipStream_t st, const SpmmArgs& a0) {
     const int nvec = (a.d + 3) / 4;
     int rc = HT_OK;
     if (a.tm && a.t_items) a.tm->begin(a.t_items);
-    if (ctx->agg_variant == 0) {
+    if (a.units && unit_shape(a, nvec)) {
+      const int lpr = nvec <= 8 ? 8 : UNIT_LANES, nu = (nvec + lpr - 1) / lpr, G = 64 / lpr;
+      const bool small = a.src_rows * a.src_ld < ((int64_t)1 << 30);
+      for (int u0 = 0; u0 < nu && rc == HT_OK;) {
+        int S = 8;
+        while (S > nu - u0) S /= 2;
+        rc = ht_in_launches(a.n_items, HT_LAUNCH_WAVES / S * G, [&](int64_t i, int64_t n) {
+          SpmmArgs b = a;
+          b.items += i;
+          b.n_items = n;
+          const int64_t blocks = (n + 4 * G - 1) / (4 * G), parts = 8 / S;
+          const unsigned nb = (unsigned)((blocks + parts - 1) / parts * 8);
+          if (lpr == 8) small ? k_spmm_unit<8, true><<<nb, 256, 0, st>>>(b, S, u0) : k_spmm_unit<8, false><<<nb, 256, 0, st>>>(b, S, u0);
+          else small ? k_spmm_unit<UNIT_LANES, true><<<nb, 256, 0, st>>>(b, S, u0) : k_spmm_unit<UNIT_LANES, false><<<nb, 256, 0, st>>>(b, S, u0);
+          HT_LAUNCH_CHECK(ctx);
+          return (int)HT_OK;
+        });
+        u0 += S;
+      }
+    } else if (ctx->agg_variant == 0) {
       SlabShape sh;
       HT_TRY(ht_slab_shape(ctx, a, &sh));
       const int S = sh.S, nvs = sh.nvs, eps = sh.eps;

@@ -110,6 +110,13 @@ def test_rest_and_short_items(planned, V, d):
     _check(c.run(), c.ref())
 
 
+@pytest.mark.parametrize("V,d", [(300_007, 64), (140_003, 128), (300_007, 24), (600_011, 32)])
+def test_column_units(planned, V, d):
+    """Rows beyond 64 MiB (and one below): a wave works on 4 or 8 short items."""
+    c = Case(V, "rmat", d)
+    _check(c.run(), c.ref())
+
+
 @pytest.mark.parametrize("d", [20, 130])
 def test_values_out_of_range(planned, d):
     """Infinities and NaN reach exactly the rows that name them; values that the scaled parts cannot hold and subnormal ones are as exact
