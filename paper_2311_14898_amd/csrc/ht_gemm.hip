@@ -17,6 +17,9 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 
 constexpr int BK = 16;        // reduction depth of one LDS stage
 constexpr int BM = 128;       // rows of A per block (NN) / output rows per block (TN)
+// Rows up to which a product reads W as it is, a launch less (10 k rows: 2.5 us and the gap before the next one).  Beyond a block per CU
+// the single loads and the bounds tests would be paid by every block.
+constexpr int64_t HT_PACK_ROWS = 32768;
 constexpr int LDA_S = BK + 1; // LDS pitch of the row-major A tile (NN): odd, conflict-free column reads
 
 __device__ __forceinline__ float4 ld4g(const float* p) { return *reinterpret_cast<const float4*>(p); }
@@ -37,8 +40,10 @@ __global__ void k_pack_b(const float* __restrict__ W, int K, int N, int transpos
 }
 
 // C = A Bp (+ReLU).  A [M x K] pitch lda (columns >= K are never used as data),
-// Bp [Kp x Np] padded.  Block: 256 threads = WM x WN waves, wave tile (TI*32) x (TJ*32).
-template <int BN, int WM, int WN, int TI, int TJ>
+// Bp [Kp x Np] padded, or W as it is: PACKED, AS_IS (W [K x N]) or TRANSPOSED (W [N x K]).  Block: 256 threads = WM x WN waves, wave tile
+// (TI*32) x (TJ*32).
+enum { PACKED, AS_IS, TRANSPOSED };
+template <int BN, int WM, int WN, int TI, int TJ, int FORM>
 __global__ void __launch_bounds__(256) k_gemm_nn(const float* __restrict__ A, int64_t lda,
                                                  const float* __restrict__ Bp, int Np, float* __restrict__ C,
                                                  int64_t ldc, int64_t M, int K, int N, int relu) {
@@ -93,8 +98,18 @@ __global__ void __launch_bounds__(256) k_gemm_nn(const float* __restrict__ A, in
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
       const int f = tid + u * 256;
-      const int kr = f / (BN / 4), nv = (f % (BN / 4)) * 4;
-      rb[u] = ld4g(Bp + (int64_t)(k0 + kr) * Np + n0 + nv);
+      if (FORM == PACKED) {
+        const int kr = f / (BN / 4), nv = (f % (BN / 4)) * 4;
+        rb[u] = ld4g(Bp + (int64_t)(k0 + kr) * Np + n0 + nv);
+      } else {   // four columns of a row of W, or four rows of a column of its transpose: contiguous either way, at any alignment
+        const int k = FORM == AS_IS ? k0 + f / (BN / 4) : k0 + (f & 3) * 4, n = FORM == AS_IS ? n0 + (f % (BN / 4)) * 4 : n0 + (f >> 2);
+        const float* p = FORM == AS_IS ? Bp + (int64_t)k * N + n : Bp + (int64_t)n * K + k;
+        const int left = k < K && n < N ? (FORM == AS_IS ? N - n : K - k) : 0;
+        rb[u].x = left > 0 ? p[0] : 0.f;
+        rb[u].y = left > 1 ? p[1] : 0.f;
+        rb[u].z = left > 2 ? p[2] : 0.f;
+        rb[u].w = left > 3 ? p[3] : 0.f;
+      }
     }
   };
   auto stash = [&]() {
@@ -108,8 +123,13 @@ __global__ void __launch_bounds__(256) k_gemm_nn(const float* __restrict__ A, in
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
       const int f = tid + u * 256;
-      const int kr = f / (BN / 4), nv = (f % (BN / 4)) * 4;
-      *reinterpret_cast<float4*>(Bs + kr * (BN + 4) + nv) = rb[u];
+      if (FORM == TRANSPOSED) {
+        float* d = Bs + (f & 3) * 4 * (BN + 4) + (f >> 2);
+        d[0] = rb[u].x; d[BN + 4] = rb[u].y; d[2 * (BN + 4)] = rb[u].z; d[3 * (BN + 4)] = rb[u].w;
+      } else {
+        const int kr = f / (BN / 4), nv = (f % (BN / 4)) * 4;
+        *reinterpret_cast<float4*>(Bs + kr * (BN + 4) + nv) = rb[u];
+      }
     }
   };
   fetch(0);
@@ -585,19 +605,30 @@ __global__ void __launch_bounds__(256) k_slice_table(const int64_t* __restrict__
 
 inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
 
-int gemm_nn_packed(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* Bp, int Np, float* C,
-                   int64_t ldc, int64_t M, int K, int N, int relu) {
+template <int FORM>
+int launch_nn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* Bp, int Np, float* C, int64_t ldc, int64_t M, int K, int N,
+              int relu) {
   if (M <= 0 || N <= 0) return HT_OK;
   const unsigned gx = (unsigned)((M + BM - 1) / BM);
-  if (N > 64) {
-    dim3 grid(gx, (unsigned)((N + 127) / 128));
-    k_gemm_nn<128, 2, 2, 2, 2><<<grid, 256, 0, st>>>(A, lda, Bp, Np, C, ldc, M, K, N, relu);
-  } else {
-    dim3 grid(gx, 1);
-    k_gemm_nn<64, 4, 1, 1, 2><<<grid, 256, 0, st>>>(A, lda, Bp, Np, C, ldc, M, K, N, relu);
-  }
+  if (N > 64) k_gemm_nn<128, 2, 2, 2, 2, FORM><<<dim3(gx, (unsigned)((N + 127) / 128)), 256, 0, st>>>(A, lda, Bp, Np, C, ldc, M, K, N, relu);
+  else k_gemm_nn<64, 4, 1, 1, 2, FORM><<<dim3(gx, 1), 256, 0, st>>>(A, lda, Bp, Np, C, ldc, M, K, N, relu);
   HT_LAUNCH_CHECK(ctx);
   return HT_OK;
+}
+
+// C = A W (+ReLU), or A W^T: out of a padded copy of W in the context's scratch, or of W itself.
+int gemm_nn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* W, bool transposed, float* C, int64_t ldc, int64_t M, int32_t K,
+            int32_t N, int relu) {
+  if (lda & 3) return ht_set_err(ctx, HT_ESHAPE, "gemm: row pitch must be a multiple of 4");
+  if (M <= HT_PACK_ROWS)
+    return transposed ? launch_nn<TRANSPOSED>(ctx, st, A, lda, W, 0, C, ldc, M, K, N, relu)
+                      : launch_nn<AS_IS>(ctx, st, A, lda, W, 0, C, ldc, M, K, N, relu);
+  const int Kp = round_up(K, BK), Np = round_up(N, 128);
+  float* Bp = nullptr;
+  HT_TRY(ht_scratch(ctx, HT_S_PACKW, (size_t)Kp * Np * 4, (void**)&Bp));
+  k_pack_b<<<(unsigned)(((int64_t)Kp * Np + 255) / 256), 256, 0, st>>>(W, transposed ? N : K, transposed ? K : N, transposed, Bp, Kp, Np);
+  HT_LAUNCH_CHECK(ctx);
+  return launch_nn<PACKED>(ctx, st, A, lda, Bp, Np, C, ldc, M, K, N, relu);
 }
 
 }  // namespace
@@ -616,26 +647,13 @@ int ht_pack_w(ht_ctx* ctx, hipStream_t st, const float* W, int32_t K, int32_t N,
 
 int ht_gemm_nn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, float* C, int64_t ldc,
                int64_t M, int32_t K, int32_t N, int relu) {
-  if (lda & 3) return ht_set_err(ctx, HT_ESHAPE, "gemm: row pitch must be a multiple of 4");
-  const int Kp = round_up(K, BK), Np = round_up(N, 128);
-  float* Bp = nullptr;
-  HT_TRY(ht_scratch(ctx, HT_S_PACKW, (size_t)Kp * Np * 4, (void**)&Bp));
-  k_pack_b<<<(unsigned)(((int64_t)Kp * Np + 255) / 256), 256, 0, st>>>(B, K, N, 0, Bp, Kp, Np);
-  HT_LAUNCH_CHECK(ctx);
-  return gemm_nn_packed(ctx, st, A, lda, Bp, Np, C, ldc, M, K, N, relu);
+  return gemm_nn(ctx, st, A, lda, B, false, C, ldc, M, K, N, relu);
 }
 
 int ht_gemm_nt(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, float* C, int64_t ldc,
                int64_t M, int32_t N, int32_t K, int accumulate) {
   // C[M x K] = A[M x N] (B[K x N])^T : reduction over N, output width K
-  if (lda & 3) return ht_set_err(ctx, HT_ESHAPE, "gemm: row pitch must be a multiple of 4");
-  const int Rp = round_up(N, BK), Cp = round_up(K, 128);
-  float* Bp = nullptr;
-  HT_TRY(ht_scratch(ctx, HT_S_PACKW, (size_t)Rp * Cp * 4, (void**)&Bp));
-  // Bp[n][k] = B[k][n]
-  k_pack_b<<<(unsigned)(((int64_t)Rp * Cp + 255) / 256), 256, 0, st>>>(B, K, N, 1, Bp, Rp, Cp);
-  HT_LAUNCH_CHECK(ctx);
-  return gemm_nn_packed(ctx, st, A, lda, Bp, Cp, C, ldc, M, N, K, accumulate ? 2 : 0);
+  return gemm_nn(ctx, st, A, lda, B, true, C, ldc, M, N, K, accumulate ? 2 : 0);
 }
 
 namespace {
