@@ -103,6 +103,7 @@ int ht_scratch(ht_ctx* ctx, int slot, size_t bytes, void** out) {
   }
   if (ctx->scratch_bytes[slot] < bytes) {
     if (ctx->scratch[slot]) {
+      if (slot == HT_S_TNPART) HT_TRY(ht_flush_products(ctx, ctx->stream));   // (sums that were left to the end of the epoch are in there)
       HT_HIP(ctx, hipStreamSynchronize(ctx->stream));
       ht_dev_free(ctx, ctx->scratch[slot], ctx->scratch_bytes[slot]);
       ctx->scratch[slot] = nullptr;
@@ -120,6 +121,7 @@ int ht_scratch(ht_ctx* ctx, int slot, size_t bytes, void** out) {
 
 int ht_scratch_release(ht_ctx* ctx, int slot) {
   if (ctx->static_mode || !ctx->scratch[slot]) return HT_OK;
+  if (slot == HT_S_TNPART) HT_TRY(ht_flush_products(ctx, ctx->stream));
   HT_HIP(ctx, hipStreamSynchronize(ctx->stream));
   ht_dev_free(ctx, ctx->scratch[slot], ctx->scratch_bytes[slot]);
   ctx->scratch[slot] = nullptr;
@@ -339,7 +341,7 @@ int ht_ctx_destroy(ht_ctx* ctx) {
   for (ht_graph* g : ctx->graphs) g->ctx = nullptr;
   for (int i = 0; i < HT_N_SCRATCH; ++i)
     if (ctx->scratch[i]) ht_dev_free(ctx, ctx->scratch[i], ctx->scratch_bytes[i]);
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < HT_N_HS; ++i)
     if (ctx->hscratch[i]) (void)hipHostFree(ctx->hscratch[i]);
   for (hipEvent_t e : ctx->ev_pool) (void)hipEventDestroy(e);
   if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);

@@ -26,7 +26,7 @@ __global__ void k_relu_mask(const float* __restrict__ dh, int64_t ld_dh, const f
   *reinterpret_cast<float4*>(dz + r * ld_dz + c) = o;
 }
 
-// The loss in three launches whatever V is: labelled vertices per block; gradient rows and per-block loss sums; their total.
+// The loss in two launches whatever V is: labelled vertices per block; gradient rows and per-block loss sums.  k_step adds those up.
 // (With an atomic per wave for the count, a wave per vertex and the vertices' losses through memory it was six, 1.5 ms at 2.45 M
 // vertices and 47 classes, where the rows' bytes take 0.2; now 0.4 ms.)
 constexpr int COUNT_BLOCKS = 256;
@@ -106,29 +106,70 @@ __global__ void __launch_bounds__(256) k_softmax_ce(const float* __restrict__ lo
   if (threadIdx.x == 0) loss[blockIdx.x] = s;
 }
 
-__global__ void __launch_bounds__(256) k_finish_loss(const double* __restrict__ part, int n, const unsigned long long* __restrict__ cnt,
-                                                     int n_cnt, float* __restrict__ loss) {
-  __shared__ double sh[256];
-  __shared__ unsigned long long shc[256];
-  double s = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) s += part[i];
-  s = block_sum(s, sh);
-  const unsigned long long T = block_sum((int)threadIdx.x < n_cnt ? cnt[threadIdx.x] : 0ull, shc);
-  if (threadIdx.x == 0) *loss = T > 0 ? (float)(s / (double)T) : 0.f;
-}
-
-// One launch for all parameters of a model (a launch each costs its 4 us whatever the size): tensor t has the blocks from
-// first[t] on.
-struct SgdBatch {
+// The end of an epoch in one launch (a launch each for every product's slices, the update, the loss and its copy cost 4 to 8 us apiece: 10 k
+// vertices 156 -> 125 us an epoch with the products that read W in place).  Tensor t has the blocks from first[t] on, the last block has the loss.
+struct StepItem {
+  float* W;
+  float* dW;                 // read, or written with the sum of the slices
+  int64_t n;
+  const float* P;            // slices of `pitch` values each, `stride` apart inside a slice, added in slice order as k_reduce_slices does
+  int64_t pitch;
+  int stride, slices;
+};
+struct StepBatch {
   int n;
   unsigned first[HT_SGD_MAX + 1];
-  ht_sgd_item t[HT_SGD_MAX];
+  StepItem t[HT_SGD_MAX];
 };
-__global__ void k_sgd(SgdBatch b, float lr) {
+__global__ void __launch_bounds__(256) k_step(StepBatch b, float lr, LossParts L, float* __restrict__ loss) {
+  if (blockIdx.x == b.first[b.n]) {
+    __shared__ double sh[256];
+    __shared__ unsigned long long shc[256];
+    double s = 0.0;
+    for (int i = threadIdx.x; i < L.n_part; i += 256) s += L.part[i];
+    s = block_sum(s, sh);
+    const unsigned long long T = block_sum((int)threadIdx.x < L.n_count ? L.count[threadIdx.x] : 0ull, shc);
+    if (threadIdx.x == 0) *loss = T > 0 ? (float)(s / (double)T) : 0.f;
+    return;
+  }
   int k = 0;
   while (k + 1 < b.n && blockIdx.x >= b.first[k + 1]) ++k;
-  const int64_t i = (int64_t)(blockIdx.x - b.first[k]) * blockDim.x + threadIdx.x;
-  if (i < b.t[k].n) b.t[k].W[i] = b.t[k].W[i] - lr * b.t[k].dW[i];
+  const StepItem it = b.t[k];
+  const int64_t blk = blockIdx.x - b.first[k];
+  if (it.slices == 0) {
+    const int64_t i = blk * 256 + threadIdx.x;
+    if (i < it.n) it.W[i] = it.W[i] - lr * it.dW[i];
+    return;
+  }
+  // 64 elements; the four waves bring 64 slices at a time into LDS while the first one adds the 64 before them
+  __shared__ float tile[2][64][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t i = blk * 64 + lane;
+  const float* P = it.P + i * it.stride;
+  float v[16];
+  auto fetch = [&](int s0) {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int s = s0 + wave * 16 + q;
+      v[q] = (s < it.slices && i < it.n) ? P[(int64_t)s * it.pitch] : 0.f;
+    }
+  };
+  float s = 0.f;
+  fetch(0);
+  for (int s0 = 0, t = 0; s0 < it.slices; s0 += 64, t ^= 1) {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) tile[t][wave * 16 + q][lane] = v[q];
+    if (s0 + 64 < it.slices) fetch(s0 + 64);
+    __syncthreads();   // (the other buffer was added before this barrier's turn came round)
+    if (wave == 0) {
+      const int m = (it.slices - s0) < 64 ? (it.slices - s0) : 64;
+      for (int q = 0; q < m; ++q) s += tile[t][q][lane];
+    }
+  }
+  if (wave == 0 && i < it.n) {
+    it.dW[i] = s;
+    it.W[i] = it.W[i] - lr * s;
+  }
 }
 
 // n16 16-byte words from p16 (16-byte aligned), then the words of the ragged ends; a bounded grid
@@ -158,7 +199,7 @@ int ht_relu_mask(ht_ctx* ctx, hipStream_t st, const float* dh, int64_t ld_dh, co
 }
 
 int ht_softmax_ce(ht_ctx* ctx, hipStream_t st, const float* logits, int64_t ld, const int32_t* labels, int64_t V,
-                  int32_t C, float* grad, int64_t ld_g, float* loss_dev) {
+                  int32_t C, float* grad, int64_t ld_g, LossParts* loss) {
   if (V <= 0 || C <= 0) return ht_set_err(ctx, HT_EINVAL, "loss: empty input");
   if ((ld & 3) || (ld_g & 3)) return ht_set_err(ctx, HT_ESHAPE, "loss: row pitch must be a multiple of 4");
   int lpr = 4;
@@ -173,28 +214,43 @@ int ht_softmax_ce(ht_ctx* ctx, hipStream_t st, const float* logits, int64_t ld, 
   HT_LAUNCH_CHECK(ctx);
   k_softmax_ce<<<nb, 256, 0, st>>>(logits, ld, labels, V, C, cnt, (int)nc, grad, ld_g, part, lpr);
   HT_LAUNCH_CHECK(ctx);
-  k_finish_loss<<<1, 256, 0, st>>>(part, (int)nb, cnt, (int)nc, loss_dev);
-  HT_LAUNCH_CHECK(ctx);
+  *loss = LossParts{part, (int)nb, cnt, (int)nc};
   return HT_OK;
 }
 
-int ht_sgd(ht_ctx* ctx, hipStream_t st, const std::vector<ht_sgd_item>& items, float lr) {
-  for (size_t i = 0; i < items.size();) {
-    SgdBatch b{};
+int ht_step(ht_ctx* ctx, hipStream_t st, const std::vector<ht_sgd_item>& items, float lr, const LossParts& parts, float* loss) {
+  auto shared = [](const ht_sgd_item& a, const ht_sgd_item& b) { return a.W < b.W + b.n && b.W < a.W + a.n; };
+  for (size_t i = 0; i < items.size(); ++i)
+    for (size_t k = 0; k < i; ++k)
+      if (shared(items[i], items[k])) HT_TRY(ht_flush_products(ctx, st));   // (parameters that share memory are updated one after the other)
+  bool last = false;
+  for (size_t i = 0; !last;) {
+    StepBatch b{};
     for (; i < items.size() && b.n < HT_SGD_MAX; ++i) {
       const ht_sgd_item& it = items[i];
       if (it.n <= 0) continue;
-      bool shared = false;      // (parameters that share memory are updated one after the other)
-      for (int k = 0; k < b.n; ++k) shared = shared || (it.W < b.t[k].W + b.t[k].n && b.t[k].W < it.W + it.n);
-      if (shared) break;
-      b.t[b.n] = it;
-      b.first[b.n + 1] = b.first[b.n] + (unsigned)((it.n + 255) / 256);
+      bool wait = false;
+      for (int k = 0; k < b.n; ++k) wait = wait || shared(it, ht_sgd_item{b.t[k].W, nullptr, b.t[k].n});
+      if (wait) break;
+      StepItem s{it.W, const_cast<float*>(it.dW), it.n, nullptr, 0, 1, 0};
+      for (const PendingTn& p : ctx->tn_pending) {
+        for (int c = 0; c < 2; ++c)
+          if (p.column[c] == it.dW) { s.P = p.P + c; s.stride = 4; s.pitch = p.n; s.slices = p.slices; }
+        if (!p.column[0] && p.C == it.dW) { s.P = p.P; s.pitch = p.n; s.slices = p.slices; }
+      }
+      b.t[b.n] = s;
+      b.first[b.n + 1] = b.first[b.n] + (unsigned)((it.n + (s.slices ? 63 : 255)) / (s.slices ? 64 : 256));
       ++b.n;
     }
-    if (b.n == 0) continue;
-    k_sgd<<<b.first[b.n], 256, 0, st>>>(b, lr);
+    last = i >= items.size();
+    const unsigned blocks = b.first[b.n] + (last ? 1 : 0);
+    if (blocks == 0) continue;
+    k_step<<<blocks, 256, 0, st>>>(b, lr, parts, loss);
     HT_LAUNCH_CHECK(ctx);
   }
+  ctx->tn_pending.clear();
+  ctx->tn_used = 0;
+  ctx->tn_defer = false;
   return HT_OK;
 }
 

@@ -1215,6 +1215,9 @@ int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
   // the staging memory was used by the earlier phases: copies into it start behind their last reader
   if (lk.used) HT_TRY(lk.fork());
   bool first = true;
+  TnLater da_later;
+  da_later.column[0] = da_dst;
+  da_later.column[1] = da_src;
   int k = 0;
   for (int64_t r0 = 0; r0 < g->V; r0 += step, ++k) {
     const int64_t nr = std::min(step, g->V - r0);
@@ -1239,8 +1242,10 @@ int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
       HT_TRY(lk.wait(st, ev_bin));
     }
     tm->begin(&local->t_gemm_ms);
-    HT_TRY(ht_gemm_tn(ctx, st, ws.T + r0 * ws.ld_t, ws.ld_t, ws.pq4 + r0 * 4, 4, da4, nr, d, 4, first ? 0 : 1));
-    HT_TRY(ht_gemm_tn(ctx, st, h_rows, H_in->ld, dT + r0 * ld_dt, ld_dt, dW, nr, desc->d_in, d, first ? 0 : 1));
+    const bool all = nr == g->V;
+    TnLater later;
+    HT_TRY(ht_gemm_tn(ctx, st, ws.T + r0 * ws.ld_t, ws.ld_t, ws.pq4 + r0 * 4, 4, da4, nr, d, 4, first ? 0 : 1, all ? &da_later : nullptr));
+    HT_TRY(ht_gemm_tn(ctx, st, h_rows, H_in->ld, dT + r0 * ld_dt, ld_dt, dW, nr, desc->d_in, d, first ? 0 : 1, all ? &later : nullptr));
     if (dH_in)
       HT_TRY(ht_gemm_nt(ctx, st, dT + r0 * ld_dt, ld_dt, W, dh_rows, dH_in->ld, nr, d, desc->d_in, dh_add ? 1 : 0));
     tm->end();
@@ -1259,8 +1264,10 @@ int gat_bwd_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const 
     HT_TRY(ht_fill_zero(ctx, st, dW, (size_t)desc->d_in * d * 4));
     HT_TRY(ht_fill_zero(ctx, st, da4, (size_t)d * 16));
   }
-  k_gat_split<<<(unsigned)((d + 255) / 256), 256, 0, st>>>(da4, d, da_dst, da_src);
-  HT_LAUNCH_CHECK(ctx);
+  if (!da_later.left) {
+    k_gat_split<<<(unsigned)((d + 255) / 256), 256, 0, st>>>(da4, d, da_dst, da_src);
+    HT_LAUNCH_CHECK(ctx);
+  }
   if (lk.used) HT_TRY(lk.join());
   return HT_OK;
 }
@@ -1369,13 +1376,17 @@ static int gat_epoch_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_model* mo
     dad[l] = take(model->dims[l + 1]);
     das[l] = take(model->dims[l + 1]);
   }
-  float* loss_dev = take(4);
+  float *loss_host = nullptr, *loss_gpu = nullptr;
+  HT_TRY(ht_host_scratch(ctx, HT_HS_LOSS, 64, (void**)&loss_host));
+  HT_HIP(ctx, hipHostGetDevicePointer((void**)&loss_gpu, loss_host, 0));
+  LossParts loss_parts{};
   ht_stats local{};
   Timer tm(ctx, st, stats != nullptr);
   auto fail = [&](int rc) {
     (void)hipStreamSynchronize(st);
     (void)hipStreamSynchronize(ctx->side[0]);
     (void)hipStreamSynchronize(ctx->side[1]);
+    (void)ht_flush_products(ctx, st, true);
     ctx->ev_next = 0;
     return rc;
   };
@@ -1412,13 +1423,18 @@ static int gat_epoch_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_model* mo
   }
   bool changed = false;   // (only this call's own buffers)
   auto passes = [&]() -> int {
+    std::vector<size_t> products;
+    for (int l = 0; l < L; ++l)
+      for (int32_t d : {model->dims[l], 0})
+        products.push_back(ht_gemm_tn_bytes(V, d ? d : model->dims[l + 1], d ? model->dims[l + 1] : 4));
+    HT_TRY(ht_defer_products(ctx, products));
     for (int l = 0; l < L; ++l) {
       ht_gat_desc d{model->dims[l], model->dims[l + 1], l < L - 1 ? HT_ACT_RELU : HT_ACT_NONE, model->slope};
       HT_TRY(gat_fwd_impl(ctx, g, &d, l == 0 ? X : &h[l], model->W[l], model->a_dst[l], model->a_src[l], &h[l + 1],
                           keep.empty() ? nullptr : &keep[l], &local, &tm, l));
     }
     tm.begin(&local.t_loss_ms);
-    HT_TRY(ht_softmax_ce(ctx, st, h[L].ptr, h[L].ld, labels, V, model->dims[L], gh[L].ptr, gh[L].ld, loss_dev));
+    HT_TRY(ht_softmax_ce(ctx, st, h[L].ptr, h[L].ld, labels, V, model->dims[L], gh[L].ptr, gh[L].ld, &loss_parts));
     tm.end();
     for (int l = L - 1; l >= 0; --l) {
       ht_gat_desc d{model->dims[l], model->dims[l + 1], l < L - 1 ? HT_ACT_RELU : HT_ACT_NONE, model->slope};
@@ -1445,18 +1461,15 @@ static int gat_epoch_impl(ht_ctx* ctx, const ht_graph* g, const ht_gat_model* mo
     params.push_back({model->a_dst[l], dad[l], model->dims[l + 1]});
     params.push_back({model->a_src[l], das[l], model->dims[l + 1]});
   }
-  rc = ht_sgd(ctx, st, params, model->lr);
+  rc = ht_step(ctx, st, params, model->lr, loss_parts, loss_gpu);
   if (rc != HT_OK) return fail(rc);
-  {
-    hipError_t e = hipMemcpyAsync(loss_out, loss_dev, 4, hipMemcpyDeviceToHost, st);
-    if (e != hipSuccess) return fail(ht_set_err(ctx, HT_EHIP, "loss copy: %s", hipGetErrorString(e)));
-  }
   {
     hipError_t e = hipStreamSynchronize(st);
     if (e != hipSuccess) return fail(ht_set_err(ctx, HT_EHIP, "synchronize: %s", hipGetErrorString(e)));
     int rc = tm.resolve();
     ctx->ev_next = 0;
     if (rc != HT_OK) return rc;
+    *loss_out = *(volatile float*)loss_host;
   }
   if (stats) {
     for (int l = 0; l < HT_MAX_LAYERS; ++l) local.t_spmm_fwd_ms += local.t_agg_fwd_layer_ms[l];

@@ -20,6 +20,9 @@ constexpr int BM = 128;       // rows of A per block (NN) / output rows per bloc
 // Rows up to which a product reads W as it is, a launch less (10 k rows: 2.5 us and the gap before the next one).  Beyond a block per CU
 // the single loads and the bounds tests would be paid by every block.
 constexpr int64_t HT_PACK_ROWS = 32768;
+// Partial tiles of an epoch's products up to which they are added up by its last launch (each keeps its own until then).  Beyond it the
+// products take far longer than the launches that are saved.
+constexpr size_t HT_DEFER_BYTES = (size_t)64 << 20;
 constexpr int LDA_S = BK + 1; // LDS pitch of the row-major A tile (NN): odd, conflict-free column reads
 
 __device__ __forceinline__ float4 ld4g(const float* p) { return *reinterpret_cast<const float4*>(p); }
@@ -558,6 +561,19 @@ __global__ void __launch_bounds__(256) k_reduce_slices(const float* __restrict__
   if (wave == 0 && i < n) C[i] = s;
 }
 
+// The first two of every four values, each a vector of its own (the same sums).
+__global__ void __launch_bounds__(256) k_reduce_columns(const float* __restrict__ P, int64_t n, int slices, float* __restrict__ c0, float* __restrict__ c1) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n / 4) return;
+  float a = 0.f, b = 0.f;
+  for (int s = 0; s < slices; ++s) {
+    a += P[(int64_t)s * n + i * 4];
+    b += P[(int64_t)s * n + i * 4 + 1];
+  }
+  c0[i] = a;
+  c1[i] = b;
+}
+
 // Slices of a reduction over M rows: as many as fill the GPU with `tiles` output tiles each, not below 256 rows; a slice is a
 // multiple of the step.  `alone` (one row group, nothing beside it): down to 64 rows until there is a block per CU.  A slice is
 // a chain of loads, about 1.7 us per step of 16 rows, and slices add partial tiles to write and read: 10,000 rows, 64 x 32:
@@ -668,12 +684,21 @@ bool use_split_tn(int64_t rows, int32_t K, int32_t N) {
   return K > 64 && N > 64 && (rows >= 32768 || (double)rows * K * N >= 1e9);
 }
 
+size_t pad256(size_t b) { return (b + 255) & ~(size_t)255; }
+
 // rows: destination rows behind all slices
 int launch_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t M, int32_t K,
-              int32_t N, int64_t slice_rows, int64_t slices, const int64_t* tab, int64_t rows, int accumulate) {
+              int32_t N, int64_t slice_rows, int64_t slices, const int64_t* tab, int64_t rows, int accumulate, TnLater* later) {
   const int64_t kn = (int64_t)K * N;
   float* P = nullptr;
-  HT_TRY(ht_scratch(ctx, HT_S_TNPART, (size_t)(slices * kn) * 4, (void**)&P));
+  const size_t bytes = pad256((size_t)(slices * kn) * 4);
+  const bool leave = later && ctx->tn_defer && !accumulate && ctx->tn_used + bytes <= ctx->scratch_bytes[HT_S_TNPART];
+  if (leave) {
+    P = (float*)((char*)ctx->scratch[HT_S_TNPART] + ctx->tn_used);
+  } else {
+    HT_TRY(ht_flush_products(ctx, st));     // (the partial tiles of this one go where theirs are)
+    HT_TRY(ht_scratch(ctx, HT_S_TNPART, bytes, (void**)&P));
+  }
   dim3 grid((unsigned)((K + BM - 1) / BM), (unsigned)(N > 64 ? (N + 127) / 128 : 1), (unsigned)slices);
   if (use_split_tn(rows, K, N))
     k_split_tn<<<grid, 256, 0, st>>>(A, lda, B, ldb, P, M, K, N, slice_rows, tab);
@@ -682,6 +707,12 @@ int launch_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const fl
   else
     k_gemm_tn<64, 4, 1, 1, 2><<<grid, 256, 0, st>>>(A, lda, B, ldb, P, M, K, N, slice_rows, tab);
   HT_LAUNCH_CHECK(ctx);
+  if (leave) {
+    ctx->tn_used += bytes;
+    ctx->tn_pending.push_back(PendingTn{P, kn, (int)slices, C, {later->column[0], later->column[1]}});
+    later->left = true;
+    return HT_OK;
+  }
   k_reduce_slices<<<(unsigned)((kn + 63) / 64), 256, 0, st>>>(P, kn, (int)slices, accumulate, C);
   HT_LAUNCH_CHECK(ctx);
   return HT_OK;
@@ -690,7 +721,7 @@ int launch_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const fl
 }  // namespace
 
 int ht_gemm_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
-               int64_t M, int32_t K, int32_t N, int accumulate) {
+               int64_t M, int32_t K, int32_t N, int accumulate, TnLater* later) {
   if ((lda & 3) || (ldb & 3)) return ht_set_err(ctx, HT_ESHAPE, "gemm: row pitch must be a multiple of 4");
   if (K <= 0 || N <= 0) return HT_OK;
   if (M <= 0) {
@@ -699,7 +730,7 @@ int ht_gemm_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const f
   }
   int64_t rows, slices;
   SliceRule{tn_tiles(K, N), true}.cut(M, &rows, &slices);
-  return launch_tn(ctx, st, A, lda, B, ldb, C, M, K, N, rows, slices, nullptr, M, accumulate);
+  return launch_tn(ctx, st, A, lda, B, ldb, C, M, K, N, rows, slices, nullptr, M, accumulate, later);
 }
 
 size_t ht_gemm_tn_bytes(int64_t M, int32_t K, int32_t N) {
@@ -741,14 +772,50 @@ void ht_gemm_groups_wants(int32_t K, int32_t N, const std::vector<int64_t>& grou
   }
 }
 
+size_t ht_gemm_groups_bytes(int32_t K, int32_t N, const std::vector<int64_t>& groups) {
+  std::vector<ScratchWant> want;
+  ht_gemm_groups_wants(K, N, groups, &want);
+  size_t bytes = 0;
+  for (const ScratchWant& w : want) bytes += w.slot == HT_S_TNPART ? pad256(w.bytes) : 0;
+  return bytes;
+}
+
+int ht_defer_products(ht_ctx* ctx, const std::vector<size_t>& bytes) {
+  ctx->tn_pending.clear();
+  ctx->tn_used = 0;
+  ctx->tn_defer = false;
+  size_t all = 0;
+  for (size_t b : bytes) all += pad256(b);
+  if (all > HT_DEFER_BYTES || !ht_may_spend(ctx)) return HT_OK;
+  const int rc = ht_scratch_all(ctx, {{HT_S_TNPART, all}});
+  ctx->tn_defer = rc == HT_OK;
+  return rc == HT_ENOMEM ? (int)HT_OK : rc;
+}
+
+int ht_flush_products(ht_ctx* ctx, hipStream_t st, bool drop) {
+  for (const PendingTn& p : ctx->tn_pending) {
+    if (drop) break;
+    if (p.column[0]) {
+      k_reduce_columns<<<(unsigned)((p.n / 4 + 255) / 256), 256, 0, st>>>(p.P, p.n, p.slices, p.column[0], p.column[1]);
+    } else {
+      k_reduce_slices<<<(unsigned)((p.n + 63) / 64), 256, 0, st>>>(p.P, p.n, p.slices, 0, p.C);
+    }
+    HT_LAUNCH_CHECK(ctx);
+  }
+  ctx->tn_pending.clear();
+  ctx->tn_used = 0;
+  if (drop) ctx->tn_defer = false;
+  return HT_OK;
+}
+
 // The row groups' sums one after the other, as ht_gemm_tn called once per group would add them, in as few launches as the
 // partial tiles' memory allows.
 int ht_gemm_tn_groups(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int32_t K,
-                      int32_t N, const std::vector<int64_t>& groups, const int64_t* d_groups) {
+                      int32_t N, const std::vector<int64_t>& groups, const int64_t* d_groups, TnLater* later) {
   const size_t G = groups.size() / 2;
   if (G <= 1) {
     const int64_t r0 = G ? groups[0] : 0;
-    return ht_gemm_tn(ctx, st, A + r0 * lda, lda, B + r0 * ldb, ldb, C, G ? groups[1] - r0 : 0, K, N, 0);
+    return ht_gemm_tn(ctx, st, A + r0 * lda, lda, B + r0 * ldb, ldb, C, G ? groups[1] - r0 : 0, K, N, 0, later);
   }
   if ((lda & 3) || (ldb & 3)) return ht_set_err(ctx, HT_ESHAPE, "gemm: row pitch must be a multiple of 4");
   if (K <= 0 || N <= 0) return HT_OK;
@@ -762,7 +829,7 @@ int ht_gemm_tn_groups(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, 
     HT_TRY(ht_scratch(ctx, HT_S_TNTAB, (size_t)total * 16, (void**)&tab));
     k_slice_table<<<(unsigned)(g1 - g0), 256, 0, st>>>(d_groups + 2 * g0, rule, tab);
     HT_LAUNCH_CHECK(ctx);
-    HT_TRY(launch_tn(ctx, st, A, lda, B, ldb, C, 0, K, N, 0, total, tab, all, g0 > 0));
+    HT_TRY(launch_tn(ctx, st, A, lda, B, ldb, C, 0, K, N, 0, total, tab, all, g0 > 0, g1 == G ? later : nullptr));
     g0 = g1;
   }
   return HT_OK;

@@ -31,6 +31,17 @@ enum {
   HT_S_LINK0, HT_S_LINK1, HT_S_LINK2, HT_S_SCAN, HT_S_RSORT, HT_S_TNTAB, HT_S_LIST, HT_S_DENSE, HT_N_SCRATCH
 };
 
+constexpr int HT_HS_READBACK = 3, HT_HS_LOSS = 4, HT_N_HS = 5;
+
+// A product A^T B whose slices (n values each) are not added up yet: the end of the epoch does it beside the update (ht_step).
+struct PendingTn {
+  const float* P;
+  int64_t n;
+  int slices;
+  float* C;                    // [n], or, of width 4, its first two columns apart:
+  float* column[2];
+};
+
 struct ht_ctx {
   int device = 0;
   hipStream_t stream = nullptr;
@@ -54,9 +65,10 @@ struct ht_ctx {
   size_t static_used = 0;
   size_t static_off[HT_N_SCRATCH] = {};
   size_t static_len[HT_N_SCRATCH] = {};
-  // pinned host scratch (slots 0-2: D2H staging of gradient rows; HT_HS_READBACK: small counts read back by ht_partition)
-  void* hscratch[4] = {nullptr, nullptr, nullptr, nullptr};
-  size_t hscratch_bytes[4] = {0, 0, 0, 0};
+  // pinned host scratch (slots 0-2: D2H staging of gradient rows; HT_HS_READBACK: small counts read back by ht_partition; HT_HS_LOSS: an
+  // epoch's loss, of one size always, so that captured epochs may keep its address)
+  void* hscratch[HT_N_HS] = {};
+  size_t hscratch_bytes[HT_N_HS] = {};
   int xcd_contig = 0;     // 1: XCDs take contiguous parts of the item list instead of interleaving it
                           // (HT_XCD_CONTIG; measured slower at cfg2: 30.7 vs 26.0 ms per epoch)
   int no_link_fence = 0;  // 1: let aggregation kernels overlap link traffic (HT_NO_LINK_FENCE, for A/B runs)
@@ -79,6 +91,9 @@ struct ht_ctx {
   size_t gat_keep_limit = 0;   // a GAT epoch that kept this many bytes between its passes ran out of memory (0: none did) ...
   int64_t gat_keep_room = 0;   // ... and had this much room without them
   int64_t device_bytes = 0;    // HT_DEVICE_BYTES: plan as if the device had no more memory than this for the context (0: as it reports)
+  bool tn_defer = false;       // inside an epoch: products that allow it leave their slices (slot HT_S_TNPART, from tn_used bytes on) to ht_step
+  size_t tn_used = 0;
+  std::vector<PendingTn> tn_pending;
   int dense = 1;               // HT_DENSE=0: no products over a graph's dense tiles (ht_dense.hip)
   int fine = 1;                // HT_FINE=0: no shorter work items for training passes
   int64_t dense_work = HT_DENSE_WORK, fine_work = HT_FINE_WORK;   // HT_DENSE_WORK, HT_FINE_WORK
@@ -155,7 +170,6 @@ int ht_with_room(ht_ctx* ctx, F&& call, const bool* changed = nullptr) {
   return rc;
 }
 // Grow-only pinned host scratch.
-constexpr int HT_HS_READBACK = 3;
 int ht_host_scratch(ht_ctx* ctx, int slot, size_t bytes, void** out);
 
 template <typename T>
@@ -537,8 +551,17 @@ int ht_gemm_nn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const f
 int ht_gemm_nt(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, float* C, int64_t ldc,
                int64_t M, int32_t N, int32_t K, int accumulate);
 // C[K x N] (+)= A[M x K]^T B[M x N]; fixed-order reduction over M slices.
+// `later` (C of width 4: with its columns, which are written instead of C): the sum may be left to ht_step; *left = it was.
+struct TnLater {
+  float* column[2] = {nullptr, nullptr};
+  bool left = false;
+};
 int ht_gemm_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
-               int64_t M, int32_t K, int32_t N, int accumulate);
+               int64_t M, int32_t K, int32_t N, int accumulate, TnLater* later = nullptr);
+// Products may leave their sums to ht_step from here on, where all of them together take little memory; `bytes`: their partial tiles.
+int ht_defer_products(ht_ctx* ctx, const std::vector<size_t>& bytes);
+// Adds up what was left (before something else needs it, or after an error: `drop`).
+int ht_flush_products(ht_ctx* ctx, hipStream_t st, bool drop = false);
 
 // Bytes of the partial tiles (slot HT_S_TNPART) of an ht_gemm_tn call over M rows.
 size_t ht_gemm_tn_bytes(int64_t M, int32_t K, int32_t N);
@@ -546,7 +569,9 @@ size_t ht_gemm_tn_bytes(int64_t M, int32_t K, int32_t N);
 void ht_gemm_groups_wants(int32_t K, int32_t N, const std::vector<int64_t>& groups, std::vector<ScratchWant>* want);
 // C[K x N] = sum over the row groups [groups[2g], groups[2g+1]) of A^T B, added group by group (d_groups: the same on the device).
 int ht_gemm_tn_groups(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int32_t K,
-                      int32_t N, const std::vector<int64_t>& groups, const int64_t* d_groups);
+                      int32_t N, const std::vector<int64_t>& groups, const int64_t* d_groups, TnLater* later = nullptr);
+// Partial tiles of such a call, all groups together.
+size_t ht_gemm_groups_bytes(int32_t K, int32_t N, const std::vector<int64_t>& groups);
 
 // Aggregate + transform of one chunk in one kernel, the aggregate kept in LDS (ht_fused.hip)
 int ht_agg_update_fused(ht_ctx* ctx, hipStream_t st, const ht_graph* g, const ChunkMeta& c, const float* H_in, int64_t in_ld,
@@ -556,8 +581,15 @@ int ht_agg_update_fused(ht_ctx* ctx, hipStream_t st, const ht_graph* g, const Ch
 // dz = dh * [ref > 0]
 int ht_relu_mask(ht_ctx* ctx, hipStream_t st, const float* dh, int64_t ld_dh, const float* ref, int64_t ld_ref,
                  float* dz, int64_t ld_dz, int64_t rows, int32_t cols);
+// The loss as the sums of its blocks; ht_step adds them up.
+struct LossParts {
+  const double* part;
+  int n_part;
+  const unsigned long long* count;   // labelled vertices per block
+  int n_count;
+};
 int ht_softmax_ce(ht_ctx* ctx, hipStream_t st, const float* logits, int64_t ld, const int32_t* labels, int64_t V,
-                  int32_t C, float* grad, int64_t ld_g, float* loss_dev /*1 float*/);
+                  int32_t C, float* grad, int64_t ld_g, LossParts* loss);
 // W -= lr dW for every item
 struct ht_sgd_item {
   float* W;
@@ -565,7 +597,9 @@ struct ht_sgd_item {
   int64_t n;
 };
 constexpr int HT_SGD_MAX = 3 * HT_MAX_LAYERS;   // items per launch
-int ht_sgd(ht_ctx* ctx, hipStream_t st, const std::vector<ht_sgd_item>& items, float lr);
+// The end of an epoch: what products have left is added up, W -= lr dW, and the loss goes to *loss (memory of the host that the GPU can
+// write, as it sees it).
+int ht_step(ht_ctx* ctx, hipStream_t st, const std::vector<ht_sgd_item>& items, float lr, const LossParts& parts, float* loss);
 int ht_fill_words(ht_ctx* ctx, hipStream_t st, void* p, size_t bytes, uint32_t value);
 inline int ht_fill_zero(ht_ctx* ctx, hipStream_t st, void* p, size_t bytes) { return ht_fill_words(ctx, st, p, bytes, 0u); }
 

@@ -30,7 +30,6 @@ struct EpochWs {
   std::vector<size_t> dev_bytes_of;  // for freeing
   std::vector<void*> dev_ptrs;
   std::vector<void*> host_ptrs;
-  float* loss_dev = nullptr;
   const float* a0_of = nullptr;      // a[0] holds A_hat X for the X at this address (nullptr: not valid)
   uint64_t a0_graph = 0;             // ... and for the graph with this serial number
   // HIP graph of one epoch's stream work (all tensors in HBM): what it was captured for, and the
@@ -890,7 +889,8 @@ int layer_bwd_direct(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, c
     dz = dz_all;
     dz_ld = ld_o;
   }
-  HT_TRY(timed_gemm([&] { return ht_gemm_tn_groups(ctx, st, a_rows, a_ld, dz, dz_ld, dW, di, dn, g->dense_groups, g->d_dense_groups.p); }));
+  TnLater later;
+  HT_TRY(timed_gemm([&] { return ht_gemm_tn_groups(ctx, st, a_rows, a_ld, dz, dz_ld, dW, di, dn, g->dense_groups, g->d_dense_groups.p, &later); }));
   if (!dH_in) return HT_OK;
   HT_TRY(timed_gemm([&] { return ht_gemm_nt(ctx, st, dz, dz_ld, W, da_all, ld_i, V, dn, di, 0); }));
   return agg_by_source(R, da_all, ld_i, di, dH_in->ptr, dH_in->ld, !R.dhin_fresh, partial, plan);
@@ -1341,7 +1341,8 @@ int layer_bwd_update_first(Run& R, const ht_layer_desc* desc, const ht_tensor* H
   for (int64_t r0 = 0; r0 < g->V; r0 += step) {
     const int64_t nr = std::min(step, g->V - r0);
     R.tm.begin(&R.st->t_gemm_ms);
-    HT_TRY(ht_gemm_tn(ctx, st, H_in->ptr + r0 * H_in->ld, H_in->ld, dT + r0 * ld_t, ld_t, dW, nr, di, dn, first ? 0 : 1));
+    TnLater later;
+    HT_TRY(ht_gemm_tn(ctx, st, H_in->ptr + r0 * H_in->ld, H_in->ld, dT + r0 * ld_t, ld_t, dW, nr, di, dn, first ? 0 : 1, nr == g->V ? &later : nullptr));
     R.tm.end();
     R.st->n_gemm += 1;
     R.st->gemm_flops += 2.0 * nr * di * dn;
@@ -1626,11 +1627,6 @@ static int epoch_impl(ht_ctx* ctx, const ht_graph* g, const ht_model* model, con
       rc = ht_dev_alloc(ctx, &p, b);
       if (rc == HT_OK) { ws->dW[l] = (float*)p; ws->dev_ptrs.push_back(p); ws->dev_bytes_of.push_back(b); }
     }
-    if (rc == HT_OK) {
-      void* p = nullptr;
-      rc = ht_dev_alloc(ctx, &p, 16);
-      if (rc == HT_OK) { ws->loss_dev = (float*)p; ws->dev_ptrs.push_back(p); ws->dev_bytes_of.push_back(16); }
-    }
     if (rc != HT_OK) {
       ht_epoch_ws_free(ctx);
       return rc;
@@ -1647,6 +1643,7 @@ static int epoch_impl(ht_ctx* ctx, const ht_graph* g, const ht_model* model, con
     return ht_set_err(ctx, HT_EINVAL, "ht_epoch: unknown stats_detail %d", plan->stats_detail);
   auto fail = [&](int rc) {
     (void)hipStreamSynchronize(ctx->stream);
+    (void)ht_flush_products(ctx, ctx->stream, true);
     ctx->ev_next = 0;
     return rc;
   };
@@ -1674,7 +1671,15 @@ static int epoch_impl(ht_ctx* ctx, const ht_graph* g, const ht_model* model, con
   // key runs eagerly (it sizes the scratch memory, which a capture may not allocate), the second is
   // captured, instantiated and launched, later ones are one graph launch.
   bool in_capture = false;
+  float *loss_host = nullptr, *loss_gpu = nullptr;
+  HT_TRY(ht_host_scratch(ctx, HT_HS_LOSS, 64, (void**)&loss_host));
+  HT_HIP(ctx, hipHostGetDevicePointer((void**)&loss_gpu, loss_host, 0));
   auto enqueue = [&]() -> int {
+    std::vector<size_t> products;
+    for (int l = 0; l < L; ++l)
+      products.push_back((upd_mask >> l) & 1 ? ht_gemm_tn_bytes(V, model->dims[l], model->dims[l + 1])
+                                             : ht_gemm_groups_bytes(model->dims[l], model->dims[l + 1], g->dense_groups));
+    HT_TRY(ht_defer_products(ctx, products));
     // ---- forward (Alg. 1)
     for (int l = 0; l < L; ++l) {
       ht_layer_desc d{};
@@ -1699,10 +1704,11 @@ static int epoch_impl(ht_ctx* ctx, const ht_graph* g, const ht_model* model, con
       }
     }
     // ---- downstream task and its gradient (Alg. 1)
+    LossParts loss_parts{};
     {
       R.tm.begin(&R.st->t_loss_ms);
       int rc = ht_softmax_ce(ctx, ctx->stream, ws->h[L].ptr, ws->h[L].ld, labels, V, model->dims[L], ws->gh[L].ptr,
-                             ws->gh[L].ld, ws->loss_dev);
+                             ws->gh[L].ld, &loss_parts);
       R.tm.end();
       if (rc != HT_OK) return rc;
     }
@@ -1741,7 +1747,7 @@ static int epoch_impl(ht_ctx* ctx, const ht_graph* g, const ht_model* model, con
     R.tm.begin(&R.st->t_update_ms);
     std::vector<ht_sgd_item> params;
     for (int l = 0; l < L; ++l) params.push_back({model->W[l], ws->dW[l], (int64_t)model->dims[l] * model->dims[l + 1]});
-    HT_TRY(ht_sgd(ctx, ctx->stream, params, model->lr));
+    HT_TRY(ht_step(ctx, ctx->stream, params, model->lr, loss_parts, loss_gpu));
     R.tm.end();
     return HT_OK;
   };
@@ -1789,6 +1795,7 @@ static int epoch_impl(ht_ctx* ctx, const ht_graph* g, const ht_model* model, con
       }
     }
     if (graph) (void)hipGraphDestroy(graph);
+    if (rc != HT_OK) (void)ht_flush_products(ctx, ctx->stream, true);
     if (!launched) {   // nothing has run: this epoch runs eagerly below, and the key is not tried again
       if (getenv("HT_GRAPH_DEBUG"))
         fprintf(stderr, "ht_epoch: graph capture failed (enqueue rc %d: %s; hip: %s)\n", rc, ctx->err.c_str(), hipGetErrorString(e));
@@ -1802,15 +1809,13 @@ static int epoch_impl(ht_ctx* ctx, const ht_graph* g, const ht_model* model, con
     if (rc != HT_OK) return fail(rc);
     ws->warm_key = key;
   }
-  {
-    hipError_t e = hipMemcpyAsync(loss_out, ws->loss_dev, 4, hipMemcpyDeviceToHost, ctx->stream);
-    if (e != hipSuccess) return fail(ht_set_err(ctx, HT_EHIP, "loss copy: %s", hipGetErrorString(e)));
-  }
   local.plan_inter = inter;
   local.plan_res_h = res_h;
   local.plan_res_a = recompute ? 0 : res_a;
   local.plan_res_g = res_g;
-  return finish(R, stats, t0, true);
+  HT_TRY(finish(R, stats, t0, true));
+  *loss_out = *(volatile float*)loss_host;
+  return HT_OK;
 }
 
 int ht_epoch(ht_ctx* ctx, const ht_graph* g, const ht_model* model, const ht_tensor* X, const int32_t* labels,
