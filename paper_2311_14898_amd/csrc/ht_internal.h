@@ -7,6 +7,7 @@
 #include <chrono>
 #include <cstdio>
 #include <string>
+#include <unordered_map>
 #include <vector>
 
 #include "../../include/hongtu.h"
@@ -42,6 +43,13 @@ struct PendingTn {
   float* column[2];
 };
 
+// Device blocks that a context keeps for its next allocations.
+struct KeptBlock {
+  void* p;
+  size_t bytes;
+};
+constexpr size_t HT_KEPT_BYTES = (size_t)4 << 30, HT_KEPT_BLOCKS = 64;
+
 struct ht_ctx {
   int device = 0;
   hipStream_t stream = nullptr;
@@ -50,6 +58,9 @@ struct ht_ctx {
   std::string err;
   int64_t hbm_budget = 0;  // 0 = unlimited
   int64_t hbm_used = 0;
+  std::vector<KeptBlock> kept;                 // oldest first
+  size_t kept_bytes = 0;
+  std::unordered_map<void*, size_t> larger;    // blocks in use that hold more than was asked for
   std::vector<hipEvent_t> ev_pool;
   size_t ev_next = 0;
   EpochWs* ws = nullptr;  // buffers of the last ht_epoch
@@ -127,6 +138,8 @@ void ht_static_end(ht_ctx* ctx);
 // Device allocation with budget accounting.
 int ht_dev_alloc(ht_ctx* ctx, void** out, size_t bytes);
 void ht_dev_free(ht_ctx* ctx, void* p, size_t bytes);
+void ht_kept_release(ht_ctx* ctx);
+void ht_free_orphan(ht_graph* g);   // a graph whose context is gone
 // Grow-only scratch slot (kept on the context).
 int ht_scratch(ht_ctx* ctx, int slot, size_t bytes, void** out);
 // Gives a slot's memory back (after the work in flight).

@@ -2035,7 +2035,11 @@ int ht_partition(ht_ctx* ctx, int64_t V, int64_t E, const int32_t* src, const in
 
 int ht_graph_destroy(ht_graph* g) {
   if (!g) return HT_EINVAL;
-  if (g->ctx) {
+  if (!g->ctx) {
+    ht_free_orphan(g);
+    return HT_OK;
+  }
+  {
     (void)hipStreamSynchronize(g->ctx->stream);
     std::vector<ht_graph*>& all = g->ctx->graphs;
     all.erase(std::remove(all.begin(), all.end(), g), all.end());
