@@ -190,54 +190,48 @@ __global__ void __launch_bounds__(256) k_spmm_slab(SpmmArgs a, int S, int nvs, i
   const float* srcc = a.src + coff;
 
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  auto fetch = [&](int32_t base, int32_t* c, float* w) {   // the lane's entry of the next 64
+    *c = 0;
+    *w = 0.f;
+    if (base + lane < len) {
+      *c = a.idx[e0 + base + lane];
+      *w = a.w_edge ? a.w_edge[e0 - a.w0 + base + lane] : (a.ew ? a.ew[*c] : 1.f);
+    }
+  };
+  int32_t next_idx;
+  float next_w;
+  fetch(0, &next_idx, &next_w);
   for (int32_t base = 0; base < len; base += 64) {
     const int32_t n_here = (len - base) < 64 ? (len - base) : 64;
-    int32_t my_idx = 0;
-    float my_w = 0.f;
-    if (lane < n_here) {
-      my_idx = a.idx[e0 + base + lane];
-      my_w = a.w_edge ? a.w_edge[e0 - a.w0 + base + lane] : (a.ew ? a.ew[my_idx] : 1.f);
-    }
-    if (UNI) {
-      // one edge per step for the whole wave: the index and weight are wave-uniform
-      for (int32_t k = 0; k < n_here; k += U) {
-        int32_t c[U];
-        float w[U];
+    const int32_t my_idx = next_idx;
+    const float my_w = next_w;
+    if (base + 64 < len) fetch(base + 64, &next_idx, &next_w);
+    const int step = UNI ? U : U * eps;      // (one edge per slot and step; UNI: one slot, so index and weight are the wave's)
+    for (int32_t k = 0; k < n_here; k += step) {
+      int32_t c[U];
+      float w[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int kk = k + u;
-          const int kc = kk < n_here ? kk : (n_here - 1);
+      for (int u = 0; u < U; ++u) {
+        const int kk = UNI ? k + u : k + u * eps + es;
+        const int kc = kk < n_here ? kk : (n_here - 1);   // past the end: the last edge's row again, as zeros
+        if (UNI) {
           c[u] = __builtin_amdgcn_readlane(my_idx, kc);
           w[u] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_w), kc));
-          if (kk >= n_here) w[u] = 0.f;
-        }
-        if (active) {
-          float4 v[U];
-#pragma unroll
-          for (int u = 0; u < U; ++u) v[u] = ld4(srcc + (int64_t)c[u] * a.src_ld);
-#pragma unroll
-          for (int u = 0; u < U; ++u) acc = fma4(w[u], v[u], acc);
-        }
-      }
-    } else {
-      for (int32_t k = 0; k < n_here; k += U * eps) {
-        int32_t c[U];
-        float w[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int kk = k + u * eps + es;
-          const int kc = kk < n_here ? kk : (n_here - 1);   // past the end: re-read the last edge with weight 0
+        } else {
           c[u] = __shfl(my_idx, kc, 64);
           w[u] = __shfl(my_w, kc, 64);
-          if (kk >= n_here) w[u] = 0.f;
         }
-        if (active) {
-          float4 v[U];
+      }
+      if (active) {
+        float4 v[U];
 #pragma unroll
-          for (int u = 0; u < U; ++u) v[u] = ld4(srcc + (int64_t)c[u] * a.src_ld);
+        for (int u = 0; u < U; ++u) v[u] = ld4(srcc + (int64_t)c[u] * a.src_ld);
+        if (k + step > n_here)
 #pragma unroll
-          for (int u = 0; u < U; ++u) acc = fma4(w[u], v[u], acc);
-        }
+          for (int u = 0; u < U; ++u)
+            if ((UNI ? k + u : k + u * eps + es) >= n_here) v[u] = make_float4(0.f, 0.f, 0.f, 0.f), w[u] = 0.f;
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc = fma4(w[u], v[u], acc);
       }
     }
   }
