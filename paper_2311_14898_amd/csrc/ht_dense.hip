@@ -222,7 +222,8 @@ __device__ __forceinline__ int64_t cell_at(int64_t tile, int row, int col) {
 }
 
 // The entries of the taken tiles go into their cells; keep[e] = 0 for them, and rest[row] loses them.
-__global__ void __launch_bounds__(TB) k_dense_fill(RowEntries R, const float* __restrict__ w, const float* __restrict__ s, int n_cg,
+__global__ void __launch_bounds__(TB) k_dense_fill(RowEntries R, const float* __restrict__ w, const float* __restrict__ mult,
+                                                   const float* __restrict__ s, int n_cg,
                                                    const int32_t* __restrict__ tile_of, uint8_t* __restrict__ cells, uint8_t* __restrict__ keep,
                                                    int32_t* __restrict__ rest, int32_t* __restrict__ pos) {
   __shared__ int32_t tab[MAX_CG], gone[DENSE_ROWS];
@@ -237,28 +238,50 @@ __global__ void __launch_bounds__(TB) k_dense_fill(RowEntries R, const float* __
   gone[threadIdx.x] = 0;
   if (!__syncthreads_or(any)) return;
   const int32_t limit = n_cg * DENSE_COLS;
-  for (int64_t f = P.f0 + threadIdx.x; f < P.f1; f += TB) {
-    const int r = P.row_of(f);
-    const int64_t e0 = P.first[r], e = e0 + (f - P.at[r]), e1 = e0 + (P.at[r + 1] - P.at[r]);
-    const int32_t u = R.idx[e], c = R.crank[u];
-    const int32_t t = c < limit ? tab[c / DENSE_COLS] : -1;
-    if (t < 0) continue;
-    float m = 0.f;
-    bool first = true;
-    if (w) {
-      // (the multiplicity out of w = multiplicity * s: both roundings together are off by less than 2^-23 of it)
-      m = rintf(w[e] / s[u]);
-    } else {   // a run of equal entries; one of more than 255 stays as it is
-      int64_t a = e, z = e + 1;
-      while (a > e0 && e - a < 256 && R.idx[a - 1] == u) --a;
-      while (z < e1 && z - e < 256 && R.idx[z] == u) ++z;
-      m = (float)(z - a);
-      first = a == e;
+  // (four entries a thread at a time: each is a chain of loads)
+  for (int64_t f = P.f0 + threadIdx.x; f < P.f1; f += 4 * TB) {
+    int r[4];
+    int64_t e[4];
+    int32_t u[4], c[4], t[4];
+    float m[4];
+    bool first[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t x = f + q * TB;
+      r[q] = x < P.f1 ? P.row_of(x) : 0;
+      e[q] = x < P.f1 ? P.first[r[q]] + (x - P.at[r[q]]) : -1;
+      u[q] = e[q] >= 0 ? R.idx[e[q]] : 0;
+      m[q] = w && e[q] >= 0 ? (mult ? mult : w)[e[q]] : 0.f;
     }
-    if (!(m >= 1.f && m <= 255.f)) continue;
-    if (first) cells[cell_at(t, r, c % DENSE_COLS)] = (uint8_t)m;
-    keep[e] = 0;
-    atomicAdd(&gone[r], 1);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      c[q] = e[q] >= 0 ? R.crank[u[q]] : limit;
+      // (the multiplicity out of w = multiplicity * s: both roundings together are off by less than 2^-23 of it)
+      if (w && !mult) m[q] = rintf(m[q] / s[u[q]]);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      t[q] = c[q] < limit ? tab[c[q] / DENSE_COLS] : -1;
+      first[q] = true;
+      if (!w && t[q] >= 0) {   // a run of equal entries; one of more than 255 stays as it is
+        const int64_t e0 = P.first[r[q]], e1 = e0 + (P.at[r[q] + 1] - P.at[r[q]]);
+        int64_t a = e[q], z = e[q] + 1;
+        while (a > e0 && e[q] - a < 256 && R.idx[a - 1] == u[q]) --a;
+        while (z < e1 && z - e[q] < 256 && R.idx[z] == u[q]) ++z;
+        m[q] = (float)(z - a);
+        first[q] = a == e[q];
+      }
+      const bool take = t[q] >= 0 && m[q] >= 1.f && m[q] <= 255.f;
+      if (take) {
+        if (first[q]) cells[cell_at(t[q], r[q], c[q] % DENSE_COLS)] = (uint8_t)m[q];
+        keep[e[q]] = 0;
+      }
+      // (a wave's entries are mostly one row's)
+      const int r0 = __builtin_amdgcn_readfirstlane(r[q]);
+      const uint64_t same = __ballot(take && r[q] == r0);
+      if ((int)(threadIdx.x & 63) == __builtin_ctzll(same | (1ull << 63)) && same) atomicAdd(&gone[r0], __popcll(same));
+      if (take && r[q] != r0) atomicAdd(&gone[r[q]], 1);
+    }
   }
   __syncthreads();
   const int32_t row = R.order[(int64_t)P.rb * DENSE_ROWS + threadIdx.x];
@@ -647,7 +670,7 @@ int build_dense(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, DenseSide& 
   HT_TRY(ht_fill_words(ctx, st, t.keep.p, ((size_t)n_ent + 3) & ~(size_t)3, 0x01010101u));
   k_row_lengths<<<nblk(V), TB, 0, st>>>(ptr, V, t.rest.p);
   HT_LAUNCH_CHECK(ctx);
-  k_dense_fill<<<(unsigned)t.n_parts, TB, 0, st>>>(R, w, g->s.p, n_cg, t.flag.p, D.cells.p, t.keep.p, t.rest.p, D.pos.p);
+  k_dense_fill<<<(unsigned)t.n_parts, TB, 0, st>>>(R, w, fwd && g->merged ? g->umult.p : nullptr, g->s.p, n_cg, t.flag.p, D.cells.p, t.keep.p, t.rest.p, D.pos.p);
   HT_LAUNCH_CHECK(ctx);
   // what is left, in the same order
   const int64_t et = ceil_div64(n_ent, ETILE);
