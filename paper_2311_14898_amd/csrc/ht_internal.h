@@ -83,7 +83,10 @@ struct ht_ctx {
   int xcd_contig = 0;     // 1: XCDs take contiguous parts of the item list instead of interleaving it
                           // (HT_XCD_CONTIG; measured slower at cfg2: 30.7 vs 26.0 ms per epoch)
   int no_link_fence = 0;  // 1: let aggregation kernels overlap link traffic (HT_NO_LINK_FENCE, for A/B runs)
-  int link_blocks = 64;   // workgroups of a kernel that moves rows over the host link (HT_LINK_BLOCKS)
+  // workgroups of a kernel that moves rows over the host link (HT_LINK_BLOCKS): the link takes no more than a few give it, and the others only
+  // stand in the way of the gather and the compute beside it (64, 32, 16, 8: 612 k vertices, 15 M edges, h and grad h on the host 159.6, 154.7,
+  // 152.3, 154.4 ms an epoch, with a^l there too 206, 197, 194; GAT 179, 176, 173)
+  int link_blocks = 16;
   int gather_blocks = 128; // workgroups of the neighbour-row gather from host memory (HT_GATHER_BLOCKS): beside a D2H
                            // copy the gather's read requests queue behind the write data, and more waves keep more in flight
   int link_memcpy = 0;    // hipMemcpyAsync for contiguous host<->device row ranges: 1 both ways, 2 to the host only, 3 from the host only (HT_LINK_MEMCPY)
