@@ -82,7 +82,6 @@ struct ht_ctx {
   size_t hscratch_bytes[HT_N_HS] = {};
   int xcd_contig = 0;     // 1: XCDs take contiguous parts of the item list instead of interleaving it
                           // (HT_XCD_CONTIG; measured slower at cfg2: 30.7 vs 26.0 ms per epoch)
-  int no_link_fence = 0;  // 1: let aggregation kernels overlap link traffic (HT_NO_LINK_FENCE, for A/B runs)
   // workgroups of a kernel that moves rows over the host link (HT_LINK_BLOCKS): the link takes no more than a few give it, and the others only
   // stand in the way of the gather and the compute beside it (64, 32, 16, 8: 612 k vertices, 15 M edges, h and grad h on the host 159.6, 154.7,
   // 152.3, 154.4 ms an epoch, with a^l there too 206, 197, 194; GAT 179, 176, 173)

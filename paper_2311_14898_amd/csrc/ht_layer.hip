@@ -147,22 +147,6 @@ struct Pipe {
     HT_HIP(ctx, hipStreamWaitEvent(s, e, 0));
     return HT_OK;
   }
-  // Link traffic and the aggregation kernels are kept apart in time: run together both slow
-  // down several-fold on this GPU (measured), while the dense transforms and the host-side
-  // adds overlap with link traffic at no cost.
-  hipEvent_t last_in = nullptr, last_out = nullptr, quiet = nullptr;
-  bool fence = false;
-  int link_begin(hipStream_t s) { return fence ? wait(s, quiet) : HT_OK; }
-  int link_end(hipStream_t s) {
-    if (!fence) return HT_OK;
-    return rec(s, s == s_in ? &last_in : &last_out);
-  }
-  int agg_begin() {
-    if (!fence) return HT_OK;
-    HT_TRY(wait(s_c, last_in));
-    return wait(s_c, last_out);
-  }
-  int agg_end() { return fence ? rec(s_c, &quiet) : HT_OK; }
 };
 
 // Rows of N_j \ N_{j-1} from H_in (HBM or pinned host, read in place by the
@@ -516,7 +500,6 @@ int layer_fwd_impl(Run& R, const ht_layer_desc* desc, const ht_tensor* H_in, con
   if (buffer) HT_TRY(ht_scratch(ctx, HT_S_NBUF, (size_t)g->cache_rows * H_in->ld * 4, (void**)&nbuf));
 
   Pipe P(ctx);
-  P.fence = (side_in || staged) && !ctx->no_link_fence;
   if (side_in) {
     hipEvent_t ev_start = nullptr;
     HT_TRY(P.rec(P.s_c, &ev_start));
@@ -552,9 +535,7 @@ int layer_fwd_impl(Run& R, const ht_layer_desc* desc, const ht_tensor* H_in, con
     if (buffer) {
       if (side_in) {
         HT_TRY(P.wait(P.s_in, ev_agg_prev));   // the buffer is updated in place
-        HT_TRY(P.link_begin(P.s_in));
         HT_TRY(gather_chunk(R, j, H_in, Hin, di, nbuf, P.s_in));
-        HT_TRY(P.link_end(P.s_in));
         hipEvent_t ev_g = nullptr;
         HT_TRY(P.rec(P.s_in, &ev_g));
         HT_TRY(P.wait(P.s_c, ev_g));
@@ -578,9 +559,7 @@ int layer_fwd_impl(Run& R, const ht_layer_desc* desc, const ht_tensor* H_in, con
     }
     if (staged) HT_TRY(P.wait(P.s_c, ev_out[b]));
     float* a_dst = a_dev ? A_ckpt->ptr + c.dst0 * a_ld : a_stage[b];
-    HT_TRY(P.agg_begin());
     HT_TRY(spmm_chunk(R, j, buffer, buffer ? nbuf : Hin, H_in->ld, di, a_dst, a_ld));
-    HT_TRY(P.agg_end());
     if (side_in) HT_TRY(P.rec(P.s_c, &ev_agg_prev));
     if (merge_dense) {
       if (pend0 >= 0 && c.dst0 != pend1) HT_TRY(flush_dense());   // not adjacent in vertex order (reorganised schedule)
@@ -599,14 +578,12 @@ int layer_fwd_impl(Run& R, const ht_layer_desc* desc, const ht_tensor* H_in, con
       hipEvent_t ev_c = nullptr;
       HT_TRY(P.rec(P.s_c, &ev_c));
       HT_TRY(P.wait(P.s_out, ev_c));
-      HT_TRY(P.link_begin(P.s_out));
       P.used_out = true;
       if (a_host)
         HT_TRY(copy_rows(R, P.s_out, A_ckpt->ptr + c.dst0 * a_ld, a_stage[b], (size_t)ndst * a_ld * 4, hipMemcpyDeviceToHost));
       if (!h_dev)
         HT_TRY(copy_rows(R, P.s_out, H_out->ptr + c.dst0 * H_out->ld, h_stage[b], (size_t)ndst * H_out->ld * 4,
                          hipMemcpyDeviceToHost));
-      HT_TRY(P.link_end(P.s_out));
       HT_TRY(P.rec(P.s_out, &ev_out[b]));
     }
   }
@@ -1023,7 +1000,6 @@ int layer_bwd_impl(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, con
   AccWorker worker(ctx);   // declared after P: joined before P's destructor waits for the streams
   if (cpu_accum) worker.start();
   R.changed = true;
-  P.fence = (in_host || cpu_accum || store_home) && !ctx->no_link_fence;
   if (in_host) {
     hipEvent_t ev_start = nullptr;
     HT_TRY(P.rec(P.s_c, &ev_start));
@@ -1043,14 +1019,12 @@ int layer_bwd_impl(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, con
       hipEvent_t ev_done = nullptr, ev_st = nullptr;
       HT_TRY(P.rec(P.s_c, &ev_done));
       HT_TRY(P.wait(P.s_out, ev_done));
-      HT_TRY(P.link_begin(P.s_out));
       P.used_out = true;
       const int id = R.tm.begin_on(&R.st->t_copy_ms, P.s_out);
       HT_TRY(ht_gather_rows(ctx, P.s_out, gbuf, ld_i, g->leave_slot.p + c.leave_off, dhin_gpu, dH_in->ld,
                             g->leave.p + c.leave_off, c.n_leave, di, nullptr, ctx->link_blocks));
       R.tm.end_id(id);
       R.st->bytes_d2h += c.n_leave * (int64_t)di * 4;
-      HT_TRY(P.link_end(P.s_out));
       HT_TRY(P.rec(P.s_out, &ev_st));
       ev_stored = ev_st;   // waited for before the next aggregation writes freed positions, and at the end
     } else if (!cpu_accum) {
@@ -1070,10 +1044,8 @@ int layer_bwd_impl(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, con
         HT_TRY(P.wait(P.s_out, ev_comp));
         if (n_left > NLV) worker.wait_done(n_left - NLV);   // the host has consumed leave_pin[r]
         if (worker.failed()) return ht_set_err(ctx, HT_EHIP, "host-side accumulation: waiting for a copy failed");
-        HT_TRY(P.link_begin(P.s_out));
         P.used_out = true;
         HT_TRY(copy_rows(R, P.s_out, leave_pin[r], leave_dev[r], (size_t)nk * ld_i * 4, hipMemcpyDeviceToHost));
-        HT_TRY(P.link_end(P.s_out));
         HT_TRY(P.rec(P.s_out, &ev_leave_free[r]));
         worker.push(AccTask{ev_leave_free[r], dH_in->ptr, dH_in->ld, g->leave_host.data() + off, leave_pin[r], ld_i, nk, di});
       }
@@ -1097,7 +1069,6 @@ int layer_bwd_impl(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, con
     int64_t ref_ld = 0;
     if (in_host) {
       HT_TRY(P.wait(P.s_in, ev_cdone[b]));
-      HT_TRY(P.link_begin(P.s_in));
     }
     if (agg_ckpt) {
       if (a_host) {
@@ -1125,7 +1096,6 @@ int layer_bwd_impl(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, con
       }
     }
     if (in_host) {
-      HT_TRY(P.link_end(P.s_in));
       hipEvent_t ev_in = nullptr;
       HT_TRY(P.rec(P.s_in, &ev_in));
       HT_TRY(P.wait(P.s_c, ev_in));
@@ -1135,9 +1105,7 @@ int layer_bwd_impl(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, con
       for (int j = j0; j <= j1; ++j) {
         const ChunkMeta& cj = g->chunks[j];
         if (agg_buffer) HT_TRY(gather_chunk(R, j, ckpt, Hin, di, nbuf, st));
-        HT_TRY(P.agg_begin());
         HT_TRY(spmm_chunk(R, j, agg_buffer, agg_buffer ? nbuf : Hin, ckpt->ld, di, a_stage[b] + (cj.dst0 - c.dst0) * a_ld, a_ld));
-        HT_TRY(P.agg_end());
       }
       a_rows = a_stage[b];
     }
@@ -1191,11 +1159,9 @@ int layer_bwd_impl(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, con
         a.partial = partial;
         a.max_slabs = ctx->slabs_bwd;
         HT_TRY(P.wait(P.s_c, ev_stored));   // positions freed by the last store are written from here on
-        HT_TRY(P.agg_begin());
         R.tm.begin(&R.st->t_spmm_bwd_ms);
         HT_TRY(ht_spmm_launch(ctx, st, a));
         R.tm.end();
-        HT_TRY(P.agg_end());
         R.st->n_spmm_bwd += 1;
         R.st->edges += cj.nnz;
         R.st->spmm_bwd_alg_bytes += spmm_alg_bytes(cj, di);
