@@ -255,10 +255,14 @@ int64_t ht_held(const ht_ctx* ctx) {
   return held;
 }
 
+bool ht_caller_captures(ht_ctx* ctx) {
+  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(ctx->stream, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone;
+}
+
 bool ht_give_back(ht_ctx* ctx) {
   if (ctx->static_mode || ctx->no_grow || ctx->lean || ht_held(ctx) == 0) return false;
-  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;   // (by the owner of the stream)
-  if (hipStreamIsCapturing(ctx->stream, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone) return false;
+  if (ht_caller_captures(ctx)) return false;
   (void)hipStreamSynchronize(ctx->stream);
   for (hipStream_t s : ctx->side) (void)hipStreamSynchronize(s);
   for (int k = 0; k < HT_N_SCRATCH; ++k) (void)ht_scratch_release(ctx, k);

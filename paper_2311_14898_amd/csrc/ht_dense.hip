@@ -707,6 +707,7 @@ int ht_pass_plan(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, PassPlan* 
   // makes `what` (its part of the plan) unless there was no memory for it with as much room as there is now
   auto make = [&](auto& what, auto&& build) -> int {
     if (!may || (what.refused >= 0 && ht_room(ctx) <= what.refused)) return HT_OK;
+    if (ht_caller_captures(ctx)) return HT_OK;   // (building allocates and waits)
     const int rc = build();
     if (rc != HT_ENOMEM) return rc;
     (void)hipStreamSynchronize(ctx->stream);

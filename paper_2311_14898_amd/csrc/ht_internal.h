@@ -171,6 +171,7 @@ struct ScratchMark {
 // all the same is made again once everything the context can do without was given back (scratch slots, by-source lists), with `lean`
 // set.  From then on nothing is spent until there is more room than was left by that call.
 bool ht_may_spend(ht_ctx* ctx);
+bool ht_caller_captures(ht_ctx* ctx);   // the owner of the context's stream records what is launched there: nothing may be allocated
 bool ht_give_back(ht_ctx* ctx);   // false: there was nothing to give back
 int64_t ht_held(const ht_ctx* ctx);   // bytes that ht_give_back would free
 // `changed`: the call has begun to change what the caller handed in, and cannot be made again.

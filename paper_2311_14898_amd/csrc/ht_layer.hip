@@ -288,7 +288,10 @@ int take_plan(Run& R, bool fwd, int d, int64_t ld, PassPlan* out) {
   HT_TRY(ht_pass_plan(ctx, R.g, fwd, d, &p));
   const int64_t part_bytes = p.parts() * ld * 4;
   if (!p.items || part_bytes > HT_PLAN_BYTES) return HT_OK;
-  const int rc = ht_scratch_all(ctx, {{HT_S_SPART, (size_t)part_bytes}, {HT_S_DENSE, p.dense ? ht_dense_bytes(*p.dense, d) : 0}});
+  const size_t dense_bytes = p.dense ? ht_dense_bytes(*p.dense, d) : 0;
+  const bool grows = ctx->scratch_bytes[HT_S_SPART] < (size_t)part_bytes || ctx->scratch_bytes[HT_S_DENSE] < dense_bytes;
+  if (grows && ht_caller_captures(ctx)) return HT_OK;
+  const int rc = ht_scratch_all(ctx, {{HT_S_SPART, (size_t)part_bytes}, {HT_S_DENSE, dense_bytes}});
   if (rc == HT_OK) *out = p;
   return rc == HT_ENOMEM ? (int)HT_OK : rc;
 }

@@ -186,3 +186,38 @@ def test_no_room_for_the_plan(planned):
     finally:
         B.ht_graph_destroy(g)
         B.ht_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("planned", [{"HT_DENSE_WORK": "1"}, {"HT_DENSE": "0", "HT_FINE_WORK": "1"}], indirect=True)
+def test_first_pass_inside_a_callers_capture(planned, monkeypatch):
+    """A pass that would make its plan while its caller records the stream records the graph's own items instead, with the bits of the
+    forward that keeps no aggregate; the plan is made by the next pass outside of a capture."""
+    c = Case(2000, "rmat", 40)
+    st = torch.cuda.Stream()
+    ctx = B.ht_ctx_create(0, st.cuda_stream)
+    g = B.ht_partition(ctx, c.V, c.src.cuda(), c.dst.cuda(), 2)
+    try:
+        I, Xd = torch.eye(40, device="cuda"), B.to_matrix(c.X)
+        H, H2, A = (B.alloc_matrix(c.V, 40) for _ in range(3))
+        torch.cuda.synchronize()
+        B.ht_layer_fwd(ctx, g, 40, 40, B.HT_ACT_NONE, Xd, I, H)
+        B.ht_sync(ctx)
+        before = B.ht_graph_info_get(g).hbm_bytes
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=st), monkeypatch.context() as m:
+            m.setattr(torch.cuda, "synchronize", lambda *a: None)     # (the binding's, before every call)
+            B.ht_layer_fwd(ctx, g, 40, 40, B.HT_ACT_NONE, Xd, I, H2, A)
+        assert B.ht_graph_info_get(g).hbm_bytes == before
+        for _ in range(3):
+            H2.zero_()
+            A.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(H2[:, :40], H[:, :40]) and torch.equal(A[:, :40], H[:, :40])
+        B.ht_layer_fwd(ctx, g, 40, 40, B.HT_ACT_NONE, Xd, I, H2, A)
+        B.ht_sync(ctx)
+        assert B.ht_graph_info_get(g).hbm_bytes > before
+    finally:
+        B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)
