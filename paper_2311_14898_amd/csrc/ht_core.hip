@@ -80,6 +80,7 @@ int ht_dev_alloc(ht_ctx* ctx, void** out, size_t bytes) {
   if (ctx->hbm_budget > 0 && ctx->hbm_used + (int64_t)bytes > ctx->hbm_budget)
     return ht_set_err(ctx, HT_ENOMEM, "HBM budget exceeded: %lld in use + %zu requested > %lld",
                       (long long)ctx->hbm_used, bytes, (long long)ctx->hbm_budget);
+  if (ctx->refuse_alloc > 0 && --ctx->refuse_alloc == 0) return ht_set_err(ctx, HT_ENOMEM, "allocation of %zu bytes refused (HT_REFUSE_ALLOC)", bytes);
   size_t best = ctx->kept.size();
   for (size_t k = 0; k < ctx->kept.size(); ++k) {
     const size_t have = ctx->kept[k].bytes;
@@ -369,6 +370,7 @@ int ht_ctx_create(ht_ctx** out, int device, void* hip_stream) {
   if (const char* v = getenv("HT_FINE_WORK")) c->fine_work = std::max<int64_t>(1, atoll(v));
   if (const char* v = getenv("HT_FUSE_UPDATE")) c->fuse_update = atoi(v);
   if (const char* v = getenv("HT_AGG_PHASES")) c->agg_phases = atoi(v) > 1 ? atoi(v) : 1;
+  if (const char* v = getenv("HT_REFUSE_ALLOC")) c->refuse_alloc = atoll(v);
   if (const char* v = getenv("HT_DEVICE_BYTES")) c->device_bytes = atoll(v);
   if (const char* v = getenv("HT_LINK_BLOCK_ROWS")) c->link_block_rows = atoll(v) > 0 ? atoll(v) : c->link_block_rows;
   if (hip_stream) {

@@ -103,6 +103,7 @@ struct ht_ctx {
   int64_t tight_room = -1;     // room that was left after the last such call (-1: none since memory was plentiful)
   size_t gat_keep_limit = 0;   // a GAT epoch that kept this many bytes between its passes ran out of memory (0: none did) ...
   int64_t gat_keep_room = 0;   // ... and had this much room without them
+  int64_t refuse_alloc = 0;    // HT_REFUSE_ALLOC=k: the context's k-th device allocation is refused, as if the device had no memory (tests)
   int64_t device_bytes = 0;    // HT_DEVICE_BYTES: plan as if the device had no more memory than this for the context (0: as it reports)
   bool tn_defer = false;       // inside an epoch: products that allow it leave their slices (slot HT_S_TNPART, from tn_used bytes on) to ht_step
   size_t tn_used = 0;
@@ -155,6 +156,8 @@ int64_t ht_room(ht_ctx* ctx);
 struct ScratchWant { int slot; size_t bytes; };
 // All of them at these sizes, or HT_ENOMEM and none of them larger than before.  What has to grow is looked up in ht_room first (with
 // `beside` further bytes that the caller is about to take), so that a pass that does not fit frees and allocates nothing, call after call.
+// Where the device refuses memory that the figures promised, a slot may be left smaller than before, or empty: whoever goes on after
+// HT_ENOMEM asks for every slot again before using it.
 int ht_scratch_all(ht_ctx* ctx, const std::vector<ScratchWant>& want, int64_t beside = 0);
 // The slots one after the other, whatever it takes (HT_ENOMEM: some of them).
 int ht_scratch_each(ht_ctx* ctx, const std::vector<ScratchWant>& want);

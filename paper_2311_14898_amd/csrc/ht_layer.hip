@@ -832,16 +832,16 @@ int layer_bwd_direct(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, c
   const int rc = dH_in ? take_by_source(ctx, g, want, dH_in->ld, fwd_parts, HT_S_DACHUNK) : ht_scratch_all(ctx, want);
   if (rc == HT_ENOMEM) return HT_OK;
   HT_TRY(rc);
-  auto get = [&](int slot, size_t bytes, float** p) { return bytes ? ht_scratch(ctx, slot, bytes, (void**)p) : (int)HT_OK; };
-  HT_TRY(get(HT_S_ACHUNK, a_bytes, &a_all));
-  HT_TRY(get(HT_S_DZCHUNK, dz_bytes, &dz_all));
-  HT_TRY(get(HT_S_DACHUNK, da_bytes, &da_all));
-  // (both passes' partial sums before a pointer to them is kept)
   PassPlan plan, again;
   if (!agg_ckpt) HT_TRY(take_plan(R, true, di, a_ld, &again));
   if (dH_in) HT_TRY(take_plan(R, false, di, dH_in->ld, &plan));
-  if (plan.items) partial = (float*)ctx->scratch[HT_S_SPART];
-  else if (dH_in) HT_TRY(get(HT_S_SPART, by_source_parts(g, dH_in->ld), &partial));
+  // Every slot again before a pointer into one is kept: plans let them grow, and one that was refused memory half-way may have left them smaller.
+  if (dH_in && !plan.items) want.push_back({HT_S_SPART, by_source_parts(g, dH_in->ld)});
+  HT_TRY(ht_scratch_each(ctx, want));
+  if (a_bytes) a_all = (float*)ctx->scratch[HT_S_ACHUNK];
+  if (dz_bytes) dz_all = (float*)ctx->scratch[HT_S_DZCHUNK];
+  if (da_bytes) da_all = (float*)ctx->scratch[HT_S_DACHUNK];
+  partial = (float*)ctx->scratch[HT_S_SPART];
   *done = true;
   const float* a_rows = ckpt->ptr;
   if (!agg_ckpt) {   // pure recomputation: aggregate again from h^l
@@ -1265,9 +1265,9 @@ int layer_bwd_update_first(Run& R, const ht_layer_desc* desc, const ht_tensor* H
                part_bytes = at_once ? by_source_parts(g, ld_t) : (size_t)(g->max_bpart * ld_t) * 4;
   want.push_back({HT_S_DZCHUNK, dz_bytes});
   want.push_back({HT_S_SPART, part_bytes});
-  HT_TRY(ht_scratch_each(ctx, want));
   PassPlan plan;
   if (at_once) HT_TRY(take_plan(R, false, dn, ld_t, &plan));
+  HT_TRY(ht_scratch_each(ctx, want));   // (behind the plan: one that was refused memory half-way may have left slots smaller)
   dz_chunk = (float*)ctx->scratch[HT_S_DZCHUNK];
   partial = (float*)ctx->scratch[HT_S_SPART];
   R.changed = true;

@@ -1,0 +1,90 @@
+"""One device allocation of a program is refused, each in turn (HT_REFUSE_ALLOC): the call gets through with less, with the same results, or
+returns HT_ENOMEM and has changed nothing.  Plans and their scratch memory are among what is refused; a slot that a refused plan left smaller must not
+be used at its old size."""
+import pytest
+import torch
+
+from paper_2311_14898_amd import binding as B
+from paper_2311_14898_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+V, DI, DN = 3_000, 72, 40
+ALLOCS = 64          # more than a graph, a call and its plans take
+
+
+@pytest.fixture(scope="module")
+def data():
+    src, dst = inputs.rmat_edges(V, 150_000, 5)
+    gen = torch.Generator().manual_seed(2)
+    rand = lambda d: B.to_matrix(torch.randn(V, d, generator=gen))
+    return dict(src=src.cuda(), dst=dst.cuda(), X=rand(DI), A=rand(DI), dz=rand(DN), kept=rand(DN),
+                W=[w.cuda() for w in inputs.glorot_weights([DI, DN, 8], seed=4)],
+                y=torch.randint(0, 8, (V,), generator=gen).to(torch.int32).cuda())
+
+
+def _call(ctx, g, what, d):
+    """The outputs of the call, and the tensor that a refused call may not have changed."""
+    out = {}
+    order = B.HT_ORDER_UPDATE_FIRST if what.endswith("update_first") else B.HT_ORDER_AGG_FIRST
+    if what.startswith("bwd"):
+        dX, dW = B.alloc_matrix(V, DI), torch.empty(DI, DN, device="cuda")
+        dX.fill_(3.0)
+        keeps = what == "bwd"
+        try:
+            B.ht_layer_bwd(ctx, g, DI, DN, B.HT_ACT_RELU, d["A"] if keeps else d["X"], d["W"][0], d["dz"], dW, dH_in=dX, H_out=d["kept"],
+                           ckpt_kind=B.HT_CKPT_AGG if keeps else B.HT_CKPT_INPUT, order=order)
+        except B.HongtuError:
+            B.ht_sync(ctx)
+            assert (dX == 3.0).all(), "a refused call has added to dH_in"
+            raise
+        out = {"dX": dX[:, :DI], "dW": dW}
+    elif what.startswith("fwd"):
+        H, A = B.alloc_matrix(V, DN), B.alloc_matrix(V, DI)
+        B.ht_layer_fwd(ctx, g, DI, DN, B.HT_ACT_RELU, d["X"], d["W"][0], H, A if what == "fwd" else None, order=order)
+        out = {"H": H[:, :DN]}
+    else:
+        W = [w.clone() for w in d["W"]]
+        try:
+            loss, _ = B.ht_epoch(ctx, g, [DI, DN, 8], W, 1.0, d["X"], d["y"],
+                                 inter=B.HT_INTER_RECOMPUTE if what == "epoch_recompute" else B.HT_INTER_AUTO,
+                                 order=B.HT_ORDER_AUTO if what == "epoch_auto" else B.HT_ORDER_AGG_FIRST)
+        except B.HongtuError:
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b) for a, b in zip(W, d["W"])), "a refused epoch has updated weights"
+            raise
+        out = {"loss": torch.tensor([loss]), "W0": W[0], "W1": W[1]}
+    B.ht_sync(ctx)
+    return {k: v.double().cpu().clone() for k, v in out.items()}
+
+
+@pytest.mark.parametrize("what", ["bwd", "bwd_recompute", "bwd_update_first", "fwd", "fwd_update_first", "epoch", "epoch_auto", "epoch_recompute"])
+def test_each_allocation_refused(data, what, monkeypatch):
+    monkeypatch.setenv("HT_DENSE_WORK", "1")
+    monkeypatch.setenv("HT_FINE_WORK", "1")
+    want, through = None, 0
+    for k in [0] + list(range(1, ALLOCS)):
+        monkeypatch.setenv("HT_REFUSE_ALLOC", str(k))
+        ctx = B.ht_ctx_create(0)
+        g = None
+        try:
+            try:
+                g = B.ht_partition(ctx, V, data["src"], data["dst"], 3)
+                got = _call(ctx, g, what, data)
+            except B.HongtuError as e:
+                assert k > 0 and e.code == B.HT_ENOMEM
+                if g is None:
+                    continue
+                got = _call(ctx, g, what, data)      # and the next call finds the memory
+            again = _call(ctx, g, what, data)
+        finally:
+            if g is not None:
+                B.ht_graph_destroy(g)
+            B.ht_ctx_destroy(ctx)
+        want = want or got
+        through += 1
+        for r in (got, again):
+            for name, w in want.items():
+                # sums of the same terms in other orders: fp32 rounding of a few hundred terms, far below the terms themselves
+                assert (r[name] - w).abs().max() <= 2e-5 * w.abs().max(), (k, name)
+    assert through > ALLOCS // 2
