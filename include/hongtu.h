@@ -296,7 +296,10 @@ typedef struct {
  *   H_out[V_j] = act(a[V_j] W)                              (update,   Eq. 2)
  * H_in [V x d_in], H_out [V x d_out]: device or pinned host.  W: device,
  * row-major [d_in x d_out], dense.  A_ckpt [V x d_in] (nullable): receives the
- * aggregate output as the recomputation checkpoint.
+ * aggregate output as the recomputation checkpoint.  With it the call counts as
+ * one of many over the graph and may run over a plan of it (see "Scratch
+ * memory"), which adds a row's terms in another order: the same values within
+ * fp32 rounding, the same bits from call to call.
  * With desc->order = HT_ORDER_UPDATE_FIRST: t = H_in W for every vertex, then
  * H_out[V_j] = act(s_v * sum s_{u_e} t[u_e]); A_ckpt is not written (there is
  * no aggregate of width d_in); H_in and H_out must be in HBM, else HT_ESHAPE. */
@@ -328,6 +331,9 @@ int ht_layer_fwd_static(ht_ctx *ctx, const ht_graph *g, const ht_layer_desc *des
  *   dW = a^T dz (overwritten) ; da = dz W^T ; dH_in[N_j] += s_u * sum s_v da[v]
  * ckpt: a^l (HT_CKPT_AGG) or h^l (HT_CKPT_INPUT).  H_out (nullable): when
  * given, the ReLU derivative is taken from [H_out > 0] and z is not recomputed.
+ * With HT_CKPT_INPUT and tensors in HBM, a and z are those of an ht_layer_fwd
+ * without A_ckpt, and of ht_layer_fwd_static, bit for bit.  ht_layer_fwd with
+ * A_ckpt may add in another order (see there): after it, pass a^l or H_out.
  * dH_in (nullable: no input gradient wanted) is in/out: ACCUMULATED into, the
  * caller zeroes it.  All vertex tensors: device or pinned host.
  * With desc->order = HT_ORDER_UPDATE_FIRST (all tensors in HBM): ckpt is the

@@ -458,6 +458,8 @@ struct ht_graph {
 int ht_graph_by_source(ht_ctx* ctx, const ht_graph* g, int slot);
 // Bytes that it takes, and that making it takes of the slot (0: it is there).
 void ht_graph_by_source_bytes(const ht_graph* g, int64_t* list, size_t* slot);
+// Partial sums of a by-source list over so many entries, at most.
+int64_t ht_by_source_parts_bound(int64_t entries);
 // Makes g->by_src.mult of a merged graph whose by_src is there (HT_ENOMEM: no memory for it).
 int ht_graph_by_source_mult(ht_ctx* ctx, const ht_graph* g);
 

@@ -112,6 +112,16 @@ struct Run {
   bool dhin_fresh = false;  // dH_in counts as zeros: a host tensor holds them (leaving rows may be stored, not added), a device
                             // tensor holds anything and every row is written or cleared first
   bool planned = false;     // one of many passes over this graph: it may make and use the graph's plan (ht_dense.hip)
+  // An aggregate that no tensor keeps is made again by the backward pass and must be the same there, to the last bit: ReLU's mask and grad W
+  // belong to the activations that the forward pass has returned.  It takes the plan only inside an epoch whose tensors are all in HBM
+  // (again_ok), and the layers in which it did are noted for the backward pass.
+  bool again_ok = false;
+  std::vector<char> again;
+  bool made_planned() const { return (size_t)layer < again.size() && again[layer]; }
+  void note_planned(bool yes) {
+    if ((size_t)layer >= again.size()) again.resize((size_t)layer + 1);
+    again[layer] = yes;
+  }
   bool changed = false;     // the caller's gradients may have been added to: the call cannot be made again
   Run(ht_ctx* c, const ht_graph* gr, ht_stats* s, bool timed) : ctx(c), g(gr), tm(c, c->stream, timed), st(s) {}
 };
@@ -355,10 +365,8 @@ int64_t most_parts(const std::vector<ChunkRange>& ranges) {
   return parts;
 }
 
-// Aggregates of all destinations: out row = vertex.
-int agg_all(Run& R, const float* src, int64_t src_ld, int d, float* out, int64_t out_ld, int relu) {
-  PassPlan plan;
-  HT_TRY(take_plan(R, true, d, out_ld, &plan));
+// Aggregates of all destinations: out row = vertex.  `plan`: what was taken of the graph's plan, with its scratch memory.
+int agg_all(Run& R, const float* src, int64_t src_ld, int d, float* out, int64_t out_ld, int relu, const PassPlan& plan) {
   if (plan.items) return agg_range(R, whole_graph(R.g), src, src_ld, d, out, out_ld, relu, (float*)R.ctx->scratch[HT_S_SPART], plan);
   auto ranges = chunk_ranges(R.g, out_ld * 4, 0, ht_may_spend(R.ctx) ? HT_RANGE_BYTES : 0);
   int64_t parts = most_parts(ranges);
@@ -373,6 +381,17 @@ int agg_all(Run& R, const float* src, int64_t src_ld, int d, float* out, int64_t
   if (parts > 0) HT_TRY(ht_scratch(R.ctx, HT_S_SPART, (size_t)parts * out_ld * 4, (void**)&partial));
   for (const ChunkRange& r : ranges) HT_TRY(agg_range(R, r, src, src_ld, d, out + r.row0 * out_ld, out_ld, relu, partial));
   return HT_OK;
+}
+
+// Scratch memory up to which a backward pass holds dz and grad a of all vertices at once.
+constexpr int64_t HT_DIRECT_BYTES = (int64_t)8 << 30;
+
+// Whether an aggregate of di columns that nothing keeps may take the plan: only where by its sizes the backward pass of the layer holds all
+// rows at once (layer_bwd_direct) and can take the plan too.
+bool again_fits(const Run& R, int di, int dn) {
+  const ht_graph* g = R.g;
+  const int64_t ld_i = ht_row_pitch(di, true), ld_o = ht_row_pitch(dn, true), entries = g->merged ? g->n_unique : g->Ep;
+  return R.again_ok && ht_may_spend(R.ctx) && g->V * (2 * ld_i + ld_o) * 4 <= HT_DIRECT_BYTES && ht_by_source_parts_bound(entries) * ld_i * 4 <= HT_RANGE_BYTES;
 }
 
 // Forward of one layer with everything in HBM and rows read in place.
@@ -397,13 +416,15 @@ int layer_fwd_direct(Run& R, const ht_layer_desc* desc, const ht_tensor* H_in, c
     rows = 0;
     for (const ChunkRange& r : ranges) rows = std::max(rows, r.rows);
   };
-  PassPlan again;
-  HT_TRY(take_plan(R, true, di, a_ld, &again));
-  if (again.items && (A_ckpt || g->V * a_ld * 4 <= HT_RANGE_BYTES)) {
+  PassPlan planned;
+  if (A_ckpt || again_fits(R, di, dn)) HT_TRY(take_plan(R, true, di, a_ld, &planned));
+  R.note_planned(false);
+  if (planned.items) {
     const int rc = ht_scratch_all(ctx, {{HT_S_ACHUNK, A_ckpt ? 0 : (size_t)(g->V * a_ld) * 4}, {HT_S_PACKW, (size_t)ht_packed_w_bytes(di, dn)}});
     if (rc == HT_OK) {
       float* a = A_ckpt ? A_ckpt->ptr : (float*)ctx->scratch[HT_S_ACHUNK];
-      HT_TRY(agg_range(R, whole_graph(g), H_in->ptr, H_in->ld, di, a, a_ld, 0, (float*)ctx->scratch[HT_S_SPART], again));
+      R.note_planned(!A_ckpt);
+      HT_TRY(agg_range(R, whole_graph(g), H_in->ptr, H_in->ld, di, a, a_ld, 0, (float*)ctx->scratch[HT_S_SPART], planned));
       return gemm(a, 0, g->V);
     }
     if (rc != HT_ENOMEM) HT_TRY(rc);
@@ -802,9 +823,6 @@ int take_by_source(ht_ctx* ctx, const ht_graph* g, std::vector<ScratchWant> want
   return rc;
 }
 
-// Scratch memory up to which a backward pass holds dz and grad a of all vertices at once.
-constexpr int64_t HT_DIRECT_BYTES = (int64_t)8 << 30;
-
 // Backward of one layer with everything in HBM, all destinations at once: one launch of every dense kernel, and an
 // aggregation by source over the whole graph, which reads and writes every row of dH_in once (chunk by chunk a row is read and
 // written again for every chunk that names its vertex, and the work items are as many times shorter: 1 M vertices, 20 M edges,
@@ -833,7 +851,10 @@ int layer_bwd_direct(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, c
   if (rc == HT_ENOMEM) return HT_OK;
   HT_TRY(rc);
   PassPlan plan, again;
-  if (!agg_ckpt) HT_TRY(take_plan(R, true, di, a_ld, &again));
+  if (!agg_ckpt && R.made_planned()) {
+    HT_TRY(take_plan(R, true, di, a_ld, &again));
+    if (!again.items) return HT_OK;
+  }
   if (dH_in) HT_TRY(take_plan(R, false, di, dH_in->ld, &plan));
   // Every slot again before a pointer into one is kept: plans let them grow, and one that was refused memory half-way may have left them smaller.
   if (dH_in && !plan.items) want.push_back({HT_S_SPART, by_source_parts(g, dH_in->ld)});
@@ -845,7 +866,7 @@ int layer_bwd_direct(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, c
   *done = true;
   const float* a_rows = ckpt->ptr;
   if (!agg_ckpt) {   // pure recomputation: aggregate again from h^l
-    HT_TRY(agg_all(R, ckpt->ptr, ckpt->ld, di, a_all, a_ld, 0));
+    HT_TRY(agg_all(R, ckpt->ptr, ckpt->ld, di, a_all, a_ld, 0, again));
     a_rows = a_all;
   }
   R.changed = true;
@@ -939,6 +960,8 @@ int layer_bwd_impl(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, con
     HT_TRY(layer_bwd_direct(R, desc, ckpt, W, dH_out, relu ? H_out : nullptr, dH_in, dW, &done));
     if (done) return HT_OK;
   }
+  // (there was memory for the forward pass's plan and is none now: the call is made again, without)
+  if (!agg_ckpt && R.made_planned()) return ht_set_err(ctx, HT_ENOMEM, "backward pass: no memory for the aggregate that the forward pass has not kept");
   if (dH_in && R.dhin_fresh && dH_in->loc == HT_LOC_DEVICE) HT_TRY(ht_fill_zero(ctx, st, dH_in->ptr, (size_t)dH_in->rows * dH_in->ld * 4));
   if (!agg_ckpt || a_host) {
     HT_TRY(ht_scratch(ctx, HT_S_ACHUNK, (size_t)gmax * a_ld * 4 * 2, (void**)&a_stage[0]));
@@ -1220,7 +1243,9 @@ int layer_fwd_update_first(Run& R, const ht_layer_desc* desc, const ht_tensor* H
     R.st->n_gemm += 1;
     R.st->gemm_flops += 2.0 * nr * di * dn;
   }
-  return agg_all(R, T, ld_t, dn, H_out->ptr, H_out->ld, desc->act == HT_ACT_RELU);
+  PassPlan plan;
+  HT_TRY(take_plan(R, true, dn, H_out->ld, &plan));
+  return agg_all(R, T, ld_t, dn, H_out->ptr, H_out->ld, desc->act == HT_ACT_RELU, plan);
 }
 
 int layer_bwd_update_first(Run& R, const ht_layer_desc* desc, const ht_tensor* H_in, const float* W,
@@ -1605,6 +1630,7 @@ static int epoch_impl(ht_ctx* ctx, const ht_graph* g, const ht_model* model, con
   ht_stats local{};
   Run R(ctx, g, &local, stats != nullptr);
   R.planned = true;
+  R.again_ok = recompute && res_h == HT_RES_HBM && res_g == HT_RES_HBM && gather_mode != HT_GATHER_BUFFER;
   if (plan && plan->stats_detail == HT_STATS_AGG_FWD) {
     R.tm.only_lo = &local.t_agg_fwd_layer_ms[0];
     R.tm.only_hi = &local.t_agg_fwd_layer_ms[0] + HT_MAX_LAYERS;

@@ -1872,6 +1872,8 @@ int build_by_source(ht_ctx* ctx, const ht_graph* g, int slot) {
 
 }  // namespace
 
+int64_t ht_by_source_parts_bound(int64_t entries) { return 2 * entries / ItemSwitches().seg_bwd + 1; }   // (a cut row has more than one item's)
+
 void ht_graph_by_source_bytes(const ht_graph* g, int64_t* list, size_t* slot) {
   DevBlock kept, tmp;
   if (!g->by_src.ok) plan_by_source(g, &kept, &tmp);
