@@ -1,7 +1,7 @@
 // Aggregation over the dense core of a graph on the matrix cores (Eq. 2's AGGREGATE and its backward).
 //
 // On a power-law graph the rows with most entries and the columns named most often meet in blocks that are far from sparse (233 k vertices,
-// 78 M distinct pairs: two thirds of them lie in tiles of 256 rows x 64 columns that are at least 5 % full, once both sides are
+// 78 M distinct pairs: two thirds of them lie in tiles of 256 rows x 64 columns that are at least 4 % full, once both sides are
 // sorted by degree).  A gather moves 4 d bytes per entry and is held up by the requests a CU can have in flight; a tile's product
 // costs the same whatever it holds, so above a few per cent of fill it is cheaper on the matrix cores.
 //
@@ -341,26 +341,30 @@ __global__ void __launch_bounds__(TB) k_keep_copy(const uint8_t* __restrict__ ke
 // ---- the products
 
 constexpr float DSCALE = 0x1p24f, DUNSCALE = 0x1p-24f;
-// Rows with larger values (or any that are not finite) go entry by entry: 0 x inf would reach rows that do not name them, and scaled sums could
-// overflow.  Below it 2^20 products of 255 and the scale stay finite.
+// Columns with larger values (or any that are not finite) are zeros to the products and are added entry by entry behind them: 0 x inf would reach
+// rows that do not name them, and scaled sums could overflow.  Below it 2^20 products of 255 and the scale stay finite.
 constexpr float DLARGEST = 0x1p64f;
 
 // s_u h_u of 32 columns as three bf16 each, in the order in which k_dense reads them: [column block][part][16 columns][feature][16].
-// bad[group][feature / 64]: something in it is too large or not finite.  Grid: groups of 32 columns x 64 features.
+// odd[group][feature / 64]: a bit for each column that holds a value too large or not finite among these features; it is packed as zeros.
+// Grid: groups of 32 columns x 64 features (a wave has eight columns, a feature per lane).
 __global__ void __launch_bounds__(TB) k_dense_pack(const float* __restrict__ src, int64_t ld, const float* __restrict__ s, int d, int dp, int n128,
-                                                   const int32_t* __restrict__ cols, __bf16* __restrict__ planes, uint8_t* __restrict__ bad) {
+                                                   const int32_t* __restrict__ cols, __bf16* __restrict__ planes, uint32_t* __restrict__ odd) {
   const int f = blockIdx.y * 64 + (threadIdx.x & 63), oct = threadIdx.x >> 6;
   const bool wide = f < n128 * 128;
   const int f0 = wide ? f & ~127 : n128 * 128, bn = wide ? 128 : 64;
   const int64_t g = blockIdx.x;
   v8bf p[3];
-  int odd = 0;
+  uint32_t out_of_range = 0;
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     const int32_t u = cols[g * 32 + oct * 8 + j];
     float x = 0.f;
     if (u >= 0 && f < d) x = s[u] * src[(int64_t)u * ld + f];
-    odd |= !(fabsf(x) <= DLARGEST);
+    if (__ballot(!(fabsf(x) <= DLARGEST))) {
+      out_of_range |= 1u << j;
+      x = 0.f;
+    }
     x *= DSCALE;
     p[0][j] = (__bf16)x;
     const float r = x - (float)p[0][j];
@@ -370,8 +374,7 @@ __global__ void __launch_bounds__(TB) k_dense_pack(const float* __restrict__ src
   __bf16* out = planes + g * dp * 96 + (int64_t)f0 * 96 + ((oct >> 1) * bn + (f - f0)) * 16 + (oct & 1) * 8;
 #pragma unroll
   for (int q = 0; q < 3; ++q) *reinterpret_cast<v8bf*>(out + q * 2 * bn * 16) = p[q];
-  odd = __syncthreads_or(odd);
-  if (threadIdx.x == 0) bad[g * (dp / 64) + blockIdx.y] = (uint8_t)(odd != 0);
+  if ((threadIdx.x & 63) == 0) reinterpret_cast<uint8_t*>(odd + g * (dp / 64) + blockIdx.y)[oct] = (uint8_t)out_of_range;
 }
 
 struct DenseArgs {
@@ -380,7 +383,7 @@ struct DenseArgs {
   const DenseSeg* segs;
   const int32_t* cols;
   const __bf16* planes;
-  const uint8_t* bad;
+  const uint32_t* odd;
   const float* src;
   const float* s;
   int64_t ld, out_ld;
@@ -417,42 +420,14 @@ __global__ void __launch_bounds__(512) k_dense(DenseArgs a) {
   __syncthreads();
   float* out = a.partial + (int64_t)blockIdx.x * DENSE_ROWS * a.out_ld;
 
-  int odd = 0;
-  for (int t = tid; t < seg.n * 2 * (BN / 64); t += 512) {
-    const int g = t / (BN / 64);
-    odd |= a.bad[((int64_t)cg[g >> 1] * 2 + (g & 1)) * (a.dp / 64) + f0 / 64 + t % (BN / 64)];
-  }
-  if (__syncthreads_or(odd)) {   // entry by entry: a feature per thread, four rows at a time
-    const int f = f0 + tid % BN;
-    if (f >= ((a.d + 3) & ~3)) return;
-    for (int r0 = tid / BN * 4; r0 < DENSE_ROWS; r0 += 512 / BN * 4) {
-      float acc[4] = {0.f, 0.f, 0.f, 0.f};
-      for (int t = 0; t < seg.n; ++t)
-        for (int q = 0; q < 4; ++q) {
-          const uint8_t* c = a.cells + cell_at(seg.tile0 + t, r0, (q >> 1) * 32 + (q & 1) * 8);
-          v4u m[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) m[i] = *reinterpret_cast<const v4u*>(c + i * 16);
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-              uint32_t bits = m[i][x];
-              while (bits) {
-                const int b = (__ffs(bits) - 1) >> 3;
-                const float mult = (float)((bits >> (b * 8)) & 255u);
-                bits &= ~(255u << (b * 8));
-                const int k = (q >> 1) * 32 + (x >> 1) * 16 + (q & 1) * 8 + (x & 1) * 4 + b;
-                const int32_t u = a.cols[(int64_t)cg[t] * DENSE_COLS + k];
-                if (f < a.d) acc[i] = fmaf(mult, a.s[u] * a.src[(int64_t)u * a.ld + f], acc[i]);
-              }
-            }
-        }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) out[(int64_t)(r0 + i) * a.out_ld + f] = acc[i];
-    }
-    return;
-  }
+  // columns of 32 that have to be added entry by entry, for any of these features
+  auto odd_columns = [&](int g) {
+    const uint32_t* p = a.odd + ((int64_t)cg[g >> 1] * 2 + (g & 1)) * (a.dp / 64) + f0 / 64;
+    return BN > 64 ? p[0] | p[BN / 64 - 1] : p[0];
+  };
+  uint32_t some = 0;
+  for (int g = tid; g < seg.n * 2; g += 512) some |= odd_columns(g);
+  const bool any_odd = __syncthreads_or(some != 0);
 
   v16f hi[2][TJ], lo[2][TJ];
 #pragma unroll
@@ -534,6 +509,37 @@ __global__ void __launch_bounds__(512) k_dense(DenseArgs a) {
         out[(int64_t)r * a.out_ld + f] = (hi[i][j][e] + lo[i][j][e]) * DUNSCALE;
       }
   }
+  if (!any_odd) return;
+  // What the products took for zeros: a feature and a quarter (an eighth) of the rows per thread, column by column.  233 k vertices, 115 M edges,
+  // one value of 1e25 in a column that most segments hold: 61 ms an epoch when such a segment left the matrix cores altogether, 12.8 now (12.8
+  // without the value); in one vertex of fifty 66 | 13.1, in one of fifty and in every block of 64 features 189 | 14.8.  Where every value is out of
+  // range (a training run that has diverged) it is 61 ms, and 20.5 over work items alone.
+  __syncthreads();
+  constexpr int PER = DENSE_ROWS / (512 / BN);
+  const int f = f0 + tid % BN, r0 = __builtin_amdgcn_readfirstlane(tid / BN) * PER;
+  if (f >= a.d) return;
+  float acc[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) acc[i] = out[(int64_t)(r0 + i) * a.out_ld + f];
+  for (int g = 0; g < S; ++g) {
+    uint32_t left = __builtin_amdgcn_readfirstlane(odd_columns(g));
+    while (left) {
+      const int k = (g & 1) * 32 + __builtin_ctz(left);
+      left &= left - 1;
+      const int32_t u = a.cols[(int64_t)cg[g >> 1] * DENSE_COLS + k];
+      // (a column that is odd in the other 64 of these features alone was in the products)
+      const bool mine = (a.odd[((int64_t)cg[g >> 1] * 2 + (g & 1)) * (a.dp / 64) + f / 64] >> (k & 31)) & 1;
+      const float x = mine ? a.s[u] * a.src[(int64_t)u * a.ld + f] : 0.f;
+      const uint8_t* c = a.cells + cell_at(seg.tile0 + (g >> 1), r0, k);
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        const uint32_t m = c[(i >> 5) * 1024 + (i & 31) * 16];
+        if (m) acc[i] = fmaf((float)m, x, acc[i]);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < PER; ++i) out[(int64_t)(r0 + i) * a.out_ld + f] = acc[i];
 }
 
 int pad_features(int d, int* n128) {
@@ -742,7 +748,7 @@ int ht_pass_plan(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, PassPlan* 
 size_t ht_dense_bytes(const DenseSide& D, int d) {
   int n128;
   const size_t dp = (size_t)pad_features(d, &n128);
-  return (size_t)D.n_cols / 32 * (dp * 192 + dp / 64) + 256;
+  return (size_t)D.n_cols / 32 * (dp * 192 + dp / 64 * 4) + 256;
 }
 
 // The segments' sums into partial ([segment][256] rows of pitch out_ld).
@@ -753,10 +759,10 @@ int ht_dense_launch(ht_ctx* ctx, hipStream_t st, const DenseSide& D, const float
   void* mem = nullptr;
   HT_TRY(ht_scratch(ctx, HT_S_DENSE, ht_dense_bytes(D, d), &mem));
   __bf16* planes = (__bf16*)mem;
-  uint8_t* bad = (uint8_t*)mem + (size_t)D.n_cols / 32 * dp * 192;
-  k_dense_pack<<<dim3((unsigned)(D.n_cols / 32), dp / 64), TB, 0, st>>>(src, ld, s, d, dp, n128, D.cols.p, planes, bad);
+  uint32_t* odd = (uint32_t*)((char*)mem + (size_t)D.n_cols / 32 * dp * 192);
+  k_dense_pack<<<dim3((unsigned)(D.n_cols / 32), dp / 64), TB, 0, st>>>(src, ld, s, d, dp, n128, D.cols.p, planes, odd);
   HT_LAUNCH_CHECK(ctx);
-  DenseArgs a{D.cells.p, D.tile_cg.p, D.segs.p, D.cols.p, planes, bad, src, s, ld, out_ld, d, dp, 0, partial};
+  DenseArgs a{D.cells.p, D.tile_cg.p, D.segs.p, D.cols.p, planes, odd, src, s, ld, out_ld, d, dp, 0, partial};
   if (n128 > 0) k_dense<128><<<dim3((unsigned)D.n_segs, n128), 512, 0, st>>>(a);
   HT_LAUNCH_CHECK(ctx);
   if (dp > n128 * 128) {
