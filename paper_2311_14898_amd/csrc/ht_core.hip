@@ -252,7 +252,8 @@ int64_t ht_held(const ht_ctx* ctx) {
   int64_t held = 0;
   for (size_t b : ctx->scratch_bytes) held += (int64_t)b;
   for (const ht_graph* g : ctx->graphs)
-    held += (int64_t)((g == ctx->list_owner ? 0 : g->by_src.blk.mem.bytes()) + g->by_src.mult.bytes()) + g->plan_fwd.bytes() + g->plan_bwd.bytes();
+    held += (int64_t)((g == ctx->list_owner ? 0 : g->by_src.blk.mem.bytes()) + g->by_src.mult.bytes()) + g->plan_fwd.bytes() + g->plan_bwd.bytes() +
+            (int64_t)g->ranks.mem.mem.bytes();
   return held;
 }
 
@@ -271,6 +272,7 @@ bool ht_give_back(ht_ctx* ctx) {
     g->by_src = SourceRows();
     g->plan_fwd.release();
     g->plan_bwd.release();
+    g->ranks = DegreeRanks();
   }
   ctx->list_owner = nullptr;
   ht_kept_release(ctx);

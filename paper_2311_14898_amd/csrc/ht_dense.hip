@@ -46,20 +46,53 @@ typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
 // ---- choosing the tiles
 
-// key = (most entries first, vertex)
-__global__ void k_rank_keys(const int64_t* __restrict__ ptr, const int32_t* __restrict__ cnt, int64_t V, uint64_t* __restrict__ keys) {
-  const int64_t v = (int64_t)blockIdx.x * TB + threadIdx.x;
-  if (v >= V) return;
-  const int64_t deg = ptr ? ptr[v + 1] - ptr[v] : (int64_t)cnt[v];
-  const uint64_t k = 0xFFFFFFu - (uint64_t)(deg < 0xFFFFFF ? deg : 0xFFFFFF);
-  keys[v] = (k << 32) | (uint64_t)v;
+// Numbers of entries of both sides' vertices: [0] destinations, [1] sources, by a list's first entries or counted.
+struct Degrees {
+  const int64_t* ptr[2];
+  const int32_t* cnt;      // sources, where ptr[1] is null
+  __device__ __forceinline__ int64_t of(int side, int64_t v) const { return ptr[side] ? ptr[side][v + 1] - ptr[side][v] : (int64_t)cnt[v]; }
+};
+
+// How many vertices of each side have how many entries: bins of an eighth of an octave, vertices and their entries in each.
+constexpr int DEG_BINS = 256;
+__global__ void __launch_bounds__(TB) k_degree_bins(Degrees D, int64_t V, unsigned long long* __restrict__ bins) {
+  __shared__ unsigned long long n[DEG_BINS], sum[DEG_BINS];
+  static_assert(DEG_BINS == TB, "a thread per bin");
+  const int side = blockIdx.y;
+  n[threadIdx.x] = sum[threadIdx.x] = 0;
+  __syncthreads();
+  for (int64_t v = (int64_t)blockIdx.x * TB + threadIdx.x; v < V; v += (int64_t)gridDim.x * TB) {
+    const int64_t d = D.of(side, v);
+    if (d <= 0) continue;
+    const int e = 63 - __clzll((unsigned long long)d);
+    const int b = e * 8 + (int)(e >= 3 ? (d >> (e - 3)) & 7 : (d << (3 - e)) & 7);   // (entries are below 2^31)
+    atomicAdd(&n[b], 1ull);
+    atomicAdd(&sum[b], (unsigned long long)d);
+  }
+  __syncthreads();
+  if (n[threadIdx.x]) {
+    atomicAdd(&bins[(side * 2 + 0) * DEG_BINS + threadIdx.x], n[threadIdx.x]);
+    atomicAdd(&bins[(side * 2 + 1) * DEG_BINS + threadIdx.x], sum[threadIdx.x]);
+  }
 }
-// order[i] = the i-th vertex (-1 behind the last), rank[v] = its place
-__global__ void k_rank(const uint64_t* __restrict__ keys, int64_t V, int64_t n_order, int32_t* __restrict__ order, int32_t* __restrict__ rank) {
+
+// key = (side, most entries first, vertex)
+__global__ void k_rank_keys(Degrees D, int64_t V, uint64_t* __restrict__ keys) {
+  const int64_t v = (int64_t)blockIdx.x * TB + threadIdx.x;
+  const int side = blockIdx.y;
+  if (v >= V) return;
+  const int64_t deg = D.of(side, v);
+  const uint64_t k = 0x7FFFFFu - (uint64_t)(deg < 0x7FFFFF ? deg : 0x7FFFFF);
+  keys[side * V + v] = ((uint64_t)side << 55) | (k << 32) | (uint64_t)v;
+}
+// order[side][i] = the i-th vertex (-1 behind the last), rank[side][v] = its place
+__global__ void k_rank(const uint64_t* __restrict__ keys, int64_t V, int64_t n_order, int32_t* __restrict__ order0, int32_t* __restrict__ order1,
+                       int32_t* __restrict__ rank0, int32_t* __restrict__ rank1) {
   const int64_t i = (int64_t)blockIdx.x * TB + threadIdx.x;
-  const int32_t v = i < V ? (int32_t)(keys[i] & 0xFFFFFFFFu) : -1;
-  if (v >= 0 && rank) rank[v] = (int32_t)i;
-  if (i < n_order) order[i] = v;
+  const int side = blockIdx.y;
+  const int32_t v = i < V ? (int32_t)(keys[side * V + i] & 0xFFFFFFFFu) : -1;
+  if (v >= 0) (side ? rank1 : rank0)[v] = (int32_t)i;
+  if (i < n_order) (side ? order1 : order0)[i] = v;
 }
 
 // The entries of row blocks, in parts of about PART_ENTRIES: part p of block b takes an equal share of them, counted through its rows one
@@ -550,20 +583,13 @@ int pad_features(int d, int* n128) {
 // Scratch memory of the making; it is the products' own slot, which is not in use yet.
 struct DenseTmp {
   DevBlock blk;
-  DevArr<uint64_t> keysA, keysB;
-  DevArr<int32_t> cnt, crank, order_r, order_c, rparts, parts, flag, tile_cg, rest, kcnt;
+  DevArr<int32_t> rparts, parts, flag, tile_cg, rest, kcnt;
   DevArr<int64_t> part0, id, kbase, total;
   DevArr<uint8_t> keep;
   int64_t V, n_ent, n_rb, n_cg, n_parts;
   template <class F>
   void each(F&& f) {
     const int64_t T = n_rb * n_cg, et = ceil_div64(n_ent, ETILE);
-    f(keysA, V);
-    f(keysB, V);
-    f(cnt, V);
-    f(crank, V);
-    f(order_r, n_rb * DENSE_ROWS);
-    f(order_c, n_cg * DENSE_COLS);
     f(rparts, n_rb);
     f(part0, n_rb + 1);
     f(parts, n_parts * n_cg);
@@ -587,35 +613,118 @@ struct DenseTmp {
   }
 };
 
+// Both sides' numbers of entries, into a piece of `tmp` where the sources' have to be counted; `more` words behind it.
+int take_degrees(ht_ctx* ctx, const ht_graph* g, DevBlock* tmp, size_t more, Degrees* out, DevArr<uint64_t>* words) {
+  const bool listed = g->by_src.ok;
+  DevArr<int32_t> cnt;
+  DevArr<int64_t> lists;
+  tmp->add<uint64_t>(more);
+  if (!listed) {
+    tmp->add<int32_t>((size_t)g->V);
+    tmp->add<int64_t>(2 * ((size_t)g->n + 1));
+  }
+  HT_TRY(tmp->alloc_in(ctx, HT_S_DENSE));
+  tmp->take(*words, more);
+  if (!listed) {
+    tmp->take(cnt, (size_t)g->V);
+    tmp->take(lists, 2 * ((size_t)g->n + 1));
+    HT_TRY(ht_graph_source_counts(ctx, g, lists.p, cnt.p));
+  }
+  *out = Degrees{{ht_row_ptr(g, true), listed ? g->by_src.ptr.p : nullptr}, cnt.p};
+  return HT_OK;
+}
+
+// What the graph's dense tiles should hold if entries were spread by their row's and column's numbers of entries alone (r c / E where they have r and
+// c), for either direction.  Against what they do hold: R-MAT graphs of 3 k to 2.45 M vertices 0.89 to 1.01 of it, with communities 1.15, bipartite
+// 0.88.  It takes 60 us where counting the tiles of 1 M vertices, 20 M edges takes 580 for each direction, to find a fifth of what a pass over 64
+// columns needs.
+int estimate_tiles(ht_ctx* ctx, const ht_graph* g) {
+  hipStream_t st = ctx->stream;
+  DevBlock tmp;
+  DevArr<uint64_t> bins;
+  Degrees D;
+  HT_TRY(take_degrees(ctx, g, &tmp, 4 * DEG_BINS, &D, &bins));
+  HT_TRY(ht_fill_zero(ctx, st, bins.p, 4 * DEG_BINS * 8));
+  k_degree_bins<<<dim3((unsigned)std::min<int64_t>(nblk(g->V), 512), 2), TB, 0, st>>>(D, g->V, (unsigned long long*)bins.p);
+  HT_LAUNCH_CHECK(ctx);
+  void* p = nullptr;
+  HT_TRY(ht_host_scratch(ctx, HT_HS_READBACK, 4 * DEG_BINS * 8, &p));
+  HT_HIP(ctx, hipMemcpyAsync(p, bins.p, 4 * DEG_BINS * 8, hipMemcpyDeviceToHost, st));
+  HT_HIP(ctx, hipStreamSynchronize(st));
+  // each side's heaviest vertices, as many as tiles are made of, most entries first
+  struct Bin { double each, all; };
+  std::vector<Bin> side[2];
+  for (int k = 0; k < 2; ++k) {
+    const uint64_t* h = (const uint64_t*)p + k * 2 * DEG_BINS;
+    double left = (double)MAX_RB * DENSE_ROWS;
+    static_assert(MAX_RB * DENSE_ROWS == MAX_CG * DENSE_COLS, "as many rows as columns");
+    for (int b = DEG_BINS - 1; b >= 0 && left > 0; --b) {
+      if (!h[b]) continue;
+      const double n = std::min(left, (double)h[b]), each = (double)h[DEG_BINS + b] / (double)h[b];
+      side[k].push_back(Bin{each, n * each});
+      left -= n;
+    }
+  }
+  const double E = (double)std::max<int64_t>(ht_entries(g), 1), least = (double)DENSE_LEAST * E / (DENSE_ROWS * DENSE_COLS);
+  double sum = 0, cols = 0;
+  size_t c = 0;
+  for (size_t r = side[0].size(); r-- > 0;) {   // (the lightest rows first: they ask for the heaviest columns)
+    for (; c < side[1].size() && side[0][r].each * side[1][c].each >= least; ++c) cols += side[1][c].all;
+    sum += side[0][r].all * cols / E;
+  }
+  g->tile_estimate = (int64_t)sum;
+  return HT_OK;
+}
+
+// g->ranks
+int make_ranks(ht_ctx* ctx, const ht_graph* g) {
+  hipStream_t st = ctx->stream;
+  const int64_t V = g->V, n_order = std::min<int64_t>(ceil_div64(V, DENSE_ROWS), MAX_RB) * DENSE_ROWS;
+  DegreeRanks& K = g->ranks;
+  K = DegreeRanks();
+  for (int k = 0; k < 2; ++k) {
+    K.mem.add<int32_t>((size_t)n_order);
+    K.mem.add<int32_t>((size_t)V);
+  }
+  HT_TRY(K.mem.alloc(ctx));
+  for (int k = 0; k < 2; ++k) {
+    K.mem.take(K.order[k], (size_t)n_order);
+    K.mem.take(K.rank[k], (size_t)V);
+  }
+  DevBlock tmp;
+  DevArr<uint64_t> keys;
+  Degrees D;
+  HT_TRY(take_degrees(ctx, g, &tmp, 4 * (size_t)V, &D, &keys));
+  k_rank_keys<<<dim3(nblk(V), 2), TB, 0, st>>>(D, V, keys.p);
+  HT_LAUNCH_CHECK(ctx);
+  uint64_t* sorted = nullptr;
+  HT_TRY(ht_radix_sort_u64(ctx, keys.p, keys.p + 2 * V, 2 * V, 32, 56, &sorted));
+  k_rank<<<dim3(nblk(std::max(V, n_order)), 2), TB, 0, st>>>(sorted, V, n_order, K.order[0].p, K.order[1].p, K.rank[0].p, K.rank[1].p);
+  HT_LAUNCH_CHECK(ctx);
+  K.ok = true;
+  return HT_OK;
+}
+
 // Counts the graph's dense tiles (D.taken), and makes the dense part where they hold enough for a pass over d columns.
 int build_dense(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, DenseSide& D) {
   hipStream_t st = ctx->stream;
   const int64_t V = g->V, n_ent = ht_entries(g);
-  const int64_t *dst_ptr = ht_row_ptr(g, true), *ptr = ht_row_ptr(g, fwd);
+  const int64_t* ptr = ht_row_ptr(g, fwd);
   const int32_t* idx = fwd ? (g->merged ? g->ucol.p : g->col.p) : g->by_src.idx.p;
   const float* w = !g->merged ? nullptr : fwd ? g->uw_fwd.p : g->by_src.w.p;
   DenseTmp t(V, n_ent);
   // (no more than a quarter of what is there: other passes want memory too)
   const int64_t room = ht_room(ctx);
-  if ((int64_t)t.blk.planned > room / 4 && t.blk.planned > ctx->scratch_bytes[HT_S_DENSE]) return HT_ENOMEM;
+  const size_t sorting = 32 * (size_t)V + 4 * (size_t)V;
+  if ((int64_t)std::max(t.blk.planned, sorting) > room / 4 && std::max(t.blk.planned, sorting) > ctx->scratch_bytes[HT_S_DENSE]) return HT_ENOMEM;
+  if (!g->ranks.ok) HT_TRY(make_ranks(ctx, g));
+  const int32_t *order_r = g->ranks.order[fwd ? 0 : 1].p, *order_c = g->ranks.order[fwd ? 1 : 0].p, *crank = g->ranks.rank[fwd ? 1 : 0].p;
   HT_TRY(t.blk.alloc_in(ctx, HT_S_DENSE));
   t.take();
   const int64_t n_rb = t.n_rb, T = n_rb * t.n_cg;
   const int n_cg = (int)t.n_cg;
-  // both sides by their number of entries
-  for (int side = 0; side < 2; ++side) {
-    const bool rows = side == 0, by_dst = rows == fwd;
-    if (!by_dst) HT_TRY(ht_graph_source_counts(ctx, g, t.cnt.p));
-    k_rank_keys<<<nblk(V), TB, 0, st>>>(by_dst ? dst_ptr : nullptr, t.cnt.p, V, t.keysA.p);
-    HT_LAUNCH_CHECK(ctx);
-    uint64_t* sorted = nullptr;
-    HT_TRY(ht_radix_sort_u64(ctx, t.keysA.p, t.keysB.p, V, 32, 56, &sorted));
-    const int64_t n_order = rows ? n_rb * DENSE_ROWS : t.n_cg * DENSE_COLS;
-    k_rank<<<nblk(std::max(V, n_order)), TB, 0, st>>>(sorted, V, n_order, rows ? t.order_r.p : t.order_c.p, rows ? nullptr : t.crank.p);
-    HT_LAUNCH_CHECK(ctx);
-  }
-  const RowEntries R{ptr, idx, t.order_r.p, t.crank.p, t.part0.p, (int)n_rb};
-  k_dense_parts<<<(unsigned)n_rb, TB, 0, st>>>(ptr, t.order_r.p, t.rparts.p);
+  const RowEntries R{ptr, idx, order_r, crank, t.part0.p, (int)n_rb};
+  k_dense_parts<<<(unsigned)n_rb, TB, 0, st>>>(ptr, order_r, t.rparts.p);
   HT_LAUNCH_CHECK(ctx);
   HT_TRY(ht_scan_i32(ctx, t.rparts.p, t.part0.p, n_rb, true));
   void *p = nullptr, *host_dev = nullptr;
@@ -669,7 +778,7 @@ int build_dense(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, DenseSide& 
   D.tiles.take(D.cols, (size_t)D.n_cols);
   HT_HIP(ctx, hipMemcpyAsync(D.segs.p, segs.data(), segs.size() * sizeof(DenseSeg), hipMemcpyHostToDevice, st));
   HT_HIP(ctx, hipMemcpyAsync(D.seg0.p, seg0.data(), seg0.size() * 4, hipMemcpyHostToDevice, st));
-  HT_HIP(ctx, hipMemcpyAsync(D.cols.p, t.order_c.p, (size_t)D.n_cols * 4, hipMemcpyDeviceToDevice, st));
+  HT_HIP(ctx, hipMemcpyAsync(D.cols.p, order_c, (size_t)D.n_cols * 4, hipMemcpyDeviceToDevice, st));
   HT_HIP(ctx, hipMemcpyAsync(D.tile_cg.p, t.tile_cg.p, (size_t)n_tiles * 4, hipMemcpyDeviceToDevice, st));
   HT_TRY(ht_fill_zero(ctx, st, D.cells.p, cell_bytes));
   HT_TRY(ht_fill_words(ctx, st, D.pos.p, (size_t)V * 4, 0xFFFFFFFFu));
@@ -686,18 +795,24 @@ int build_dense(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, DenseSide& 
   HT_HIP(ctx, hipMemcpyAsync(host, t.kbase.p + et, 8, hipMemcpyDeviceToHost, st));
   HT_HIP(ctx, hipStreamSynchronize(st));
   D.n_rest = host[0];
-  D.rest.add<int32_t>((size_t)std::max<int64_t>(D.n_rest, 1));
-  D.rest.add<float>((size_t)std::max<int64_t>(D.n_rest, 1));
+  const size_t n_rest = (size_t)std::max<int64_t>(D.n_rest, 1);
+  const size_t items = (size_t)ht_row_items_bound(V, D.n_rest, REST_SEG), cuts = (size_t)ht_row_cuts_bound(D.n_rest, REST_SEG, n_rb * DENSE_ROWS);
+  D.rest.add<int32_t>(n_rest);
+  D.rest.add<float>(n_rest);
   D.rest.add<int64_t>((size_t)V + 1);
+  D.rest.add<WorkItem>(items);
+  D.rest.add<CutRow>(cuts);
   HT_TRY(D.rest.alloc(ctx));
-  D.rest.take(D.idx, (size_t)std::max<int64_t>(D.n_rest, 1));
-  D.rest.take(D.w, (size_t)std::max<int64_t>(D.n_rest, 1));
+  D.rest.take(D.idx, n_rest);
+  D.rest.take(D.w, n_rest);
   DevArr<int64_t> rptr;
   D.rest.take(rptr, (size_t)V + 1);
+  D.rest.take(D.items.items, items);
+  D.rest.take(D.items.cuts, cuts);
   k_keep_copy<<<(unsigned)et, TB, 0, st>>>(t.keep.p, n_ent, t.kbase.p, idx, w, g->s.p, D.idx.p, D.w.p);
   HT_LAUNCH_CHECK(ctx);
   HT_TRY(ht_scan_i32(ctx, t.rest.p, rptr.p, V, true));
-  HT_TRY(ht_graph_row_items(ctx, V, rptr.p, D.n_rest, D.idx.p, D.pos.p, REST_SEG, HT_S_DENSE, &D.items));
+  HT_TRY(ht_graph_row_items(ctx, V, rptr.p, D.n_rest, D.idx.p, D.pos.p, REST_SEG, HT_S_DENSE, nullptr, &D.items));
   D.ok = true;
   return HT_OK;
 }
@@ -718,13 +833,23 @@ int ht_pass_plan(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, PassPlan* 
     if (rc != HT_ENOMEM) return rc;
     (void)hipStreamSynchronize(ctx->stream);
     what = std::remove_reference_t<decltype(what)>();
+    g->ranks = DegreeRanks();
     (void)ht_scratch_release(ctx, HT_S_DENSE);
     what.refused = ht_room(ctx);
     return HT_OK;
   };
   if (ctx->dense && n_ent * d >= ctx->dense_work) {
     DenseSide& D = P.dense;
-    if (!D.ok && (D.taken < 0 || D.taken * d >= ctx->dense_work)) HT_TRY(make(D, [&] { return build_dense(ctx, g, fwd, d, D); }));
+    // (half as much again as the estimate: see there)
+    auto enough = [&] { return D.taken >= 0 ? D.taken * d >= ctx->dense_work : g->tile_estimate < 0 || g->tile_estimate * 3 / 2 * d >= ctx->dense_work; };
+    if (!D.ok && enough())
+      HT_TRY(make(D, [&]() -> int {
+        if (g->tile_estimate < 0) HT_TRY(estimate_tiles(ctx, g));
+        if (!enough()) return HT_OK;
+        HT_TRY(build_dense(ctx, g, fwd, d, D));
+        if (g->plan_fwd.dense.taken >= 0 && g->plan_bwd.dense.taken >= 0) g->ranks = DegreeRanks();
+        return HT_OK;
+      }));
     if (D.ok && D.taken * d >= ctx->dense_work) {
       out->items = &D.items;
       out->dense = &D;
@@ -736,7 +861,7 @@ int ht_pass_plan(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, PassPlan* 
     if (!F.ok)
       HT_TRY(make(F, [&]() -> int {
         const int32_t* idx = fwd ? (g->merged ? g->ucol.p : g->col.p) : g->by_src.idx.p;
-        HT_TRY(ht_graph_row_items(ctx, g->V, ht_row_ptr(g, fwd), n_ent, idx, nullptr, FINE_SEG, HT_S_DENSE, &F.items));
+        HT_TRY(ht_graph_row_items(ctx, g->V, ht_row_ptr(g, fwd), n_ent, idx, nullptr, FINE_SEG, HT_S_DENSE, &F.mem, &F.items));
         F.ok = true;
         return HT_OK;
       }));

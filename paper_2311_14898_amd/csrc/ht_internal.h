@@ -352,6 +352,7 @@ struct SourceRows {
 struct ShortItems {
   bool ok = false;
   int64_t refused = -1;          // there was no memory for it with this much room
+  DevBlock mem;
   GraphItems items;              // rows = destinations, or sources
 };
 // Tiles of DENSE_ROWS x DENSE_COLS multiplicities, rows and columns in order of their number of entries, and work items over the entries in
@@ -374,21 +375,28 @@ struct DenseSide {
   DevArr<int32_t> cols;          // [n_cols] vertex of each column (-1: none)
   DevArr<int32_t> idx;           // entries in no tile ...
   DevArr<float> w;               // ... and their weights
-  GraphItems items;              // rows in row blocks are all cut rows
+  GraphItems items;              // rows in row blocks are all cut rows (in `rest`)
   int64_t n_tiles = 0, n_segs = 0, n_cols = 0, n_rest = 0;
 };
 struct GraphPlan {
   ShortItems fine;
   DenseSide dense;
   int64_t bytes() const {
-    return (int64_t)(fine.items.items.bytes() + fine.items.cuts.bytes() + dense.tiles.mem.bytes() + dense.rest.mem.bytes() +
-                     dense.items.items.bytes() + dense.items.cuts.bytes());
+    return (int64_t)(fine.mem.mem.bytes() + dense.tiles.mem.bytes() + dense.rest.mem.bytes());
   }
   void release() {               // what was counted stays known
     const int64_t taken = dense.taken;
     *this = GraphPlan();
     dense.taken = taken;
   }
+};
+// Vertices in order of their number of entries, as destinations [0] and as sources [1]: both directions' tiles are made of the two.  Made with
+// the first direction's, given back with the second's.
+struct DegreeRanks {
+  bool ok = false;
+  DevBlock mem;
+  DevArr<int32_t> order[2];      // the first vertices, in row blocks of DENSE_ROWS (-1 behind the last)
+  DevArr<int32_t> rank[2];       // [V]
 };
 // What a pass takes of it.
 struct PassPlan {
@@ -444,6 +452,8 @@ struct ht_graph {
   DevArr<int64_t> d_dense_groups;
   mutable SourceRows by_src;
   mutable GraphPlan plan_fwd, plan_bwd;
+  mutable DegreeRanks ranks;
+  mutable int64_t tile_estimate = -1;   // entries that dense tiles should hold, by the vertices' numbers of entries alone (-1: not looked at)
   DevBlock blk_csc, blk_pairs, blk_chunks;   // the allocations behind the CSC, the distinct-pair arrays, and the per-chunk arenas with the work items
   int64_t v_ori = 0, v_ru = 0, v_load = 0;  // v_load: rows actually loaded per pass with this buffer
   int64_t max_nsrc = 0, max_ndst = 0, max_nnz = 0, max_fpart = 0, max_bpart = 0;
@@ -463,12 +473,16 @@ int64_t ht_by_source_parts_bound(int64_t entries);
 // Makes g->by_src.mult of a merged graph whose by_src is there (HT_ENOMEM: no memory for it).
 int ht_graph_by_source_mult(ht_ctx* ctx, const ht_graph* g);
 
-// Distinct entries (entries, where duplicates are not merged) of every source, into cnt[V].
-int ht_graph_source_counts(ht_ctx* ctx, const ht_graph* g, int32_t* cnt);
+// Distinct entries (entries, where duplicates are not merged) of every source, into cnt[V].  lists: scratch memory of 2 (g->n + 1) words.
+int ht_graph_source_counts(ht_ctx* ctx, const ht_graph* g, int64_t* lists, int32_t* cnt);
 // Work items over rows 0 .. V - 1 with entries ptr[r] .. ptr[r + 1] of idx (values below V); rows with pos[r] >= 0 (pos may be null) become cut
-// rows whatever their length.  The slot is overwritten on the way.
+// rows whatever their length.  The slot is overwritten on the way.  out's arrays are taken out of `mem`, or are there already, of the sizes that
+// ht_row_items_bound and ht_row_cuts_bound say (null).
 int ht_graph_row_items(ht_ctx* ctx, int64_t V, const int64_t* ptr, int64_t n_ent, const int32_t* idx, const int32_t* pos, int seg, int slot,
-                       GraphItems* out);
+                       DevBlock* mem, GraphItems* out);
+inline int64_t ht_row_items_bound(int64_t rows, int64_t entries, int seg) { return rows + entries / seg + 1; }
+// (rows that are cut because they are longer than an item, and `forced` ones)
+inline int64_t ht_row_cuts_bound(int64_t entries, int seg, int64_t forced) { return entries / seg + 1 + forced; }
 // Rows of a direction's list: first entries of its rows.
 inline const int64_t* ht_row_ptr(const ht_graph* g, bool fwd) { return !fwd ? g->by_src.ptr.p : g->merged ? g->uindptr.p : g->indptr.p; }
 inline int64_t ht_entries(const ht_graph* g) { return g->merged ? g->n_unique : g->Ep; }

@@ -946,8 +946,8 @@ struct ItemBuild {
 };
 
 // Items a list of `rows` rows with `entries` entries can make: ceil(len / seg) per row, at least one.
-inline int64_t item_bound(int64_t rows, int64_t entries, int seg) { return rows + entries / seg + 1; }
-inline int64_t cut_bound(int64_t entries, int seg) { return entries / seg + 1; }
+inline int64_t item_bound(int64_t rows, int64_t entries, int seg) { return ht_row_items_bound(rows, entries, seg); }
+inline int64_t cut_bound(int64_t entries, int seg) { return ht_row_cuts_bound(entries, seg, 0); }
 
 // h_tot (pinned, 3 words): the totals' prefix sums, valid once the stream is synchronised
 int count_items(ht_ctx* ctx, const ItemBuild& b, int64_t* h_tot) {
@@ -1909,10 +1909,8 @@ int ht_graph_by_source_mult(ht_ctx* ctx, const ht_graph* g) {
   return HT_OK;
 }
 
-int ht_graph_source_counts(ht_ctx* ctx, const ht_graph* g, int32_t* cnt) {
+int ht_graph_source_counts(ht_ctx* ctx, const ht_graph* g, int64_t* lists, int32_t* cnt) {
   const size_t n1 = (size_t)g->n + 1;
-  DevArr<int64_t> lists;
-  HT_TRY(lists.alloc(ctx, 2 * n1));
   void* p = nullptr;
   HT_TRY(ht_host_scratch(ctx, HT_HS_READBACK, 2 * n1 * 8, &p));
   int64_t* hl = (int64_t*)p;
@@ -1923,19 +1921,19 @@ int ht_graph_source_counts(ht_ctx* ctx, const ht_graph* g, int32_t* cnt) {
   }
   hl[g->n] = g->v_ori;
   hl[n1 + g->n] = g->merged ? g->n_unique : g->Ep;
-  HT_HIP(ctx, hipMemcpyAsync(lists.p, hl, 2 * n1 * 8, hipMemcpyHostToDevice, ctx->stream));
+  HT_HIP(ctx, hipMemcpyAsync(lists, hl, 2 * n1 * 8, hipMemcpyHostToDevice, ctx->stream));
   HT_TRY(ht_fill_zero(ctx, ctx->stream, cnt, (size_t)g->V * 4));
   if (g->v_ori > 0) {
-    const RowSet arena{g->merged ? g->usptr.p : g->sptr.p, lists.p, lists.p + n1, g->n};
+    const RowSet arena{g->merged ? g->usptr.p : g->sptr.p, lists, lists + n1, g->n};
     k_src_counts<<<nblk(g->v_ori), TB, 0, ctx->stream>>>(g->nbr.p, arena, g->v_ori, cnt);
     HT_LAUNCH_CHECK(ctx);
   }
-  HT_HIP(ctx, hipStreamSynchronize(ctx->stream));   // (the lists go with this call)
+  HT_HIP(ctx, hipStreamSynchronize(ctx->stream));   // (the pinned copy of the lists is used again)
   return HT_OK;
 }
 
 int ht_graph_row_items(ht_ctx* ctx, int64_t V, const int64_t* ptr, int64_t n_ent, const int32_t* idx, const int32_t* pos, int seg, int slot,
-                       GraphItems* out) {
+                       DevBlock* mem, GraphItems* out) {
   const ItemSwitches sw;
   ItemBuild b;
   b.nrows = V;
@@ -1978,8 +1976,16 @@ int ht_graph_row_items(ht_ctx* ctx, int64_t V, const int64_t* ptr, int64_t n_ent
   b.rows = RowSet{ptr, first.p, nullptr, 1, pos};
   HT_TRY(count_items(ctx, b, h));
   HT_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  HT_TRY(out->items.alloc(ctx, (size_t)std::max<int64_t>(h[0], 1)));
-  HT_TRY(out->cuts.alloc(ctx, (size_t)std::max<int64_t>(h[2] - h[1], 1)));
+  const size_t ni = (size_t)std::max<int64_t>(h[0], 1), nc = (size_t)std::max<int64_t>(h[2] - h[1], 1);
+  if (mem) {
+    mem->add<WorkItem>(ni);
+    mem->add<CutRow>(nc);
+    HT_TRY(mem->alloc(ctx));
+    mem->take(out->items, ni);
+    mem->take(out->cuts, nc);
+  } else if (out->items.n < ni || out->cuts.n < nc) {
+    return ht_set_err(ctx, HT_ESTATE, "work items: %zu and %zu cut rows, more than was planned for", ni, nc);
+  }
   return fill_items(ctx, b, h, made.p, (size_t)bound, keysA.p, keysB.p, (size_t)bound, sw.order);
 }
 
@@ -1988,7 +1994,7 @@ int64_t ht_graph::hbm_bytes() const {
               sptr.bytes() + sdst.bytes() + slot.bytes() + gslot.bytes() + reuse.bytes() + load.bytes() +
               load_slot.bytes() + leave.bytes() + leave_slot.bytes() + uindptr.bytes() + ucol.bytes() +
               ucol_slot.bytes() + uw_fwd.bytes() + umult.bytes() + usdst.bytes() + uw_bwd.bytes() + umult_bwd.bytes() + usptr.bytes();
-  b += (int64_t)(by_src.blk.mem.bytes() + by_src.mult.bytes()) + plan_fwd.bytes() + plan_bwd.bytes();
+  b += (int64_t)(by_src.blk.mem.bytes() + by_src.mult.bytes()) + plan_fwd.bytes() + plan_bwd.bytes() + (int64_t)ranks.mem.mem.bytes();
   for (const GraphItems* i : {&fwd_items, &bwd_items}) b += i->n_items * (int64_t)sizeof(WorkItem) + i->n_cut * (int64_t)sizeof(CutRow);
   return b;
 }
