@@ -131,8 +131,8 @@ struct Part {
     }
     rb = lo;
     const int64_t p = blockIdx.x - R.part0[rb], P = R.part0[rb + 1] - R.part0[rb];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int32_t row = R.order[(int64_t)rb * DENSE_ROWS + tid];
+    const int tid = threadIdx.x, lane = tid & 63;      // (threads beyond the rows have none)
+    const int32_t row = tid < DENSE_ROWS ? R.order[(int64_t)rb * DENSE_ROWS + tid] : -1;
     const int64_t e0 = row >= 0 ? R.ptr[row] : 0, len = row >= 0 ? R.ptr[row + 1] - e0 : 0;
     int64_t inc = len;
 #pragma unroll
@@ -140,7 +140,7 @@ struct Part {
       const int64_t y = __shfl_up(inc, o, 64);
       if (lane >= o) inc += y;
     }
-    if (lane == 63) s_wave[tid >> 6] = inc;
+    if (lane == 63 && tid < DENSE_ROWS) s_wave[tid >> 6] = inc;
     __syncthreads();
     int64_t before = 0, tot = 0;
 #pragma unroll
@@ -148,8 +148,10 @@ struct Part {
       if (w < (tid >> 6)) before += s_wave[w];
       tot += s_wave[w];
     }
-    s_at[tid] = before + inc - len;
-    s_first[tid] = e0;
+    if (tid < DENSE_ROWS) {
+      s_at[tid] = before + inc - len;
+      s_first[tid] = e0;
+    }
     if (tid == 0) s_at[DENSE_ROWS] = tot;
     at = s_at;
     first = s_first;
@@ -255,32 +257,64 @@ __device__ __forceinline__ int64_t cell_at(int64_t tile, int row, int col) {
 }
 
 // The entries of the taken tiles go into their cells; keep[e] = 0 for them, and rest[row] loses them.
-__global__ void __launch_bounds__(TB) k_dense_fill(RowEntries R, const float* __restrict__ w, const float* __restrict__ mult,
-                                                   const float* __restrict__ s, int n_cg,
+//
+// A row's entries are in order of their columns' numbers, not ranks, so one after the other they go to tiles all over the row block, a byte each: a
+// line of cells was written, and left the caches, once for each of the four or five entries that a part has for it (116 k vertices, 57 M edges, 25 M
+// entries in tiles: 664 us forward, 746 backward).  The part's entries are therefore put in order of their tiles in LDS first, at the places that the
+// counts give, and a tile's go out together.
+constexpr int FILL_TB = 1024, FILL_LANES = 16;
+__global__ void __launch_bounds__(FILL_TB) k_dense_fill(RowEntries R, const float* __restrict__ w, const float* __restrict__ mult,
+                                                   const float* __restrict__ s, int n_cg, const int32_t* __restrict__ cnt,
                                                    const int32_t* __restrict__ tile_of, uint8_t* __restrict__ cells, uint8_t* __restrict__ keep,
                                                    int32_t* __restrict__ rest, int32_t* __restrict__ pos) {
-  __shared__ int32_t tab[MAX_CG], gone[DENSE_ROWS];
+  __shared__ uint32_t item[PART_ENTRIES];      // row in the block, column in the tile << 8, multiplicity << 14
+  __shared__ int32_t tab[MAX_CG], next[MAX_CG], gone[DENSE_ROWS], waves[FILL_TB / 64];
+  __shared__ uint16_t from[MAX_CG];
   Part P;
   if (!P.open(R)) return;
+  const int tid = threadIdx.x;
   const int32_t* mine = tile_of + (int64_t)P.rb * n_cg;
-  int any = 0;
-  for (int c = threadIdx.x; c < n_cg; c += TB) {
-    tab[c] = mine[c];
-    any |= tab[c] >= 0;
+  const int32_t* held = cnt + (int64_t)blockIdx.x * n_cg;
+  // places: the part's entries of the taken tiles before each tile's
+  constexpr int PER = MAX_CG / FILL_TB;
+  int32_t n[PER], sum = 0;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int c = tid * PER + q;
+    const int32_t t = c < n_cg ? mine[c] : -1;
+    tab[c] = t;
+    n[q] = t >= 0 ? held[c] : 0;
+    sum += n[q];
   }
-  gone[threadIdx.x] = 0;
-  if (!__syncthreads_or(any)) return;
+  if (tid < DENSE_ROWS) gone[tid] = 0;
+  if (!__syncthreads_or(sum)) return;
+  int32_t inc = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int32_t y = __shfl_up(inc, o, 64);
+    if ((tid & 63) >= o) inc += y;
+  }
+  if ((tid & 63) == 63) waves[tid >> 6] = inc;
+  __syncthreads();
+  int32_t place = inc - sum;
+  for (int k = 0; k < (tid >> 6); ++k) place += waves[k];
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    next[tid * PER + q] = place;
+    from[tid * PER + q] = (uint16_t)place;
+    place += n[q];
+  }
+  __syncthreads();
   const int32_t limit = n_cg * DENSE_COLS;
   // (four entries a thread at a time: each is a chain of loads)
-  for (int64_t f = P.f0 + threadIdx.x; f < P.f1; f += 4 * TB) {
+  for (int64_t f = P.f0 + tid; f < P.f1; f += 4 * FILL_TB) {
     int r[4];
     int64_t e[4];
-    int32_t u[4], c[4], t[4];
+    int32_t u[4], c[4];
     float m[4];
-    bool first[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int64_t x = f + q * TB;
+      const int64_t x = f + q * FILL_TB;
       r[q] = x < P.f1 ? P.row_of(x) : 0;
       e[q] = x < P.f1 ? P.first[r[q]] + (x - P.at[r[q]]) : -1;
       u[q] = e[q] >= 0 ? R.idx[e[q]] : 0;
@@ -294,34 +328,43 @@ __global__ void __launch_bounds__(TB) k_dense_fill(RowEntries R, const float* __
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      t[q] = c[q] < limit ? tab[c[q] / DENSE_COLS] : -1;
-      first[q] = true;
-      if (!w && t[q] >= 0) {   // a run of equal entries; one of more than 255 stays as it is
+      const int32_t t = c[q] < limit ? tab[c[q] / DENSE_COLS] : -1;
+      bool first = true;
+      if (!w && t >= 0) {   // a run of equal entries; one of more than 255 stays as it is
         const int64_t e0 = P.first[r[q]], e1 = e0 + (P.at[r[q] + 1] - P.at[r[q]]);
         int64_t a = e[q], z = e[q] + 1;
         while (a > e0 && e[q] - a < 256 && R.idx[a - 1] == u[q]) --a;
         while (z < e1 && z - e[q] < 256 && R.idx[z] == u[q]) ++z;
         m[q] = (float)(z - a);
-        first[q] = a == e[q];
+        first = a == e[q];
       }
-      const bool take = t[q] >= 0 && m[q] >= 1.f && m[q] <= 255.f;
+      const bool take = t >= 0 && m[q] >= 1.f && m[q] <= 255.f;
       if (take) {
-        if (first[q]) cells[cell_at(t[q], r[q], c[q] % DENSE_COLS)] = (uint8_t)m[q];
+        if (first) item[atomicAdd(&next[c[q] / DENSE_COLS], 1)] = (uint32_t)r[q] | (uint32_t)(c[q] % DENSE_COLS) << 8 | (uint32_t)m[q] << 14;
         keep[e[q]] = 0;
       }
       // (a wave's entries are mostly one row's)
       const int r0 = __builtin_amdgcn_readfirstlane(r[q]);
       const uint64_t same = __ballot(take && r[q] == r0);
-      if ((int)(threadIdx.x & 63) == __builtin_ctzll(same | (1ull << 63)) && same) atomicAdd(&gone[r0], __popcll(same));
+      if ((tid & 63) == __builtin_ctzll(same | (1ull << 63)) && same) atomicAdd(&gone[r0], __popcll(same));
       if (take && r[q] != r0) atomicAdd(&gone[r[q]], 1);
     }
   }
   __syncthreads();
-  const int32_t row = R.order[(int64_t)P.rb * DENSE_ROWS + threadIdx.x];
+  for (int c = tid / FILL_LANES; c < n_cg; c += FILL_TB / FILL_LANES) {
+    const int32_t t = tab[c];
+    if (t < 0) continue;
+    for (int k = from[c] + tid % FILL_LANES; k < next[c]; k += FILL_LANES) {
+      const uint32_t x = item[k];
+      cells[cell_at(t, x & 255, (x >> 8) & 63)] = (uint8_t)(x >> 14);
+    }
+  }
+  const int32_t row = tid < DENSE_ROWS ? R.order[(int64_t)P.rb * DENSE_ROWS + tid] : -1;
   if (row < 0) return;
-  if (gone[threadIdx.x] > 0) atomicSub(&rest[row], gone[threadIdx.x]);
-  pos[row] = (int32_t)(P.rb * DENSE_ROWS + threadIdx.x);
+  if (gone[tid] > 0) atomicSub(&rest[row], gone[tid]);
+  pos[row] = (int32_t)(P.rb * DENSE_ROWS + tid);
 }
+static_assert(DENSE_ROWS == 256 && DENSE_COLS == 64 && PART_ENTRIES <= 65535, "row, column and place in an item");
 
 // entries kept of every ETILE of them
 __global__ void __launch_bounds__(TB) k_keep_count(const uint8_t* __restrict__ keep, int64_t n, int32_t* __restrict__ cnt) {
@@ -785,7 +828,7 @@ int build_dense(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, DenseSide& 
   HT_TRY(ht_fill_words(ctx, st, t.keep.p, ((size_t)n_ent + 3) & ~(size_t)3, 0x01010101u));
   k_row_lengths<<<nblk(V), TB, 0, st>>>(ptr, V, t.rest.p);
   HT_LAUNCH_CHECK(ctx);
-  k_dense_fill<<<(unsigned)t.n_parts, TB, 0, st>>>(R, w, fwd && g->merged ? g->umult.p : nullptr, g->s.p, n_cg, t.flag.p, D.cells.p, t.keep.p, t.rest.p, D.pos.p);
+  k_dense_fill<<<(unsigned)t.n_parts, FILL_TB, 0, st>>>(R, w, fwd && g->merged ? g->umult.p : nullptr, g->s.p, n_cg, t.parts.p, t.flag.p, D.cells.p, t.keep.p, t.rest.p, D.pos.p);
   HT_LAUNCH_CHECK(ctx);
   // what is left, in the same order
   const int64_t et = ceil_div64(n_ent, ETILE);
