@@ -94,6 +94,12 @@ int ht_sync(ht_ctx *ctx);
  * A call that is refused memory, by the cap or by the device, gives all of
  * that back and is made again chunk by chunk, so no call fails for memory that
  * an earlier one or a faster pass holds.
+ *
+ * Without a cap, blocks of device memory that calls and destroyed graphs free
+ * (not scratch memory) are kept for the context's next allocations: up to
+ * 4 GiB a context and 12 GiB on a device.  Another context gets them when its
+ * allocation fails; for the caller's own allocator, any call of
+ * ht_ctx_set_hbm_budget, with 0 too, gives back what the context keeps.
  */
 int ht_ctx_set_hbm_budget(ht_ctx *ctx, int64_t bytes);
 /* Number of ht_epoch calls on this context that ran as one HIP graph launch

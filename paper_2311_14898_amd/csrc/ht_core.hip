@@ -63,14 +63,100 @@ int ht_set_err(ht_ctx* ctx, int code, const char* fmt, ...) {
 }
 
 // An allocation or a release costs 50 to 200 us of the host, a release some 3 ms per GiB, and makes the device idle; a graph that is
-// seen once takes a dozen blocks.  Freed blocks are therefore kept, up to HT_KEPT_BYTES per context, and handed out again where they fit well;
-// work on the context's stream is in order, and what runs beside it is waited for by that stream before a call ends.  Nothing is kept under a
-// byte budget, and everything is given back where memory runs out.  Partition and one layer of a graph seen once: 10 k vertices 567 -> 502 us,
+// seen once takes a dozen blocks.  Blocks that a context frees are therefore kept and handed out again, to the same context, where they fit well:
+// work on a context's stream is in order, and what runs beside it is waited for by that stream before a call ends.  A context keeps up to
+// HT_KEPT_BYTES, those of a device together up to HT_KEPT_ALL.  Nothing is kept under a byte budget, nor of scratch slots (a caller may have recorded a pass that works in
+// one); a graph's end keeps nothing where less than an eighth of the device is free; and whatever any context keeps is given back where an
+// allocation of another fails, by ht_ctx_set_hbm_budget and with the context.  Partition and one layer of a graph seen once: 10 k vertices 567 -> 502 us,
 // 2.45 M vertices, 62 M edges 14.8 -> 13.6 ms.
+namespace {
+struct KeptBlock {
+  void* p;
+  size_t bytes;
+  ht_ctx* ctx;
+};
+std::mutex g_kept_lock;              // contexts may be used by several threads, one each
+std::vector<KeptBlock>& g_kept = *new std::vector<KeptBlock>();       // oldest first (contexts may be destroyed as late as they like)
+
+// Takes the blocks that `which` says off the list and releases them.
+template <class F>
+void kept_drop(F&& which) {
+  std::vector<KeptBlock> drop;
+  {
+    std::lock_guard<std::mutex> hold(g_kept_lock);
+    const auto keep = std::stable_partition(g_kept.begin(), g_kept.end(), [&](const KeptBlock& k) { return !which(k); });
+    drop.assign(keep, g_kept.end());
+    g_kept.erase(keep, g_kept.end());
+  }
+  if (drop.empty()) return;
+  (void)hipDeviceSynchronize();      // (a context's own work may still be on them)
+  for (const KeptBlock& k : drop) (void)hipFree(k.p);
+}
+size_t kept_bytes(int device) {
+  std::lock_guard<std::mutex> hold(g_kept_lock);
+  size_t sum = 0;
+  for (const KeptBlock& k : g_kept) sum += k.ctx->device == device ? k.bytes : 0;
+  return sum;
+}
+// The smallest of the context's blocks that fits `bytes` well.
+bool kept_take(ht_ctx* ctx, size_t bytes, KeptBlock* out) {
+  std::lock_guard<std::mutex> hold(g_kept_lock);
+  auto best = g_kept.end();
+  for (auto k = g_kept.begin(); k != g_kept.end(); ++k)
+    if (k->ctx == ctx && k->bytes >= bytes && k->bytes <= bytes + bytes / 4 + 65536 && (best == g_kept.end() || k->bytes < best->bytes)) best = k;
+  if (best == g_kept.end()) return false;
+  *out = *best;
+  g_kept.erase(best);
+  return true;
+}
+// false: the caller releases it.  The context's oldest blocks make room for it.
+bool kept_put(ht_ctx* ctx, void* p, size_t bytes) {
+  std::vector<KeptBlock> drop;
+  bool put = true;
+  {
+    std::lock_guard<std::mutex> hold(g_kept_lock);
+    for (;;) {
+      size_t all = bytes, own = bytes, blocks = 0;
+      auto oldest = g_kept.end();
+      for (auto k = g_kept.begin(); k != g_kept.end(); ++k) {
+        if (k->ctx->device != ctx->device) continue;
+        all += k->bytes;
+        if (k->ctx != ctx) continue;
+        own += k->bytes;
+        ++blocks;
+        if (oldest == g_kept.end()) oldest = k;
+      }
+      if (own <= HT_KEPT_BYTES && all <= HT_KEPT_ALL && blocks < HT_KEPT_BLOCKS) break;
+      if (oldest == g_kept.end()) {
+        put = false;
+        break;
+      }
+      drop.push_back(*oldest);
+      g_kept.erase(oldest);
+    }
+    if (put) g_kept.push_back(KeptBlock{p, bytes, ctx});
+  }
+  for (const KeptBlock& k : drop) (void)hipFree(k.p);
+  return put;
+}
+}  // namespace
+
 void ht_kept_release(ht_ctx* ctx) {
-  for (const KeptBlock& k : ctx->kept) (void)hipFree(k.p);
-  ctx->kept.clear();
-  ctx->kept_bytes = 0;
+  kept_drop([&](const KeptBlock& k) { return k.ctx == ctx; });
+}
+
+void ht_kept_trim(ht_ctx* ctx) {
+  if (kept_bytes(ctx->device) < ((size_t)64 << 20)) return;
+  size_t free_b = 0, total_b = 0;
+  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+    (void)hipGetLastError();
+    return;
+  }
+  if (ctx->device_bytes > 0) {
+    total_b = (size_t)ctx->device_bytes;
+    free_b = (size_t)std::max<int64_t>(0, ctx->device_bytes - ctx->hbm_used);
+  }
+  if (free_b < total_b / 8) ht_kept_release(ctx);
 }
 
 int ht_dev_alloc(ht_ctx* ctx, void** out, size_t bytes) {
@@ -81,24 +167,18 @@ int ht_dev_alloc(ht_ctx* ctx, void** out, size_t bytes) {
     return ht_set_err(ctx, HT_ENOMEM, "HBM budget exceeded: %lld in use + %zu requested > %lld",
                       (long long)ctx->hbm_used, bytes, (long long)ctx->hbm_budget);
   if (ctx->refuse_alloc > 0 && --ctx->refuse_alloc == 0) return ht_set_err(ctx, HT_ENOMEM, "allocation of %zu bytes refused (HT_REFUSE_ALLOC)", bytes);
-  size_t best = ctx->kept.size();
-  for (size_t k = 0; k < ctx->kept.size(); ++k) {
-    const size_t have = ctx->kept[k].bytes;
-    if (have >= bytes && have <= bytes + bytes / 4 + 65536 && (best == ctx->kept.size() || have < ctx->kept[best].bytes)) best = k;
-  }
-  if (best < ctx->kept.size()) {
-    const KeptBlock k = ctx->kept[best];
-    ctx->kept.erase(ctx->kept.begin() + (std::ptrdiff_t)best);
-    ctx->kept_bytes -= k.bytes;
+  KeptBlock k;
+  if (kept_take(ctx, bytes, &k)) {
     if (k.bytes != bytes) ctx->larger[k.p] = k.bytes;
     *out = k.p;
     ctx->hbm_used += (int64_t)bytes;
     return HT_OK;
   }
-  hipError_t e = hipMalloc(out, bytes);
-  if (e != hipSuccess && !ctx->kept.empty()) {
+  const bool refuse = ctx->refuse_alloc < 0 && ++ctx->refuse_alloc == 0;
+  hipError_t e = refuse ? hipErrorOutOfMemory : hipMalloc(out, bytes);
+  if (e != hipSuccess && kept_bytes(ctx->device) > 0) {
     (void)hipGetLastError();
-    ht_kept_release(ctx);
+    kept_drop([&](const KeptBlock& b) { return b.ctx->device == ctx->device; });
     e = hipMalloc(out, bytes);
   }
   if (e != hipSuccess) {
@@ -110,7 +190,7 @@ int ht_dev_alloc(ht_ctx* ctx, void** out, size_t bytes) {
   return HT_OK;
 }
 
-void ht_dev_free(ht_ctx* ctx, void* p, size_t bytes) {
+static void dev_free(ht_ctx* ctx, void* p, size_t bytes, bool keep) {
   if (!p) return;
   if (!ctx || g_orphans) {      // (the context is gone)
     (void)hipFree(p);
@@ -123,18 +203,9 @@ void ht_dev_free(ht_ctx* ctx, void* p, size_t bytes) {
     have = it->second;
     ctx->larger.erase(it);
   }
-  if (ctx->hbm_budget > 0 || have > HT_KEPT_BYTES) {
-    (void)hipFree(p);
-    return;
-  }
-  while (ctx->kept_bytes + have > HT_KEPT_BYTES || ctx->kept.size() >= HT_KEPT_BLOCKS) {   // the oldest go first
-    (void)hipFree(ctx->kept.front().p);
-    ctx->kept_bytes -= ctx->kept.front().bytes;
-    ctx->kept.erase(ctx->kept.begin());
-  }
-  ctx->kept.push_back(KeptBlock{p, have});
-  ctx->kept_bytes += have;
+  if (!keep || ctx->hbm_budget > 0 || have > HT_KEPT_BYTES || !kept_put(ctx, p, have)) (void)hipFree(p);
 }
+void ht_dev_free(ht_ctx* ctx, void* p, size_t bytes) { dev_free(ctx, p, bytes, true); }
 
 static size_t ht_scratch_size(size_t bytes) { return bytes + bytes / 8 + 256; }   // of a slot that is asked for so many
 
@@ -163,7 +234,7 @@ int ht_scratch(ht_ctx* ctx, int slot, size_t bytes, void** out) {
     if (ctx->scratch[slot]) {
       if (slot == HT_S_TNPART) HT_TRY(ht_flush_products(ctx, ctx->stream));   // (sums that were left to the end of the epoch are in there)
       HT_HIP(ctx, hipStreamSynchronize(ctx->stream));
-      ht_dev_free(ctx, ctx->scratch[slot], ctx->scratch_bytes[slot]);
+      dev_free(ctx, ctx->scratch[slot], ctx->scratch_bytes[slot], false);
       ctx->scratch[slot] = nullptr;
       ctx->scratch_bytes[slot] = 0;
     }
@@ -181,7 +252,7 @@ int ht_scratch_release(ht_ctx* ctx, int slot) {
   if (ctx->static_mode || !ctx->scratch[slot]) return HT_OK;
   if (slot == HT_S_TNPART) HT_TRY(ht_flush_products(ctx, ctx->stream));
   HT_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  ht_dev_free(ctx, ctx->scratch[slot], ctx->scratch_bytes[slot]);
+  dev_free(ctx, ctx->scratch[slot], ctx->scratch_bytes[slot], false);
   ctx->scratch[slot] = nullptr;
   ctx->scratch_bytes[slot] = 0;
   ++ctx->scratch_gen;
@@ -191,7 +262,7 @@ int ht_scratch_release(ht_ctx* ctx, int slot) {
 int64_t ht_device_free(ht_ctx* ctx) {
   int64_t room = INT64_MAX;
   size_t free_b = 0, total_b = 0;
-  if (hipMemGetInfo(&free_b, &total_b) == hipSuccess) room = (int64_t)(free_b + ctx->kept_bytes);
+  if (hipMemGetInfo(&free_b, &total_b) == hipSuccess) room = (int64_t)(free_b + kept_bytes(ctx->device));
   else (void)hipGetLastError();
   if (ctx->device_bytes > 0) room = std::min(room, std::max<int64_t>(0, ctx->device_bytes - ctx->hbm_used));
   return room;
@@ -405,7 +476,7 @@ int ht_ctx_destroy(ht_ctx* ctx) {
   ht_epoch_ws_free(ctx);
   for (ht_graph* g : ctx->graphs) g->ctx = nullptr;
   for (int i = 0; i < HT_N_SCRATCH; ++i)
-    if (ctx->scratch[i]) ht_dev_free(ctx, ctx->scratch[i], ctx->scratch_bytes[i]);
+    if (ctx->scratch[i]) dev_free(ctx, ctx->scratch[i], ctx->scratch_bytes[i], false);
   ht_kept_release(ctx);
   for (int i = 0; i < HT_N_HS; ++i)
     if (ctx->hscratch[i]) (void)hipHostFree(ctx->hscratch[i]);
@@ -426,7 +497,8 @@ int64_t ht_ctx_graph_launches(const ht_ctx* ctx) { return ctx ? ctx->graph_launc
 
 int ht_ctx_set_hbm_budget(ht_ctx* ctx, int64_t bytes) {
   if (!ctx || bytes < 0) return HT_EINVAL;
-  if (bytes > 0) ht_kept_release(ctx);
+  (void)hipSetDevice(ctx->device);
+  ht_kept_release(ctx);
   ctx->hbm_budget = bytes;
   ctx->tight_room = -1;
   ctx->gat_keep_limit = 0;

@@ -43,12 +43,8 @@ struct PendingTn {
   float* column[2];
 };
 
-// Device blocks that a context keeps for its next allocations.
-struct KeptBlock {
-  void* p;
-  size_t bytes;
-};
-constexpr size_t HT_KEPT_BYTES = (size_t)4 << 30, HT_KEPT_BLOCKS = 64;
+// Device blocks that a context keeps for its next allocations, and all of a device's contexts together.
+constexpr size_t HT_KEPT_BYTES = (size_t)4 << 30, HT_KEPT_BLOCKS = 64, HT_KEPT_ALL = (size_t)12 << 30;
 
 struct ht_ctx {
   int device = 0;
@@ -58,8 +54,6 @@ struct ht_ctx {
   std::string err;
   int64_t hbm_budget = 0;  // 0 = unlimited
   int64_t hbm_used = 0;
-  std::vector<KeptBlock> kept;                 // oldest first
-  size_t kept_bytes = 0;
   std::unordered_map<void*, size_t> larger;    // blocks in use that hold more than was asked for
   std::vector<hipEvent_t> ev_pool;
   size_t ev_next = 0;
@@ -103,7 +97,7 @@ struct ht_ctx {
   int64_t tight_room = -1;     // room that was left after the last such call (-1: none since memory was plentiful)
   size_t gat_keep_limit = 0;   // a GAT epoch that kept this many bytes between its passes ran out of memory (0: none did) ...
   int64_t gat_keep_room = 0;   // ... and had this much room without them
-  int64_t refuse_alloc = 0;    // HT_REFUSE_ALLOC=k: the context's k-th device allocation is refused, as if the device had no memory (tests)
+  int64_t refuse_alloc = 0;    // HT_REFUSE_ALLOC=k: the context's k-th allocation is refused; -k: its k-th hipMalloc fails (tests)
   int64_t device_bytes = 0;    // HT_DEVICE_BYTES: plan as if the device had no more memory than this for the context (0: as it reports)
   bool tn_defer = false;       // inside an epoch: products that allow it leave their slices (slot HT_S_TNPART, from tn_used bytes on) to ht_step
   size_t tn_used = 0;
@@ -141,7 +135,8 @@ void ht_static_end(ht_ctx* ctx);
 // Device allocation with budget accounting.
 int ht_dev_alloc(ht_ctx* ctx, void** out, size_t bytes);
 void ht_dev_free(ht_ctx* ctx, void* p, size_t bytes);
-void ht_kept_release(ht_ctx* ctx);
+void ht_kept_release(ht_ctx* ctx);  // gives back the blocks that the context keeps ...
+void ht_kept_trim(ht_ctx* ctx);     // ... where the device is nearly full
 void ht_free_orphan(ht_graph* g);   // a graph whose context is gone
 // Grow-only scratch slot (kept on the context).
 int ht_scratch(ht_ctx* ctx, int slot, size_t bytes, void** out);

@@ -2047,16 +2047,15 @@ int ht_graph_destroy(ht_graph* g) {
     ht_free_orphan(g);
     return HT_OK;
   }
-  {
-    (void)hipStreamSynchronize(g->ctx->stream);
-    std::vector<ht_graph*>& all = g->ctx->graphs;
-    all.erase(std::remove(all.begin(), all.end(), g), all.end());
-    if (g->ctx->list_owner == g) {
-      g->ctx->list_owner = nullptr;
-      if (g->ctx->scratch_bytes[HT_S_LIST] > LIST_KEPT_BYTES) (void)ht_scratch_release(g->ctx, HT_S_LIST);
-    }
+  ht_ctx* ctx = g->ctx;
+  (void)hipStreamSynchronize(ctx->stream);
+  ctx->graphs.erase(std::remove(ctx->graphs.begin(), ctx->graphs.end(), g), ctx->graphs.end());
+  if (ctx->list_owner == g) {
+    ctx->list_owner = nullptr;
+    if (ctx->scratch_bytes[HT_S_LIST] > LIST_KEPT_BYTES) (void)ht_scratch_release(ctx, HT_S_LIST);
   }
   delete g;
+  ht_kept_trim(ctx);
   return HT_OK;
 }
 
