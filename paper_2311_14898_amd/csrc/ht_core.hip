@@ -440,7 +440,12 @@ int ht_ctx_create(ht_ctx** out, int device, void* hip_stream) {
   if (const char* v = getenv("HT_DENSE")) c->dense = atoi(v);
   if (const char* v = getenv("HT_FINE")) c->fine = atoi(v);
   if (const char* v = getenv("HT_DENSE_WORK")) c->dense_work = std::max<int64_t>(1, atoll(v));
-  if (const char* v = getenv("HT_FINE_WORK")) c->fine_work = std::max<int64_t>(1, atoll(v));
+  if (const char* v = getenv("HT_FINE_WORK")) {
+    c->fine_work = std::max<int64_t>(1, atoll(v));
+    c->fine_rows = 0;
+  }
+  if (const char* v = getenv("HT_FINE_ROWS")) c->fine_rows = atoll(v);
+  if (const char* v = getenv("HT_UNIT_SMALL")) c->unit_small = std::min<int64_t>(atoll(v), c->unit_small);
   if (const char* v = getenv("HT_FUSE_UPDATE")) c->fuse_update = atoi(v);
   if (const char* v = getenv("HT_AGG_PHASES")) c->agg_phases = atoi(v) > 1 ? atoi(v) : 1;
   if (const char* v = getenv("HT_REFUSE_ALLOC")) c->refuse_alloc = atoll(v);

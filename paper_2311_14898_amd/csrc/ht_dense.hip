@@ -34,9 +34,6 @@ constexpr int ETILE = 2048;
 // 468 us (all with other kernels beside them).
 constexpr int32_t DENSE_LEAST = 650;
 constexpr int SEG_BLOCKS = 512;                 // segments that a graph's tiles are cut into at least
-// (smaller than that the rows stay in the L2s whatever the order: 100 k rows of 40 columns, 10 M entries 388 -> 409 us a layer with short
-// items; 60 k of 129, 3 M entries 441 -> 413, 300 k of 64, 6 M entries 643 -> 588, 1 M of 128, 30 M entries 4.4 -> 3.6 ms)
-constexpr int64_t FINE_ROWS = (int64_t)24 << 20;
 constexpr int REST_SEG = 48, FINE_SEG = 64;     // entries of a work item
 inline unsigned nblk(int64_t n, int tb = TB) { return (unsigned)((n + tb - 1) / tb); }
 
@@ -899,7 +896,7 @@ int ht_pass_plan(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, PassPlan* 
       return HT_OK;
     }
   }
-  if (ctx->fine && n_ent * d >= ctx->fine_work && (ctx->fine_work < HT_FINE_WORK || g->V * d * 4 >= FINE_ROWS)) {
+  if (ctx->fine && n_ent * d >= ctx->fine_work && g->V * d * 4 >= ctx->fine_rows) {
     ShortItems& F = P.fine;
     if (!F.ok)
       HT_TRY(make(F, [&]() -> int {

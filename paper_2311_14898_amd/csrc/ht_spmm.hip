@@ -461,7 +461,7 @@ int ht_spmm_launch(ht_ctx* ctx, hipStream_t st, const SpmmArgs& a0) {
     if (a.tm && a.t_items) a.tm->begin(a.t_items);
     if (a.units && unit_shape(a, nvec)) {
       const int lpr = nvec <= 8 ? 8 : UNIT_LANES, nu = (nvec + lpr - 1) / lpr, G = 64 / lpr;
-      const bool small = a.src_rows * a.src_ld < ((int64_t)1 << 30);
+      const bool small = a.src_rows * a.src_ld < ctx->unit_small;
       for (int u0 = 0; u0 < nu && rc == HT_OK;) {
         int S = 8;
         while (S > nu - u0) S /= 2;

@@ -1,0 +1,135 @@
+"""Both sides of the rules that small graphs do not reach by themselves: rows wider than a column block over dense tiles, rows that column units
+address in 64 bits, the least rows for short items, and the end of a GAT epoch whose attention vectors share memory."""
+import pytest
+import torch
+
+from paper_2311_14898_amd import binding as B
+from paper_2311_14898_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def _passes(V, src, dst, d, n=2, passes=("fwd", "bwd")):
+    """(aggregate, backward aggregate, bytes that the graph holds before and after)"""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d)
+    X, dz = B.alloc_matrix(V, d), B.alloc_matrix(V, d)
+    X[:, :d], dz[:, :d] = (torch.randn(V, d, generator=gen, device="cuda") for _ in range(2))
+    W = torch.eye(d, device="cuda")
+    ctx = B.ht_ctx_create(0)
+    g = B.ht_partition(ctx, V, src.cuda(), dst.cuda(), n)
+    try:
+        H, A, dX, dW = B.alloc_matrix(V, d), B.alloc_matrix(V, d), B.alloc_matrix(V, d), torch.empty(d, d, device="cuda")
+        held = [B.ht_graph_info_get(g).hbm_bytes]
+        B.ht_layer_fwd(ctx, g, d, d, B.HT_ACT_NONE, X, W, H, A)
+        B.ht_sync(ctx)
+        held.append(B.ht_graph_info_get(g).hbm_bytes)
+        if "bwd" in passes:
+            dX.zero_()
+            B.ht_layer_bwd(ctx, g, d, d, B.HT_ACT_NONE, A, W, dz, dW, dH_in=dX)
+            B.ht_sync(ctx)
+        return X[:, :d], dz[:, :d], A[:, :d], dX[:, :d], held
+    finally:
+        B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("d", [1024, 1030, 1100, 2050])
+def test_rows_wider_than_a_column_block(d, monkeypatch):
+    monkeypatch.setenv("HT_DENSE_WORK", "1")
+    V = 700
+    src, dst = inputs.rmat_edges(V, 40 * V, 3)
+    X, dz, A, dX, held = _passes(V, src, dst, d)
+    assert held[1] > held[0], "the pass was meant to plan"
+    loop = torch.arange(V)
+    u, v = torch.cat([src.long(), loop]).cuda(), torch.cat([dst.long(), loop]).cuda()
+    s = torch.bincount(v, minlength=V).double().rsqrt()
+    w = (s[u] * s[v])[:, None]
+    for got, a, b, Z in ((A, u, v, X), (dX, v, u, dz)):
+        want, mag = (torch.zeros(V, d, dtype=torch.float64, device="cuda").index_add_(0, b, w * Y.double()[a]) for Y in (Z, Z.abs()))
+        # (dX goes through a product with the unit matrix, exact)
+        assert ((got.double() - want).abs() <= 16 * 2.0 ** -24 * mag).all()
+
+
+@pytest.mark.parametrize("V,E,d", [(300_007, 3_000_000, 64), (600_011, 3_000_000, 32), (140_003, 2_000_000, 128)])
+def test_rows_addressed_in_64_bits(V, E, d, monkeypatch):
+    """The same sums at either width of the offsets; rows of 4 GiB and more need the wider ones."""
+    monkeypatch.setenv("HT_DENSE", "0")
+    monkeypatch.setenv("HT_FINE_WORK", "1")
+    src, dst = inputs.rmat_edges(V, E, 3, device="cuda")
+    _, _, A, dX, held = _passes(V, src, dst, d)
+    assert held[1] > held[0]
+    monkeypatch.setenv("HT_UNIT_SMALL", "0")
+    _, _, A2, dX2, _ = _passes(V, src, dst, d)
+    assert torch.equal(A, A2) and torch.equal(dX, dX2)
+    assert A.isfinite().all() and float(A.abs().sum()) > 0
+
+
+def test_rows_beyond_four_gib():
+    """... and rows that really are that large, against the sums of an equal graph's passes that do not plan."""
+    V, E, d = 8_600_000, 9_000_000, 128
+    src, dst = inputs.rmat_edges(V, E, 3, device="cuda")
+    ctx = B.ht_ctx_create(0)
+    g = B.ht_partition(ctx, V, src, dst, 4)
+    try:
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(1)
+        X, A, H, H2 = B.alloc_matrix(V, d), B.alloc_matrix(V, d), B.alloc_matrix(V, 4), B.alloc_matrix(V, 4)
+        X.normal_(generator=gen)
+        W = torch.randn(d, 4, generator=gen, device="cuda")
+        base = B.ht_graph_info_get(g).hbm_bytes
+        B.ht_layer_fwd(ctx, g, d, 4, B.HT_ACT_NONE, X, W, H, A)
+        B.ht_layer_fwd(ctx, g, d, 4, B.HT_ACT_NONE, X, W, H2)
+        B.ht_sync(ctx)
+        assert B.ht_graph_info_get(g).hbm_bytes > base, "the pass was meant to plan"
+        # (rows of up to a few thousand terms, then a product over 128: orders of the same fp32 sums)
+        assert float((H - H2).norm() / H2.norm()) <= 1e-6
+        assert float((H - H2).abs().max()) <= 1e-5 * float(H2.abs().max())
+    finally:
+        B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)
+
+
+def test_least_rows_for_short_items(monkeypatch):
+    V, d = 3_000, 40
+    src, dst = inputs.rmat_edges(V, 100_000, 3)
+    monkeypatch.setenv("HT_DENSE", "0")
+    monkeypatch.setenv("HT_FINE_WORK", "1")
+    outs = []
+    for rows, planned in ((V * d * 4, True), (V * d * 4 + 1, False)):
+        monkeypatch.setenv("HT_FINE_ROWS", str(rows))
+        _, _, A, _, held = _passes(V, src, dst, d, passes=("fwd",))
+        assert (held[1] > held[0]) == planned
+        outs.append(A)
+    assert float((outs[0] - outs[1]).norm() / outs[1].norm()) <= 1e-6
+
+
+def test_gat_parameters_that_share_memory():
+    """Two layers with one pair of attention vectors: both layers' steps reach them."""
+    V, d = 2_000, 24
+    src, dst = inputs.rmat_edges(V, 20_000, 5)
+    gen = torch.Generator().manual_seed(1)
+    X, y = B.to_matrix(torch.randn(V, d, generator=gen)), torch.randint(0, d, (V,), generator=gen).to(torch.int32).cuda()
+    W0 = inputs.glorot_weights([d, d, d], seed=4)
+    a0 = [torch.randn(d, generator=gen) / 5 for _ in range(2)]
+    ctx = B.ht_ctx_create(0)
+    g = B.ht_partition(ctx, V, src.cuda(), dst.cuda(), 2)
+    try:
+        def epoch(a_dst, a_src):
+            W = [w.clone().cuda() for w in W0]
+            loss, _ = B.ht_gat_epoch(ctx, g, [d, d, d], W, a_dst, a_src, 0.5, X, y)
+            return loss, W
+        apart = [[a.clone().cuda() for _ in range(2)] for a in a0]
+        shared = [a.clone().cuda() for a in a0]
+        loss1, W1 = epoch(*apart)
+        loss2, W2 = epoch([shared[0]] * 2, [shared[1]] * 2)
+        assert loss1 == loss2 and all(torch.equal(a, b) for a, b in zip(W1, W2))
+        for a, two, one in zip(a0, apart, shared):
+            steps = [t.cpu().double() - a.double() for t in two]
+            assert all(float(s.abs().max()) > 0 for s in steps)
+            want = a.double() + steps[0] + steps[1]
+            # one rounding for each of the three updates that are compared
+            assert ((one.cpu().double() - want).abs() <= 4 * 2.0 ** -24 * (a.double().abs() + want.abs())).all()
+    finally:
+        B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)

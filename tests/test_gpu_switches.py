@@ -26,11 +26,12 @@ SETTINGS = [
     {"HT_ITEM_ORDER": "0"},
     {"HT_SEG_FWD": "64", "HT_SEG_BWD": "256"},
     {"HT_LINK_MEMCPY": "1"},
-    {"HT_LINK_MEMCPY": "1", "HT_NO_LINK_FENCE": "1"},
     {"HT_LINK_MEMCPY": "2"},
     {"HT_LINK_MEMCPY": "3"},
-    {"HT_NO_LINK_FENCE": "1"},
-    {"HT_LINK_BLOCKS": "16", "HT_GATHER_BLOCKS": "512"},
+    {"HT_LINK_BLOCKS": "64", "HT_GATHER_BLOCKS": "512"},
+    {"HT_LINK_BLOCKS": "1", "HT_GATHER_BLOCKS": "1"},
+    {"HT_DENSE_WORK": "1", "HT_FINE_WORK": "1"},
+    {"HT_DENSE": "0", "HT_FINE_WORK": "1"},
 ]
 
 
