@@ -91,6 +91,15 @@ int ht_sync(ht_ctx *ctx);
  * sums, and on a graph from its first backward pass on its entries grouped by
  * source (4 or 8 bytes each; up to 1 GiB of a destroyed graph's stay for the
  * next one); ht_gat_epoch up to 16 GiB more for rows kept between its passes.
+ *
+ * Plans: passes over a graph that are meant to be many (ht_epoch, ht_layer_bwd,
+ * ht_layer_fwd with A_ckpt; tensors in HBM) order its entries anew where that
+ * pays, at the first such pass in each direction, and keep that with the graph:
+ * blocks of 16 KiB for 650 entries or more, 8 bytes for each other entry and
+ * 16 for each 48 or 64 of them and for each vertex, in no more than a quarter of
+ * the memory that is free when it is made; such a pass keeps up to 8 GiB of partial
+ * sums and 6 bytes for each value of the rows that those blocks name.
+ *
  * A call that is refused memory, by the cap or by the device, gives all of
  * that back and is made again chunk by chunk, so no call fails for memory that
  * an earlier one or a faster pass holds.
@@ -313,8 +322,10 @@ int ht_layer_fwd(ht_ctx *ctx, const ht_graph *g, const ht_layer_desc *desc, cons
                  const float *W, ht_tensor *H_out, ht_tensor *A_ckpt, ht_stats *stats);
 
 /* ht_layer_fwd for callers that cannot allocate device memory: code under HIP
- * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
- * result as ht_layer_fwd (the same kernels in the same order), restricted to
+ * graph capture, tight serving loops, harnesses that forbid hipMalloc.  It has
+ * the bits of ht_layer_fwd without A_ckpt (the same kernels in the same order),
+ * and of ht_layer_fwd with it unless that runs over a plan (from 2 * 10^8
+ * entries x d_in on): the same values then within fp32 rounding.  Restricted to
  * the all-in-HBM path: H_in, H_out and A_ckpt (required) in device memory,
  * aggregate-first order, rows read in place (no neighbour buffer), no stats.
  * Its two scratch buffers (the tile-padded copy of W and the partial sums of

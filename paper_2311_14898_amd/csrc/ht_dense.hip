@@ -802,7 +802,8 @@ int build_dense(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, DenseSide& 
   D.n_segs = (int64_t)segs.size();
   D.n_cols = host[n_rb + 2] * DENSE_COLS;
   const size_t cell_bytes = (size_t)n_tiles * DENSE_ROWS * DENSE_COLS;
-  if ((int64_t)cell_bytes + 8 * (n_ent - taken) > room / 4) return HT_ENOMEM;
+  const int64_t left = n_ent - taken;
+  if ((int64_t)cell_bytes + 8 * left + 16 * ht_row_items_bound(V, left, REST_SEG) > room / 4) return HT_ENOMEM;
   D.tiles.add<uint8_t>(cell_bytes);
   D.tiles.add<int32_t>((size_t)n_tiles);
   D.tiles.add<DenseSeg>(segs.size());

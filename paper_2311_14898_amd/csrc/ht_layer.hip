@@ -1447,8 +1447,8 @@ int ht_layer_fwd(ht_ctx* ctx, const ht_graph* g, const ht_layer_desc* desc, cons
   });
 }
 
-// ht_layer_fwd for callers that cannot allocate: the same kernels in the same order, with the two scratch buffers of
-// the all-in-HBM path (the packed copy of W, the partial sums of cut rows) taken from the device's static array.
+// ht_layer_fwd for callers that cannot allocate: the kernels of a forward that keeps no aggregate, in the same order (no plan is taken), with the two
+// scratch buffers of the all-in-HBM path (the packed copy of W, the partial sums of cut rows) taken from the device's static array.
 int ht_layer_fwd_static(ht_ctx* ctx, const ht_graph* g, const ht_layer_desc* desc, const ht_tensor* H_in, const float* W,
                         ht_tensor* H_out, ht_tensor* A_ckpt) {
   if (!ctx) return HT_EINVAL;
