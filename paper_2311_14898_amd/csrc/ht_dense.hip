@@ -860,7 +860,31 @@ int build_dense(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, DenseSide& 
 
 }  // namespace
 
-int ht_pass_plan(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, PassPlan* out) {
+namespace {
+
+// Whether a pass over short items of the graph's own entries is the faster one, by direction, width, rows and entries.  Measured over 18 R-MAT graphs of 10 k to
+// 2 M vertices, 10 to 400 entries a row, and 19 widths of 16 to 602 columns; time over the graph's own items / over short ones:
+//   column units   forward   1.02 .. 1.74; 8 lanes (32 columns and less) over long rows that are hardly more than the caches hold 0.94
+//                  backward  up to 64 columns 1.01 .. 1.39 below 64 entries a row, 0.93 .. 0.98 above; wider ones in (nearly) whole units 0.99 .. 1.16, with
+//                            fewer than 16 entries a row 0.94 .. 0.98 from three units on; with half a unit at the end (96, 160 columns) 0.89 .. 1.06
+//   slab kernel    forward   from 64 columns on 1.01 .. 1.38, 0.95 .. 1.04 below 16 entries a row; narrower 0.83 .. 1.00
+//                  backward  0.84 .. 1.03; 129 to 256 columns below 48 entries a row 1.00 .. 1.04
+// (Items of the graph itself have 256 entries forward and 128 backward, so that there is less to gain backward.)
+bool short_items_pay(const ht_graph* g, bool fwd, int32_t d, int64_t src_ld) {
+  const int64_t V = g->V, n_ent = ht_entries(g);
+  const int nvec = (std::min(d, 1024) + 3) / 4, n_units = (nvec + UNIT_LANES - 1) / UNIT_LANES;
+  if (ht_unit_shape(V, src_ld, nvec, true)) {
+    if (fwd) return nvec > 8 || n_ent <= 64 * V || V * src_ld * 4 >= ((int64_t)128 << 20);
+    if (n_units == 1) return n_ent <= 64 * V;
+    return nvec * 10 >= n_units * UNIT_LANES * 9 && (n_units == 2 || n_ent >= 16 * V);
+  }
+  if (fwd) return d >= 64 && n_ent >= 16 * V;
+  return d > 128 && d <= 256 && n_ent <= 48 * V;
+}
+
+}  // namespace
+
+int ht_pass_plan(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, int64_t src_ld, PassPlan* out) {
   *out = PassPlan();
   GraphPlan& P = fwd ? g->plan_fwd : g->plan_bwd;
   const int64_t n_ent = ht_entries(g);
@@ -897,7 +921,7 @@ int ht_pass_plan(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, PassPlan* 
       return HT_OK;
     }
   }
-  if (ctx->fine && n_ent * d >= ctx->fine_work && g->V * d * 4 >= ctx->fine_rows) {
+  if (ctx->fine && n_ent * d >= ctx->fine_work && g->V * d * 4 >= ctx->fine_rows && (ctx->fine_rows == 0 || short_items_pay(g, fwd, d, src_ld))) {
     ShortItems& F = P.fine;
     if (!F.ok)
       HT_TRY(make(F, [&]() -> int {

@@ -22,8 +22,7 @@ constexpr int HT_SEG = 256;
 // (170) 195 | 195, 1e5, 10 M, 128 (510) 675 | 696; 3e4, 12 M, 300 (1,200) 1,096 | 824, 1e5, 40 M, 128 (2,200) 1,581 | 1,162.  A plan takes a
 // millisecond or two to make, so it is left where a pass would gain less than some 100 us; short items (0.2 ms) where it would gain less than 5.
 constexpr int64_t HT_DENSE_WORK = 1000000000, HT_FINE_WORK = 200000000;
-// ... and bytes of rows: fewer stay in the L2s whatever the order (100 k rows of 40 columns, 10 M entries 388 -> 409 us a layer with short
-// items; 60 k of 129, 3 M entries 441 -> 413, 300 k of 64, 6 M entries 643 -> 588, 1 M of 128, 30 M entries 4.4 -> 3.6 ms).
+// ... and bytes of rows for short items: fewer stay in the L2s whatever the order (which shapes gain beyond that: short_items_pay).
 constexpr int64_t HT_FINE_ROWS = (int64_t)24 << 20;
 
 struct EpochWs;
@@ -485,13 +484,22 @@ inline int64_t ht_row_cuts_bound(int64_t entries, int seg, int64_t forced) { ret
 // Rows of a direction's list: first entries of its rows.
 inline const int64_t* ht_row_ptr(const ht_graph* g, bool fwd) { return !fwd ? g->by_src.ptr.p : g->merged ? g->uindptr.p : g->indptr.p; }
 inline int64_t ht_entries(const ht_graph* g) { return g->merged ? g->n_unique : g->Ep; }
-// What a pass over rows of d columns should take, made if it is not there and may be.  (Backward: by_src is there.)
-int ht_pass_plan(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, PassPlan* out);
+// What a pass over rows of d columns, src_ld floats apart, should take, made if it is not there and may be.  (Backward: by_src is there.)
+int ht_pass_plan(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, int64_t src_ld, PassPlan* out);
 // Scratch memory (slot HT_S_DENSE) of a pass over rows of d columns.
 size_t ht_dense_bytes(const DenseSide& D, int d);
 // The segments' sums of s_u src[u] into partial: DENSE_ROWS rows of pitch out_ld each.
 int ht_dense_launch(ht_ctx* ctx, hipStream_t st, const DenseSide& D, const float* src, int64_t ld, const float* s, int32_t d, float* partial,
                     int64_t out_ld);
+
+// Column units (k_spmm_unit): lanes, each with a float4, that own one item's part of a row.
+constexpr int UNIT_LANES = 16;
+// Rows go in column units where those are whole cache lines (a line that two units share is fetched twice: 2 M vertices, 30 M edges, 200
+// columns in rows of 800 bytes 13.5 -> 15.9 ms a layer) or there is one unit, and where the rows that are read are more than the caches
+// hold (116 k rows of 132: no difference; 60 k of 132: 86 us a pass, 70 expected of the slab kernel; 1 M of 64: 950 -> 870).
+inline bool ht_unit_shape(int64_t src_rows, int64_t src_ld, int nvec, bool aligned) {
+  return (((src_ld & 31) == 0 && aligned) || nvec <= UNIT_LANES) && src_rows * src_ld * 4 >= ((int64_t)64 << 20);
+}
 
 // ---- compute kernels' host launchers -----------------------------------------------------
 // Aggregation over work items (ht_spmm.hip).  One wave (or a lane group of it)

@@ -288,14 +288,14 @@ double agg_all_bytes(const ht_graph* g, int64_t edges, int64_t rows, int d) {
 // Scratch memory up to which a planned pass keeps partial sums.
 constexpr int64_t HT_PLAN_BYTES = (int64_t)8 << 30;
 
-// What a pass over rows of d columns, partial sums at pitch ld, takes of the graph's plan, and the scratch memory of that; nothing where
-// there is none or no memory for it.
-int take_plan(Run& R, bool fwd, int d, int64_t ld, PassPlan* out) {
+// What a pass over rows of d columns at pitch src_ld, partial sums at pitch ld, takes of the graph's plan, and the scratch memory of that; nothing
+// where there is none or no memory for it.
+int take_plan(Run& R, bool fwd, int d, int64_t src_ld, int64_t ld, PassPlan* out) {
   ht_ctx* ctx = R.ctx;
   *out = PassPlan();
   if (!R.planned || ctx->agg_variant != 0) return HT_OK;
   PassPlan p;
-  HT_TRY(ht_pass_plan(ctx, R.g, fwd, d, &p));
+  HT_TRY(ht_pass_plan(ctx, R.g, fwd, d, src_ld, &p));
   const int64_t part_bytes = p.parts() * ld * 4;
   if (!p.items || part_bytes > HT_PLAN_BYTES) return HT_OK;
   const size_t dense_bytes = p.dense ? ht_dense_bytes(*p.dense, d) : 0;
@@ -417,7 +417,7 @@ int layer_fwd_direct(Run& R, const ht_layer_desc* desc, const ht_tensor* H_in, c
     for (const ChunkRange& r : ranges) rows = std::max(rows, r.rows);
   };
   PassPlan planned;
-  if (A_ckpt || again_fits(R, di, dn)) HT_TRY(take_plan(R, true, di, a_ld, &planned));
+  if (A_ckpt || again_fits(R, di, dn)) HT_TRY(take_plan(R, true, di, H_in->ld, a_ld, &planned));
   R.note_planned(false);
   if (planned.items) {
     const int rc = ht_scratch_all(ctx, {{HT_S_ACHUNK, A_ckpt ? 0 : (size_t)(g->V * a_ld) * 4}, {HT_S_PACKW, (size_t)ht_packed_w_bytes(di, dn)}});
@@ -852,10 +852,10 @@ int layer_bwd_direct(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, c
   HT_TRY(rc);
   PassPlan plan, again;
   if (!agg_ckpt && R.made_planned()) {
-    HT_TRY(take_plan(R, true, di, a_ld, &again));
+    HT_TRY(take_plan(R, true, di, ckpt->ld, a_ld, &again));
     if (!again.items) return HT_OK;
   }
-  if (dH_in) HT_TRY(take_plan(R, false, di, dH_in->ld, &plan));
+  if (dH_in) HT_TRY(take_plan(R, false, di, ld_i, dH_in->ld, &plan));
   // Every slot again before a pointer into one is kept: plans let them grow, and one that was refused memory half-way may have left them smaller.
   if (dH_in && !plan.items) want.push_back({HT_S_SPART, by_source_parts(g, dH_in->ld)});
   HT_TRY(ht_scratch_each(ctx, want));
@@ -1244,7 +1244,7 @@ int layer_fwd_update_first(Run& R, const ht_layer_desc* desc, const ht_tensor* H
     R.st->gemm_flops += 2.0 * nr * di * dn;
   }
   PassPlan plan;
-  HT_TRY(take_plan(R, true, dn, H_out->ld, &plan));
+  HT_TRY(take_plan(R, true, dn, ld_t, H_out->ld, &plan));
   return agg_all(R, T, ld_t, dn, H_out->ptr, H_out->ld, desc->act == HT_ACT_RELU, plan);
 }
 
@@ -1291,7 +1291,7 @@ int layer_bwd_update_first(Run& R, const ht_layer_desc* desc, const ht_tensor* H
   want.push_back({HT_S_DZCHUNK, dz_bytes});
   want.push_back({HT_S_SPART, part_bytes});
   PassPlan plan;
-  if (at_once) HT_TRY(take_plan(R, false, dn, ld_t, &plan));
+  if (at_once) HT_TRY(take_plan(R, false, dn, relu ? ld_t : dH_out->ld, ld_t, &plan));
   HT_TRY(ht_scratch_each(ctx, want));   // (behind the plan: one that was refused memory half-way may have left slots smaller)
   dz_chunk = (float*)ctx->scratch[HT_S_DZCHUNK];
   partial = (float*)ctx->scratch[HT_S_SPART];

@@ -257,7 +257,6 @@ __global__ void __launch_bounds__(256) k_spmm_slab(SpmmArgs a, int S, int nvs, i
 // lists of short items (the slab kernel | this): 233 k vertices, the 26 M entries outside dense tiles, 602 and 256 columns 14.75 | 13.64 ms an
 // epoch, L2 hits 28 -> 67 %; 2.45 M vertices, 62 M edges, 256 columns 57.6 | 51.9 ms, hits 24 -> 46 %.  One line a unit keeps more (56 %)
 // but reads every index twice as often: 57.4 ms; four row reads in flight a lane: 8 52.8, 16 60.4 where this takes 52.7.
-constexpr int UNIT_LANES = 16;
 template <int LPR, bool SMALL>
 __global__ void __launch_bounds__(256) k_spmm_unit(SpmmArgs a, int S, int unit0) {
   constexpr int U = 4;
@@ -413,14 +412,6 @@ static_assert(row_blocks(1ll << 26, 4, 0) * 256 < (1ll << 32), "a row launch mus
 static_assert(row_blocks(111'000'000ll, 4, 0) == HT_ROW_GRID_MAX && row_blocks(int64_t(1) << 40, 1, 0) == HT_ROW_GRID_MAX, "");
 static_assert(row_blocks(1000, 4, 64) == 64 && row_blocks(100, 4, 64) == 25 && row_blocks(5, 4, 0) == 2, "");
 
-// Rows go in column units where those are whole cache lines (a line that two units share is fetched twice: 2 M vertices, 30 M edges, 200
-// columns in rows of 800 bytes 13.5 -> 15.9 ms a layer) or there is one unit, and where the rows that are read are more than the caches
-// hold (116 k rows of 132: no difference; 60 k of 132: 86 us a pass, 70 expected of the slab kernel; 1 M of 64: 950 -> 870).
-bool unit_shape(const SpmmArgs& a, int nvec) {
-  const bool lines = (a.src_ld & 31) == 0 && ((uintptr_t)a.src & 127) == 0;
-  return (lines || nvec <= UNIT_LANES) && a.src_rows * a.src_ld * 4 >= ((int64_t)64 << 20);
-}
-
 }  // namespace
 
 int ht_slab_shape(ht_ctx* ctx, const SpmmArgs& a, SlabShape* out) {
@@ -459,7 +450,7 @@ int ht_spmm_launch(ht_ctx* ctx, hipStream_t st, const SpmmArgs& a0) {
     const int nvec = (a.d + 3) / 4;
     int rc = HT_OK;
     if (a.tm && a.t_items) a.tm->begin(a.t_items);
-    if (a.units && unit_shape(a, nvec)) {
+    if (a.units && ht_unit_shape(a.src_rows, a.src_ld, nvec, ((uintptr_t)a.src & 127) == 0)) {
       const int lpr = nvec <= 8 ? 8 : UNIT_LANES, nu = (nvec + lpr - 1) / lpr, G = 64 / lpr;
       const bool small = a.src_rows * a.src_ld < ctx->unit_small;
       for (int u0 = 0; u0 < nu && rc == HT_OK;) {

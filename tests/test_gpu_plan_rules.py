@@ -90,18 +90,55 @@ def test_rows_beyond_four_gib():
         B.ht_ctx_destroy(ctx)
 
 
-def test_least_rows_for_short_items(monkeypatch):
-    V, d = 3_000, 40
-    src, dst = inputs.rmat_edges(V, 100_000, 3)
+def _held(V, src, dst, d, fine, monkeypatch):
+    """Bytes that the graph holds before any pass, after a forward and after a backward pass; the aggregates."""
     monkeypatch.setenv("HT_DENSE", "0")
-    monkeypatch.setenv("HT_FINE_WORK", "1")
-    outs = []
-    for rows, planned in ((V * d * 4, True), (V * d * 4 + 1, False)):
-        monkeypatch.setenv("HT_FINE_ROWS", str(rows))
-        _, _, A, _, held = _passes(V, src, dst, d, passes=("fwd",))
-        assert (held[1] > held[0]) == planned
-        outs.append(A)
-    assert float((outs[0] - outs[1]).norm() / outs[1].norm()) <= 1e-6
+    monkeypatch.setenv("HT_FINE", fine)
+    X, W, dh = B.alloc_matrix(V, d), torch.ones(d, 4, device="cuda") / d, B.alloc_matrix(V, 4)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d)
+    X.normal_(generator=gen)
+    dh.normal_(generator=gen)
+    ctx = B.ht_ctx_create(0)
+    g = B.ht_partition(ctx, V, src, dst, 3)
+    try:
+        H, A, dX, dW = B.alloc_matrix(V, 4), B.alloc_matrix(V, d), B.alloc_matrix(V, d), torch.empty(d, 4, device="cuda")
+        held = [B.ht_graph_info_get(g).hbm_bytes]
+        B.ht_layer_fwd(ctx, g, d, 4, B.HT_ACT_NONE, X, W, H, A)
+        B.ht_sync(ctx)
+        held.append(B.ht_graph_info_get(g).hbm_bytes)
+        dX.zero_()
+        B.ht_layer_bwd(ctx, g, d, 4, B.HT_ACT_NONE, A, W, dh, dW, dH_in=dX)
+        B.ht_sync(ctx)
+        held.append(B.ht_graph_info_get(g).hbm_bytes)
+        return held, A[:, :d].clone(), dX[:, :d].clone()
+    finally:
+        B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("V,E,d,fwd,bwd", [
+    (100_000, 2_500_000, 96, True, False),      # the slab kernel: forward from 64 columns and 16 entries a row on
+    (100_000, 1_300_000, 160, False, True),     # ... fewer entries a row; backward between 129 and 256 columns
+    (220_000, 9_000_000, 32, False, False),     # ... narrow
+    (70_000, 3_000_000, 80, False, False),      # ... rows of less than 24 MiB
+    (70_000, 5_000_000, 130, True, False),      # ... long rows
+    (300_000, 4_000_000, 64, True, True),       # one column unit
+    (300_000, 24_000_000, 64, True, False),     # ... long rows
+    (300_000, 4_000_000, 96, True, False),      # one and a half
+    (300_000, 4_000_000, 128, True, True),      # two
+    (300_000, 4_000_000, 192, True, False),     # three, few entries a row
+    (300_000, 6_000_000, 192, True, True),      # three
+])
+def test_which_passes_take_short_items(V, E, d, fwd, bwd, monkeypatch):
+    src, dst = inputs.rmat_edges(V, E, 3, device="cuda")
+    plain, A, dX = _held(V, src, dst, d, "0", monkeypatch)
+    held, A2, dX2 = _held(V, src, dst, d, "1", monkeypatch)
+    extra = [h - p for h, p in zip(held, plain)]
+    assert extra[0] == 0
+    assert (extra[1] > 0) == fwd and (extra[2] > extra[1]) == bwd
+    for x, y, planned in ((A, A2, fwd), (dX, dX2, bwd)):
+        assert float((x - y).norm() / x.norm()) <= (1e-6 if planned else 0.0)
 
 
 def test_gat_parameters_that_share_memory():
