@@ -105,7 +105,8 @@ int ht_sync(ht_ctx *ctx);
  * an earlier one or a faster pass holds.
  *
  * Without a cap, blocks of device memory that calls and destroyed graphs free
- * (not scratch memory) are kept for the context's next allocations: up to
+ * (scratch memory only until a caller has recorded a pass on its stream) are
+ * kept for the context's next allocations: up to
  * 4 GiB a context and 12 GiB on a device.  Another context gets them when its
  * allocation fails; for the caller's own allocator, any call of
  * ht_ctx_set_hbm_budget, with 0 too, gives back what the context keeps.

@@ -65,8 +65,8 @@ int ht_set_err(ht_ctx* ctx, int code, const char* fmt, ...) {
 // An allocation or a release costs 50 to 200 us of the host, a release some 3 ms per GiB, and makes the device idle; a graph that is
 // seen once takes a dozen blocks.  Blocks that a context frees are therefore kept and handed out again, to the same context, where they fit well:
 // work on a context's stream is in order, and what runs beside it is waited for by that stream before a call ends.  A context keeps up to
-// HT_KEPT_BYTES, those of a device together up to HT_KEPT_ALL.  Nothing is kept under a byte budget, nor of scratch slots (a caller may have recorded a pass that works in
-// one); a graph's end keeps nothing where less than an eighth of the device is free; and whatever any context keeps is given back where an
+// HT_KEPT_BYTES, those of a device together up to HT_KEPT_ALL.  Nothing is kept under a byte budget, nor of scratch slots once a caller has recorded a pass, which works in
+// them; a graph's end keeps nothing where less than an eighth of the device is free; and whatever any context keeps is given back where an
 // allocation of another fails, by ht_ctx_set_hbm_budget and with the context.  Partition and one layer of a graph seen once: 10 k vertices 567 -> 502 us,
 // 2.45 M vertices, 62 M edges 14.8 -> 13.6 ms.
 namespace {
@@ -234,7 +234,7 @@ int ht_scratch(ht_ctx* ctx, int slot, size_t bytes, void** out) {
     if (ctx->scratch[slot]) {
       if (slot == HT_S_TNPART) HT_TRY(ht_flush_products(ctx, ctx->stream));   // (sums that were left to the end of the epoch are in there)
       HT_HIP(ctx, hipStreamSynchronize(ctx->stream));
-      dev_free(ctx, ctx->scratch[slot], ctx->scratch_bytes[slot], false);
+      dev_free(ctx, ctx->scratch[slot], ctx->scratch_bytes[slot], !ctx->recorded);
       ctx->scratch[slot] = nullptr;
       ctx->scratch_bytes[slot] = 0;
     }
@@ -252,7 +252,7 @@ int ht_scratch_release(ht_ctx* ctx, int slot) {
   if (ctx->static_mode || !ctx->scratch[slot]) return HT_OK;
   if (slot == HT_S_TNPART) HT_TRY(ht_flush_products(ctx, ctx->stream));
   HT_HIP(ctx, hipStreamSynchronize(ctx->stream));
-  dev_free(ctx, ctx->scratch[slot], ctx->scratch_bytes[slot], false);
+  dev_free(ctx, ctx->scratch[slot], ctx->scratch_bytes[slot], !ctx->recorded);
   ctx->scratch[slot] = nullptr;
   ctx->scratch_bytes[slot] = 0;
   ++ctx->scratch_gen;

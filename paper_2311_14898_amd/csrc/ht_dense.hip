@@ -755,8 +755,12 @@ int build_dense(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, DenseSide& 
   DenseTmp t(V, n_ent);
   // (no more than a quarter of what is there: other passes want memory too)
   const int64_t room = ht_room(ctx);
-  const size_t sorting = 32 * (size_t)V + 4 * (size_t)V;
-  if ((int64_t)std::max(t.blk.planned, sorting) > room / 4 && std::max(t.blk.planned, sorting) > ctx->scratch_bytes[HT_S_DENSE]) return HT_ENOMEM;
+  // The slot at once as large as any step asks for it: sorting, the counts, the items of what is left.
+  const size_t most = std::max(std::max(t.blk.planned, 36 * (size_t)V + 16 * ((size_t)g->n + 1) + 2048),
+                               (size_t)(ht_row_items_bound(V, n_ent, REST_SEG) * 32 + ceil_div64(V, 16) + 65536));
+  if ((int64_t)most > room / 4 && most > ctx->scratch_bytes[HT_S_DENSE]) return HT_ENOMEM;
+  void* slot = nullptr;
+  HT_TRY(ht_scratch(ctx, HT_S_DENSE, most, &slot));
   if (!g->ranks.ok) HT_TRY(make_ranks(ctx, g));
   const int32_t *order_r = g->ranks.order[fwd ? 0 : 1].p, *order_c = g->ranks.order[fwd ? 1 : 0].p, *crank = g->ranks.rank[fwd ? 1 : 0].p;
   HT_TRY(t.blk.alloc_in(ctx, HT_S_DENSE));

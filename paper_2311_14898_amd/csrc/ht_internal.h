@@ -99,6 +99,7 @@ struct ht_ctx {
   int64_t tight_room = -1;     // room that was left after the last such call (-1: none since memory was plentiful)
   size_t gat_keep_limit = 0;   // a GAT epoch that kept this many bytes between its passes ran out of memory (0: none did) ...
   int64_t gat_keep_room = 0;   // ... and had this much room without them
+  bool recorded = false;       // the owner of the stream has recorded a pass, which may be replayed for as long as it likes
   int64_t refuse_alloc = 0;    // HT_REFUSE_ALLOC=k: the context's k-th allocation is refused; -k: its k-th hipMalloc fails (tests)
   int64_t device_bytes = 0;    // HT_DEVICE_BYTES: plan as if the device had no more memory than this for the context (0: as it reports)
   bool tn_defer = false;       // inside an epoch: products that allow it leave their slices (slot HT_S_TNPART, from tn_used bytes on) to ht_step
@@ -178,6 +179,7 @@ int64_t ht_held(const ht_ctx* ctx);   // bytes that ht_give_back would free
 // `changed`: the call has begun to change what the caller handed in, and cannot be made again.
 template <class F>
 int ht_with_room(ht_ctx* ctx, F&& call, const bool* changed = nullptr) {
+  if (!ctx->recorded) ctx->recorded = ht_caller_captures(ctx);
   int rc = call();
   if (rc != HT_ENOMEM || (changed && *changed) || !ht_give_back(ctx)) return rc;
   ctx->lean = true;
