@@ -17,9 +17,18 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 
 constexpr int BK = 16;        // reduction depth of one LDS stage
 constexpr int BM = 128;       // rows of A per block (NN) / output rows per block (TN)
-// Rows up to which a product reads W as it is, a launch less (10 k rows: 2.5 us and the gap before the next one).  Beyond a block per CU
-// the single loads and the bounds tests would be paid by every block.
+// Rows up to which a product may read W as it is, a launch less (2.5 us and the gap before the next one).  Its single loads and bounds tests cost about
+// 0.1 us a step of 16 of the reduction, in each round of blocks over the chip, so that it pays for short chains alone.  In place - packed (us), layers
+// without edges, 300 | 3,000 | 10,000 | 20,000 | 32,768 rows: 64 x 32 -2.6 | -2.1 | -2.3 | -1.4 | -1.3, 128 x 256 -1.5 | -1.3 | -1.5 | -0.3 | +1.2, 256 x 256
+// -0.3 | 0.0 | -1.0 | +1.0 | +3.7, 602 x 256 +3.7 | +3.3 | +2.8 | +8.6 | +10.5, 256 x 41 -1.4 | -0.7 | -1.4 | -1.7 | -2.2, 602 x 16 +0.8 | +0.9 | +0.6 | +0.3 | -0.4;
+// the transpose, 256 columns to 128 +0.7 | +1.6 | 0.0 | +0.4 | +3.0, 129 to 300 -0.8 | -1.2 | -2.2 | +0.2 | +2.7.
 constexpr int64_t HT_PACK_ROWS = 32768;
+constexpr int HT_PACK_CHAIN = 192, HT_PACK_CHAIN_NARROW = 512;   // (up to 64 columns a block stores half as much of W at a step)
+inline bool reads_w_in_place(int64_t M, int32_t K, int32_t N, bool transposed) {
+  if (M > HT_PACK_ROWS) return false;
+  const int64_t blocks = (M + BM - 1) / BM * (N > 64 ? (N + 127) / 128 : 1);
+  return K * std::max<int64_t>(blocks, 256) <= 256 * (N <= 64 && !transposed ? HT_PACK_CHAIN_NARROW : HT_PACK_CHAIN);
+}
 // Partial tiles of an epoch's products up to which they are added up by its last launch (each keeps its own until then).  Beyond it the
 // products take far longer than the launches that are saved.
 constexpr size_t HT_DEFER_BYTES = (size_t)64 << 20;
@@ -636,7 +645,7 @@ int launch_nn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const fl
 int gemm_nn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* W, bool transposed, float* C, int64_t ldc, int64_t M, int32_t K,
             int32_t N, int relu) {
   if (lda & 3) return ht_set_err(ctx, HT_ESHAPE, "gemm: row pitch must be a multiple of 4");
-  if (M <= HT_PACK_ROWS)
+  if (reads_w_in_place(M, K, N, transposed))
     return transposed ? launch_nn<TRANSPOSED>(ctx, st, A, lda, W, 0, C, ldc, M, K, N, relu)
                       : launch_nn<AS_IS>(ctx, st, A, lda, W, 0, C, ldc, M, K, N, relu);
   const int Kp = round_up(K, BK), Np = round_up(N, 128);

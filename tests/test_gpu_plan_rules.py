@@ -1,4 +1,4 @@
-"""Both sides of the rules that small graphs do not reach by themselves: rows wider than a column block over dense tiles, rows that column units
+"""Both sides of the rules that small graphs do not reach by themselves: products that read W in place, rows wider than a column block over dense tiles, rows that column units
 address in 64 bits, the least rows for short items, and the end of a GAT epoch whose attention vectors share memory."""
 import pytest
 import torch
@@ -123,12 +123,15 @@ def _held(V, src, dst, d, fine, monkeypatch):
     (220_000, 9_000_000, 32, False, False),     # ... narrow
     (70_000, 3_000_000, 80, False, False),      # ... rows of less than 24 MiB
     (70_000, 5_000_000, 130, True, False),      # ... long rows
+    (20_000, 400_000, 602, True, True),         # ... wide
+    (20_000, 800_000, 602, True, False),        # ... wide and long
     (300_000, 4_000_000, 64, True, True),       # one column unit
     (300_000, 24_000_000, 64, True, False),     # ... long rows
     (300_000, 4_000_000, 96, True, False),      # one and a half
     (300_000, 4_000_000, 128, True, True),      # two
     (300_000, 4_000_000, 192, True, False),     # three, few entries a row
     (300_000, 6_000_000, 192, True, True),      # three
+    (100_000, 1_300_000, 256, True, True),      # four
 ])
 def test_which_passes_take_short_items(V, E, d, fwd, bwd, monkeypatch):
     src, dst = inputs.rmat_edges(V, E, 3, device="cuda")
@@ -139,6 +142,41 @@ def test_which_passes_take_short_items(V, E, d, fwd, bwd, monkeypatch):
     assert (extra[1] > 0) == fwd and (extra[2] > extra[1]) == bwd
     for x, y, planned in ((A, A2, fwd), (dX, dX2, bwd)):
         assert float((x - y).norm() / x.norm()) <= (1e-6 if planned else 0.0)
+
+
+@pytest.mark.parametrize("V", [200, 20_000])
+@pytest.mark.parametrize("K,N", [(192, 100), (193, 100), (120, 256), (512, 64), (513, 64), (100, 192), (100, 193), (602, 256)])
+def test_products_around_the_packing_rule(V, K, N):
+    """No edges but the self-loops: the layer is H W forward and dz W^T backward, the same whether W is read in place or packed."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K + N)
+    rand = lambda a, b: torch.randn(a, b, generator=gen, device="cuda")
+    H, W, dz = rand(V, K), rand(K, N), rand(V, N)
+    ctx = B.ht_ctx_create(0)
+    none = torch.empty(0, dtype=torch.int32, device="cuda")
+    g = B.ht_partition(ctx, V, none, none, 1)
+    more = B.ht_partition(ctx, 40_000, none, none, 1)      # (beyond the rows that read W in place)
+    try:
+        def both(graph, H, dz):
+            v = H.shape[0]
+            out, A, dX, dW = B.alloc_matrix(v, N), B.alloc_matrix(v, K), B.alloc_matrix(v, K), torch.empty(K, N, device="cuda")
+            dX.zero_()
+            B.ht_layer_fwd(ctx, graph, K, N, B.HT_ACT_NONE, B.to_matrix(H), W, out, A)
+            B.ht_layer_bwd(ctx, graph, K, N, B.HT_ACT_NONE, A, W, B.to_matrix(dz), dW, dH_in=dX)
+            B.ht_sync(ctx)
+            return out[:, :N], dX[:, :K]
+        got = both(g, H, dz)
+        for x, a, b in zip(got, (H, dz), (W, W.t())):
+            want, mag = a.double() @ b.double(), a.abs().double() @ b.abs().double()
+            # n fp32 products and sums: off by at most (n + 2) 2^-24 of the sum of absolute values
+            assert ((x.double() - want).abs() <= (b.shape[0] + 4) * 2.0 ** -24 * mag).all()
+        times = 40_000 // V + 1
+        packed = both(more, H.repeat(times, 1)[:40_000], dz.repeat(times, 1)[:40_000])
+        assert all(torch.equal(x, y[:V]) for x, y in zip(got, packed))
+    finally:
+        for x in (g, more):
+            B.ht_graph_destroy(x)
+        B.ht_ctx_destroy(ctx)
 
 
 def test_gat_parameters_that_share_memory():
