@@ -869,10 +869,10 @@ namespace {
 // Whether a pass over short items of the graph's own entries is the faster one, by direction, width, rows and entries.  Measured over 18 R-MAT graphs of 10 k to
 // 2 M vertices, 10 to 400 entries a row, and 19 widths of 16 to 602 columns; time over the graph's own items / over short ones:
 //   column units   forward   1.02 .. 1.74; 8 lanes (32 columns and less) over long rows that are hardly more than the caches hold 0.94
-//                  backward  up to 64 columns 1.01 .. 1.39 below 64 entries a row, 0.93 .. 0.98 above; wider ones in (nearly) whole units 0.99 .. 1.16, with
-//                            fewer than 16 entries a row 0.94 .. 0.98 from three units on; with half a unit at the end (96, 160 columns) 0.89 .. 1.06
+//                  backward  up to 64 columns 1.01 .. 1.39 below 64 entries a row, 0.93 .. 0.98 above; wider ones in (nearly) whole units 0.99 .. 1.16 (three
+//                            units and fewer than 16 entries a row 0.98); with half a unit at the end (96, 160 columns) 0.89 .. 1.06
 //   slab kernel    forward   from 64 columns on 1.01 .. 1.38, 0.95 .. 1.04 below 16 entries a row; narrower 0.83 .. 1.00
-//                  backward  0.84 .. 1.03; 129 to 256 columns below 48 entries a row 1.00 .. 1.04
+//                  backward  0.84 .. 1.03; 129 to 256 columns below 48 entries a row 1.00 .. 1.04, wider ones 0.96 .. 0.99, below 24 entries 1.00 .. 1.08
 // (Items of the graph itself have 256 entries forward and 128 backward, so that there is less to gain backward.)
 bool short_items_pay(const ht_graph* g, bool fwd, int32_t d, int64_t src_ld) {
   const int64_t V = g->V, n_ent = ht_entries(g);
@@ -880,10 +880,10 @@ bool short_items_pay(const ht_graph* g, bool fwd, int32_t d, int64_t src_ld) {
   if (ht_unit_shape(V, src_ld, nvec, true)) {
     if (fwd) return nvec > 8 || n_ent <= 64 * V || V * src_ld * 4 >= ((int64_t)128 << 20);
     if (n_units == 1) return n_ent <= 64 * V;
-    return nvec * 10 >= n_units * UNIT_LANES * 9 && (n_units == 2 || n_ent >= 16 * V);
+    return nvec * 10 >= n_units * UNIT_LANES * 9 && (n_units != 3 || n_ent >= 16 * V);
   }
   if (fwd) return d >= 64 && n_ent >= 16 * V;
-  return d > 128 && d <= 256 && n_ent <= 48 * V;
+  return d > 128 && n_ent <= (d <= 256 ? 48 : 24) * V;
 }
 
 }  // namespace
