@@ -308,6 +308,8 @@ int take_plan(Run& R, bool fwd, int d, int64_t src_ld, int64_t ld, PassPlan* out
 // The pass's launches, `a` being those of the unplanned pass over the whole graph with the partial sums in place.
 int planned_launch(Run& R, const PassPlan& p, SpmmArgs a) {
   const ht_graph* g = R.g;
+  if ((size_t)(p.parts() * a.out_ld) * 4 > R.ctx->scratch_bytes[HT_S_SPART])
+    return ht_set_err(R.ctx, HT_ESTATE, "aggregation: %lld partial sums of %lld floats, more than their slot was asked for", (long long)p.parts(), (long long)a.out_ld);
   a.items = p.items->items.p; a.n_items = p.items->n_items;
   a.cuts = p.items->cuts.p; a.n_fix = p.items->n_cut;
   a.part0 = 0;
@@ -858,6 +860,7 @@ int layer_bwd_direct(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, c
   if (dH_in) HT_TRY(take_plan(R, false, di, ld_i, dH_in->ld, &plan));
   // Every slot again before a pointer into one is kept: plans let them grow, and one that was refused memory half-way may have left them smaller.
   if (dH_in && !plan.items) want.push_back({HT_S_SPART, by_source_parts(g, dH_in->ld)});
+  want.push_back({HT_S_SPART, (size_t)(again.parts() * a_ld) * 4});
   HT_TRY(ht_scratch_each(ctx, want));
   if (a_bytes) a_all = (float*)ctx->scratch[HT_S_ACHUNK];
   if (dz_bytes) dz_all = (float*)ctx->scratch[HT_S_DZCHUNK];

@@ -88,3 +88,42 @@ def test_each_allocation_refused(data, what, monkeypatch):
                 # sums of the same terms in other orders: fp32 rounding of a few hundred terms, far below the terms themselves
                 assert (r[name] - w).abs().max() <= 2e-5 * w.abs().max(), (k, name)
     assert through > ALLOCS // 2
+
+
+def test_backward_plan_refused_behind_a_repeated_aggregate(monkeypatch):
+    """A recomputing epoch whose backward plan needs more partial sums than the forward one, which needs more than either list without plans: where
+    the larger slot is refused, the aggregate that is made again still finds room for its own."""
+    for k, v in {"HT_DENSE": "0", "HT_FINE_WORK": "1", "HT_MERGE_DUPS": "0"}.items():
+        monkeypatch.setenv(k, v)
+    E, dims = 150_000, [24, 72, 8]
+    gen = torch.Generator().manual_seed(3)
+    draw = lambda lo, hi, n: torch.randint(lo, hi, (n,), generator=gen).to(torch.int32)
+    # (all entries in long rows by source, seven tenths by destination: in items of 64 some 2,340 and 1,640 partial sums, by source in items of 128 some 1,170)
+    src, dst = draw(0, 100, E).cuda(), torch.cat([draw(100, 150, E * 7 // 10), draw(150, V, E - E * 7 // 10)])[torch.randperm(E, generator=gen)].cuda()
+    X, y = B.to_matrix(torch.randn(V, dims[0], generator=gen)), draw(0, dims[-1], V).cuda()
+    want, through = None, 0
+    for k in [0] + list(range(1, ALLOCS)):
+        monkeypatch.setenv("HT_REFUSE_ALLOC", str(k))
+        ctx = B.ht_ctx_create(0)
+        g = None
+        try:
+            W = [w.cuda() for w in inputs.glorot_weights(dims, seed=4)]
+            epoch = lambda: B.ht_epoch(ctx, g, dims, W, 1.0, X, y, inter=B.HT_INTER_RECOMPUTE)[0]
+            try:
+                g = B.ht_partition(ctx, V, src, dst, 3)
+                loss = epoch()
+            except B.HongtuError as e:
+                assert k > 0 and e.code == B.HT_ENOMEM, (k, e)
+                if g is None:
+                    continue
+                loss = epoch()      # (a refused epoch has updated nothing)
+            got = [torch.tensor(loss).double()] + [w.double().cpu() for w in W]
+        finally:
+            if g is not None:
+                B.ht_graph_destroy(g)
+            B.ht_ctx_destroy(ctx)
+        want = want or got
+        through += 1
+        for r, w in zip(got, want):
+            assert (r - w).abs().max() <= 2e-5 * w.abs().max(), k
+    assert through > ALLOCS // 2
