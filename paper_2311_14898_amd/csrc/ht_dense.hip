@@ -16,7 +16,8 @@
 // Measured, ms an epoch, all entries by 256-entry items | with this: 233 k vertices, 115 M edges, 602-256-41 20.8 | 13.0; 116 k, 57 M, 301-129-47
 // 4.18 | 2.86; 2.45 M, 62 M, 100-256-256-47 64.3 | 51.2 (there 14 % of the entries lie in tiles; the short items of the rest give as much).
 // Relative error against fp64 (2-norm), all by items | with this: 40 k vertices, 4 M edges, 602 columns 3.4e-8 | 3.0e-8; 20 k, 2 M, 41 columns
-// 3.2e-8 | 3.2e-8; 5 k, 0.4 M, 130 columns 4.3e-8 | 3.5e-8.
+// 3.2e-8 | 3.2e-8; 5 k, 0.4 M, 130 columns 4.3e-8 | 3.5e-8.  Where duplicates are not merged, s_u h_u is rounded here and was inside the FMA there:
+// the same graphs 3.6e-8 | 3.0e-8, 3.2e-8 | 3.2e-8, 5.2e-8 | 3.5e-8; backward 3.6e-8 | 3.4e-8, 3.6e-8 | 3.6e-8, 4.8e-8 | 3.8e-8.
 #include <algorithm>
 #include <vector>
 
