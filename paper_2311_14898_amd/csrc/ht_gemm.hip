@@ -193,6 +193,148 @@ __global__ void __launch_bounds__(256) k_gemm_nn(const float* __restrict__ A, in
     }
 }
 
+// C = A W (+ReLU), or A W^T, with the block's columns of W in LDS and the rows of A straight to registers, for widths that k_gemm_nn would pad
+// (rows_shape).  A wave owns 32 rows x TJ tiles of 32 columns, takes strip after strip of rows, and waits for no other wave once W is there; its rows' pieces
+// come NBUF steps of 32 values ahead, across strips.  Lane l32 + 32 half holds row l32 and the values 8 q + 4 half .. + 3 of a step (a load covers 32
+// contiguous bytes of each row, a step its whole cache line); W lies in LDS in fours along the reduction, so that a lane's four values of a column are
+// one read.  The order of an element's sum is that of the reduction alone: it does not depend on rows, tiles or blocks.
+// What bounds it: the fp32 matrix cores (2.45 M rows, 256 x 256: 79 % busy, as k_gemm_nn's, and 85 without its loads and stores), and for
+// narrow results the rows' reads (1 M x 64 x 20: 5 TB/s).
+constexpr int RS = 32;                       // values of a step
+constexpr int ROWS_LDS = 160 << 10;          // LDS of a CU
+constexpr int rows_lds(int K, int tj) { return (K + 7) / 8 * 2 * (tj * 32 + 1) * 16; }   // (a pitch of odd float4s: the transposed W is stored across rows)
+
+template <int TJ, int NBUF, bool T>
+__global__ void __launch_bounds__(512) k_rows_w(const float* __restrict__ A, int64_t lda, const float* __restrict__ W, float* __restrict__ C,
+                                                int64_t ldc, int64_t M, int K, int N, int relu) {
+  extern __shared__ float4 Bs[];
+  constexpr int NT = TJ * 32, P = NT + 1;
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+  const int waves = blockDim.x >> 6, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n0 = blockIdx.y * NT, K4 = (K + 7) / 8 * 2;
+  const int64_t strips = (M + 31) / 32, stride = (int64_t)gridDim.x * waves;
+  int64_t strip = (int64_t)blockIdx.x * waves + wave;
+  const int steps = (K + RS - 1) / RS;
+
+  float4 buf[NBUF][4];
+  auto row_of = [&](int64_t s) {   // (rows behind the last: the last again, not stored)
+    const int64_t r = s * 32 + l32;
+    return A + (r < M ? r : M - 1) * lda + half * 4;
+  };
+  auto fetch = [&](float4* b, const float* row, int c) {
+    const float* p = row + c * RS;
+    if ((c + 1) * RS <= K) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) b[q] = ld4g(p + q * 8);
+    } else {   // (what lies behind a row's last value is not looked at: it may be anything)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        int left = K - (c * RS + q * 8 + half * 4);
+        asm volatile("" : "+v"(left));   // (or the conditions of every step's end are made before the loop, and kept)
+        const float4 v = ld4g(p + (left > 0 ? q * 8 : (K - 1 - c * RS - half * 4) & ~3));
+        auto kept = [&](float x, int i) { return __int_as_float(__float_as_int(x) & ((i - left) >> 31)); };
+        b[q] = make_float4(kept(v.x, 0), kept(v.y, 1), kept(v.z, 2), kept(v.w, 3));
+      }
+    }
+  };
+  const float* row = row_of(strip < strips ? strip : strips - 1);
+#pragma unroll
+  for (int u = 0; u < NBUF; ++u)
+    if (u < steps) fetch(buf[u], row, u);
+  // W: fours along the reduction, one after the other along the columns of W, or eight along a row of its transpose, as it lies in memory
+  const int n_w = (T ? (K4 + 7) / 8 * 8 : K4) * NT;
+  const bool vec = T && (K & 3) == 0 && (reinterpret_cast<uintptr_t>(W) & 15) == 0;
+  for (int i0 = tid; i0 < n_w; i0 += 4 * blockDim.x) {
+    float4 v[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      const int i = i0 + x * blockDim.x, k = (T ? i / (8 * NT) * 8 + i % 8 : i / NT) * 4, n = n0 + (T ? i / 8 % NT : i % NT);
+      v[x] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (i >= n_w || n >= N || k >= K) continue;
+      const float* p = T ? W + (int64_t)n * K + k : W + (int64_t)k * N + n;
+      if (vec) {
+        v[x] = ld4g(p);
+      } else {
+        const int d = T ? 1 : N;
+        v[x].x = p[0];
+        if (k + 1 < K) v[x].y = p[d];
+        if (k + 2 < K) v[x].z = p[2 * (int64_t)d];
+        if (k + 3 < K) v[x].w = p[3 * (int64_t)d];
+      }
+    }
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      const int i = i0 + x * blockDim.x, k4 = T ? i / (8 * NT) * 8 + i % 8 : i / NT;
+      if (i < n_w && k4 < K4) Bs[k4 * P + (T ? i / 8 % NT : i % NT)] = v[x];
+    }
+  }
+  __syncthreads();
+  for (; strip < strips; strip += stride) {
+    v16f acc[TJ];
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
+    const int64_t m0 = strip * 32;
+    const bool more = strip + stride < strips;
+    const float* next = more ? row_of(strip + stride) : row;
+    for (int c0 = 0; c0 < steps; c0 += NBUF) {
+#pragma unroll
+      for (int u = 0; u < NBUF; ++u) {
+        const int c = c0 + u;
+        if (c >= steps) break;
+        const float4* B = Bs + (c * 8 + half) * P + l32;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if (q > 0 && c * RS + q * 8 >= K) break;
+          float4 b[TJ];
+#pragma unroll
+          for (int j = 0; j < TJ; ++j) b[j] = B[q * 2 * P + j * 32];
+          const float4 a = buf[u][q];
+#pragma unroll
+          for (int j = 0; j < TJ; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b[j].x, acc[j], 0, 0, 0);
+#pragma unroll
+          for (int j = 0; j < TJ; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b[j].y, acc[j], 0, 0, 0);
+#pragma unroll
+          for (int j = 0; j < TJ; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b[j].z, acc[j], 0, 0, 0);
+#pragma unroll
+          for (int j = 0; j < TJ; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b[j].w, acc[j], 0, 0, 0);
+        }
+        // what takes this piece's place: of this strip, or of the next
+        if (c + NBUF < steps) fetch(buf[u], row, c + NBUF);
+        else if (more) fetch(buf[u], next, u);
+      }
+    }
+    // D layout of a 32x32 tile: lane holds column l32, rows (e/4)*8 + half*4 + e%4
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) {
+      const int gc = n0 + j * 32 + l32;
+      if (gc >= N) continue;
+      float* cp = C + (m0 + half * 4) * ldc + gc;
+      if (m0 + 32 <= M && relu < 2) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          float v = acc[j][e];
+          if (relu) v = v > 0.f ? v : 0.f;
+          cp[((e >> 2) * 8 + (e & 3)) * ldc] = v;
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int r = (e >> 2) * 8 + (e & 3);
+          if (m0 + half * 4 + r < M) {
+            float v = acc[j][e];
+            if (relu & 1) v = v > 0.f ? v : 0.f;
+            if (relu & 2) v += cp[r * ldc];
+            cp[r * ldc] = v;
+          }
+        }
+      }
+    }
+    row = next;
+  }
+}
+
 // Partial tile of C[K x N] = A[M x K]^T B[M x N] over the M-slice blockIdx.z (rows tab[2z] .. tab[2z + 1], or slice_rows each).
 // P[slice][K x N] dense.  Block tile: BM output rows (k) x BN output columns.
 template <int BN, int WM, int WN, int TI, int TJ>
@@ -633,7 +775,6 @@ inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
 template <int FORM>
 int launch_nn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* Bp, int Np, float* C, int64_t ldc, int64_t M, int K, int N,
               int relu) {
-  if (M <= 0 || N <= 0) return HT_OK;
   const unsigned gx = (unsigned)((M + BM - 1) / BM);
   if (N > 64) k_gemm_nn<128, 2, 2, 2, 2, FORM><<<dim3(gx, (unsigned)((N + 127) / 128)), 256, 0, st>>>(A, lda, Bp, Np, C, ldc, M, K, N, relu);
   else k_gemm_nn<64, 4, 1, 1, 2, FORM><<<dim3(gx, 1), 256, 0, st>>>(A, lda, Bp, Np, C, ldc, M, K, N, relu);
@@ -641,10 +782,63 @@ int launch_nn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const fl
   return HT_OK;
 }
 
+// Products whose columns, in tiles of 32, are at most four fifths of what k_gemm_nn's blocks of 64 or 128 would compute go through k_rows_w.  us, k_gemm_nn (with
+// its packed W) | k_rows_w, at rows x K x N: 10 k x 64 x 32 5.8 | 4.7, 60 k x 67 x 129 40.4 | 23.4, 60 k x 129 x 67 34.3 | 25.0, 116 k x 301 x 129 165 | 135, 233 k x 256 x
+// 20 79 | 49, 300 k x 129 x 67 113 | 97, 1 M x 64 x 20 85 | 68.  Beyond the line: 300 k x 64 x 300 187 | 195, 233 k x 256 x 41 85 | 89, 1 M x 64 x 64 112 | 120, 2.45 M x 100 x 256
+// 1,415 | 1,430 (the memory's rate or, in long runs, the power that fp32 matrix cores draw).  The line is drawn by K and N alone: a row must not depend
+// on how many rows are multiplied at once.
+struct RowsShape {
+  int tj = 0, waves = 0;     // tj 0: k_gemm_nn's
+  unsigned gx = 0, gy = 0;
+};
+RowsShape rows_shape(int64_t M, int K, int N) {
+  RowsShape s;
+  const int tiles = (N + 31) / 32, blocks = N > 64 ? (N + 127) / 128 * 4 : 2;
+  int best = blocks * 4 / 5;
+  for (int tj = 1; tj <= 5 && rows_lds(K, tj) <= ROWS_LDS; ++tj) {
+    const int n = (tiles + tj - 1) / tj * tj;
+    if (n <= best) best = n, s.tj = tj;
+  }
+  if (!s.tj) return s;
+  const int64_t strips = (M + 31) / 32;
+  while (s.tj > 1 && strips * ((tiles + s.tj - 1) / s.tj) < 1024) --s.tj;   // (a wave for every SIMD)
+  s.gy = (unsigned)((tiles + s.tj - 1) / s.tj);
+  // eight waves a CU in two blocks, or in one where W takes most of the LDS: more waves do not help (their strips come round by round), fewer wait for their loads
+  const int per_cu = 2 * rows_lds(K, s.tj) <= ROWS_LDS ? 2 : 1;
+  s.waves = strips * s.gy < 1024 ? 2 : 8 / per_cu;
+  s.gx = (unsigned)std::min<int64_t>((strips + s.waves - 1) / s.waves, std::max(1u, 256u * per_cu * (8 / per_cu / s.waves) / s.gy));
+  return s;
+}
+template <int TJ, int NBUF, bool T>
+int launch_rows(ht_ctx* ctx, hipStream_t st, const RowsShape& s, const float* A, int64_t lda, const float* W, float* C, int64_t ldc, int64_t M, int K,
+                int N, int relu) {
+  const int lds = rows_lds(K, TJ);
+  if (lds > (64 << 10))
+    HT_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_rows_w<TJ, NBUF, T>), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+  k_rows_w<TJ, NBUF, T><<<dim3(s.gx, s.gy), s.waves * 64, lds, st>>>(A, lda, W, C, ldc, M, K, N, relu);
+  HT_LAUNCH_CHECK(ctx);
+  return HT_OK;
+}
+template <bool T>
+int rows_w(ht_ctx* ctx, hipStream_t st, const RowsShape& s, const float* A, int64_t lda, const float* W, float* C, int64_t ldc, int64_t M, int K, int N,
+           int relu) {
+  switch (s.tj) {
+    case 1: return launch_rows<1, 4, T>(ctx, st, s, A, lda, W, C, ldc, M, K, N, relu);
+    case 2: return launch_rows<2, 4, T>(ctx, st, s, A, lda, W, C, ldc, M, K, N, relu);
+    case 3: return launch_rows<3, 2, T>(ctx, st, s, A, lda, W, C, ldc, M, K, N, relu);
+    case 4: return launch_rows<4, 2, T>(ctx, st, s, A, lda, W, C, ldc, M, K, N, relu);
+    default: return launch_rows<5, 2, T>(ctx, st, s, A, lda, W, C, ldc, M, K, N, relu);
+  }
+}
+
 // C = A W (+ReLU), or A W^T: out of a padded copy of W in the context's scratch, or of W itself.
 int gemm_nn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* W, bool transposed, float* C, int64_t ldc, int64_t M, int32_t K,
             int32_t N, int relu) {
   if (lda & 3) return ht_set_err(ctx, HT_ESHAPE, "gemm: row pitch must be a multiple of 4");
+  if (M <= 0 || N <= 0) return HT_OK;
+  const RowsShape shape = rows_shape(M, K, N);
+  if (shape.tj)
+    return transposed ? rows_w<true>(ctx, st, shape, A, lda, W, C, ldc, M, K, N, relu) : rows_w<false>(ctx, st, shape, A, lda, W, C, ldc, M, K, N, relu);
   if (reads_w_in_place(M, K, N, transposed))
     return transposed ? launch_nn<TRANSPOSED>(ctx, st, A, lda, W, 0, C, ldc, M, K, N, relu)
                       : launch_nn<AS_IS>(ctx, st, A, lda, W, 0, C, ldc, M, K, N, relu);

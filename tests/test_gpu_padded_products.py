@@ -1,0 +1,63 @@
+"""Products whose widths fill tiles of 32 columns better than blocks of 64 or 128, at the edges of tiles, steps of the reduction, strips of
+rows and of what of W fits into a CU's memory, against fp64."""
+import pytest
+import torch
+
+from paper_2311_14898_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("V", [1, 33, 3_000, 40_001])
+@pytest.mark.parametrize("K,N", [(1, 1), (31, 32), (33, 8), (64, 65), (67, 129), (129, 96), (301, 160), (300, 161), (96, 257), (416, 66), (424, 66), (1216, 20), (1217, 20)])
+def test_layer_without_edges(V, K, N):
+    """No edges but the self-loops: the layer is H W forward and dz W^T backward; the widths are taken both ways."""
+    if V > 10_000 and K > 500:
+        pytest.skip("the rows' rule is tested at the narrower widths")
+    ctx = B.ht_ctx_create(0)
+    none = torch.empty(0, dtype=torch.int32, device="cuda")
+    g = B.ht_partition(ctx, V, none, none, 1)
+    try:
+        for di, dn in ((K, N), (N, K)):
+            gen = torch.Generator().manual_seed(di)
+            H, W, dz = torch.randn(V, di, generator=gen), torch.randn(di, dn, generator=gen), torch.randn(V, dn, generator=gen)
+            out, A, dX, dW = B.alloc_matrix(V, dn), B.alloc_matrix(V, di), B.alloc_matrix(V, di), torch.empty(di, dn, device="cuda")
+            Hd, dzd = B.to_matrix(H), B.to_matrix(dz)
+            for m, cols in ((Hd, di), (dzd, dn), (A, di)):
+                m[:, cols:] = float("nan")     # what lies behind a row's last value is nobody's business
+            out.fill_(-3.0)
+            dX.zero_()
+            Wd = torch.cat([torch.full((3,), float("nan")), W.reshape(-1), torch.full((5,), float("nan"))]).cuda()[3:3 + di * dn].view(di, dn)
+            B.ht_layer_fwd(ctx, g, di, dn, B.HT_ACT_RELU, Hd, Wd, out, A)
+            B.ht_layer_bwd(ctx, g, di, dn, B.HT_ACT_NONE, A, Wd, dzd, dW, dH_in=dX)
+            B.ht_sync(ctx)
+            assert bool((out[:, dn:] == -3.0).all())
+            # n fp32 products and sums: off by at most (n + 4) 2^-24 of the sum of absolute values
+            for got, a, b, relu in ((out[:, :dn], H, W, True), (dX[:, :di], dz, W.t(), False)):
+                want, mag = a.double() @ b.double(), a.abs().double() @ b.abs().double()
+                if relu:
+                    want = want.clamp(min=0)
+                assert ((got.cpu().double() - want).abs() <= (b.shape[0] + 4) * 2.0 ** -24 * mag).all(), (di, dn)
+    finally:
+        B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("K,N", [(67, 129), (129, 67), (50, 20)])
+def test_rows_do_not_depend_on_their_number(K, N):
+    """The same bits whether a row is multiplied among 100, 5,000 or 200,000."""
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    H, W = torch.randn(200_000, K, generator=gen, device="cuda"), torch.randn(K, N, generator=gen, device="cuda")
+    rows = []
+    none = torch.empty(0, dtype=torch.int32, device="cuda")
+    for V in (100, 5_000, 200_000):
+        ctx = B.ht_ctx_create(0)
+        g = B.ht_partition(ctx, V, none, none, 1)
+        Hd, out = B.alloc_matrix(V, K), B.alloc_matrix(V, N)
+        Hd[:, :K] = H[:V]
+        B.ht_layer_fwd(ctx, g, K, N, B.HT_ACT_NONE, Hd, W, out)
+        B.ht_sync(ctx)
+        rows.append(out[:100, :N].clone())
+        B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)
+    assert torch.equal(rows[0], rows[1]) and torch.equal(rows[0], rows[2])
