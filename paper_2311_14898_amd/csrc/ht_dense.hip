@@ -415,53 +415,19 @@ __global__ void __launch_bounds__(TB) k_keep_copy(const uint8_t* __restrict__ ke
 // ---- the products
 
 constexpr float DSCALE = 0x1p24f, DUNSCALE = 0x1p-24f;
-// Columns with larger values (or any that are not finite) are zeros to the products and are added entry by entry behind them: 0 x inf would reach
+// Larger values (or any that are not finite) are zeros to the products and are added entry by entry behind them: 0 x inf would reach
 // rows that do not name them, and scaled sums could overflow.  Below it 2^20 products of 255 and the scale stay finite.
 constexpr float DLARGEST = 0x1p64f;
-
-// s_u h_u of 32 columns as three bf16 each, in the order in which k_dense reads them: [column block][part][16 columns][feature][16].
-// odd[group][feature / 64]: a bit for each column that holds a value too large or not finite among these features; it is packed as zeros.
-// Grid: groups of 32 columns x 64 features (a wave has eight columns, a feature per lane).
-__global__ void __launch_bounds__(TB) k_dense_pack(const float* __restrict__ src, int64_t ld, const float* __restrict__ s, int d, int dp, int n128,
-                                                   const int32_t* __restrict__ cols, __bf16* __restrict__ planes, uint32_t* __restrict__ odd) {
-  const int f = blockIdx.y * 64 + (threadIdx.x & 63), oct = threadIdx.x >> 6;
-  const bool wide = f < n128 * 128;
-  const int f0 = wide ? f & ~127 : n128 * 128, bn = wide ? 128 : 64;
-  const int64_t g = blockIdx.x;
-  v8bf p[3];
-  uint32_t out_of_range = 0;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int32_t u = cols[g * 32 + oct * 8 + j];
-    float x = 0.f;
-    if (u >= 0 && f < d) x = s[u] * src[(int64_t)u * ld + f];
-    if (__ballot(!(fabsf(x) <= DLARGEST))) {
-      out_of_range |= 1u << j;
-      x = 0.f;
-    }
-    x *= DSCALE;
-    p[0][j] = (__bf16)x;
-    const float r = x - (float)p[0][j];
-    p[1][j] = (__bf16)r;
-    p[2][j] = (__bf16)(r - (float)p[1][j]);
-  }
-  __bf16* out = planes + g * dp * 96 + (int64_t)f0 * 96 + ((oct >> 1) * bn + (f - f0)) * 16 + (oct & 1) * 8;
-#pragma unroll
-  for (int q = 0; q < 3; ++q) *reinterpret_cast<v8bf*>(out + q * 2 * bn * 16) = p[q];
-  if ((threadIdx.x & 63) == 0) reinterpret_cast<uint8_t*>(odd + g * (dp / 64) + blockIdx.y)[oct] = (uint8_t)out_of_range;
-}
 
 struct DenseArgs {
   const uint8_t* cells;
   const int32_t* tile_cg;
   const DenseSeg* segs;
   const int32_t* cols;
-  const __bf16* planes;
-  const uint32_t* odd;
   const float* src;
   const float* s;
   int64_t ld, out_ld;
-  int d, dp, f0;
+  int d, f0;
   float* partial;         // [segment][256] rows
 };
 
@@ -476,32 +442,33 @@ __device__ __forceinline__ v8bf cells8(uint32_t lo, uint32_t hi) {
   return __builtin_bit_cast(v8bf, r);
 }
 
-// One segment (tiles of one row block) x BN features: 8 waves of 64 rows x BN / 2 features, one block per CU (128 accumulators a lane).
-// 256 rows, because every column's parts are read once per row block and 128 rows would ask L2 for 32 bytes a clock and CU, all
-// it gives; 32 columns a stage, in order of the lanes that multiply them, so that they go to LDS as they are.  22.6 k tiles
-// x 1,152 columns (602 + 256 + 256) 2.66 ms, 0.96 PFLOP/s of the three products; an 8192^3 bf16 product of the vendor's library runs at 1.23.  Loads one stage
-// ahead 3.2 ms; two and three ahead 3.0; the stage's column group out of LDS instead of memory (its load waited for all before it) 2.66.
+// One segment (tiles of one row block) x BN features: 8 waves of 64 rows x BN / 2 features; one block per CU with 128 features (128 accumulators a lane), two
+// with 64.  256 rows, because every column's values are read once per row block and 128 rows would ask L2 for 32 bytes a clock and CU, all
+// it gives; 32 columns a stage.  The stage's columns' rows come as they are, three stages ahead (a wave takes eight of them, 256 bytes each, at
+// addresses that are the same in all its lanes), and are scaled and split into three bf16 on their way into LDS.  Split by a pass of their own they were half as
+// many bytes again to read: 22.6 k tiles x 602, 256 and 256 columns 2.51 ms and 0.42 for the pass, 2.79 now; 4.9 k tiles x 256 395 us, 348 now.  What bounds it: a barrier
+// a stage, behind which all waves split, convert their cells and read LDS before the matrix cores have work again (49 % busy), and 3.7 TB/s of
+// columns and cells that miss L2.  Tried: a range check of each value apart, with the lookup of its column, 3.9 ms; matrix and vector instructions interleaved by hand, no
+// difference; LDS without its two-way conflicts (as it is here), no difference alone; segments of 24 or 88 tiles, no difference.
 template <int BN>
 __global__ void __launch_bounds__(512) k_dense(DenseArgs a) {
-  constexpr int TJ = BN / 64, STAGE = 6 * BN * 16, CH = STAGE * 2 / 16, NB = (CH + 511) / 512;   // 16-byte pieces of a stage
+  constexpr int TJ = BN / 64, STAGE = 96 * BN, CPT = 32 * BN / 512;   // bf16 of a stage [part][8 columns][feature][8]; columns of a thread
   __shared__ __attribute__((aligned(16))) __bf16 Bs[2][STAGE];
+  __shared__ int32_t col_of[DENSE_SEG * DENSE_COLS];     // the segment's columns: vertex (-1: none) ...
+  __shared__ float scale_of[DENSE_SEG * DENSE_COLS];     // ... and factor
+  __shared__ uint32_t odd[DENSE_SEG * 2];                // a bit for each that has a value out of range among these features
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, half = lane >> 5;
   const DenseSeg seg = a.segs[blockIdx.x];
-  const int f0 = a.f0 + (int)blockIdx.y * BN;
-  __shared__ int32_t cg[DENSE_SEG];   // (read from memory on the way, a stage's number would wait for every load before it)
-  if (tid < seg.n) cg[tid] = a.tile_cg[seg.tile0 + tid];
-  __syncthreads();
+  const int f0 = a.f0 + (int)blockIdx.y * BN, S = seg.n * 2;
   float* out = a.partial + (int64_t)blockIdx.x * DENSE_ROWS * a.out_ld;
-
-  // columns of 32 that have to be added entry by entry, for any of these features
-  auto odd_columns = [&](int g) {
-    const uint32_t* p = a.odd + ((int64_t)cg[g >> 1] * 2 + (g & 1)) * (a.dp / 64) + f0 / 64;
-    return BN > 64 ? p[0] | p[BN / 64 - 1] : p[0];
-  };
-  uint32_t some = 0;
-  for (int g = tid; g < seg.n * 2; g += 512) some |= odd_columns(g);
-  const bool any_odd = __syncthreads_or(some != 0);
+  for (int c = tid; c < seg.n * DENSE_COLS; c += 512) {
+    const int32_t u = a.cols[(int64_t)a.tile_cg[seg.tile0 + c / DENSE_COLS] * DENSE_COLS + c % DENSE_COLS];
+    col_of[c] = u < 0 ? 0 : u;
+    scale_of[c] = u >= 0 ? a.s[u] * DSCALE : 0.f;
+  }
+  if (tid < S) odd[tid] = 0;
+  __syncthreads();
 
   v16f hi[2][TJ], lo[2][TJ];
 #pragma unroll
@@ -511,35 +478,72 @@ __global__ void __launch_bounds__(512) k_dense(DenseArgs a) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) hi[i][j][e] = lo[i][j][e] = 0.f;
 
-  const int S = seg.n * 2;
-  // Pieces of the columns' rows travel through registers into one of two LDS stages, three stages ahead of their use; the cells, two.
-  v4u rb[2][NB], ra[2][2];
-  auto fetch_b = [&](int st, v4u* r) {
-    if (st >= S) return;
-    const int group = __builtin_amdgcn_readfirstlane(cg[st >> 1]) * 2 + (st & 1);
-    const v4u* p = reinterpret_cast<const v4u*>(a.planes + (int64_t)group * a.dp * 96 + (int64_t)f0 * 96);
+  // a thread's columns of a stage, and its feature (the columns are the same in all lanes of a wave)
+  const int c0 = __builtin_amdgcn_readfirstlane(tid / BN) * CPT, fl = tid % BN, f = f0 + fl;
+  const bool has = f < a.d;
+  const int fc = has ? f : a.d - 1;
+  float rb[2][CPT];
+  v4u ra[2][2];
+  int32_t cn[CPT];   // the columns of the next stage to be fetched
+  auto next_cols = [&](int st) {
 #pragma unroll
-    for (int q = 0; q < NB; ++q)
-      if (CH % 512 == 0 || tid + q * 512 < CH) r[q] = p[tid + q * 512];
+    for (int j = 0; j < CPT; ++j) cn[j] = col_of[(st < S ? st : S - 1) * 32 + c0 + j];
   };
-  auto store_b = [&](int b, const v4u* r) {
-    v4u* p = reinterpret_cast<v4u*>(Bs[b]);
+  auto fetch_b = [&](int st, float* r) {
+    st = st < S ? st : S - 1;
 #pragma unroll
-    for (int q = 0; q < NB; ++q)
-      if (CH % 512 == 0 || tid + q * 512 < CH) p[tid + q * 512] = r[q];
+    for (int j = 0; j < CPT; ++j) {
+      r[j] = (a.src + (int64_t)__builtin_amdgcn_readfirstlane(cn[j]) * a.ld)[fc];
+    }
+  };
+  auto store_b = [&](int st, int b, const float* r) {
+    typedef __bf16 vbf __attribute__((ext_vector_type(CPT)));
+    vbf p[3];
+    float x[CPT];
+    uint32_t most = 0;
+#pragma unroll
+    for (int j = 0; j < CPT; ++j) {
+      x[j] = scale_of[st * 32 + c0 + j] * r[j];
+      const uint32_t mag = __float_as_uint(x[j]) & 0x7FFFFFFFu;
+      most = mag > most ? mag : most;
+    }
+    if (__ballot(most > __float_as_uint(DLARGEST * DSCALE))) {
+      uint32_t out_of_range = 0;
+#pragma unroll
+      for (int j = 0; j < CPT; ++j) {
+        const bool large = !(fabsf(x[j]) <= DLARGEST * DSCALE);
+        if (__ballot(large)) out_of_range |= 1u << j;
+        if (large) x[j] = 0.f;
+      }
+      if (lane == 0) atomicOr(&odd[st], out_of_range << c0);
+    }
+#pragma unroll
+    for (int j = 0; j < CPT; ++j) {
+      p[0][j] = (__bf16)x[j];
+      const float q = x[j] - (float)p[0][j];
+      p[1][j] = (__bf16)q;
+      p[2][j] = (__bf16)(q - (float)p[1][j]);
+    }
+    __bf16* to = Bs[b] + ((c0 >> 3) * BN + fl) * 8 + (c0 & 7);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) *reinterpret_cast<vbf*>(to + q * 32 * BN) = p[q];
   };
   auto fetch_a = [&](int st, v4u* r) {
-    if (st >= S) return;
+    st = st < S ? st : S - 1;
     const v4u* p = reinterpret_cast<const v4u*>(a.cells + ((int64_t)seg.tile0 * 2 + st) * (DENSE_ROWS * 32) + wm * 2048);
     r[0] = p[lane];
     r[1] = p[lane + 64];
   };
+  next_cols(0);
   fetch_b(0, rb[0]);
   fetch_a(0, ra[0]);
+  next_cols(1);
   fetch_b(1, rb[1]);
   fetch_a(1, ra[1]);
-  store_b(0, rb[0]);
+  next_cols(2);
+  store_b(0, 0, rb[0]);
   fetch_b(2, rb[0]);
+  next_cols(3);
   for (int st0 = 0; st0 < S; st0 += 2)   // (S is even)
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
@@ -551,17 +555,18 @@ __global__ void __launch_bounds__(512) k_dense(DenseArgs a) {
         m[0][i] = cells8(ra[x][i].x, ra[x][i].y);
         m[1][i] = cells8(ra[x][i].z, ra[x][i].w);
       }
-      if (st + 1 < S) store_b(x ^ 1, rb[x ^ 1]);
+      store_b(st + 1 < S ? st + 1 : S - 1, x ^ 1, rb[x ^ 1]);   // (behind the last: the last again, into the stage that nobody reads)
       fetch_a(st + 2, ra[x]);
       fetch_b(st + 3, rb[x ^ 1]);
-      const __bf16* B = Bs[x] + (wn * (BN / 2) + l32) * 16 + half * 8;
+      next_cols(st + 4);
+      const __bf16* B = Bs[x] + (half * BN + wn * (BN / 2) + l32) * 8;
 #pragma unroll
       for (int k = 0; k < 2; ++k)
 #pragma unroll
         for (int p = 0; p < 3; ++p) {
           v8bf b[TJ];
 #pragma unroll
-          for (int j = 0; j < TJ; ++j) b[j] = *reinterpret_cast<const v8bf*>(B + ((p * 2 + k) * BN + j * 32) * 16);
+          for (int j = 0; j < TJ; ++j) b[j] = *reinterpret_cast<const v8bf*>(B + ((p * 4 + k * 2) * BN + j * 32) * 8);
 #pragma unroll
           for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -573,41 +578,38 @@ __global__ void __launch_bounds__(512) k_dense(DenseArgs a) {
     }
 #pragma unroll
   for (int j = 0; j < TJ; ++j) {
-    const int f = f0 + wn * (BN / 2) + j * 32 + l32;
-    if (f >= ((a.d + 3) & ~3)) continue;   // (zeros up to whole float4)
+    const int fo = f0 + wn * (BN / 2) + j * 32 + l32;
+    if (fo >= ((a.d + 3) & ~3)) continue;   // (zeros up to whole float4)
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int r = wm * 64 + i * 32 + (e >> 2) * 8 + half * 4 + (e & 3);
-        out[(int64_t)r * a.out_ld + f] = (hi[i][j][e] + lo[i][j][e]) * DUNSCALE;
+        out[(int64_t)r * a.out_ld + fo] = (hi[i][j][e] + lo[i][j][e]) * DUNSCALE;
       }
   }
-  if (!any_odd) return;
+  if (!__syncthreads_or(tid < S && odd[tid] != 0)) return;
   // What the products took for zeros: a feature and a quarter (an eighth) of the rows per thread, column by column.  233 k vertices, 115 M edges,
   // one value of 1e25 in a column that most segments hold: 61 ms an epoch when such a segment left the matrix cores altogether, 12.8 now (12.8
   // without the value); in one vertex of fifty 66 | 13.1, in one of fifty and in every block of 64 features 189 | 14.8.  Where every value is out of
   // range (a training run that has diverged) it is 61 ms, and 20.5 over work items alone.
-  __syncthreads();
   constexpr int PER = DENSE_ROWS / (512 / BN);
-  const int f = f0 + tid % BN, r0 = __builtin_amdgcn_readfirstlane(tid / BN) * PER;
-  if (f >= a.d) return;
+  const int r0 = __builtin_amdgcn_readfirstlane(tid / BN) * PER;
+  if (!has) return;
   float acc[PER];
 #pragma unroll
   for (int i = 0; i < PER; ++i) acc[i] = out[(int64_t)(r0 + i) * a.out_ld + f];
   for (int g = 0; g < S; ++g) {
-    uint32_t left = __builtin_amdgcn_readfirstlane(odd_columns(g));
+    uint32_t left = __builtin_amdgcn_readfirstlane(odd[g]);
     while (left) {
-      const int k = (g & 1) * 32 + __builtin_ctz(left);
+      const int c = g * 32 + __builtin_ctz(left), k = c & 63;
       left &= left - 1;
-      const int32_t u = a.cols[(int64_t)cg[g >> 1] * DENSE_COLS + k];
-      // (a column that is odd in the other 64 of these features alone was in the products)
-      const bool mine = (a.odd[((int64_t)cg[g >> 1] * 2 + (g & 1)) * (a.dp / 64) + f / 64] >> (k & 31)) & 1;
-      const float x = mine ? a.s[u] * a.src[(int64_t)u * a.ld + f] : 0.f;
-      const uint8_t* c = a.cells + cell_at(seg.tile0 + (g >> 1), r0, k);
+      float x = scale_of[c] * a.src[(int64_t)col_of[c] * a.ld + f];
+      x = fabsf(x) <= DLARGEST * DSCALE ? 0.f : a.s[col_of[c]] * a.src[(int64_t)col_of[c] * a.ld + f];   // (0: that one was in the products)
+      const uint8_t* cell = a.cells + cell_at(seg.tile0 + (g >> 1), r0, k);
 #pragma unroll
       for (int i = 0; i < PER; ++i) {
-        const uint32_t m = c[(i >> 5) * 1024 + (i & 31) * 16];
+        const uint32_t m = cell[(i >> 5) * 1024 + (i & 31) * 16];
         if (m) acc[i] = fmaf((float)m, x, acc[i]);
       }
     }
@@ -616,12 +618,9 @@ __global__ void __launch_bounds__(512) k_dense(DenseArgs a) {
   for (int i = 0; i < PER; ++i) out[(int64_t)(r0 + i) * a.out_ld + f] = acc[i];
 }
 
-int pad_features(int d, int* n128) {
-  *n128 = d / 128 + (d % 128 > 64);
-  return *n128 * 128 + (d > *n128 * 128 ? 64 : 0);
-}
+constexpr int64_t WIDE_TILES = 32768;
 
-// Scratch memory of the making; it is the products' own slot, which is not in use yet.
+// Scratch memory of the making (slot HT_S_DENSE).
 struct DenseTmp {
   DevBlock blk;
   DevArr<int32_t> rparts, parts, flag, tile_cg, rest, kcnt;
@@ -940,29 +939,21 @@ int ht_pass_plan(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, int64_t sr
   return HT_OK;
 }
 
-size_t ht_dense_bytes(const DenseSide& D, int d) {
-  int n128;
-  const size_t dp = (size_t)pad_features(d, &n128);
-  return (size_t)D.n_cols / 32 * (dp * 192 + dp / 64 * 4) + 256;
-}
-
 // The segments' sums into partial ([segment][256] rows of pitch out_ld).
 int ht_dense_launch(ht_ctx* ctx, hipStream_t st, const DenseSide& D, const float* src, int64_t ld, const float* s, int32_t d, float* partial,
                     int64_t out_ld) {
-  int n128;
-  const int dp = pad_features(d, &n128);
-  void* mem = nullptr;
-  HT_TRY(ht_scratch(ctx, HT_S_DENSE, ht_dense_bytes(D, d), &mem));
-  __bf16* planes = (__bf16*)mem;
-  uint32_t* odd = (uint32_t*)((char*)mem + (size_t)D.n_cols / 32 * dp * 192);
-  k_dense_pack<<<dim3((unsigned)(D.n_cols / 32), dp / 64), TB, 0, st>>>(src, ld, s, d, dp, n128, D.cols.p, planes, odd);
-  HT_LAUNCH_CHECK(ctx);
-  DenseArgs a{D.cells.p, D.tile_cg.p, D.segs.p, D.cols.p, planes, odd, src, s, ld, out_ld, d, dp, 0, partial};
-  if (n128 > 0) k_dense<128><<<dim3((unsigned)D.n_segs, n128), 512, 0, st>>>(a);
-  HT_LAUNCH_CHECK(ctx);
-  if (dp > n128 * 128) {
+  // Blocks of 128 features decode a cell half as often, blocks of 64 leave shorter last rounds and take what is left behind the last 128 along.  us, 128 (and 64) | 64 alone: 22.6 k
+  // tiles x 602 1546 | 1634, x 256 610 | 659; 4.9 k x 256 346 | 320, x 100 199 | 197; 7 k x 129 312 | 283.
+  int n128 = d / 128 + (d % 128 > 64);
+  if (D.n_tiles * n128 < WIDE_TILES) n128 = 0;
+  DenseArgs a{D.cells.p, D.tile_cg.p, D.segs.p, D.cols.p, src, s, ld, out_ld, d, 0, partial};
+  if (n128 > 0) {
+    k_dense<128><<<dim3((unsigned)D.n_segs, n128), 512, 0, st>>>(a);
+    HT_LAUNCH_CHECK(ctx);
+  }
+  if (d > n128 * 128) {
     a.f0 = n128 * 128;
-    k_dense<64><<<dim3((unsigned)D.n_segs, 1), 512, 0, st>>>(a);
+    k_dense<64><<<dim3((unsigned)D.n_segs, (unsigned)((d - a.f0 + 63) / 64)), 512, 0, st>>>(a);
     HT_LAUNCH_CHECK(ctx);
   }
   return HT_OK;

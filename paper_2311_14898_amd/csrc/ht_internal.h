@@ -501,8 +501,6 @@ inline const int64_t* ht_row_ptr(const ht_graph* g, bool fwd) { return !fwd ? g-
 inline int64_t ht_entries(const ht_graph* g) { return g->merged ? g->n_unique : g->Ep; }
 // What a pass over rows of d columns, src_ld floats apart, should take, made if it is not there and may be.  (Backward: by_src is there.)
 int ht_pass_plan(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, int64_t src_ld, PassPlan* out);
-// Scratch memory (slot HT_S_DENSE) of a pass over rows of d columns.
-size_t ht_dense_bytes(const DenseSide& D, int d);
 // The segments' sums of s_u src[u] into partial: DENSE_ROWS rows of pitch out_ld each.
 int ht_dense_launch(ht_ctx* ctx, hipStream_t st, const DenseSide& D, const float* src, int64_t ld, const float* s, int32_t d, float* partial,
                     int64_t out_ld);

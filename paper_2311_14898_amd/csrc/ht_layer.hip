@@ -298,10 +298,8 @@ int take_plan(Run& R, bool fwd, int d, int64_t src_ld, int64_t ld, PassPlan* out
   HT_TRY(ht_pass_plan(ctx, R.g, fwd, d, src_ld, &p));
   const int64_t part_bytes = p.parts() * ld * 4;
   if (!p.items || part_bytes > HT_PLAN_BYTES) return HT_OK;
-  const size_t dense_bytes = p.dense ? ht_dense_bytes(*p.dense, d) : 0;
-  const bool grows = ctx->scratch_bytes[HT_S_SPART] < (size_t)part_bytes || ctx->scratch_bytes[HT_S_DENSE] < dense_bytes;
-  if (grows && ht_caller_captures(ctx)) return HT_OK;
-  const int rc = ht_scratch_all(ctx, {{HT_S_SPART, (size_t)part_bytes}, {HT_S_DENSE, dense_bytes}});
+  if (ctx->scratch_bytes[HT_S_SPART] < (size_t)part_bytes && ht_caller_captures(ctx)) return HT_OK;
+  const int rc = ht_scratch_all(ctx, {{HT_S_SPART, (size_t)part_bytes}});
   if (rc == HT_OK) *out = p;
   return rc == HT_ENOMEM ? (int)HT_OK : rc;
 }
