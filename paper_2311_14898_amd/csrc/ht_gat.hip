@@ -113,6 +113,9 @@ __global__ void __launch_bounds__(256) k_gat_pq(const float* __restrict__ T, int
 //   2. per row cut into several items: m_v = max m_i, Z_v = sum s_i exp(m_i - m_v), in a fixed order;
 //   3. where they are used: w_e = mult_e exp(x_e - m_v) / Z_v.
 // Rows are vertices; w holds the entries from ent0 on, part_* the partial results from part0 on.
+// What bounds step 1 is the chain of loads of an entry (its source, the source's q) in items of up to 256 entries: one after the other they took 485 us for 78 M
+// entries, 360 with four a lane on the way together and kept.
+constexpr int SCORE_REGS = 4;
 __global__ void __launch_bounds__(256) k_gat_scores(const WorkItem* __restrict__ items, int64_t n_items, int64_t ent0, int64_t part0,
                                                     const int32_t* __restrict__ col, const float* __restrict__ mult,
                                                     const float* __restrict__ p, const float* __restrict__ q, float slope,
@@ -127,15 +130,38 @@ __global__ void __launch_bounds__(256) k_gat_scores(const WorkItem* __restrict__
   const int64_t e0 = it.e0;
   w -= ent0;
   const float pv = p[r];
-  float m = -3.0e38f;
-  for (int32_t k = lane; k < len; k += 64) {
-    const float x = lrelu(pv + q[col[e0 + k]], slope);
-    w[e0 + k] = x;
-    m = fmaxf(m, x);
+  float m = -3.0e38f, s = 0.f;
+  if (len <= 64 * SCORE_REGS) {   // the entries' scores stay in registers between the two sums, and their loads are on the way together
+    int32_t c[SCORE_REGS];
+    float x[SCORE_REGS], w_e[SCORE_REGS];
+#pragma unroll
+    for (int j = 0; j < SCORE_REGS; ++j) {
+      const int32_t k = j * 64 + lane;
+      c[j] = k < len ? col[e0 + k] : -1;
+      w_e[j] = k < len && mult ? mult[e0 + k] : 1.f;
+    }
+#pragma unroll
+    for (int j = 0; j < SCORE_REGS; ++j) x[j] = c[j] >= 0 ? q[c[j]] : 0.f;
+#pragma unroll
+    for (int j = 0; j < SCORE_REGS; ++j) {
+      if (c[j] < 0) continue;
+      x[j] = lrelu(pv + x[j], slope);
+      w[e0 + j * 64 + lane] = x[j];
+      m = fmaxf(m, x[j]);
+    }
+    m = wave_max(m);
+#pragma unroll
+    for (int j = 0; j < SCORE_REGS; ++j)
+      if (c[j] >= 0) s += w_e[j] * expf(x[j] - m);
+  } else {
+    for (int32_t k = lane; k < len; k += 64) {
+      const float x = lrelu(pv + q[col[e0 + k]], slope);
+      w[e0 + k] = x;
+      m = fmaxf(m, x);
+    }
+    m = wave_max(m);
+    for (int32_t k = lane; k < len; k += 64) s += (mult ? mult[e0 + k] : 1.f) * expf(w[e0 + k] - m);
   }
-  m = wave_max(m);
-  float s = 0.f;
-  for (int32_t k = lane; k < len; k += 64) s += (mult ? mult[e0 + k] : 1.f) * expf(w[e0 + k] - m);
   s = wave_sum(s);
   if (lane == 0) {
     if (part >= 0) {
