@@ -337,7 +337,10 @@ __global__ void __launch_bounds__(512) k_rows_w(const float* __restrict__ A, int
 
 // Partial tile of C[K x N] = A[M x K]^T B[M x N] over the M-slice blockIdx.z (rows tab[2z] .. tab[2z + 1], or slice_rows each).
 // P[slice][K x N] dense.  Block tile: BM output rows (k) x BN output columns.
-template <int BN, int WM, int WN, int TI, int TJ>
+// What bounds it is the loads of a step of 16 rows, PD steps of which are in flight: up to 64 columns two, wider ones, whose accumulators leave fewer registers, one.  us, loads
+// with bounds tests one step ahead | without | two ahead | four | six, at rows x K x N: 2.45 M x 256 x 47 973 | - | 849 | 885 | 841, 1 M x 64 x 64 221 | - | 196 | 215 | 201, 60 k x 129
+// x 60 42 | - | 35 | 37 | 38, 20 k x 50 x 33 17.0 | - | 16.5 | 17.8 | 17.8; wider: 20 k x 256 x 100 32 | 26 | 27 (| 27 three), 8 k x 200 x 100 22 | 19 | 20.
+template <int BN, int WM, int WN, int TI, int TJ, int PD>
 __global__ void __launch_bounds__(256) k_gemm_tn(const float* __restrict__ A, int64_t lda,
                                                  const float* __restrict__ B, int64_t ldb, float* __restrict__ P,
                                                  int64_t M, int K, int N, int64_t slice_rows,
@@ -363,92 +366,70 @@ __global__ void __launch_bounds__(256) k_gemm_tn(const float* __restrict__ A, in
 
   constexpr int NA = BK * BM / 4 / 256, NB = BK * BN / 4 / 256;
   static_assert(NA * 256 == BK * BM / 4 && NB * 256 == BK * BN / 4, "tile loads must divide among 256 threads");
-  float4 ra[NA], rb[NB];
-  // tiles that lie inside both operands are fetched without bounds tests
+  // The tiles of PD steps are on their way at once.  Loads have no condition (outside the operands they read the last row, the last columns again), so that the
+  // waits count only the loads of the step that is next; what lies outside is cleared on the way into LDS.
+  float4 ra[PD][NA], rb[PD][NB];
   const bool full_a = kc0 + BM <= K, full_b = n0 + BN <= N;
-  auto fetch = [&](int64_t mm0) {
-    const bool full_m = mm0 + BK <= me;
-    if (full_m && full_a) {
+  const int last_a = (K - 1) & ~3, last_b = (N - 1) & ~3;
+  auto fetch = [&](int64_t mm0, float4* pa, float4* pb) {
 #pragma unroll
-      for (int u = 0; u < NA; ++u) {
-        const int f = tid + u * 256;
-        const int mr = f / (BM / 4), cv = (f % (BM / 4)) * 4;
-        ra[u] = ld4g(A + (mm0 + mr) * lda + kc0 + cv);
-      }
-    } else {
-#pragma unroll
-      for (int u = 0; u < NA; ++u) {
-        const int f = tid + u * 256;
-        const int mr = f / (BM / 4), cv = (f % (BM / 4)) * 4;
-        const int64_t gm = mm0 + mr;
-        const int gk = kc0 + cv;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (gm < me && gk < K) {
-          v = ld4g(A + gm * lda + gk);
-          if (gk + 1 >= K) v.y = 0.f;
-          if (gk + 2 >= K) v.z = 0.f;
-          if (gk + 3 >= K) v.w = 0.f;
-        }
-        ra[u] = v;
-      }
+    for (int u = 0; u < NA; ++u) {
+      const int f = tid + u * 256, c = kc0 + (f % (BM / 4)) * 4;
+      const int64_t r = mm0 + f / (BM / 4);
+      pa[u] = ld4g(A + (r < me ? r : me - 1) * lda + (c < last_a ? c : last_a));
     }
-    if (full_m && full_b) {
 #pragma unroll
-      for (int u = 0; u < NB; ++u) {
-        const int f = tid + u * 256;
-        const int mr = f / (BN / 4), cv = (f % (BN / 4)) * 4;
-        rb[u] = ld4g(B + (mm0 + mr) * ldb + n0 + cv);
-      }
-    } else {
-#pragma unroll
-      for (int u = 0; u < NB; ++u) {
-        const int f = tid + u * 256;
-        const int mr = f / (BN / 4), cv = (f % (BN / 4)) * 4;
-        const int64_t gm = mm0 + mr;
-        const int gn = n0 + cv;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (gm < me && gn < N) {
-          v = ld4g(B + gm * ldb + gn);
-          if (gn + 1 >= N) v.y = 0.f;
-          if (gn + 2 >= N) v.z = 0.f;
-          if (gn + 3 >= N) v.w = 0.f;
-        }
-        rb[u] = v;
-      }
+    for (int u = 0; u < NB; ++u) {
+      const int f = tid + u * 256, c = n0 + (f % (BN / 4)) * 4;
+      const int64_t r = mm0 + f / (BN / 4);
+      pb[u] = ld4g(B + (r < me ? r : me - 1) * ldb + (c < last_b ? c : last_b));
     }
   };
-  auto stash = [&]() {
+  auto inside = [&](float4 v, bool row, int c, int n) {
+    const int left = row ? n - c : 0;
+    return make_float4(left > 0 ? v.x : 0.f, left > 1 ? v.y : 0.f, left > 2 ? v.z : 0.f, left > 3 ? v.w : 0.f);
+  };
+  auto stash = [&](int64_t mm0, const float4* pa, const float4* pb) {
+    const bool full_m = mm0 + BK <= me;
 #pragma unroll
     for (int u = 0; u < NA; ++u) {
       const int f = tid + u * 256;
       const int mr = f / (BM / 4), cv = (f % (BM / 4)) * 4;
-      *reinterpret_cast<float4*>(As + mr * (BM + 4) + cv) = ra[u];
+      *reinterpret_cast<float4*>(As + mr * (BM + 4) + cv) = full_m && full_a ? pa[u] : inside(pa[u], mm0 + mr < me, kc0 + cv, K);
     }
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
       const int f = tid + u * 256;
       const int mr = f / (BN / 4), cv = (f % (BN / 4)) * 4;
-      *reinterpret_cast<float4*>(Bs + mr * (BN + 4) + cv) = rb[u];
+      *reinterpret_cast<float4*>(Bs + mr * (BN + 4) + cv) = full_m && full_b ? pb[u] : inside(pb[u], mm0 + mr < me, n0 + cv, N);
     }
   };
-  if (ms < me) fetch(ms);
-  for (int64_t mm0 = ms; mm0 < me; mm0 += BK) {
-    stash();
-    __syncthreads();
-    if (mm0 + BK < me) fetch(mm0 + BK);
+  if (ms < me) {
 #pragma unroll
-    for (int kk = 0; kk < BK; kk += 2) {
-      float af[TI], bf[TJ];
+    for (int u = 0; u < PD; ++u) fetch(ms + u * BK, ra[u], rb[u]);
+  }
+  for (int64_t m1 = ms; m1 < me; m1 += PD * BK) {
 #pragma unroll
-      for (int i = 0; i < TI; ++i) af[i] = As[(kk + half) * (BM + 4) + wm * TI * 32 + i * 32 + l32];
+    for (int u = 0; u < PD; ++u) {
+      const int64_t mm0 = m1 + u * BK;
+      if (mm0 >= me) break;
+      stash(mm0, ra[u], rb[u]);
+      __syncthreads();
+      fetch(mm0 + PD * BK, ra[u], rb[u]);
 #pragma unroll
-      for (int j = 0; j < TJ; ++j) bf[j] = Bs[(kk + half) * (BN + 4) + wn * TJ * 32 + j * 32 + l32];
+      for (int kk = 0; kk < BK; kk += 2) {
+        float af[TI], bf[TJ];
 #pragma unroll
-      for (int i = 0; i < TI; ++i)
+        for (int i = 0; i < TI; ++i) af[i] = As[(kk + half) * (BM + 4) + wm * TI * 32 + i * 32 + l32];
 #pragma unroll
-        for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i], bf[j], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < TJ; ++j) bf[j] = Bs[(kk + half) * (BN + 4) + wn * TJ * 32 + j * 32 + l32];
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+          for (int j = 0; j < TJ; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i], bf[j], acc[i][j], 0, 0, 0);
+      }
+      __syncthreads();
     }
-    __syncthreads();
   }
   float* Ps = P + (int64_t)blockIdx.z * K * N;
 #pragma unroll
@@ -906,9 +887,9 @@ int launch_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const fl
   if (use_split_tn(rows, K, N))
     k_split_tn<<<grid, 256, 0, st>>>(A, lda, B, ldb, P, M, K, N, slice_rows, tab);
   else if (N > 64)
-    k_gemm_tn<128, 2, 2, 2, 2><<<grid, 256, 0, st>>>(A, lda, B, ldb, P, M, K, N, slice_rows, tab);
+    k_gemm_tn<128, 2, 2, 2, 2, 1><<<grid, 256, 0, st>>>(A, lda, B, ldb, P, M, K, N, slice_rows, tab);
   else
-    k_gemm_tn<64, 4, 1, 1, 2><<<grid, 256, 0, st>>>(A, lda, B, ldb, P, M, K, N, slice_rows, tab);
+    k_gemm_tn<64, 4, 1, 1, 2, 2><<<grid, 256, 0, st>>>(A, lda, B, ldb, P, M, K, N, slice_rows, tab);
   HT_LAUNCH_CHECK(ctx);
   if (leave) {
     ctx->tn_used += bytes;

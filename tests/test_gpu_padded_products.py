@@ -61,3 +61,25 @@ def test_rows_do_not_depend_on_their_number(K, N):
         B.ht_graph_destroy(g)
         B.ht_ctx_destroy(ctx)
     assert torch.equal(rows[0], rows[1]) and torch.equal(rows[0], rows[2])
+
+
+@pytest.mark.parametrize("V", [1, 15, 17, 33, 49, 1_000, 20_011])
+@pytest.mark.parametrize("K,N", [(1, 1), (5, 4), (33, 7), (129, 64), (128, 61), (130, 66), (40, 130)])
+def test_weight_gradients_by_steps_of_rows(V, K, N):
+    """grad W = H^T dz over slices of rows that end anywhere in a step, with anything behind the rows' last values."""
+    ctx = B.ht_ctx_create(0)
+    none = torch.empty(0, dtype=torch.int32, device="cuda")
+    g = B.ht_partition(ctx, V, none, none, 1)
+    try:
+        gen = torch.Generator().manual_seed(V)
+        A, dz = torch.randn(V, K, generator=gen), torch.randn(V, N, generator=gen)
+        Ad, dzd, dW = B.to_matrix(A), B.to_matrix(dz), torch.full((K, N), 7.0, device="cuda")
+        Ad[:, K:], dzd[:, N:] = float("nan"), float("inf")
+        B.ht_layer_bwd(ctx, g, K, N, B.HT_ACT_NONE, Ad, torch.randn(K, N, generator=gen).cuda(), dzd, dW)
+        B.ht_sync(ctx)
+        want, mag = A.double().t() @ dz.double(), A.double().abs().t() @ dz.double().abs()
+        # V fp32 products and sums: off by at most (V + 4) 2^-24 of the sum of absolute values
+        assert ((dW.cpu().double() - want).abs() <= (V + 4) * 2.0 ** -24 * mag).all()
+    finally:
+        B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)
