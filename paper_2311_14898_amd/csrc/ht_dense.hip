@@ -35,7 +35,16 @@ constexpr int ETILE = 2048;
 // 468 us (all with other kernels beside them).
 constexpr int32_t DENSE_LEAST = 650;
 constexpr int SEG_BLOCKS = 512;                 // segments that a graph's tiles are cut into at least
-constexpr int REST_SEG = 48, FINE_SEG = 64;     // entries of a work item
+// Entries of a work item.  The shorter, the narrower the range of rows that the items in flight read, and the more of them the L2s keep; but a row that is cut has its partial
+// sums written and read, so the line lies with the entries a row.  ms an epoch with items of the rest of 24 | 32 | 40 | 48 | 64 | 96 entries: 2.45 M vertices, 22 entries
+// a row left, 49.6 | 49.2 | 50.7 | 51.2 | 52.0 | 52.7; 233 k, 111 a row, 13.4 | 13.0 | 12.8 | 12.7 | 13.0 | 13.2; 116 k, 160 a row, 2.83 | 2.72 | 2.67 | 2.67 | 2.67 | 2.82.
+// Over all entries, 32 | 48 | 64: layer of 1.5 M, 20 M edges, 128 columns 4.36 | 4.32 | 4.46, three-layer epoch of 1 M, 10 M edges 2.37 | 2.34 | 2.37.
+constexpr int REST_SEG = 48, REST_SEG_SPARSE = 32, FINE_SEG = 48;
+constexpr int64_t REST_SPARSE = 48;   // entries left a row up to which they are the shorter ones
+inline int rest_seg(int64_t V, int64_t left) { return left <= REST_SPARSE * V ? REST_SEG_SPARSE : REST_SEG; }
+inline int64_t rest_items_bound(int64_t V, int64_t most) {   // whatever part of `most` entries is left
+  return std::max(ht_row_items_bound(V, most, REST_SEG), ht_row_items_bound(V, std::min(most, REST_SPARSE * V), REST_SEG_SPARSE));
+}
 inline unsigned nblk(int64_t n, int tb = TB) { return (unsigned)((n + tb - 1) / tb); }
 
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
@@ -757,7 +766,7 @@ int build_dense(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, DenseSide& 
   const int64_t room = ht_room(ctx);
   // The slot at once as large as any step asks for it: sorting, the counts, the items of what is left.
   const size_t most = std::max(std::max(t.blk.planned, 36 * (size_t)V + 16 * ((size_t)g->n + 1) + 2048),
-                               (size_t)(ht_row_items_bound(V, n_ent, REST_SEG) * 32 + ceil_div64(V, 16) + 65536));
+                               (size_t)(rest_items_bound(V, n_ent) * 32 + ceil_div64(V, 16) + 65536));
   if ((int64_t)most > room / 4 && most > ctx->scratch_bytes[HT_S_DENSE]) return HT_ENOMEM;
   void* slot = nullptr;
   HT_TRY(ht_scratch(ctx, HT_S_DENSE, most, &slot));
@@ -807,7 +816,8 @@ int build_dense(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, DenseSide& 
   D.n_cols = host[n_rb + 2] * DENSE_COLS;
   const size_t cell_bytes = (size_t)n_tiles * DENSE_ROWS * DENSE_COLS;
   const int64_t left = n_ent - taken;
-  if ((int64_t)cell_bytes + 8 * left + 16 * ht_row_items_bound(V, left, REST_SEG) > room / 4) return HT_ENOMEM;
+  const int seg = rest_seg(V, left);
+  if ((int64_t)cell_bytes + 8 * left + 16 * ht_row_items_bound(V, left, seg) > room / 4) return HT_ENOMEM;
   D.tiles.add<uint8_t>(cell_bytes);
   D.tiles.add<int32_t>((size_t)n_tiles);
   D.tiles.add<DenseSeg>(segs.size());
@@ -841,7 +851,7 @@ int build_dense(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, DenseSide& 
   HT_HIP(ctx, hipStreamSynchronize(st));
   D.n_rest = host[0];
   const size_t n_rest = (size_t)std::max<int64_t>(D.n_rest, 1);
-  const size_t items = (size_t)ht_row_items_bound(V, D.n_rest, REST_SEG), cuts = (size_t)ht_row_cuts_bound(D.n_rest, REST_SEG, n_rb * DENSE_ROWS);
+  const size_t items = (size_t)ht_row_items_bound(V, D.n_rest, seg), cuts = (size_t)ht_row_cuts_bound(D.n_rest, seg, n_rb * DENSE_ROWS);
   D.rest.add<int32_t>(n_rest);
   D.rest.add<float>(n_rest);
   D.rest.add<int64_t>((size_t)V + 1);
@@ -857,7 +867,7 @@ int build_dense(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, DenseSide& 
   k_keep_copy<<<(unsigned)et, TB, 0, st>>>(t.keep.p, n_ent, t.kbase.p, idx, w, g->s.p, D.idx.p, D.w.p);
   HT_LAUNCH_CHECK(ctx);
   HT_TRY(ht_scan_i32(ctx, t.rest.p, rptr.p, V, true));
-  HT_TRY(ht_graph_row_items(ctx, V, rptr.p, D.n_rest, D.idx.p, D.pos.p, REST_SEG, HT_S_DENSE, nullptr, &D.items));
+  HT_TRY(ht_graph_row_items(ctx, V, rptr.p, D.n_rest, D.idx.p, D.pos.p, seg, HT_S_DENSE, nullptr, &D.items));
   D.ok = true;
   return HT_OK;
 }
