@@ -8,6 +8,7 @@
 //       slices whose partial tiles are added in slice order (no atomics).
 // The small operand W is first packed into a zero-padded tile-aligned copy.
 #include <algorithm>
+#include <type_traits>
 
 #include "ht_internal.h"
 
@@ -335,14 +336,16 @@ __global__ void __launch_bounds__(512) k_rows_w(const float* __restrict__ A, int
   }
 }
 
+// MASKED: B counts where mask.ref is positive, and is 0 elsewhere (dz, where nothing else reads it: 2.45 M rows, 100 x 256, with a pass that writes it 2.61 ms, so 1.64; 233 k, 602 x
+// 256 719 us, 714).
 // Partial tile of C[K x N] = A[M x K]^T B[M x N] over the M-slice blockIdx.z (rows tab[2z] .. tab[2z + 1], or slice_rows each).
 // P[slice][K x N] dense.  Block tile: BM output rows (k) x BN output columns.
 // What bounds it is the loads of a step of 16 rows, PD steps of which are in flight: up to 64 columns two, wider ones, whose accumulators leave fewer registers, one.  us, loads
 // with bounds tests one step ahead | without | two ahead | four | six, at rows x K x N: 2.45 M x 256 x 47 973 | - | 849 | 885 | 841, 1 M x 64 x 64 221 | - | 196 | 215 | 201, 60 k x 129
 // x 60 42 | - | 35 | 37 | 38, 20 k x 50 x 33 17.0 | - | 16.5 | 17.8 | 17.8; wider: 20 k x 256 x 100 32 | 26 | 27 (| 27 three), 8 k x 200 x 100 22 | 19 | 20.
-template <int BN, int WM, int WN, int TI, int TJ, int PD>
+template <int BN, int WM, int WN, int TI, int TJ, int PD, bool MASKED>
 __global__ void __launch_bounds__(256) k_gemm_tn(const float* __restrict__ A, int64_t lda,
-                                                 const float* __restrict__ B, int64_t ldb, float* __restrict__ P,
+                                                 const float* __restrict__ B, int64_t ldb, ReluMask mask, float* __restrict__ P,
                                                  int64_t M, int K, int N, int64_t slice_rows,
                                                  const int64_t* __restrict__ tab) {
   static_assert(WM * WN == 4 && WM * TI * 32 == BM && WN * TJ * 32 == BN, "tile shape");
@@ -368,10 +371,10 @@ __global__ void __launch_bounds__(256) k_gemm_tn(const float* __restrict__ A, in
   static_assert(NA * 256 == BK * BM / 4 && NB * 256 == BK * BN / 4, "tile loads must divide among 256 threads");
   // The tiles of PD steps are on their way at once.  Loads have no condition (outside the operands they read the last row, the last columns again), so that the
   // waits count only the loads of the step that is next; what lies outside is cleared on the way into LDS.
-  float4 ra[PD][NA], rb[PD][NB];
+  float4 ra[PD][NA], rb[PD][NB], rm[MASKED ? PD : 1][NB];
   const bool full_a = kc0 + BM <= K, full_b = n0 + BN <= N;
   const int last_a = (K - 1) & ~3, last_b = (N - 1) & ~3;
-  auto fetch = [&](int64_t mm0, float4* pa, float4* pb) {
+  auto fetch = [&](int64_t mm0, float4* pa, float4* pb, float4* pm) {
 #pragma unroll
     for (int u = 0; u < NA; ++u) {
       const int f = tid + u * 256, c = kc0 + (f % (BM / 4)) * 4;
@@ -383,13 +386,14 @@ __global__ void __launch_bounds__(256) k_gemm_tn(const float* __restrict__ A, in
       const int f = tid + u * 256, c = n0 + (f % (BN / 4)) * 4;
       const int64_t r = mm0 + f / (BN / 4);
       pb[u] = ld4g(B + (r < me ? r : me - 1) * ldb + (c < last_b ? c : last_b));
+      if (MASKED) pm[u] = ld4g(mask.ref + (r < me ? r : me - 1) * mask.ld + (c < last_b ? c : last_b));
     }
   };
   auto inside = [&](float4 v, bool row, int c, int n) {
     const int left = row ? n - c : 0;
     return make_float4(left > 0 ? v.x : 0.f, left > 1 ? v.y : 0.f, left > 2 ? v.z : 0.f, left > 3 ? v.w : 0.f);
   };
-  auto stash = [&](int64_t mm0, const float4* pa, const float4* pb) {
+  auto stash = [&](int64_t mm0, const float4* pa, const float4* pb, const float4* pm) {
     const bool full_m = mm0 + BK <= me;
 #pragma unroll
     for (int u = 0; u < NA; ++u) {
@@ -401,21 +405,23 @@ __global__ void __launch_bounds__(256) k_gemm_tn(const float* __restrict__ A, in
     for (int u = 0; u < NB; ++u) {
       const int f = tid + u * 256;
       const int mr = f / (BN / 4), cv = (f % (BN / 4)) * 4;
-      *reinterpret_cast<float4*>(Bs + mr * (BN + 4) + cv) = full_m && full_b ? pb[u] : inside(pb[u], mm0 + mr < me, n0 + cv, N);
+      float4 v = pb[u];
+      if (MASKED) v = make_float4(pm[u].x > 0.f ? v.x : 0.f, pm[u].y > 0.f ? v.y : 0.f, pm[u].z > 0.f ? v.z : 0.f, pm[u].w > 0.f ? v.w : 0.f);
+      *reinterpret_cast<float4*>(Bs + mr * (BN + 4) + cv) = full_m && full_b ? v : inside(v, mm0 + mr < me, n0 + cv, N);
     }
   };
   if (ms < me) {
 #pragma unroll
-    for (int u = 0; u < PD; ++u) fetch(ms + u * BK, ra[u], rb[u]);
+    for (int u = 0; u < PD; ++u) fetch(ms + u * BK, ra[u], rb[u], rm[MASKED ? u : 0]);
   }
   for (int64_t m1 = ms; m1 < me; m1 += PD * BK) {
 #pragma unroll
     for (int u = 0; u < PD; ++u) {
       const int64_t mm0 = m1 + u * BK;
       if (mm0 >= me) break;
-      stash(mm0, ra[u], rb[u]);
+      stash(mm0, ra[u], rb[u], rm[MASKED ? u : 0]);
       __syncthreads();
-      fetch(mm0 + PD * BK, ra[u], rb[u]);
+      fetch(mm0 + PD * BK, ra[u], rb[u], rm[MASKED ? u : 0]);
 #pragma unroll
       for (int kk = 0; kk < BK; kk += 2) {
         float af[TI], bf[TJ];
@@ -575,7 +581,8 @@ struct SplitTile {
 static_assert(BK * (BM + 4) * sizeof(float) <= 6 * SB * sizeof(__bf16), "the fp32 stages fit where the split ones were");
 
 // Partial tile of C[K x N] = A^T B over a slice of rows, as k_gemm_tn
-__global__ void __launch_bounds__(256, 2) k_split_tn(const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
+template <bool MASKED>
+__global__ void __launch_bounds__(256, 2) k_split_tn(const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb, ReluMask mask,
                                                   float* __restrict__ P, int64_t M, int K, int N, int64_t slice_rows,
                                                   const int64_t* __restrict__ tab) {
   __shared__ __attribute__((aligned(16))) __bf16 As[6 * SB];
@@ -591,7 +598,7 @@ __global__ void __launch_bounds__(256, 2) k_split_tn(const float* __restrict__ A
   const int c = tid & 127, st = __builtin_amdgcn_readfirstlane(tid >> 7);
   const bool has_a = kc0 + c < K, has_b = n0 + c < N;
   const unsigned ca = has_a ? kc0 + c : 0, cb = has_b ? n0 + c : 0;
-  float ra[16], rb[16];
+  float ra[16], rb[16], rm[MASKED ? 16 : 1];
   auto fetch = [&](int64_t mm) {
     const int64_t r0 = mm + st * 16;
     if (r0 + 16 <= me) {
@@ -599,14 +606,21 @@ __global__ void __launch_bounds__(256, 2) k_split_tn(const float* __restrict__ A
       for (int u = 0; u < 16; ++u) {
         ra[u] = (A + (r0 + u) * lda)[ca];
         rb[u] = (B + (r0 + u) * ldb)[cb];
+        if (MASKED) rm[u] = (mask.ref + (r0 + u) * mask.ld)[cb];
       }
     } else {
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
         ra[u] = r0 + u < me ? (A + (r0 + u) * lda)[ca] : 0.f;
         rb[u] = r0 + u < me ? (B + (r0 + u) * ldb)[cb] : 0.f;
+        if (MASKED) rm[u] = r0 + u < me ? (mask.ref + (r0 + u) * mask.ld)[cb] : 0.f;
       }
     }
+  };
+  auto masked = [&] {   // (when the loads are there, not where they are issued)
+    if (MASKED)
+#pragma unroll
+      for (int u = 0; u < 16; ++u) rb[u] = rm[u] > 0.f ? rb[u] : 0.f;
   };
   auto put = [&](const float* v, bool has, __bf16* S) {
 #pragma unroll
@@ -629,6 +643,7 @@ __global__ void __launch_bounds__(256, 2) k_split_tn(const float* __restrict__ A
   if (ms < me) fetch(ms);
   for (int64_t mm = ms; mm < me; mm += SK) {
     put(ra, has_a, As);
+    masked();
     put(rb, has_b, Bs);
     __syncthreads();
     if (mm + SK < me) fetch(mm + SK);
@@ -639,7 +654,7 @@ __global__ void __launch_bounds__(256, 2) k_split_tn(const float* __restrict__ A
   if (__syncthreads_or(!t.all_finite()))
     t.in_fp32(reinterpret_cast<float*>(As), reinterpret_cast<float*>(Bs), ms, me, wm, wn, l32, half,
               [&](int r, int64_t m) { return kc0 + r < K ? A[m * lda + kc0 + r] : 0.f; },
-              [&](int q, int64_t m) { return n0 + q < N ? B[m * ldb + n0 + q] : 0.f; });
+              [&](int q, int64_t m) { return n0 + q < N && (!MASKED || mask.ref[m * mask.ld + n0 + q] > 0.f) ? B[m * ldb + n0 + q] : 0.f; });
   else
     t.unscale();
   float* Ps = P + (int64_t)blockIdx.z * K * N;
@@ -872,7 +887,7 @@ size_t pad256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 // rows: destination rows behind all slices
 int launch_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t M, int32_t K,
-              int32_t N, int64_t slice_rows, int64_t slices, const int64_t* tab, int64_t rows, int accumulate, TnLater* later) {
+              int32_t N, int64_t slice_rows, int64_t slices, const int64_t* tab, int64_t rows, int accumulate, TnLater* later, ReluMask mask) {
   const int64_t kn = (int64_t)K * N;
   float* P = nullptr;
   const size_t bytes = pad256((size_t)(slices * kn) * 4);
@@ -884,12 +899,16 @@ int launch_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const fl
     HT_TRY(ht_scratch(ctx, HT_S_TNPART, bytes, (void**)&P));
   }
   dim3 grid((unsigned)((K + BM - 1) / BM), (unsigned)(N > 64 ? (N + 127) / 128 : 1), (unsigned)slices);
-  if (use_split_tn(rows, K, N))
-    k_split_tn<<<grid, 256, 0, st>>>(A, lda, B, ldb, P, M, K, N, slice_rows, tab);
-  else if (N > 64)
-    k_gemm_tn<128, 2, 2, 2, 2, 1><<<grid, 256, 0, st>>>(A, lda, B, ldb, P, M, K, N, slice_rows, tab);
-  else
-    k_gemm_tn<64, 4, 1, 1, 2, 2><<<grid, 256, 0, st>>>(A, lda, B, ldb, P, M, K, N, slice_rows, tab);
+  auto launch = [&](auto masked) {
+    constexpr bool MASKED = decltype(masked)::value;
+    if (use_split_tn(rows, K, N))
+      k_split_tn<MASKED><<<grid, 256, 0, st>>>(A, lda, B, ldb, mask, P, M, K, N, slice_rows, tab);
+    else if (N > 64)
+      k_gemm_tn<128, 2, 2, 2, 2, 1, MASKED><<<grid, 256, 0, st>>>(A, lda, B, ldb, mask, P, M, K, N, slice_rows, tab);
+    else
+      k_gemm_tn<64, 4, 1, 1, 2, 2, MASKED><<<grid, 256, 0, st>>>(A, lda, B, ldb, mask, P, M, K, N, slice_rows, tab);
+  };
+  mask.ref ? launch(std::true_type{}) : launch(std::false_type{});
   HT_LAUNCH_CHECK(ctx);
   if (leave) {
     ctx->tn_used += bytes;
@@ -905,8 +924,8 @@ int launch_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const fl
 }  // namespace
 
 int ht_gemm_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
-               int64_t M, int32_t K, int32_t N, int accumulate, TnLater* later) {
-  if ((lda & 3) || (ldb & 3)) return ht_set_err(ctx, HT_ESHAPE, "gemm: row pitch must be a multiple of 4");
+               int64_t M, int32_t K, int32_t N, int accumulate, TnLater* later, ReluMask mask) {
+  if ((lda & 3) || (ldb & 3) || (mask.ld & 3)) return ht_set_err(ctx, HT_ESHAPE, "gemm: row pitch must be a multiple of 4");
   if (K <= 0 || N <= 0) return HT_OK;
   if (M <= 0) {
     if (!accumulate) HT_TRY(ht_fill_zero(ctx, st, C, (size_t)K * N * 4));
@@ -914,7 +933,7 @@ int ht_gemm_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const f
   }
   int64_t rows, slices;
   SliceRule{tn_tiles(K, N), true}.cut(M, &rows, &slices);
-  return launch_tn(ctx, st, A, lda, B, ldb, C, M, K, N, rows, slices, nullptr, M, accumulate, later);
+  return launch_tn(ctx, st, A, lda, B, ldb, C, M, K, N, rows, slices, nullptr, M, accumulate, later, mask);
 }
 
 size_t ht_gemm_tn_bytes(int64_t M, int32_t K, int32_t N) {
@@ -995,13 +1014,14 @@ int ht_flush_products(ht_ctx* ctx, hipStream_t st, bool drop) {
 // The row groups' sums one after the other, as ht_gemm_tn called once per group would add them, in as few launches as the
 // partial tiles' memory allows.
 int ht_gemm_tn_groups(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int32_t K,
-                      int32_t N, const std::vector<int64_t>& groups, const int64_t* d_groups, TnLater* later) {
+                      int32_t N, const std::vector<int64_t>& groups, const int64_t* d_groups, TnLater* later, ReluMask mask) {
   const size_t G = groups.size() / 2;
   if (G <= 1) {
     const int64_t r0 = G ? groups[0] : 0;
-    return ht_gemm_tn(ctx, st, A + r0 * lda, lda, B + r0 * ldb, ldb, C, G ? groups[1] - r0 : 0, K, N, 0, later);
+    return ht_gemm_tn(ctx, st, A + r0 * lda, lda, B + r0 * ldb, ldb, C, G ? groups[1] - r0 : 0, K, N, 0, later,
+                      ReluMask{mask.ref ? mask.ref + r0 * mask.ld : nullptr, mask.ld});
   }
-  if ((lda & 3) || (ldb & 3)) return ht_set_err(ctx, HT_ESHAPE, "gemm: row pitch must be a multiple of 4");
+  if ((lda & 3) || (ldb & 3) || (mask.ld & 3)) return ht_set_err(ctx, HT_ESHAPE, "gemm: row pitch must be a multiple of 4");
   if (K <= 0 || N <= 0) return HT_OK;
   const SliceRule rule{tn_tiles(K, N)};
   int64_t all = 0;
@@ -1013,7 +1033,7 @@ int ht_gemm_tn_groups(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, 
     HT_TRY(ht_scratch(ctx, HT_S_TNTAB, (size_t)total * 16, (void**)&tab));
     k_slice_table<<<(unsigned)(g1 - g0), 256, 0, st>>>(d_groups + 2 * g0, rule, tab);
     HT_LAUNCH_CHECK(ctx);
-    HT_TRY(launch_tn(ctx, st, A, lda, B, ldb, C, 0, K, N, 0, total, tab, all, g0 > 0, g1 == G ? later : nullptr));
+    HT_TRY(launch_tn(ctx, st, A, lda, B, ldb, C, 0, K, N, 0, total, tab, all, g0 > 0, g1 == G ? later : nullptr, mask));
     g0 = g1;
   }
   return HT_OK;

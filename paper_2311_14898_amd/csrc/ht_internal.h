@@ -611,8 +611,13 @@ struct TnLater {
   float* column[2] = {nullptr, nullptr};
   bool left = false;
 };
+// `mask`: B's values count where mask.ref (as many rows and columns) is positive, and are 0 elsewhere.
+struct ReluMask {
+  const float* ref = nullptr;
+  int64_t ld = 0;
+};
 int ht_gemm_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
-               int64_t M, int32_t K, int32_t N, int accumulate, TnLater* later = nullptr);
+               int64_t M, int32_t K, int32_t N, int accumulate, TnLater* later = nullptr, ReluMask mask = ReluMask());
 // Products may leave their sums to ht_step from here on, where all of them together take little memory; `bytes`: their partial tiles.
 int ht_defer_products(ht_ctx* ctx, const std::vector<size_t>& bytes);
 // Adds up what was left (before something else needs it, or after an error: `drop`).
@@ -624,7 +629,7 @@ size_t ht_gemm_tn_bytes(int64_t M, int32_t K, int32_t N);
 void ht_gemm_groups_wants(int32_t K, int32_t N, const std::vector<int64_t>& groups, std::vector<ScratchWant>* want);
 // C[K x N] = sum over the row groups [groups[2g], groups[2g+1]) of A^T B, added group by group (d_groups: the same on the device).
 int ht_gemm_tn_groups(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int32_t K,
-                      int32_t N, const std::vector<int64_t>& groups, const int64_t* d_groups, TnLater* later = nullptr);
+                      int32_t N, const std::vector<int64_t>& groups, const int64_t* d_groups, TnLater* later = nullptr, ReluMask mask = ReluMask());
 // Partial tiles of such a call, all groups together.
 size_t ht_gemm_groups_bytes(int32_t K, int32_t N, const std::vector<int64_t>& groups);
 

@@ -83,3 +83,31 @@ def test_weight_gradients_by_steps_of_rows(V, K, N):
     finally:
         B.ht_graph_destroy(g)
         B.ht_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("V,K,N", [(1, 3, 5), (17, 33, 7), (3_000, 129, 64), (3_001, 40, 130), (40_003, 70, 66)])
+def test_masked_weight_gradients(V, K, N):
+    """Without an input gradient grad W masks dz on the way: the bits of the call that also makes one, which masks it first."""
+    ctx = B.ht_ctx_create(0)
+    none = torch.empty(0, dtype=torch.int32, device="cuda")
+    g = B.ht_partition(ctx, V, none, none, 3)
+    try:
+        gen = torch.Generator().manual_seed(V)
+        A, dH, H, W = B.to_matrix(torch.randn(V, K, generator=gen)), B.to_matrix(torch.randn(V, N, generator=gen)), torch.randn(V, N, generator=gen), torch.randn(K, N, generator=gen).cuda()
+        H[::3] = 0.0
+        H[::7] = float("nan")                        # (not positive: the derivative is 0)
+        Hd = B.to_matrix(H)
+        A[:, K:], dH[:, N:], Hd[:, N:] = float("nan"), float("inf"), float("nan")
+        got = []
+        for dX in (None, B.alloc_matrix(V, K).zero_()):
+            dW = torch.full((K, N), 7.0, device="cuda")
+            B.ht_layer_bwd(ctx, g, K, N, B.HT_ACT_RELU, A, W, dH, dW, dH_in=dX, H_out=Hd)
+            B.ht_sync(ctx)
+            got.append(dW)
+        assert torch.equal(*got)
+        dz = torch.where(H > 0, dH[:, :N].cpu(), torch.zeros(())).double()
+        want, mag = A[:, :K].cpu().double().t() @ dz, A[:, :K].cpu().double().abs().t() @ dz.abs()
+        assert ((got[0].cpu().double() - want).abs() <= (V + 4) * 2.0 ** -24 * mag).all()
+    finally:
+        B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)
