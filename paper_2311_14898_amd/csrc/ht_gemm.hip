@@ -601,19 +601,29 @@ __global__ void __launch_bounds__(256, 2) k_split_tn(const float* __restrict__ A
   float ra[16], rb[16], rm[MASKED ? 16 : 1];
   auto fetch = [&](int64_t mm) {
     const int64_t r0 = mm + st * 16;
-    if (r0 + 16 <= me) {
+    // (row pointers that step along: kept for all rows of a stage, they take more scalar registers than there are)
+    const float *pa = A + r0 * lda, *pb = B + r0 * ldb, *pm = MASKED ? mask.ref + r0 * mask.ld : nullptr;
+    asm volatile("" : "+s"(pa), "+s"(pb), "+s"(pm));
+    const int64_t left = me - r0;
+    if (left >= 16) {
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
-        ra[u] = (A + (r0 + u) * lda)[ca];
-        rb[u] = (B + (r0 + u) * ldb)[cb];
-        if (MASKED) rm[u] = (mask.ref + (r0 + u) * mask.ld)[cb];
+        ra[u] = pa[ca];
+        rb[u] = pb[cb];
+        if (MASKED) rm[u] = pm[cb];
+        pa += lda;
+        pb += ldb;
+        if (MASKED) pm += mask.ld;
       }
     } else {
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
-        ra[u] = r0 + u < me ? (A + (r0 + u) * lda)[ca] : 0.f;
-        rb[u] = r0 + u < me ? (B + (r0 + u) * ldb)[cb] : 0.f;
-        if (MASKED) rm[u] = r0 + u < me ? (mask.ref + (r0 + u) * mask.ld)[cb] : 0.f;
+        ra[u] = u < left ? pa[ca] : 0.f;
+        rb[u] = u < left ? pb[cb] : 0.f;
+        if (MASKED) rm[u] = u < left ? pm[cb] : 0.f;
+        pa += lda;
+        pb += ldb;
+        if (MASKED) pm += mask.ld;
       }
     }
   };
