@@ -84,8 +84,9 @@ __device__ __forceinline__ float dot4(float4 a, float4 b, float s) { return fmaf
 unsigned row_grid(int64_t rows, int lpr) { return (unsigned)std::min<int64_t>((rows * lpr + 255) / 256, 8192); }
 int row_lanes(int64_t ld) { return ld <= 32 ? 8 : ld <= 64 ? 16 : ld <= 128 ? 32 : 64; }
 
-// p[v] = a_dst . T[v], q[v] = a_src . T[v]; lpr lanes per vertex
-__global__ void __launch_bounds__(256) k_gat_pq(const float* __restrict__ T, int64_t ld, int d, const float* __restrict__ a_dst,
+// p[v] = a_dst . T[v], q[v] = a_src . T[v]; lpr lanes per vertex.  The pads of T up to the next multiple of 4 columns, which later passes read as data, become
+// zeros on the way (clearing all of T before the product was a launch of its own).
+__global__ void __launch_bounds__(256) k_gat_pq(float* __restrict__ T, int64_t ld, int d, const float* __restrict__ a_dst,
                                                 const float* __restrict__ a_src, int64_t V, float* __restrict__ p,
                                                 float* __restrict__ q, int lpr) {
   __shared__ AttVec sa;
@@ -93,8 +94,14 @@ __global__ void __launch_bounds__(256) k_gat_pq(const float* __restrict__ T, int
   const int rpb = 256 / lpr, ll = threadIdx.x % lpr;
   for (int64_t v = (int64_t)blockIdx.x * rpb + threadIdx.x / lpr; v < V; v += (int64_t)gridDim.x * rpb) {
     float sp = 0.f, sq = 0.f;
-    for (int c = ll * 4; c < d; c += lpr * 4) {   // (the pads of t up to the next multiple of 4 are zero)
-      const float4 t = ld4(T + v * ld + c);
+    for (int c = ll * 4; c < d; c += lpr * 4) {
+      float4 t = ld4(T + v * ld + c);
+      if (c + 4 > d) {
+        if (c + 1 >= d) t.y = 0.f;
+        if (c + 2 >= d) t.z = 0.f;
+        t.w = 0.f;
+        st4(T + v * ld + c, t);
+      }
       sp = dot4(sa.dst[c >> 2], t, sp);
       sq = dot4(sa.src[c >> 2], t, sq);
     }
@@ -810,8 +817,6 @@ int prepare(ht_ctx* ctx, const ht_graph* g, const ht_gat_desc* desc, const ht_te
             const float* a_src, const GatWs* ws, ht_stats* st, Timer* tm, Link* lk) {
   hipStream_t s = ctx->stream;
   const int64_t V = std::max<int64_t>(g->V, 1);
-  // (a row's float4 reads end at the next multiple of 4 columns: those pads are read, and 0 times a pad must be 0)
-  if (desc->d_out & 3) HT_TRY(ht_fill_zero(ctx, s, ws->T, (size_t)g->V * ws->ld_t * 4));
   const bool host = on_host(H);
   const int64_t step = host ? ctx->link_block_rows : BLOCK_HBM;   // rows per staged block / per GEMM call
   float* stage[2] = {nullptr, nullptr};
