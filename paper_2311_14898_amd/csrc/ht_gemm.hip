@@ -20,8 +20,8 @@ constexpr int BK = 16;        // reduction depth of one LDS stage
 constexpr int BM = 128;       // rows of A per block (NN) / output rows per block (TN)
 // Rows up to which a product may read W as it is, a launch less (2.5 us and the gap before the next one).  Its single loads and bounds tests cost about
 // 0.1 us a step of 16 of the reduction, in each round of blocks over the chip, so that it pays for short chains alone.  In place - packed (us), layers
-// without edges, 300 | 3,000 | 10,000 | 20,000 | 32,768 rows: 64 x 32 -2.6 | -2.1 | -2.3 | -1.4 | -1.3, 128 x 256 -1.5 | -1.3 | -1.5 | -0.3 | +1.2, 256 x 256
-// -0.3 | 0.0 | -1.0 | +1.0 | +3.7, 602 x 256 +3.7 | +3.3 | +2.8 | +8.6 | +10.5, 256 x 41 -1.4 | -0.7 | -1.4 | -1.7 | -2.2, 602 x 16 +0.8 | +0.9 | +0.6 | +0.3 | -0.4;
+// without edges, 300 | 3,000 | 10,000 | 20,000 | 32,768 rows: 128 x 256 -1.5 | -1.3 | -1.5 | -0.3 | +1.2, 256 x 256
+// -0.3 | 0.0 | -1.0 | +1.0 | +3.7, 602 x 256 +3.7 | +3.3 | +2.8 | +8.6 | +10.5, 256 x 41 -1.4 | -0.7 | -1.4 | -1.7 | -2.2;
 // the transpose, 256 columns to 128 +0.7 | +1.6 | 0.0 | +0.4 | +3.0, 129 to 300 -0.8 | -1.2 | -2.2 | +0.2 | +2.7.
 constexpr int64_t HT_PACK_ROWS = 32768;
 constexpr int HT_PACK_CHAIN = 192, HT_PACK_CHAIN_NARROW = 512;   // (up to 64 columns a block stores half as much of W at a step)
@@ -197,8 +197,9 @@ __global__ void __launch_bounds__(256) k_gemm_nn(const float* __restrict__ A, in
 // C = A W (+ReLU), or A W^T, with the block's columns of W in LDS and the rows of A straight to registers, for widths that k_gemm_nn would pad
 // (rows_shape).  A wave owns 32 rows x TJ tiles of 32 columns, takes strip after strip of rows, and waits for no other wave once W is there; its rows' pieces
 // come NBUF steps of 32 values ahead, across strips.  Lane l32 + 32 half holds row l32 and the values 8 q + 4 half .. + 3 of a step (a load covers 32
-// contiguous bytes of each row, a step its whole cache line); W lies in LDS in fours along the reduction, so that a lane's four values of a column are
-// one read.  The order of an element's sum is that of the reduction alone: it does not depend on rows, tiles or blocks.
+// contiguous bytes of each row, a step its whole cache line); two exchanges between the halves of the wave turn four registers with the values 0 .. 3 | 4 .. 7
+// into 0 | 1, 2 | 3, 4 | 5, 6 | 7, so that an element is summed up in the order of k_gemm_nn, to the same bits.  W lies in LDS as fours of every second value of the
+// reduction, 0, 2, 4, 6 and 1, 3, 5, 7 of each eight: what a lane multiplies with them is one read.
 // What bounds it: the fp32 matrix cores (2.45 M rows, 256 x 256: 79 % busy, as k_gemm_nn's, and 85 without its loads and stores), and for
 // narrow results the rows' reads (1 M x 64 x 20: 5 TB/s).
 constexpr int RS = 32;                       // values of a step
@@ -266,7 +267,10 @@ __global__ void __launch_bounds__(512) k_rows_w(const float* __restrict__ A, int
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
       const int i = i0 + x * blockDim.x, k4 = T ? i / (8 * NT) * 8 + i % 8 : i / NT;
-      if (i < n_w && k4 < K4) Bs[k4 * P + (T ? i / 8 % NT : i % NT)] = v[x];
+      if (i >= n_w || k4 >= K4) continue;
+      float4* to = Bs + (k4 & ~1) * P + (T ? i / 8 % NT : i % NT);
+      reinterpret_cast<float2*>(to)[k4 & 1] = make_float2(v[x].x, v[x].z);
+      reinterpret_cast<float2*>(to + P)[k4 & 1] = make_float2(v[x].y, v[x].w);
     }
   }
   __syncthreads();
@@ -291,7 +295,10 @@ __global__ void __launch_bounds__(512) k_rows_w(const float* __restrict__ A, int
           float4 b[TJ];
 #pragma unroll
           for (int j = 0; j < TJ; ++j) b[j] = B[q * 2 * P + j * 32];
-          const float4 a = buf[u][q];
+          const float4 v = buf[u][q];
+          const auto xy = __builtin_amdgcn_permlane32_swap(__float_as_uint(v.x), __float_as_uint(v.y), false, false);
+          const auto zw = __builtin_amdgcn_permlane32_swap(__float_as_uint(v.z), __float_as_uint(v.w), false, false);
+          const float4 a = make_float4(__uint_as_float(xy[0]), __uint_as_float(zw[0]), __uint_as_float(xy[1]), __uint_as_float(zw[1]));
 #pragma unroll
           for (int j = 0; j < TJ; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b[j].x, acc[j], 0, 0, 0);
 #pragma unroll

@@ -63,6 +63,29 @@ def test_rows_do_not_depend_on_their_number(K, N):
     assert torch.equal(rows[0], rows[1]) and torch.equal(rows[0], rows[2])
 
 
+@pytest.mark.parametrize("K", [1, 7, 17, 50, 67, 130])
+@pytest.mark.parametrize("N", [3, 32, 65, 129])
+def test_columns_do_not_depend_on_the_width(K, N):
+    """The same bits whether a column is among those of a padded width or of one that fills its blocks."""
+    V, wide = 5_000, 64 if N <= 32 else 256
+    gen = torch.Generator().manual_seed(K)
+    H, W = torch.randn(V, K, generator=gen), torch.randn(K, wide, generator=gen)
+    none = torch.empty(0, dtype=torch.int32, device="cuda")
+    ctx = B.ht_ctx_create(0)
+    g = B.ht_partition(ctx, V, none, none, 1)
+    try:
+        got = []
+        for n in (N, wide):
+            out = B.alloc_matrix(V, n)
+            B.ht_layer_fwd(ctx, g, K, n, B.HT_ACT_NONE, B.to_matrix(H), W[:, :n].contiguous().cuda(), out)
+            B.ht_sync(ctx)
+            got.append(out[:, :N].cpu())
+        assert torch.equal(*got)
+    finally:
+        B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)
+
+
 @pytest.mark.parametrize("V", [1, 15, 17, 33, 49, 1_000, 20_011])
 @pytest.mark.parametrize("K,N", [(1, 1), (5, 4), (33, 7), (129, 64), (128, 61), (130, 66), (40, 130)])
 def test_weight_gradients_by_steps_of_rows(V, K, N):
