@@ -440,6 +440,7 @@ int ht_ctx_create(ht_ctx** out, int device, void* hip_stream) {
   if (const char* v = getenv("HT_DENSE")) c->dense = atoi(v);
   if (const char* v = getenv("HT_FINE")) c->fine = atoi(v);
   if (const char* v = getenv("HT_DENSE_WORK")) c->dense_work = std::max<int64_t>(1, atoll(v));
+  if (const char* v = getenv("HT_DENSE_WIDE")) c->dense_wide = atoll(v);
   if (const char* v = getenv("HT_FINE_WORK")) {
     c->fine_work = std::max<int64_t>(1, atoll(v));
     c->fine_rows = 0;

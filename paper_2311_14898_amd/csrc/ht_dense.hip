@@ -627,8 +627,6 @@ __global__ void __launch_bounds__(512) k_dense(DenseArgs a) {
   for (int i = 0; i < PER; ++i) out[(int64_t)(r0 + i) * a.out_ld + f] = acc[i];
 }
 
-constexpr int64_t WIDE_TILES = 32768;
-
 // Scratch memory of the making (slot HT_S_DENSE).
 struct DenseTmp {
   DevBlock blk;
@@ -955,7 +953,7 @@ int ht_dense_launch(ht_ctx* ctx, hipStream_t st, const DenseSide& D, const float
   // Blocks of 128 features decode a cell half as often, blocks of 64 leave shorter last rounds and take what is left behind the last 128 along.  us, 128 (and 64) | 64 alone: 22.6 k
   // tiles x 602 1546 | 1634, x 256 610 | 659; 4.9 k x 256 346 | 320, x 100 199 | 197; 7 k x 129 312 | 283.
   int n128 = d / 128 + (d % 128 > 64);
-  if (D.n_tiles * n128 < WIDE_TILES) n128 = 0;
+  if (D.n_tiles * n128 < ctx->dense_wide) n128 = 0;
   DenseArgs a{D.cells.p, D.tile_cg.p, D.segs.p, D.cols.p, src, s, ld, out_ld, d, 0, partial};
   if (n128 > 0) {
     k_dense<128><<<dim3((unsigned)D.n_segs, n128), 512, 0, st>>>(a);

@@ -22,6 +22,8 @@ constexpr int HT_SEG = 256;
 // (170) 195 | 195, 1e5, 10 M, 128 (510) 675 | 696; 3e4, 12 M, 300 (1,200) 1,096 | 824, 1e5, 40 M, 128 (2,200) 1,581 | 1,162.  A plan takes a
 // millisecond or two to make, so it is left where a pass would gain less than some 100 us; short items (0.2 ms) where it would gain less than 5.
 constexpr int64_t HT_DENSE_WORK = 1000000000, HT_FINE_WORK = 200000000;
+// Dense tiles times blocks of 128 columns from which those are taken and not blocks of 64 (both sides: ht_dense_launch).
+constexpr int64_t HT_DENSE_WIDE = 32768;
 // ... and bytes of rows for short items: fewer stay in the L2s whatever the order (which shapes gain beyond that: short_items_pay).
 constexpr int64_t HT_FINE_ROWS = (int64_t)24 << 20;
 
@@ -108,6 +110,7 @@ struct ht_ctx {
   int dense = 1;               // HT_DENSE=0: no products over a graph's dense tiles (ht_dense.hip)
   int fine = 1;                // HT_FINE=0: no shorter work items for training passes
   int64_t dense_work = HT_DENSE_WORK, fine_work = HT_FINE_WORK, fine_rows = HT_FINE_ROWS;   // HT_DENSE_WORK, HT_FINE_WORK, HT_FINE_ROWS
+  int64_t dense_wide = HT_DENSE_WIDE;   // HT_DENSE_WIDE
   int64_t unit_small = (int64_t)1 << 30;   // floats of rows below which column units address them in 32 bits (HT_UNIT_SMALL)
   int fuse_update = 0;  // HT_FUSE_UPDATE=1: layers that keep no aggregate run aggregate + transform as one kernel (A/B)
   int n_threads = 0;  // host threads for CPU-side accumulation (0 = chosen on first use)
