@@ -690,39 +690,56 @@ __global__ void __launch_bounds__(256, 2) k_split_tn(const float* __restrict__ A
 }
 
 // C[i] (+)= the slices' partial sums, one after the other in slice order.  The adds of one element are a chain, the loads are
-// not: a block takes 64 elements, its four waves bring 64 slices at a time into LDS (16 loads in flight per lane) while the
-// first wave adds the 64 before them.  (One thread per element that loads as it adds took 43 us where this takes 15.)
+// not: a block takes E elements, its four waves bring 4,096 values at a time into LDS (16 loads in flight per lane) while E
+// lanes add those before them.  (One thread per element that loads as it adds took 43 us where this takes 15.)  What bounds it: the loads that the blocks there are
+// have in flight, so tiles of few elements go 16 to a block: a layer of 1 M vertices, 64 x 64 (3,906 slices, 69 us of it) 3.084 -> 3.047 ms.
+// Large ones stay at 64, whose reads are whole cache lines: an epoch of 233 k vertices, 602-256-41 12.63 | 12.65 ms with 64 | 16.
+template <int E>
 __global__ void __launch_bounds__(256) k_reduce_slices(const float* __restrict__ P, int64_t n, int slices, int accumulate,
                                                        float* __restrict__ C) {
-  __shared__ float tile[2][64][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+  constexpr int AT_ONCE = 256 / E, STAGE = 16 * AT_ONCE, PITCH = STAGE + 4;
+  __shared__ __attribute__((aligned(16))) float tile[2][E][PITCH];
+  const int e = threadIdx.x % E, sl = threadIdx.x / E;
+  const int64_t i = (int64_t)blockIdx.x * E + e;
+  const bool adds = threadIdx.x < E && i < n;
   float v[16];
   auto fetch = [&](int s0) {
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
-      const int k = s0 + wave * 16 + q;
+      const int k = s0 + q * AT_ONCE + sl;
       v[q] = (k < slices && i < n) ? P[(int64_t)k * n + i] : 0.f;
     }
   };
-  float s = (accumulate && wave == 0 && i < n) ? C[i] : 0.f;
+  float s = accumulate && adds ? C[i] : 0.f;
   fetch(0);
-  for (int s0 = 0, b = 0; s0 < slices; s0 += 64, b ^= 1) {
+  for (int s0 = 0, b = 0; s0 < slices; s0 += STAGE, b ^= 1) {
 #pragma unroll
-    for (int q = 0; q < 16; ++q) tile[b][wave * 16 + q][lane] = v[q];
-    if (s0 + 64 < slices) fetch(s0 + 64);
+    for (int q = 0; q < 16; ++q) tile[b][e][q * AT_ONCE + sl] = v[q];
+    if (s0 + STAGE < slices) fetch(s0 + STAGE);
     __syncthreads();   // (the other buffer was added before this barrier's turn came round)
-    if (wave == 0) {
-      const int m = (slices - s0) < 64 ? (slices - s0) : 64;
-      if (m == 64) {
-#pragma unroll 16
-        for (int k = 0; k < 64; ++k) s += tile[b][k][lane];
+    if (adds) {
+      const int m = slices - s0;
+      if (m >= STAGE) {
+#pragma unroll 4
+        for (int k = 0; k < STAGE; k += 4) {
+          const float4 x = *reinterpret_cast<const float4*>(&tile[b][e][k]);
+          s += x.x;
+          s += x.y;
+          s += x.z;
+          s += x.w;
+        }
       } else {
-        for (int k = 0; k < m; ++k) s += tile[b][k][lane];
+        for (int k = 0; k < m; ++k) s += tile[b][e][k];
       }
     }
   }
-  if (wave == 0 && i < n) C[i] = s;
+  if (adds) C[i] = s;
+}
+
+constexpr int REDUCE_WIDE = 512;   // blocks of 64 elements from which those are taken
+void launch_reduce(hipStream_t st, const float* P, int64_t n, int slices, int accumulate, float* C) {
+  if (n >= REDUCE_WIDE * 64) k_reduce_slices<64><<<(unsigned)((n + 63) / 64), 256, 0, st>>>(P, n, slices, accumulate, C);
+  else k_reduce_slices<16><<<(unsigned)((n + 15) / 16), 256, 0, st>>>(P, n, slices, accumulate, C);
 }
 
 // The first two of every four values, each a vector of its own (the same sums).
@@ -933,7 +950,7 @@ int launch_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const fl
     later->left = true;
     return HT_OK;
   }
-  k_reduce_slices<<<(unsigned)((kn + 63) / 64), 256, 0, st>>>(P, kn, (int)slices, accumulate, C);
+  launch_reduce(st, P, kn, (int)slices, accumulate, C);
   HT_LAUNCH_CHECK(ctx);
   return HT_OK;
 }
@@ -1018,7 +1035,7 @@ int ht_flush_products(ht_ctx* ctx, hipStream_t st, bool drop) {
     if (p.column[0]) {
       k_reduce_columns<<<(unsigned)((p.n / 4 + 255) / 256), 256, 0, st>>>(p.P, p.n, p.slices, p.column[0], p.column[1]);
     } else {
-      k_reduce_slices<<<(unsigned)((p.n + 63) / 64), 256, 0, st>>>(p.P, p.n, p.slices, 0, p.C);
+      launch_reduce(st, p.P, p.n, p.slices, 0, p.C);
     }
     HT_LAUNCH_CHECK(ctx);
   }
