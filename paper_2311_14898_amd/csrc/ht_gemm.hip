@@ -762,10 +762,9 @@ __global__ void __launch_bounds__(256) k_reduce_columns(const float* __restrict_
 struct SliceRule {
   int tiles;
   bool alone = false;
-  int64_t least = 256;   // rows of a slice
   __host__ __device__ void cut(int64_t M, int64_t* rows, int64_t* slices) const {
     int64_t s = (1024 + tiles - 1) / tiles;
-    int64_t most = (M + least - 1) / least;
+    int64_t most = (M + 255) / 256;
     if (alone) {
       const int64_t per_cu = (256 + tiles - 1) / tiles, finest = (M + 63) / 64;
       const int64_t fine = finest < per_cu ? finest : per_cu;
@@ -979,18 +978,6 @@ size_t ht_gemm_tn_bytes(int64_t M, int32_t K, int32_t N) {
 
 namespace {
 
-// Blocks of a product over several row groups, of 128 columns and of up to 64: beyond them shorter slices hide no more loads and are more partial tiles to
-// write and read.  ms with 1,024 | 2,048 | 4,096 | 8,192 | slices of 256 rows: epoch of 2.45 M vertices, 100-256-256-47 49.0 | 48.4 | 48.1 | 48.3 | 48.5, of 233 k,
-// 602-256-41 12.66 | 12.62 | 12.60 | 12.64 | 12.63; layer of 1 M vertices, 64 x 64 3.063 | 3.032 | 3.048 | 3.049 | 3.049.
-constexpr int64_t GROUP_BLOCKS = 4096, GROUP_BLOCKS_NARROW = 2048;
-SliceRule group_rule(int32_t K, int32_t N, const std::vector<int64_t>& groups) {
-  SliceRule rule{tn_tiles(K, N)};
-  int64_t rows = 0;
-  for (size_t g = 0; g + 1 < groups.size(); g += 2) rows += groups[g + 1] - groups[g];
-  rule.least = std::max<int64_t>(256, rows * rule.tiles / (N > 64 ? GROUP_BLOCKS : GROUP_BLOCKS_NARROW));
-  return rule;
-}
-
 // [g0, g1) and its slices: the row groups that one launch of ht_gemm_tn_groups takes
 size_t next_groups(const SliceRule& rule, int32_t K, int32_t N, const std::vector<int64_t>& groups, size_t g0, int64_t* slices) {
   const int64_t most = std::max<int64_t>(1024, std::min<int64_t>(32768, ((int64_t)1 << 30) / ((int64_t)K * N * 4)));   // slices per launch
@@ -1013,7 +1000,7 @@ void ht_gemm_groups_wants(int32_t K, int32_t N, const std::vector<int64_t>& grou
     want->push_back({HT_S_TNPART, ht_gemm_tn_bytes(G ? groups[1] - groups[0] : 0, K, N)});
     return;
   }
-  const SliceRule rule = group_rule(K, N, groups);
+  const SliceRule rule{tn_tiles(K, N)};
   for (size_t g0 = 0; g0 < G;) {
     int64_t slices;
     g0 = next_groups(rule, K, N, groups, g0, &slices);
@@ -1070,7 +1057,7 @@ int ht_gemm_tn_groups(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, 
   }
   if ((lda & 3) || (ldb & 3) || (mask.ld & 3)) return ht_set_err(ctx, HT_ESHAPE, "gemm: row pitch must be a multiple of 4");
   if (K <= 0 || N <= 0) return HT_OK;
-  const SliceRule rule = group_rule(K, N, groups);
+  const SliceRule rule{tn_tiles(K, N)};
   int64_t all = 0;
   for (size_t k = 0; k < G; ++k) all += groups[2 * k + 1] - groups[2 * k];
   for (size_t g0 = 0; g0 < G;) {
