@@ -198,7 +198,7 @@ __global__ void __launch_bounds__(256) k_gemm_nn(const float* __restrict__ A, in
 // (rows_shape).  A wave owns 32 rows x TJ tiles of 32 columns, takes strip after strip of rows, and waits for no other wave once W is there; its rows' pieces
 // come NBUF steps of 32 values ahead, across strips.  Lane l32 + 32 half holds row l32 and the values 8 q + 4 half .. + 3 of a step (a load covers 32
 // contiguous bytes of each row, a step its whole cache line); two exchanges between the halves of the wave turn four registers with the values 0 .. 3 | 4 .. 7
-// into 0 | 1, 2 | 3, 4 | 5, 6 | 7, so that an element is summed up in the order of k_gemm_nn, to the same bits.  W lies in LDS as fours of every second value of the
+// into 0 | 1, 2 | 3, 4 | 5, 6 | 7, so that an element is summed up in the order of k_gemm_nn, to the same bits (0.5 % of a layer of 60 k rows, 67 x 129).  W lies in LDS as fours of every second value of the
 // reduction, 0, 2, 4, 6 and 1, 3, 5, 7 of each eight: what a lane multiplies with them is one read.
 // What bounds it: the fp32 matrix cores (2.45 M rows, 256 x 256: 79 % busy, as k_gemm_nn's, and 85 without its loads and stores), and for
 // narrow results the rows' reads (1 M x 64 x 20: 5 TB/s).
@@ -344,7 +344,7 @@ __global__ void __launch_bounds__(512) k_rows_w(const float* __restrict__ A, int
 }
 
 // MASKED: B counts where mask.ref is positive, and is 0 elsewhere (dz, where nothing else reads it: 2.45 M rows, 100 x 256, with a pass that writes it 2.61 ms, so 1.64; 233 k, 602 x
-// 256 719 us, 714).
+// 256 720 us, 668).
 // Partial tile of C[K x N] = A[M x K]^T B[M x N] over the M-slice blockIdx.z (rows tab[2z] .. tab[2z + 1], or slice_rows each).
 // P[slice][K x N] dense.  Block tile: BM output rows (k) x BN output columns.
 // What bounds it is the loads of a step of 16 rows, PD steps of which are in flight: up to 64 columns two, wider ones, whose accumulators leave fewer registers, one.  us, loads
