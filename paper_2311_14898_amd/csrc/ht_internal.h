@@ -614,11 +614,15 @@ struct TnLater {
   float* column[2] = {nullptr, nullptr};
   bool left = false;
 };
-// `mask`: B's values count where mask.ref (as many rows and columns) is positive, and are 0 elsewhere.
+// `mask`: B's values count where mask.ref (as many rows and columns) is positive, and are 0 elsewhere; with mask.to (which may be mask.ref) what counts
+// is also written there, rows up to their next multiple of 4.  Only products for which ht_gemm_tn_writes holds take a mask.to.
 struct ReluMask {
   const float* ref = nullptr;
   int64_t ld = 0;
+  float* to = nullptr;
+  int64_t to_ld = 0;
 };
+bool ht_gemm_tn_writes(int64_t rows, int32_t K, int32_t N);
 int ht_gemm_tn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
                int64_t M, int32_t K, int32_t N, int accumulate, TnLater* later = nullptr, ReluMask mask = ReluMask());
 // Products may leave their sums to ht_step from here on, where all of them together take little memory; `bytes`: their partial tiles.

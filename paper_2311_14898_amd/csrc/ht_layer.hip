@@ -888,17 +888,23 @@ int layer_bwd_direct(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, c
     const int64_t ref_ld = H_out ? H_out->ld : ld_o;
     if (!H_out)   // re-forward of the update stage (Alg. 1)
       HT_TRY(timed_gemm([&] { return ht_gemm_nn(ctx, st, a_rows, a_ld, W, dz_all, ld_o, V, di, dn, 0); }));
-    if (dH_in) {
+    if (!dH_in) {   // grad W alone reads dz, and masks it on the way
+      mask = ReluMask{ref, ref_ld};
+    } else if (ht_gemm_tn_writes(V, di, dn)) {   // ... and leaves it for the other product
+      mask = ReluMask{ref, ref_ld, dz_all, ld_o};
+    } else {
       HT_TRY(ht_relu_mask(ctx, st, dH_out->ptr, dH_out->ld, ref, ref_ld, dz_all, ld_o, V, dn));
       dz = dz_all;
       dz_ld = ld_o;
-    } else {   // grad W alone reads dz, and masks it on the way
-      mask = ReluMask{ref, ref_ld};
     }
   }
   TnLater later;
   HT_TRY(timed_gemm([&] { return ht_gemm_tn_groups(ctx, st, a_rows, a_ld, dz, dz_ld, dW, di, dn, g->dense_groups, g->d_dense_groups.p, &later, mask); }));
   if (!dH_in) return HT_OK;
+  if (mask.to) {
+    dz = mask.to;
+    dz_ld = mask.to_ld;
+  }
   HT_TRY(timed_gemm([&] { return ht_gemm_nt(ctx, st, dz, dz_ld, W, da_all, ld_i, V, dn, di, 0); }));
   return agg_by_source(R, da_all, ld_i, di, dH_in->ptr, dH_in->ld, !R.dhin_fresh, partial, plan);
 }

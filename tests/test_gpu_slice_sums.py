@@ -1,4 +1,5 @@
-"""grad W out of many slices: tiles of few and of many elements, as many slices as a stage takes and some more, in one group of rows and in several."""
+"""grad W out of many slices: tiles of few and of many elements, as many slices as a stage takes and some more, in one group of rows and in several;
+and dz written by the product on its way."""
 import pytest
 import torch
 
@@ -30,6 +31,38 @@ def test_sums_of_slices(V, K, N, n):
         want, mag = a.t().contiguous() @ b, a.abs().t().contiguous() @ b.abs()
         # V fp32 products and sums, in random order of size and sign: 64 of the roundings are well above sqrt(V) of them over V terms
         assert ((got[0].double() - want).abs() <= 64 * 2.0 ** -24 * mag).all()
+    finally:
+        B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("V,K,N", [(1, 3, 5), (17, 33, 7), (3_000, 128, 64), (3_001, 40, 130), (3_002, 129, 64), (70_003, 64, 41), (70_003, 100, 67)])
+@pytest.mark.parametrize("n", [1, 5])
+def test_dz_written_by_the_product(V, K, N, n):
+    """A layer whose grad W masks dz for the other product too: the bits of the call whose dz was masked before, whether the activation is
+    given or made again into the memory that dz takes."""
+    ctx = B.ht_ctx_create(0)
+    none = torch.empty(0, dtype=torch.int32, device="cuda")
+    g = B.ht_partition(ctx, V, none, none, n)
+    try:
+        gen = torch.Generator(device="cuda").manual_seed(V + K)
+        A, dH, H, W = B.alloc_matrix(V, K), B.alloc_matrix(V, N), B.alloc_matrix(V, N), torch.randn(K, N, generator=gen, device="cuda")
+        A.normal_(generator=gen)
+        dH.normal_(generator=gen)
+        A[:, K:], dH[:, N:] = float("nan"), float("inf")
+        B.ht_layer_fwd(ctx, g, K, N, B.HT_ACT_RELU, A, W, H)     # (no edges but the self-loops: the aggregate is A)
+        B.ht_sync(ctx)
+        H[:, N:] = float("nan")
+        dz = dH.clone()
+        dz[:, :N] *= (H[:, :N] > 0)
+        got = []
+        for act, grad, h in ((B.HT_ACT_NONE, dz, None), (B.HT_ACT_RELU, dH, H), (B.HT_ACT_RELU, dH, None)):
+            dW, dX = torch.full((K, N), 7.0, device="cuda"), B.alloc_matrix(V, K).zero_()
+            B.ht_layer_bwd(ctx, g, K, N, act, A, W, grad, dW, dH_in=dX, H_out=h)
+            B.ht_sync(ctx)
+            got.append((dW, dX[:, :K].clone()))
+        for dW, dX in got[1:]:
+            assert torch.equal(dW, got[0][0]) and torch.equal(dX, got[0][1])
     finally:
         B.ht_graph_destroy(g)
         B.ht_ctx_destroy(ctx)
