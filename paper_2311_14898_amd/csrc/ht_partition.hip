@@ -978,11 +978,10 @@ int count_items(ht_ctx* ctx, const ItemBuild& b, int64_t* h_tot) {
   return HT_OK;
 }
 
-// Items that are few and read few rows stay in row order: what they read lies in every L2 whatever the order, and sorting them is a chain of six launches a direction (partition
-// and one layer of 10,000 vertices, 100,000 edges 492 -> 450 us; its layers, 64 columns, take as long).  Beyond it: 20,000 vertices, 400,000 edges, 128 columns, the
-// aggregation 23 us in dispatch order, 25 in row order.
-constexpr int64_t UNSORTED_ITEMS = 65536, UNSORTED_RANGE = 16384;
-
+// Items go into dispatch order however few they are and however few rows they read: row order (the sort is six launches a direction) was faster to make and slower to
+// use.  Partition and one layer of 10,000 vertices, 100,000 edges, 40 columns 495 us sorted, 430 in row order; but in row order neighbouring rows, which in many graphs
+// are alike in length, fall to the same CUs and XCDs: us of an aggregation sorted | in row order, 8,000 vertices, 40 edges a row, 128 columns 29.8 | 39.2, 256
+// columns 51 | 70; 10 a row 25.6 | 31.7, 46 | 56; 4,000 vertices, 10 a row, 256 columns 39 | 43; an epoch of 10,000 vertices, 100,000 edges, 64-32-8 111 | 117.
 // made: room for n_made items in row order, before they are permuted; keysA, keysB: nkeys words each.  Where made does not hold all
 // items, they are put in order range by range (the order is by range first in any case; h_starts: pinned, rows.n + 1 words).
 int fill_items(ht_ctx* ctx, const ItemBuild& b, const int64_t* h_tot, WorkItem* made, size_t n_made, uint64_t* keysA, uint64_t* keysB,
@@ -994,7 +993,7 @@ int fill_items(ht_ctx* ctx, const ItemBuild& b, const int64_t* h_tot, WorkItem* 
   b.out->n_items = ni;
   b.out->n_part = np;
   b.out->n_cut = nc;
-  const bool sorted_items = order && ni > 1 && (ni > UNSORTED_ITEMS || b.range > UNSORTED_RANGE || b.classes), at_once = ni <= (int64_t)n_made;
+  const bool sorted_items = order && ni > 1, at_once = ni <= (int64_t)n_made;
   const int kbits = b.rows.n > 1 ? bits_for(b.rows.n) : 0, vbits = bits_for(b.range);
   const int fbits = std::min(vbits, 32 - kbits - b.classes), fshift = vbits - fbits;
   const ItemOut to{b.seg, fbits, fshift, b.classes, b.idx, sorted_items && at_once ? made : b.out->items.p, sorted_items ? keysA : nullptr};
