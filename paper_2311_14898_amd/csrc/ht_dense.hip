@@ -38,8 +38,10 @@ constexpr int SEG_BLOCKS = 512;                 // segments that a graph's tiles
 // Entries of a work item.  The shorter, the narrower the range of rows that the items in flight read, and the more of them the L2s keep; but a row that is cut has its partial
 // sums written and read, so the line lies with the entries a row.  ms an epoch with items of the rest of 24 | 32 | 40 | 48 | 64 | 96 entries: 2.45 M vertices, 22 entries
 // a row left, 49.6 | 49.2 | 50.7 | 51.2 | 52.0 | 52.7; 233 k, 111 a row, 13.4 | 13.0 | 12.8 | 12.7 | 13.0 | 13.2; 116 k, 160 a row, 2.83 | 2.72 | 2.67 | 2.67 | 2.67 | 2.82.
-// Over all entries, 32 | 48 | 64: layer of 1.5 M, 20 M edges, 128 columns 4.36 | 4.32 | 4.46, three-layer epoch of 1 M, 10 M edges 2.37 | 2.34 | 2.37.
-constexpr int REST_SEG = 48, REST_SEG_SPARSE = 32, FINE_SEG = 48;
+// Over all entries 64, however sparse the graph: with 48, graphs whose rows are alike lose more than skewed ones gain.  Layers, forward and backward, ms with items of 48 | 64
+// entries: every row 54 entries, 1 M vertices, 64 columns 7.24 | 5.89, 200 k 1.08 | 0.92, 160 columns 13.7 | 13.2; 46 on average 5.76 | 5.06; R-MAT, 100 k vertices, 50 a row, 160
+// columns 0.628 | 0.608, 60 k, 50 a row, 129 columns 0.374 | 0.365; 1.5 M, 13 a row, 128 columns 4.33 | 4.37, 256 columns 8.36 | 8.56, an epoch of 1 M, 10 a row, three layers 6.77 | 6.88.
+constexpr int REST_SEG = 48, REST_SEG_SPARSE = 32, FINE_SEG = 64;
 constexpr int64_t REST_SPARSE = 48;   // entries left a row up to which they are the shorter ones
 inline int rest_seg(int64_t V, int64_t left) { return left <= REST_SPARSE * V ? REST_SEG_SPARSE : REST_SEG; }
 inline int64_t rest_items_bound(int64_t V, int64_t most) {   // whatever part of `most` entries is left

@@ -65,6 +65,32 @@ def test_rows_addressed_in_64_bits(V, E, d, monkeypatch):
     assert A.isfinite().all() and float(A.abs().sum()) > 0
 
 
+@pytest.mark.parametrize("entries,cut", [(64, False), (65, True)])
+def test_length_of_short_items(entries, cut, monkeypatch):
+    """Rows of up to 64 entries are one work item: no partial sums, two rows of them for each row beyond."""
+    monkeypatch.setenv("HT_DENSE", "0")
+    monkeypatch.setenv("HT_MERGE_DUPS", "0")
+    V, d = 400_000, 64
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    dst = torch.arange(V, dtype=torch.int32, device="cuda").repeat_interleave(entries - 1)
+    src = torch.randint(0, V, (dst.numel(),), generator=gen, dtype=torch.int32, device="cuda")
+    ctx = B.ht_ctx_create(0)
+    g = B.ht_partition(ctx, V, src, dst, 1)
+    try:
+        X, A, H, W = B.alloc_matrix(V, d).zero_(), B.alloc_matrix(V, d), B.alloc_matrix(V, 16), torch.zeros(d, 16, device="cuda")
+        held = B.ht_graph_info_get(g).hbm_bytes
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        B.ht_layer_fwd(ctx, g, d, 16, B.HT_ACT_NONE, X, W, H, A)
+        B.ht_sync(ctx)
+        assert B.ht_graph_info_get(g).hbm_bytes > held, "the pass was meant to plan"
+        taken = free - torch.cuda.mem_get_info()[0]
+        assert (taken >= 2 * V * d * 4) == cut, taken
+    finally:
+        B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)
+
+
 def test_rows_beyond_four_gib():
     """... and rows that really are that large, against the sums of an equal graph's passes that do not plan."""
     V, E, d = 8_600_000, 9_000_000, 128
