@@ -36,14 +36,17 @@ constexpr int ETILE = 2048;
 constexpr int32_t DENSE_LEAST = 650;
 constexpr int SEG_BLOCKS = 512;                 // segments that a graph's tiles are cut into at least
 // Entries of a work item.  The shorter, the narrower the range of rows that the items in flight read, and the more of them the L2s keep; but a row that is cut has its partial
-// sums written and read, so the line lies with the entries a row.  ms an epoch with items of the rest of 24 | 32 | 40 | 48 | 64 | 96 entries: 2.45 M vertices, 22 entries
+// sums written and read.  ms an epoch with items of the rest of 24 | 32 | 40 | 48 | 64 | 96 entries: 2.45 M vertices, 22 entries
 // a row left, 49.6 | 49.2 | 50.7 | 51.2 | 52.0 | 52.7; 233 k, 111 a row, 13.4 | 13.0 | 12.8 | 12.7 | 13.0 | 13.2; 116 k, 160 a row, 2.83 | 2.72 | 2.67 | 2.67 | 2.67 | 2.82.
+// So items of 32 where few entries a row are left, and few rows are ones that items of 48 leave whole.  32 | 48, R-MAT epochs at 29, 40, 41, 51, 57 and 74 a row: 9.50 | 10.0, 5.14 | 5.18,
+// 5.70 | 5.81, 6.20 | 6.21, 5.03 | 5.10, 5.11 | 5.11 (up to 2 % of the rows have 33 to 48 entries, 8 to 11 from 51 a row on); layers of 200 k vertices, 256 columns, whose rows are alike, 20 a row (1 %) 1.84 | 1.83, 24
+// (7 %) 2.08 | 2.04, 28 (20 %) 2.40 | 2.27, 36 (70 %) 3.03 | 2.73, every row 37 2.96 | 2.65.
 // Over all entries 64, however sparse the graph: with 48, graphs whose rows are alike lose more than skewed ones gain.  Layers, forward and backward, ms with items of 48 | 64
 // entries: every row 54 entries, 1 M vertices, 64 columns 7.24 | 5.89, 200 k 1.08 | 0.92, 160 columns 13.7 | 13.2; 46 on average 5.76 | 5.06; R-MAT, 100 k vertices, 50 a row, 160
 // columns 0.628 | 0.608, 60 k, 50 a row, 129 columns 0.374 | 0.365; 1.5 M, 13 a row, 128 columns 4.33 | 4.37, 256 columns 8.36 | 8.56, an epoch of 1 M, 10 a row, three layers 6.77 | 6.88.
 constexpr int REST_SEG = 48, REST_SEG_SPARSE = 32, FINE_SEG = 64;
-constexpr int64_t REST_SPARSE = 48;   // entries left a row up to which they are the shorter ones
-inline int rest_seg(int64_t V, int64_t left) { return left <= REST_SPARSE * V ? REST_SEG_SPARSE : REST_SEG; }
+constexpr int64_t REST_SPARSE = 48;   // entries left a row up to which they may be the shorter ones ...
+constexpr int64_t REST_ALIKE = 32;    // ... unless one row of so many has more than those take and no more than the longer ones do
 inline int64_t rest_items_bound(int64_t V, int64_t most) {   // whatever part of `most` entries is left
   return std::max(ht_row_items_bound(V, most, REST_SEG), ht_row_items_bound(V, std::min(most, REST_SPARSE * V), REST_SEG_SPARSE));
 }
@@ -255,6 +258,14 @@ __global__ void __launch_bounds__(TB) k_dense_tiles(const int64_t* __restrict__ 
 __global__ void k_row_lengths(const int64_t* __restrict__ ptr, int64_t V, int32_t* __restrict__ len) {
   const int64_t v = (int64_t)blockIdx.x * TB + threadIdx.x;
   if (v < V) len[v] = (int32_t)(ptr[v + 1] - ptr[v]);
+}
+
+// adds up how many lengths are above lo and not above hi
+__global__ void __launch_bounds__(TB) k_count_lengths(const int32_t* __restrict__ len, int64_t V, int lo, int hi, unsigned long long* __restrict__ total) {
+  const int64_t v = (int64_t)blockIdx.x * TB + threadIdx.x;
+  const int32_t l = v < V ? len[v] : lo;
+  const uint64_t in = __ballot(l > lo && l <= hi);
+  if ((threadIdx.x & 63) == 0 && in) atomicAdd(total, (unsigned long long)__popcll(in));
 }
 
 // byte of (row, column) of a tile: 32-column stages, 32-row parts, and 16 bytes for each lane of the wave that multiplies them: its
@@ -816,8 +827,8 @@ int build_dense(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, DenseSide& 
   D.n_cols = host[n_rb + 2] * DENSE_COLS;
   const size_t cell_bytes = (size_t)n_tiles * DENSE_ROWS * DENSE_COLS;
   const int64_t left = n_ent - taken;
-  const int seg = rest_seg(V, left);
-  if ((int64_t)cell_bytes + 8 * left + 16 * ht_row_items_bound(V, left, seg) > room / 4) return HT_ENOMEM;
+  auto fits = [&](int seg) { return (int64_t)cell_bytes + 8 * left + 16 * ht_row_items_bound(V, left, seg) <= room / 4; };
+  if (!fits(REST_SEG)) return HT_ENOMEM;
   D.tiles.add<uint8_t>(cell_bytes);
   D.tiles.add<int32_t>((size_t)n_tiles);
   D.tiles.add<DenseSeg>(segs.size());
@@ -847,9 +858,14 @@ int build_dense(ht_ctx* ctx, const ht_graph* g, bool fwd, int32_t d, DenseSide& 
   k_keep_count<<<(unsigned)et, TB, 0, st>>>(t.keep.p, n_ent, t.kcnt.p);
   HT_LAUNCH_CHECK(ctx);
   HT_TRY(ht_scan_i32(ctx, t.kcnt.p, t.kbase.p, et, true));
+  HT_TRY(ht_fill_zero(ctx, st, t.total.p, 16));
+  k_count_lengths<<<nblk(V), TB, 0, st>>>(t.rest.p, V, REST_SEG_SPARSE, REST_SEG, (unsigned long long*)t.total.p);
+  HT_LAUNCH_CHECK(ctx);
   HT_HIP(ctx, hipMemcpyAsync(host, t.kbase.p + et, 8, hipMemcpyDeviceToHost, st));
+  HT_HIP(ctx, hipMemcpyAsync(host + 1, t.total.p, 8, hipMemcpyDeviceToHost, st));
   HT_HIP(ctx, hipStreamSynchronize(st));
   D.n_rest = host[0];
+  const int seg = left <= REST_SPARSE * V && host[1] * REST_ALIKE <= V && fits(REST_SEG_SPARSE) ? REST_SEG_SPARSE : REST_SEG;
   const size_t n_rest = (size_t)std::max<int64_t>(D.n_rest, 1);
   const size_t items = (size_t)ht_row_items_bound(V, D.n_rest, seg), cuts = (size_t)ht_row_cuts_bound(D.n_rest, seg, n_rb * DENSE_ROWS);
   D.rest.add<int32_t>(n_rest);

@@ -49,13 +49,51 @@ def test_block_widths(monkeypatch, wide, d, odd):
     _check(V, d, src, dst, X)
 
 
-@pytest.mark.parametrize("others", [1, 47, 49, 50, 51, 130])
+HUBS = 1024
+
+
+def _hubs_and(V, lengths, seed, each=400):
+    """1,024 vertices with `each` edges each among themselves (tiles); lengths[i] edges from anywhere for each vertex i behind them."""
+    gen = torch.Generator().manual_seed(seed)
+    dst = torch.cat([torch.arange(HUBS).repeat_interleave(each), torch.arange(HUBS, V).repeat_interleave(lengths)])
+    src = torch.cat([torch.randint(0, HUBS, (HUBS * each,), generator=gen), torch.randint(0, V, (int(lengths.sum()),), generator=gen)])
+    return src.to(torch.int32), dst.to(torch.int32)
+
+
+@pytest.mark.parametrize("others", [1, 31, 32, 47, 49, 50, 51, 130])
 def test_items_of_what_tiles_leave(monkeypatch, others):
-    """1,024 vertices with 400 edges each among themselves (tiles), the others with `others` edges from anywhere: the rows of the others
-    are left, on either side of the line between the two lengths of items."""
-    V, hubs, d = 20_000, 1024, 36
-    gen = torch.Generator().manual_seed(others)
-    dst = torch.cat([torch.arange(hubs).repeat_interleave(400), torch.arange(hubs, V).repeat_interleave(others)])
-    src = torch.cat([torch.randint(0, hubs, (hubs * 400,), generator=gen), torch.randint(0, V, ((V - hubs) * others,), generator=gen)])
+    """The rows of the others are left, on either side of the lines between the two lengths of items; half of them have 20 edges fewer or more."""
+    V, d = 20_000, 36
+    lengths = torch.full((V - HUBS,), others)
+    if others > 31:
+        lengths[::4], lengths[1::4] = others - 20, others + 20
     monkeypatch.setenv("HT_DENSE_WORK", "1")
-    _check(V, d, src.to(torch.int32), dst.to(torch.int32), torch.randn(V, d, generator=gen))
+    _check(V, d, *_hubs_and(V, lengths, others), torch.randn(V, d, generator=torch.Generator().manual_seed(others)))
+
+
+# stored entries a row: (of one row of `every`, of the others); rows that items of the rest cut
+@pytest.mark.parametrize("every,long,short,cut", [(1, 40, 40, False), (1, 48, 48, False), (1, 60, 60, True), (33, 40, 8, True), (31, 40, 8, False), (33, 48, 8, True), (33, 33, 8, True), (33, 32, 8, False)])
+def test_length_of_items_of_what_tiles_leave(monkeypatch, every, long, short, cut):
+    """Items of 32 entries for sparse rests, but not where that cuts many rows that items of 48 leave whole: by the memory of the partial sums."""
+    V, wide = 300_000, 512
+    lengths = torch.full((V - HUBS,), short - 1)
+    lengths[::every] = long - 1
+    src, dst = _hubs_and(V, lengths, 1, 1000)
+    monkeypatch.setenv("HT_DENSE_WORK", "1")
+    monkeypatch.setenv("HT_MERGE_DUPS", "0")
+    ctx = B.ht_ctx_create(0)
+    B.ht_ctx_set_hbm_budget(ctx, 1 << 40)      # (nothing is kept of what the partition gives back)
+    g = B.ht_partition(ctx, V, src.cuda(), dst.cuda(), 1)
+    try:
+        H, W, held, free = B.alloc_matrix(V, 16), torch.zeros(wide, 16, device="cuda"), B.ht_graph_info_get(g).hbm_bytes, []
+        layers = [(d, B.alloc_matrix(V, d), B.alloc_matrix(V, d)) for d in (4, wide)]      # the plan and its making; partial sums alone
+        for d, X, A in layers:
+            B.ht_layer_fwd(ctx, g, d, 16, B.HT_ACT_NONE, X, W[:d], H, A)
+            B.ht_sync(ctx)
+            free.append(torch.cuda.mem_get_info()[0])
+        assert B.ht_graph_info_get(g).hbm_bytes > held + 8 * int(lengths.sum()), "the pass was meant to go over tiles"
+        sums = int((lengths == long - 1).sum()) * 2 * wide * 4      # two of each row that is cut, beside those of the tiles (some 19 MB)
+        assert (free[0] - free[1] > 0.9 * sums) == cut, (free[0] - free[1], sums)
+    finally:
+        B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)
