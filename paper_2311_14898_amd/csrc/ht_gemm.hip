@@ -8,6 +8,7 @@
 //       slices whose partial tiles are added in slice order (no atomics).
 // The small operand W is first packed into a zero-padded tile-aligned copy.
 #include <algorithm>
+#include <atomic>
 #include <type_traits>
 
 #include "ht_internal.h"
@@ -845,8 +846,14 @@ template <int TJ, int NBUF, bool T>
 int launch_rows(ht_ctx* ctx, hipStream_t st, const RowsShape& s, const float* A, int64_t lda, const float* W, float* C, int64_t ldc, int64_t M, int K,
                 int N, int relu) {
   const int lds = rows_lds(K, TJ);
-  if (lds > (64 << 10))
-    HT_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_rows_w<TJ, NBUF, T>), hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+  // The limit belongs to the kernel on its device, for all contexts and threads: raised to all of the LDS, once, and never lowered (by the bytes of each call it could fall
+  // between another thread's raising it and its launch).
+  static std::atomic<uint64_t> raised{0};   // a bit for each device
+  const uint64_t bit = ctx->device < 64 ? 1ull << ctx->device : 0;
+  if (lds > (64 << 10) && !(raised.load(std::memory_order_relaxed) & bit)) {
+    HT_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_rows_w<TJ, NBUF, T>), hipFuncAttributeMaxDynamicSharedMemorySize, ROWS_LDS));
+    raised.fetch_or(bit, std::memory_order_relaxed);
+  }
   k_rows_w<TJ, NBUF, T><<<dim3(s.gx, s.gy), s.waves * 64, lds, st>>>(A, lda, W, C, ldc, M, K, N, relu);
   HT_LAUNCH_CHECK(ctx);
   return HT_OK;

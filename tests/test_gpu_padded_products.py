@@ -1,5 +1,8 @@
 """Products whose widths fill tiles of 32 columns better than blocks of 64 or 128, at the edges of tiles, steps of the reduction, strips of
 rows and of what of W fits into a CU's memory, against fp64."""
+import ctypes
+import threading
+
 import pytest
 import torch
 
@@ -61,6 +64,41 @@ def test_rows_do_not_depend_on_their_number(K, N):
         B.ht_graph_destroy(g)
         B.ht_ctx_destroy(ctx)
     assert torch.equal(rows[0], rows[1]) and torch.equal(rows[0], rows[2])
+
+
+def test_threads_with_unlike_lds():
+    """Two threads, each with its context, through one kernel with 68 and 161 KB of LDS: neither is refused its launch, and both get their product."""
+    V, N, calls = 64, 96, 3_000
+    none, out = torch.empty(0, dtype=torch.int32, device="cuda"), {}
+
+    def run(K):
+        try:
+            stream = torch.cuda.Stream()
+            ctx = B.ht_ctx_create(0, stream.cuda_stream)
+            g = B.ht_partition(ctx, V, none, none, 1)
+            gen = torch.Generator().manual_seed(K)
+            H, W, got = torch.randn(V, K, generator=gen), torch.randn(K, N, generator=gen), B.alloc_matrix(V, N)
+            Hd, Wd = B.to_matrix(H), W.cuda()
+            torch.cuda.synchronize()
+            desc, views = B.ht_layer_desc(K, N, B.HT_ACT_NONE, B.HT_GATHER_AUTO, 0, B.HT_ORDER_AGG_FIRST), (B.tensor_view(Hd, K), B.tensor_view(got, N))
+            for _ in range(calls):
+                rc = B.load().ht_layer_fwd(ctx, g, ctypes.byref(desc), ctypes.byref(views[0]), ctypes.c_void_p(Wd.data_ptr()), ctypes.byref(views[1]), None, None)
+                assert rc == 0, rc
+            B.ht_sync(ctx)
+            want, mag = H.double() @ W.double(), H.abs().double() @ W.abs().double()
+            assert ((got[:, :N].cpu().double() - want).abs() <= (K + 4) * 2.0 ** -24 * mag).all()
+            B.ht_graph_destroy(g)
+            B.ht_ctx_destroy(ctx)
+            out[K] = "done"
+        except BaseException as e:      # (a thread's failure is the test's)
+            out[K] = repr(e)
+
+    threads = [threading.Thread(target=run, args=(K,)) for K in (416, 176)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert out == {416: "done", 176: "done"}
 
 
 @pytest.mark.parametrize("K", [1, 7, 17, 50, 67, 130])
