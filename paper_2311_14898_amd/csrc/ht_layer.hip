@@ -839,7 +839,8 @@ int layer_bwd_direct(Run& R, const ht_layer_desc* desc, const ht_tensor* ckpt, c
   const int64_t a_ld = agg_ckpt ? ckpt->ld : ld_i;
   *done = false;
   float *a_all = nullptr, *dz_all = nullptr, *da_all = nullptr, *partial = nullptr;
-  const size_t a_bytes = agg_ckpt ? 0 : (size_t)V * a_ld * 4, dz_bytes = relu ? (size_t)V * ld_o * 4 : 0,
+  // (dz: for grad a, or for the activations made again; grad W alone masks its rows on the way)
+  const size_t a_bytes = agg_ckpt ? 0 : (size_t)V * a_ld * 4, dz_bytes = relu && (dH_in || !H_out) ? (size_t)V * ld_o * 4 : 0,
                da_bytes = dH_in ? (size_t)V * ld_i * 4 : 0;
   if (!ht_may_spend(ctx) || (int64_t)(a_bytes + dz_bytes + da_bytes) > HT_DIRECT_BYTES) return HT_OK;
   // everything that this pass will ask for: nothing may fail once dH_in is being added to

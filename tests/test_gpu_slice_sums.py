@@ -66,3 +66,32 @@ def test_dz_written_by_the_product(V, K, N, n):
     finally:
         B.ht_graph_destroy(g)
         B.ht_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("given,first,takes", [(True, True, False), (False, True, True), (True, False, True)])
+def test_dz_is_held_where_it_is_used(given, first, takes):
+    """A first layer (no input gradient) whose activations are given masks dz inside grad W: no memory for dz of all vertices."""
+    V, K, N = 400_000, 20, 256
+    ctx = B.ht_ctx_create(0)
+    B.ht_ctx_set_hbm_budget(ctx, 1 << 40)      # (nothing is kept of what is given back)
+    none = torch.empty(0, dtype=torch.int32, device="cuda")
+    g = B.ht_partition(ctx, V, none, none, 1)
+    try:
+        gen = torch.Generator(device="cuda").manual_seed(1)
+        A, dH, H, dX, W, dW = B.alloc_matrix(V, K), B.alloc_matrix(V, N), B.alloc_matrix(V, N), B.alloc_matrix(V, K), torch.zeros(K, N, device="cuda"), torch.empty(K, N, device="cuda")
+        A.normal_(generator=gen)
+        dH.normal_(generator=gen)
+        H.normal_(generator=gen)
+        mask = H > 0 if given else torch.zeros_like(H, dtype=torch.bool)       # (W is 0: made again, no activation is positive)
+        want, mag = A[:, :K].double().t().contiguous() @ (dH * mask).double(), A[:, :K].double().abs().t().contiguous() @ (dH * mask).double().abs()
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        B.ht_layer_bwd(ctx, g, K, N, B.HT_ACT_RELU, A, W, dH, dW, dH_in=None if first else dX, H_out=H if given else None)
+        B.ht_sync(ctx)
+        taken = free - torch.cuda.mem_get_info()[0]
+        assert (taken >= V * N * 4) == takes, taken
+        # (as above)
+        assert ((dW.double() - want).abs() <= 64 * 2.0 ** -24 * mag).all()
+    finally:
+        B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)
