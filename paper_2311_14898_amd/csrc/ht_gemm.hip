@@ -818,8 +818,12 @@ int launch_nn(ht_ctx* ctx, hipStream_t st, const float* A, int64_t lda, const fl
 // Products whose columns, in tiles of 32, are at most four fifths of what k_gemm_nn's blocks of 64 or 128 would compute go through k_rows_w.  us, k_gemm_nn (with
 // its packed W) | k_rows_w, at rows x K x N: 10 k x 64 x 32 5.8 | 4.7, 60 k x 67 x 129 40.4 | 23.4, 60 k x 129 x 67 34.3 | 25.0, 116 k x 301 x 129 165 | 135, 233 k x 256 x
 // 20 79 | 49, 300 k x 129 x 67 113 | 97, 1 M x 64 x 20 85 | 68.  Beyond the line: 300 k x 64 x 300 187 | 195, 233 k x 256 x 41 85 | 89, 1 M x 64 x 64 112 | 120, 2.45 M x 100 x 256
-// 1,415 | 1,430 (the memory's rate or, in long runs, the power that fp32 matrix cores draw).  The line is drawn by K and N alone: a row must not depend
-// on how many rows are multiplied at once.
+// 1,415 | 1,430 (the memory's rate or, in long runs, the power that fp32 matrix cores draw).
+// Where W's columns do not fit the LDS together the rows are read once for every tile or two.  That pays while it spares enough products: 5 of 8 tiles, 300 k x 602 x 160 744 | 621, 2.45 M x
+// 1216 x 132 12,599 | 9,397; 6 of 8, 1 M x 800 x 192 3,234 | 3,016; 9 of 12, 1 M x 602 x 288 3,894 | 3,567.  Not with 3 of 4 tiles over many rows: 424 x 70 and 602 x 96, 60 k rows
+// 81 | 66 and 103 | 86, 300 k 308 | 293 and 411 | 398, 600 k 540 | 571 and 749 | 779, 2.45 M 2,115 | 2,308 and 2,956 | 3,120.
+// An element is summed up in the same order by both, so that a row does not depend on how many are multiplied at once.
+constexpr int64_t ROWS_THRICE = 400000;   // rows up to which they are read three times for the sake of a quarter of the products
 struct RowsShape {
   int tj = 0, waves = 0;     // tj 0: k_gemm_nn's
   unsigned gx = 0, gy = 0;
@@ -832,6 +836,7 @@ RowsShape rows_shape(int64_t M, int K, int N) {
     const int n = (tiles + tj - 1) / tj * tj;
     if (n <= best) best = n, s.tj = tj;
   }
+  if (tiles == 3 && s.tj == 1 && M > ROWS_THRICE) s.tj = 0;
   if (!s.tj) return s;
   const int64_t strips = (M + 31) / 32;
   while (s.tj > 1 && strips * ((tiles + s.tj - 1) / s.tj) < 1024) --s.tj;   // (a wave for every SIMD)

@@ -46,24 +46,26 @@ def test_layer_without_edges(V, K, N):
         B.ht_ctx_destroy(ctx)
 
 
-@pytest.mark.parametrize("K,N", [(67, 129), (129, 67), (50, 20)])
-def test_rows_do_not_depend_on_their_number(K, N):
-    """The same bits whether a row is multiplied among 100, 5,000 or 200,000."""
+@pytest.mark.parametrize("K,N,sizes", [(67, 129, (100, 5_000, 200_000)), (129, 67, (100, 12_000, 20_000, 200_000)), (50, 20, (100, 5_000, 200_000)),
+                                       (424, 70, (100, 400_000, 400_001)), (417, 96, (20_000, 400_001))])
+def test_rows_do_not_depend_on_their_number(K, N, sizes):
+    """The same bits however many rows are multiplied, in tiles of any number of columns and, beyond 400,000 rows of three tiles, in blocks."""
     gen = torch.Generator(device="cuda").manual_seed(3)
-    H, W = torch.randn(200_000, K, generator=gen, device="cuda"), torch.randn(K, N, generator=gen, device="cuda")
+    H, W = torch.randn(max(sizes), K, generator=gen, device="cuda"), torch.randn(K, N, generator=gen, device="cuda")
     rows = []
     none = torch.empty(0, dtype=torch.int32, device="cuda")
-    for V in (100, 5_000, 200_000):
+    for V in sizes:
         ctx = B.ht_ctx_create(0)
         g = B.ht_partition(ctx, V, none, none, 1)
         Hd, out = B.alloc_matrix(V, K), B.alloc_matrix(V, N)
         Hd[:, :K] = H[:V]
         B.ht_layer_fwd(ctx, g, K, N, B.HT_ACT_NONE, Hd, W, out)
         B.ht_sync(ctx)
-        rows.append(out[:100, :N].clone())
+        rows.append(out[:, :N].clone())
         B.ht_graph_destroy(g)
         B.ht_ctx_destroy(ctx)
-    assert torch.equal(rows[0], rows[1]) and torch.equal(rows[0], rows[2])
+    for less, more in zip(rows, rows[1:]):
+        assert torch.equal(less, more[:less.shape[0]])
 
 
 def test_threads_with_unlike_lds():
