@@ -97,3 +97,35 @@ def test_length_of_items_of_what_tiles_leave(monkeypatch, every, long, short, cu
     finally:
         B.ht_graph_destroy(g)
         B.ht_ctx_destroy(ctx)
+
+
+def test_shorter_items_refuse_no_plan(monkeypatch):
+    """Every other row has 85 entries: two rows of sums in items of 48, 7.2 GB of them, three in items of 32, 10.8 GB, over which the pass plans all the same."""
+    V, d = 100_000, 18_000
+    lengths = torch.ones(V - HUBS, dtype=torch.int64)
+    lengths[::2] = 84
+    src, dst = _hubs_and(V, lengths, 1, 1000)
+    monkeypatch.setenv("HT_DENSE_WORK", "1")
+    monkeypatch.setenv("HT_MERGE_DUPS", "0")
+    ctx = B.ht_ctx_create(0)
+    B.ht_ctx_set_hbm_budget(ctx, 1 << 40)
+    g = B.ht_partition(ctx, V, src.cuda(), dst.cuda(), 1)
+    try:
+        X, A, H, W = B.alloc_matrix(V, d), B.alloc_matrix(V, d), B.alloc_matrix(V, 16), torch.zeros(d, 16, device="cuda")
+        at = [0, 1, 9_000, d - 1]
+        X[:, at] = torch.randn(V, len(at), generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        B.ht_layer_fwd(ctx, g, d, 16, B.HT_ACT_NONE, X, W, H, A)
+        B.ht_sync(ctx)
+        assert free - torch.cuda.mem_get_info()[0] >= 3 * ((V - HUBS) // 2) * d * 4
+        loop = torch.arange(V)
+        u, v = torch.cat([src.long(), loop]).cuda(), torch.cat([dst.long(), loop]).cuda()
+        s = torch.bincount(v, minlength=V).double().rsqrt()
+        want, mag = (torch.zeros(V, len(at), dtype=torch.float64, device="cuda").index_add_(0, v, (s[u] * s[v])[:, None] * Z[u]) for Z in (X[:, at].double(), X[:, at].double().abs()))
+        assert ((A[:, at].double() - want).abs() <= 16 * 2.0 ** -24 * mag).all()
+    finally:
+        B.ht_graph_destroy(g)
+        B.ht_ctx_destroy(ctx)
+        del X, A
+        torch.cuda.empty_cache()
