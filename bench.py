@@ -536,7 +536,7 @@ def main():
     bytes_per_pass = agg["bytes"] / args.steps
     achieved = bytes_per_pass / (pass_ms * 1e-3) / 1e9 if pass_ms > 0 else 0.0
     traffic = read_traffic(f"agg_fwd_{args.workload}_traffic.txt") if args.scale == 1.0 else None
-    roofline = {"bound": "hbm", "kernel": "forward aggregation, layer 0 (k_dense_pack + k_dense + k_spmm_unit; k_spmm_slab where no plan is made)", "achieved": achieved,
+    roofline = {"bound": "hbm", "kernel": "forward aggregation, layer 0 (k_dense + k_spmm_unit; k_spmm_slab where no plan is made)", "achieved": achieved,
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                 "traffic_source": None if traffic is None else f"profiles/agg_fwd_{args.workload}_traffic.txt (two rocprofv3 --pmc runs of this "
                                   "command, committed; not measured in this run)",

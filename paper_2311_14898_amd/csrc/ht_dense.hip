@@ -468,8 +468,8 @@ __device__ __forceinline__ v8bf cells8(uint32_t lo, uint32_t hi) {
 // with 64.  256 rows, because every column's values are read once per row block and 128 rows would ask L2 for 32 bytes a clock and CU, all
 // it gives; 32 columns a stage.  The stage's columns' rows come as they are, three stages ahead (a wave takes eight of them, 256 bytes each, at
 // addresses that are the same in all its lanes), and are scaled and split into three bf16 on their way into LDS.  Split by a pass of their own they were half as
-// many bytes again to read: 22.6 k tiles x 602, 256 and 256 columns 2.51 ms and 0.42 for the pass, 2.79 now; 4.9 k tiles x 256 395 us, 348 now.  What bounds it: a barrier
-// a stage, behind which all waves split, convert their cells and read LDS before the matrix cores have work again (49 % busy), and 3.7 TB/s of
+// many bytes again to read: 22.6 k tiles x 602, 256 and 256 columns 2.51 ms and 0.42 for the pass, 2.79 now; 4.9 k tiles x 256 395 us, 348 now, in blocks of 64 features 320.  What bounds it: a barrier
+// a stage, behind which all waves split, convert their cells and read LDS before the matrix cores have work again (39 to 42 % busy), and 3.7 TB/s of
 // columns and cells that miss L2.  Tried: a range check of each value apart, with the lookup of its column, 3.9 ms; matrix and vector instructions interleaved by hand, no
 // difference; LDS without its two-way conflicts (as it is here), no difference alone; segments of 24 or 88 tiles, no difference.
 template <int BN>
@@ -601,7 +601,7 @@ __global__ void __launch_bounds__(512) k_dense(DenseArgs a) {
 #pragma unroll
   for (int j = 0; j < TJ; ++j) {
     const int fo = f0 + wn * (BN / 2) + j * 32 + l32;
-    if (fo >= ((a.d + 3) & ~3)) continue;   // (zeros up to whole float4)
+    if (fo >= ((a.d + 3) & ~3)) continue;   // (up to whole float4: lanes behind the last feature have worked on that one again, so the pads hold its sums)
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -970,6 +970,7 @@ int ht_dense_launch(ht_ctx* ctx, hipStream_t st, const DenseSide& D, const float
                     int64_t out_ld) {
   // Blocks of 128 features decode a cell half as often, blocks of 64 leave shorter last rounds and take what is left behind the last 128 along.  us, 128 (and 64) | 64 alone: 22.6 k
   // tiles x 602 1546 | 1634, x 256 610 | 659; 4.9 k x 256 346 | 320, x 100 199 | 197; 7 k x 129 312 | 283.
+  // Between them either does; ms a layer forward and backward, 12.3 k x 256 2.38 | 2.37, x 384 3.37 | 3.35, x 602 5.28 | 5.27; 16.9 k x 256 3.21 | 3.22, x 512 6.56 | 6.60; 20.3 k x 256 4.21 | 4.18.
   int n128 = d / 128 + (d % 128 > 64);
   if (D.n_tiles * n128 < ctx->dense_wide) n128 = 0;
   DenseArgs a{D.cells.p, D.tile_cg.p, D.segs.p, D.cols.p, src, s, ld, out_ld, d, 0, partial};

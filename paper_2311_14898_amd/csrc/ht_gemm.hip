@@ -201,8 +201,9 @@ __global__ void __launch_bounds__(256) k_gemm_nn(const float* __restrict__ A, in
 // contiguous bytes of each row, a step its whole cache line); two exchanges between the halves of the wave turn four registers with the values 0 .. 3 | 4 .. 7
 // into 0 | 1, 2 | 3, 4 | 5, 6 | 7, so that an element is summed up in the order of k_gemm_nn, to the same bits (0.5 % of a layer of 60 k rows, 67 x 129).  W lies in LDS as fours of every second value of the
 // reduction, 0, 2, 4, 6 and 1, 3, 5, 7 of each eight: what a lane multiplies with them is one read.
-// What bounds it: the fp32 matrix cores (2.45 M rows, 256 x 256: 79 % busy, as k_gemm_nn's, and 85 without its loads and stores), and for
-// narrow results the rows' reads (1 M x 64 x 20: 5 TB/s).
+// What bounds it: the fp32 matrix cores (1 M rows, 416 x 288 122 TFLOP/s of the 155 that an fp32 product of the vendor's reaches; 2.45 M, 256 x 256, which rows_shape leaves to k_gemm_nn,
+// kept them 79 % busy, as k_gemm_nn does, and 85 without loads and stores), for narrow results the rows' reads (1 M x 64 x 20: 5 TB/s), and where W does not fit the LDS, reading the rows once
+// for every tile or two.
 constexpr int RS = 32;                       // values of a step
 constexpr int ROWS_LDS = 160 << 10;          // LDS of a CU
 constexpr int rows_lds(int K, int tj) { return (K + 7) / 8 * 2 * (tj * 32 + 1) * 16; }   // (a pitch of odd float4s: the transposed W is stored across rows)

@@ -285,7 +285,8 @@ double agg_all_bytes(const ht_graph* g, int64_t edges, int64_t rows, int d) {
   return 4.0 * edges + 8.0 * rows + 4.0 * d * (double)g->V + 4.0 * d * (double)rows + 4.0 * ((double)g->V + (double)rows);
 }
 
-// Scratch memory up to which a planned pass keeps partial sums.  (8 GiB of them in items of 48 entries are up to 12 in items of 32: a graph's rule for the length asks for no width.)
+// Scratch memory up to which a planned pass keeps partial sums.  (8 GiB of them in items of 48 entries are up to 12 in items of 32: a graph's rule for the length asks for no width.
+// 100 k vertices, 4.6 M entries left, 18,000 columns, 10.8 GB of sums: a forward pass 35.6 ms over the plan, 44.3 without.)
 constexpr int64_t HT_PLAN_BYTES = (int64_t)12 << 30;
 
 // What a pass over rows of d columns at pitch src_ld, partial sums at pitch ld, takes of the graph's plan, and the scratch memory of that; nothing
