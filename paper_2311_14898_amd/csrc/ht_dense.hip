@@ -37,7 +37,7 @@ constexpr int32_t DENSE_LEAST = 650;
 constexpr int SEG_BLOCKS = 512;                 // segments that a graph's tiles are cut into at least
 // Entries of a work item.  The shorter, the narrower the range of rows that the items in flight read, and the more of them the L2s keep; but a row that is cut has its partial
 // sums written and read.  ms an epoch with items of the rest of 24 | 32 | 40 | 48 | 64 | 96 entries: 2.45 M vertices, 22 entries
-// a row left, 49.6 | 49.2 | 50.7 | 51.2 | 52.0 | 52.7; 233 k, 111 a row, 13.4 | 13.0 | 12.8 | 12.7 | 13.0 | 13.2; 116 k, 160 a row, 2.83 | 2.72 | 2.67 | 2.67 | 2.67 | 2.82.
+// a row left, 49.6 | 49.2 | 50.7 | 51.2 | 52.0 | 52.7; 233 k, 111 a row, 13.4 | 13.0 | 12.8 | 12.7 | 13.0 | 13.2; 116 k, 82 a row, 2.83 | 2.72 | 2.67 | 2.67 | 2.67 | 2.82.
 // So items of 32 where few entries a row are left, and few rows are ones that items of 48 leave whole.  32 | 48, R-MAT epochs at 29, 40, 41, 51, 57 and 74 a row: 9.50 | 10.0, 5.14 | 5.18,
 // 5.70 | 5.81, 6.20 | 6.21, 5.03 | 5.10, 5.11 | 5.11 (up to 2 % of the rows have 33 to 48 entries, 8 to 11 from 51 a row on); layers of 200 k vertices, 256 columns, whose rows are alike, 20 a row (1 %) 1.84 | 1.83, 24
 // (7 %) 2.08 | 2.04, 28 (20 %) 2.40 | 2.27, 36 (70 %) 3.03 | 2.73, every row 37 2.96 | 2.65.
